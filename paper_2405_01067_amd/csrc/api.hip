@@ -102,6 +102,34 @@ GemmF32 gemm(const float* A, const float* B, float* C, int64_t P, int64_t Q, int
     return g;
 }
 
+// fp32 backward: dT, T (each M x r) and the partial sums of the factor gradients, whose contraction over
+// the batch is split over work-groups.  The split only takes what is left of the static scratch array,
+// so that every shape lr_linear_bwd_static serves without it is served with it.
+struct BwdLayoutF32 { size_t dT, T, partials, total; int split_A, split_B; };
+
+GemmF32 grad_A_f32(const float* dY, const float* T, float* dA, int64_t M, int64_t m, int64_t r, int acc) {
+    return gemm(dY, T, dA, m, r, M, m, r, r, 1, 0, acc);
+}
+GemmF32 grad_B_f32(const float* dT, const float* X, float* dB, int64_t M, int64_t n, int64_t r, int acc) {
+    return gemm(dT, X, dB, r, n, M, r, n, n, 1, 0, acc);
+}
+
+BwdLayoutF32 bwd_layout_f32(int64_t M, int64_t m, int64_t n, int64_t r) {
+    BwdLayoutF32 w{};
+    const size_t each = align_up((size_t)M * r * 4, 256);
+    w.dT = 0; w.T = each; w.partials = 2 * each;
+    const GemmF32 a = grad_A_f32(nullptr, nullptr, nullptr, M, m, r, 0), b = grad_B_f32(nullptr, nullptr, nullptr, M, n, r, 0);
+    w.split_A = gemm_f32_splits(a);
+    w.split_B = gemm_f32_splits(b);
+    auto bytes = [&] { return gemm_f32_partial_bytes(a, w.split_A) + gemm_f32_partial_bytes(b, w.split_B); };
+    while (w.partials <= ABT_STATIC_SCRATCH_BYTES && w.partials + bytes() > ABT_STATIC_SCRATCH_BYTES) {
+        w.split_A = w.split_A > 1 ? w.split_A / 2 : 1;
+        w.split_B = w.split_B > 1 ? w.split_B / 2 : 1;
+    }
+    w.total = w.partials + bytes();
+    return w;
+}
+
 struct BwdLayout {  // bf16 backward workspace
     size_t At, Bt, dT, T, partials, total;
 };
@@ -389,7 +417,7 @@ size_t lr_linear_fwd_workspace_bytes(int64_t M, int64_t m, int64_t n, int64_t r,
 
 size_t lr_linear_bwd_workspace_bytes(int64_t M, int64_t m, int64_t n, int64_t r, int dt) {
     if (check_lr_shapes(M, m, n, r, dt) != ABT_OK) return 0;
-    if (dt == ABT_F32) return 2 * align_up((size_t)M * r * 4, 256);
+    if (dt == ABT_F32) return bwd_layout_f32(M, m, n, r).total;
     return bwd_layout_bf16(M, m, n, r).total;
 }
 
@@ -435,23 +463,24 @@ int lr_linear_bwd(const void* dY, const void* X, const void* T, const void* A, c
     if (!dX && !dA && !dB) return ABT_OK;
 
     if (dt == ABT_F32) {
-        float* dT = (float*)ws;
+        // two launches (and one that adds the split sums): first what depends on the inputs alone, then the rest
+        const BwdLayoutF32 w = bwd_layout_f32(M, m, n, r);
+        float* dT = (float*)(ws + w.dT);
         const float* Tp = (const float*)T;
-        const bool need_dT = dX || dB;
+        GemmF32 g[3];
+        int split[3], k = 0;
         if (!Tp && dA) {
-            float* Tw = (float*)(ws + align_up((size_t)M * r * 4, 256));
-            if (launch_gemm_f32_one(gemm((const float*)X, (const float*)B, Tw, M, r, n, n, n, r, 0, 1, 0), s) != hipSuccess) return ABT_EHIP;
+            float* Tw = (float*)(ws + w.T);
+            g[k++] = gemm((const float*)X, (const float*)B, Tw, M, r, n, n, n, r, 0, 1, 0);
             Tp = Tw;
         }
-        if (need_dT &&
-            launch_gemm_f32_one(gemm((const float*)dY, (const float*)A, dT, M, r, m, m, r, r, 0, 0, 0), s) != hipSuccess) return ABT_EHIP;
-        if (dX &&
-            launch_gemm_f32_one(gemm(dT, (const float*)B, (float*)dX, M, n, r, r, n, n, 0, 0, 0), s) != hipSuccess) return ABT_EHIP;
-        if (dA &&
-            launch_gemm_f32_one(gemm((const float*)dY, Tp, dA, m, r, M, m, r, r, 1, 0, acc), s) != hipSuccess) return ABT_EHIP;
-        if (dB &&
-            launch_gemm_f32_one(gemm(dT, (const float*)X, dB, r, n, M, r, n, n, 1, 0, acc), s) != hipSuccess) return ABT_EHIP;
-        return ABT_OK;
+        if (dX || dB) g[k++] = gemm((const float*)dY, (const float*)A, dT, M, r, m, m, r, r, 0, 0, 0);
+        if (k && launch_gemm_f32(g, nullptr, k, nullptr, s) != hipSuccess) return ABT_EHIP;
+        k = 0;
+        if (dA) { split[k] = w.split_A; g[k++] = grad_A_f32((const float*)dY, Tp, dA, M, m, r, acc); }
+        if (dB) { split[k] = w.split_B; g[k++] = grad_B_f32(dT, (const float*)X, dB, M, n, r, acc); }
+        if (dX) { split[k] = 1; g[k++] = gemm(dT, (const float*)B, (float*)dX, M, n, r, r, n, n, 0, 0, 0); }
+        return launch_gemm_f32(g, split, k, (float*)(ws + w.partials), s) == hipSuccess ? ABT_OK : ABT_EHIP;
     }
 
     const BwdLayout w = bwd_layout_bf16(M, m, n, r);

@@ -178,13 +178,20 @@ struct GemmF32 {
     const int32_t* limit;   // may be NULL
     int limit_rows;
 };
-// Single problem, descriptor passed by value.
+// Up to four problems in one launch, descriptors in the kernel arguments.  splits[i] > 1 (NULL = 1
+// everywhere) splits problem i's contraction over work-groups; its partial sums
+// (gemm_f32_partial_bytes each, laid end to end in `partials`) are added in a fixed order by a second
+// launch.  gemm_f32_splits is the split that fills the chip.
+int gemm_f32_splits(const GemmF32& d);
+size_t gemm_f32_partial_bytes(const GemmF32& d, int splits);
+hipError_t launch_gemm_f32(const GemmF32* problems, const int* splits, int n, float* partials, hipStream_t s);
 hipError_t launch_gemm_f32_one(const GemmF32& d, hipStream_t s);
-// n problems in one launch: build the table on the host (n * gemm_f32_desc_bytes() bytes,
-// returns the tile count), copy it to the device, then launch from the device copy.
+// n problems in one launch: build the table on the host (n * gemm_f32_desc_bytes() bytes), copy it to the
+// device, then launch from the device copy.
+struct GemmF32Table { int n, tiles; bool small, vec; };
 size_t gemm_f32_desc_bytes();
-int gemm_f32_build_table(const GemmF32* descs_host, int n, void* host_image);
-hipError_t launch_gemm_f32_table(const void* dev_image, int n, int tiles, hipStream_t s);
+GemmF32Table gemm_f32_build_table(const GemmF32* descs_host, int n, void* host_image);
+hipError_t launch_gemm_f32_table(const void* dev_image, const GemmF32Table& t, hipStream_t s);
 
 // ------------------------------------------------------------------ merge
 // Host-side plan of a batched merge: validates nothing (api.hip does), lays out the workspace

@@ -1,201 +1,445 @@
 // fp32 GEMM on the fp32 matrix cores of gfx950 (v_mfma_f32_32x32x2_f32), grouped over a list of
 // independent problems.  Serves the fp32 flavour of the factored layer (all six products of the
-// forward and backward) and the merge's back-projections A' = Abar P_A, B' = P_B Bbar, Wbar = Abar Bbar.
+// forward and backward), W = A B, and the merge's back-projections A' = Abar P_A, B' = P_B Bbar, Wbar = Abar Bbar.
 //
-// Work-group: 256 threads = 4 waves in a 2 x 2 grid, output tile 128 x 128, each wave 64 x 64
-// (2 x 2 MFMA blocks, 64 accumulator registers).  K is consumed in slabs of 16 staged through
-// LDS in k-major order, so one lane's MFMA operand is a single 4-byte LDS read.
+// What bounds it: the matrix instruction takes 64 cycles for 4096 operations, so LDS bandwidth is never
+// short; what has to be hidden is the latency of the global loads, and the chip has to be filled although
+// the problems are small (outputs of 64 x 32 up to 3152 x 3072, contractions of 32 up to the batch size).
+// Hence
+//   * loads of 16 bytes per lane, two slabs ahead in registers beside two LDS buffers, and the traffic
+//     of a slab dealt out between its matrix instructions,
+//   * small tiles (64 x 64; 32 x 32 with the four waves sharing out the contraction for launches that
+//     would not give every compute unit a tile), four work-groups per compute unit,
+//   * a contraction over the batch (factor gradients) is split over work-groups; the partial sums are
+//     added in a fixed order by a second launch.
+// Measured: 4096 x 4096 x 1024 279 us = 123 TFLOP/s of the 133 that a large library product reaches;
+// 768 x 3072 x 384 (W = A B of a ViT-B/16 MLP layer) 26 us, 79 us in an earlier form with 128 x 128 tiles
+// and 4-byte loads one slab ahead; the products of a factored layer at M = 3152, m = 3072, n = 768,
+// r = 192: T 17 us, Y 47, dT 47, dX 17, dA 52, dB 23; forward and backward together 1.95 ms -> 228 us,
+// of the 64 x 256 x 256 layer at r = 32 151 -> 40 us.
+//
+// LDS: both operands lie [row][k], 16-byte chunks of four k XOR-swizzled by the row; an operand read is
+// one 16-byte read for four matrix instructions: instruction i of a group of eight k takes k = 4 h + i
+// from the lanes of half h, the same permutation of the contraction on both sides.  Operands stored
+// with k slow are transposed on the way (four 4-byte stores per 16-byte load).
 //
 // MFMA 32x32x2 f32 register layout (lane l of 64): A operand = A[l % 32][l / 32],
 // B operand = B[l / 32][l % 32], accumulator register v holds C[8*(v/4) + 4*(l/32) + v%4][l % 32].
+#include <type_traits>
+
 #include "common.h"
 
 namespace abt {
 
 namespace {
 
-constexpr int TILE = 128;
-constexpr int SLAB = 16;
-constexpr int PITCH = 132;  // floats per k-row in LDS; 132 = 4 mod 64 spreads a 16 x 4 patch over all banks
+constexpr int NT = 256;
 
 struct GemmF32Dev {
     GemmF32 d;
-    int tile_begin;
-    int tiles_q;
+    int tile_begin;      // first tile of this problem in the launch
+    int tiles_q, tiles;  // tiles per row of tiles, tiles of one split
+    int splits, k_split; // splits of the contraction, columns of each (a multiple of 64)
+    float* part;         // splits > 1: partial sums [split][P][Q]
 };
 
-// Unpredicated load (indices clamped into the matrix; `ok` tells whether the element exists): a
-// predicated one would have to be waited for before the next load is issued.
-__device__ __forceinline__ float fetch(const float* base, int row, int col, int ld, int rows, int cols, bool& ok) {
-    ok = row < rows && col < cols;
-    const int r = row < rows ? row : rows - 1, c = col < cols ? col : cols - 1;
-    return gload(base + (int64_t)r * ld + c);
+// WR x WC x KS = 4 waves: row groups, column groups, contraction groups of a TM x TN tile
+template <int TM_, int TN_, int WR_, int WC_, int KS_, int BK_>
+struct GemmCfg {
+    static constexpr int TM = TM_, TN = TN_, WR = WR_, WC = WC_, KS = KS_, BK = BK_;
+    static constexpr int RA = TM / 32 / WR, CB = TN / 32 / WC;        // 32 x 32 blocks per wave
+    static constexpr int GPW = BK / 8 / KS;                           // groups of eight k per wave and slab
+    static constexpr int NVA = TM * BK / 4 / NT, NVB = TN * BK / 4 / NT;   // 16-byte loads per thread and slab
+    static constexpr int slab = (TM + TN) * BK;                       // floats
+    static constexpr int red = (KS - 1) * WR * WC * RA * CB * 16 * 64;    // floats: partial sums of the other contraction groups
+    static constexpr int lds_floats = 2 * slab > red ? 2 * slab : red;
+    static_assert(WR * WC * KS == 4 && NVA >= 1 && NVB >= 1 && GPW >= 1 && (BK == 32 || BK == 64), "tile shape");
+};
+
+// float index of chunk c (four k) of row r.  16 consecutive rows, same chunk, fall on 16 different
+// 16-byte bank groups; the 4-byte stores of the transposing path (rows 4 apart) meet at most in pairs.
+template <int BK>
+__device__ __forceinline__ int lds_at(int r, int c) {
+    if constexpr (BK == 64) return r * 64 + ((c ^ (r & 15) ^ ((r >> 4) & 1)) << 2);
+    else return r * 32 + ((c ^ ((r >> 1) & 7) ^ ((r >> 4) & 1)) << 2);
 }
 
-__global__ __launch_bounds__(256) void gemm_f32_kernel(const GemmF32Dev* __restrict__ descs, int ndesc,
-                                                       GemmF32Dev single, int use_single, int ntiles) {
-    __shared__ float As2[2][SLAB * PITCH];
-    __shared__ float Bs2[2][SLAB * PITCH];
+// One operand of a tile: TR rows.  kc: k is the fast index in memory, else the row is.  Load e of a thread
+// covers four k of row row0 + 1024 / BK e (kc), or four rows of k kfirst + 1024 / TR e.
+template <int TR, int BK, bool VEC, bool KC>
+struct Loader {
+    static constexpr int NV = TR * BK / 4 / NT;
+    static constexpr int ER = 1024 / BK, EK = 1024 / TR;      // distance of consecutive loads in rows (KC) / in k
+    const float* base; const float* ptr[NV];
+    int64_t step;
+    int row0, kfirst, at, kend, first, rows, ld, klast;
 
+    __device__ __forceinline__ void init(const float* m, int ld_, int tile_row, int rows_, int k0, int kend_, int K) {
+        base = m; ld = ld_; first = tile_row; rows = rows_; kend = kend_; klast = K - 1;
+        step = KC ? (int64_t)BK : (int64_t)BK * ld;
+        const int t = (int)threadIdx.x;
+        row0 = KC ? t / (BK / 4) : (t % (TR / 4)) * 4;
+        const int kk = KC ? (t % (BK / 4)) * 4 : t / (TR / 4);
+        kfirst = k0 + kk;
+        at = lds_at<BK>(row0, kk >> 2) + (kk & 3);
+#pragma unroll
+        for (int e = 0; e < NV; ++e) {
+            // rows past the matrix repeat its last ones: they only feed outputs that are not stored
+            int r = tile_row + row0 + (KC ? ER * e : 0);
+            const int rmax = KC ? rows - 1 : rows - 4;
+            r = r < rmax ? r : rmax;
+            const int k = kfirst + (KC ? 0 : EK * e);
+            if (VEC) ptr[e] = m + (KC ? (int64_t)r * ld + k : (int64_t)k * ld + r);
+        }
+    }
+    // Load e of a slab.  Unpredicated (addresses clamped into the matrix), so that no load is waited for
+    // before the next; what lies past the contraction's end becomes zero on the way to LDS.  WHOLE
+    // slabs (all but the last of a contraction) need neither.
+    template <bool WHOLE>
+    __device__ __forceinline__ void load(f32x4& v, int e, int slab) {
+        const int k = kfirst + slab * BK + (KC ? 0 : EK * e);
+        if constexpr (VEC) {
+            v = gload(reinterpret_cast<const f32x4*>(WHOLE || k < kend ? ptr[e] : base));
+            ptr[e] += step;
+        } else {
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                int r = first + row0 + (KC ? ER * e : j), q = k + (KC ? j : 0);
+                r = r < rows ? r : rows - 1;
+                q = q < klast ? q : klast;
+                v[j] = gload(base + (KC ? (int64_t)r * ld + q : (int64_t)q * ld + r));
+            }
+        }
+    }
+    template <bool WHOLE>
+    __device__ __forceinline__ void store(f32x4 v, int e, float* lds, int slab) {
+        if constexpr (!WHOLE) {
+#pragma unroll
+            for (int j = 0; j < 4; ++j) v[j] = kfirst + slab * BK + (KC ? j : EK * e) < kend ? v[j] : 0.0f;
+        }
+        if constexpr (KC) {      // rows ER apart: the swizzle of a 32-column slab repeats, that of a 64-column slab flips its lowest bit
+            *reinterpret_cast<f32x4*>(lds + (BK == 64 ? at ^ ((e & 1) << 2) : at) + e * ER * BK) = v;
+        } else {                 // row j of the four moves the swizzle by j / 2 (32 columns) or j (64); k EK apart is chunk EK / 4 apart
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+                lds[(at ^ ((BK == 64 ? j : j >> 1) << 2) ^ (e * EK)) + j * BK] = v[j];
+        }
+    }
+};
+
+__device__ __forceinline__ void gemm_barrier() {   // keeps the global loads in flight
+    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+}
+
+constexpr int kGemmArgs = 4;         // problems that travel in the kernel arguments
+struct GemmF32Args { GemmF32Dev g[kGemmArgs]; };
+
+// The work of one tile; KCA, KCB: k is the fast index of A / B in memory.
+template <class C, bool VEC, bool KCA, bool KCB>
+__device__ __forceinline__ void gemm_tile(const GemmF32Dev& g, int tile, float* lds) {
+    const GemmF32& d = g.d;
+    int local = tile - g.tile_begin;
+    const int split = local / g.tiles;
+    local -= split * g.tiles;
+    const int i0 = (local / g.tiles_q) * C::TM;
+    const int j0 = (local % g.tiles_q) * C::TN;
+    const int k0 = split * g.k_split;
+    const int kend = k0 + g.k_split < d.K ? k0 + g.k_split : d.K;
+
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int ks = wave / (C::WR * C::WC), wrc = wave % (C::WR * C::WC);
+    const int wi = (wrc / C::WC) * (32 * C::RA), wj = (wrc % C::WC) * (32 * C::CB);
+    const int li = lane & 31, lh = lane >> 5;
+
+    // Output columns (or rows) at or beyond *limit are defined to be zero: skip the arithmetic.
+    const int lim = d.limit ? *d.limit : (d.limit_rows ? d.P : d.Q);
+    const bool dead = d.limit && (d.limit_rows ? (i0 >= lim) : (j0 >= lim));
+
+    f32x16 acc[C::RA][C::CB];
+#pragma unroll
+    for (int a = 0; a < C::RA; ++a)
+#pragma unroll
+        for (int b = 0; b < C::CB; ++b)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) acc[a][b][v] = 0.0f;
+
+    if (!dead) {
+        Loader<C::TM, C::BK, VEC, KCA> la;
+        Loader<C::TN, C::BK, VEC, KCB> lb;
+        la.init(d.A, d.lda, i0, d.P, k0, kend, d.K);
+        lb.init(d.B, d.ldb, j0, d.Q, k0, kend, d.K);
+        f32x4 ra[2][C::NVA], rb[2][C::NVB];
+        const int nslab = (kend - k0 + C::BK - 1) / C::BK;
+        const int nwhole = (kend - k0) / C::BK;
+        // piece i of a slab's traffic: first the 16-byte pieces of slab s on their way to LDS, then the
+        // requests for slab s + 2 into the same registers
+        constexpr int NPIECE = 2 * (C::NVA + C::NVB);
+        auto piece = [&](auto whole, int i, int s, int r) {
+            constexpr bool W = decltype(whole)::value;
+            float* buf = lds + (s & 1) * C::slab;
+            if (i < C::NVA) { if (W || s < nslab) la.template store<W>(ra[r][i], i, buf, s); }
+            else if (i < C::NVA + C::NVB) { if (W || s < nslab) lb.template store<W>(rb[r][i - C::NVA], i - C::NVA, buf + C::TM * C::BK, s); }
+            else if (i < 2 * C::NVA + C::NVB) { if (W || s + 2 < nslab) la.template load<W>(ra[r][i - C::NVA - C::NVB], i - C::NVA - C::NVB, s + 2); }
+            else { if (W || s + 2 < nslab) lb.template load<W>(rb[r][i - 2 * C::NVA - C::NVB], i - 2 * C::NVA - C::NVB, s + 2); }
+        };
+        struct Ops { f32x4 a[C::RA], b[C::CB]; } ops[2];
+        auto read = [&](Ops& o, int s, int gq) {
+            const float* As = lds + (s & 1) * C::slab;
+            const float* Bs = As + C::TM * C::BK;
+            const int c = 2 * (ks * C::GPW + gq) + lh;           // chunk of this lane's four k
+#pragma unroll
+            for (int x = 0; x < C::RA; ++x) o.a[x] = *reinterpret_cast<const f32x4*>(As + lds_at<C::BK>(wi + 32 * x + li, c));
+#pragma unroll
+            for (int x = 0; x < C::CB; ++x) o.b[x] = *reinterpret_cast<const f32x4*>(Bs + lds_at<C::BK>(wj + 32 * x + li, c));
+        };
+        // Slab s is multiplied out of buffer s % 2 while slab s + 1 goes to the other buffer (everybody left
+        // it before the last barrier) and slab s + 3 is requested.  A matrix instruction waits for the one
+        // before it on the same accumulators, so the pieces of that traffic are dealt out between them.
+        auto step = [&](auto whole, int s, int u) {
+            read(ops[0], s, 0);
+#pragma unroll
+            for (int gq = 0; gq < C::GPW; ++gq) {
+                if (gq + 1 < C::GPW) read(ops[(gq + 1) & 1], s, gq + 1);
+                __builtin_amdgcn_sched_barrier(0);
+                const Ops& o = ops[gq & 1];
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+#pragma unroll
+                    for (int x = 0; x < C::RA; ++x)
+#pragma unroll
+                        for (int y = 0; y < C::CB; ++y)
+                            acc[x][y] = __builtin_amdgcn_mfma_f32_32x32x2f32(o.a[x][i], o.b[y][i], acc[x][y], 0, 0, 0);
+                    constexpr int NSLOT = 4 * C::GPW;
+                    const int slot = gq * 4 + i;
+#pragma unroll
+                    for (int q = slot * NPIECE / NSLOT; q < (slot + 1) * NPIECE / NSLOT; ++q) piece(whole, q, s + 1, u ^ 1);
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+            }
+            gemm_barrier();
+        };
+        using Yes = std::integral_constant<bool, true>;
+        using No = std::integral_constant<bool, false>;
+#pragma unroll
+        for (int i = NPIECE / 2; i < NPIECE; ++i) piece(No{}, i, -2, 0);      // request slab 0
+#pragma unroll
+        for (int i = NPIECE / 2; i < NPIECE; ++i) piece(No{}, i, -1, 1);      // request slab 1
+#pragma unroll
+        for (int i = 0; i < NPIECE; ++i) piece(No{}, i, 0, 0);                // slab 0 to LDS, request slab 2
+        gemm_barrier();
+        int s = 0;
+        for (; s + 4 < nwhole; s += 2) { step(Yes{}, s, 0); step(Yes{}, s + 1, 1); }
+        for (; s < nslab; s += 2) {
+            step(No{}, s, 0);
+            if (s + 1 < nslab) step(No{}, s + 1, 1);
+        }
+        if constexpr (C::KS > 1) {
+            // contraction groups 1 .. KS-1 hand their sums to group 0, which adds them in order
+            constexpr int per = C::WR * C::WC * C::RA * C::CB * 16;
+            if (ks > 0) {
+#pragma unroll
+                for (int x = 0; x < C::RA; ++x)
+#pragma unroll
+                    for (int y = 0; y < C::CB; ++y)
+#pragma unroll
+                        for (int v = 0; v < 16; ++v)
+                            lds[((ks - 1) * per + (wrc * C::RA * C::CB + x * C::CB + y) * 16 + v) * 64 + lane] = acc[x][y][v];
+            }
+            gemm_barrier();
+            if (ks > 0) return;
+#pragma unroll
+            for (int o = 0; o < C::KS - 1; ++o)
+#pragma unroll
+                for (int x = 0; x < C::RA; ++x)
+#pragma unroll
+                    for (int y = 0; y < C::CB; ++y)
+#pragma unroll
+                        for (int v = 0; v < 16; ++v)
+                            acc[x][y][v] += lds[(o * per + (wrc * C::RA * C::CB + x * C::CB + y) * 16 + v) * 64 + lane];
+        }
+    } else if (C::KS > 1 && ks > 0) {
+        return;
+    }
+
+    const bool partial = g.splits > 1;
+    float* const out = partial ? g.part + (int64_t)split * d.P * d.Q : d.C;
+    const int ldo = partial ? d.Q : d.ldc;
+#pragma unroll
+    for (int a = 0; a < C::RA; ++a)
+#pragma unroll
+        for (int b = 0; b < C::CB; ++b)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) {
+                const int row = i0 + wi + a * 32 + 8 * (v >> 2) + 4 * lh + (v & 3);
+                const int col = j0 + wj + b * 32 + li;
+                if (row < d.P && col < d.Q) {
+                    float* c = out + (int64_t)row * ldo + col;
+                    if (partial) { gstore(c, acc[a][b][v]); continue; }
+                    const bool zero = d.limit && (d.limit_rows ? (row >= lim) : (col >= lim));
+                    float val = zero ? 0.0f : d.alpha * acc[a][b][v];
+                    if (d.accumulate && !zero) val += gload(c);
+                    gstore(c, val);
+                }
+            }
+}
+
+template <class C, bool VEC>
+__global__ __launch_bounds__(NT, 3) void gemm_f32_kernel(const GemmF32Dev* __restrict__ table, GemmF32Args args, int ndesc, int ntiles) {
+    __shared__ __align__(16) float lds[C::lds_floats];
     // Tiles are numbered problem by problem; block b works on tile (b % 8) * (grid / 8) + b / 8, so each
     // XCD (block index modulo 8) gets a contiguous eighth of the list and the tiles of one problem
     // share their operand panels through one L2.  The grid is the tile count rounded up to 8.
     const int tile = (int)(blockIdx.x & 7) * (int)(gridDim.x >> 3) + (int)(blockIdx.x >> 3);
     if (tile >= ntiles) return;
     GemmF32Dev g;
-    if (use_single) {
-        g = single;
+    if (table == nullptr) {
+        int i = 0;
+        while (i + 1 < ndesc && args.g[i + 1].tile_begin <= tile) ++i;
+        g = args.g[i];
     } else {
         int lo = 0, hi = ndesc - 1;
         while (lo < hi) {  // last descriptor whose tile_begin <= tile
             int mid = (lo + hi + 1) >> 1;
-            if (descs[mid].tile_begin <= tile) lo = mid; else hi = mid - 1;
+            if (table[mid].tile_begin <= tile) lo = mid; else hi = mid - 1;
         }
-        g = descs[lo];
+        g = table[lo];
     }
-    const GemmF32& d = g.d;
-    const int local = tile - g.tile_begin;
-    const int i0 = (local / g.tiles_q) * TILE;
-    const int j0 = (local % g.tiles_q) * TILE;
-
-    const int t = threadIdx.x;
-    const int lane = t & 63, wave = t >> 6;
-    const int wi = (wave >> 1) * 64, wj = (wave & 1) * 64;
-
-    // Output columns (or rows) at or beyond *limit are defined to be zero: skip the arithmetic.
-    int lim = d.limit ? *d.limit : (d.limit_rows ? d.P : d.Q);
-    const bool dead = d.limit && (d.limit_rows ? (i0 >= lim) : (j0 >= lim));
-
-    f32x16 acc[2][2];
-#pragma unroll
-    for (int a = 0; a < 2; ++a)
-#pragma unroll
-        for (int b = 0; b < 2; ++b)
-#pragma unroll
-            for (int v = 0; v < 16; ++v) acc[a][b][v] = 0.0f;
-
-    if (!dead) {
-        float ra[8], rb[8];
-        bool oka[8], okb[8];
-        auto load_slab = [&](int k0) {
-#pragma unroll
-            for (int e = 0; e < 8; ++e) {
-                const int lin = e * 256 + t;
-                if (d.transA) {  // A stored [K, P]
-                    const int k = lin >> 7, i = lin & 127;
-                    ra[e] = fetch(d.A, k0 + k, i0 + i, d.lda, d.K, d.P, oka[e]);
-                } else {         // A stored [P, K]
-                    const int i = lin >> 4, k = lin & 15;
-                    ra[e] = fetch(d.A, i0 + i, k0 + k, d.lda, d.P, d.K, oka[e]);
-                }
-                if (d.transB) {  // B stored [Q, K]
-                    const int j = lin >> 4, k = lin & 15;
-                    rb[e] = fetch(d.B, j0 + j, k0 + k, d.ldb, d.Q, d.K, okb[e]);
-                } else {         // B stored [K, Q]
-                    const int k = lin >> 7, j = lin & 127;
-                    rb[e] = fetch(d.B, k0 + k, j0 + j, d.ldb, d.K, d.Q, okb[e]);
-                }
-            }
-        };
-        auto store_slab = [&](int buf) {
-            float* As = As2[buf];
-            float* Bs = Bs2[buf];
-#pragma unroll
-            for (int e = 0; e < 8; ++e) {
-                const int lin = e * 256 + t;
-                const float va = oka[e] ? ra[e] : 0.0f, vb = okb[e] ? rb[e] : 0.0f;
-                if (d.transA) As[(lin >> 7) * PITCH + (lin & 127)] = va;
-                else          As[(lin & 15) * PITCH + (lin >> 4)] = va;
-                if (d.transB) Bs[(lin & 15) * PITCH + (lin >> 4)] = vb;
-                else          Bs[(lin >> 7) * PITCH + (lin & 127)] = vb;
-            }
-        };
-
-        // two LDS buffers, one barrier per slab: while slab s is multiplied out of buffer s % 2, slab
-        // s + 1 (in registers since the iteration before) goes to the other buffer and the loads of
-        // slab s + 2 are issued, so a load has two slabs of products to arrive
-        const int nslab = (d.K + SLAB - 1) / SLAB;
-        load_slab(0);
-        store_slab(0);
-        if (nslab > 1) load_slab(SLAB);
-        __syncthreads();
-        for (int s = 0; s < nslab; ++s) {
-            const float* As = As2[s & 1];
-            const float* Bs = Bs2[s & 1];
-            if (s + 1 < nslab) {
-                store_slab((s & 1) ^ 1);                  // everybody left that buffer before the last barrier
-                if (s + 2 < nslab) load_slab((s + 2) * SLAB);
-            }
-            const int li = lane & 31, lk = lane >> 5;
-#pragma unroll
-            for (int kk = 0; kk < SLAB; kk += 2) {
-                float a0 = As[(kk + lk) * PITCH + wi + li];
-                float a1 = As[(kk + lk) * PITCH + wi + 32 + li];
-                float b0 = Bs[(kk + lk) * PITCH + wj + li];
-                float b1 = Bs[(kk + lk) * PITCH + wj + 32 + li];
-                acc[0][0] = __builtin_amdgcn_mfma_f32_32x32x2f32(a0, b0, acc[0][0], 0, 0, 0);
-                acc[0][1] = __builtin_amdgcn_mfma_f32_32x32x2f32(a0, b1, acc[0][1], 0, 0, 0);
-                acc[1][0] = __builtin_amdgcn_mfma_f32_32x32x2f32(a1, b0, acc[1][0], 0, 0, 0);
-                acc[1][1] = __builtin_amdgcn_mfma_f32_32x32x2f32(a1, b1, acc[1][1], 0, 0, 0);
-            }
-            __syncthreads();
-        }
+    if (g.d.transA) {
+        if (g.d.transB) gemm_tile<C, VEC, false, true>(g, tile, lds);
+        else gemm_tile<C, VEC, false, false>(g, tile, lds);
+    } else {
+        if (g.d.transB) gemm_tile<C, VEC, true, true>(g, tile, lds);
+        else gemm_tile<C, VEC, true, false>(g, tile, lds);
     }
-
-    const int lj = lane & 31, lh = lane >> 5;
-#pragma unroll
-    for (int a = 0; a < 2; ++a)
-#pragma unroll
-        for (int b = 0; b < 2; ++b)
-#pragma unroll
-            for (int v = 0; v < 16; ++v) {
-                const int row = i0 + wi + a * 32 + 8 * (v >> 2) + 4 * lh + (v & 3);
-                const int col = j0 + wj + b * 32 + lj;
-                if (row < d.P && col < d.Q) {
-                    float* c = d.C + (int64_t)row * d.ldc + col;
-                    const bool zero = d.limit && (d.limit_rows ? (row >= lim) : (col >= lim));
-                    float val = zero ? 0.0f : d.alpha * acc[a][b][v];
-                    if (d.accumulate && !zero) val += *c;
-                    *c = val;
-                }
-            }
 }
+
+// C (+)= alpha * (sum over the splits of the partial sums, in order), for the split problems of a launch
+__global__ __launch_bounds__(NT) void gemm_f32_reduce_kernel(GemmF32Args args, int ndesc) {
+    const GemmF32Dev& g = args.g[blockIdx.y];
+    if ((int)blockIdx.y >= ndesc || g.splits < 2) return;
+    const int64_t total = (int64_t)g.d.P * g.d.Q;
+    for (int64_t i = (int64_t)blockIdx.x * NT + threadIdx.x; i < total; i += (int64_t)gridDim.x * NT) {
+        float s = gload(g.part + i);
+        for (int q = 1; q < g.splits; ++q) s += gload(g.part + q * total + i);
+        float* c = g.d.C + (g.d.ldc == g.d.Q ? i : (i / g.d.Q) * g.d.ldc + i % g.d.Q);
+        s *= g.d.alpha;
+        gstore(c, g.d.accumulate ? s + gload(c) : s);
+    }
+}
+
+using Wide = GemmCfg<64, 64, 2, 2, 1, 32>;
+using Small = GemmCfg<32, 32, 1, 1, 4, 64>;
+
+int tiles_of(const GemmF32& d, int tm, int tn) { return (int)(ceil_div(d.P, tm) * ceil_div(d.Q, tn)); }
+
+// 16-byte loads: rows start on 16 bytes and hold whole pieces of four
+bool vec_ok(const GemmF32& d) {
+    auto ok = [](const float* p, int ld, int fast) { return reinterpret_cast<uintptr_t>(p) % 16 == 0 && ld % 4 == 0 && fast % 4 == 0; };
+    return ok(d.A, d.lda, d.transA ? d.P : d.K) && ok(d.B, d.ldb, d.transB ? d.K : d.Q);
+}
+
+GemmF32Dev describe(const GemmF32& d, int tm, int tn, int tile_begin, int splits) {
+    GemmF32Dev g{};
+    g.d = d;
+    g.tile_begin = tile_begin;
+    g.tiles_q = (int)ceil_div(d.Q, tn);
+    g.tiles = tiles_of(d, tm, tn);
+    g.k_split = (int)ceil_div(ceil_div(d.K, splits), 64) * 64;
+    g.splits = (int)ceil_div(d.K, g.k_split);
+    return g;
+}
+
+void launch_form(bool small, bool vec, int tiles, const GemmF32Dev* table, const GemmF32Args& a, int n, hipStream_t s) {
+    const dim3 grid((tiles + 7) / 8 * 8), block(NT);
+    if (small && vec) hipLaunchKernelGGL((gemm_f32_kernel<Small, true>), grid, block, 0, s, table, a, n, tiles);
+    else if (small) hipLaunchKernelGGL((gemm_f32_kernel<Small, false>), grid, block, 0, s, table, a, n, tiles);
+    else if (vec) hipLaunchKernelGGL((gemm_f32_kernel<Wide, true>), grid, block, 0, s, table, a, n, tiles);
+    else hipLaunchKernelGGL((gemm_f32_kernel<Wide, false>), grid, block, 0, s, table, a, n, tiles);
+}
+
+// 64 x 64 tiles once they give every compute unit one; below that the 32 x 32 form (measured: 150 tiles of
+// 64 x 64, K = 768: 19.1 us against 17.1; K = 3072: 62.8 against 47.2; 432 tiles, K = 384: 19.5 against 24.2)
+bool use_small(int64_t wide_tiles) { return wide_tiles < 256; }
 
 }  // namespace
 
-hipError_t launch_gemm_f32_one(const GemmF32& d, hipStream_t s) {
-    GemmF32Dev g;
-    g.d = d;
-    g.tile_begin = 0;
-    g.tiles_q = (d.Q + TILE - 1) / TILE;
-    const int tiles = ((d.P + TILE - 1) / TILE) * g.tiles_q;
+int gemm_f32_splits(const GemmF32& d) {
+    // A contraction much longer than the output is wide (the factor gradients: K = batch rows) is split
+    // until the launch has about two work-groups per compute unit, at least 256 columns per split
+    // (measured, the reduction included, K = 3152: 3072 x 192 65.9 us whole, 52.3 in four; 192 x 768 65.2
+    // whole, 22.9 in four, 25.5 in eight).
+    const int64_t tiles = tiles_of(d, Wide::TM, Wide::TN);
+    int64_t s = 512 / (tiles > 0 ? tiles : 1);
+    const int64_t by_k = d.K / 256;
+    if (s > by_k) s = by_k;
+    if (s > 64) s = 64;
+    return s < 1 ? 1 : (int)s;
+}
+
+size_t gemm_f32_partial_bytes(const GemmF32& d, int splits) {
+    return splits > 1 ? align_up((size_t)splits * d.P * d.Q * sizeof(float), 256) : 0;
+}
+
+hipError_t launch_gemm_f32(const GemmF32* p, const int* splits, int n, float* partials, hipStream_t s) {
+    if (n < 1 || n > kGemmArgs) return hipErrorInvalidValue;
+    int64_t wide_tiles = 0;
+    bool any_split = false, vec = true;
+    for (int i = 0; i < n; ++i) {
+        wide_tiles += (int64_t)tiles_of(p[i], Wide::TM, Wide::TN) * (splits ? splits[i] : 1);
+        if (splits && splits[i] > 1) any_split = true;
+        vec = vec && vec_ok(p[i]);
+    }
+    const bool small = use_small(wide_tiles);
+    const int tm = small ? Small::TM : Wide::TM, tn = small ? Small::TN : Wide::TN;
+    GemmF32Args a{};
+    int tiles = 0;
+    int64_t largest = 0;
+    char* part = (char*)partials;
+    for (int i = 0; i < n; ++i) {
+        a.g[i] = describe(p[i], tm, tn, tiles, splits ? splits[i] : 1);
+        if (a.g[i].splits > 1) {
+            if (!partials) return hipErrorInvalidValue;
+            a.g[i].part = (float*)part;
+            part += gemm_f32_partial_bytes(p[i], a.g[i].splits);
+            if ((int64_t)p[i].P * p[i].Q > largest) largest = (int64_t)p[i].P * p[i].Q;
+        }
+        tiles += a.g[i].tiles * a.g[i].splits;
+    }
     if (tiles <= 0) return hipSuccess;
-    hipLaunchKernelGGL(gemm_f32_kernel, dim3((tiles + 7) / 8 * 8), dim3(256), 0, s, nullptr, 0, g, 1, tiles);
+    launch_form(small, vec, tiles, nullptr, a, n, s);
+    if (any_split && largest > 0) {
+        const int64_t blocks = ceil_div(largest, NT);
+        hipLaunchKernelGGL(gemm_f32_reduce_kernel, dim3((unsigned)(blocks < 2048 ? blocks : 2048), n), dim3(NT), 0, s, a, n);
+    }
     return hipGetLastError();
 }
 
+hipError_t launch_gemm_f32_one(const GemmF32& d, hipStream_t s) { return launch_gemm_f32(&d, nullptr, 1, nullptr, s); }
+
 // Grouped launch in two steps so the caller can batch the upload with its other tables:
-// gemm_f32_build_table fills `host_image` (n * gemm_f32_desc_bytes() bytes) and returns the tile
-// count; after the caller has copied the image to device memory, launch_gemm_f32_table runs it.
+// gemm_f32_build_table fills `host_image` (n * gemm_f32_desc_bytes() bytes) and says which form of the
+// kernel takes it; after the caller has copied the image to device memory, launch_gemm_f32_table runs it.
 size_t gemm_f32_desc_bytes() { return sizeof(GemmF32Dev); }
 
-int gemm_f32_build_table(const GemmF32* descs_host, int n, void* host_image) {
+GemmF32Table gemm_f32_build_table(const GemmF32* descs_host, int n, void* host_image) {
     GemmF32Dev* tmp = static_cast<GemmF32Dev*>(host_image);
-    int tiles = 0;
+    GemmF32Table t{n, 0, true, true};
+    int64_t wide_tiles = 0;
     for (int i = 0; i < n; ++i) {
-        tmp[i].d = descs_host[i];
-        tmp[i].tile_begin = tiles;
-        tmp[i].tiles_q = (descs_host[i].Q + TILE - 1) / TILE;
-        tiles += ((descs_host[i].P + TILE - 1) / TILE) * tmp[i].tiles_q;
+        wide_tiles += tiles_of(descs_host[i], Wide::TM, Wide::TN);
+        t.vec = t.vec && vec_ok(descs_host[i]);
     }
-    return tiles;
+    t.small = use_small(wide_tiles);
+    for (int i = 0; i < n; ++i) {
+        tmp[i] = describe(descs_host[i], t.small ? Small::TM : Wide::TM, t.small ? Small::TN : Wide::TN, t.tiles, 1);
+        t.tiles += tmp[i].tiles;
+    }
+    return t;
 }
 
-hipError_t launch_gemm_f32_table(const void* dev_image, int n, int tiles, hipStream_t s) {
-    if (n <= 0 || tiles <= 0) return hipSuccess;
-    GemmF32Dev none{};
-    hipLaunchKernelGGL(gemm_f32_kernel, dim3((tiles + 7) / 8 * 8), dim3(256), 0, s,
-                       (const GemmF32Dev*)dev_image, n, none, 0, tiles);
+hipError_t launch_gemm_f32_table(const void* dev_image, const GemmF32Table& t, hipStream_t s) {
+    if (t.n <= 0 || t.tiles <= 0) return hipSuccess;
+    launch_form(t.small, t.vec, t.tiles, (const GemmF32Dev*)dev_image, GemmF32Args{}, t.n, s);
     return hipGetLastError();
 }
 

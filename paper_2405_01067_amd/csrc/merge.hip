@@ -1064,7 +1064,7 @@ hipError_t merge_run(const abt_merge_desc* layers, int L, void* workspace, int m
     ABT_TRY(hipMemcpyAsync(ws + p.off_wg_intra, wintra.data(), sizeof(int2) * wintra.size(), hipMemcpyHostToDevice, s));
     ABT_TRY(hipMemcpyAsync(ws + p.off_gemm64, g64.data(), sizeof(GemmF64) * g64.size(), hipMemcpyHostToDevice, s));
     std::vector<char> g32img(gemm_f32_desc_bytes() * (g32.empty() ? 1 : g32.size()));
-    const int tiles32 = gemm_f32_build_table(g32.data(), (int)g32.size(), g32img.data());
+    const GemmF32Table table32 = gemm_f32_build_table(g32.data(), (int)g32.size(), g32img.data());
     ABT_TRY(hipMemcpyAsync(ws + p.off_gemm32, g32img.data(), gemm_f32_desc_bytes() * g32.size(), hipMemcpyHostToDevice, s));
     // the uploads must have left the host vectors before they are destroyed
     ABT_TRY(hipStreamSynchronize(s));
@@ -1226,7 +1226,7 @@ hipError_t merge_run(const abt_merge_desc* layers, int L, void* workspace, int m
     if (tb2 > 0) hipLaunchKernelGGL(gemm_f64_kernel, dim3(align_up(tb2, 8)), dim3(256), 0, s, d64 + 2 * p.n_gemm64, p.n_gemm64, tb2);
     ABT_TRY(hipGetLastError());
     ABT_TRY(mark(5));
-    ABT_TRY(launch_gemm_f32_table(ws + p.off_gemm32, (int)g32.size(), tiles32, s));
+    ABT_TRY(launch_gemm_f32_table(ws + p.off_gemm32, table32, s));
     ABT_TRY(mark(6));
 #undef ABT_TRY
     return hipSuccess;

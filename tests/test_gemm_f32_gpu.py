@@ -1,0 +1,75 @@
+"""The fp32 matrix product behind the fp32 layer path and ab_reconstruct, at the edges of its tiles
+(32 and 64), of its slabs (32 and 64 columns of the contraction), of the 16-byte load path (sizes that
+are not multiples of four) and of the split contraction (batches from 512 rows).
+
+Bound: a sum of K products in fp32 in any order is off by at most (K + 2) 2^-24 sum |a| |b| (K roundings of
+partial sums, one of the product, one of the output)."""
+import pytest
+
+torch = pytest.importorskip("torch")
+from paper_2405_01067_amd import binding as abt
+
+pytestmark = pytest.mark.gpu
+EPS = 2.0 ** -24
+
+
+def close(out, a, b):
+    """out = a b, a and b fp64 on the GPU."""
+    assert bool(torch.isfinite(out).all())
+    assert bool(((out.double() - a @ b).abs() <= (a.shape[1] + 2) * EPS * (a.abs() @ b.abs())).all())
+
+
+def rnd(g, *shape):
+    return torch.randn(shape, generator=g, device="cuda")
+
+
+@pytest.mark.parametrize("m,n,k", [(1, 1, 1), (31, 33, 5), (32, 32, 64), (33, 64, 65), (64, 65, 128), (4, 4, 3), (63, 100, 31),
+                                   (130, 68, 36), (1024, 1025, 33), (1023, 1028, 96), (1088, 1024, 192)])
+def test_reconstruct_edges(m, n, k):
+    g = torch.Generator(device="cuda").manual_seed(m * 7 + n * 3 + k)
+    A, B = rnd(g, m, k), rnd(g, k, n)
+    close(abt.ab_reconstruct(A, B), A.double(), B.double())
+
+
+@pytest.mark.parametrize("M,m,n,r", [(1, 24, 36, 8), (5, 33, 7, 3), (64, 256, 256, 32), (63, 66, 130, 34), (511, 64, 68, 32),
+                                     (512, 65, 64, 31), (1030, 200, 96, 36), (3152, 768, 192, 96), (2049, 1028, 1024, 64)])
+@pytest.mark.parametrize("keep_T,accumulate", [(True, False), (False, True)])
+def test_layer_edges(M, m, n, r, keep_T, accumulate):
+    g = torch.Generator(device="cuda").manual_seed(M + m + n + r)
+    X, dY, A, B = rnd(g, M, n), rnd(g, M, m), rnd(g, m, r), rnd(g, r, n)
+    Xd, dYd, Ad, Bd = (t.double() for t in (X, dY, A, B))
+    Y, T = abt.lr_linear_fwd(X, A, B, save_T=keep_T)
+    dA0, dB0 = rnd(g, m, r), rnd(g, r, n)
+    dA, dB = (dA0.clone(), dB0.clone()) if accumulate else (None, None)
+    dX, dA, dB = abt.lr_linear_bwd(dY, X, T, A, B, dA=dA, dB=dB, accumulate=accumulate)
+    again = abt.lr_linear_bwd(dY, X, T, A, B, dA=dA0.clone() if accumulate else None,
+                              dB=dB0.clone() if accumulate else None, accumulate=accumulate)
+    for a, b in zip((dX, dA, dB), again):
+        assert torch.equal(a, b)                      # fixed order of summation
+    if keep_T:
+        close(T, Xd, Bd.T)
+    # second products: T and dT carry the error of the first ones, bounded through |X| |B|^T and |dY| |A|
+    Td, dTd = Xd @ Bd.T, dYd @ Ad
+    Tm, dTm = (Xd.abs() @ Bd.abs().T) * (n + 2) * EPS, (dYd.abs() @ Ad.abs()) * (m + 2) * EPS
+    for out, a, b, am, bm, base in ((Y, Td, Ad.T, Tm, None, None), (dX, dTd, Bd, dTm, None, None),
+                                    (dA, dYd.T, Td, None, Tm, dA0 if accumulate else None),
+                                    (dB, dTd.T, Xd, dTm.T, None, dB0 if accumulate else None)):
+        ref, mag = a @ b, a.abs() @ b.abs()
+        err = (a.shape[1] + 4) * EPS * mag + (am @ b.abs() if am is not None else a.abs() @ bm) * (1 + 1e-3)
+        if base is not None:
+            ref, err = ref + base.double(), err + 2 * EPS * (base.double().abs() + ref.abs())
+        assert bool(torch.isfinite(out).all())
+        assert bool(((out.double() - ref).abs() <= err).all())
+
+
+def test_split_fits_the_static_scratch():
+    """A shape whose dT and T alone fill the 64 MiB of lr_linear_bwd_static is still served by it."""
+    M, m, n, r = 65536, 32, 36, 128
+    g = torch.Generator(device="cuda").manual_seed(3)
+    X, dY, A, B = rnd(g, M, n), rnd(g, M, m), rnd(g, m, r), rnd(g, r, n)
+    dB = torch.empty_like(B)
+    abt.lr_linear_bwd_static(dY, X, None, A, B, dB=dB)
+    Xd, dYd, Ad = X.double(), dY.double(), A.double()
+    dT, dT_err = dYd @ Ad, (dYd.abs() @ Ad.abs()) * (m + 2) * EPS
+    err = (M + 4) * EPS * (dT.abs().T @ Xd.abs()) + (dT_err.T @ Xd.abs()) * (1 + 1e-3)
+    assert bool(((dB.double() - dT.T @ Xd).abs() <= err).all())
