@@ -42,10 +42,68 @@ ChainShape choose_chain_shape(int64_t M, int p, int q, int R, bool second_stage,
     return cost128 < cost64 ? ChainShape{128, parts} : small;
 }
 
+// Work-groups per row block of the narrow-rank kernel: as many as find an idle compute unit, while one more
+// saves a tenth of the slabs (each repeats the p / 64 slabs of stage 1).
+int narrow_parts(int64_t row_blocks, int p, int q, bool second_stage) {
+    if (!second_stage) return 1;
+    const int ns1 = p / 64, ntile = q / 64;
+    int best = 1;
+    for (int parts = 2; parts <= ntile && row_blocks * parts <= 256; ++parts) {
+        const int now = ns1 + (ntile + best - 1) / best, then = ns1 + (ntile + parts - 1) / parts;
+        if (10 * then <= 9 * now) best = parts;
+    }
+    return best;
+}
+// Rows per work-group of the narrow-rank kernel: the smallest whole number of work-groups per compute unit with at
+// most 128 rows each, and the rows shared out evenly among them (39597 rows as 512 work-groups of 80 rows instead of
+// 310 of 128: 82 us instead of 89, 69 instead of 75, at 3072 x 768, r = 96).  A small batch keeps 128 rows: its
+// row blocks are shared by output tiles instead.
+int narrow_rows(int64_t M) {
+    if (M <= 8192) return 128;
+    const int64_t per_cu = ceil_div(M, 256 * 128);
+    return (int)(ceil_div(ceil_div(M, 256 * per_cu), 4) * 4);
+}
+// Where the narrow-rank kernel is taken for a matrix operand (times of a forward in us, this kernel / what was taken
+// before, inputs not in the last-level cache):
+//   at most 8192 rows and p <= q: its work-groups can share a row block's output tiles.  197 x 768 -> 3072: 12 / 25
+//     at r = 96, 17 / 30 at r = 192; 6304 rows 24 / 32, 33 / 38; 768 -> 768: 12 / 13 at r = 96, but 19 / 15 at
+//     r = 192, hence 2 p <= q beyond r = 96.  (197 x 3072 -> 768: 32 / 22.)
+//   more than 32768 rows, i.e. at least two work-groups per compute unit, r <= 160: 39597 x 768 -> 3072 / 3072 -> 768 /
+//     768 -> 768 at r = 96: 69 / 83, 82 / 94, 40 / 46; r = 64: 65 / 68, 80 / 89, 33 / 45; 100000 rows, r = 64: 164 / 171,
+//     160 / 171, 75 / 82; r = 128: 188 / 179, 195 / 201, 84 / 94; r = 160: 220 / 241, 225 / 291, 93 / 136.
+//     (r = 192: 241 / 213, 246 / 226, 104 / 100.)  r = 32 only where p >= q: 153 / 150, but 149 / 161, 61 / 70.
+//     One work-group alone on a compute unit waits for its loads (12608 rows, r = 96: 44 / 28, 45 / 36, 23 / 20); at
+//     r = 160, where the other kernel has 64-row work-groups only, two rounds of those are slower still: from 16384
+//     rows on (17000: 59 / 47, 60 / 85, 29 / 41).
+// (The rule does not ask for the second stage: a T that the backward computes again comes from the same kernel.)
+bool use_narrow(int64_t rows, int p, int q, int R) {
+    if (g_chain_rows.load() != 0 || g_chain_parts.load() != 0 || !chain4_supports(R, p, q)) return false;
+    if (rows <= 8192) return R <= 96 ? p <= q : 2 * p <= q;
+    if (R == 160) return rows > 16384;
+    return rows > 32768 && (R == 32 ? p >= q : R <= 128);
+}
+
+// From an image: a lane has one pixel for the whole kernel, while the loader waves of the other kernels compute
+// a range check per 16 bytes.  Forward, us, this kernel / the better of the others, r = 64: 56 x 56 x 64
+// (200704 rows) 50 / 110, 28 x 28 x 128 (50176 rows) 29 / 43; with few row blocks the other kernels' deeper prefetch
+// wins back (14 x 14 x 256, 12544 rows: 28 / 26, r = 192 45 / 32) except where the patches are strided
+// (28 x 28 x 128, stride 2: 17 / 20; r = 192 27 / 24).
+bool narrow_gather(int64_t row_blocks, int mul, int p, int q, int R) {
+    if (g_chain_rows.load() != 0 || g_chain_parts.load() != 0 || !chain4_supports(R, p, q)) return false;
+    return row_blocks > 128 || (mul == 2 && R <= 96);
+}
+
 // the gathered chain (factored convolution): same choice of work-group height, no column parts
 hipError_t chain_gather(const void* image, const PatchGeom& g, const void* P, const void* Q, void* Yout, void* Tout,
                         int t_pitch, int64_t M, int q, int R, hipStream_t s) {
     const int p = g.kh * g.kw * ((g.Cin + 63) / 64) * 64;
+    if (g.shift == 0 && narrow_gather(ceil_div(M, 128), g.mul, p, q, R)) {
+        const ChainGather cg{g.H, g.W, g.Cin, 0, g.kh, g.kw, g.sign, g.kh / 2, g.kw / 2, g.RH, g.RW, g.mul, 1, 0, 0, g.RH, g.RW};
+        const GatherProblem one{image, P, Q, Yout, Tout, M, cg};
+        const hipError_t e = launch_chain4_gather_bf16(&one, 1, q, R, t_pitch, narrow_rows(M), narrow_parts(ceil_div(M, narrow_rows(M)), p, q, Yout != nullptr), s);
+        if (e != hipErrorInvalidValue) return e;
+        (void)hipGetLastError();
+    }
     const ChainShape sh = choose_chain_shape(M, p, q, R, Yout != nullptr, false);
     if (sh.rows == 128) {
         // the tall launcher checks the image window of a 128-row block before it launches anything and
@@ -59,6 +117,10 @@ hipError_t chain_gather(const void* image, const PatchGeom& g, const void* P, co
 
 hipError_t chain(const void* Xin, const void* P, const void* Q, void* Yout, void* Tout,
                  int64_t M, int p, int q, int R, hipStream_t s) {
+    if (use_narrow(M, p, q, R)) {
+        const ChainProblem one{Xin, P, Q, Yout, Tout};
+        return launch_chain4_bf16(&one, 1, M, p, q, R, narrow_rows(M), narrow_parts(ceil_div(M, narrow_rows(M)), p, q, Yout != nullptr), s);
+    }
     const ChainShape sh = choose_chain_shape(M, p, q, R, Yout != nullptr, true);
     if (sh.rows == 128) return launch_chain2_tall_bf16(Xin, P, Q, Yout, Tout, M, p, q, R, sh.parts, s);
     if (chain2_supports(R, p, q)) return launch_chain2_bf16(Xin, P, Q, Yout, Tout, M, p, q, R, s);
@@ -252,6 +314,66 @@ ConvBwdLayout conv_bwd_layout(const abt_conv_geom& g, int64_t m, int64_t r) {
     return w;
 }
 
+// dAct[q, c] = sum over taps and j of dT[(q - shift(tap)) / stride, j] B[j, tap, c] (only where the division
+// is exact): the same gathered product as the forward, on the image dT [N, H', W', r] with mirrored
+// shifts, against the re-laid-out factor Pst; rows are the input pixels.
+// With stride 2 a tap reaches only the pixels of one parity, so the pixels are taken parity by
+// parity, each with its own taps: 2.25 instead of 9 taps per pixel for a 3 x 3 window.  All parities and blocks
+// of output channels go into one launch (whole backward, us, against the kernel for all taps, batch 64, r = 64:
+// 28 x 28 x 128 stride 2 56 / 75, stride 1 75 / 91; 56 x 56 x 64 stride 2 79 / 179; 7 x 7 x 2048 1 x 1 48 / 101).
+hipError_t conv_dact(const void* dT, const void* B, void* dAct, void* Pst, const abt_conv_geom& g, int r, int r_pad, hipStream_t s) {
+    const int C = (int)g.C, taps = g.kh * g.kw;
+    const int Ho = (int)conv_out(g.H, g.stride), Wo = (int)conv_out(g.W, g.stride);
+    const int64_t M_in = g.N * g.H * g.W;
+    hipError_t e;
+    if (g_chain_rows.load() == 0 && g_chain_parts.load() == 0 && chain4_supports(64, taps * r_pad, 64)) {
+        int chunk = 64;
+        for (int v : {192, 160, 128, 96}) if (C % v == 0) { chunk = v; break; }
+        const bool by_parity = g.stride == 2;
+        GatherProblem pr[kChainMaxGroups];
+        int n = 0;
+        bool wide = false;                       // a window that 32-bit offsets do not cover: the kernels below check again
+        e = launch_conv_bstack_bf16(B, Pst, r, C, g.kh, g.kw, r_pad, by_parity, s);
+        if (e != hipSuccess) return e;
+        for (int cls = by_parity ? 3 : 0; cls >= 0 && !wide; --cls) {      // most taps first
+            const int py = cls >> 1, px = cls & 1;
+            ChainGather cg{Ho, Wo, r, 0, g.kh, g.kw, -1, g.kh / 2, g.kw / 2, (int)g.H, (int)g.W, 1, 1, 0, 0, (int)g.H, (int)g.W};
+            int64_t before = 0;
+            if (by_parity) {
+                const int ny = parity_count(g.kh, py), nx = parity_count(g.kw, px), ny0 = parity_count(g.kh, 0), nx0 = parity_count(g.kw, 0);
+                before = (py ? ny0 * g.kw : 0) + (px ? ny * nx0 : 0);
+                cg.kh = ny; cg.kw = nx;
+                cg.cy = (py - parity_first(g.kh, py) + g.kh / 2) / 2; cg.cx = (px - parity_first(g.kw, px) + g.kw / 2) / 2;
+                cg.RH = ((int)g.H - py + 1) / 2; cg.RW = ((int)g.W - px + 1) / 2;
+                cg.omul = 2; cg.oy = py; cg.ox = px;
+                if (ny * nx == 0) { cg.H = 0; cg.kh = cg.kw = 1; cg.cy = cg.cx = 0; before = 0; }     // no tap: zeros
+            }
+            const int64_t pitch = (int64_t)cg.kh * cg.kw * r_pad, M = g.N * cg.RH * cg.RW;
+            for (int c0 = 0; c0 < C && !wide; c0 += chunk) {
+                pr[n++] = GatherProblem{dT, (const char*)Pst + ((before * C) * r_pad + (int64_t)c0 * pitch) * 2, nullptr, nullptr,
+                                        (char*)dAct + (size_t)c0 * 2, M, cg};
+                if (n == kChainMaxGroups || (cls == 0 && c0 + chunk >= C)) {
+                    e = launch_chain4_gather_bf16(pr, n, 64, chunk, C, 128, 1, s);
+                    if (e == hipErrorInvalidValue) { (void)hipGetLastError(); wide = true; break; }
+                    if (e != hipSuccess) return e;
+                    n = 0;
+                }
+            }
+        }
+        if (!wide) return hipSuccess;
+    }
+    e = launch_conv_bstack_bf16(B, Pst, r, C, g.kh, g.kw, r_pad, false, s);
+    if (e != hipSuccess) return e;
+    const PatchGeom adj = conv_adjoint_geom(g, r);
+    const int chunk = conv_dact_chunk(C);        // one launch per block of output channels
+    const int64_t pst_pitch = (int64_t)taps * r_pad;
+    for (int64_t c0 = 0; c0 < C; c0 += chunk) {
+        e = chain_gather(dT, adj, (const char*)Pst + (size_t)c0 * pst_pitch * 2, nullptr, nullptr, (char*)dAct + c0 * 2, C, M_in, 64, chunk, s);
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
+}
+
 }  // namespace
 
 size_t lr_conv_bwd_workspace_bytes(const abt_conv_geom* geom, int64_t m, int64_t r, int dt) {
@@ -290,7 +412,7 @@ int lr_conv_bwd(const void* dY, const void* act, const void* T, const void* A, c
     if (!dAct && !dA && !dB) return ABT_OK;
     hipStream_t s = (hipStream_t)stream;
     char* ws = (char*)workspace;
-    const int64_t M = conv_rows(g), M_in = g.N * g.H * g.W;     // output pixels (rows of dY, T, dT), input pixels
+    const int64_t M = conv_rows(g);     // output pixels (rows of dY, T, dT)
     const int taps = g.kh * g.kw;
     const int acc = accumulate ? 1 : 0;
     const PatchGeom fwd_geom = conv_patches_geom(g);
@@ -308,20 +430,8 @@ int lr_conv_bwd(const void* dY, const void* act, const void* T, const void* A, c
         if (chain(dY, ws + w.At, nullptr, nullptr, dT, M, (int)m, 64, (int)r, s) != hipSuccess) return ABT_EHIP;
     }
     if (dAct) {
-        // dAct[q, c] = sum over taps and j of dT[(q - shift(tap)) / stride, j] B[j, tap, c] (only where
-        // the division is exact): the same gathered product as the forward, on the image
-        // dT [N, H', W', r] with mirrored shifts, against the re-laid-out factor Pst [C, taps r_pad];
-        // rows are the input pixels; one launch per block of output channels
-        if (launch_conv_bstack_bf16(B, ws + w.Pst, (int)r, (int)g.C, taps, w.r_pad, s) != hipSuccess) return ABT_EHIP;
-        const PatchGeom adj = conv_adjoint_geom(g, (int)r);
-        const int chunk = conv_dact_chunk(g.C);
-        const int64_t pst_pitch = (int64_t)taps * w.r_pad;
-        for (int64_t c0 = 0; c0 < g.C; c0 += chunk) {
-            const char* Pc = ws + w.Pst + (size_t)c0 * pst_pitch * 2;
-            if (chain_gather(dT, adj, Pc, nullptr, nullptr, (char*)dAct + c0 * 2, (int)g.C, M_in, 64, chunk, s) !=
-                hipSuccess)
-                return ABT_EHIP;
-        }
+        const hipError_t e = conv_dact(dT, B, dAct, ws + w.Pst, g, (int)r, w.r_pad, s);
+        if (e != hipSuccess) return ABT_EHIP;
     }
     // factor gradients: dA = dY^T T (plain) and dB = patches(act)^T dT (gathered), one launch
     TnJob jobs[2];
@@ -559,6 +669,11 @@ hipError_t chain_grouped(const ChainProblem* pr, int G, int64_t M, int p, int q,
             if ((has2 && second) || (!has2 && !second && pr[g].Tout)) sel[n++] = pr[g];
         }
         if (n == 0) continue;
+        if (use_narrow(n * M, p, q, R)) {
+            const hipError_t e = launch_chain4_bf16(sel, n, M, p, q, R, narrow_rows(n * M), narrow_parts(n * ceil_div(M, narrow_rows(n * M)), p, q, second != 0), s);
+            if (e != hipSuccess) return e;
+            continue;
+        }
         const hipError_t e = launch_chain2_grouped_bf16(sel, n, M, p, q, R, chain_rows_for_groups(n, M, p, q, R), 1, s);
         if (e != hipSuccess) return e;
     }

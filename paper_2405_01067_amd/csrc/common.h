@@ -140,6 +140,18 @@ hipError_t launch_chain2_gather_bf16(const void* image, const PatchGeom& g, cons
                                      void* Yout, void* Tout, int t_pitch, int64_t M, int q, int R, hipStream_t s);
 hipError_t launch_chain2_tall_gather_bf16(const void* image, const PatchGeom& g, const void* P, const void* Q,
                                      void* Yout, void* Tout, int t_pitch, int64_t M, int q, int R, hipStream_t s);
+// The same chain for R <= 192 with work-groups of four waves and `rows` rows (a multiple of four, at most 128),
+// two or three per compute unit; p, q multiples of 64, at most 2^20.  With parts > 1 a row block is shared by that many work-groups, each
+// repeating stage 1 and doing its share of the 64-column output tiles (parts <= q / 64, second stage only).
+bool chain4_supports(int R, int p, int q);
+hipError_t launch_chain4_bf16(const ChainProblem* problems, int G, int64_t M, int p, int q, int R, int rows, int parts, hipStream_t s);
+// Its gathered form, up to kChainMaxGroups problems of one R and q in a launch.  As PatchGeom, but the
+// window may have any size and centre: tap (ky, kx) reads the image pixel sign (ky - cy, kx - cx) away from the
+// centre (mul y, mul x) of grid row (y, x); an image of height 0 reads as zeros everywhere.  Row (y, x) of
+// the result is pixel (omul y + oy, omul x + ox) of a grid OH x OW (omul = 2 without a second stage only).
+struct ChainGather { int H, W, Cin, cpb, kh, kw, sign, cy, cx, RH, RW, mul, omul, oy, ox, OH, OW; };   // cpb: set by the launcher
+struct GatherProblem { const void* image; const void* P; const void* Q; void* Yout; void* Tout; int64_t M; ChainGather g; };
+hipError_t launch_chain4_gather_bf16(const GatherProblem* problems, int n, int q, int R, int t_pitch, int rows, int parts, hipStream_t s);
 // dst[c, r] = src[r, c] for a bf16 matrix of `rows` x `cols`.
 struct TransposeJob { const void* src; void* dst; int rows, cols; };   // dst[cols, rows] = src[rows, cols]^T
 constexpr int kTransposeMaxJobs = 16;   // per launch
@@ -156,7 +168,12 @@ hipError_t launch_tn_bf16(const TnJob* jobs, int njobs, int64_t M, int R, int ac
                           float* partials, hipStream_t s);
 
 // Pst [C, taps r_pad] (bf16) from B [r, taps C]: Pst[c, tap r_pad + j] = B[j, tap C + c], zero for j >= r.
-hipError_t launch_conv_bstack_bf16(const void* B, void* Pst, int r, int C, int taps, int r_pad, hipStream_t s);
+// by_parity: four matrices end to end instead, one per parity (py, px) of the pixel in the order (0,0), (0,1),
+// (1,0), (1,1), each [C, taps of that parity r_pad] with the taps ky = py + kh/2 (mod 2), kx = px + kw/2 (mod 2).
+hipError_t launch_conv_bstack_bf16(const void* B, void* Pst, int r, int C, int kh, int kw, int r_pad, bool by_parity, hipStream_t s);
+// taps of one parity along one axis of a window of k taps (centre k / 2): first, first + 2, ..; count may be 0
+inline __host__ __device__ int parity_first(int k, int parity) { return (parity + k / 2) & 1; }
+inline __host__ __device__ int parity_count(int k, int parity) { const int f = parity_first(k, parity); return f < k ? (k - f + 1) / 2 : 0; }
 // One or two jobs; the U of the LAST one is the patch matrix of a channels-last image (g.sign is
 // ignored: always +1): column tap Cin + c of row i is channel c of pixel (y + ky - kh/2, x + kx - kw/2),
 // and its P = kh kw Cin.  A job before it is a plain one.  Partials as for launch_tn_bf16.

@@ -263,7 +263,8 @@ __global__ __launch_bounds__(256) void transpose_bf16_kernel(TrArgs args) {
 // (every tap padded to a multiple of 64 columns, the slab width of the chain kernel).  One thread
 // writes eight consecutive j (16 bytes).
 __global__ __launch_bounds__(256) void conv_bstack_kernel(const uint16_t* __restrict__ B, uint16_t* __restrict__ Pst,
-                                                          int r, int C, int taps, int r_pad) {
+                                                          int r, int C, int kh, int kw, int r_pad, int by_parity) {
+    const int taps = kh * kw;
     const int per_row = taps * (r_pad / 8);
     const int64_t idx = (int64_t)blockIdx.x * 256 + threadIdx.x;
     if (idx >= (int64_t)C * per_row) return;
@@ -274,16 +275,25 @@ __global__ __launch_bounds__(256) void conv_bstack_kernel(const uint16_t* __rest
     for (int i = 0; i < 8; ++i) v[i] = j0 + i < r ? B[(int64_t)(j0 + i) * taps * C + (int64_t)tap * C + c] : (uint16_t)0;
     u32x4 o = {(uint32_t)v[0] | ((uint32_t)v[1] << 16), (uint32_t)v[2] | ((uint32_t)v[3] << 16),
                (uint32_t)v[4] | ((uint32_t)v[5] << 16), (uint32_t)v[6] | ((uint32_t)v[7] << 16)};
-    *reinterpret_cast<u32x4*>(Pst + (int64_t)c * taps * r_pad + (int64_t)tap * r_pad + j0) = o;
+    int64_t dst = (int64_t)c * taps * r_pad + (int64_t)tap * r_pad;
+    if (by_parity) {
+        // the parity this tap belongs to, the taps of the parities before it, its place among its own
+        const int ky = tap / kw, kx = tap - ky * kw, py = (ky + kh / 2) & 1, px = (kx + kw / 2) & 1;
+        const int ny0 = parity_count(kh, 0), nx0 = parity_count(kw, 0), ny = py ? kh - ny0 : ny0, nx = px ? kw - nx0 : nx0;
+        const int before = (py ? ny0 * kw : 0) + (px ? ny * nx0 : 0);
+        const int place = ((ky - parity_first(kh, py)) >> 1) * nx + ((kx - parity_first(kw, px)) >> 1);
+        dst = ((int64_t)before * C + (int64_t)c * ny * nx + place) * r_pad;
+    }
+    *reinterpret_cast<u32x4*>(Pst + dst + j0) = o;
 }
 
 }  // namespace
 
-hipError_t launch_conv_bstack_bf16(const void* B, void* Pst, int r, int C, int taps, int r_pad, hipStream_t s) {
-    if (r < 1 || C < 1 || taps < 1 || r_pad % 64 || r_pad < r) return hipErrorInvalidValue;
-    const int64_t n = (int64_t)C * taps * (r_pad / 8);
+hipError_t launch_conv_bstack_bf16(const void* B, void* Pst, int r, int C, int kh, int kw, int r_pad, bool by_parity, hipStream_t s) {
+    if (r < 1 || C < 1 || kh < 1 || kw < 1 || r_pad % 64 || r_pad < r) return hipErrorInvalidValue;
+    const int64_t n = (int64_t)C * kh * kw * (r_pad / 8);
     hipLaunchKernelGGL(conv_bstack_kernel, dim3((unsigned)ceil_div(n, 256)), dim3(256), 0, s,
-                       (const uint16_t*)B, (uint16_t*)Pst, r, C, taps, r_pad);
+                       (const uint16_t*)B, (uint16_t*)Pst, r, C, kh, kw, r_pad, by_parity ? 1 : 0);
     return hipGetLastError();
 }
 

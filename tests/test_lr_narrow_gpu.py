@@ -1,0 +1,87 @@
+"""The narrow-rank chain kernel (r <= 192, several work-groups per compute unit) where its dispatch takes it:
+small batches whose row blocks are shared by output tiles, large ones with evenly shared rows, and the
+factored convolution, whose activation gradient is taken parity by parity with stride 2.
+
+Against the CPU oracle with the layer's tolerance (1e-2: bf16 storage, fp32 accumulation), and against the
+kernels for all ranks (forced by set_chain_rows): the same products summed in fp32 in another order and
+rounded to bf16 twice (T or dT, then the result), so two results differ by single roundings of a few entries:
+below 2^-8 = 4e-3 in norm."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import ab_oracle as orc
+from paper_2405_01067_amd import binding as abt
+from paper_2405_01067_amd import inputs as gen
+
+pytestmark = pytest.mark.gpu
+
+TOL, TOL_ORDER = 1e-2, 4e-3
+BF = torch.bfloat16
+
+
+def rel(a, b):
+    a = np.asarray(a, dtype=np.float64)
+    b = np.asarray(b, dtype=np.float64)
+    return float(np.linalg.norm(a - b) / max(np.linalg.norm(b), 1e-300))
+
+
+def dev(x):
+    return torch.from_numpy(np.ascontiguousarray(x)).to("cuda:0").to(BF)
+
+
+def host(t):
+    return t.detach().float().cpu().numpy().astype(np.float64)
+
+
+@pytest.mark.parametrize("M,m,n,r", [
+    (1, 64, 64, 32),            # one row, one slab, one output tile
+    (33, 448, 64, 96),          # one slab; seven tiles, shared by as many work-groups
+    (129, 192, 128, 64),        # ragged second row block
+    (700, 640, 320, 192),       # odd numbers of slabs and tiles at the widest rank
+    (8192, 128, 64, 128),       # the largest small batch
+    (32769, 64, 64, 96),        # the smallest large one: two work-groups per compute unit
+    (40001, 128, 192, 64),      # rows that do not divide evenly among the work-groups
+    (33333, 64, 128, 160),
+])
+def test_linear_step(M, m, n, r):
+    c = gen.lr_case(M=M, m=m, n=n, r=r, seed=M + m + n + r)
+    X, dY, A, B = (dev(c[k]) for k in ("X", "dY", "A", "B"))
+    Y, T = abt.lr_linear_fwd(X, A, B, save_T=True)
+    dX, dA, dB = abt.lr_linear_bwd(dY, X, T, A, B)
+    torch.cuda.synchronize()
+    Yo, To = orc.lr_linear_fwd(c["X"], c["A"], c["B"])
+    dXo, dAo, dBo, _ = orc.lr_linear_bwd(c["dY"], c["X"], c["A"], c["B"])
+    errs = {k: rel(host(a), b) for k, a, b in (("Y", Y, Yo), ("T", T, To), ("dX", dX, dXo), ("dA", dA, dAo), ("dB", dB, dBo))}
+    assert all(e < TOL for e in errs.values()), errs
+
+
+@pytest.mark.parametrize("N,H,W,C,m,r,kh,kw,stride", [
+    (2, 7, 9, 64, 64, 96, 3, 3, 2),       # odd sides: the parities have grids of different sizes
+    (3, 6, 5, 128, 64, 32, 1, 1, 2),      # 1 x 1: three parities without a tap
+    (2, 9, 6, 192, 64, 64, 5, 3, 2),      # 3 + 2 taps by 2 + 1
+    (1, 1, 11, 64, 64, 64, 7, 7, 2),      # height 1: two parities without a row
+    (5, 12, 12, 320, 64, 160, 3, 3, 1),   # channel blocks of 160
+    (3, 10, 10, 512, 64, 32, 3, 3, 2),    # four blocks of 128 channels x four parities: two launches
+    (86, 14, 14, 64, 192, 64, 3, 3, 1),   # more than 128 row blocks: the forward too
+])
+def test_convolution_agrees_with_the_kernels_for_all_ranks(N, H, W, C, m, r, kh, kw, stride):
+    c = gen.conv_case(N, H, W, C, m, r, kh, kw, seed=N + 10 * H + W + C + r, stride=stride)
+    act, dY, A, B = (dev(c[k]) for k in ("act", "dY", "A", "B"))
+
+    def step():
+        Y, T = abt.lr_conv_fwd(act, A, B, kh, kw, save_T=True, stride=stride)
+        out = (Y, T) + tuple(abt.lr_conv_bwd(dY, act, T, A, B, kh, kw, stride=stride))
+        torch.cuda.synchronize()
+        return out
+
+    got = step()
+    prev = abt.set_chain_rows(64)
+    try:
+        want = step()
+    finally:
+        abt.set_chain_rows(prev)
+    for name, a, b in zip(("Y", "T", "dAct", "dA", "dB"), got, want):
+        assert rel(host(a), host(b)) < TOL_ORDER, name
+    # pixels that no window reaches get exact zeros from both
+    assert torch.equal(got[2] == 0, want[2] == 0)
