@@ -26,7 +26,7 @@
  *         forked from and joined back into `stream` inside the call.  The stages they enqueue
  *         last (back-projection) may still be running when they return.  Not capturable in a
  *         HIP graph.
- *       ab_merge_info: waits for `stream`.
+ *       ab_merge_info, ab_merge_info_batched: wait for `stream`.
  *   - `workspace` is caller-owned device scratch of at least the size the matching
  *     *_workspace_bytes() query returns, 256-byte aligned; its contents are undefined
  *     afterwards.  Calls that share a workspace must be stream-ordered.
@@ -229,6 +229,9 @@ size_t ab_merge_batched_workspace_bytes(const abt_merge_desc* layers, int L);
  * of the last merge that ran on this workspace.  sweeps / n_sigma: HOST, may be NULL. */
 int ab_merge_info(const void* workspace, int layer, int32_t* sweeps, int32_t* n_sigma,
                   void* stream);
+/* The same for layers first .. first + count - 1 of the workspace in one read: sweeps and n_sigma are HOST arrays
+ * of `count` entries (either may be NULL); ABT_ENOCONV if any of them hit the cap. */
+int ab_merge_info_batched(const void* workspace, int first, int count, int32_t* sweeps, int32_t* n_sigma, void* stream);
 
 /* -------------------------------------------------------------------------------------
  * ab_factorize: Eq. 3 for a DENSE weight, the abDecomposition step of Algorithm 1 that opens

@@ -23,7 +23,7 @@ EXPORTS = (
     "lr_linear_bwd", "lr_linear_bwd_workspace_bytes", "lr_linear_bwd_static",
     "lr_linear_fwd_grouped", "lr_linear_bwd_grouped", "lr_linear_bwd_grouped_workspace_bytes",
     "ab_merge", "ab_merge_workspace_bytes",
-    "ab_merge_batched", "ab_merge_batched_workspace_bytes", "ab_merge_info",
+    "ab_merge_batched", "ab_merge_batched_workspace_bytes", "ab_merge_info", "ab_merge_info_batched",
     "ab_factorize", "ab_factorize_workspace_bytes",
     "ab_factorize_batched", "ab_factorize_batched_workspace_bytes",
     "ab_adamw_step", "ab_lr_rebound_scale", "ab_reconstruct",
@@ -134,6 +134,9 @@ def load():
     lib.ab_merge_batched_workspace_bytes.argtypes = [ctypes.POINTER(MergeDesc), ci]
     lib.ab_merge_info.restype = ci
     lib.ab_merge_info.argtypes = [vp, ci, ctypes.POINTER(ctypes.c_int32), ctypes.POINTER(ctypes.c_int32), vp]
+    pi32 = ctypes.POINTER(ctypes.c_int32)
+    lib.ab_merge_info_batched.restype = ci
+    lib.ab_merge_info_batched.argtypes = [vp, ci, ci, pi32, pi32, vp]
     lib.ab_factorize.restype = ci
     lib.ab_factorize.argtypes = [vp, i64, i64, ctypes.c_float, i64, vp, vp, vp, vp, i64, vp, sz, vp]
     lib.ab_factorize_workspace_bytes.restype = sz
@@ -563,9 +566,8 @@ def ab_merge_batched(layers: List[dict], workspace=None, check_converged: bool =
     for o in outs:
         o["workspace"] = ws
     if check_converged:
-        for i in range(L):
-            sweeps, nsig = merge_info(ws, i)
-            outs[i]["sweeps"] = sweeps
+        for o, sweeps in zip(outs, _sweeps_of_all(ws, L)):
+            o["sweeps"] = sweeps
     return outs
 
 
@@ -608,11 +610,11 @@ def ab_factorize_batched(layers: List[dict], workspace=None, check_converged: bo
     if workspace is None or workspace.numel() < need:
         workspace = torch.empty(need, dtype=torch.uint8, device=dev)
     _check(lib.ab_factorize_batched(descs, L, _ptr(workspace), workspace.numel(), _stream()), "ab_factorize_batched")
-    for i, o in enumerate(outs):
+    for o in outs:
         o["workspace"] = workspace
         o.pop("_W")
-        if check_converged:
-            merge_info(workspace, i)
+    if check_converged:
+        _sweeps_of_all(workspace, L)
     return outs
 
 
@@ -683,3 +685,10 @@ def merge_info(workspace, layer: int = 0):
     code = lib.ab_merge_info(_ptr(workspace), int(layer), ctypes.byref(sweeps), ctypes.byref(nsig), _stream())
     _check(code, "ab_merge_info")
     return sweeps.value, nsig.value
+
+
+def _sweeps_of_all(workspace, L: int):
+    """Sweeps of the L layers of a finished merge; raises if one of them hit the sweep cap."""
+    sweeps = (ctypes.c_int32 * L)()
+    _check(load().ab_merge_info_batched(_ptr(workspace), 0, L, sweeps, None, _stream()), "ab_merge_info")
+    return list(sweeps)

@@ -962,15 +962,25 @@ int ab_factorize(const float* W, int64_t m, int64_t n, float tau, int64_t k_fixe
     return ab_factorize_batched(&f, 1, workspace, workspace_bytes, stream);
 }
 
+int ab_merge_info_batched(const void* workspace, int first, int count, int32_t* sweeps, int32_t* n_sigma, void* stream) {
+    if (!workspace || first < 0 || count < 1) return ABT_EINVAL;
+    return guarded([&]() -> int {
+        std::vector<int32_t> info(4 * (size_t)count);
+        const hipError_t e = merge_read_info(workspace, first, count, info.data(), (hipStream_t)stream);
+        if (e == hipErrorInvalidValue) return ABT_EINVAL;       // not a merge workspace, or no such layers in it
+        if (e != hipSuccess) return ABT_EHIP;
+        bool converged = true;
+        for (int i = 0; i < count; ++i) {
+            if (sweeps) sweeps[i] = info[4 * i];
+            if (n_sigma) n_sigma[i] = info[4 * i + 1];
+            converged &= info[4 * i + 2] != 0;
+        }
+        return converged ? ABT_OK : ABT_ENOCONV;
+    });
+}
+
 int ab_merge_info(const void* workspace, int layer, int32_t* sweeps, int32_t* n_sigma, void* stream) {
-    if (!workspace || layer < 0) return ABT_EINVAL;
-    int32_t info[4] = {0, 0, 0, 0};
-    const hipError_t e = merge_read_info(workspace, layer, info, (hipStream_t)stream);
-    if (e == hipErrorInvalidValue) return ABT_EINVAL;       // not a merge workspace, or no such layer in it
-    if (e != hipSuccess) return ABT_EHIP;
-    if (sweeps) *sweeps = info[0];
-    if (n_sigma) *n_sigma = info[1];
-    return info[2] ? ABT_OK : ABT_ENOCONV;
+    return ab_merge_info_batched(workspace, layer, 1, sweeps, n_sigma, stream);
 }
 
 }  // extern "C"

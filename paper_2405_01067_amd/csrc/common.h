@@ -215,7 +215,8 @@ hipError_t launch_gemm_f32_table(const void* dev_image, const GemmF32Table& t, h
 // and enqueues every stage.
 size_t merge_workspace_bytes(const abt_merge_desc* layers, int L);
 hipError_t merge_run(const abt_merge_desc* layers, int L, void* workspace, int max_sweeps, hipStream_t s);
-hipError_t merge_read_info(const void* workspace, int layer, int32_t out[4], hipStream_t s);
+// (sweeps, values, converged, rank) of `count` layers; hipErrorInvalidValue: not a workspace of that many layers
+hipError_t merge_read_info(const void* workspace, int first, int count, int32_t* out, hipStream_t s);
 hipError_t launch_identity_f32(float* dst, int K, hipStream_t s);   // dst[K, K] = I
 // Stage timers of the batched merge: with the switch on, merge_run records events on the caller's
 // stream at its stage boundaries and merge_stage_ms waits for the last and returns the elapsed

@@ -19,6 +19,7 @@
 // Abar = [A_1 .. A_G] / G (m x Gk) and Bbar = [B_1; ..; B_G] (Gk x n).
 #include <algorithm>
 #include <atomic>
+#include <cstring>
 #include <mutex>
 #include <vector>
 
@@ -27,14 +28,6 @@
 namespace abt {
 
 namespace {
-
-// ------------------------------------------------------------------------------------------
-// zero-fill by a kernel (fill kernels, not memset nodes, are what stays correct under graph replay)
-// ------------------------------------------------------------------------------------------
-__global__ void fill_i32_kernel(int* p, int64_t n, int v) {
-    int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n) p[i] = v;
-}
 
 __global__ void identity_f32_kernel(float* p, int K) {
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -952,16 +945,21 @@ hipError_t launch_identity_f32(float* dst, int K, hipStream_t s) {
 
 constexpr int kWorkspaceMagic = 0x41425431;
 
-hipError_t merge_read_info(const void* workspace, int layer, int32_t out[4], hipStream_t s) {
+hipError_t merge_read_info(const void* workspace, int first, int count, int32_t* out, hipStream_t s) {
     hipError_t e = hipStreamSynchronize(s);
     if (e != hipSuccess) return e;
-    int hdr[4] = {0, 0, 0, 0};
-    e = hipMemcpy(hdr, workspace, sizeof(hdr), hipMemcpyDeviceToHost);
-    if (e != hipSuccess) return e;
-    if (hdr[0] != kWorkspaceMagic || layer < 0 || layer >= hdr[1]) return hipErrorInvalidValue;
     // the info table follows the 256-byte header slot (see make_plan)
-    return hipMemcpy(out, (const char*)workspace + 256 + sizeof(int) * kInfoInts * layer,
-                     sizeof(int) * kInfoInts, hipMemcpyDeviceToHost);
+    const size_t bytes = 256 + sizeof(int) * kInfoInts * ((size_t)first + count);
+    std::vector<char> image(bytes);
+    e = hipMemcpy(image.data(), workspace, 256, hipMemcpyDeviceToHost);
+    if (e != hipSuccess) return e;
+    int hdr[4];
+    memcpy(hdr, image.data(), sizeof(hdr));
+    if (hdr[0] != kWorkspaceMagic || hdr[1] - count < first) return hipErrorInvalidValue;
+    e = hipMemcpy(image.data() + 256, (const char*)workspace + 256, bytes - 256, hipMemcpyDeviceToHost);
+    if (e != hipSuccess) return e;
+    memcpy(out, image.data() + 256 + sizeof(int) * kInfoInts * first, sizeof(int) * kInfoInts * count);
+    return hipSuccess;
 }
 
 hipError_t merge_run(const abt_merge_desc* layers, int L, void* workspace, int max_sweeps, hipStream_t s) {
@@ -1052,21 +1050,23 @@ hipError_t merge_run(const abt_merge_desc* layers, int L, void* workspace, int m
         }
     }
 
-    // ---- upload the tables (pageable sources: staged by the runtime before each call returns)
+    // ---- upload the tables, which lie end to end at the start of the workspace, and the cleared convergence
+    // flags behind them in one copy (eight copies of a few KB each cost a small merge 50 us)
     hipError_t e;
 #define ABT_TRY(x) do { e = (x); if (e != hipSuccess) return e; } while (0)
+    std::vector<char> image(p.off_data, 0);
+    auto put = [&](size_t off, const void* src, size_t bytes) { if (bytes) memcpy(image.data() + off, src, bytes); };
     const int header[4] = {kWorkspaceMagic, L, 0, 0};
-    ABT_TRY(hipMemcpyAsync(ws + p.off_header, header, sizeof(header), hipMemcpyHostToDevice, s));
-    ABT_TRY(hipMemcpyAsync(ws + p.off_layers, hl.data(), sizeof(LayerDev) * L, hipMemcpyHostToDevice, s));
-    ABT_TRY(hipMemcpyAsync(ws + p.off_ptrs, hptrs.data(), sizeof(void*) * p.n_ptrs, hipMemcpyHostToDevice, s));
-    ABT_TRY(hipMemcpyAsync(ws + p.off_gram_tiles, gtiles.data(), sizeof(GramJob) * gtiles.size(), hipMemcpyHostToDevice, s));
-    ABT_TRY(hipMemcpyAsync(ws + p.off_wg_cross, wcross.data(), sizeof(int2) * wcross.size(), hipMemcpyHostToDevice, s));
-    ABT_TRY(hipMemcpyAsync(ws + p.off_wg_intra, wintra.data(), sizeof(int2) * wintra.size(), hipMemcpyHostToDevice, s));
-    ABT_TRY(hipMemcpyAsync(ws + p.off_gemm64, g64.data(), sizeof(GemmF64) * g64.size(), hipMemcpyHostToDevice, s));
-    std::vector<char> g32img(gemm_f32_desc_bytes() * (g32.empty() ? 1 : g32.size()));
-    const GemmF32Table table32 = gemm_f32_build_table(g32.data(), (int)g32.size(), g32img.data());
-    ABT_TRY(hipMemcpyAsync(ws + p.off_gemm32, g32img.data(), gemm_f32_desc_bytes() * g32.size(), hipMemcpyHostToDevice, s));
-    // the uploads must have left the host vectors before they are destroyed
+    put(p.off_header, header, sizeof(header));
+    put(p.off_layers, hl.data(), sizeof(LayerDev) * L);
+    put(p.off_ptrs, hptrs.data(), sizeof(void*) * p.n_ptrs);
+    put(p.off_gram_tiles, gtiles.data(), sizeof(GramJob) * gtiles.size());
+    put(p.off_wg_cross, wcross.data(), sizeof(int2) * wcross.size());
+    put(p.off_wg_intra, wintra.data(), sizeof(int2) * wintra.size());
+    put(p.off_gemm64, g64.data(), sizeof(GemmF64) * g64.size());
+    const GemmF32Table table32 = gemm_f32_build_table(g32.data(), (int)g32.size(), image.data() + p.off_gemm32);
+    ABT_TRY(hipMemcpyAsync(ws, image.data(), image.size(), hipMemcpyHostToDevice, s));
+    // the upload must have left the host image before it is destroyed
     ABT_TRY(hipStreamSynchronize(s));
 
     std::unique_lock<std::mutex> stage_lock(g_stage_mutex, std::defer_lock);
@@ -1084,11 +1084,6 @@ hipError_t merge_run(const abt_merge_desc* layers, int L, void* workspace, int m
     };
     const LayerDev* dl = (const LayerDev*)(ws + p.off_layers);
     ABT_TRY(mark(0));
-    {
-        const int64_t n = (int64_t)(kMaxSweepsCap + 1) * L;
-        hipLaunchKernelGGL(fill_i32_kernel, dim3((unsigned)ceil_div(n, 256)), dim3(256), 0, s,
-                           (int*)(ws + p.off_rotated), n, 0);
-    }
     ABT_TRY(launch_mean_gram(dl, (const GramJob*)(ws + p.off_gram_tiles), gram_aligned, p.n_gram_tiles - gram_aligned, s));
     ABT_TRY(mark(1));
     if (p.K_max <= kCholMaxK) {
