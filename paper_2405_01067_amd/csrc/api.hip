@@ -844,7 +844,7 @@ int ab_merge_batched(const abt_merge_desc* layers, int L, void* workspace, size_
     return guarded([&]() -> int {
         if (!workspace || workspace_bytes < merge_workspace_bytes(layers, L)) return ABT_EWORKSPACE;
         if (!aligned(workspace, 256)) return ABT_EALIGN;
-        return merge_run(layers, L, workspace, g_max_sweeps, (hipStream_t)stream) == hipSuccess ? ABT_OK : ABT_EHIP;
+        return merge_run(layers, nullptr, L, workspace, g_max_sweeps, (hipStream_t)stream) == hipSuccess ? ABT_OK : ABT_EHIP;
     });
 }
 
@@ -930,9 +930,11 @@ int ab_factorize_batched(const abt_factorize_desc* layers, int L, void* workspac
     if (!aligned(workspace, 256)) return ABT_EALIGN;
     // one pointer pair per layer: (W, I) or (I, W); the arrays are read before merge_run returns
     std::vector<const float*> a_ptr(L), b_ptr(L);
+    std::vector<MergeSide> identity(L);
     for (int l = 0; l < L; ++l) {
         const float* eye = (const float*)((const char*)workspace + p.eye_off[p.eye_of_layer[l]]);
         const bool tall = layers[l].n <= layers[l].m;
+        identity[l] = tall ? MergeSide::B : MergeSide::A;
         a_ptr[l] = tall ? layers[l].W : eye;
         b_ptr[l] = tall ? eye : layers[l].W;
         p.merge[l].A_copies = &a_ptr[l];
@@ -943,7 +945,7 @@ int ab_factorize_batched(const abt_factorize_desc* layers, int L, void* workspac
     for (size_t i = 0; i < p.Ks.size(); ++i)
         if (launch_identity_f32((float*)((char*)workspace + p.eye_off[i]), (int)p.Ks[i], (hipStream_t)stream) != hipSuccess)
             return ABT_EHIP;
-    return merge_run(p.merge.data(), L, workspace, g_max_sweeps, (hipStream_t)stream) == hipSuccess ? ABT_OK : ABT_EHIP;
+    return merge_run(p.merge.data(), identity.data(), L, workspace, g_max_sweeps, (hipStream_t)stream) == hipSuccess ? ABT_OK : ABT_EHIP;
     });
 }
 

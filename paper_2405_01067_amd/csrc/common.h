@@ -214,7 +214,9 @@ hipError_t launch_gemm_f32_table(const void* dev_image, const GemmF32Table& t, h
 // Host-side plan of a batched merge: validates nothing (api.hip does), lays out the workspace
 // and enqueues every stage.
 size_t merge_workspace_bytes(const abt_merge_desc* layers, int L);
-hipError_t merge_run(const abt_merge_desc* layers, int L, void* workspace, int max_sweeps, hipStream_t s);
+// identity: per layer the side whose (only) copy is the K x K identity, i.e. the layer is a dense weight; NULL: none
+enum class MergeSide : uint8_t { none, A, B };
+hipError_t merge_run(const abt_merge_desc* layers, const MergeSide* identity, int L, void* workspace, int max_sweeps, hipStream_t s);
 // (sweeps, values, converged, rank) of `count` layers; hipErrorInvalidValue: not a workspace of that many layers
 hipError_t merge_read_info(const void* workspace, int first, int count, int32_t* out, hipStream_t s);
 hipError_t launch_identity_f32(float* dst, int K, hipStream_t s);   // dst[K, K] = I

@@ -35,141 +35,191 @@ __global__ void identity_f32_kernel(float* p, int K) {
 }
 
 // ------------------------------------------------------------------------------------------
-// Stage 3: Cholesky G = L L^T in place (lower triangle; the strict upper triangle is zeroed),
-// blocked left-looking, one work-group per matrix.  Positive SEMI-definite input is allowed:
-// a pivot that drops below 1e-14 * max diag(G) marks a direction already spanned by earlier
-// columns; its column of L is set to zero (L L^T = G still holds to that accuracy).
+// Stage 3: Cholesky G = L L^T in place (lower triangle; the strict upper triangle is zeroed) of a
+// list of matrices.  Positive SEMI-definite input is allowed: a pivot that drops below
+// 1e-14 * max diag(G) marks a direction already spanned by earlier columns; its column of L is set to
+// zero (L L^T = G still holds to that accuracy).
 // ------------------------------------------------------------------------------------------
-__global__ __launch_bounds__(256) void cholesky_kernel(const LayerDev* __restrict__ layers) {
-    __shared__ double Ljj[32][33];
-    __shared__ double Lrow[32][33];
-    __shared__ double red[256];
-    const LayerDev& L = layers[blockIdx.x >> 1];
-    double* Gm = (blockIdx.x & 1) ? L.LB : L.LA;
-    const int K = L.K;
-    const int t = threadIdx.x;
+struct CholMat {
+    double* G;
+    double* scratch;      // blocked form: K x 32 (the factored diagonal blocks), then the pivot floor
+    int K;
+};
 
-    double mx = 0.0, tr = 0.0;
-    for (int i = t; i < K; i += 256) { const double d = Gm[(int64_t)i * K + i]; mx = fmax(mx, d); tr += d; }
+__device__ __forceinline__ double lane_value(double v, int src) {
+    const int lo = __builtin_amdgcn_readlane(__double2loint(v), src);
+    const int hi = __builtin_amdgcn_readlane(__double2hiint(v), src);
+    return __hiloint2double(hi, lo);
+}
+
+// Factor a 32 x 32 block in one wave: lane r (and r + 32) holds row r; step c takes the pivot and the
+// finished column c from the other lanes with lane reads (no LDS, no waits).  keep(c, 1 / pivot or 0).
+template <class F>
+__device__ __forceinline__ void factor_diagonal_block(double (&row)[32], int r, double floor_piv, F&& keep) {
+#pragma unroll
+    for (int c = 0; c < 32; ++c) {
+        const double d = lane_value(row[c], c);
+        const bool ok = d > floor_piv;
+        // 1 / sqrt(d): hardware estimate and two Newton steps (a square root and a division in
+        // fp64 would be several times the rest of the step); the pivot itself is d / sqrt(d)
+        const double dd = ok ? d : 1.0;
+        double y = __builtin_amdgcn_rsq(dd);
+        y = y * fma(-0.5 * dd, y * y, 1.5);
+        y = y * fma(-0.5 * dd, y * y, 1.5);
+        const double ip = ok ? y : 0.0;
+        const double piv = ok ? dd * y : 0.0;
+        const double v = (r == c) ? piv : (r > c ? row[c] * ip : 0.0);
+        row[c] = v;
+        keep(c, ip);
+#pragma unroll
+        for (int cc = c + 1; cc < 32; ++cc) row[cc] = fma(-v, lane_value(v, cc), row[cc]);
+    }
+}
+
+// ---- blocked form over several launches (K > kCholSmallK): per block column of 32 one launch that factors the
+// diagonal block and solves the rows below, 64 rows per wave, and one that updates the trailing matrix, 64 x 64
+// tiles on the fp64 matrix cores; a last one zeroes the upper triangle.  A single work-group per matrix walks
+// through the same steps with nobody to share the trailing update: 16 matrices with K = 768 took 4.7 ms that way.
+__global__ __launch_bounds__(256) void chol_begin_kernel(const CholMat* __restrict__ mats) {
+    __shared__ double red[256];
+    const CholMat m = mats[blockIdx.x];
+    const int t = threadIdx.x;
+    double mx = 0.0;
+    for (int i = t; i < m.K; i += 256) mx = fmax(mx, gload(m.G + (int64_t)i * m.K + i));
     red[t] = mx;
     __syncthreads();
     for (int s = 128; s > 0; s >>= 1) {
         if (t < s) red[t] = fmax(red[t], red[t + s]);
         __syncthreads();
     }
-    const double floor_piv = red[0] * 1e-14;
-    __syncthreads();
-    red[t] = tr;
-    __syncthreads();
-    for (int s = 128; s > 0; s >>= 1) {
-        if (t < s) red[t] += red[t + s];
-        __syncthreads();
-    }
-    if (t == 0) L.trace[blockIdx.x & 1] = red[0];
-    __syncthreads();
+    if (t == 0) m.scratch[m.K * 32] = red[0] * 1e-14;
+}
 
-    for (int j0 = 0; j0 < K; j0 += 32) {
-        // (a) panel update: rows i >= j0, columns j0..j0+31, subtract the contribution of columns < j0
-        for (int ibase = j0; ibase < K; ibase += 256) {
-            const int i = ibase + t;
-            double acc[32];
-            if (i < K) {
+__global__ __launch_bounds__(64) void chol_panel_kernel(const CholMat* __restrict__ mats, int j0) {
+    __shared__ double Ljj[32][33];
+    __shared__ double invp[32];
+    const CholMat m = mats[blockIdx.y];
+    const int K = m.K, lane = threadIdx.x, r = lane & 31;
+    const int i = j0 + 32 + 64 * (int)blockIdx.x + lane;         // this lane's row below the diagonal block
+    if (j0 >= K || (blockIdx.x > 0 && i - lane >= K)) return;    // the first work-group also keeps the diagonal block
+    double row[32], x[32];
+    const f64x2* src = reinterpret_cast<const f64x2*>(m.G + (int64_t)(j0 + r) * K + j0);
 #pragma unroll
-                for (int c = 0; c < 32; ++c) acc[c] = Gm[(int64_t)i * K + j0 + c];
-            }
-            for (int t0 = 0; t0 < j0; t0 += 32) {
-                __syncthreads();
-                for (int e = t; e < 32 * 32; e += 256) Lrow[e >> 5][e & 31] = Gm[(int64_t)(j0 + (e >> 5)) * K + t0 + (e & 31)];
-                __syncthreads();
-                if (i < K) {
-                    for (int tt = 0; tt < 32; ++tt) {
-                        const double li = Gm[(int64_t)i * K + t0 + tt];
+    for (int c = 0; c < 16; ++c) { const f64x2 v = gload(src + c); row[2 * c] = v[0]; row[2 * c + 1] = v[1]; }
+    const f64x2* xsrc = reinterpret_cast<const f64x2*>(m.G + (int64_t)(i < K ? i : K - 1) * K + j0);
 #pragma unroll
-                        for (int c = 0; c < 32; ++c) acc[c] = fma(-li, Lrow[c][tt], acc[c]);
-                    }
-                }
-            }
-            if (i < K) {
+    for (int c = 0; c < 16; ++c) { const f64x2 v = gload(xsrc + c); x[2 * c] = v[0]; x[2 * c + 1] = v[1]; }
+    factor_diagonal_block(row, r, gload(m.scratch + K * 32), [&](int c, double ip) { if (lane == c) invp[c] = ip; });
+    if (lane < 32) {
 #pragma unroll
-                for (int c = 0; c < 32; ++c) Gm[(int64_t)i * K + j0 + c] = acc[c];
-            }
+        for (int c = 0; c < 32; ++c) Ljj[r][c] = row[c];
+        if (blockIdx.x == 0) {
+            // not into G: the other work-groups of this matrix read the unfactored block
+#pragma unroll
+            for (int c = 0; c < 32; ++c) gstore(m.scratch + (j0 + r) * 32 + c, row[c]);
         }
-        __threadfence_block();
-        __syncthreads();
-        // (b) factor the 32 x 32 diagonal block in LDS
-        for (int e = t; e < 32 * 32; e += 256) Ljj[e >> 5][e & 31] = Gm[(int64_t)(j0 + (e >> 5)) * K + j0 + (e & 31)];
-        __syncthreads();
-        if (t < 64) {
-            const int r = t & 31;  // lanes 0..31 work, 32..63 idle (one wave keeps the steps in lockstep)
-            for (int c = 0; c < 32; ++c) {
-                const double d = Ljj[c][c];
-                const bool ok = d > floor_piv;
-                const double piv = ok ? sqrt(d) : 0.0;
-                double v = 0.0;
-                if (t < 32 && r >= c) v = (r == c) ? piv : (ok ? Ljj[r][c] / piv : 0.0);
-                // one wave in lockstep: the fences only pin the order of the LDS accesses
-                __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
-                __builtin_amdgcn_wave_barrier();
-                if (t < 32 && r >= c) Ljj[r][c] = v;
-                __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
-                __builtin_amdgcn_wave_barrier();
-                if (t < 32 && r > c) {
-                    for (int cc = c + 1; cc <= r; ++cc) Ljj[r][cc] -= v * Ljj[cc][c];
-                }
-                __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
-                __builtin_amdgcn_wave_barrier();
-            }
-        }
-        __syncthreads();
-        // (c) write the diagonal block back (upper part zero) and solve the rows below
-        for (int e = t; e < 32 * 32; e += 256) {
-            const int r = e >> 5, c = e & 31;
-            Gm[(int64_t)(j0 + r) * K + j0 + c] = (c <= r) ? Ljj[r][c] : 0.0;
-        }
-        for (int i = j0 + 32 + t; i < K; i += 256) {
-            double x[32];
+    }
+    __syncthreads();
+    // x = row L_jj^(-T), column by column so that the updates of a step are independent
 #pragma unroll
-            for (int c = 0; c < 32; ++c) x[c] = Gm[(int64_t)i * K + j0 + c];
+    for (int c = 0; c < 32; ++c) {
+        x[c] *= invp[c];
 #pragma unroll
-            for (int c = 0; c < 32; ++c) {
-                double v = x[c];
+        for (int c2 = c + 1; c2 < 32; ++c2) x[c2] = fma(-x[c], Ljj[c2][c], x[c2]);
+    }
+    if (i < K) {
+        f64x2* dst = reinterpret_cast<f64x2*>(m.G + (int64_t)i * K + j0);
 #pragma unroll
-                for (int d = 0; d < c; ++d) v = fma(-x[d], Ljj[c][d], v);
-                const double piv = Ljj[c][c];
-                x[c] = piv > 0.0 ? v / piv : 0.0;
-            }
-#pragma unroll
-            for (int c = 0; c < 32; ++c) Gm[(int64_t)i * K + j0 + c] = x[c];
-        }
-        // zero the strict upper triangle right of this block row
-        for (int e = t; e < 32 * (K - j0 - 32); e += 256) {
-            const int r = e / (K - j0 - 32), c = e % (K - j0 - 32);
-            Gm[(int64_t)(j0 + r) * K + j0 + 32 + c] = 0.0;
-        }
-        __threadfence_block();
-        __syncthreads();
+        for (int c = 0; c < 16; ++c) gstore(dst + c, f64x2{x[2 * c], x[2 * c + 1]});
     }
 }
 
+// trailing matrix -= X X^T, X = the solved rows: lower-triangle tiles of 64 x 64, a 32 x 32 part per wave
+__global__ __launch_bounds__(256) void chol_update_kernel(const CholMat* __restrict__ mats, int j0) {
+    const CholMat m = mats[blockIdx.y];
+    const int K = m.K, first = j0 + 32;
+    int ti = (int)((sqrtf(8.0f * (float)blockIdx.x + 1.0f) - 1.0f) * 0.5f);
+    while ((ti + 1) * (ti + 2) / 2 <= (int)blockIdx.x) ++ti;
+    while (ti * (ti + 1) / 2 > (int)blockIdx.x) --ti;
+    const int tj = (int)blockIdx.x - ti * (ti + 1) / 2;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, n = lane & 15, kq = lane >> 4;
+    const int i0 = first + 64 * ti + 32 * (wave >> 1), c0 = first + 64 * tj + 32 * (wave & 1);
+    if (i0 >= K || c0 > i0) return;                              // K is a multiple of 32: parts are whole
+    // operands of v_mfma_f64_16x16x4: lane l holds X[16 a + l % 16][l / 16 + 4 s]; accumulator register v is
+    // C[l / 16 + 4 v][l % 16]
+    double xa[2][8], xb[2][8];
+    f64x4 acc[2][2];
+#pragma unroll
+    for (int a = 0; a < 2; ++a)
+#pragma unroll
+        for (int s = 0; s < 8; ++s) {
+            xa[a][s] = gload(m.G + (int64_t)(i0 + 16 * a + n) * K + j0 + 4 * s + kq);
+            xb[a][s] = gload(m.G + (int64_t)(c0 + 16 * a + n) * K + j0 + 4 * s + kq);
+        }
+#pragma unroll
+    for (int a = 0; a < 2; ++a)
+#pragma unroll
+        for (int b = 0; b < 2; ++b)
+#pragma unroll
+            for (int v = 0; v < 4; ++v) acc[a][b][v] = gload(m.G + (int64_t)(i0 + 16 * a + kq + 4 * v) * K + c0 + 16 * b + n);
+#pragma unroll
+    for (int s = 0; s < 8; ++s)
+#pragma unroll
+        for (int a = 0; a < 2; ++a)
+#pragma unroll
+            for (int b = 0; b < 2; ++b) acc[a][b] = __builtin_amdgcn_mfma_f64_16x16x4f64(-xa[a][s], xb[b][s], acc[a][b], 0, 0, 0);
+#pragma unroll
+    for (int a = 0; a < 2; ++a)
+#pragma unroll
+        for (int b = 0; b < 2; ++b)
+#pragma unroll
+            for (int v = 0; v < 4; ++v) gstore(m.G + (int64_t)(i0 + 16 * a + kq + 4 * v) * K + c0 + 16 * b + n, acc[a][b][v]);
+}
+
+__global__ __launch_bounds__(256) void chol_finish_kernel(const CholMat* __restrict__ mats) {
+    const CholMat m = mats[blockIdx.y];
+    const int i = blockIdx.x;
+    if (i >= m.K) return;
+    for (int j = threadIdx.x; j < m.K; j += 256) {
+        if (j > i) gstore(m.G + (int64_t)i * m.K + j, 0.0);
+        else if (j >> 5 == i >> 5) gstore(m.G + (int64_t)i * m.K + j, gload(m.scratch + i * 32 + (j & 31)));
+    }
+}
+
+// Ct = L^T (32 x 32 tiles): the columns of a lower triangle as the rows that the Jacobi iteration works on
+struct TriPair { const double* L; double* Ct; int K; };
+__global__ __launch_bounds__(256) void lower_to_columns_kernel(const TriPair* __restrict__ pairs) {
+    __shared__ double tile[32][33];
+    const TriPair p = pairs[blockIdx.z];
+    const int i0 = 32 * blockIdx.x, j0 = 32 * blockIdx.y, c = threadIdx.x & 31, r0 = threadIdx.x >> 5;
+    if (i0 >= p.K || j0 >= p.K) return;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) tile[r0 + 8 * e][c] = gload(p.L + (int64_t)(i0 + r0 + 8 * e) * p.K + j0 + c);
+    __syncthreads();
+#pragma unroll
+    for (int e = 0; e < 4; ++e) gstore(p.Ct + (int64_t)(j0 + r0 + 8 * e) * p.K + i0 + c, tile[c][r0 + 8 * e]);
+}
+
 // ------------------------------------------------------------------------------------------
-// Stage 3 for K <= kCholMaxK: the same factorisation, right-looking, with the panel in LDS and the
-// trailing update on the fp64 matrix cores.  One work-group per matrix.  Per block column j0:
+// The same factorisation of small matrices in one launch, one work-group per matrix (K <= kCholSmallK): right-looking,
+// with the panel in LDS and the trailing update on the fp64 matrix cores.  Per block column j0:
 //   load the 32 x 32 diagonal block and the (K - j0 - 32) x 32 panel below it into LDS,
 //   factor the diagonal block (one wave, 32 dependent steps), X = panel L_jj^(-T) (a thread per row),
 //   write L's block column, and subtract X X^T from the lower triangle of the trailing matrix:
 //   16 x 16 tiles, C tile from / to memory (L2), operands of v_mfma_f64_16x16x4 from the LDS panel.
 // ------------------------------------------------------------------------------------------
 constexpr int kCholMaxK = 544;     // (K - 32) x 34 doubles of panel: 136 KB
+constexpr int kCholSmallK = 128;
 constexpr int kCholPitch = 34;     // doubles per panel row: 16 rows x 2 column groups of an operand read cover all banks
 
 constexpr int kCholThreads = 256;  // (512 threads measured the same: the serial diagonal-block and row-solve phases dominate)
 
-__global__ __launch_bounds__(kCholThreads) void cholesky_mfma_kernel(const LayerDev* __restrict__ layers) {
+__global__ __launch_bounds__(kCholThreads) void cholesky_mfma_kernel(const CholMat* __restrict__ mats) {
     constexpr int NT = kCholThreads;
     extern __shared__ __align__(16) unsigned char lds_raw[];
-    const LayerDev& L = layers[blockIdx.x >> 1];
-    double* Gm = (blockIdx.x & 1) ? L.LB : L.LA;
-    const int K = L.K;
+    const CholMat m = mats[blockIdx.x];
+    double* Gm = m.G;
+    const int K = m.K;
     if (K > kCholMaxK) return;
     double* Xp = reinterpret_cast<double*>(lds_raw);                 // [K - 32][kCholPitch]
     double (*Ljj)[33] = reinterpret_cast<double (*)[33]>(Xp + (size_t)(K > 32 ? K - 32 : 0) * kCholPitch);
@@ -177,8 +227,8 @@ __global__ __launch_bounds__(kCholThreads) void cholesky_mfma_kernel(const Layer
     double* red = invp + 32;                                         // [NT]
     const int t = threadIdx.x, lane = t & 63, wave = t >> 6, n = lane & 15, kq = lane >> 4;
 
-    double mx = 0.0, tr = 0.0;
-    for (int i = t; i < K; i += NT) { const double d = gload(Gm + (int64_t)i * K + i); mx = fmax(mx, d); tr += d; }
+    double mx = 0.0;
+    for (int i = t; i < K; i += NT) mx = fmax(mx, gload(Gm + (int64_t)i * K + i));
     red[t] = mx;
     __syncthreads();
     for (int s = NT / 2; s > 0; s >>= 1) {
@@ -186,14 +236,6 @@ __global__ __launch_bounds__(kCholThreads) void cholesky_mfma_kernel(const Layer
         __syncthreads();
     }
     const double floor_piv = red[0] * 1e-14;
-    __syncthreads();
-    red[t] = tr;
-    __syncthreads();
-    for (int s = NT / 2; s > 0; s >>= 1) {
-        if (t < s) red[t] += red[t + s];
-        __syncthreads();
-    }
-    if (t == 0) L.trace[blockIdx.x & 1] = red[0];
     __syncthreads();
 
     for (int j0 = 0; j0 < K; j0 += 32) {
@@ -224,29 +266,7 @@ __global__ __launch_bounds__(kCholThreads) void cholesky_mfma_kernel(const Layer
             double row[32];
 #pragma unroll
             for (int c = 0; c < 32; ++c) row[c] = Ljj[r][c];
-            auto lane_value = [](double v, int src) {
-                const int lo = __builtin_amdgcn_readlane(__double2loint(v), src);
-                const int hi = __builtin_amdgcn_readlane(__double2hiint(v), src);
-                return __hiloint2double(hi, lo);
-            };
-#pragma unroll
-            for (int c = 0; c < 32; ++c) {
-                const double d = lane_value(row[c], c);
-                const bool ok = d > floor_piv;
-                // 1 / sqrt(d): hardware estimate and two Newton steps (a square root and a division in
-                // fp64 would be several times the rest of the step); the pivot itself is d / sqrt(d)
-                const double dd = ok ? d : 1.0;
-                double y = __builtin_amdgcn_rsq(dd);
-                y = y * fma(-0.5 * dd, y * y, 1.5);
-                y = y * fma(-0.5 * dd, y * y, 1.5);
-                const double ip = ok ? y : 0.0;
-                const double piv = ok ? dd * y : 0.0;
-                const double v = (r == c) ? piv : (r > c ? row[c] * ip : 0.0);
-                row[c] = v;
-                if (lane == c) invp[c] = ip;
-#pragma unroll
-                for (int cc = c + 1; cc < 32; ++cc) row[cc] = fma(-v, lane_value(v, cc), row[cc]);
-            }
+            factor_diagonal_block(row, r, floor_piv, [&](int c, double ip) { if (lane == c) invp[c] = ip; });
             if (lane < 32) {
 #pragma unroll
                 for (int c = 0; c < 32; ++c) Ljj[r][c] = row[c];
@@ -326,6 +346,30 @@ __global__ __launch_bounds__(kCholThreads) void cholesky_mfma_kernel(const Layer
     }
 }
 
+hipError_t launch_cholesky(const CholMat* mats, int n, int K_max, hipStream_t s) {
+    if (n < 1) return hipSuccess;
+    if (K_max <= kCholSmallK) {
+        const size_t lds = sizeof(double) * ((size_t)(K_max > 32 ? K_max - 32 : 0) * kCholPitch + 32 * 33 + 32 + kCholThreads);
+        static std::atomic<size_t> attr{0};
+        if (lds > attr.load()) {
+            const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&cholesky_mfma_kernel),
+                                                     hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+            if (e != hipSuccess) return e;
+            attr.store(lds);
+        }
+        hipLaunchKernelGGL(cholesky_mfma_kernel, dim3(n), dim3(kCholThreads), lds, s, mats);
+        return hipGetLastError();
+    }
+    hipLaunchKernelGGL(chol_begin_kernel, dim3(n), dim3(256), 0, s, mats);
+    for (int j0 = 0; j0 < K_max; j0 += 32) {
+        const int below = K_max - j0 - 32, t = (below + 63) / 64;
+        hipLaunchKernelGGL(chol_panel_kernel, dim3(t > 0 ? t : 1, n), dim3(64), 0, s, mats, j0);
+        if (t > 0) hipLaunchKernelGGL(chol_update_kernel, dim3(t * (t + 1) / 2, n), dim3(256), 0, s, mats, j0);
+    }
+    hipLaunchKernelGGL(chol_finish_kernel, dim3(K_max, n), dim3(256), 0, s, mats);
+    return hipGetLastError();
+}
+
 // ------------------------------------------------------------------------------------------
 // fp64 GEMM for the K x K stages (grouped):  C = op(A) . op(B) with optional row gather on
 // op(A), per-row / per-column scaling, fp64 and/or fp32 output.
@@ -341,6 +385,7 @@ struct GemmF64 {
     const int* row_gather;            // op(A) row i is read at row row_gather[i] (transA == 0 only)
     const double* row_scale32;        // C32[i][j] = row_scale32[i] * acc (NULL = 1)
     const double* col_scale32;        // C32[i][j] *= col_scale32[j]      (NULL = 1)
+    int trans32;                      // C32 is stored transposed: C32[j][i]
     const int32_t* limit; int limit_rows;  // tiles at or beyond *limit produce zeros
     int tile_begin, tiles_q;
 };
@@ -462,7 +507,7 @@ __global__ __launch_bounds__(256) void gemm_f64_kernel(const GemmF64* __restrict
                         double val = val0;
                         if (d.row_scale32) val *= d.row_scale32[i];
                         if (d.col_scale32) val *= d.col_scale32[j];
-                        d.C32[(int64_t)i * d.ldc32 + j] = (float)val;
+                        d.C32[d.trans32 ? (int64_t)j * d.ldc32 + i : (int64_t)i * d.ldc32 + j] = (float)val;
                     }
                 }
             }
@@ -706,13 +751,13 @@ __global__ __launch_bounds__(256) void finalize_kernel(const LayerDev* __restric
 struct Plan {
     int L = 0;
     size_t off_header = 0, off_info = 0, off_layers = 0, off_ptrs = 0, off_gram_tiles = 0, off_wg_cross = 0,
-           off_wg_intra = 0, off_gemm64 = 0, off_gemm32 = 0, off_rotated = 0, off_data = 0, total = 0;
+           off_wg_intra = 0, off_gemm64 = 0, off_chol = 0, off_pairs = 0, off_gemm32 = 0, off_rotated = 0, off_data = 0, total = 0;
     int n_gram_tiles = 0, n_wg_cross = 0, n_wg_intra = 0, n_gemm64 = 0, n_gemm32 = 0, n_ptrs = 0;
     int nb_max = 0, K_max = 0, jb_max = 0;
     size_t lds_jacobi = 0;  // largest jb * K * 8 over the layers
     struct PerLayer {
         int K, jb, nb;
-        size_t Abar, Bbar, LA, GB, LB, Ct, Yt, sigma, s3, s5, trace, nrm, perm, PA, PB;
+        size_t Abar, Bbar, LA, GB, LB, Ct, Yt, sigma, s3, s5, trace, nrm, perm, PA, PB, chol;
     };
     std::vector<PerLayer> pl;
 };
@@ -799,6 +844,8 @@ Plan make_plan(const abt_merge_desc* layers, int L) {
     p.off_wg_intra = take(sizeof(int2) * p.n_wg_intra);
     p.off_gemm64 = take(sizeof(GemmF64) * p.n_gemm64 * 3);   // three fp64 stages, staged up front
     p.off_gemm32 = take(gemm_f32_desc_bytes() * p.n_gemm32);
+    p.off_chol = take(sizeof(CholMat) * 3 * L);              // the Gram matrices of both sides, then the cores of dense layers
+    p.off_pairs = take(sizeof(TriPair) * L);
     p.off_rotated = take(sizeof(int) * (kMaxSweepsCap + 1) * L);
     p.off_data = off;
     for (int l = 0; l < L; ++l) {
@@ -820,6 +867,7 @@ Plan make_plan(const abt_merge_desc* layers, int L) {
         q.perm = take(sizeof(int) * K);
         q.PA = take(sizeof(float) * K * kc);
         q.PB = take(sizeof(float) * kc * K);
+        q.chol = take(sizeof(double) * 2 * (32 * K + 2));
     }
     p.total = off;
     return p;
@@ -962,7 +1010,7 @@ hipError_t merge_read_info(const void* workspace, int first, int count, int32_t*
     return hipSuccess;
 }
 
-hipError_t merge_run(const abt_merge_desc* layers, int L, void* workspace, int max_sweeps, hipStream_t s) {
+hipError_t merge_run(const abt_merge_desc* layers, const MergeSide* identity, int L, void* workspace, int max_sweeps, hipStream_t s) {
     const Plan p = make_plan(layers, L);
     char* ws = (char*)workspace;
     if (max_sweeps > kMaxSweepsCap) max_sweeps = kMaxSweepsCap;
@@ -977,6 +1025,10 @@ hipError_t merge_run(const abt_merge_desc* layers, int L, void* workspace, int m
     std::vector<int2> wintra; wintra.reserve(p.n_wg_intra);
     std::vector<GemmF64> g64(p.n_gemm64 * 3);
     std::vector<GemmF32> g32; g32.reserve(p.n_gemm32);
+    std::vector<CholMat> chol; chol.reserve(3 * (size_t)L);          // first the Gram matrices, then (from n_gram on) the cores
+    std::vector<CholMat> chol2;
+    std::vector<TriPair> pairs;
+    int K_gram = 0, K_core = 0;
     const float* const* dptrs = (const float* const*)(ws + p.off_ptrs);
     int ptr_cursor = 0;
     int tb0 = 0, tb1 = 0, tb2 = 0;
@@ -1011,26 +1063,52 @@ hipError_t merge_run(const abt_merge_desc* layers, int L, void* workspace, int m
 
         const int kc = (int)(d.k_cap < K ? d.k_cap : K);
         const int tq = (K + 63) / 64;
-        // stage 4: Ct = L_B^T L_A   (Ct[j][i] = C[i][j], C = L_A^T L_B)
+        // A dense weight W = W I or I W: one side's Gram matrix is the identity (and so is its factor).  The core is
+        // then the other side's factor transposed, and the iteration is run on the Cholesky factor of C C^T
+        // instead of on C: same left singular vectors and values, columns two steps of the triangular QR
+        // iteration nearer to orthogonal (768 x 768 weights: 9 sweeps instead of 15).  Of the two orientations the one whose
+        // triangle is on the near side is taken: with A = I the problem is handled transposed (V Sigma in place
+        // of U Sigma, the roles of A and B exchanged).
+        const MergeSide id = identity ? identity[l] : MergeSide::none;
+        const bool mirror = id == MergeSide::A;
+        double* const scratch[2] = {(double*)(ws + q.chol), (double*)(ws + q.chol) + 32 * K + 2};
+        if (id != MergeSide::A) chol.push_back(CholMat{v.LA, scratch[0], K});
+        if (id != MergeSide::B) chol.push_back(CholMat{v.LB, scratch[1], K});
+        if (K > K_gram) K_gram = K;
+        if (id != MergeSide::none) {
+            chol2.push_back(CholMat{v.Yt, scratch[0], K});
+            pairs.push_back(TriPair{v.Yt, v.Ct, K});
+            if (K > K_core) K_core = K;
+        }
+        double* const near = mirror ? v.LB : v.LA;      // L_A, or L_B where the roles are exchanged
+        // stage 4: Ct = L_B^T L_A   (Ct[j][i] = C[i][j], C = L_A^T L_B); dense: C C^T = L^T L, factored next
         GemmF64& a = g64[l];
         a = GemmF64{};
-        a.A = v.LB; a.B = v.LA; a.C = v.Ct; a.P = K; a.Q = K; a.K = K;
+        a.A = id == MergeSide::none ? v.LB : near; a.B = near; a.C = id == MergeSide::none ? v.Ct : v.Yt; a.P = K; a.Q = K; a.K = K;
         a.lda = K; a.ldb = K; a.ldc = K; a.transA = 1; a.transB = 0;
         a.tile_begin = tb0; a.tiles_q = tq; tb0 += tq * tq;
-        // stage 7a: Yt[j][:] = (L_A c_perm(j))^T = Ct[perm(j)][:] L_A^T ; PB = diag(s3) Yt (fp32)
+        // stage 7a: Yt[j][:] = (L_A c_perm(j))^T = Ct[perm(j)][:] L_A^T ; PB = diag(s3) Yt (fp32), exchanged: PA = its transpose
         GemmF64& b = g64[p.n_gemm64 + l];
         b = GemmF64{};
-        b.A = v.Ct; b.B = v.LA; b.C = v.Yt; b.C32 = v.PB; b.P = kc; b.Q = K; b.K = K;
-        b.lda = K; b.ldb = K; b.ldc = K; b.ldc32 = K; b.transA = 0; b.transB = 1;
+        b.A = v.Ct; b.B = near; b.C = v.Yt; b.P = kc; b.Q = K; b.K = K;
+        b.lda = K; b.ldb = K; b.ldc = K; b.transA = 0; b.transB = 1;
+        b.C32 = mirror ? v.PA : v.PB; b.ldc32 = mirror ? (int)d.k_cap : K; b.trans32 = mirror ? 1 : 0;
         b.row_gather = v.perm; b.row_scale32 = v.s3; b.limit = d.k_out; b.limit_rows = 1;
         b.tile_begin = tb1; b.tiles_q = tq; tb1 += ((kc + 63) / 64) * tq;
-        // stage 7b: PA = G_B Yt^T diag(s5)   (fp32 only)
+        // stage 7b: PA = G_B Yt^T diag(s5), exchanged: PB = diag(s5) Yt G_A   (fp32 only)
         GemmF64& c = g64[2 * p.n_gemm64 + l];
         c = GemmF64{};
-        c.A = v.GB; c.B = v.Yt; c.C32 = v.PA; c.P = K; c.Q = kc; c.K = K;
-        c.lda = K; c.ldb = K; c.ldc32 = (int)d.k_cap; c.transA = 0; c.transB = 1;
-        c.col_scale32 = v.s5; c.limit = d.k_out; c.limit_rows = 0;
-        c.tile_begin = tb2; c.tiles_q = (kc + 63) / 64; tb2 += tq * ((kc + 63) / 64);
+        c.K = K; c.lda = K; c.ldb = K; c.limit = d.k_out;
+        if (mirror) {
+            c.A = v.Yt; c.B = v.LA; c.C32 = v.PB; c.P = kc; c.Q = K;          // G_A = L_A = I
+            c.ldc32 = K; c.transA = 0; c.transB = 0; c.row_scale32 = v.s5; c.limit_rows = 1;
+            c.tiles_q = tq;
+        } else {
+            c.A = v.GB; c.B = v.Yt; c.C32 = v.PA; c.P = K; c.Q = kc;
+            c.ldc32 = (int)d.k_cap; c.transA = 0; c.transB = 1; c.col_scale32 = v.s5; c.limit_rows = 0;
+            c.tiles_q = (kc + 63) / 64;
+        }
+        c.tile_begin = tb2; tb2 += tq * ((kc + 63) / 64);
         // stage 8: back-projection (fp32 MFMA): A' = Abar PA, B' = PB Bbar, Wbar = Abar Bbar
         GemmF32 ga{};
         ga.A = v.Abar; ga.B = v.PA; ga.C = d.A_out; ga.P = (int)d.m; ga.Q = (int)d.k_cap; ga.K = K;
@@ -1064,6 +1142,10 @@ hipError_t merge_run(const abt_merge_desc* layers, int L, void* workspace, int m
     put(p.off_wg_cross, wcross.data(), sizeof(int2) * wcross.size());
     put(p.off_wg_intra, wintra.data(), sizeof(int2) * wintra.size());
     put(p.off_gemm64, g64.data(), sizeof(GemmF64) * g64.size());
+    const size_t n_gram = chol.size();
+    chol.insert(chol.end(), chol2.begin(), chol2.end());
+    put(p.off_chol, chol.data(), sizeof(CholMat) * chol.size());
+    put(p.off_pairs, pairs.data(), sizeof(TriPair) * pairs.size());
     const GemmF32Table table32 = gemm_f32_build_table(g32.data(), (int)g32.size(), image.data() + p.off_gemm32);
     ABT_TRY(hipMemcpyAsync(ws, image.data(), image.size(), hipMemcpyHostToDevice, s));
     // the upload must have left the host image before it is destroyed
@@ -1086,21 +1168,17 @@ hipError_t merge_run(const abt_merge_desc* layers, int L, void* workspace, int m
     ABT_TRY(mark(0));
     ABT_TRY(launch_mean_gram(dl, (const GramJob*)(ws + p.off_gram_tiles), gram_aligned, p.n_gram_tiles - gram_aligned, s));
     ABT_TRY(mark(1));
-    if (p.K_max <= kCholMaxK) {
-        const size_t lds = sizeof(double) * ((size_t)(p.K_max > 32 ? p.K_max - 32 : 0) * kCholPitch + 32 * 33 + 32 + kCholThreads);
-        static std::atomic<size_t> chol_attr{0};
-        if (lds > chol_attr.load()) {
-            ABT_TRY(hipFuncSetAttribute(reinterpret_cast<const void*>(&cholesky_mfma_kernel),
-                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
-            chol_attr.store(lds);
-        }
-        hipLaunchKernelGGL(cholesky_mfma_kernel, dim3(2 * L), dim3(kCholThreads), lds, s, dl);
-    } else {
-        hipLaunchKernelGGL(cholesky_kernel, dim3(2 * L), dim3(256), 0, s, dl);
-    }
+    const CholMat* mats = (const CholMat*)(ws + p.off_chol);
+    ABT_TRY(launch_cholesky(mats, (int)n_gram, K_gram, s));
     ABT_TRY(mark(2));
     const GemmF64* d64 = (const GemmF64*)(ws + p.off_gemm64);
     hipLaunchKernelGGL(gemm_f64_kernel, dim3(align_up(tb0, 8)), dim3(256), 0, s, d64, p.n_gemm64, tb0);
+    if (!pairs.empty()) {
+        ABT_TRY(launch_cholesky(mats + n_gram, (int)pairs.size(), K_core, s));
+        const unsigned nt = (unsigned)(K_core / 32);
+        hipLaunchKernelGGL(lower_to_columns_kernel, dim3(nt, nt, (unsigned)pairs.size()), dim3(256), 0, s,
+                           (const TriPair*)(ws + p.off_pairs));
+    }
     hipLaunchKernelGGL(frob2_kernel, dim3(8, L), dim3(256), 0, s, dl);
     ABT_TRY(hipGetLastError());
     ABT_TRY(mark(3));

@@ -32,7 +32,7 @@ struct LayerDev {
     float* Abar; float* Bbar;
     double* LA; double* GB; double* LB; double* Ct; double* Yt;
     double* sigma; double* s3; double* s5;
-    double* trace;         // [10]: trace(G_A), trace(G_B), then eight partial sums of ||C||_F^2
+    double* trace;         // [10]: the last eight are partial sums of ||C||_F^2
     double* nrm;           // [K]: squared column norms of the rotated core (colnorm_kernel -> finalize_kernel)
     int* perm;
     float* PA; float* PB;
