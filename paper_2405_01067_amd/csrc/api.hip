@@ -307,8 +307,8 @@ ConvBwdLayout conv_bwd_layout(const abt_conv_geom& g, int64_t m, int64_t r) {
     w.Pst = take((size_t)g.C * taps * w.r_pad * 2);
     const TnJob ja{nullptr, nullptr, nullptr, (int)m, 0}, jb{nullptr, nullptr, nullptr, (int)(taps * g.C), 1};
     const TnJob both[2] = {ja, jb};
-    const size_t pa = tn_partials_bytes(M, &ja, 1, (int)r), pb = tn_partials_bytes(M, &jb, 1, (int)r);
-    const size_t pab = tn_partials_bytes(M, both, 2, (int)r);
+    const size_t pa = tn_partials_bytes(M, &ja, 1, (int)r), pb = tn_partials_bytes(M, &jb, 1, (int)r, true);
+    const size_t pab = tn_partials_bytes(M, both, 2, (int)r, true);
     w.partials = take(pa > pb ? (pa > pab ? pa : pab) : (pb > pab ? pb : pab));
     w.total = off;
     return w;

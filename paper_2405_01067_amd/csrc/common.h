@@ -163,7 +163,7 @@ struct TnJob {
     const void* U; const void* V; float* out; int P; int transposed;
 };
 constexpr int kTnMaxJobs = 16;   // per launch (all with the same M and R)
-size_t tn_partials_bytes(int64_t M, const TnJob* jobs, int njobs, int R);
+size_t tn_partials_bytes(int64_t M, const TnJob* jobs, int njobs, int R, bool gather = false);
 hipError_t launch_tn_bf16(const TnJob* jobs, int njobs, int64_t M, int R, int accumulate,
                           float* partials, hipStream_t s);
 

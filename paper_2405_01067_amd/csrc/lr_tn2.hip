@@ -29,7 +29,13 @@ constexpr int TP = 128;      // U columns per work-group
 constexpr int BKM = 64;      // batch rows per slab
 constexpr int NMW = 4;       // MFMA waves
 
-template <int R>
+// Two work-groups per compute unit for a gathered operand at narrow ranks: a loader wave there spends a slab on
+// range checks and transposition with nobody to take its place, and a second work-group on half the ring does
+// (factor gradients of 256 x 14 x 14, batch 256, r = 64: 59 -> 42 us; 128 x 28 x 28, stride 2: 46 -> 33).  A
+// matrix operand streams at memory rate with one.
+constexpr bool tn2_two(int R, bool gather) { return gather && R <= 128; }
+
+template <int R, bool GATHER>
 struct Tn2 {
     static constexpr int RB = R / 32;
     static constexpr bool even = (RB % 2) == 0;
@@ -45,7 +51,9 @@ struct Tn2 {
     static constexpr int NT = 64 * (NMW + NUW + NVW);
     // slabs in flight in the loaders' register ring: a CU wants about 64 KB of loads outstanding,
     // which two slabs only give when a slab is 40 KB or more (R >= 192)
-    static constexpr int D = slab * 2 >= 64 * 1024 ? 2 : (slab * 3 >= 64 * 1024 ? 3 : 4);
+    static constexpr int D = tn2_two(R, GATHER) || slab * 2 >= 64 * 1024 ? 2 : (slab * 3 >= 64 * 1024 ? 3 : 4);
+    // waves per SIMD the registers are budgeted for: two work-groups of seven or eight waves need four
+    static constexpr int WPS = tn2_two(R, GATHER) ? 4 : 1;
     static_assert(lds_bytes <= 160 * 1024, "slab shape");
 };
 
@@ -284,9 +292,9 @@ __device__ __forceinline__ void tn_loader(const uint16_t* src, int pitch, int co
 }
 
 template <int R, bool GATHER>
-__global__ __launch_bounds__(Tn2<R>::NT) void tn2_bf16_kernel(Tn2Args args) {
+__global__ __launch_bounds__((Tn2<R, GATHER>::NT), (Tn2<R, GATHER>::WPS)) void tn2_bf16_kernel(Tn2Args args) {
     extern __shared__ __align__(1024) unsigned char lds[];
-    using C = Tn2<R>;
+    using C = Tn2<R, GATHER>;
     constexpr int D = C::D;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
 
@@ -395,21 +403,48 @@ __global__ __launch_bounds__(Tn2<R>::NT) void tn2_bf16_kernel(Tn2Args args) {
         }
 }
 
-// out (+)= sum over splits of part[split], element-wise (part already has the layout of out).
+// out (+)= sum over splits of part[split], element-wise (part already has the layout of out).  Few splits: four
+// elements per thread, which walks through the splits.  From kRedSplit splits on a work-group takes a quarter of
+// the elements and each of its four waves adds every fourth split; the four sums are added in wave order (81920
+// elements in 51 splits: 17 us for 80 work-groups with a serial chain of 51 loads, 6 us; at 5 splits of 737280
+// elements the plain form is 1.5 us the faster).
 struct Red2Job { const float* part; float* out; int64_t total; int block_begin; };
 struct Red2Args { Red2Job job[kTnMaxJobs]; int njobs; int splits; int accumulate; };
+constexpr int kRedSplit = 16;
 
 __global__ __launch_bounds__(256) void tn2_reduce_kernel(Red2Args a) {
+    __shared__ f32x4 sums[3][64];
     int jid = 0;
     for (int i = 1; i < a.njobs; ++i)
         if ((int)blockIdx.x >= a.job[i].block_begin) jid = i;
     const Red2Job j = a.job[jid];
-    const int64_t idx = ((int64_t)((int)blockIdx.x - j.block_begin) * 256 + threadIdx.x) * 4;
-    if (idx >= j.total) return;   // totals are multiples of 4 (R % 32 == 0)
-    f32x4 sum = *reinterpret_cast<const f32x4*>(j.part + idx);
-    for (int s = 1; s < a.splits; ++s) sum += *reinterpret_cast<const f32x4*>(j.part + (int64_t)s * j.total + idx);
-    if (a.accumulate) sum += *reinterpret_cast<const f32x4*>(j.out + idx);
-    *reinterpret_cast<f32x4*>(j.out + idx) = sum;
+    const int block = (int)blockIdx.x - j.block_begin;
+    if (a.splits < kRedSplit) {
+        const int64_t idx = ((int64_t)block * 256 + threadIdx.x) * 4;
+        if (idx >= j.total) return;   // totals are multiples of 4 (R % 32 == 0)
+        f32x4 sum = *reinterpret_cast<const f32x4*>(j.part + idx);
+        for (int s = 1; s < a.splits; ++s) sum += *reinterpret_cast<const f32x4*>(j.part + (int64_t)s * j.total + idx);
+        if (a.accumulate) sum += *reinterpret_cast<const f32x4*>(j.out + idx);
+        *reinterpret_cast<f32x4*>(j.out + idx) = sum;
+        return;
+    }
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int64_t idx = ((int64_t)block * 64 + lane) * 4;
+    const bool live = idx < j.total;
+    f32x4 sum = {0.0f, 0.0f, 0.0f, 0.0f};
+    if (live) {
+#pragma unroll 4
+        for (int s = wave; s < a.splits; s += 4) sum += gload(reinterpret_cast<const f32x4*>(j.part + (int64_t)s * j.total + idx));
+        if (wave > 0) sums[wave - 1][lane] = sum;
+    }
+    __syncthreads();
+    if (wave > 0 || !live) return;
+    sum += sums[0][lane];
+    sum += sums[1][lane];
+    sum += sums[2][lane];
+    f32x4* out = reinterpret_cast<f32x4*>(j.out + idx);
+    if (a.accumulate) sum += gload(out);
+    gstore(out, sum);
 }
 
 int tn2_total_tiles(const TnJob* jobs, int njobs) {
@@ -418,10 +453,10 @@ int tn2_total_tiles(const TnJob* jobs, int njobs) {
     return tiles;
 }
 
-int tn2_choose_splits(int64_t M, int total_tiles) {
-    // one 8-wave work-group per compute unit and every work-group writes one fp32 partial tile:
-    // aim at one full round of the 256 compute units, at least 8 slabs each
-    int64_t want = 256 / total_tiles;
+int tn2_choose_splits(int64_t M, int total_tiles, int per_cu) {
+    // every work-group writes one fp32 partial tile: aim at one full round of the 256 compute units
+    // (`per_cu` work-groups on each), at least 8 slabs each
+    int64_t want = 256 * per_cu / total_tiles;
     int64_t max_by_rows = M / (8 * 64);
     if (max_by_rows < 1) max_by_rows = 1;
     if (want > max_by_rows) want = max_by_rows;
@@ -432,7 +467,7 @@ int tn2_choose_splits(int64_t M, int total_tiles) {
 
 template <int R, bool GATHER>
 hipError_t launch_tn2_r(const Tn2Args& args, int tiles, int splits, hipStream_t s) {
-    constexpr int lds_bytes = Tn2<R>::lds_bytes;
+    constexpr int lds_bytes = Tn2<R, GATHER>::lds_bytes;
     static bool attr_set = false;
     if (!attr_set) {
         hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&tn2_bf16_kernel<R, GATHER>),
@@ -440,14 +475,14 @@ hipError_t launch_tn2_r(const Tn2Args& args, int tiles, int splits, hipStream_t 
         if (e != hipSuccess) return e;
         attr_set = true;
     }
-    hipLaunchKernelGGL((tn2_bf16_kernel<R, GATHER>), dim3(8 * ((tiles * splits + 7) / 8)), dim3(Tn2<R>::NT), lds_bytes, s, args);
+    hipLaunchKernelGGL((tn2_bf16_kernel<R, GATHER>), dim3(8 * ((tiles * splits + 7) / 8)), dim3(Tn2<R, GATHER>::NT), lds_bytes, s, args);
     return hipGetLastError();
 }
 
 }  // namespace
 
-size_t tn_partials_bytes(int64_t M, const TnJob* jobs, int njobs, int R) {
-    const int splits = tn2_choose_splits(M, tn2_total_tiles(jobs, njobs));
+size_t tn_partials_bytes(int64_t M, const TnJob* jobs, int njobs, int R, bool gather) {
+    const int splits = tn2_choose_splits(M, tn2_total_tiles(jobs, njobs), tn2_two(R, gather) ? 2 : 1);
     size_t elems = 0;
     for (int i = 0; i < njobs; ++i) elems += (size_t)jobs[i].P * R;
     return elems * splits * sizeof(float);
@@ -459,11 +494,12 @@ hipError_t launch_tn_common(const TnJob* jobs, int njobs, int64_t M, int R, int 
                             float* partials, const Tn2Gather* gather, hipStream_t s) {
     if (njobs < 1 || njobs > kTnMaxJobs || (gather && njobs > 2)) return hipErrorInvalidValue;
     const int tiles = tn2_total_tiles(jobs, njobs);
-    const int splits = tn2_choose_splits(M, tiles);
+    const int splits = tn2_choose_splits(M, tiles, tn2_two(R, gather != nullptr) ? 2 : 1);
     Tn2Args args{};
     Red2Args red{};
     args.njobs = red.njobs = njobs;
     args.tiles = tiles; args.splits = splits;
+    const bool direct = splits == 1 && !accumulate;      // one split: its sums are the result
     args.M = M;
     if (gather) args.g = *gather;
     int64_t rps = ceil_div(M, splits);
@@ -475,7 +511,7 @@ hipError_t launch_tn_common(const TnJob* jobs, int njobs, int64_t M, int R, int 
     for (int i = 0; i < njobs; ++i) {
         args.job[i].U = (const uint16_t*)jobs[i].U;
         args.job[i].V = (const uint16_t*)jobs[i].V;
-        args.job[i].part = part;
+        args.job[i].part = direct ? jobs[i].out : part;
         args.job[i].P = jobs[i].P;
         args.job[i].tile_begin = tile_begin;
         args.job[i].transposed = jobs[i].transposed;
@@ -485,7 +521,7 @@ hipError_t launch_tn_common(const TnJob* jobs, int njobs, int64_t M, int R, int 
         red.job[i].total = (int64_t)jobs[i].P * R;
         tile_begin += (jobs[i].P + TP - 1) / TP;
         red.job[i].block_begin = red_blocks;
-        red_blocks += (int)ceil_div((int64_t)jobs[i].P * R / 4, 256);
+        red_blocks += (int)ceil_div((int64_t)jobs[i].P * R / 4, splits < kRedSplit ? 256 : 64);
         part += (size_t)jobs[i].P * R * splits;
     }
     hipError_t e;
@@ -497,7 +533,7 @@ hipError_t launch_tn_common(const TnJob* jobs, int njobs, int64_t M, int R, int 
 #undef ABT_CASE
         default: return hipErrorInvalidValue;
     }
-    if (e != hipSuccess) return e;
+    if (e != hipSuccess || direct) return e;
     hipLaunchKernelGGL(tn2_reduce_kernel, dim3(red_blocks), dim3(256), 0, s, red);
     return hipGetLastError();
 }
@@ -523,7 +559,7 @@ hipError_t launch_tn_gather_bf16(const TnJob* jobs, int njobs, const PatchGeom& 
     // one descriptor per row split: its window of the image (the centres of the split's rows, the
     // reach of the window on both sides, the padded slabs of the loaders' ring) must stay below 2 GiB
     {
-        const int splits = tn2_choose_splits(M, tn2_total_tiles(jobs, njobs));
+        const int splits = tn2_choose_splits(M, tn2_total_tiles(jobs, njobs), tn2_two(R, true) ? 2 : 1);
         const int64_t rps = ceil_div(ceil_div(M, splits), 64) * 64;
         const int64_t reach = (g.kh / 2) * (int64_t)g.W + g.kw / 2;
         const int64_t span = (int64_t)g.mul * g.mul * (rps + 64 * 8 + g.RW + 2) + 2 * (int64_t)g.mul * g.W;
