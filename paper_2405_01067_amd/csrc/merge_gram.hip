@@ -48,7 +48,6 @@ __global__ __launch_bounds__(256, 1) void mean_gram_kernel(const LayerDev* __res
     const int strip0 = job.ti * GT, strip1 = job.tj * GT;     // first column (A side) / row (B side) of the strips
     const int t = threadIdx.x, lane = t & 63, wave = t >> 6, n = lane & 15, kq = lane >> 4;
     const int wr = wave >> 1, wc = wave & 1;
-    const bool idle = diag && wr == 0 && wc == 1;              // mirror image of the wave (1, 0)
     const float* const* src = bside ? L.B_ptrs : L.A_ptrs;
     float* mean_out = bside ? L.Bbar : L.Abar;
     const int ncopies = mode == 0 ? G : 1;
@@ -175,19 +174,40 @@ __global__ __launch_bounds__(256, 1) void mean_gram_kernel(const LayerDev* __res
 #pragma unroll
         for (int b = 0; b < 4; ++b) acc[a][b] = f64x4{0.0, 0.0, 0.0, 0.0};
     const int offA = wr * 64, offB = (diag ? 0 : GT) + wc * 64;   // this wave's operand columns in the slab
-    auto kstep = [&](const float* Xb, int q) {
+    // The operands of step q + 1 are read before the products of step q: a step is 1024 cycles of matrix time
+    // and an LDS read in front of it would stand alone.  Of a part that reaches beyond K only the 16 x 16 blocks
+    // inside it are multiplied (K = 32: 4 blocks of one wave instead of 48 of three).
+    const int na = (K - strip0 - wr * 64 + 15) >> 4, nb = (K - strip1 - wc * 64 + 15) >> 4;
+    const bool idle = (diag && wr == 0 && wc == 1) || na <= 0 || nb <= 0;      // the mirror image of wave (1, 0), or nothing inside K
+    const bool whole = na >= 4 && nb >= 4;
+    float fa[4], fb[4];
+    auto fetch = [&](const float* Xb, int q) {
         const int cc = 4 * q + kq;
-        double av[4], bv[4];
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-            av[i] = (double)Xb[cc * GPITCH + gsw(cc, offA + 16 * i + n)];
-            bv[i] = (double)Xb[cc * GPITCH + gsw(cc, offB + 16 * i + n)];
+            fa[i] = Xb[cc * GPITCH + gsw(cc, offA + 16 * i + n)];
+            fb[i] = Xb[cc * GPITCH + gsw(cc, offB + 16 * i + n)];
         }
+    };
+    auto kstep = [&](const float* Xb, int q) {
+        double av[4], bv[4];
 #pragma unroll
-        for (int i = 0; i < 4; ++i)
+        for (int i = 0; i < 4; ++i) { av[i] = (double)fa[i]; bv[i] = (double)fb[i]; }
+        fetch(Xb, q < 7 ? q + 1 : 7);
+        __builtin_amdgcn_sched_barrier(0);
+        if (whole) {
 #pragma unroll
-            for (int j = 0; j < 4; ++j)
-                acc[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(av[i], bv[j], acc[i][j], 0, 0, 0);
+            for (int i = 0; i < 4; ++i)
+#pragma unroll
+                for (int j = 0; j < 4; ++j)
+                    acc[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(av[i], bv[j], acc[i][j], 0, 0, 0);
+        } else {
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+#pragma unroll
+                for (int j = 0; j < 4; ++j)
+                    if (i < na && j < nb) acc[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(av[i], bv[j], acc[i][j], 0, 0, 0);
+        }
     };
 
     // ---- prologue: slab 0
@@ -201,6 +221,7 @@ __global__ __launch_bounds__(256, 1) void mean_gram_kernel(const LayerDev* __res
         __syncthreads();          // slab sl visible; everybody is done reading buffer b ^ 1 (slab sl - 1)
         const float* Xb = X[b];
         clear_sum();
+        if (!idle) fetch(Xb, 0);
         int q = 0;
         if (sl + 1 < nslab) {
             // the copies of the next slab arrive between the products: two copies in flight, copy g is
