@@ -1192,7 +1192,9 @@ hipError_t merge_run(const abt_merge_desc* layers, const MergeSide* identity, in
             if (flags[(size_t)l * (kMaxSweepsCap + 1) + q] == 0) return true;
         return false;
     };
-    if (p.K_max <= 768) {
+    if (p.K_max == 32) {
+        ABT_TRY(launch_jacobi_single_pair(dl, cross, p.n_wg_cross, max_sweeps, s));
+    } else if (p.K_max <= 768) {
         // block form on the matrix cores, layers in groups (contiguous layer ranges with about the
         // same number of work-groups); wcross is layer-major, so a group is a slice of it
         std::unique_lock<std::mutex> lock(g_side_mutex);

@@ -100,4 +100,7 @@ hipError_t launch_mean_gram(const LayerDev* layers, const GramJob* jobs, int njo
 hipError_t launch_jacobi_block_round(const LayerDev* layers, const int2* wg_map, int n_wg, int K_max,
                                      int sweep, int round, hipStream_t s);
 
+// All sweeps of layers with K = 32 (every layer of the batch): one work-group per layer, one launch.
+hipError_t launch_jacobi_single_pair(const LayerDev* layers, const int2* wg_map, int n_wg, int max_sweeps, hipStream_t s);
+
 }  // namespace abt

@@ -84,7 +84,10 @@ __device__ __forceinline__ void pair_of(int st, int intra, int p, int& i, int& j
 }
 
 // NT: 16-row tiles per wave (two per 32-row chunk: its even and its odd rows), K <= 64 NT.
-template <int NT>
+// WHOLE (K = 32: two blocks, one pair): the work-group holds the whole core, so it runs all sweeps in one launch, the
+// panel in registers throughout; `round` is the sweep cap.  A launch and a poll of the convergence flags per
+// sweep took 129 us for one core of 32 (four sweeps), this 86.
+template <int NT, bool WHOLE>
 __global__ __launch_bounds__(256, (NT <= 6 ? 3 : 1)) void jacobi_block_kernel(const LayerDev* __restrict__ layers,
                                                                                const int2* __restrict__ wg_map,
                                                                                int sweep, int round) {
@@ -93,7 +96,9 @@ __global__ __launch_bounds__(256, (NT <= 6 ? 3 : 1)) void jacobi_block_kernel(co
     const LayerDev& L = layers[wm.x];
     if (sweep_finished(L, sweep)) return;
     const int K = L.K, nb = K >> 4;
-    if (round >= nb - 1 || K > 64 * NT) return;
+    const int max_sweeps = WHOLE ? round : 0;
+    if (WHOLE) round = 0;
+    if (round >= nb - 1 || K > 64 * NT || (WHOLE && nb != 2)) return;
     // circle method: slot 0 pairs block nb-1 with `round`; slot j pairs (round + j) with (round - j)
     int bI, bJ;
     if (wm.y == 0) { bI = nb - 1; bJ = round; }
@@ -115,6 +120,7 @@ __global__ __launch_bounds__(256, (NT <= 6 ? 3 : 1)) void jacobi_block_kernel(co
         }
     }
 
+    for (;; ++sweep) {                                   // one turn; WHOLE: until a sweep rotates nothing of weight
     // ---- S = P^T P: three 16 x 16 tiles (II, IJ, JJ), this wave's rows
     f64x4 gII = {0.0, 0.0, 0.0, 0.0}, gIJ = gII, gJJ = gII;
     double* stage = sh.stage[wave];
@@ -187,7 +193,10 @@ __global__ __launch_bounds__(256, (NT <= 6 ? 3 : 1)) void jacobi_block_kernel(co
         test(i, 16 + j);
         if (intra && i < j) { test(i, j); test(16 + i, 16 + j); }
     }
-    if (!__syncthreads_or(need)) return;     // the data is untouched: nothing to store
+    if (!__syncthreads_or(need)) {
+        if (WHOLE) break;
+        return;                              // the data is untouched: nothing to store
+    }
 
     // ---- cyclic Jacobi on S, accumulated in Q.  A thread owns the 2 x 2 cell rows(pair u) x
     // columns(pair v) of S and two rows of the columns(pair v) of Q.
@@ -284,6 +293,7 @@ __global__ __launch_bounds__(256, (NT <= 6 ? 3 : 1)) void jacobi_block_kernel(co
             __syncthreads();
         }
     }
+    const bool again = WHOLE && __syncthreads_or(any_signif);
     if (any_signif) L.rotated[sweep] = 1;
 
     // ---- P <- P Q as (Q^T P^T): A operand = Q^T tile, B operand = the panel registers
@@ -302,6 +312,9 @@ __global__ __launch_bounds__(256, (NT <= 6 ? 3 : 1)) void jacobi_block_kernel(co
         }
 #pragma unroll
         for (int v = 0; v < 4; ++v) { D[t][v] = acc0[v]; D[t][4 + v] = acc1[v]; }
+    }
+    if (!again || sweep + 1 >= max_sweeps) break;
+    __syncthreads();                                     // Q is read, the next sweep's stages may overwrite
     }
 
     // ---- store
@@ -324,12 +337,18 @@ hipError_t launch_jacobi_block_round(const LayerDev* layers, const int2* wg_map,
                                      int sweep, int round, hipStream_t s) {
     if (n_wg <= 0) return hipSuccess;
     const dim3 grid(n_wg), block(256);
-    if (K_max <= 128) hipLaunchKernelGGL(jacobi_block_kernel<2>, grid, block, 0, s, layers, wg_map, sweep, round);
-    else if (K_max <= 256) hipLaunchKernelGGL(jacobi_block_kernel<4>, grid, block, 0, s, layers, wg_map, sweep, round);
-    else if (K_max <= 384) hipLaunchKernelGGL(jacobi_block_kernel<6>, grid, block, 0, s, layers, wg_map, sweep, round);
-    else if (K_max <= 512) hipLaunchKernelGGL(jacobi_block_kernel<8>, grid, block, 0, s, layers, wg_map, sweep, round);
-    else if (K_max <= 768) hipLaunchKernelGGL(jacobi_block_kernel<12>, grid, block, 0, s, layers, wg_map, sweep, round);
+    if (K_max <= 128) hipLaunchKernelGGL((jacobi_block_kernel<2, false>), grid, block, 0, s, layers, wg_map, sweep, round);
+    else if (K_max <= 256) hipLaunchKernelGGL((jacobi_block_kernel<4, false>), grid, block, 0, s, layers, wg_map, sweep, round);
+    else if (K_max <= 384) hipLaunchKernelGGL((jacobi_block_kernel<6, false>), grid, block, 0, s, layers, wg_map, sweep, round);
+    else if (K_max <= 512) hipLaunchKernelGGL((jacobi_block_kernel<8, false>), grid, block, 0, s, layers, wg_map, sweep, round);
+    else if (K_max <= 768) hipLaunchKernelGGL((jacobi_block_kernel<12, false>), grid, block, 0, s, layers, wg_map, sweep, round);
     else return hipErrorInvalidValue;
+    return hipGetLastError();
+}
+
+hipError_t launch_jacobi_single_pair(const LayerDev* layers, const int2* wg_map, int n_wg, int max_sweeps, hipStream_t s) {
+    if (n_wg <= 0) return hipSuccess;
+    hipLaunchKernelGGL((jacobi_block_kernel<2, true>), dim3(n_wg), dim3(256), 0, s, layers, wg_map, 0, max_sweeps);
     return hipGetLastError();
 }
 

@@ -1,0 +1,58 @@
+"""Merges whose core is a single pair of column blocks (K = 32) run all Jacobi sweeps in one launch; with a larger
+layer in the batch the same layer goes through a launch per round.  Both do the same rotations in the same
+order on the same numbers: the singular values agree bit for bit.  And decompositions of dense weights around
+the sizes where the Cholesky factorisation changes its form, against an fp64 SVD."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2405_01067_amd import binding as abt
+from paper_2405_01067_amd import inputs as gen
+
+pytestmark = pytest.mark.gpu
+
+
+def layer(m, n, k, seed, g=2, gap_at=12):
+    lay = gen.merge_layer(m, n, seed=seed, k_in=k, g=g, gap_at=gap_at)
+    up = lambda xs: [torch.from_numpy(np.ascontiguousarray(x)).to("cuda:0") for x in xs]
+    return {"A_copies": up(lay["A_copies"]), "B_copies": up(lay["B_copies"]), "tau": 0.0}
+
+
+@pytest.mark.parametrize("m,n,count", [(64, 48, 1), (256, 256, 3), (33, 1000, 2)])
+def test_single_pair_core_agrees_with_a_mixed_batch(m, n, count):
+    small = [layer(m, n, 32, seed=10 * m + i) for i in range(count)]
+    alone = abt.ab_merge_batched(small)
+    mixed = abt.ab_merge_batched(small + [layer(128, 96, 64, seed=3)])
+    for a, b in zip(alone, mixed):
+        assert torch.equal(a["S"], b["S"]) and a["sweeps"] == b["sweeps"] > 1
+        W, V = (o["A"].double() @ o["B"].double() for o in (a, b))
+        assert float((W - V).norm() / V.norm()) < 1e-6
+
+
+def test_single_pair_core_reports_the_sweep_cap():
+    lay = layer(200, 100, 32, seed=77)
+    prev = abt.set_jacobi_max_sweeps(1)
+    try:
+        with pytest.raises(abt.AbtError):
+            abt.ab_merge_batched([lay])
+    finally:
+        abt.set_jacobi_max_sweeps(prev)
+
+
+@pytest.mark.parametrize("m,n", [(128, 128), (160, 160), (544, 600), (700, 576), (100, 96)])
+def test_dense_decomposition_around_the_cholesky_forms(m, n):
+    # 96, 128: one launch; 160 and more: blocked, 64 x 64 tiles of the trailing matrix with 32-wide remainders
+    g = torch.Generator().manual_seed(m + n)
+    K = min(m, n) // 32 * 32
+    W = torch.randn((m, n), generator=g, dtype=torch.float64)
+    W = W[:K] if m <= n else W[:, :K]
+    W = (W * torch.logspace(0, -2, W.shape[1], dtype=torch.float64)).float().contiguous()
+    keep = K // 2
+    out = abt.ab_factorize(W.to("cuda:0"), tau=0.0, k_fixed=keep)
+    U, s, V = torch.linalg.svd(W.double(), full_matrices=False)
+    assert float(((out["S"].cpu().double()[:keep] - s[:keep]).abs() / s[:keep]).max()) < 1e-5
+    got = out["A"].cpu().double()[:, :keep] @ out["B"].cpu().double()[:keep]
+    want = (U[:, :keep] * s[:keep]) @ V[:keep]
+    # fp32 factors and products; the cut falls into a spectrum without a gap, but the values around it agree
+    # to far better than their distance
+    assert float((got - want).norm() / want.norm()) < 1e-5
