@@ -13,7 +13,8 @@ namespace {
 
 std::atomic<int> g_max_sweeps{30};
 
-// Chain kernel choice: for large batches the 128-row kernel where it supports the rank (32, 64, 96,
+// Chain kernel choice: the narrow-rank kernel where use_narrow / narrow_gather say so; else for large batches the
+// 128-row kernel where it supports the rank (32, 64, 96,
 // 128, 192); else the 64-row kernel with loader and MFMA waves wherever that supports the rank
 // (32, 64, 96, 128, 160, 192, 256, 320, 384), else the older kernel (224, 288, 352).
 std::atomic<int> g_chain_rows{0};    // 0: automatic; 64 or 128: force that work-group height where the rank allows it

@@ -4,8 +4,9 @@
 // What bounds it: at these ranks the layer moves about as many bytes as it has matrix work for, so the
 // activations have to stream at memory rate while the factors come out of L2.  One work-group of
 // specialised waves per compute unit (lr_chain2.hip) waits a whole load latency at each of its barriers
-// and has nobody else to run meanwhile; here a work-group is four waves with 16 to 50 KB of LDS, and two
-// or three of them share a compute unit.
+// and has nobody else to run meanwhile; here a work-group is four waves with 26 to 67 KB of LDS, and two
+// or three of them share a compute unit (39597 x 3072 -> 768 at r = 96: 98 -> 82 us; 100000 x 768 -> 768 at r = 160:
+// 136 -> 93; a 3 x 3 forward on 256 x 28 x 28 x 128 at r = 64: 150 -> 85).
 //
 //   * A wave owns 32 rows through both stages, and each activation element is used by one wave only.
 //     From a matrix the wave loads whole 128-byte lines (slabs of 64 columns, two slabs ahead in registers)

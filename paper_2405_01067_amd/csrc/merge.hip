@@ -208,8 +208,9 @@ __global__ __launch_bounds__(256) void lower_to_columns_kernel(const TriPair* __
 //   write L's block column, and subtract X X^T from the lower triangle of the trailing matrix:
 //   16 x 16 tiles, C tile from / to memory (L2), operands of v_mfma_f64_16x16x4 from the LDS panel.
 // ------------------------------------------------------------------------------------------
-constexpr int kCholMaxK = 544;     // (K - 32) x 34 doubles of panel: 136 KB
-constexpr int kCholSmallK = 128;
+// 128 columns: 0.07 ms in one launch (the blocked form would be eight of 14 us); 384 columns, one matrix pair: 0.47 ms in
+// one launch, 0.24 blocked, and 0.47 either way for 48 of them.
+constexpr int kCholSmallK = 128;   // (K - 32) x 34 doubles of panel: 26 KB
 constexpr int kCholPitch = 34;     // doubles per panel row: 16 rows x 2 column groups of an operand read cover all banks
 
 constexpr int kCholThreads = 256;  // (512 threads measured the same: the serial diagonal-block and row-solve phases dominate)
@@ -220,7 +221,7 @@ __global__ __launch_bounds__(kCholThreads) void cholesky_mfma_kernel(const CholM
     const CholMat m = mats[blockIdx.x];
     double* Gm = m.G;
     const int K = m.K;
-    if (K > kCholMaxK) return;
+    if (K > kCholSmallK) return;
     double* Xp = reinterpret_cast<double*>(lds_raw);                 // [K - 32][kCholPitch]
     double (*Ljj)[33] = reinterpret_cast<double (*)[33]>(Xp + (size_t)(K > 32 ? K - 32 : 0) * kCholPitch);
     double* invp = &Ljj[0][0] + 32 * 33;                             // [32] reciprocal pivots (0: dropped column)
@@ -350,13 +351,6 @@ hipError_t launch_cholesky(const CholMat* mats, int n, int K_max, hipStream_t s)
     if (n < 1) return hipSuccess;
     if (K_max <= kCholSmallK) {
         const size_t lds = sizeof(double) * ((size_t)(K_max > 32 ? K_max - 32 : 0) * kCholPitch + 32 * 33 + 32 + kCholThreads);
-        static std::atomic<size_t> attr{0};
-        if (lds > attr.load()) {
-            const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&cholesky_mfma_kernel),
-                                                     hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-            if (e != hipSuccess) return e;
-            attr.store(lds);
-        }
         hipLaunchKernelGGL(cholesky_mfma_kernel, dim3(n), dim3(kCholThreads), lds, s, mats);
         return hipGetLastError();
     }
