@@ -90,6 +90,12 @@ constexpr int64_t kStreamOutBytes = 64ll << 20;
 
 inline int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
 inline size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
+// Do two byte ranges share memory?  (A caller may hand in an output that lies over an input, as far as everything
+// that reads the input is done before the output is written.)
+inline bool overlap(const void* a, int64_t na, const void* b, int64_t nb) {
+    const uintptr_t x = reinterpret_cast<uintptr_t>(a), y = reinterpret_cast<uintptr_t>(b);
+    return a && b && x < y + (uintptr_t)nb && y < x + (uintptr_t)na;
+}
 
 // ------------------------------------------------------------------ bf16 factored layer
 // Fused chain  Tout[M,R] = Xin[M,p] . P[R,p]^T ;  Yout[M,q] = Tout . Q[q,R]^T  (bf16, fp32 acc).

@@ -490,6 +490,17 @@ size_t tn_partials_bytes(int64_t M, const TnJob* jobs, int njobs, int R, bool ga
 
 namespace {
 // gather != NULL: the LAST job's U is gathered from an image, any job before it is plain
+// Does a result lie over an operand of the launch?  Then it may only be written once all operands are read.
+bool tn2_result_over_operand(const TnJob* jobs, int njobs, int64_t M, int R, const Tn2Gather* g) {
+    for (int o = 0; o < njobs; ++o)
+        for (int i = 0; i < njobs; ++i) {
+            const int64_t u = g && i == njobs - 1 ? M / ((int64_t)g->RH * g->RW) * g->H * g->W * g->C : M * jobs[i].P;
+            const int64_t out = (int64_t)jobs[o].P * R * 4;
+            if (overlap(jobs[o].out, out, jobs[i].U, u * 2) || overlap(jobs[o].out, out, jobs[i].V, M * R * 2)) return true;
+        }
+    return false;
+}
+
 hipError_t launch_tn_common(const TnJob* jobs, int njobs, int64_t M, int R, int accumulate,
                             float* partials, const Tn2Gather* gather, hipStream_t s) {
     if (njobs < 1 || njobs > kTnMaxJobs || (gather && njobs > 2)) return hipErrorInvalidValue;
@@ -499,7 +510,8 @@ hipError_t launch_tn_common(const TnJob* jobs, int njobs, int64_t M, int R, int 
     Red2Args red{};
     args.njobs = red.njobs = njobs;
     args.tiles = tiles; args.splits = splits;
-    const bool direct = splits == 1 && !accumulate;      // one split: its sums are the result
+    // one split: its sums are the result
+    const bool direct = splits == 1 && !accumulate && !tn2_result_over_operand(jobs, njobs, M, R, gather);
     args.M = M;
     if (gather) args.g = *gather;
     int64_t rps = ceil_div(M, splits);
