@@ -587,11 +587,23 @@ int lr_linear_bwd(const void* dY, const void* X, const void* T, const void* A, c
         }
         if (dX || dB) g[k++] = gemm((const float*)dY, (const float*)A, dT, M, r, m, m, r, r, 0, 0, 0);
         if (k && launch_gemm_f32(g, nullptr, k, nullptr, s) != hipSuccess) return ABT_EHIP;
+        // an output over an operand of the second launch is written after its readers: one product after the other
+        const void* out[3] = {dX, dA, dB};
+        const int64_t out_bytes[3] = {M * n * 4, m * r * 4, r * n * 4};
+        bool in_turn = false;
+        for (int i = 0; i < 3; ++i)
+            in_turn |= overlap(out[i], out_bytes[i], dY, M * m * 4) || overlap(out[i], out_bytes[i], Tp, M * r * 4) ||
+                       overlap(out[i], out_bytes[i], X, M * n * 4) || overlap(out[i], out_bytes[i], B, r * n * 4);
         k = 0;
+        if (dX && in_turn) { split[k] = 1; g[k++] = gemm(dT, (const float*)B, (float*)dX, M, n, r, r, n, n, 0, 0, 0); }
         if (dA) { split[k] = w.split_A; g[k++] = grad_A_f32((const float*)dY, Tp, dA, M, m, r, acc); }
         if (dB) { split[k] = w.split_B; g[k++] = grad_B_f32(dT, (const float*)X, dB, M, n, r, acc); }
-        if (dX) { split[k] = 1; g[k++] = gemm(dT, (const float*)B, (float*)dX, M, n, r, r, n, n, 0, 0, 0); }
-        return launch_gemm_f32(g, split, k, (float*)(ws + w.partials), s) == hipSuccess ? ABT_OK : ABT_EHIP;
+        if (dX && !in_turn) { split[k] = 1; g[k++] = gemm(dT, (const float*)B, (float*)dX, M, n, r, r, n, n, 0, 0, 0); }
+        float* const partials = (float*)(ws + w.partials);
+        if (!in_turn) return launch_gemm_f32(g, split, k, partials, s) == hipSuccess ? ABT_OK : ABT_EHIP;
+        for (int i = 0; i < k; ++i)
+            if (launch_gemm_f32(g + i, split + i, 1, partials, s) != hipSuccess) return ABT_EHIP;
+        return ABT_OK;
     }
 
     const BwdLayout w = bwd_layout_bf16(M, m, n, r);

@@ -47,3 +47,34 @@ def test_convolution_gradient_over_the_activation():
     buf = act.clone()
     got = abt.lr_conv_bwd(dY, buf, T, A, B, 3, 3, dB=over(buf, (r, 9 * C)), **kw)[2]
     assert torch.equal(got, want)
+
+
+def near(a, b, terms=2000):
+    # The same fp32 products in a launch of another tile form.  Sums of up to `terms` products in another order: the
+    # roundings of the partial sums walk at random, sqrt(terms) 2^-24 in norm per product; two products and both sides: 4.
+    assert float((a - b).norm() / b.norm()) < 4 * terms ** 0.5 * 2.0 ** -24
+
+
+@pytest.mark.parametrize("M,m,n,r", [(64, 256, 256, 32), (300, 130, 130, 20), (2000, 256, 256, 32)])
+def test_fp32_backward_over_its_inputs(M, m, n, r):
+    f32 = torch.float32
+    X, dY, A, B = rnd(1, M, n, dtype=f32), rnd(2, M, m, dtype=f32), rnd(3, m, r, dtype=f32), rnd(4, r, n, dtype=f32)
+    T = abt.lr_linear_fwd(X, A, B)[1]
+    want = abt.lr_linear_bwd(dY, X, T, A, B)
+    # dB over B: dX is computed from B first; and added to it in place, a step of plain descent
+    Bc = B.clone()
+    got = abt.lr_linear_bwd(dY, X, T, A, Bc, dB=Bc)
+    near(got[0], want[0]), near(got[1], want[1]), near(Bc, want[2])
+    Bc = B.clone()
+    near(abt.lr_linear_bwd(dY, X, T, A, Bc, dB=Bc, accumulate=True, need_dA=False)[0], want[0])
+    near(Bc, B + want[2])
+    # dA over A, dX over dY (no dA) and over X (no dB)
+    Ac = A.clone()
+    got = abt.lr_linear_bwd(dY, X, T, Ac, B, dA=Ac)
+    near(got[0], want[0]), near(Ac, want[1]), near(got[2], want[2])
+    d = dY.clone()
+    got = abt.lr_linear_bwd(d, X, T, A, B, dX=d, need_dA=False)
+    near(d, want[0]), near(got[2], want[2])
+    x = X.clone()
+    got = abt.lr_linear_bwd(dY, x, T, A, B, dX=x, need_dB=False)
+    near(x, want[0]), near(got[1], want[1])
