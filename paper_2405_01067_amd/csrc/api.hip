@@ -84,6 +84,12 @@ bool use_narrow(int64_t rows, int p, int q, int R) {
     return rows > 32768 && (R == 32 ? p >= q : R <= 128);
 }
 
+// Work-groups that share a row block all read its rows of Xin, and the first of them to finish writes its share of the
+// output: not with an output over Xin (the other kernels have one reader per row block, which reads before it writes).
+bool narrow_in_place(const ChainProblem& c, int64_t M, int p, int q, int R) {
+    return overlap(c.Xin, M * p * 2, c.Yout, M * q * 2) || overlap(c.Xin, M * p * 2, c.Tout, M * R * 2);
+}
+
 // From an image: a lane has one pixel for the whole kernel, while the loader waves of the other kernels compute
 // a range check per 16 bytes.  Forward, us, this kernel / the better of the others, r = 64: 56 x 56 x 64
 // (200704 rows) 50 / 110, 28 x 28 x 128 (50176 rows) 29 / 43; with few row blocks the other kernels' deeper prefetch
@@ -120,7 +126,8 @@ hipError_t chain(const void* Xin, const void* P, const void* Q, void* Yout, void
                  int64_t M, int p, int q, int R, hipStream_t s) {
     if (use_narrow(M, p, q, R)) {
         const ChainProblem one{Xin, P, Q, Yout, Tout};
-        return launch_chain4_bf16(&one, 1, M, p, q, R, narrow_rows(M), narrow_parts(ceil_div(M, narrow_rows(M)), p, q, Yout != nullptr), s);
+        const int rows = narrow_rows(M), parts = narrow_parts(ceil_div(M, rows), p, q, Yout != nullptr);
+        if (parts == 1 || !narrow_in_place(one, M, p, q, R)) return launch_chain4_bf16(&one, 1, M, p, q, R, rows, parts, s);
     }
     const ChainShape sh = choose_chain_shape(M, p, q, R, Yout != nullptr, true);
     if (sh.rows == 128) return launch_chain2_tall_bf16(Xin, P, Q, Yout, Tout, M, p, q, R, sh.parts, s);
@@ -683,9 +690,14 @@ hipError_t chain_grouped(const ChainProblem* pr, int G, int64_t M, int p, int q,
         }
         if (n == 0) continue;
         if (use_narrow(n * M, p, q, R)) {
-            const hipError_t e = launch_chain4_bf16(sel, n, M, p, q, R, narrow_rows(n * M), narrow_parts(n * ceil_div(M, narrow_rows(n * M)), p, q, second != 0), s);
-            if (e != hipSuccess) return e;
-            continue;
+            const int rows = narrow_rows(n * M), parts = narrow_parts(n * ceil_div(M, rows), p, q, second != 0);
+            bool in_place = false;
+            for (int g = 0; g < n && parts > 1; ++g) in_place |= narrow_in_place(sel[g], M, p, q, R);
+            if (!in_place) {
+                const hipError_t e = launch_chain4_bf16(sel, n, M, p, q, R, rows, parts, s);
+                if (e != hipSuccess) return e;
+                continue;
+            }
         }
         const hipError_t e = launch_chain2_grouped_bf16(sel, n, M, p, q, R, chain_rows_for_groups(n, M, p, q, R), 1, s);
         if (e != hipSuccess) return e;

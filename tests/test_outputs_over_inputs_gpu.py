@@ -78,3 +78,35 @@ def test_fp32_backward_over_its_inputs(M, m, n, r):
     x = X.clone()
     got = abt.lr_linear_bwd(dY, x, T, A, B, dX=x, need_dB=False)
     near(x, want[0]), near(got[1], want[1])
+
+
+def close16(a, b):
+    # bf16 results of the same products summed in fp32 in another order: T and the result differ by single roundings
+    # of a few entries, below 2^-8 in norm
+    assert float((a.double() - b.double()).norm() / b.double().norm()) < 2.0 ** -8
+
+
+@pytest.mark.parametrize("M", [40, 700, 8192])
+@pytest.mark.parametrize("m,r", [(128, 32), (768, 96)])
+def test_layer_in_place(M, m, r):
+    # up to 8192 rows several work-groups share a row block; not when the block's input is overwritten
+    X, dY, A, B = rnd(1, M, m), rnd(2, M, m, std=1e-2), rnd(3, m, r, std=r ** -0.5), rnd(4, r, m, std=m ** -0.5)
+    Y, T = abt.lr_linear_fwd(X, A, B)
+    x = X.clone()
+    close16(abt.lr_linear_fwd(x, A, B, Y=x, save_T=False)[0], Y)
+    xs = [X.clone(), X.clone()]
+    for (y, t) in abt.lr_linear_fwd_grouped([dict(X=x, Y=x, A=A, B=B) for x in xs]):
+        close16(y, Y), close16(t, T)
+    want = abt.lr_linear_bwd(dY, X, T, A, B, need_dA=False)
+    d = dY.clone()
+    got = abt.lr_linear_bwd(d, X, T, A, B, need_dA=False, dX=d)
+    close16(d, want[0]), close16(got[2], want[2])
+
+
+def test_saved_product_over_the_input():
+    M, m, r = 700, 1024, 64                      # T and X have the same shape
+    X, A, B = rnd(1, M, r), rnd(2, m, r, std=r ** -0.5), rnd(3, r, r, std=r ** -0.5)
+    Y, T = abt.lr_linear_fwd(X, A, B)
+    x = X.clone()
+    y, t = abt.lr_linear_fwd(x, A, B, T=x)
+    close16(y, Y), close16(t, T)
