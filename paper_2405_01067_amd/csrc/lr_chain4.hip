@@ -27,6 +27,7 @@
 #include <atomic>
 
 #include "common.h"
+#include "grid_window.h"
 
 namespace abt {
 
@@ -428,8 +429,8 @@ hipError_t launch_chain4_gather_bf16(const GatherProblem* problems, int n, int q
             return hipErrorInvalidValue;
         // 32-bit offsets inside a row block's window of the image and of the result
         const int64_t reach = (int64_t)g.kh * g.W + g.kw;
-        const int64_t span = (int64_t)g.mul * g.mul * (rows + 2 * g.RW + 2) + 2 * (int64_t)g.mul * g.W + 2 * reach;
-        const int64_t ospan = (int64_t)g.omul * g.omul * (rows + 2 * g.RW + 2) + 2 * (int64_t)g.omul * g.OW;
+        const int64_t span = grid_window(rows, g.RH, g.RW, g.mul, g.H, g.W) + 2 * reach;
+        const int64_t ospan = grid_window(rows, g.RH, g.RW, g.omul, g.OH, g.OW);
         if (span * g.Cin * 2 >= kBufMaxBytes || ospan * t_pitch * 2 >= kBufMaxBytes || (int64_t)R * p * 2 >= kBufMaxBytes) return hipErrorInvalidValue;
         if (per && (c.M / per) * g.H * g.W > 0x7fffffff) return hipErrorInvalidValue;
         a.e[i] = C4Entry{(const uint16_t*)c.image, (const uint16_t*)c.P, (const uint16_t*)c.Q, (uint16_t*)c.Yout, (uint16_t*)c.Tout, c.M, (int)p, g};

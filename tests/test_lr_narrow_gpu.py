@@ -85,3 +85,22 @@ def test_convolution_agrees_with_the_kernels_for_all_ranks(N, H, W, C, m, r, kh,
         assert rel(host(a), host(b)) < TOL_ORDER, name
     # pixels that no window reaches get exact zeros from both
     assert torch.equal(got[2] == 0, want[2] == 0)
+
+
+@pytest.mark.parametrize("C", [1 << 19, 1 << 20])
+def test_activation_gradient_of_many_tiny_images_with_wide_rows(C):
+    # 3 x 3 images, 1 x 1 window, stride 2: a row block of the odd pixels spans as many images as it has rows, and at 2^20
+    # channels 128 of them are beyond 32-bit offsets (the kernels for all ranks take the call)
+    N, side, m, r = 128, 3, 64, 32
+    g = torch.Generator(device="cuda").manual_seed(9)
+    rnd = lambda shape, std: (torch.randn(shape, generator=g, device="cuda") * std).to(BF)
+    B, A, dY = rnd((r, C), r ** -0.5), rnd((m, r), r ** -0.5), rnd((N * 4, m), 1.0)
+    act = torch.zeros((N, side, side, C), dtype=BF, device="cuda")
+    dAct = torch.full_like(act, 7.0)
+    abt.lr_conv_bwd(dY, act, None, A, B, 1, 1, need_dA=False, need_dB=False, dAct=dAct, stride=2)
+    even = dAct[:, ::2, ::2, :].reshape(N * 4, C)
+    dT = (dY.float() @ A.float()).to(BF).float()
+    for i in range(0, N * 4, 64):                        # in slices: the product in fp32 is 2 GB
+        want = dT[i:i + 64] @ B.float()
+        assert float((even[i:i + 64].float() - want).norm() / want.norm()) < TOL
+    assert not dAct[:, 1].any() and not dAct[:, :, 1].any()
