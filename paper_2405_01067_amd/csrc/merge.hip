@@ -987,21 +987,21 @@ hipError_t launch_identity_f32(float* dst, int K, hipStream_t s) {
 
 constexpr int kWorkspaceMagic = 0x41425431;
 
-hipError_t merge_read_info(const void* workspace, int first, int count, int32_t* out, hipStream_t s) {
+hipError_t merge_layer_count(const void* workspace, int* layers, hipStream_t s) {
     hipError_t e = hipStreamSynchronize(s);
     if (e != hipSuccess) return e;
-    // the info table follows the 256-byte header slot (see make_plan)
-    const size_t bytes = 256 + sizeof(int) * kInfoInts * ((size_t)first + count);
-    std::vector<char> image(bytes);
-    e = hipMemcpy(image.data(), workspace, 256, hipMemcpyDeviceToHost);
+    int hdr[4] = {0, 0, 0, 0};
+    e = hipMemcpy(hdr, workspace, sizeof(hdr), hipMemcpyDeviceToHost);
     if (e != hipSuccess) return e;
-    int hdr[4];
-    memcpy(hdr, image.data(), sizeof(hdr));
-    if (hdr[0] != kWorkspaceMagic || hdr[1] - count < first) return hipErrorInvalidValue;
-    e = hipMemcpy(image.data() + 256, (const char*)workspace + 256, bytes - 256, hipMemcpyDeviceToHost);
-    if (e != hipSuccess) return e;
-    memcpy(out, image.data() + 256 + sizeof(int) * kInfoInts * first, sizeof(int) * kInfoInts * count);
+    if (hdr[0] != kWorkspaceMagic || hdr[1] < 1) return hipErrorInvalidValue;
+    *layers = hdr[1];
     return hipSuccess;
+}
+
+hipError_t merge_read_info(const void* workspace, int first, int count, int32_t* out) {
+    // the info table follows the 256-byte header slot (see make_plan)
+    return hipMemcpy(out, (const char*)workspace + 256 + sizeof(int) * kInfoInts * (size_t)first,
+                     sizeof(int) * kInfoInts * (size_t)count, hipMemcpyDeviceToHost);
 }
 
 hipError_t merge_run(const abt_merge_desc* layers, const MergeSide* identity, int L, void* workspace, int max_sweeps, hipStream_t s) {
