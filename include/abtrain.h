@@ -112,8 +112,10 @@ size_t lr_linear_bwd_workspace_bytes(int64_t M, int64_t m, int64_t n, int64_t r,
  * array of ABT_STATIC_SCRATCH_BYTES inside the library's device code (each GPU the library
  * runs on holds its own copy until the process ends).  The call allocates nothing, on the
  * host or on the device, and frees nothing.
- * A shape for which lr_linear_bwd_workspace_bytes() exceeds ABT_STATIC_SCRATCH_BYTES is
- * rejected with ABT_ETOOLARGE before anything is enqueued.
+ * ABT_BF16: a shape for which lr_linear_bwd_workspace_bytes() exceeds ABT_STATIC_SCRATCH_BYTES is
+ * rejected with ABT_ETOOLARGE before anything is enqueued.  ABT_F32: a shape whose dT and T
+ * (8 M r bytes) do; where the partial sums of dA / dB do not fit beside them, the rows are split less
+ * than in lr_linear_bwd (another summation order of the fp32 sums, and slower).
  * All calls on one GPU share that GPU's array: two calls whose kernels may overlap (different
  * streams, different host threads) race on it and give undefined gradients; calls on one
  * stream are safe back to back.  Nothing in the array has to start at zero, and nothing a

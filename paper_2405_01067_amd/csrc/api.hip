@@ -173,8 +173,9 @@ GemmF32 gemm(const float* A, const float* B, float* C, int64_t P, int64_t Q, int
 }
 
 // fp32 backward: dT, T (each M x r) and the partial sums of the factor gradients, whose contraction over
-// the batch is split over work-groups.  The split only takes what is left of the static scratch array,
-// so that every shape lr_linear_bwd_static serves without it is served with it.
+// the batch is split over work-groups.  `limit`: in the static scratch array the split only takes what dT and T
+// leave of it, so that every shape that fits without one is served; a workspace of the caller's has room for the
+// split that fills the chip (whole backward, 256 x 256, r = 256, 32768 rows: 285 us; 783 without a split).
 struct BwdLayoutF32 { size_t dT, T, partials, total; int split_A, split_B; };
 
 GemmF32 grad_A_f32(const float* dY, const float* T, float* dA, int64_t M, int64_t m, int64_t r, int acc) {
@@ -184,7 +185,7 @@ GemmF32 grad_B_f32(const float* dT, const float* X, float* dB, int64_t M, int64_
     return gemm(dT, X, dB, r, n, M, r, n, n, 1, 0, acc);
 }
 
-BwdLayoutF32 bwd_layout_f32(int64_t M, int64_t m, int64_t n, int64_t r) {
+BwdLayoutF32 bwd_layout_f32(int64_t M, int64_t m, int64_t n, int64_t r, size_t limit) {
     BwdLayoutF32 w{};
     const size_t each = align_up((size_t)M * r * 4, 256);
     w.dT = 0; w.T = each; w.partials = 2 * each;
@@ -192,7 +193,7 @@ BwdLayoutF32 bwd_layout_f32(int64_t M, int64_t m, int64_t n, int64_t r) {
     w.split_A = gemm_f32_splits(a);
     w.split_B = gemm_f32_splits(b);
     auto bytes = [&] { return gemm_f32_partial_bytes(a, w.split_A) + gemm_f32_partial_bytes(b, w.split_B); };
-    while (w.partials <= ABT_STATIC_SCRATCH_BYTES && w.partials + bytes() > ABT_STATIC_SCRATCH_BYTES) {
+    while (w.partials + bytes() > limit && (w.split_A > 1 || w.split_B > 1)) {
         w.split_A = w.split_A > 1 ? w.split_A / 2 : 1;
         w.split_B = w.split_B > 1 ? w.split_B / 2 : 1;
     }
@@ -221,6 +222,11 @@ BwdLayout bwd_layout_bf16(int64_t M, int64_t m, int64_t n, int64_t r) {
     w.partials = take(part);
     w.total = off;
     return w;
+}
+
+// what a backward needs if it may use `limit` bytes at most (more than that: it does not fit)
+size_t bwd_bytes(int64_t M, int64_t m, int64_t n, int64_t r, int dt, size_t limit) {
+    return dt == ABT_F32 ? bwd_layout_f32(M, m, n, r, limit).total : bwd_layout_bf16(M, m, n, r).total;
 }
 
 int check_merge_layer(const abt_merge_desc& d) {
@@ -535,8 +541,7 @@ size_t lr_linear_fwd_workspace_bytes(int64_t M, int64_t m, int64_t n, int64_t r,
 
 size_t lr_linear_bwd_workspace_bytes(int64_t M, int64_t m, int64_t n, int64_t r, int dt) {
     if (check_lr_shapes(M, m, n, r, dt) != ABT_OK) return 0;
-    if (dt == ABT_F32) return bwd_layout_f32(M, m, n, r).total;
-    return bwd_layout_bf16(M, m, n, r).total;
+    return bwd_bytes(M, m, n, r, dt, SIZE_MAX);
 }
 
 int lr_linear_fwd(const void* X, const void* A, const void* B, void* Y, void* T_save,
@@ -563,17 +568,18 @@ int lr_linear_fwd(const void* X, const void* A, const void* B, void* Y, void* T_
     return ABT_OK;
 }
 
-int lr_linear_bwd(const void* dY, const void* X, const void* T, const void* A, const void* B,
-                  void* dX, float* dA, float* dB,
-                  int64_t M, int64_t m, int64_t n, int64_t r, int dt, int accumulate,
-                  void* workspace, size_t workspace_bytes, void* stream) {
+namespace {
+int linear_bwd(const void* dY, const void* X, const void* T, const void* A, const void* B,
+               void* dX, float* dA, float* dB,
+               int64_t M, int64_t m, int64_t n, int64_t r, int dt, int accumulate,
+               void* workspace, size_t workspace_bytes, size_t limit, void* stream) {
     int st = check_lr_shapes(M, m, n, r, dt);
     if (st != ABT_OK) return st;
     if (!dY || !X || !A || !B) return ABT_EINVAL;
     if (!aligned(dY, 16) || !aligned(X, 16) || !aligned(T, 16) || !aligned(A, 16) || !aligned(B, 16) ||
         !aligned(dX, 16) || !aligned(dA, 16) || !aligned(dB, 16))
         return ABT_EALIGN;
-    if (!workspace || workspace_bytes < lr_linear_bwd_workspace_bytes(M, m, n, r, dt)) return ABT_EWORKSPACE;
+    if (!workspace || workspace_bytes < bwd_bytes(M, m, n, r, dt, limit)) return ABT_EWORKSPACE;
     if (!aligned(workspace, 256)) return ABT_EALIGN;
     hipStream_t s = (hipStream_t)stream;
     char* ws = (char*)workspace;
@@ -582,7 +588,7 @@ int lr_linear_bwd(const void* dY, const void* X, const void* T, const void* A, c
 
     if (dt == ABT_F32) {
         // two launches (and one that adds the split sums): first what depends on the inputs alone, then the rest
-        const BwdLayoutF32 w = bwd_layout_f32(M, m, n, r);
+        const BwdLayoutF32 w = bwd_layout_f32(M, m, n, r, limit);
         float* dT = (float*)(ws + w.dT);
         const float* Tp = (const float*)T;
         GemmF32 g[3];
@@ -639,6 +645,14 @@ int lr_linear_bwd(const void* dY, const void* X, const void* T, const void* A, c
         if (e != hipSuccess) return ABT_EHIP;
     }
     return ABT_OK;
+}
+}  // namespace
+
+int lr_linear_bwd(const void* dY, const void* X, const void* T, const void* A, const void* B,
+                  void* dX, float* dA, float* dB,
+                  int64_t M, int64_t m, int64_t n, int64_t r, int dt, int accumulate,
+                  void* workspace, size_t workspace_bytes, void* stream) {
+    return linear_bwd(dY, X, T, A, B, dX, dA, dB, M, m, n, r, dt, accumulate, workspace, workspace_bytes, SIZE_MAX, stream);
 }
 
 // ------------------------------------------------------------------ G emulated groups per launch
@@ -843,12 +857,12 @@ int lr_linear_bwd_static(const void* dY, const void* X, const void* T, const voi
                          int64_t M, int64_t m, int64_t n, int64_t r, int dt, int accumulate, void* stream) {
     const int st = check_lr_shapes(M, m, n, r, dt);
     if (st != ABT_OK) return st;
-    if (lr_linear_bwd_workspace_bytes(M, m, n, r, dt) > (size_t)ABT_STATIC_SCRATCH_BYTES) return ABT_ETOOLARGE;
+    constexpr size_t limit = ABT_STATIC_SCRATCH_BYTES;
+    if (bwd_bytes(M, m, n, r, dt, limit) > limit) return ABT_ETOOLARGE;
     void* ws = nullptr;
     const int sp = static_scratch(&ws);
     if (sp != ABT_OK) return sp;
-    return lr_linear_bwd(dY, X, T, A, B, dX, dA, dB, M, m, n, r, dt, accumulate, ws,
-                         (size_t)ABT_STATIC_SCRATCH_BYTES, stream);
+    return linear_bwd(dY, X, T, A, B, dX, dA, dB, M, m, n, r, dt, accumulate, ws, limit, limit, stream);
 }
 
 size_t ab_merge_batched_workspace_bytes(const abt_merge_desc* layers, int L) {

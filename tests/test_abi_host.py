@@ -61,6 +61,16 @@ def test_workspace_queries(lib):
     assert lib.ab_merge_workspace_bytes(0, 10, 10, 32, 32, 0) == 0
 
 
+def test_fp32_backward_workspace_holds_the_full_split(lib):
+    # beside dT and T the partial sums of the split that fills the chip, whatever the static scratch array could hold
+    need = lambda M, m, n, r: lib.lr_linear_bwd_workspace_bytes(M, m, n, r, abt.ABT_F32) - 2 * (M * r * 4 + 255) // 256 * 256
+    for m, n, r in ((256, 256, 256), (768, 768, 256)):
+        partials = need(20000, m, n, r)
+        assert partials > 0
+        for M in (28000, 32000, 32767, 32768, 32769, 100000):
+            assert need(M, m, n, r) == partials
+
+
 def test_argument_validation_without_device(lib):
     buf = ctypes.create_string_buffer(4096 + 256)
     base = (ctypes.addressof(buf) + 255) // 256 * 256          # fake, aligned, never dereferenced

@@ -73,3 +73,29 @@ def test_split_fits_the_static_scratch():
     dT, dT_err = dYd @ Ad, (dYd.abs() @ Ad.abs()) * (m + 2) * EPS
     err = (M + 4) * EPS * (dT.abs().T @ Xd.abs()) + (dT_err.T @ Xd.abs()) * (1 + 1e-3)
     assert bool(((dB.double() - dT.T @ Xd).abs() <= err).all())
+
+
+@pytest.mark.parametrize("M", [24575, 28000, 32767, 32768, 32769])
+def test_split_beside_the_static_scratch(M):
+    """256 x 256 x 256: up to 24575 rows the partial sums of 32 splits fit the 64 MiB beside dT and T, at 28000 those of
+    16, at 32767 none, and 32769 rows do not fit; a caller's workspace always has room for 32."""
+    m = n = r = 256
+    g = torch.Generator(device="cuda").manual_seed(M)
+    X, dY, A, B = rnd(g, M, n), rnd(g, M, m), rnd(g, m, r), rnd(g, r, n)
+    dX, dA, dB = abt.lr_linear_bwd(dY, X, None, A, B)
+    out = [torch.full_like(t, 7.0) for t in (dX, dA, dB)]
+    if M > 32768:
+        with pytest.raises(abt.AbtError):
+            abt.lr_linear_bwd_static(dY, X, None, A, B, *out)
+    else:
+        abt.lr_linear_bwd_static(dY, X, None, A, B, *out)
+        assert torch.equal(out[0], dX)
+        if M <= 24575:
+            assert torch.equal(out[1], dA) and torch.equal(out[2], dB)
+    Xd, dYd, Ad, Bd = (t.double() for t in (X, dY, A, B))
+    T, dT = Xd @ Bd.T, dYd @ Ad
+    T_err, dT_err = (Xd.abs() @ Bd.abs().T) * (n + 2) * EPS, (dYd.abs() @ Ad.abs()) * (m + 2) * EPS
+    for got in ((dA, dB), out[1:]) if M <= 32768 else ((dA, dB),):
+        for o, a, b, err in ((got[0], dYd, T, dYd.abs().T @ T_err), (got[1], dT, Xd, dT_err.T @ Xd.abs())):
+            bound = (M + 4) * EPS * (a.abs().T @ b.abs()) + err * (1 + 1e-3)
+            assert bool(((o.double() - a.T @ b).abs() <= bound).all())
