@@ -64,24 +64,41 @@ int narrow_rows(int64_t M) {
     const int64_t per_cu = ceil_div(M, 256 * 128);
     return (int)(ceil_div(ceil_div(M, 256 * per_cu), 4) * 4);
 }
-// Where the narrow-rank kernel is taken for a matrix operand (times of a forward in us, this kernel / what was taken
-// before, inputs not in the last-level cache):
-//   at most 8192 rows and p <= q: its work-groups can share a row block's output tiles.  197 x 768 -> 3072: 12 / 25
-//     at r = 96, 17 / 30 at r = 192; 6304 rows 24 / 32, 33 / 38; 768 -> 768: 12 / 13 at r = 96, but 19 / 15 at
-//     r = 192, hence 2 p <= q beyond r = 96.  (197 x 3072 -> 768: 32 / 22.)
-//   more than 32768 rows, i.e. at least two work-groups per compute unit, r <= 160: 39597 x 768 -> 3072 / 3072 -> 768 /
-//     768 -> 768 at r = 96: 69 / 83, 82 / 94, 40 / 46; r = 64: 65 / 68, 80 / 89, 33 / 45; 100000 rows, r = 64: 164 / 171,
-//     160 / 171, 75 / 82; r = 128: 188 / 179, 195 / 201, 84 / 94; r = 160: 220 / 241, 225 / 291, 93 / 136.
-//     (r = 192: 241 / 213, 246 / 226, 104 / 100.)  r = 32 only where p >= q: 153 / 150, but 149 / 161, 61 / 70.
-//     One work-group alone on a compute unit waits for its loads (12608 rows, r = 96: 44 / 28, 45 / 36, 23 / 20); at
-//     r = 160, where the other kernel has 64-row work-groups only, two rounds of those are slower still: from 16384
-//     rows on (17000: 59 / 47, 60 / 85, 29 / 41).
+// Where the narrow-rank kernel is taken for a matrix operand (times of a forward in us, this kernel / the better of the
+// others, inputs not in the last-level cache):
+//   At most 8192 rows: its work-groups can share a row block's output tiles, the more of them the better, so p <= q.
+//     768 -> 3072: 197 rows 12 / 25 at r = 96, 18 / 30 at r = 192; 6304 rows 24 / 32, 33 / 38.  With 2 p <= q it pays
+//     at any rank, until the p / 64 slabs that each of them repeats are too many (2048 -> 4096, 8192 rows: 48 / 41 at
+//     r = 128, 59 / 48 at r = 192; 1536 -> 3072, 8000 rows, r = 32: 29 / 30, but T alone 4 us the slower).  Below that
+//     only at r <= 96 (768 -> 768, r = 192: 19 / 15): 768 -> 768 with 197 rows 12 / 13 at r = 96, 8 / 10 at r = 32; with 8192
+//     rows 18 / 19, 15 / 14; 1536 -> 1536 with 8192 rows 29 / 28, 27 / 25 at r = 64, 25 / 22 at r = 32.
+//   8192 to 32768 rows: one work-group alone on a compute unit waits for its loads (12608 rows, r = 96: 44 / 28, 45 / 36,
+//     23 / 20).  Only at r = 160, where the others have 64-row work-groups: 17000 rows, 3072 -> 768 60 / 85, 768 -> 768
+//     29 / 41, but 768 -> 3072 59 / 47, from 45000 rows on 106 / 107; 3072 -> 3072 103 / 94, 25000 rows the same.
+//   More than 32768 rows, at least two work-groups per compute unit, r <= 128.  768 -> 3072 / 3072 -> 768 / 768 -> 768
+//     with 39597 rows: r = 64 66 / 68, 79 / 89, 33 / 46; r = 96 68 / 76, 82 / 95, 34 / 44; with 100864 rows 164 / 176, 168 / 176,
+//     - and 186 / 175, 179 / 194, -: at r = 96 not for the widest layers there (1536 -> 1536 155 / 146).  r = 128, where the
+//     others are better at long contractions and wide outputs: 33000 rows 82 / 69, 88 / 114, 42 / 56, 3072 -> 3072
+//     137 / 132; 65536 rows 120 / 115, 124 / 118, 50 / 52.  r = 32 only with p >= q (50432 rows: 75 / 80 and 31 / 36,
+//     768 -> 3072 91 / 86).  (r = 192, 100000 rows: 241 / 213, 246 / 226, 104 / 100.)
 // (The rule does not ask for the second stage: a T that the backward computes again comes from the same kernel.)
 bool use_narrow(int64_t rows, int p, int q, int R) {
     if (g_chain_rows.load() != 0 || g_chain_parts.load() != 0 || !chain4_supports(R, p, q)) return false;
-    if (rows <= 8192) return R <= 96 ? p <= q : 2 * p <= q;
-    if (R == 160) return rows > 16384;
-    return rows > 32768 && (R == 32 ? p >= q : R <= 128);
+    if (rows <= 8192) {
+        if (2 * p <= q) return p <= 768 || rows <= 4096 || (p <= 1536 && R >= 96);
+        if (p > q || R > 96) return false;
+        if (p <= 512 || (R == 96 && rows <= 2048)) return true;
+        return p <= 1024 && rows <= (R == 32 ? 1024 : R == 64 ? 4096 : 8192);
+    }
+    if (R == 160) return rows > 16384 && (q <= 1536 || rows > 45056 || (p >= q && rows > 24576));
+    if (rows <= 32768) return false;
+    switch (R) {
+        case 32: return p >= q;
+        case 64: return true;
+        case 96: return rows <= 65536 || q <= 1024 || p + q < 3072;
+        case 128: return p >= q ? p <= 1024 || (rows <= 49152 && q <= 1536) : q <= 1024;
+        default: return false;
+    }
 }
 
 // Work-groups that share a row block all read its rows of Xin, and the first of them to finish writes its share of the
