@@ -101,10 +101,41 @@ bool use_narrow(int64_t rows, int p, int q, int R) {
     }
 }
 
-// Work-groups that share a row block all read its rows of Xin, and the first of them to finish writes its share of the
-// output: not with an output over Xin (the other kernels have one reader per row block, which reads before it writes).
-bool narrow_in_place(const ChainProblem& c, int64_t M, int p, int q, int R) {
-    return overlap(c.Xin, M * p * 2, c.Yout, M * q * 2) || overlap(c.Xin, M * p * 2, c.Tout, M * R * 2);
+// Columns of T per work-group where only T is wanted: nothing shares a row block's output tiles then, and at wide ranks
+// a slab of the whole P takes longer than the other kernels' loaders (T of 197 rows, p = 1536, r = 192, and dA: 36 us,
+// 22 with 32 columns each, 26 before; p = 768, r = 96: 18.6, 16.2, 18.8).  The sums of a column do not change.
+int narrow_cols(int n, int64_t row_blocks, int R) {
+    for (int c : {32, 64, 96})
+        if (R % c == 0 && n * (R / c) <= kChainMaxGroups && row_blocks * (R / c) <= 256) return c;
+    return R;
+}
+
+// Runs n problems of one shape, all with a second stage or none, in the narrow-rank kernel if the rule above says so.
+// Work-groups that share a row block all read its rows of Xin, and the first of them to finish writes: not with an output
+// over Xin (the other kernels have one reader per row block, which reads before it writes).
+bool narrow_chain(const ChainProblem* problems, int n, int64_t M, int p, int q, int R, hipStream_t s, hipError_t* e) {
+    if (!use_narrow(n * M, p, q, R)) return false;
+    const bool second = problems[0].Yout != nullptr;
+    const int rows = narrow_rows(n * M);
+    const int64_t blocks = n * ceil_div(M, rows);
+    const int parts = narrow_parts(blocks, p, q, second);
+    int cols = second || n * M > 8192 ? R : narrow_cols(n, blocks, R);
+    bool in_place = false;
+    for (int g = 0; g < n; ++g)
+        in_place |= overlap(problems[g].Xin, M * p * 2, problems[g].Yout, M * q * 2) ||
+                    overlap(problems[g].Xin, M * p * 2, problems[g].Tout, M * R * 2);
+    if (in_place && parts > 1) return false;
+    if (in_place) cols = R;
+    ChainProblem share[kChainMaxGroups];
+    int k = 0;
+    for (int g = 0; g < n; ++g) {
+        const ChainProblem& c = problems[g];
+        share[k++] = c;
+        for (int c0 = cols; c0 < R; c0 += cols)
+            share[k++] = ChainProblem{c.Xin, (const char*)c.P + (size_t)c0 * p * 2, nullptr, nullptr, (char*)c.Tout + (size_t)c0 * 2};
+    }
+    *e = launch_chain4_bf16(share, k, M, p, q, cols, R, rows, parts, s);
+    return true;
 }
 
 // From an image: a lane has one pixel for the whole kernel, while the loader waves of the other kernels compute
@@ -141,11 +172,9 @@ hipError_t chain_gather(const void* image, const PatchGeom& g, const void* P, co
 
 hipError_t chain(const void* Xin, const void* P, const void* Q, void* Yout, void* Tout,
                  int64_t M, int p, int q, int R, hipStream_t s) {
-    if (use_narrow(M, p, q, R)) {
-        const ChainProblem one{Xin, P, Q, Yout, Tout};
-        const int rows = narrow_rows(M), parts = narrow_parts(ceil_div(M, rows), p, q, Yout != nullptr);
-        if (parts == 1 || !narrow_in_place(one, M, p, q, R)) return launch_chain4_bf16(&one, 1, M, p, q, R, rows, parts, s);
-    }
+    const ChainProblem one{Xin, P, Q, Yout, Tout};
+    hipError_t e;
+    if (narrow_chain(&one, 1, M, p, q, R, s, &e)) return e;
     const ChainShape sh = choose_chain_shape(M, p, q, R, Yout != nullptr, true);
     if (sh.rows == 128) return launch_chain2_tall_bf16(Xin, P, Q, Yout, Tout, M, p, q, R, sh.parts, s);
     if (chain2_supports(R, p, q)) return launch_chain2_bf16(Xin, P, Q, Yout, Tout, M, p, q, R, s);
@@ -720,17 +749,9 @@ hipError_t chain_grouped(const ChainProblem* pr, int G, int64_t M, int p, int q,
             if ((has2 && second) || (!has2 && !second && pr[g].Tout)) sel[n++] = pr[g];
         }
         if (n == 0) continue;
-        if (use_narrow(n * M, p, q, R)) {
-            const int rows = narrow_rows(n * M), parts = narrow_parts(n * ceil_div(M, rows), p, q, second != 0);
-            bool in_place = false;
-            for (int g = 0; g < n && parts > 1; ++g) in_place |= narrow_in_place(sel[g], M, p, q, R);
-            if (!in_place) {
-                const hipError_t e = launch_chain4_bf16(sel, n, M, p, q, R, rows, parts, s);
-                if (e != hipSuccess) return e;
-                continue;
-            }
-        }
-        const hipError_t e = launch_chain2_grouped_bf16(sel, n, M, p, q, R, chain_rows_for_groups(n, M, p, q, R), 1, s);
+        hipError_t e;
+        if (!narrow_chain(sel, n, M, p, q, R, s, &e))
+            e = launch_chain2_grouped_bf16(sel, n, M, p, q, R, chain_rows_for_groups(n, M, p, q, R), 1, s);
         if (e != hipSuccess) return e;
     }
     return hipSuccess;

@@ -148,9 +148,10 @@ hipError_t launch_chain2_tall_gather_bf16(const void* image, const PatchGeom& g,
                                      void* Yout, void* Tout, int t_pitch, int64_t M, int q, int R, hipStream_t s);
 // The same chain for R <= 192 with work-groups of four waves and `rows` rows (a multiple of four, at most 128),
 // two or three per compute unit; p, q multiples of 64, at most 2^20.  With parts > 1 a row block is shared by that many work-groups, each
-// repeating stage 1 and doing its share of the 64-column output tiles (parts <= q / 64, second stage only).
+// repeating stage 1 and doing its share of the 64-column output tiles (parts <= q / 64, second stage only).  Rows of Tout
+// are t_pitch elements apart (>= R).
 bool chain4_supports(int R, int p, int q);
-hipError_t launch_chain4_bf16(const ChainProblem* problems, int G, int64_t M, int p, int q, int R, int rows, int parts, hipStream_t s);
+hipError_t launch_chain4_bf16(const ChainProblem* problems, int G, int64_t M, int p, int q, int R, int t_pitch, int rows, int parts, hipStream_t s);
 // Its gathered form, up to kChainMaxGroups problems of one R and q in a launch.  As PatchGeom, but the
 // window may have any size and centre: tap (ky, kx) reads the image pixel sign (ky - cy, kx - cx) away from the
 // centre (mul y, mul x) of grid row (y, x); an image of height 0 reads as zeros everywhere.  Row (y, x) of

@@ -395,9 +395,9 @@ bool chain4_supports(int R, int p, int q) {
     return R >= 32 && R <= 192 && R % 32 == 0 && p >= 64 && p % 64 == 0 && q % 64 == 0 && p <= (1 << 20) && q <= (1 << 20);
 }
 
-hipError_t launch_chain4_bf16(const ChainProblem* problems, int G, int64_t M, int p, int q, int R, int rows, int parts, hipStream_t s) {
+hipError_t launch_chain4_bf16(const ChainProblem* problems, int G, int64_t M, int p, int q, int R, int t_pitch, int rows, int parts, hipStream_t s) {
     if (rows < 4 || rows > kMaxRows || rows % 4) return hipErrorInvalidValue;
-    if (!problems || G < 1 || G > kChainMaxGroups || parts < 1 || !chain4_supports(R, p, q) || M < 1) return hipErrorInvalidValue;
+    if (!problems || G < 1 || G > kChainMaxGroups || parts < 1 || !chain4_supports(R, p, q) || M < 1 || t_pitch < R) return hipErrorInvalidValue;
     C4Args a{};
     int64_t out_bytes = 0;
     for (int g = 0; g < G; ++g) {
@@ -407,7 +407,7 @@ hipError_t launch_chain4_bf16(const ChainProblem* problems, int G, int64_t M, in
         out_bytes = M * ((c.Yout ? q : 0) + R) * 2;
     }
     if (parts > q / 64) return hipErrorInvalidValue;
-    a.q = q; a.t_pitch = R; a.rows = rows; a.parts = parts; a.stream_out = out_bytes >= kStreamOutBytes;
+    a.q = q; a.t_pitch = t_pitch; a.rows = rows; a.parts = parts; a.stream_out = out_bytes >= kStreamOutBytes;
     return launch_any<false>(R, a, G, ceil_div(M, rows), s);
 }
 

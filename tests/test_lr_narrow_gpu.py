@@ -104,3 +104,34 @@ def test_activation_gradient_of_many_tiny_images_with_wide_rows(C):
         want = dT[i:i + 64] @ B.float()
         assert float((even[i:i + 64].float() - want).norm() / want.norm()) < TOL
     assert not dAct[:, 1].any() and not dAct[:, :, 1].any()
+
+
+@pytest.mark.parametrize("r", [32, 64, 96, 128, 160, 192])
+@pytest.mark.parametrize("M", [1, 197, 4000, 8192])
+def test_first_stage_alone_repeats_the_saved_product(M, r):
+    # T again, without a second stage: its columns are shared among work-groups, by 32, 64 or not at all
+    m, n = 640, 320
+    c = gen.lr_case(M=M, m=m, n=n, r=r, seed=M + r)
+    X, dY, A, B = (dev(c[k]) for k in ("X", "dY", "A", "B"))
+    T = abt.lr_linear_fwd(X, A, B)[1]
+    with_T = abt.lr_linear_bwd(dY, X, T, A, B, need_dX=False)
+    again = abt.lr_linear_bwd(dY, X, None, A, B, need_dX=False)
+    assert torch.equal(again[1], with_T[1]) and torch.equal(again[2], with_T[2])
+    # dT alone, p = m: 64 -> 64 and wider
+    dX, _, dB = abt.lr_linear_bwd(dY, X, T, A, B, need_dA=False)
+    assert torch.equal(dB, with_T[2])
+    assert rel(host(dX), orc.lr_linear_bwd(c["dY"], c["X"], c["A"], c["B"])[0]) < TOL
+
+
+def test_first_stage_of_several_groups_repeats_the_saved_products():
+    M, m, n, r = 500, 640, 320, 96
+    groups, outs = [], []
+    for g in range(3):
+        c = gen.lr_case(M=M, m=m, n=n, r=r, seed=70 + g)
+        groups.append({k: dev(c[k]) for k in ("X", "dY", "A", "B")})
+    for e, (_, T) in zip(groups, abt.lr_linear_fwd_grouped([{k: e[k] for k in ("X", "A", "B")} for e in groups])):
+        e["T"] = T
+    with_T = abt.lr_linear_bwd_grouped([dict(e, dA=True) for e in groups])
+    again = abt.lr_linear_bwd_grouped([dict(e, T=None, dA=True) for e in groups])
+    for a, b in zip(again, with_T):
+        assert torch.equal(a[1], b[1])
