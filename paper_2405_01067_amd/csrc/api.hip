@@ -152,7 +152,7 @@ bool narrow_gather(int64_t row_blocks, int mul, int p, int q, int R) {
 hipError_t chain_gather(const void* image, const PatchGeom& g, const void* P, const void* Q, void* Yout, void* Tout,
                         int t_pitch, int64_t M, int q, int R, hipStream_t s) {
     const int p = g.kh * g.kw * ((g.Cin + 63) / 64) * 64;
-    if (g.shift == 0 && narrow_gather(ceil_div(M, 128), g.mul, p, q, R)) {
+    if (g.sign > 0 && narrow_gather(ceil_div(M, 128), g.mul, p, q, R)) {
         const ChainGather cg{g.H, g.W, g.Cin, 0, g.kh, g.kw, g.sign, g.kh / 2, g.kw / 2, g.RH, g.RW, g.mul, 1, 0, 0, g.RH, g.RW};
         const GatherProblem one{image, P, Q, Yout, Tout, M, cg};
         const hipError_t e = launch_chain4_gather_bf16(&one, 1, q, R, t_pitch, narrow_rows(M), narrow_parts(ceil_div(M, narrow_rows(M)), p, q, Yout != nullptr), s);
@@ -374,6 +374,17 @@ ConvBwdLayout conv_bwd_layout(const abt_conv_geom& g, int64_t m, int64_t r) {
     return w;
 }
 
+// Where the narrow-rank kernel computes the activation gradient (a product without a second stage, one launch for all
+// parities and blocks of output channels; gradient of the activation alone, us, this kernel / the others): with stride
+// 2, for its parities; where the others take a launch per block of channels (14 x 14 x 1024, 1 x 1, r = 64, batch 1 to
+// 128: 17 / 42 to 41 / 86; 7 x 7 x 512, 3 x 3: 22 / 34); for a single slab (1 x 1, r <= 64: 17 / 18); and for large batches
+// (28 x 28 x 128, r = 64: 32 images 26 / 28, 128 images 53 / 83). With few row blocks and one launch on both sides the
+// others' deeper prefetch wins: 28 x 28 x 128, 16 images 24 / 23, r = 384 58 / 50; 27 x 27 x 192, 32 images, r = 192 45 / 43.
+bool narrow_dact(const abt_conv_geom& g, int p) {
+    if (g_chain_rows.load() != 0 || g_chain_parts.load() != 0 || !chain4_supports(64, p, 64)) return false;
+    return g.stride == 2 || g.C > conv_dact_chunk(g.C) || p == 64 || ceil_div(g.N * g.H * g.W, 128) > 192;
+}
+
 // dAct[q, c] = sum over taps and j of dT[(q - shift(tap)) / stride, j] B[j, tap, c] (only where the division
 // is exact): the same gathered product as the forward, on the image dT [N, H', W', r] with mirrored
 // shifts, against the re-laid-out factor Pst; rows are the input pixels.
@@ -386,7 +397,7 @@ hipError_t conv_dact(const void* dT, const void* B, void* dAct, void* Pst, const
     const int Ho = (int)conv_out(g.H, g.stride), Wo = (int)conv_out(g.W, g.stride);
     const int64_t M_in = g.N * g.H * g.W;
     hipError_t e;
-    if (g_chain_rows.load() == 0 && g_chain_parts.load() == 0 && chain4_supports(64, taps * r_pad, 64)) {
+    if (narrow_dact(g, taps * r_pad)) {
         int chunk = 64;
         for (int v : {192, 160, 128, 96}) if (C % v == 0) { chunk = v; break; }
         const bool by_parity = g.stride == 2;
