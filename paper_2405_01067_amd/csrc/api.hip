@@ -142,10 +142,11 @@ bool narrow_chain(const ChainProblem* problems, int n, int64_t M, int p, int q, 
 // a range check per 16 bytes.  Forward, us, this kernel / the better of the others, r = 64: 56 x 56 x 64
 // (200704 rows) 50 / 110, 28 x 28 x 128 (50176 rows) 29 / 43; with few row blocks the other kernels' deeper prefetch
 // wins back (14 x 14 x 256, 12544 rows: 28 / 26, r = 192 45 / 32) except where the patches are strided
-// (28 x 28 x 128, stride 2: 17 / 20; r = 192 27 / 24).
+// (28 x 28 x 128, stride 2: 17 / 20; r = 192 27 / 24) and not too many for one row block (7 x 7 x 512, 3 x 3, stride 2,
+// r = 96: 1 image 42 / 38, 4 images 43 / 44; r = 64 34 / 35).
 bool narrow_gather(int64_t row_blocks, int mul, int p, int q, int R) {
     if (g_chain_rows.load() != 0 || g_chain_parts.load() != 0 || !chain4_supports(R, p, q)) return false;
-    return row_blocks > 128 || (mul == 2 && R <= 96);
+    return row_blocks > 128 || (mul == 2 && (R <= 64 || (R == 96 && (p <= 4096 || row_blocks > 1))));
 }
 
 // the gathered chain (factored convolution): same choice of work-group height, no column parts
