@@ -460,6 +460,10 @@ int tn2_choose_splits(int64_t M, int total_tiles, int per_cu) {
     int64_t max_by_rows = M / (8 * 64);
     if (max_by_rows < 1) max_by_rows = 1;
     if (want > max_by_rows) want = max_by_rows;
+    // few rows: where two per compute unit would not be 5/3 of one round, one round (14 x 14 x 320, r = 128, 6272 rows:
+    // 288 work-groups 38 us, 240 35; 360 with 7840 rows 40 / 38; from 400 on the two are equal or better)
+    const int64_t one = 256 / total_tiles;
+    if (one >= 1 && want > one && 3 * want <= 5 * one) want = one;
     if (want < 1) want = 1;
     if (want > 64) want = 64;
     return (int)want;

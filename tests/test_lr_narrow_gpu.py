@@ -135,3 +135,17 @@ def test_first_stage_of_several_groups_repeats_the_saved_products():
     again = abt.lr_linear_bwd_grouped([dict(e, T=None, dA=True) for e in groups])
     for a, b in zip(again, with_T):
         assert torch.equal(a[1], b[1])
+
+
+@pytest.mark.parametrize("N", [28, 30, 48])       # splits of six tiles: 42 (rows for no more), 42 instead of 45, 64
+def test_convolution_gradients_between_one_and_two_work_groups_per_unit(N):
+    H, C, m, r = 28, 64, 64, 32
+    c = gen.conv_case(N, H, H, C, m, r, 3, 3, seed=N)
+    act, dY, A, B = (dev(c[k]) for k in ("act", "dY", "A", "B"))
+    T = abt.lr_conv_fwd(act, A, B, 3, 3)[1]
+    dAct, dA, dB = abt.lr_conv_bwd(dY, act, T, A, B, 3, 3)
+    pt = torch.nn.functional.pad(act.float(), (0, 0, 1, 1, 1, 1)).unfold(1, 3, 1).unfold(2, 3, 1)      # [N, H, W, C, ky, kx]
+    patches = pt.permute(0, 1, 2, 4, 5, 3).reshape(N * H * H, 9 * C)
+    dT = (dY.float() @ A.float()).to(BF).float()
+    assert rel(host(dB), (dT.t() @ patches).cpu()) < TOL
+    assert rel(host(dA), (dY.float().t() @ T.float()).cpu()) < TOL
