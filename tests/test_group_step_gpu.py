@@ -329,3 +329,21 @@ def test_grouped_backward_accumulates_and_fills_the_chip_shape():
     for g in range(4):
         key = "dA" if g < 2 else "dB"
         assert rel(host(acc[g][key]), 2 * host(outs[g][1 if g < 2 else 2])) < 1e-6
+
+
+@pytest.mark.parametrize("G,M,m,n,r", [(4, 8501, 192, 128, 96), (3, 11003, 128, 192, 160), (5, 7001, 64, 64, 64), (2, 16390, 64, 320, 32)])
+def test_grouped_step_narrow_rank_work_groups_of_fewer_rows(G, M, m, n, r):
+    """More than 32768 rows in all: the narrow-rank kernel with its row count shared out over all groups, and a ragged last
+    row block in every one of them; the last group asks for dB alone (the launch without a second stage)."""
+    cases = [gen.lr_case(M=M, m=m, n=n, r=r, seed=500 + 10 * g + r) for g in range(G)]
+    groups = [{k: dev(c[k], torch.bfloat16) for k in ("X", "A", "B", "dY")} for c in cases]
+    fwd = abt.lr_linear_fwd_grouped([{k: e[k] for k in ("X", "A", "B")} for e in groups])
+    want = [dict(dX=True, dA=True)] + [dict(dX=True, dA=True, dB=True)] * (G - 2) + [dict(dB=True)]
+    bwd = abt.lr_linear_bwd_grouped([dict(e, T=t if g else None, **w) for g, (e, (_, t), w) in enumerate(zip(groups, fwd, want))])
+    for c, (Y, T), (dX, dA, dB), w in zip(cases, fwd, bwd, want):
+        Yo, To = orc.lr_linear_fwd(c["X"], c["A"], c["B"])
+        dXo, dAo, dBo, _ = orc.lr_linear_bwd(c["dY"], c["X"], c["A"], c["B"])
+        assert rel(host(Y), Yo) < 1e-2 and rel(host(T), To) < 1e-2
+        for key, got, ref in (("dX", dX, dXo), ("dA", dA, dAo), ("dB", dB, dBo)):
+            assert (got is None) == (key not in w)
+            assert got is None or rel(host(got), ref) < 1e-2, key
