@@ -84,8 +84,9 @@ __device__ __forceinline__ void buf_store16_maybe_stream(bool stream, u32x4 v, r
     if (stream) buf_store16_stream(v, r, lane_off, wave_off);
     else buf_store16(v, r, lane_off, wave_off);
 }
-// Outputs of a launch (Yout and Tout of the chain kernels) of this many bytes or more are stored with
-// the hint: a quarter of the 256 MB last-level cache.
+// Outputs (Yout and Tout of the chain kernels) of this many bytes or more are stored with the hint: a quarter of
+// the 256 MB last-level cache.  Counted per problem of a grouped launch; the parities and channel blocks of one image
+// are one output.
 constexpr int64_t kStreamOutBytes = 64ll << 20;
 
 inline int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
@@ -139,7 +140,8 @@ hipError_t launch_chain3_bf16(const ChainProblem* problems, int G, int64_t M, in
 //   patches, stride 2:        RH x RW = output grid, mul = 2, shift = 0, sign = +1
 //   adjoint gather, stride 1: the same with sign = -1
 //   adjoint gather, stride 2: image = gradient on the output grid, RH x RW = input grid, mul = 1,
-//                             shift = 1, sign = -1.
+//                             shift = 1, sign = -1 (only where a work-group height is forced, which the tests of the form
+//                             by parity compare it with, and where a parity's window is beyond 32-bit offsets).
 // Tout rows are t_pitch elements apart (>= R).
 struct PatchGeom { int H, W, Cin, kh, kw, sign, RH, RW, mul, shift; };
 hipError_t launch_chain2_gather_bf16(const void* image, const PatchGeom& g, const void* P, const void* Q,

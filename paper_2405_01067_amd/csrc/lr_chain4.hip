@@ -399,14 +399,13 @@ hipError_t launch_chain4_bf16(const ChainProblem* problems, int G, int64_t M, in
     if (rows < 4 || rows > kMaxRows || rows % 4) return hipErrorInvalidValue;
     if (!problems || G < 1 || G > kChainMaxGroups || parts < 1 || !chain4_supports(R, p, q) || M < 1 || t_pitch < R) return hipErrorInvalidValue;
     C4Args a{};
-    int64_t out_bytes = 0;
     for (int g = 0; g < G; ++g) {
         const ChainProblem& c = problems[g];
         a.e[g] = C4Entry{(const uint16_t*)c.Xin, (const uint16_t*)c.P, (const uint16_t*)c.Q, (uint16_t*)c.Yout, (uint16_t*)c.Tout, M, p, ChainGather{}};
         if (c.Yout == nullptr && parts != 1) return hipErrorInvalidValue;
-        out_bytes = M * ((c.Yout ? q : 0) + R) * 2;
     }
     if (parts > q / 64) return hipErrorInvalidValue;
+    const int64_t out_bytes = M * ((problems[0].Yout ? q : 0) + R) * 2;
     a.q = q; a.t_pitch = t_pitch; a.rows = rows; a.parts = parts; a.stream_out = out_bytes >= kStreamOutBytes;
     return launch_any<false>(R, a, G, ceil_div(M, rows), s);
 }

@@ -52,7 +52,8 @@ struct Tn2 {
     // slabs in flight in the loaders' register ring: a CU wants about 64 KB of loads outstanding,
     // which two slabs only give when a slab is 40 KB or more (R >= 192)
     static constexpr int D = tn2_two(R, GATHER) || slab * 2 >= 64 * 1024 ? 2 : (slab * 3 >= 64 * 1024 ? 3 : 4);
-    // waves per SIMD the registers are budgeted for: two work-groups of seven or eight waves need four
+    // waves per SIMD the registers are budgeted for: two work-groups of seven or eight waves need four, 128 registers
+    // each (a loader wave spills six in its prologue, once per work-group; no loop touches scratch)
     static constexpr int WPS = tn2_two(R, GATHER) ? 4 : 1;
     static_assert(lds_bytes <= 160 * 1024, "slab shape");
 };
