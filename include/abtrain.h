@@ -231,7 +231,7 @@ size_t ab_merge_batched_workspace_bytes(const abt_merge_desc* layers, int L);
  * of the last merge that ran on this workspace.  sweeps / n_sigma: HOST, may be NULL. */
 int ab_merge_info(const void* workspace, int layer, int32_t* sweeps, int32_t* n_sigma,
                   void* stream);
-/* The same for layers first .. first + count - 1 of the workspace in one read: sweeps and n_sigma are HOST arrays
+/* The same for layers first .. first + count - 1 of the workspace in one call: sweeps and n_sigma are HOST arrays
  * of `count` entries (either may be NULL); ABT_ENOCONV if any of them hit the cap. */
 int ab_merge_info_batched(const void* workspace, int first, int count, int32_t* sweeps, int32_t* n_sigma, void* stream);
 
