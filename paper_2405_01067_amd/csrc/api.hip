@@ -74,13 +74,13 @@ int narrow_rows(int64_t M) {
 //     rows 18 / 19, 15 / 14; 1536 -> 1536 with 8192 rows 29 / 28, 27 / 25 at r = 64, 25 / 22 at r = 32.
 //   8192 to 32768 rows: one work-group alone on a compute unit waits for its loads (12608 rows, r = 96: 44 / 28, 45 / 36,
 //     23 / 20).  Only at r = 160, where the others have 64-row work-groups: 17000 rows, 3072 -> 768 60 / 85, 768 -> 768
-//     29 / 41, but 768 -> 3072 59 / 47, from 45000 rows on 106 / 107; 3072 -> 3072 103 / 94, 25000 rows the same.
+//     29 / 41, but 768 -> 3072 59 / 47, from 45000 rows on 106 / 107; 3072 -> 3072 103 / 94, but 25000 rows 100 / 117.
 //   More than 32768 rows, at least two work-groups per compute unit, r <= 128.  768 -> 3072 / 3072 -> 768 / 768 -> 768
-//     with 39597 rows: r = 64 66 / 68, 79 / 89, 33 / 46; r = 96 68 / 76, 82 / 95, 34 / 44; with 100864 rows 164 / 176, 168 / 176,
-//     - and 186 / 175, 179 / 194, -: at r = 96 not for the widest layers there (1536 -> 1536 155 / 146).  r = 128, where the
-//     others are better at long contractions and wide outputs: 33000 rows 82 / 69, 88 / 114, 42 / 56, 3072 -> 3072
-//     137 / 132; 65536 rows 120 / 115, 124 / 118, 50 / 52.  r = 32 only with p >= q (50432 rows: 75 / 80 and 31 / 36,
-//     768 -> 3072 91 / 86).  (r = 192, 100000 rows: 241 / 213, 246 / 226, 104 / 100.)
+//     with 39597 rows: r = 64 66 / 68, 79 / 89, 33 / 46; r = 96 68 / 76, 82 / 95, 34 / 44.  With 100864 rows: r = 64
+//     164 / 176, 168 / 176; r = 96 186 / 175, 179 / 194 and, 1536 -> 1536, 155 / 146: not for the widest layers there.
+//     r = 128, where the others are better at long contractions and wide outputs: 33000 rows 82 / 69, 88 / 114, 42 / 56,
+//     3072 -> 3072 137 / 132; 65536 rows 120 / 115, 124 / 118, 50 / 52.  r = 32 only with p >= q: 50432 rows 91 / 86,
+//     75 / 80, 31 / 36.  (r = 192, 100000 rows: 241 / 213, 246 / 226, 104 / 100.)
 // (The rule does not ask for the second stage: a T that the backward computes again comes from the same kernel.)
 bool use_narrow(int64_t rows, int p, int q, int R) {
     if (g_chain_rows.load() != 0 || g_chain_parts.load() != 0 || !chain4_supports(R, p, q)) return false;
@@ -103,7 +103,7 @@ bool use_narrow(int64_t rows, int p, int q, int R) {
 
 // Columns of T per work-group where only T is wanted: nothing shares a row block's output tiles then, and at wide ranks
 // a slab of the whole P takes longer than the other kernels' loaders (T of 197 rows, p = 1536, r = 192, and dA: 36 us,
-// 22 with 32 columns each, 26 before; p = 768, r = 96: 18.6, 16.2, 18.8).  The sums of a column do not change.
+// 22 with 32 columns each, 26 in the other kernels; p = 768, r = 96: 18.6, 16.2, 18.8).  The sums of a column do not change.
 int narrow_cols(int n, int64_t row_blocks, int R) {
     for (int c : {32, 64, 96})
         if (R % c == 0 && n * (R / c) <= kChainMaxGroups && row_blocks * (R / c) <= 256) return c;
