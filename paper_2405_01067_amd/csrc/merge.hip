@@ -751,7 +751,7 @@ struct Plan {
     size_t lds_jacobi = 0;  // largest jb * K * 8 over the layers
     struct PerLayer {
         int K, jb, nb;
-        size_t Abar, Bbar, LA, GB, LB, Ct, Yt, sigma, s3, s5, trace, nrm, perm, PA, PB, chol;
+        size_t Abar, Bbar, LA, GB, LB, Ct, Yt, sigma, s3, s5, trace, diag, nrm, perm, PA, PB, chol;
     };
     std::vector<PerLayer> pl;
 };
@@ -857,6 +857,7 @@ Plan make_plan(const abt_merge_desc* layers, int L) {
         q.s3 = take(sizeof(double) * K);
         q.s5 = take(sizeof(double) * K);
         q.trace = take(sizeof(double) * 10);
+        q.diag = take(sizeof(double) * 16 * K);
         q.nrm = take(sizeof(double) * K);
         q.perm = take(sizeof(int) * K);
         q.PA = take(sizeof(float) * K * kc);
@@ -1044,6 +1045,7 @@ hipError_t merge_run(const abt_merge_desc* layers, const MergeSide* identity, in
         v.Ct = (double*)(ws + q.Ct); v.Yt = (double*)(ws + q.Yt);
         v.sigma = (double*)(ws + q.sigma); v.s3 = (double*)(ws + q.s3); v.s5 = (double*)(ws + q.s5);
         v.trace = (double*)(ws + q.trace);
+        v.diag = (double*)(ws + q.diag);
         v.nrm = (double*)(ws + q.nrm);
         v.perm = (int*)(ws + q.perm);
         v.PA = (float*)(ws + q.PA); v.PB = (float*)(ws + q.PB);

@@ -33,6 +33,7 @@ struct LayerDev {
     double* LA; double* GB; double* LB; double* Ct; double* Yt;
     double* sigma; double* s3; double* s5;
     double* trace;         // [10]: the last eight are partial sums of ||C||_F^2
+    double* diag;          // [K / 16][16][16]: Gram matrices of the column blocks between two rounds of a sweep
     double* nrm;           // [K]: squared column norms of the rotated core (colnorm_kernel -> finalize_kernel)
     int* perm;
     float* PA; float* PB;

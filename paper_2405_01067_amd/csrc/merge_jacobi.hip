@@ -4,10 +4,10 @@
 // The columns of C (rows of Ct) are grouped in blocks of 16; a round pairs every block with one
 // partner (round-robin tournament over the blocks), one work-group per block pair.  For its 32
 // columns P (K x 32) a work-group
-//   1. forms the Gram matrix S = P^T P (32 x 32) with v_mfma_f64_16x16x4,
-//   2. runs the cyclic Jacobi eigenvalue iteration on S in LDS: 16 steps of 16 disjoint rotations,
-//      one step per cyclic shift of the partner block, every rotation applied to S from both sides
-//      and accumulated in Q (32 x 32).  These are the plane rotations the column form of the
+//   1. forms the Gram matrix S = P^T P (32 x 32) with v_mfma_f64_16x16x4: the 16 x 16 tile between the blocks; the
+//      tiles inside them are what the last round's rotations left of S, and formed anew in round 0 of a sweep only,
+//   2. runs the cyclic Jacobi eigenvalue iteration on S: 16 steps of 16 disjoint rotations, every rotation applied to S
+//      from both sides and accumulated in Q (32 x 32).  These are the plane rotations the column form of the
 //      method would apply to the 256 column pairs of the two blocks, in the same order; they are
 //      worked out on the 32 x 32 Gram matrix instead of on K-long columns,
 //   3. applies them at once: P <- P Q, again on the matrix cores.
@@ -18,6 +18,14 @@
 // product taken as (Q^T P^T) the result tile comes out of the matrix core in that same layout, so
 // the update is in place.  Step 1 needs the transposed operand order (contraction over rows); each
 // wave passes its row tiles through a private 4 KB LDS tile for that.
+#include <type_traits>
+
+//
+// What bounds it: a round is one dependent chain.  K = 384, cycles of a work-group: panel load 3400 alone, 7000 to 10000 with 576
+// of them (nothing survives in L2 from the round before), Gram matrix 3000 (6500 with the tiles inside the blocks), rotations 14000 of which Q
+// 2000, update 6400 (fp64 matrix instructions), store 2000, and some 10000 between the end of a round and the start of
+// the next.  Sweeps of config 5 (48 cores of 384, 8 sweeps): 6.07 ms before the rotations moved to registers, 4.97 after,
+// 4.60 with the kept diagonal tiles; 16 cores of 768, 9 sweeps: 17.5, 16.7, 16.2 ms (one work-group per compute unit, 384 of them).
 #include "merge_internal.h"
 
 namespace abt {
@@ -32,12 +40,37 @@ __device__ __forceinline__ int stage_addr(int n, int c) {
 
 struct __align__(16) JacobiShared {
     double stage[4][16 * 32];       // per wave: transposition tile; afterwards the waves' partial Gram tiles
-    // pitch 48: rows 96 words apart, so the cells of two neighbouring rows times sixteen columns that
-    // a half wave touches at once fall into different halves of the 64 banks
-    double S[2][32][48];            // read from one copy, written to the other, swapped every step
+    double S[32][48];
     double Q[32][48];
-    f64x2 cs[2][16];                // (cosine, sine) of the 16 rotations of a step (two copies: steps alternate)
+    f64x2 cs[31][16];               // (cosine, sine) of the rotations of all steps
 };
+
+// ---- The rotations of a block pair.  Columns 0..31 (the two blocks) are paired by exclusive or: step m pairs every i with
+// i ^ m, so 31 steps meet all pairs once, m = 16..31 those between the blocks, m < 16 those inside them.  The
+// steps whose m has p as its highest bit form level p: with L(u), R(u) = the 4-bit u with a 0 or a 1 put in at bit p, step t pairs L(u)
+// with R(u ^ t), t below 2^p.
+__device__ __forceinline__ int left_of(int u, int p) { return ((u >> p) << (p + 1)) | (u & ((1 << p) - 1)); }
+__device__ __forceinline__ int right_of(int u, int p) { return left_of(u, p) | (1 << p); }
+
+template <int N, class F, int I = 0>
+__device__ __forceinline__ void static_for(F&& f) {
+    if constexpr (I < N) { f(std::integral_constant<int, I>{}); static_for<N, F, I + 1>(static_cast<F&&>(f)); }
+}
+
+template <int CTRL>
+__device__ __forceinline__ double dpp(double v) {
+    return __hiloint2double(__builtin_amdgcn_update_dpp(0, __double2hiint(v), CTRL, 0xf, 0xf, true),
+                            __builtin_amdgcn_update_dpp(0, __double2loint(v), CTRL, 0xf, 0xf, true));
+}
+// the value of lane ^ B (B = 1, 2, 3, 4, 8) by data-parallel moves: quad permutations, mirrored half rows, rotated rows
+template <int B>
+__device__ __forceinline__ double lane_xor(double v) {
+    if constexpr (B == 1) return dpp<0xB1>(v);
+    else if constexpr (B == 2) return dpp<0x4E>(v);
+    else if constexpr (B == 3) return dpp<0x1B>(v);
+    else if constexpr (B == 4) return dpp<0x1B>(dpp<0x141>(v));
+    else return dpp<0x128>(v);
+}
 
 // The rotation of jacobi_rotation(), arranged for a short dependency chain (the 16 steps of a block
 // pair are serial, and this is the longest link of a step): no branches, the tangent in fp32, the
@@ -68,29 +101,114 @@ __device__ __forceinline__ void fast_rotation(double alpha, double beta, double 
     s = rot ? cc * tn : 0.0;
 }
 
-// endpoints of pair p (0..15) in step st: the first `intra` steps pair columns inside each block
-// (circle method on 16 players, pairs 0..7 in the first block, 8..15 in the second), the following
-// 16 steps pair column p of the first block with column (p + t) mod 16 of the second.
-__device__ __forceinline__ void pair_of(int st, int intra, int p, int& i, int& j) {
-    if (st < intra) {
-        const int base = p < 8 ? 0 : 16, u = p & 7;
-        if (u == 0) { i = 15; j = st; }
-        else { i = (st + u) % 15; j = (st - u + 15) % 15; }
-        i += base; j += base;
-    } else {
-        i = p;
-        j = 16 + ((p + st - intra) & 15);
+// Level p on S by one wave, S in registers: lane (u = l % 16, q = l / 16) owns, for x = 4 q + e, the 2 x 2 cell rows
+// L(u), R(u ^ t) x columns L(v), R(v ^ t) with v = u ^ x.  t runs through a Gray code; when bit b of it changes, a cell finds its new
+// off-diagonal entries in the cell x ^ b (another register of the lane for b = 1, 2) and its new last
+// entry, like the one below the diagonal, in lane ^ b: register names and data-parallel moves, no LDS and no barrier
+// in a step.  The pairs' own cells are x = 0, in the first 16 lanes, which work the rotations out; the lanes that need
+// them fetch them with a lane permute.  A step takes 790 cycles, most of it the chain of the rotation formula, the permute
+// and the update of the pairs' cells.  With S in LDS, cells dealt to four waves and a barrier a step it took 1150; in a loop of four
+// steps a turn, with half the code, 920.
+template <int P>
+__device__ __forceinline__ void rotate_level(double (*S)[48], f64x2 (*cs)[16], double floor2, double scale, bool& any_signif,
+                                             double* diagI = nullptr, double* diagJ = nullptr) {
+    const int lane = threadIdx.x & 63, u = lane & 15, q = lane >> 4;
+    double m00[4], m01[4], m10[4], m11[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        const int v = u ^ (4 * q + e);
+        m00[e] = S[left_of(u, P)][left_of(v, P)]; m01[e] = S[left_of(u, P)][right_of(v, P)];
+        m10[e] = S[right_of(u, P)][left_of(v, P)]; m11[e] = S[right_of(u, P)][right_of(v, P)];
     }
+    // one step; B: the bit of t that changes after it (0: the last step)
+    auto step = [&](auto bit, int k) {
+        constexpr int B = decltype(bit)::value;
+        double c, s; bool signif;
+        fast_rotation(m00[0], m11[0], m01[0], floor2, scale, c, s, signif);
+        if (lane < 16) { any_signif |= signif; cs[k][u] = f64x2{c, s}; }
+        const double c1 = __shfl(c, u, 64), s1 = __shfl(s, u, 64);
+        double c2[4], s2[4];
+        c2[0] = __shfl(c, u ^ (4 * q), 64); s2[0] = __shfl(s, u ^ (4 * q), 64);
+        c2[1] = lane_xor<1>(c2[0]); s2[1] = lane_xor<1>(s2[0]);
+        c2[2] = lane_xor<2>(c2[0]); s2[2] = lane_xor<2>(s2[0]);
+        c2[3] = lane_xor<3>(c2[0]); s2[3] = lane_xor<3>(s2[0]);
+        double n01[4], n10[4], n11[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const double t00 = c1 * m00[e] - s1 * m10[e], t01 = c1 * m01[e] - s1 * m11[e];
+            const double t10 = s1 * m00[e] + c1 * m10[e], t11 = s1 * m01[e] + c1 * m11[e];
+            m00[e] = c2[e] * t00 - s2[e] * t01; n01[e] = s2[e] * t00 + c2[e] * t01;
+            n10[e] = c2[e] * t10 - s2[e] * t11; n11[e] = s2[e] * t10 + c2[e] * t11;
+        }
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            if constexpr (B == 0) { m01[e] = n01[e]; m10[e] = n10[e]; m11[e] = n11[e]; }
+            else if constexpr (B < 4) { m01[e] = n01[e ^ B]; m10[e] = lane_xor<B>(n10[e ^ B]); m11[e] = lane_xor<B>(n11[e]); }
+            else {
+                m01[e] = __shfl_xor(n01[e], 4 * B, 64); m10[e] = __shfl_xor(n10[e], 5 * B, 64); m11[e] = lane_xor<B>(n11[e]);
+            }
+        }
+    };
+    static_for<(1 << P)>([&](auto i) {
+        constexpr int k = decltype(i)::value;
+        step(std::integral_constant<int, (k + 1 < (1 << P) ? (k + 1) & -(k + 1) : 0)>{}, k);
+    });
+    constexpr int t = ((1 << P) - 1) ^ (((1 << P) - 1) >> 1);
+    if (P == 4) {                                        // the last level: the two diagonal blocks, for the next round
+        if (diagI == nullptr) return;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const int v = u ^ (4 * q + e);
+            gstore(diagI + 16 * u + v, m00[e]);
+            gstore(diagJ + 16 * (u ^ t) + (v ^ t), m11[e]);
+        }
+        return;
+    }
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        const int v = u ^ (4 * q + e);
+        S[left_of(u, P)][left_of(v, P)] = m00[e]; S[left_of(u, P)][right_of(v ^ t, P)] = m01[e];
+        S[right_of(u ^ t, P)][left_of(v, P)] = m10[e]; S[right_of(u ^ t, P)][right_of(v ^ t, P)] = m11[e];
+    }
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// The same rotations on the columns of Q, rows 8 wave .. 8 wave + 7 by this wave: lane (u, q) owns columns L(u), R(u ^ t) of
+// rows q and q + 4 of them.
+template <int P>
+__device__ __forceinline__ void accumulate_level(double (*Q)[48], const f64x2 (*cs)[16]) {
+    const int lane = threadIdx.x & 63, u = lane & 15, r = 8 * (threadIdx.x >> 6) + (lane >> 4);
+    double a0 = Q[r][left_of(u, P)], b0 = Q[r][right_of(u, P)], a1 = Q[r + 4][left_of(u, P)], b1 = Q[r + 4][right_of(u, P)];
+    auto step = [&](auto bit, int k) {
+        constexpr int B = decltype(bit)::value;
+        const f64x2 rot = cs[k][u];
+        const double c = rot[0], s = rot[1];
+        const double x0 = c * a0 - s * b0, y0 = s * a0 + c * b0, x1 = c * a1 - s * b1, y1 = s * a1 + c * b1;
+        a0 = x0; a1 = x1;
+        if constexpr (B == 0) { b0 = y0; b1 = y1; }
+        else { b0 = lane_xor<B>(y0); b1 = lane_xor<B>(y1); }
+    };
+    static_for<(1 << P)>([&](auto i) {
+        constexpr int k = decltype(i)::value;
+        step(std::integral_constant<int, (k + 1 < (1 << P) ? (k + 1) & -(k + 1) : 0)>{}, k);
+    });
+    constexpr int t = ((1 << P) - 1) ^ (((1 << P) - 1) >> 1);
+    Q[r][left_of(u, P)] = a0; Q[r][right_of(u ^ t, P)] = b0; Q[r + 4][left_of(u, P)] = a1; Q[r + 4][right_of(u ^ t, P)] = b1;
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
 // NT: 16-row tiles per wave (two per 32-row chunk: its even and its odd rows), K <= 64 NT.
+// (Three work-groups per compute unit at K = 384 spill and take 7.0 ms in place of 4.6 over a merge; two at K = 768, 24.7 of 16.2.)
 // WHOLE (K = 32: two blocks, one pair): the work-group holds the whole core, so it runs all sweeps in one launch, the
 // panel in registers throughout; `round` is the sweep cap.  A launch and a poll of the convergence flags per
-// sweep took 129 us for one core of 32 (four sweeps), this 86.
+// sweep took 129 us for one core of 32, this 54.
 template <int NT, bool WHOLE>
-__global__ __launch_bounds__(256, (NT <= 6 ? 3 : 1)) void jacobi_block_kernel(const LayerDev* __restrict__ layers,
-                                                                               const int2* __restrict__ wg_map,
-                                                                               int sweep, int round) {
+__global__ __launch_bounds__(256, (WHOLE ? 1 : NT <= 2 ? 3 : NT <= 6 ? 2 : 1))
+void jacobi_block_kernel(const LayerDev* __restrict__ layers, const int2* __restrict__ wg_map, int sweep, int round) {
     __shared__ JacobiShared sh;
     const int2 wm = wg_map[blockIdx.x];                   // (layer, pair slot)
     const LayerDev& L = layers[wm.x];
@@ -105,7 +223,15 @@ __global__ __launch_bounds__(256, (NT <= 6 ? 3 : 1)) void jacobi_block_kernel(co
     else { bI = (round + wm.y) % (nb - 1); bJ = (round - wm.y + (nb - 1)) % (nb - 1); }
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, n = lane & 15, kq = lane >> 4;
 
-    // ---- load the panel: D[t][s] = P[row(t, n)][column kq + 4 s], columns 0..15 = block I, 16..31 = block J
+    // Gram matrices of the two blocks as the last round left them, a value of each per thread; ||C||_F^2
+    const int gi = (tid >> 6) + 4 * (tid & 3), gj = (tid >> 2) & 15;      // this thread's element of a 16 x 16 tile
+    double* const diagI = L.diag + bI * 256;
+    double* const diagJ = L.diag + bJ * 256;
+    const bool fresh = WHOLE || round == 0;               // formed again from the columns once per sweep
+    double ownII = fresh ? 0.0 : gload(diagI + 16 * gi + gj), ownJJ = fresh ? 0.0 : gload(diagJ + 16 * gi + gj);
+    const double frob = frob2(L);
+    // ---- load the panel: D[t][s] = P[row(t, n)][column kq + 4 s], columns 0..15 = block I, 16..31 = block J (rows past K
+    // repeat row 0 and are cleared behind the last load: a predicate on a load would be waited for with it)
     double D[NT][8];
 #pragma unroll
     for (int tt = 0; tt < NT / 2; ++tt) {
@@ -113,81 +239,93 @@ __global__ __launch_bounds__(256, (NT <= 6 ? 3 : 1)) void jacobi_block_kernel(co
 #pragma unroll
         for (int s = 0; s < 8; ++s) {
             const int col = (s < 4 ? bI * 16 + kq + 4 * s : bJ * 16 + kq + 4 * (s - 4));
-            f64x2 v = {0.0, 0.0};
-            if (row0 < K) v = gload(reinterpret_cast<const f64x2*>(L.Ct + (int64_t)col * K + row0));
+            const f64x2 v = gload(reinterpret_cast<const f64x2*>(L.Ct + (int64_t)col * K + (row0 < K ? row0 : 0)));
             D[2 * tt][s] = v[0];
             D[2 * tt + 1][s] = v[1];
         }
     }
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int tt = 0; tt < NT / 2; ++tt) {
+        const bool in = 32 * (wave + 4 * tt) + 2 * n < K;
+#pragma unroll
+        for (int s = 0; s < 8; ++s) {
+            D[2 * tt][s] = in ? D[2 * tt][s] : 0.0;
+            D[2 * tt + 1][s] = in ? D[2 * tt + 1][s] : 0.0;
+        }
+    }
 
     for (;; ++sweep) {                                   // one turn; WHOLE: until a sweep rotates nothing of weight
-    // ---- S = P^T P: three 16 x 16 tiles (II, IJ, JJ), this wave's rows
+    // ---- S = P^T P: the tile between the blocks, and those inside them (II, JJ) if there are none of the last round
     f64x4 gII = {0.0, 0.0, 0.0, 0.0}, gIJ = gII, gJJ = gII;
     double* stage = sh.stage[wave];
+    auto gram = [&](auto all) {
 #pragma unroll
-    for (int t = 0; t < NT; ++t) {
+        for (int t = 0; t < NT; ++t) {
 #pragma unroll
-        for (int s = 0; s < 8; ++s) stage[stage_addr(n, kq + 4 * s)] = D[t][s];
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-        double a0[4], a1[4];
+            for (int s = 0; s < 8; ++s) stage[stage_addr(n, kq + 4 * s)] = D[t][s];
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+            double a0[4], a1[4];
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            a0[q] = stage[stage_addr(4 * q + kq, n)];
-            a1[q] = stage[stage_addr(4 * q + kq, 16 + n)];
+            for (int q = 0; q < 4; ++q) {
+                a0[q] = stage[stage_addr(4 * q + kq, n)];
+                a1[q] = stage[stage_addr(4 * q + kq, 16 + n)];
+            }
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                if (decltype(all)::value) gII = __builtin_amdgcn_mfma_f64_16x16x4f64(a0[q], a0[q], gII, 0, 0, 0);
+                gIJ = __builtin_amdgcn_mfma_f64_16x16x4f64(a0[q], a1[q], gIJ, 0, 0, 0);
+                if (decltype(all)::value) gJJ = __builtin_amdgcn_mfma_f64_16x16x4f64(a1[q], a1[q], gJJ, 0, 0, 0);
+            }
         }
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            gII = __builtin_amdgcn_mfma_f64_16x16x4f64(a0[q], a0[q], gII, 0, 0, 0);
-            gIJ = __builtin_amdgcn_mfma_f64_16x16x4f64(a0[q], a1[q], gIJ, 0, 0, 0);
-            gJJ = __builtin_amdgcn_mfma_f64_16x16x4f64(a1[q], a1[q], gJJ, 0, 0, 0);
-        }
-    }
+    };
+    if (fresh) gram(std::true_type{});
+    else gram(std::false_type{});
     // partial tiles of the four waves, added in wave order; result element (i, j) of a tile sits in
     // lane (j, i % 4), register i / 4
+    auto total = [&](int at) { return ((sh.stage[0][at] + sh.stage[1][at]) + sh.stage[2][at]) + sh.stage[3][at]; };
 #pragma unroll
     for (int v = 0; v < 4; ++v) {
-        stage[0 * 256 + lane * 4 + v] = gII[v];
         stage[1 * 256 + lane * 4 + v] = gIJ[v];
+        if (fresh) stage[0 * 256 + lane * 4 + v] = gII[v];
     }
     __syncthreads();
     {
-        const int l = tid >> 2, v = tid & 3, i = (l >> 4) + 4 * v, j = l & 15;
-        const double sII = ((sh.stage[0][tid] + sh.stage[1][tid]) + sh.stage[2][tid]) + sh.stage[3][tid];
-        const double sIJ = ((sh.stage[0][256 + tid] + sh.stage[1][256 + tid]) + sh.stage[2][256 + tid]) + sh.stage[3][256 + tid];
-        sh.S[0][i][j] = sII;
-        sh.S[0][i][16 + j] = sIJ;
-        sh.S[0][16 + j][i] = sIJ;
+        const double sIJ = total(256 + tid);
+        sh.S[gi][16 + gj] = sIJ;
+        sh.S[16 + gj][gi] = sIJ;
+        if (fresh) ownII = total(tid);
     }
-    __syncthreads();
+    if (fresh) {
+        __syncthreads();
 #pragma unroll
-    for (int v = 0; v < 4; ++v) stage[lane * 4 + v] = gJJ[v];
-    __syncthreads();
-    {
-        const int l = tid >> 2, v = tid & 3, i = (l >> 4) + 4 * v, j = l & 15;
-        sh.S[0][16 + i][16 + j] = ((sh.stage[0][tid] + sh.stage[1][tid]) + sh.stage[2][tid]) + sh.stage[3][tid];
+        for (int v = 0; v < 4; ++v) stage[lane * 4 + v] = gJJ[v];
+        __syncthreads();
+        ownJJ = total(tid);
+    }
+    sh.S[gi][gj] = ownII;
+    sh.S[16 + gi][16 + gj] = ownJJ;
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            const int idx = tid + 256 * e;
-            sh.Q[idx >> 5][idx & 31] = (idx >> 5) == (idx & 31) ? 1.0 : 0.0;
-        }
+    for (int e = 0; e < 4; ++e) {
+        const int idx = tid + 256 * e;
+        sh.Q[idx >> 5][idx & 31] = (idx >> 5) == (idx & 31) ? 1.0 : 0.0;
     }
     __syncthreads();
 
     // ---- anything to rotate?  (pairs inside the blocks count in round 0 only)
-    const double frob = frob2(L);
     const double floor2 = kZeroColumn2 * frob;
     const double scale = ldexp(1.0, -__builtin_amdgcn_frexp_exp(frob));
-    const int intra = round == 0 ? 15 : 0;
+    const bool intra = round == 0;
     int need = 0;
     {
         const int i = tid >> 4, j = tid & 15;
         auto test = [&](int p, int q) {
-            const double a = sh.S[0][p][p], b = sh.S[0][q][q], g = sh.S[0][p][q];
+            const double a = sh.S[p][p], b = sh.S[q][q], g = sh.S[p][q];
             if (a > floor2 && b > floor2 && g * g > (kRotateTol * kRotateTol) * (a * b)) need = 1;
         };
         test(i, 16 + j);
@@ -195,104 +333,31 @@ __global__ __launch_bounds__(256, (NT <= 6 ? 3 : 1)) void jacobi_block_kernel(co
     }
     if (!__syncthreads_or(need)) {
         if (WHOLE) break;
-        return;                              // the data is untouched: nothing to store
+        if (fresh) { gstore(diagI + 16 * gi + gj, ownII); gstore(diagJ + 16 * gi + gj, ownJJ); }
+        return;                              // the columns are untouched: nothing else to store
     }
 
-    // ---- cyclic Jacobi on S, accumulated in Q.  A thread owns the 2 x 2 cell rows(pair u) x
-    // columns(pair v) of S and two rows of the columns(pair v) of Q.
+    // ---- cyclic Jacobi on S by one wave (which one differs among the work-groups that share a compute unit), then the
+    // same rotations on Q by all
     bool any_signif = false;
-    if (tid < 16) {                                      // rotations of the first step
-        int i, j;
-        pair_of(0, intra, tid, i, j);
-        double c, s; bool signif;
-        fast_rotation(sh.S[0][i][i], sh.S[0][j][j], sh.S[0][i][j], floor2, scale, c, s, signif);
-        any_signif |= signif;
-        sh.cs[0][tid] = f64x2{c, s};
+    if (wave == (int)(blockIdx.x & 3)) {
+        if (intra) {
+            rotate_level<3>(sh.S, sh.cs + 16, floor2, scale, any_signif);
+            rotate_level<2>(sh.S, sh.cs + 24, floor2, scale, any_signif);
+            rotate_level<1>(sh.S, sh.cs + 28, floor2, scale, any_signif);
+            rotate_level<0>(sh.S, sh.cs + 30, floor2, scale, any_signif);
+        }
+        rotate_level<4>(sh.S, sh.cs, floor2, scale, any_signif, WHOLE ? nullptr : diagI, WHOLE ? nullptr : diagJ);
     }
     __syncthreads();
-    // (a) round 0 only: the 15 steps inside the two blocks.  Two barriers per step: the rotations of
-    // the next step are worked out from the new S by 16 threads while the others update Q.
-    for (int st = 0; st < intra; ++st) {
-        const double (*Sr)[48] = sh.S[st & 1];
-        double (*Sw)[48] = sh.S[(st & 1) ^ 1];
-        const int cu = tid >> 4, cv = tid & 15;
-        int iu, ju, iv, jv;
-        pair_of(st, intra, cu, iu, ju);
-        pair_of(st, intra, cv, iv, jv);
-        const f64x2 r1 = sh.cs[st & 1][cu], r2 = sh.cs[st & 1][cv];
-        const double c1 = r1[0], s1 = r1[1], c2 = r2[0], s2 = r2[1];
-        const double m00 = Sr[iu][iv], m01 = Sr[iu][jv], m10 = Sr[ju][iv], m11 = Sr[ju][jv];
-        const double t00 = c1 * m00 - s1 * m10, t01 = c1 * m01 - s1 * m11;
-        const double t10 = s1 * m00 + c1 * m10, t11 = s1 * m01 + c1 * m11;
-        Sw[iu][iv] = c2 * t00 - s2 * t01; Sw[iu][jv] = s2 * t00 + c2 * t01;
-        Sw[ju][iv] = c2 * t10 - s2 * t11; Sw[ju][jv] = s2 * t10 + c2 * t11;
-        __syncthreads();
-        if (tid < 16) {
-            int i, j;
-            pair_of(st + 1, intra, tid, i, j);
-            double c, s; bool signif;
-            fast_rotation(Sw[i][i], Sw[j][j], Sw[i][j], floor2, scale, c, s, signif);
-            any_signif |= signif;
-            sh.cs[(st + 1) & 1][tid] = f64x2{c, s};
-        }
-#pragma unroll
-        for (int h = 0; h < 2; ++h) {
-            const int r = cu + 16 * h;
-            const double q0 = sh.Q[r][iv], q1 = sh.Q[r][jv];
-            sh.Q[r][iv] = c2 * q0 - s2 * q1;
-            sh.Q[r][jv] = s2 * q0 + c2 * q1;
-        }
-        __syncthreads();
+    if (intra) {
+        accumulate_level<3>(sh.Q, sh.cs + 16);
+        accumulate_level<2>(sh.Q, sh.cs + 24);
+        accumulate_level<1>(sh.Q, sh.cs + 28);
+        accumulate_level<0>(sh.Q, sh.cs + 30);
     }
-    // (b) the 16 steps between the blocks: step t pairs column u of the first block with column
-    // (u + t) mod 16 of the second.  One barrier per step.  Cells are dealt to the threads by
-    // diagonals: d = (v - u) mod 16 picks the wave and the 16-lane row, u the lane in the row.  The
-    // rotation of pair u in step t + 1 needs three entries of the new S which step t leaves in
-    // registers of one wave: S[u][j'] in the cell (u, u + 1) (j' = the next partner of u), S[u][u] and
-    // S[j'][j'] in the diagonal cells of pairs u and u + 1.  So the lanes of the row d = 1 fetch the
-    // two diagonal entries from row d = 0 by a lane permute and work the rotation out while the
-    // other waves update Q; no second barrier, no trip through LDS.  Which wave holds these two
-    // rows differs from work-group to work-group (the work-groups sharing a compute unit put this
-    // serial part on different SIMDs).
-    {
-        const int wrot = (int)(blockIdx.x & 3);
-        const int dd = (((wave - wrot) & 3) << 2) + (lane >> 4);
-        const int du = lane & 15, dv = (du + dd) & 15;
-        const bool rot_wave = wave == wrot;
-        for (int t = 0; t < 16; ++t) {
-            const int par = (intra + t) & 1;
-            const double (*Sr)[48] = sh.S[par];
-            double (*Sw)[48] = sh.S[par ^ 1];
-            const int ju = 16 + ((du + t) & 15), jv = 16 + ((dv + t) & 15);
-            const f64x2 r1 = sh.cs[par][du], r2 = sh.cs[par][dv];
-            const double c1 = r1[0], s1 = r1[1], c2 = r2[0], s2 = r2[1];
-            const double m00 = Sr[du][dv], m01 = Sr[du][jv], m10 = Sr[ju][dv], m11 = Sr[ju][jv];
-            const double t00 = c1 * m00 - s1 * m10, t01 = c1 * m01 - s1 * m11;
-            const double t10 = s1 * m00 + c1 * m10, t11 = s1 * m01 + c1 * m11;
-            const double n00 = c2 * t00 - s2 * t01, n01 = s2 * t00 + c2 * t01;
-            const double n10 = c2 * t10 - s2 * t11, n11 = s2 * t10 + c2 * t11;
-            Sw[du][dv] = n00; Sw[du][jv] = n01; Sw[ju][dv] = n10; Sw[ju][jv] = n11;
-            if (rot_wave && t < 15) {
-                // lane 16 + u: alpha = S[u][u] from lane u, beta = S[j'][j'] from lane (u + 1) mod 16
-                const double alpha = __shfl(n00, du, 64);
-                const double beta = __shfl(n11, (du + 1) & 15, 64);
-                if ((lane >> 4) == 1) {
-                    double c, s; bool signif;
-                    fast_rotation(alpha, beta, n01, floor2, scale, c, s, signif);
-                    any_signif |= signif;
-                    sh.cs[par ^ 1][du] = f64x2{c, s};
-                }
-            }
-#pragma unroll
-            for (int h = 0; h < 2; ++h) {
-                const int r = du + 16 * h;
-                const double q0 = sh.Q[r][dv], q1 = sh.Q[r][jv];
-                sh.Q[r][dv] = c2 * q0 - s2 * q1;
-                sh.Q[r][jv] = s2 * q0 + c2 * q1;
-            }
-            __syncthreads();
-        }
-    }
+    accumulate_level<4>(sh.Q, sh.cs);
+    __syncthreads();
     const bool again = WHOLE && __syncthreads_or(any_signif);
     if (any_signif) L.rotated[sweep] = 1;
 

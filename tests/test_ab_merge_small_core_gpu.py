@@ -56,3 +56,27 @@ def test_dense_decomposition_around_the_cholesky_forms(m, n):
     # fp32 factors and products; the cut falls into a spectrum without a gap, but the values around it agree
     # to far better than their distance
     assert float((got - want).norm() / want.norm()) < 1e-5
+
+
+@pytest.mark.parametrize("K", [32, 64, 96, 128, 160, 256, 288, 384, 416, 512, 544, 768])
+@pytest.mark.parametrize("zero_tail", [0, 20])
+def test_block_iteration_at_the_edges_of_its_forms(K, zero_tail):
+    # one form of the kernel up to 32, 128, 256, 384, 512 and 768 columns; the last columns of A (rows of B) zero, as
+    # padding of the rank leaves them
+    g = torch.Generator().manual_seed(K + zero_tail)
+    m, n = K + 40, K + 12
+    scale = torch.logspace(0, -2, K, dtype=torch.float64)
+    scale[K - zero_tail:] = 0.0
+    A = (torch.randn((m, K), generator=g, dtype=torch.float64) * scale).float()
+    B = torch.randn((K, n), generator=g, dtype=torch.float64).float()
+    B[K - zero_tail:] = 0.0
+    W = A.double() @ B.double()
+    U, s, V = torch.linalg.svd(W, full_matrices=False)
+    keep = (K - zero_tail) // 2
+    out = abt.ab_merge([A.to("cuda:0")], [B.to("cuda:0")], tau=0.0, k_fixed=keep)
+    # values: fp64 Gram matrices (2^-53 times the square of the condition, below 1e-9 for the kept half), rounded once to fp32
+    assert float(((out["S"].cpu().double()[:keep] - s[:keep]).abs() / s[:keep]).max()) < 3e-7
+    got = out["A"].cpu().double()[:, :keep] @ out["B"].cpu().double()[:keep]
+    want = (U[:, :keep] * s[:keep]) @ V[:keep]
+    # fp32 back-projections: sums of K products, (K + 2) 2^-24 at most, some sqrt(K) 2^-24 in the norm; factors rounded to fp32
+    assert float((got - want).norm() / want.norm()) < 4e-6
