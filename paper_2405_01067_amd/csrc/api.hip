@@ -347,6 +347,25 @@ int check_conv(const abt_conv_geom* g, int64_t m, int64_t r, int dt) {
     return ABT_OK;
 }
 
+// A 1 x 1 window with stride 1: the patch matrix is the activation itself, and the layer a linear one on N H W rows.
+inline bool is_linear(const abt_conv_geom& g) { return g.kh == 1 && g.kw == 1 && g.stride == 1; }
+
+// T = patches(act) B^T, Y = T A^T (Y NULL: T alone).  A linear layer goes to its kernels, which read whole lines, but for the
+// ranks whose gathered form has more work-groups per compute unit than the other at large batches (forward, us, as a matrix /
+// gathered: 28 x 28 x 512, r = 192, batch 256 101 / 91, 128 55 / 51; 56 x 56 x 256, r = 128, batch 128 79 / 79, r = 192 117 / 106;
+// below: 14 x 14 x 1024, batch 256, r = 128 32 / 33, r = 192 40 / 42; 7 x 7 x 2048, r = 64 18 / 25; 28 x 28 x 512, r = 256 110 / 179).
+hipError_t conv_chain(const void* act, const abt_conv_geom& g, const void* A, const void* B, void* Y, void* T, int64_t m, int64_t r,
+                      hipStream_t s) {
+    const int64_t M = conv_rows(g);
+    if (is_linear(g) && !(M > 65536 && r > 96 && r <= 192)) return chain(act, B, A, Y, T, M, (int)g.C, (int)m, (int)r, s);
+    return chain_gather(act, conv_patches_geom(g), B, A, Y, T, (int)r, M, (int)m, (int)r, s);
+}
+
+int linear_bwd(const void* dY, const void* X, const void* T, const void* A, const void* B,
+               void* dX, float* dA, float* dB,
+               int64_t M, int64_t m, int64_t n, int64_t r, int dt, int accumulate,
+               void* workspace, size_t workspace_bytes, size_t limit, void* stream);
+
 // column block of the activation gradient computed per launch: the widest supported tile that divides C
 int conv_dact_chunk(int64_t C) {
     static const int sizes[] = {384, 320, 256, 192, 160, 128, 96, 64};
@@ -359,6 +378,12 @@ struct ConvBwdLayout { size_t At, dT, T, Pst, partials, total; int r_pad; };
 ConvBwdLayout conv_bwd_layout(const abt_conv_geom& g, int64_t m, int64_t r) {
     ConvBwdLayout w{};
     const int64_t M = conv_rows(g), taps = (int64_t)g.kh * g.kw;     // rows of Y, T, dY, dT
+    if (is_linear(g)) {
+        const BwdLayout l = bwd_layout_bf16(M, m, g.C, r);
+        w.T = l.T;
+        w.total = l.total;
+        return w;
+    }
     w.r_pad = (int)((r + 63) / 64 * 64);
     size_t off = 0;
     auto take = [&](size_t bytes) { size_t o = off; off = align_up(off + bytes, 256); return o; };
@@ -460,11 +485,7 @@ int lr_conv_fwd(const void* act, const void* A, const void* B, void* Y, void* T_
     if (!act || !A || !B || !Y) return ABT_EINVAL;
     if (!aligned(act, 16) || !aligned(A, 16) || !aligned(B, 16) || !aligned(Y, 16) || !aligned(T_save, 16))
         return ABT_EALIGN;
-    const abt_conv_geom& g = *geom;
-    const int64_t M = conv_rows(g);
-    const PatchGeom pg = conv_patches_geom(g);
-    return chain_gather(act, pg, B, A, Y, T_save, (int)r, M, (int)m, (int)r, (hipStream_t)stream) == hipSuccess
-               ? ABT_OK : ABT_EHIP;
+    return conv_chain(act, *geom, A, B, Y, T_save, m, r, (hipStream_t)stream) == hipSuccess ? ABT_OK : ABT_EHIP;
 }
 
 int lr_conv_bwd(const void* dY, const void* act, const void* T, const void* A, const void* B,
@@ -491,10 +512,12 @@ int lr_conv_bwd(const void* dY, const void* act, const void* T, const void* A, c
     void* dT = ws + w.dT;
     const void* Tp = T;
     if (!Tp && dA) {   // recompute T = patches(act) B^T (first stage of the chain only)
-        if (chain_gather(act, fwd_geom, B, nullptr, nullptr, ws + w.T, (int)r, M, 64, (int)r, s) != hipSuccess)
-            return ABT_EHIP;
+        if (conv_chain(act, g, nullptr, B, nullptr, ws + w.T, m, r, s) != hipSuccess) return ABT_EHIP;
         Tp = ws + w.T;
     }
+    // as a linear layer (backward, us, gathered before / now: 7 x 7 x 2048, m = 512, r = 64, batch 256 69 / 48, batch 1 34 / 27; 14 x 14 x
+    // 1024, m = 256, batch 128 60 / 46; 56 x 56 x 256, m = 128, batch 128 198 / 142, r = 256 406 / 271)
+    if (is_linear(g)) return linear_bwd(dY, act, Tp, A, B, dAct, dA, dB, M, m, g.C, r, dt, accumulate, workspace, workspace_bytes, SIZE_MAX, stream);
     if (dAct || dB) {
         // dT = dY A = dY (A^T)^T: first stage of the plain chain on the transposed factor
         const TransposeJob tj{A, ws + w.At, (int)m, (int)r};

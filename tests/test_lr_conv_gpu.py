@@ -180,3 +180,24 @@ def test_config4_native_full_size(case):
     c = gen.conv_case(N, H, W, C, m, r, 3, 3, seed=3 + 200 + N + C)
     errs = check(c)
     print(name, errs)
+
+
+@pytest.mark.parametrize("N,side,C,m,r", [(1, 1, 64, 64, 32), (3, 5, 128, 64, 96), (2, 7, 2048, 512, 64), (21, 56, 64, 128, 128),
+                                          (22, 55, 64, 64, 192), (9, 30, 192, 128, 320)])
+@pytest.mark.parametrize("keep_T", [True, False])
+def test_one_by_one_window_is_the_linear_layer(N, side, C, m, r, keep_T):
+    # the same kernels, so the same bits; above 65536 rows the forward of r = 128 and 192 keeps the gathered kernel (another order
+    # of the fp32 sums: bf16 results differ by a rounding)
+    g = torch.Generator(device="cuda").manual_seed(N * side + C + m + r)
+    rn = lambda std, *sh: (torch.randn(sh, generator=g, device="cuda") * std).to(BF)
+    act, dY, A, B = rn(1, N, side, side, C), rn(1e-2, N * side * side, m), rn(r ** -0.5, m, r), rn(C ** -0.5, r, C)
+    X = act.view(-1, C)
+    Y, T = abt.lr_conv_fwd(act, A, B, 1, 1)
+    Yl, Tl = abt.lr_linear_fwd(X, A, B)
+    if X.shape[0] > 65536:
+        assert rel(host(Y), host(Yl)) < TOL and rel(host(T), host(Tl)) < TOL
+    else:
+        assert torch.equal(Y, Yl) and torch.equal(T, Tl)
+    out = abt.lr_conv_bwd(dY, act, T if keep_T else None, A, B, 1, 1)
+    ref = abt.lr_linear_bwd(dY, X, T, A, B)
+    assert torch.equal(out[0].view_as(ref[0]), ref[0]) and torch.equal(out[1], ref[1]) and torch.equal(out[2], ref[2])
