@@ -144,17 +144,20 @@ bool narrow_chain(const ChainProblem* problems, int n, int64_t M, int p, int q, 
 // wins back (14 x 14 x 256, 12544 rows: 28 / 26, r = 192 45 / 32) except where the patches are strided
 // (28 x 28 x 128, stride 2: 17 / 20; r = 192 27 / 24) and not too many for one row block (7 x 7 x 512, 3 x 3, stride 2,
 // r = 96: 1 image 42 / 38, 4 images 43 / 44; r = 64 34 / 35).
-bool narrow_gather(int64_t row_blocks, int mul, int p, int q, int R) {
+// Through a window in LDS (stride 1) also for few rows at r <= 64, where one block of channels keeps the order of the sums that the plain
+// kernels have on an explicit patch matrix (56 x 56 x 64, batch 1 17 / 15; with more blocks it would be 23 / 20 for 14 x 14 x 256,
+// batch 1 to 32, at r = 128 26 / 29).
+bool narrow_gather(int64_t row_blocks, bool window, int mul, int p, int q, int R) {
     if (g_chain_rows.load() != 0 || g_chain_parts.load() != 0 || !chain4_supports(R, p, q)) return false;
-    return row_blocks > 128 || (mul == 2 && (R <= 64 || (R == 96 && (p <= 4096 || row_blocks > 1))));
+    return (window && R <= 64) || row_blocks > 128 || (mul == 2 && (R <= 64 || (R == 96 && (p <= 4096 || row_blocks > 1))));
 }
 
 // the gathered chain (factored convolution): same choice of work-group height, no column parts
 hipError_t chain_gather(const void* image, const PatchGeom& g, const void* P, const void* Q, void* Yout, void* Tout,
                         int t_pitch, int64_t M, int q, int R, hipStream_t s) {
     const int p = g.kh * g.kw * ((g.Cin + 63) / 64) * 64;
-    if (g.sign > 0 && narrow_gather(ceil_div(M, 128), g.mul, p, q, R)) {
-        const ChainGather cg{g.H, g.W, g.Cin, 0, g.kh, g.kw, g.sign, g.kh / 2, g.kw / 2, g.RH, g.RW, g.mul, 1, 0, 0, g.RH, g.RW};
+    const ChainGather cg{g.H, g.W, g.Cin, 0, g.kh, g.kw, g.sign, g.kh / 2, g.kw / 2, g.RH, g.RW, g.mul, 1, 0, 0, g.RH, g.RW};
+    if (g.sign > 0 && narrow_gather(ceil_div(M, 128), g.Cin <= 64 && chain4_window(cg, R, narrow_rows(M)), g.mul, p, q, R)) {
         const GatherProblem one{image, P, Q, Yout, Tout, M, cg};
         const hipError_t e = launch_chain4_gather_bf16(&one, 1, q, R, t_pitch, narrow_rows(M), narrow_parts(ceil_div(M, narrow_rows(M)), p, q, Yout != nullptr), s);
         if (e != hipErrorInvalidValue) return e;
@@ -406,9 +409,20 @@ ConvBwdLayout conv_bwd_layout(const abt_conv_geom& g, int64_t m, int64_t r) {
 // 128: 17 / 42 to 41 / 86; 7 x 7 x 512, 3 x 3: 22 / 34); for a single slab (1 x 1, r <= 64: 17 / 18); and for large batches
 // (28 x 28 x 128, r = 64: 32 images 26 / 28, 128 images 53 / 83). With few row blocks and one launch on both sides the
 // others' deeper prefetch wins: 28 x 28 x 128, 16 images 24 / 23, r = 384 58 / 50; 27 x 27 x 192, 32 images, r = 192 45 / 43.
-bool narrow_dact(const abt_conv_geom& g, int p) {
+// Through a window in LDS always, with blocks of 64 channels while those find idle compute units (narrow_dact_chunk): 14 x 14 x 256,
+// batch 1 to 32, r = 64 23 / 24, r = 128 24 / 29, r = 192 28 / 36; 28 x 28 x 128, batch 8 23 / 23, 24 / 27, 29 / 33.
+bool narrow_dact(const abt_conv_geom& g, int p, bool window) {
     if (g_chain_rows.load() != 0 || g_chain_parts.load() != 0 || !chain4_supports(64, p, 64)) return false;
-    return g.stride == 2 || g.C > conv_dact_chunk(g.C) || p == 64 || ceil_div(g.N * g.H * g.W, 128) > 192;
+    return window || g.stride == 2 || g.C > conv_dact_chunk(g.C) || p == 64 || ceil_div(g.N * g.H * g.W, 128) > 192;
+}
+
+// Output channels per work-group there: 64 where all of those fit one launch and the compute units (a wider block: 14 x 14 x 256, batch 8, r = 128
+// 29 us, 24 with 64; 7 x 7 x 512, batch 64, r = 192 42 / 36; not with more: 28 x 28 x 128, batch 32, r = 128 31 / 34).
+int narrow_dact_chunk(const abt_conv_geom& g) {
+    const int64_t parts = g.C / 64;
+    if (parts * (g.stride == 2 ? 4 : 1) <= kChainMaxGroups && parts * ceil_div(g.N * g.H * g.W, 128) <= 256) return 64;
+    for (int v : {192, 160, 128, 96}) if (g.C % v == 0) return v;
+    return 64;
 }
 
 // dAct[q, c] = sum over taps and j of dT[(q - shift(tap)) / stride, j] B[j, tap, c] (only where the division
@@ -423,10 +437,11 @@ hipError_t conv_dact(const void* dT, const void* B, void* dAct, void* Pst, const
     const int Ho = (int)conv_out(g.H, g.stride), Wo = (int)conv_out(g.W, g.stride);
     const int64_t M_in = g.N * g.H * g.W;
     hipError_t e;
-    if (narrow_dact(g, taps * r_pad)) {
-        int chunk = 64;
-        for (int v : {192, 160, 128, 96}) if (C % v == 0) { chunk = v; break; }
-        const bool by_parity = g.stride == 2;
+    const bool by_parity = g.stride == 2;
+    const int nchunk = narrow_dact_chunk(g);
+    const ChainGather whole{Ho, Wo, r, 0, g.kh, g.kw, -1, g.kh / 2, g.kw / 2, (int)g.H, (int)g.W, 1, 1, 0, 0, (int)g.H, (int)g.W};
+    if (narrow_dact(g, taps * r_pad, !by_parity && chain4_window(whole, nchunk, 128))) {
+        const int chunk = nchunk;
         GatherProblem pr[kChainMaxGroups];
         int n = 0;
         bool wide = false;                       // a window that 32-bit offsets do not cover: the kernels below check again
@@ -434,7 +449,7 @@ hipError_t conv_dact(const void* dT, const void* B, void* dAct, void* Pst, const
         if (e != hipSuccess) return e;
         for (int cls = by_parity ? 3 : 0; cls >= 0 && !wide; --cls) {      // most taps first
             const int py = cls >> 1, px = cls & 1;
-            ChainGather cg{Ho, Wo, r, 0, g.kh, g.kw, -1, g.kh / 2, g.kw / 2, (int)g.H, (int)g.W, 1, 1, 0, 0, (int)g.H, (int)g.W};
+            ChainGather cg = whole;
             int64_t before = 0;
             if (by_parity) {
                 const int ny = parity_count(g.kh, py), nx = parity_count(g.kw, px), ny0 = parity_count(g.kh, 0), nx0 = parity_count(g.kw, 0);

@@ -14,7 +14,8 @@
 //     convolution's patches) each lane has one pixel for the whole kernel and loads the 16-byte pieces of
 //     its operand directly: a tap is one range check per lane, and neighbouring pixels keep the lines in
 //     L1.  (The direct loads on a matrix: 14 % slower at 39597 x 3072, r = 64 to 192.  The tile on an
-//     image: four pixels per lane, spills, the 3 x 3 layers 25 % slower.)
+//     image: four pixels per lane, spills, the 3 x 3 layers 25 % slower.)  Where the window of the image that a row block's
+//     patches touch is small (stride 1, up to 256 pixels), it goes to LDS once per 64 channels and all taps read it there.
 //   * The factors are shared by the four waves: slabs of 64 columns of P, then 64 rows of Q, travel
 //     through registers (two slabs ahead) into two LDS buffers, one barrier per slab.
 //   * The first operand's rows are fed in the order pi() (two bits of the row number swapped), so that the
@@ -48,6 +49,10 @@ __device__ __forceinline__ void wave_lds_order() {
 }
 
 constexpr int kMaxRows = 128, NT = 256;
+constexpr int kWinPieces = 8, kMaxWindow = 32 * kWinPieces;          // image window in LDS: 16-byte pieces per thread, pixels of 64 channels
+// Where the first operand comes from: a matrix; an image, per lane; an image through a window in LDS (one block of 64 channels;
+// several, with nine taps).
+enum Source { kMatrix, kGather, kWindow, kWindows };
 constexpr int kStagePitch = 64 * 2 + 16;             // staging tile: 32 rows x 64 columns, rows 36 words apart
 constexpr int kStage = 32 * kStagePitch;
 
@@ -65,7 +70,7 @@ struct C4 {
     // Slabs in flight per wave beside the one in use (3 and 4 measured the same, and spilled at R >= 96), and
     // work-groups per compute unit by registers (512 per lane and SIMD) and LDS (160 KB).
     static constexpr int D = 2;
-    template <bool GATHER> static constexpr int occupancy() { return R <= 96 || (GATHER && R == 128) ? 3 : 2; }
+    template <Source S> static constexpr int occupancy() { return R <= 96 || ((S == kGather || S == kWindow) && R == 128) ? 3 : 2; }
     static constexpr int U = D % 2 ? 2 * D : D;          // unrolled slabs: whole turns of the ring and of the two LDS buffers
 };
 template <int XB>
@@ -86,12 +91,14 @@ struct C4Args {
     C4Entry e[kChainMaxGroups];
     int q, t_pitch, parts, stream_out;
     int rows;                                            // per work-group: four waves of rows / 4 <= 32
+    int win_slots;                                       // pixels that the window in LDS holds, a multiple of 8
 };
 
-template <int R, bool GATHER>
-__global__ __launch_bounds__(NT, (C4<R>::template occupancy<GATHER>())) void chain4_bf16_kernel(C4Args args) {
+template <int R, Source SRC>
+__global__ __launch_bounds__(NT, (C4<R>::template occupancy<SRC>())) void chain4_bf16_kernel(C4Args args) {
     extern __shared__ __align__(1024) unsigned char lds[];
     using C = C4<R>;
+    constexpr bool GATHER = SRC != kMatrix, WINDOW = SRC == kWindow || SRC == kWindows;
     constexpr int CB = C::CB, KB = C::KB, NCH = C::NCH, D = C::D, U = C::U;
     const C4Entry en = args.e[blockIdx.y];
     const int64_t M = en.M;
@@ -134,7 +141,12 @@ __global__ __launch_bounds__(NT, (C4<R>::template occupancy<GATHER>())) void cha
         };
         const int ry = g.cy > g.kh - 1 - g.cy ? g.cy : g.kh - 1 - g.cy, rx = g.cx > g.kw - 1 - g.cx ? g.cx : g.kw - 1 - g.cx;
         const int64_t reach = (int64_t)ry * g.W + rx, pixels = (M / per) * g.H * g.W;
-        const int64_t c0 = centre(row0, 0), c1 = centre(row0 + rows_valid - 1, 1);
+        auto pixel_of = [&](int64_t i) -> int64_t {      // mul = 1
+            const int64_t img = i / per;
+            const int rem = (int)(i - img * per), y = rem / g.RW;
+            return (img * g.H + y) * g.W + (rem - y * g.RW);
+        };
+        const int64_t c0 = WINDOW ? pixel_of(row0) : centre(row0, 0), c1 = WINDOW ? pixel_of(row0 + rows_valid - 1) : centre(row0 + rows_valid - 1, 1);
         const int64_t p0 = c0 > reach ? c0 - reach : 0, p1 = c1 + reach + 1 < pixels ? c1 + reach + 1 : pixels;
         xres = make_rsrc(en.X + p0 * g.Cin, (p1 - p0) * g.Cin * 2);
         const int row = row_of(lj);
@@ -142,9 +154,10 @@ __global__ __launch_bounds__(NT, (C4<R>::template occupancy<GATHER>())) void cha
         const int rem = i - img * per, y = rem / g.RW, x = rem - y * g.RW;
         gx = g.mul * x;
         gy = row >= 0 ? g.mul * y : -(1 << 24);                  // no row: never inside the image
-        xoff[0] = (int)((((int64_t)img * g.H + (int64_t)g.mul * y) * g.W + gx - p0) * g.Cin + 8 * lh) * 2;
-        const int tap = rot1 / g.cpb;
-        xcb = rot1 - tap * g.cpb;
+        const int64_t own = ((int64_t)img * g.H + (int64_t)g.mul * y) * g.W + gx - p0;
+        xoff[0] = WINDOW ? (int)own : (int)(own * g.Cin + 8 * lh) * 2;       // (window: the slot of the centre)
+        const int tap = WINDOW ? (int)((unsigned)rb % (unsigned)(g.kh * g.kw)) : rot1 / g.cpb;
+        if (!WINDOW) xcb = rot1 - tap * g.cpb;
         xky = tap / g.kw;
         xkx = tap - xky * g.kw;
     } else {
@@ -181,52 +194,132 @@ __global__ __launch_bounds__(NT, (C4<R>::template occupancy<GATHER>())) void cha
     const int psrc = (pr * p + pc * 8) * 2;
     const int pdst = pr * 128 + ((pc ^ ((pr >> 1) & 7)) << 4);
     int pslab = rot1;
+    // window: taps in turn from the first on, then the next block of channels
+    const int taps = WINDOW ? g.kh * g.kw : 1;
+    int ptap = WINDOW ? xky * g.kw + xkx : 0, pleft = taps, pcb = 0;
+    if constexpr (WINDOW) pslab = ptap * g.cpb;
     auto load_p = [&](u32x4 (&d)[NCH]) {
 #pragma unroll
         for (int e = 0; e < NCH; ++e) d[e] = buf_load16(pres, psrc, pslab * 128 + e * 64 * p);
-        if (++pslab == ns1) pslab = 0;
+        if constexpr (WINDOW) {
+            if (++ptap == taps) ptap = 0;
+            if (--pleft == 0) { pleft = taps; if (++pcb == g.cpb) pcb = 0; }
+            pslab = ptap * g.cpb + pcb;
+        } else if (++pslab == ns1) pslab = 0;
     };
     auto store_p = [&](const u32x4 (&v)[NCH], int buf) {
 #pragma unroll
         for (int e = 0; e < NCH; ++e) *reinterpret_cast<u32x4*>(lds + buf * C::slab + pdst + e * 4096) = v[e];
     };
     const int pread = pj * 128 + ((lh ^ ((pj >> 1) & 7)) << 4);
-    u32x4 xr[D][4], fr[D][NCH];
+    u32x4 fr[D][NCH];
+    if constexpr (WINDOW) {
+        // The image window of the row block, a block of 64 channels at a time: pixels of 128 bytes, chunks XOR-swizzled by the
+        // pixel, a row of zeros behind them.  It is loaded once, as whole lines, and every tap reads its operands there: pixel
+        // shift and range check are an address (outside the image: the zeros).  Loading each tap's pieces from memory
+        // instead, 32 lines per instruction and 9 instructions for each 16 bytes, is bound by those requests: forward,
+        // batch 256, 14 x 14 x 256, r = 64 41 -> 30 us, r = 32 37 -> 23; 28 x 28 x 128, r = 64 74 -> 50, r = 192 125 -> 118; activation gradient
+        // of 56 x 56 x 64, batch 100, r = 128 153 -> 94, r = 256 283 -> 154.  Now the LDS reads are the most of a slab (48 KB at R = 64 for
+        // 256 cycles of matrix instructions, each wave reading all of P).
+        static_assert(D == 2, "ring parity");
+        unsigned char* const win = lds + 2 * C::slab;
+        const int slots = args.win_slots;
+        const int wch = tid & 7;
+        const int wsrc = ((tid >> 3) * g.Cin + 8 * wch) * 2, wstep = 32 * g.Cin * 2;
+        unsigned char* const wdst = win + (tid >> 3) * 128 + ((wch ^ ((tid >> 4) & 7)) << 4);
+        u32x4 wr[kWinPieces];
+        auto load_w = [&](u32x4& d, int e, int cb) {     // past the window, the channels or the last block: zeros
+            d = buf_load16(xres, cb * 64 + 8 * wch < g.Cin && cb < g.cpb ? wsrc + e * wstep : kBufNowhere, cb * 128);
+        };
+        auto store_w = [&]() {
 #pragma unroll
-    for (int d = 0; d < D; ++d) { load_p(fr[d]); load_x(xr[d]); }
-    store_p(fr[0], 0);
-    load_p(fr[0]);
-    wg_barrier();                                        // slab 0 is in buffer 0
-    auto slab1 = [&](const int u) __attribute__((always_inline)) {     // u: the slab's place in the unrolled loop
-        const int d = u % D, d1 = (u + 1) % D;
-        if constexpr (!GATHER) store_x(xr[d]);
-        store_p(fr[d1], (u & 1) ^ 1);
-        load_p(fr[d1]);
-        if constexpr (!GATHER) { load_x(xr[d]); wave_lds_order(); }
-        __builtin_amdgcn_sched_barrier(0);
-        const unsigned char* base = lds + (u & 1) * C::slab;
-        u32x4 xf[4];
+            for (int e = 0; e < kWinPieces; ++e)
+                if (32 * e + (tid >> 3) < slots) *reinterpret_cast<u32x4*>(wdst + e * 4096) = wr[e];
+        };
 #pragma unroll
-        for (int j = 0; j < 4; ++j) xf[j] = GATHER ? xr[d][j] : *reinterpret_cast<const u32x4*>(stage + (xread ^ (j << 5)));
+        for (int e = 0; e < kWinPieces; ++e) load_w(wr[e], e, 0);
+        load_p(fr[0]);
+        load_p(fr[1]);
+        if (tid < 8) *reinterpret_cast<u32x4*>(win + slots * 128 + tid * 16) = u32x4{0, 0, 0, 0};
+        store_w();
+        store_p(fr[0], 0);
+        load_p(fr[0]);
+        wg_barrier();
+        int cb = 0;
+        auto slab1 = [&](const int u, const int e) __attribute__((always_inline)) {     // u: parity of the slab; e: piece of the next window
+            store_p(fr[(u + 1) & 1], (u & 1) ^ 1);
+            load_p(fr[(u + 1) & 1]);
+            if constexpr (SRC == kWindows) { if (e < kWinPieces) load_w(wr[e], e, cb + 1); }
+            __builtin_amdgcn_sched_barrier(0);
+            const int dy = g.sign * (xky - g.cy), dx = g.sign * (xkx - g.cx), w = xoff[0] + dy * g.W + dx;
+            const bool ok = (unsigned)(gy + dy) < (unsigned)g.H && (unsigned)(gx + dx) < (unsigned)g.W;
+            const int xa = ok ? w * 128 + ((lh ^ ((w >> 1) & 7)) << 4) : slots * 128;
+            if (++xkx == g.kw) { xkx = 0; if (++xky == g.kh) xky = 0; }
+            const unsigned char* base = lds + (u & 1) * C::slab;
+            u32x4 xf[4];
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
+            for (int j = 0; j < 4; ++j) xf[j] = *reinterpret_cast<const u32x4*>(win + (xa ^ (j << 5)));
 #pragma unroll
-            for (int b = 0; b < CB; ++b)
-                acc[b] = mfma16(*reinterpret_cast<const u32x4*>(base + (pread ^ (j << 5)) + b * 4096), xf[j], acc[b]);
+            for (int j = 0; j < 4; ++j) {
+#pragma unroll
+                for (int b = 0; b < CB; ++b)
+                    acc[b] = mfma16(*reinterpret_cast<const u32x4*>(base + (pread ^ (j << 5)) + b * 4096), xf[j], acc[b]);
+            }
+            wg_barrier();
+        };
+        if constexpr (SRC == kWindow) {
+            int s1 = 0;
+            for (; s1 + 2 <= taps; s1 += 2) { slab1(0, 0); slab1(1, 0); }
+            if (s1 < taps) slab1(0, 0);
+        } else {
+            auto block = [&](const int u) __attribute__((always_inline)) {       // nine taps, the first of parity u
+#pragma unroll
+                for (int i = 0; i < 9; ++i) slab1(u + i, i);
+                store_w();
+                wg_barrier();
+                ++cb;
+            };
+            while (cb + 2 <= g.cpb) { block(0); block(1); }
+            if (cb < g.cpb) block(0);
         }
-        if constexpr (GATHER) load_x(xr[d]); else wave_lds_order();
-        wg_barrier();                                    // this slab's buffer may be overwritten, the other one is filled
-    };
-    // whole turns without a branch inside (a path that skips slabs would make the compiler wait for the
-    // youngest loads at the top of every turn), then the rest
-    int s1 = 0;
-    for (; s1 + U <= ns1; s1 += U) {
+    } else {
+        u32x4 xr[D][4];
 #pragma unroll
-        for (int u = 0; u < U; ++u) slab1(u);
+        for (int d = 0; d < D; ++d) { load_p(fr[d]); load_x(xr[d]); }
+        store_p(fr[0], 0);
+        load_p(fr[0]);
+        wg_barrier();                                        // slab 0 is in buffer 0
+        auto slab1 = [&](const int u) __attribute__((always_inline)) {     // u: the slab's place in the unrolled loop
+            const int d = u % D, d1 = (u + 1) % D;
+            if constexpr (!GATHER) store_x(xr[d]);
+            store_p(fr[d1], (u & 1) ^ 1);
+            load_p(fr[d1]);
+            if constexpr (!GATHER) { load_x(xr[d]); wave_lds_order(); }
+            __builtin_amdgcn_sched_barrier(0);
+            const unsigned char* base = lds + (u & 1) * C::slab;
+            u32x4 xf[4];
+#pragma unroll
+            for (int j = 0; j < 4; ++j) xf[j] = GATHER ? xr[d][j] : *reinterpret_cast<const u32x4*>(stage + (xread ^ (j << 5)));
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+#pragma unroll
+                for (int b = 0; b < CB; ++b)
+                    acc[b] = mfma16(*reinterpret_cast<const u32x4*>(base + (pread ^ (j << 5)) + b * 4096), xf[j], acc[b]);
+            }
+            if constexpr (GATHER) load_x(xr[d]); else wave_lds_order();
+            wg_barrier();                                    // this slab's buffer may be overwritten, the other one is filled
+        };
+        // whole turns without a branch inside (a path that skips slabs would make the compiler wait for the
+        // youngest loads at the top of every turn), then the rest
+        int s1 = 0;
+        for (; s1 + U <= ns1; s1 += U) {
+#pragma unroll
+            for (int u = 0; u < U; ++u) slab1(u);
+        }
+#pragma unroll
+        for (int u = 0; u + 1 < U; ++u)
+            if (s1 + u < ns1) slab1(u);
     }
-#pragma unroll
-    for (int u = 0; u + 1 < U; ++u)
-        if (s1 + u < ns1) slab1(u);
 
     // ------------------------------------------------------------------ stage 2's first factor slabs, and T
     const int ntile_all = q >> 6;
@@ -364,25 +457,34 @@ __global__ __launch_bounds__(NT, (C4<R>::template occupancy<GATHER>())) void cha
         if (t1 + u < ntile) tile2(u);
 }
 
-template <int R, bool GATHER>
+// pixels from a row block's first patch to its last (mul = 1)
+int64_t window_pixels(const ChainGather& g, int rows) {
+    const int64_t ry = g.cy > g.kh - 1 - g.cy ? g.cy : g.kh - 1 - g.cy, rx = g.cx > g.kw - 1 - g.cx ? g.cx : g.kw - 1 - g.cx;
+    return (g.RH == g.H && g.RW == g.W ? rows : grid_window(rows, g.RH, g.RW, 1, g.H, g.W)) + 2 * (ry * g.W + rx);
+}
+
+template <int R, Source SRC>
 hipError_t launch_r(const C4Args& args, int G, int64_t blocks, hipStream_t s) {
-    static_assert(C4<R>::lds_bytes <= 160 * 1024, "LDS budget");
+    static_assert(2 * C4<R>::slab + (kMaxWindow + 1) * 128 <= 160 * 1024 && C4<R>::lds_bytes <= 160 * 1024, "LDS budget");
+    constexpr bool window = SRC == kWindow || SRC == kWindows;
+    constexpr int largest = window ? 2 * C4<R>::slab + (kMaxWindow + 1) * 128 : C4<R>::lds_bytes;
     static std::atomic<bool> attr_set{false};
     if (!attr_set.load(std::memory_order_acquire)) {
-        const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&chain4_bf16_kernel<R, GATHER>),
-                                                 hipFuncAttributeMaxDynamicSharedMemorySize, C4<R>::lds_bytes);
+        const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&chain4_bf16_kernel<R, SRC>),
+                                                 hipFuncAttributeMaxDynamicSharedMemorySize, largest);
         if (e != hipSuccess) return e;
         attr_set.store(true, std::memory_order_release);
     }
-    hipLaunchKernelGGL((chain4_bf16_kernel<R, GATHER>), dim3((unsigned)(blocks * args.parts), (unsigned)G), dim3(NT), C4<R>::lds_bytes,
-                       s, args);
+    int bytes = C4<R>::lds_bytes;                        // (the staging tiles lie over the window)
+    if (window && 2 * C4<R>::slab + (args.win_slots + 1) * 128 > bytes) bytes = 2 * C4<R>::slab + (args.win_slots + 1) * 128;
+    hipLaunchKernelGGL((chain4_bf16_kernel<R, SRC>), dim3((unsigned)(blocks * args.parts), (unsigned)G), dim3(NT), bytes, s, args);
     return hipGetLastError();
 }
 
-template <bool GATHER>
+template <Source SRC>
 hipError_t launch_any(int R, const C4Args& args, int G, int64_t blocks, hipStream_t s) {
     switch (R) {
-#define ABT_CASE(RR) case RR: return launch_r<RR, GATHER>(args, G, blocks, s);
+#define ABT_CASE(RR) case RR: return launch_r<RR, SRC>(args, G, blocks, s);
         ABT_CASE(32) ABT_CASE(64) ABT_CASE(96) ABT_CASE(128) ABT_CASE(160) ABT_CASE(192)
 #undef ABT_CASE
         default: return hipErrorInvalidValue;
@@ -390,6 +492,13 @@ hipError_t launch_any(int R, const C4Args& args, int G, int64_t blocks, hipStrea
 }
 
 }  // namespace
+
+bool chain4_window(const ChainGather& g, int R, int rows) {
+    const int taps = g.kh * g.kw, cpb = (g.Cin + 63) / 64;
+    if (g.mul != 1 || taps < 2 || (cpb > 1 && taps != 9)) return false;
+    const int64_t w = window_pixels(g, rows);
+    return w <= kMaxWindow && !(R == 128 && cpb == 1 && w > 192) && !(R >= 128 && g.Cin <= 32);
+}
 
 bool chain4_supports(int R, int p, int q) {
     return R >= 32 && R <= 192 && R % 32 == 0 && p >= 64 && p % 64 == 0 && q % 64 == 0 && p <= (1 << 20) && q <= (1 << 20);
@@ -407,15 +516,16 @@ hipError_t launch_chain4_bf16(const ChainProblem* problems, int G, int64_t M, in
     if (parts > q / 64) return hipErrorInvalidValue;
     const int64_t out_bytes = M * ((problems[0].Yout ? q : 0) + R) * 2;
     a.q = q; a.t_pitch = t_pitch; a.rows = rows; a.parts = parts; a.stream_out = out_bytes >= kStreamOutBytes;
-    return launch_any<false>(R, a, G, ceil_div(M, rows), s);
+    return launch_any<kMatrix>(R, a, G, ceil_div(M, rows), s);
 }
 
 hipError_t launch_chain4_gather_bf16(const GatherProblem* problems, int n, int q, int R, int t_pitch, int rows, int parts, hipStream_t s) {
     if (rows < 4 || rows > kMaxRows || rows % 4) return hipErrorInvalidValue;
     if (!problems || n < 1 || n > kChainMaxGroups || t_pitch < R || parts < 1 || parts > 64) return hipErrorInvalidValue;
     C4Args a{};
-    int64_t blocks = 0, out_bytes = 0;
-    bool second = false;
+    int64_t blocks = 0, out_bytes = 0, window = 0;
+    bool second = false, single = true, windowed = true;
+    const bool single_tap_ok = problems[0].g.kh * problems[0].g.kw > 1;         // the parities of a small window
     for (int i = 0; i < n; ++i) {
         const GatherProblem& c = problems[i];
         ChainGather g = c.g;
@@ -434,13 +544,18 @@ hipError_t launch_chain4_gather_bf16(const GatherProblem* problems, int n, int q
         if (per && (c.M / per) * g.H * g.W > 0x7fffffff) return hipErrorInvalidValue;
         a.e[i] = C4Entry{(const uint16_t*)c.image, (const uint16_t*)c.P, (const uint16_t*)c.Q, (uint16_t*)c.Yout, (uint16_t*)c.Tout, c.M, (int)p, g};
         if (ceil_div(c.M, rows) > blocks) blocks = ceil_div(c.M, rows);
+        if (g.mul == 1 && window_pixels(g, rows) > window) window = window_pixels(g, rows);
+        windowed = windowed && (chain4_window(g, R, rows) || (single_tap_ok && g.kh * g.kw == 1 && g.mul == 1 && g.cpb == 1));
+        single = single && g.cpb == 1;
         out_bytes += c.M * ((c.Yout ? q : 0) + (c.Tout ? R : 0)) * 2;
         second |= c.Yout != nullptr;
     }
     if (parts > 1 && (!second || parts > q / 64)) return hipErrorInvalidValue;
     if (blocks == 0) return hipSuccess;
     a.q = q; a.t_pitch = t_pitch; a.rows = rows; a.parts = parts; a.stream_out = out_bytes >= kStreamOutBytes;
-    return launch_any<true>(R, a, n, blocks, s);
+    a.win_slots = (int)(ceil_div(window, 8) * 8);
+    if (windowed) return single ? launch_any<kWindow>(R, a, n, blocks, s) : launch_any<kWindows>(R, a, n, blocks, s);
+    return launch_any<kGather>(R, a, n, blocks, s);
 }
 
 }  // namespace abt

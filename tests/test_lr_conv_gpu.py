@@ -201,3 +201,24 @@ def test_one_by_one_window_is_the_linear_layer(N, side, C, m, r, keep_T):
     out = abt.lr_conv_bwd(dY, act, T if keep_T else None, A, B, 1, 1)
     ref = abt.lr_linear_bwd(dY, X, T, A, B)
     assert torch.equal(out[0].view_as(ref[0]), ref[0]) and torch.equal(out[1], ref[1]) and torch.equal(out[2], ref[2])
+
+
+# images whose windows go through LDS: windows of 1 and of 256 pixels and one beyond (rows of a block and the reach of its taps), one
+# block of channels and several, channels that are no multiple of 64 (activation gradient: r = 32, 96), parities of odd sides
+WINDOWS = [
+    # N, H, W, C, m, r, kh, kw, stride
+    (1, 1, 1, 64, 64, 32, 3, 3, 1),
+    (129, 14, 14, 192, 64, 64, 3, 3, 1),       # three blocks of channels, an odd number of blocks of nine taps
+    (90, 14, 14, 128, 64, 96, 3, 3, 1),
+    (30, 26, 63, 64, 64, 64, 3, 3, 1),         # 128 rows + 2 (63 + 1) = 256 pixels in the activation gradient
+    (30, 26, 64, 64, 64, 64, 3, 3, 1),         # 258: gathered
+    (7, 56, 56, 64, 64, 192, 3, 3, 1),         # 64 channels per work-group, three blocks
+    (40, 9, 11, 64, 64, 64, 5, 3, 1),
+    (12, 29, 27, 64, 128, 64, 3, 3, 2),
+    (700, 5, 5, 128, 64, 160, 3, 3, 1),        # windows over several images
+]
+
+
+@pytest.mark.parametrize("N,H,W,C,m,r,kh,kw,stride", WINDOWS)
+def test_conv_step_through_windows(N, H, W, C, m, r, kh, kw, stride):
+    check(gen.conv_case(N, H, W, C, m, r, kh, kw, seed=N + H + W + C + r, **({"stride": stride} if stride > 1 else {})))
