@@ -364,6 +364,24 @@ hipError_t conv_chain(const void* act, const abt_conv_geom& g, const void* A, co
     return chain_gather(act, conv_patches_geom(g), B, A, Y, T, (int)r, M, (int)m, (int)r, s);
 }
 
+// Where the two launches for few rows are the faster backward (us, the other kernels / these; m x n, r):
+//   2304 x 768, 96: 1 row 27 / 13, 197 29 / 15, 1000 35 / 18, 4000 43 / 33, 8000 50 / 59; 384: 197 rows 56 / 19, 4000 78 / 74, 8000 89 / 139;
+//   768 x 3072, 32: 197 17 / 10, 4000 34 / 25, 8000 42 / 39; 3072 x 768, 384: 4000 91 / 87; 64 x 64, 96: 197 16 / 9, 2000 22 / 15, 4000 21 / 22;
+//   256 x 1024, 32: 4000 24 / 22.
+// All gradients come from one launch: a factor gradient over something that it reads (kOver) has to wait for its end.
+enum SmallBwd { kNotSmall, kSmall, kOver };
+SmallBwd small_bwd(const void* dY, const void* X, int64_t x_bytes, const void* T, const void* B, const void* dX, const void* dA, const void* dB,
+                   int64_t M, int64_t m, int64_t n, int64_t r) {
+    if (g_chain_rows.load() != 0 || g_chain_parts.load() != 0) return kNotSmall;
+    if (M > (m + n >= 1024 ? 4096 : 2048) || !lr_small_supports(M, (int)m, (int)n, (int)r)) return kNotSmall;
+    auto over = [&](const void* out, int64_t bytes) {
+        return (dA && (overlap(out, bytes, dY, M * m * 2) || overlap(out, bytes, T, M * r * 2))) || (dB && overlap(out, bytes, X, x_bytes)) ||
+               (dX && overlap(out, bytes, B, r * n * 2));
+    };
+    if (over(dX, M * n * 2)) return kNotSmall;
+    return over(dA, m * r * 4) || over(dB, r * n * 4) ? kOver : kSmall;
+}
+
 int linear_bwd(const void* dY, const void* X, const void* T, const void* A, const void* B,
                void* dX, float* dA, float* dB,
                int64_t M, int64_t m, int64_t n, int64_t r, int dt, int accumulate,
@@ -533,7 +551,11 @@ int lr_conv_bwd(const void* dY, const void* act, const void* T, const void* A, c
     // as a linear layer (backward, us, gathered before / now: 7 x 7 x 2048, m = 512, r = 64, batch 256 69 / 48, batch 1 34 / 27; 14 x 14 x
     // 1024, m = 256, batch 128 60 / 46; 56 x 56 x 256, m = 128, batch 128 198 / 142, r = 256 406 / 271)
     if (is_linear(g)) return linear_bwd(dY, act, Tp, A, B, dAct, dA, dB, M, m, g.C, r, dt, accumulate, workspace, workspace_bytes, SIZE_MAX, stream);
-    if (dAct || dB) {
+    // few rows: dT and dA from the kernels of the linear layer (the same bits as on an explicit patch matrix)
+    const bool few = small_bwd(dY, act, g.N * g.H * g.W * g.C * 2, Tp, B, nullptr, dA, dB, M, m, taps * g.C, r) == kSmall;
+    if (few && (dAct || dB)) {
+        if (launch_lr_small_dt(dY, A, dT, M, (int)m, (int)r, s) != hipSuccess) return ABT_EHIP;
+    } else if (dAct || dB) {
         // dT = dY A = dY (A^T)^T: first stage of the plain chain on the transposed factor
         const TransposeJob tj{A, ws + w.At, (int)m, (int)r};
         if (launch_transpose_bf16(&tj, 1, s) != hipSuccess) return ABT_EHIP;
@@ -546,11 +568,13 @@ int lr_conv_bwd(const void* dY, const void* act, const void* T, const void* A, c
     // factor gradients: dA = dY^T T (plain) and dB = patches(act)^T dT (gathered), one launch
     TnJob jobs[2];
     int nj = 0;
-    if (dA) jobs[nj++] = TnJob{dY, Tp, dA, (int)m, 0};
+    if (dA && few) {
+        if (launch_lr_small_grad(dY, nullptr, Tp, nullptr, nullptr, dA, nullptr, nullptr, M, (int)m, (int)g.C, (int)r, acc, s) != hipSuccess) return ABT_EHIP;
+    } else if (dA) jobs[nj++] = TnJob{dY, Tp, dA, (int)m, 0};
     if (dB) jobs[nj++] = TnJob{act, dT, dB, taps * (int)g.C, 1};
     if (dB) {
         if (launch_tn_gather_bf16(jobs, nj, fwd_geom, M, (int)r, acc, (float*)(ws + w.partials), s) != hipSuccess) return ABT_EHIP;
-    } else if (dA) {
+    } else if (nj) {
         if (launch_tn_bf16(jobs, 1, M, (int)r, acc, (float*)(ws + w.partials), s) != hipSuccess) return ABT_EHIP;
     }
     return ABT_OK;
@@ -723,6 +747,22 @@ int linear_bwd(const void* dY, const void* X, const void* T, const void* A, cons
         e = chain(X, B, nullptr, nullptr, ws + w.T, M, (int)n, (int)m, (int)r, s);
         if (e != hipSuccess) return ABT_EHIP;
         Tp = ws + w.T;
+    }
+    const SmallBwd few = small_bwd(dY, X, M * n * 2, Tp, B, dX, dA, dB, M, m, n, r);
+    if (few != kNotSmall) {
+        float* const part = (float*)(ws + w.partials);           // room for both gradients
+        float* const dA_to = few == kOver && dA ? part : dA;
+        float* const dB_to = few == kOver && dB ? part + (dA ? m * r : 0) : dB;
+        if ((dX || dB) && launch_lr_small_dt(dY, A, dT, M, (int)m, (int)r, s) != hipSuccess) return ABT_EHIP;
+        e = launch_lr_small_grad(dY, X, Tp, B, dX, dA_to, dB_to, dT, M, (int)m, (int)n, (int)r, few == kOver ? 0 : acc, s);
+        if (e == hipSuccess && few == kOver) {
+            TnJob done[2];
+            int nd = 0;
+            if (dA) done[nd++] = TnJob{nullptr, nullptr, dA, (int)m, 0};
+            if (dB) done[nd++] = TnJob{nullptr, nullptr, dB, (int)n, 1};
+            e = launch_tn_finish(done, nd, (int)r, acc, part, s);
+        }
+        return e == hipSuccess ? ABT_OK : ABT_EHIP;
     }
     if (dX || dB) {
         // dT = dY A = dY (A^T)^T and dX = dT B = dT (B^T)^T: the forward chain on transposed factors

@@ -180,6 +180,15 @@ constexpr int kTnMaxJobs = 16;   // per launch (all with the same M and R)
 size_t tn_partials_bytes(int64_t M, const TnJob* jobs, int njobs, int R, bool gather = false);
 hipError_t launch_tn_bf16(const TnJob* jobs, int njobs, int64_t M, int R, int accumulate,
                           float* partials, hipStream_t s);
+// out (+)= sums, which lie end to end in the order of the jobs (their operands are not looked at)
+hipError_t launch_tn_finish(const TnJob* jobs, int njobs, int R, int accumulate, const float* sums, hipStream_t s);
+
+// Backward for few rows in two launches: dT = dY A, then dX = dT B, dA = dY^T T and dB = dT^T X together (NULL: not wanted; none
+// may lie over what another reads).  32-bit offsets: M, m, n and r against each other (lr_small_supports).
+bool lr_small_supports(int64_t M, int m, int n, int r);
+hipError_t launch_lr_small_dt(const void* dY, const void* A, void* dT, int64_t M, int m, int r, hipStream_t s);
+hipError_t launch_lr_small_grad(const void* dY, const void* X, const void* T, const void* B, void* dX, float* dA, float* dB, const void* dT,
+                                int64_t M, int m, int n, int r, int accumulate, hipStream_t s);
 
 // Pst [C, taps r_pad] (bf16) from B [r, taps C]: Pst[c, tap r_pad + j] = B[j, tap C + c], zero for j >= r.
 // by_parity: four matrices end to end instead, one per parity (py, px) of the pixel in the order (0,0), (0,1),

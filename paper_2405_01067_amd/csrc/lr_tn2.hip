@@ -561,6 +561,20 @@ hipError_t launch_tn_bf16(const TnJob* jobs, int njobs, int64_t M, int R, int ac
     return launch_tn_common(jobs, njobs, M, R, accumulate, partials, nullptr, s);
 }
 
+hipError_t launch_tn_finish(const TnJob* jobs, int njobs, int R, int accumulate, const float* sums, hipStream_t s) {
+    if (njobs < 1 || njobs > kTnMaxJobs) return hipErrorInvalidValue;
+    Red2Args red{};
+    red.njobs = njobs; red.splits = 1; red.accumulate = accumulate;
+    int blocks = 0;
+    for (int i = 0; i < njobs; ++i) {
+        red.job[i] = Red2Job{sums, jobs[i].out, (int64_t)jobs[i].P * R, blocks};
+        blocks += (int)ceil_div((int64_t)jobs[i].P * R / 4, 256);
+        sums += (size_t)jobs[i].P * R;
+    }
+    hipLaunchKernelGGL(tn2_reduce_kernel, dim3(blocks), dim3(256), 0, s, red);
+    return hipGetLastError();
+}
+
 hipError_t launch_tn_gather_bf16(const TnJob* jobs, int njobs, const PatchGeom& g, int64_t M, int R, int accumulate,
                                  float* partials, hipStream_t s) {
     // patches only (no adjoint form here); 32-bit offsets inside the window of the image that one
