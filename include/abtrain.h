@@ -70,12 +70,13 @@ const char* abt_status_string(int status);
  *
  *     T[M,r] = X[M,n] . B[r,n]^T          Y[M,m] = T[M,r] . A[m,r]^T
  *
- * X, A, B, Y are of type `dt`.  T_save is optional (NULL = T never leaves the chip in the
- * bf16 path); when given it receives T in type `dt` (bf16: T rounded to nearest-even, the
+ * X, A, B, Y are of type `dt`.  T_save is optional; when given it receives T in type `dt` (bf16: T rounded to nearest-even, the
  * same values the second product consumes).
  * Shapes: M >= 1 arbitrary.  ABT_BF16: m, n multiples of 64 and <= 2^20, r a multiple of 32, r <= 384.
  *         ABT_F32: any positive m, n, r.
- * Workspace: lr_linear_fwd_workspace_bytes (0 for ABT_BF16).
+ * Workspace: lr_linear_fwd_workspace_bytes.  ABT_BF16 asks for a place for T, without T_save, where the
+ * two products run one after the other (few rows, and r = 224, 288, 352), and for none elsewhere; a call
+ * that brings none keeps T on the chip.
  * ------------------------------------------------------------------------------------- */
 int lr_linear_fwd(const void* X, const void* A, const void* B, void* Y, void* T_save,
                   int64_t M, int64_t m, int64_t n, int64_t r, int dt,
@@ -135,13 +136,14 @@ int lr_linear_bwd_static(const void* dY, const void* X, const void* T, const voi
  *   forward : X, A, B, Y required, T_save optional (all groups or none).
  *   backward: dY, X, A, B required; T optional (NULL = recomputed); dX, dA, dB optional per group
  *             (a group that trains A passes dB = NULL and the other way round).
- * ABT_BF16: the forward is one launch for all groups; the backward is one launch each for the
+ * ABT_BF16: the forward is one launch (few rows: two) for all groups; the backward is one launch each for the
  * transposes, the dT/dX chain (two if only some groups ask for dX), the factor gradients of all
  * groups and their split reduction.  ABT_F32: the single-group path, group by group.
  * Results per group are those of the single-group calls up to the summation order of dA / dB
  * (the row split depends on the number of tiles in the launch); two grouped calls on the same
  * inputs give bit-identical results.  Workspace: lr_linear_bwd_grouped_workspace_bytes for the
- * backward, lr_linear_fwd_workspace_bytes * G laid end to end for the ABT_F32 forward without T_save.
+ * backward, lr_linear_fwd_workspace_bytes * G laid end to end for the forward without T_save (ABT_BF16: may be
+ * left out, as above).
  * ------------------------------------------------------------------------------------- */
 typedef struct abt_lr_group {
     const void* X;      /* [M, n] */

@@ -138,6 +138,33 @@ bool narrow_chain(const ChainProblem* problems, int n, int64_t M, int p, int q, 
     return true;
 }
 
+// Where the chain runs as two products, T and then Y (forward, us, the fused kernels / two products):
+//   Few rows (of all problems together), too few row blocks for the chip.  768 -> 2304: r = 32 197 rows 8.2 / 7.1, 4000 14.0 / 14.3; r = 96 11.7 / 7.3,
+//     16.3 / 15.4, 8192 rows 20.4 / 23.2; r = 192 4000 24 / 21, 8192 28 / 26; r = 384 37.7 / 9.1, 39 / 25, 42 / 39.  3072 -> 768: r = 96 197 rows 19.3 /
+//     10.5, 4000 22 / 17, 8192 24 / 25; r = 192 31 / 22, 31 / 33; r = 384 39 / 12, 43 / 33, 48 / 48.  More rows at r = 256, and above where the wide
+//     side is Y: 3072 -> 768, r = 256 8192 rows 36 / 35, r = 320 42 / 47; 768 -> 3072, r = 320 46 / 42.  From an image, whose fused kernels wait longer:
+//     3 x 3 on 14 x 14 x 256, r = 64 20 images 23 / 13, 8036 rows 23 / 14, 12544 24 / 20, r = 192 26 / 13, 27 / 25, 28 / 35.
+//     Not where all of P is soon read (64 -> 64, r = 96 5.3 / 6.2; 64 -> 1920, r = 192 6.8 / 6.9, 4000 rows 11 / 15; 256 -> 1024, r = 32 5.3 / 6.0, r =
+//     128 7.9 / 6.4, r = 192 2000 rows 11 / 11, 4000 12.3 / 13.2), but for the ranks above 192, whose fused kernels have few loads in flight (64 -> 1920,
+//     r = 256: 25 / 7; 64 -> 64, r = 384 10.7 / 7.6, r = 224 one row 4.4 / 6.4).
+//   At r = 224, 288 and 352, which have no fused kernel with loads under way during the products, at any number of rows except where their 64-row
+//     blocks come out at nearly whole turns of two per compute unit: 768 -> 2304, r = 224 8000 rows 90 / 33, 16000 92 / 55, 25000 91 / 82, 33000
+//     178 / 100; 3072 -> 768, r = 352 127 / 50, 129 / 76, 134 / 118, 264 / 161, and 50000 266 / 256.
+bool two_products(int64_t rows, int p, int q, int R, bool image) {
+    if (g_chain_rows.load() != 0 || g_chain_parts.load() != 0) return false;
+    const bool small = R > 192 ? p + q >= 256 : (int64_t)p * R >= 24576 && (p >= 384 || rows <= 2048);
+    const bool wide = R == 256 || (R > 256 && q >= 2 * p);
+    if (small && rows <= (image || wide ? 8192 : 4096)) return true;
+    return (R == 224 || R == 288 || R == 352) && p + q >= 256 && rows <= 24000 * ceil_div(rows, 32768);
+}
+// T needs a place, and not over the first operand, whose rows several work-groups read.
+bool two_products(const ChainProblem* problems, int n, int64_t M, int p, int q, int R) {
+    if (!two_products(n * M, p, q, R, false) || !lr_small_supports(M, q, p, R)) return false;
+    for (int g = 0; g < n; ++g)
+        if (!problems[g].Tout || overlap(problems[g].Xin, M * p * 2, problems[g].Tout, M * R * 2)) return false;
+    return true;
+}
+
 // From an image: a lane has one pixel for the whole kernel, while the loader waves of the other kernels compute
 // a range check per 16 bytes.  Forward, us, this kernel / the better of the others, r = 64: 56 x 56 x 64
 // (200704 rows) 50 / 110, 28 x 28 x 128 (50176 rows) 29 / 43; with few row blocks the other kernels' deeper prefetch
@@ -156,6 +183,9 @@ bool narrow_gather(int64_t row_blocks, bool window, int mul, int p, int q, int R
 hipError_t chain_gather(const void* image, const PatchGeom& g, const void* P, const void* Q, void* Yout, void* Tout,
                         int t_pitch, int64_t M, int q, int R, hipStream_t s) {
     const int p = g.kh * g.kw * ((g.Cin + 63) / 64) * 64;
+    if (Tout && t_pitch == R && two_products(M, p, q, R, true) && lr_small_gather_supports(g, M, q, R) &&
+        !overlap(image, (M / (g.RH * g.RW)) * g.H * g.W * g.Cin * 2, Tout, M * R * 2))
+        return launch_lr_small_fwd_gather(image, g, P, Q, Yout, Tout, M, q, R, s);
     const ChainGather cg{g.H, g.W, g.Cin, 0, g.kh, g.kw, g.sign, g.kh / 2, g.kw / 2, g.RH, g.RW, g.mul, 1, 0, 0, g.RH, g.RW};
     if (g.sign > 0 && narrow_gather(ceil_div(M, 128), g.Cin <= 64 && chain4_window(cg, R, narrow_rows(M)), g.mul, p, q, R)) {
         const GatherProblem one{image, P, Q, Yout, Tout, M, cg};
@@ -177,6 +207,7 @@ hipError_t chain_gather(const void* image, const PatchGeom& g, const void* P, co
 hipError_t chain(const void* Xin, const void* P, const void* Q, void* Yout, void* Tout,
                  int64_t M, int p, int q, int R, hipStream_t s) {
     const ChainProblem one{Xin, P, Q, Yout, Tout};
+    if (two_products(&one, 1, M, p, q, R)) return launch_lr_small_fwd(&one, 1, M, p, q, R, s);
     hipError_t e;
     if (narrow_chain(&one, 1, M, p, q, R, s, &e)) return e;
     const ChainShape sh = choose_chain_shape(M, p, q, R, Yout != nullptr, true);
@@ -656,7 +687,8 @@ int ab_merge_stage_ms(float* ms) {
 
 size_t lr_linear_fwd_workspace_bytes(int64_t M, int64_t m, int64_t n, int64_t r, int dt) {
     if (check_lr_shapes(M, m, n, r, dt) != ABT_OK) return 0;
-    return dt == ABT_F32 ? align_up((size_t)M * r * 4, 256) : 0;
+    if (dt == ABT_BF16) return two_products(M, (int)n, (int)m, (int)r, false) && lr_small_supports(M, (int)m, (int)n, (int)r) ? align_up((size_t)M * r * 2, 256) : 0;
+    return align_up((size_t)M * r * 4, 256);
 }
 
 size_t lr_linear_bwd_workspace_bytes(int64_t M, int64_t m, int64_t n, int64_t r, int dt) {
@@ -674,6 +706,9 @@ int lr_linear_fwd(const void* X, const void* A, const void* B, void* Y, void* T_
         return ABT_EALIGN;
     hipStream_t s = (hipStream_t)stream;
     if (dt == ABT_BF16) {
+        // a place for T, if the call came with one, where T is not kept
+        const size_t place = T_save ? 0 : lr_linear_fwd_workspace_bytes(M, m, n, r, dt);
+        if (place && workspace && workspace_bytes >= place && aligned(workspace, 256)) T_save = workspace;
         return chain(X, B, A, Y, T_save, M, (int)n, (int)m, (int)r, s) == hipSuccess ? ABT_OK : ABT_EHIP;
     }
     float* T = (float*)T_save;
@@ -823,14 +858,6 @@ int chain_rows_for_groups(int G, int64_t M, int p, int q, int R) {
 
 // one launch for the problems with a second stage and one for those without
 hipError_t chain_grouped(const ChainProblem* pr, int G, int64_t M, int p, int q, int R, hipStream_t s) {
-    if (!chain2_supports(R, p, q) && !chain2_tall_supports(R, p, q)) {
-        for (int g = 0; g < G; ++g) {
-            if (!pr[g].Yout && !pr[g].Tout) continue;
-            const hipError_t e = chain(pr[g].Xin, pr[g].P, pr[g].Q, pr[g].Yout, pr[g].Tout, M, p, q, R, s);
-            if (e != hipSuccess) return e;
-        }
-        return hipSuccess;
-    }
     for (int second = 1; second >= 0; --second) {
         ChainProblem sel[kChainMaxGroups];
         int n = 0;
@@ -840,8 +867,14 @@ hipError_t chain_grouped(const ChainProblem* pr, int G, int64_t M, int p, int q,
         }
         if (n == 0) continue;
         hipError_t e;
-        if (!narrow_chain(sel, n, M, p, q, R, s, &e))
+        if (two_products(sel, n, M, p, q, R)) {
+            e = launch_lr_small_fwd(sel, n, M, p, q, R, s);
+        } else if (!chain2_supports(R, p, q) && !chain2_tall_supports(R, p, q)) {
+            e = hipSuccess;
+            for (int g = 0; g < n && e == hipSuccess; ++g) e = chain(sel[g].Xin, sel[g].P, sel[g].Q, sel[g].Yout, sel[g].Tout, M, p, q, R, s);
+        } else if (!narrow_chain(sel, n, M, p, q, R, s, &e)) {
             e = launch_chain2_grouped_bf16(sel, n, M, p, q, R, chain_rows_for_groups(n, M, p, q, R), 1, s);
+        }
         if (e != hipSuccess) return e;
     }
     return hipSuccess;
@@ -878,6 +911,9 @@ int lr_linear_fwd_grouped(const abt_lr_group* groups, int G,
     }
     ChainProblem pr[kChainMaxGroups];
     for (int g = 0; g < G; ++g) pr[g] = ChainProblem{groups[g].X, groups[g].B, groups[g].A, groups[g].Y, groups[g].T_save};
+    const size_t place = groups[0].T_save ? 0 : lr_linear_fwd_workspace_bytes(M, m, n, r, dt);
+    if (place && two_products(G * M, (int)n, (int)m, (int)r, false) && workspace && workspace_bytes >= place * G && aligned(workspace, 256))
+        for (int g = 0; g < G; ++g) pr[g].Tout = (char*)workspace + place * g;
     return chain_grouped(pr, G, M, (int)n, (int)m, (int)r, (hipStream_t)stream) == hipSuccess ? ABT_OK : ABT_EHIP;
 }
 

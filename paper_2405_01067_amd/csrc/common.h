@@ -183,9 +183,17 @@ hipError_t launch_tn_bf16(const TnJob* jobs, int njobs, int64_t M, int R, int ac
 // out (+)= sums, which lie end to end in the order of the jobs (their operands are not looked at)
 hipError_t launch_tn_finish(const TnJob* jobs, int njobs, int R, int accumulate, const float* sums, hipStream_t s);
 
-// Backward for few rows in two launches: dT = dY A, then dX = dT B, dA = dY^T T and dB = dT^T X together (NULL: not wanted; none
-// may lie over what another reads).  32-bit offsets: M, m, n and r against each other (lr_small_supports).
+// 32-bit offsets: M, m, n and r against each other
 bool lr_small_supports(int64_t M, int m, int n, int r);
+// The chain for few rows as two products, T and Y or T alone (Yout NULL, for all problems or none); Tout must have a place that lies over no input.
+hipError_t launch_lr_small_fwd(const ChainProblem* problems, int G, int64_t M, int p, int q, int R, hipStream_t s);
+// first operand gathered from an image: sign = +1, shift = 0
+bool lr_small_gather_supports(const PatchGeom& g, int64_t M, int q, int R);
+hipError_t launch_lr_small_fwd_gather(const void* image, const PatchGeom& g, const void* P, const void* Q, void* Yout, void* Tout, int64_t M, int q, int R,
+                                      hipStream_t s);
+
+// Backward for few rows in two launches: dT = dY A, then dX = dT B, dA = dY^T T and dB = dT^T X together (NULL: not wanted; none
+// may lie over what another reads).
 hipError_t launch_lr_small_dt(const void* dY, const void* A, void* dT, int64_t M, int m, int r, hipStream_t s);
 hipError_t launch_lr_small_grad(const void* dY, const void* X, const void* T, const void* B, void* dX, float* dA, float* dB, const void* dT,
                                 int64_t M, int m, int n, int r, int accumulate, hipStream_t s);

@@ -1,10 +1,11 @@
-// Backward of the bf16 factored layer for few rows, in two launches:
+// The bf16 factored layer for few rows, two launches each way:
+//     T[M,r] = X[M,n] . B[r,n]^T,  Y[M,m] = T . A[m,r]^T                (small_nt_kernel, twice)
 //     dT[M,r] = dY[M,m] . A[m,r]                                       (small_dt_kernel)
 //     dX[M,n] = dT . B[r,n],  dA[m,r] = dY^T . T,  dB[r,n] = dT^T . X   (small_grad_kernel, all of them at once)
 //
 // What bounds it: latency.  The kernels for many rows walk a contraction of thousands of columns in one work-group per
 // 64 rows, a barrier per slab of 64, behind a launch that transposes the factors, and the factor gradients
-// come in two more launches.  Here nothing is staged: operands come straight from memory (L2) into registers, a work-group's waves
+// come in two more launches.  Here the backward stages nothing: operands come straight from memory (L2) into registers, a work-group's waves
 // share out the contraction and add their sums once through LDS, and tiles are small, so that a layer of 200 rows is some
 // hundred work-groups.  A factor (or a batch) whose contraction index is its slow dimension is read as it lies: a lane
 // loads, for each of the eight k of its operand, the 4 bytes of two neighbouring columns, and the two columns go to
@@ -13,6 +14,8 @@
 //
 // MFMA 32x32x16 bf16 layout (lane l, j = l % 32, h = l / 32): A operand = 8 values A[j][8h .. 8h+7], B operand
 // = B[8h .. 8h+7][j], accumulator v = C[8 (v / 4) + 4h + v % 4][j].
+#include <atomic>
+
 #include "common.h"
 
 namespace abt {
@@ -37,6 +40,156 @@ __device__ __forceinline__ void unpair(const uint32_t (&d)[8], u32x4 (&op)[2]) {
     for (int i = 0; i < 4; ++i) {
         op[0][i] = __builtin_amdgcn_perm(d[2 * i + 1], d[2 * i], 0x05040100u);
         op[1][i] = __builtin_amdgcn_perm(d[2 * i + 1], d[2 * i], 0x07060302u);
+    }
+}
+
+// ------------------------------------------------------------------ forward
+// C = U V^T (bf16, both operands contraction-fast), T = X B^T and then Y = T A^T: two launches of tiles where the fused kernels have one
+// work-group per row block, which reads all of B before it has a row of T (197 x 768 -> 2304: r = 96 12 us, 7.3 here; r = 384 38, 9.1).
+// Bound by the latency of the loads, so short chains and many of them:
+//   * A work-group of RM CN SK waves has a tile of 32 RM rows and 32 CN columns, a wave 32 x 32 of it and every SK-th unit of 64 of the
+//     contraction (sums through LDS).  Where tiles are few, SK = 8 waves share one (T of 197 x 3072, r = 32: 11 us for both launches; 23 with
+//     a tile of 64 x 64 and SK = 1); where they are many, larger tiles read less (T of 4000 x 3072, r = 384: 32 x 32 58 us, 64 x 128 35).
+//   * Whole 128-byte lines travel through registers (two stages of SK units ahead) into two LDS buffers, one barrier per stage.  (Each
+//     lane loading the pieces of its operand: 32 lines per instruction instead of 8, 197 x 3072, r = 192 16.2 us, 11.1.)
+//   * A wave's tile with 64 x 64 values instead of 32 x 32: no gain below 16000 rows.
+// The order of the sums depends on the rows, the contraction and the rank alone: T is the same bits kept or recomputed, and from an image (a
+// convolution's patches, columns ordered tap, channel) or its patch matrix.
+struct SmallNtEntry { const uint16_t* U; const uint16_t* V; uint16_t* C; };
+struct SmallNt {
+    SmallNtEntry e[kChainMaxGroups];                     // problems of one shape
+    int M, N, K, tiles_n;
+    int64_t u_bytes;
+    int H, W, Cin, kh, kw, RH, RW, mul;                  // image: rows are the pixels of a grid RH x RW, centred on pixel (mul y, mul x)
+};
+
+// this wave's LDS traffic has completed, then s_barrier; global loads in flight stay in flight
+__device__ __forceinline__ void nt_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
+
+template <int RM, int CN, int SK>
+struct Nt {
+    static constexpr int threads = 64 * RM * CN * SK, rows = 32 * RM, cols = 32 * CN;
+    static constexpr int unit = (rows + cols) * 128, stage = SK * unit, lds_bytes = 2 * stage;
+    static constexpr int NU = 4 / CN, NV = 4 / RM;       // 16-byte pieces per thread and stage
+};
+
+template <int RM, int CN, int SK, bool GATHER>
+__global__ __launch_bounds__((Nt<RM, CN, SK>::threads)) void small_nt_kernel(SmallNt p) {
+    using G = Nt<RM, CN, SK>;
+    constexpr int NU = G::NU, NV = G::NV, NT = G::threads;
+    extern __shared__ __align__(16) unsigned char lds[];
+    const int tid = threadIdx.x, lane = tid & 63, j = lane & 31, h = lane >> 5, ch = tid & 7;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int rb = (int)blockIdx.x / p.tiles_n, tn = (int)blockIdx.x - rb * p.tiles_n, row0 = G::rows * rb, col0 = G::cols * tn;
+    const SmallNtEntry en = p.e[blockIdx.y];
+    const rsrc_t ures = make_rsrc(en.U, p.u_bytes), vres = make_rsrc(en.V, (int64_t)p.N * p.K * 2);
+
+    // Piece i of U is chunk ch of row (i NT + tid) / 8 % rows, in unit (i NT + tid) / (8 rows) of the stage; V alike.  In LDS the chunks of a row
+    // are swizzled, so that 16 lanes reading one chunk of 16 rows, and 8 lanes writing a row, meet no bank twice.
+    int uoff[NU], gy[NU], gx[NU], uc[NU], uky[NU], ukx[NU], voff[NV], uslot[NU], vslot[NV];
+    auto unit_u = [&](int i) { return (i * NT + 64 * wave) / (8 * G::rows); };
+    auto unit_v = [&](int i) { return (i * NT + 64 * wave) / (8 * G::cols); };
+#pragma unroll
+    for (int i = 0; i < NU; ++i) {
+        const int row = ((i * NT + tid) / 8) % G::rows, at = row0 + row;
+        uslot[i] = unit_u(i) * G::unit + row * 128 + 16 * (ch ^ ((row >> 1) & 7));
+        if constexpr (GATHER) {
+            const int q = at < p.M ? at : 0, per = p.RH * p.RW, img = q / per, rem = q - img * per, y = rem / p.RW;
+            gx[i] = p.mul * (rem - y * p.RW);
+            uoff[i] = (((img * p.H + p.mul * y) * p.W + gx[i]) * p.Cin + 8 * ch) * 2;
+            gy[i] = at < p.M ? p.mul * y : -(1 << 24);   // no row: never inside the image
+            uc[i] = 64 * unit_u(i); uky[i] = ukx[i] = 0; // channel and tap of the next piece
+        } else {
+            uoff[i] = (at * p.K + 8 * ch) * 2;           // rows past M: outside the descriptor, zeros
+        }
+    }
+#pragma unroll
+    for (int i = 0; i < NV; ++i) {
+        const int row = ((i * NT + tid) / 8) % G::cols;
+        vslot[i] = unit_v(i) * G::unit + (G::rows + row) * 128 + 16 * (ch ^ ((row >> 1) & 7));
+        voff[i] = ((col0 + row) * p.K + 8 * ch) * 2;     // columns past N: outside the descriptor
+    }
+    struct Stage { u32x4 u[NU], v[NV]; } ring[2];
+    const int stages = (p.K + 64 * SK - 1) / (64 * SK);  // the last one may reach past the contraction: zeros there
+    auto load = [&](Stage& d, int t) {                   // stages are loaded in order
+#pragma unroll
+        for (int i = 0; i < NU; ++i) {
+            const int k = 64 * (t * SK + unit_u(i));
+            if constexpr (GATHER) {
+                while (uc[i] >= p.Cin) { uc[i] -= p.Cin; if (++ukx[i] == p.kw) { ukx[i] = 0; ++uky[i]; } }
+                const int dy = uky[i] - p.kh / 2, dx = ukx[i] - p.kw / 2;
+                const bool ok = k < p.K && (unsigned)(gy[i] + dy) < (unsigned)p.H && (unsigned)(gx[i] + dx) < (unsigned)p.W;
+                d.u[i] = buf_load16(ures, ok ? uoff[i] + ((dy * p.W + dx) * p.Cin + uc[i]) * 2 : kBufNowhere, 0);
+                uc[i] += 64 * SK;
+            } else {
+                d.u[i] = buf_load16(ures, k + 8 * ch < p.K ? uoff[i] : kBufNowhere, 2 * k);
+            }
+        }
+#pragma unroll
+        for (int i = 0; i < NV; ++i) {
+            const int k = 64 * (t * SK + unit_v(i));
+            d.v[i] = buf_load16(vres, k + 8 * ch < p.K ? voff[i] : kBufNowhere, 2 * k);
+        }
+    };
+    auto to_lds = [&](const Stage& d, int b) {
+        unsigned char* const at = lds + b * G::stage;
+#pragma unroll
+        for (int i = 0; i < NU; ++i) *reinterpret_cast<u32x4*>(at + uslot[i]) = d.u[i];
+#pragma unroll
+        for (int i = 0; i < NV; ++i) *reinterpret_cast<u32x4*>(at + vslot[i]) = d.v[i];
+    };
+    // This wave: unit s of the stage, rows 32 wr and columns 32 wc of the tile.  The columns are fed in an order (two bits of their number swapped)
+    // that leaves eight neighbouring ones in accumulators 0 .. 7 and 8 .. 15 of a lane, whose row is j.
+    const int s = wave / (RM * CN), wt = wave % (RM * CN), wr = wt / CN, wc = wt % CN;
+    const int pj = (j & 16) | ((j & 4) << 1) | ((j & 8) >> 1) | (j & 3);
+    f32x16 acc;
+    zero(acc);
+    auto multiply = [&](int b) {
+        const unsigned char* const u = lds + b * G::stage + s * G::unit + (32 * wr + j) * 128;
+        const unsigned char* const v = lds + b * G::stage + s * G::unit + (G::rows + 32 * wc + pj) * 128;
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+            acc = mfma16(*reinterpret_cast<const u32x4*>(v + 16 * ((2 * q + h) ^ ((pj >> 1) & 7))),
+                         *reinterpret_cast<const u32x4*>(u + 16 * ((2 * q + h) ^ ((j >> 1) & 7))), acc);
+    };
+    load(ring[0], 0);
+    if (1 < stages) load(ring[1], 1);
+    for (int t = 0; t < stages; t += 2) {
+#pragma unroll
+        for (int e = 0; e < 2; ++e) {
+            if (t + e >= stages) break;
+            to_lds(ring[e], e);                          // read last two stages ago, before the barrier of the stage between
+            if (t + e + 2 < stages) load(ring[e], t + e + 2);
+            nt_barrier();
+            multiply(e);
+        }
+    }
+    const rsrc_t cres = make_rsrc(en.C, (int64_t)p.M * p.N * 2);
+    const bool live = col0 + 32 * wc < p.N;              // N is a multiple of 32
+    const int out = ((row0 + 32 * wr + j) * p.N + col0 + 32 * wc + 8 * h) * 2;          // rows past M are dropped
+    if constexpr (SK == 1) {
+#pragma unroll
+        for (int g = 0; g < 2; ++g) {
+            u32x4 o;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) o[e] = pack2_bf16(acc[8 * g + 2 * e], acc[8 * g + 2 * e + 1]);
+            buf_store16(o, cres, live ? out + 32 * g : kBufNowhere, 0);
+        }
+    } else {
+        float (*red)[RM * CN][16][64] = reinterpret_cast<float (*)[RM * CN][16][64]>(lds);
+        static_assert(sizeof(float) * NT * 16 <= G::lds_bytes);
+        nt_barrier();
+#pragma unroll
+        for (int v = 0; v < 16; ++v) red[s][wt][v][lane] = acc[v];
+        nt_barrier();
+#pragma unroll
+        for (int e = 0; e < 8 / SK; ++e) {
+            const int v = (16 / SK) * s + 2 * e;
+            float t0 = 0.0f, t1 = 0.0f;
+#pragma unroll
+            for (int w = 0; w < SK; ++w) { t0 += red[w][wt][v][lane]; t1 += red[w][wt][v + 1][lane]; }
+            __builtin_amdgcn_raw_buffer_store_b32(pack2_bf16(t0, t1), cres, live ? out + 32 * (v / 8) + 2 * (v % 8) : kBufNowhere, 0, 0);
+        }
     }
 }
 
@@ -262,7 +415,80 @@ __global__ __launch_bounds__(64 * kGradWaves, 2) void small_grad_kernel(SmallGra
 
 bool lr_small_supports(int64_t M, int m, int n, int r) {
     const int64_t widest = m > n ? (m > r ? m : r) : (n > r ? n : r);
-    return M >= 1 && (M + 31) * widest * 2 < kBufMaxBytes && (int64_t)widest * r * 2 < kBufMaxBytes && m % 64 == 0 && n % 64 == 0 && r % 32 == 0;
+    return M >= 1 && (M + 127) * widest * 2 < kBufMaxBytes && (int64_t)widest * r * 2 < kBufMaxBytes && m % 64 == 0 && n % 64 == 0 && r % 32 == 0;
+}
+
+namespace {
+template <int RM, int CN, int SK, bool GATHER>
+hipError_t launch_nt(SmallNt p, int problems, hipStream_t s) {
+    using G = Nt<RM, CN, SK>;
+    static std::atomic<bool> attr_set{false};
+    if (!attr_set.load(std::memory_order_acquire)) {
+        const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&small_nt_kernel<RM, CN, SK, GATHER>),
+                                                 hipFuncAttributeMaxDynamicSharedMemorySize, G::lds_bytes);
+        if (e != hipSuccess) return e;
+        attr_set.store(true, std::memory_order_release);
+    }
+    p.tiles_n = (int)ceil_div(p.N, G::cols);
+    hipLaunchKernelGGL((small_nt_kernel<RM, CN, SK, GATHER>), dim3((unsigned)(ceil_div(p.M, G::rows) * p.tiles_n), (unsigned)problems), dim3(G::threads),
+                       G::lds_bytes, s, p);
+    return hipGetLastError();
+}
+
+// T: a long contraction and few columns.  The smallest tile whose work-groups, one per compute unit, still run all at once.  us for both launches with a
+// tile of 32 x 32 by eight waves / 32 x 64 by eight / 64 x 64 by eight / 64 x 128:
+//   768 -> 2304, r = 384: 197 rows 10.6 / 10.1 / 11.6 / 12.1, 1000 18.3 / 16.2 / 17.3 / 18.3, 2000 27.7 / 26.1 / 23.7 / 24.4, 4000 48 / 40 / 38 / 35;
+//   3072 -> 768, r = 384: 13.2 / 15.4 / 18.6 / 25.6, 22.9 / 17.5 / 21.0 / 28.5, 32.6 / 29.8 / 24.5 / 30.7, 58 / 45 / 41 / 35.
+template <bool GATHER>
+hipError_t launch_t(const SmallNt& p, int problems, hipStream_t s) {
+    auto groups = [&](int rows, int cols) { return problems * ceil_div(p.M, rows) * ceil_div(p.N, cols); };
+    if (groups(32, 32) <= 256) return launch_nt<1, 1, 8, GATHER>(p, problems, s);
+    if (groups(32, 64) <= 256) return launch_nt<1, 2, 4, GATHER>(p, problems, s);
+    if (groups(64, 64) <= 256) return launch_nt<2, 2, 2, GATHER>(p, problems, s);
+    return launch_nt<2, 4, 1, GATHER>(p, problems, s);
+}
+// Y: the contraction is the rank, which four waves read whole (64 x 64 / 64 x 128: 197 x 2304 9.2 / 9.4 at r = 384, 1000 x 2304 15.1 / 15.9,
+// 4000 x 2304 38.8 / 38.1; 32 x 64 shared by eight waves 78)
+hipError_t launch_y(const SmallNt& p, int problems, hipStream_t s) {
+    if (problems * ceil_div(p.M, 64) * ceil_div(p.N, 64) <= 1024) return launch_nt<2, 2, 1, false>(p, problems, s);
+    return launch_nt<2, 4, 1, false>(p, problems, s);
+}
+}  // namespace
+
+hipError_t launch_lr_small_fwd(const ChainProblem* problems, int G, int64_t M, int p, int q, int R, hipStream_t s) {
+    if (G < 1 || G > kChainMaxGroups || !lr_small_supports(M, q, p, R)) return hipErrorInvalidValue;
+    SmallNt t{}, y{};
+    t.M = y.M = (int)M;
+    t.N = R; t.K = p; t.u_bytes = M * p * 2;
+    y.N = q; y.K = R; y.u_bytes = M * R * 2;
+    for (int g = 0; g < G; ++g) {
+        const ChainProblem& c = problems[g];
+        if (!c.Tout || (c.Yout != nullptr) != (problems[0].Yout != nullptr)) return hipErrorInvalidValue;
+        t.e[g] = SmallNtEntry{(const uint16_t*)c.Xin, (const uint16_t*)c.P, (uint16_t*)c.Tout};
+        y.e[g] = SmallNtEntry{(const uint16_t*)c.Tout, (const uint16_t*)c.Q, (uint16_t*)c.Yout};
+    }
+    const hipError_t e = launch_t<false>(t, G, s);
+    return e != hipSuccess || !problems[0].Yout ? e : launch_y(y, G, s);
+}
+
+bool lr_small_gather_supports(const PatchGeom& g, int64_t M, int q, int R) {
+    const int64_t p = (int64_t)g.kh * g.kw * g.Cin, per = (int64_t)g.RH * g.RW;
+    if (g.sign != 1 || g.shift != 0 || g.Cin % 64 || p > (1 << 20) || per < 1 || M % per != 0) return false;
+    return (M / per) * g.H * g.W * g.Cin * 2 < kBufMaxBytes && (p + 127) * R * 2 < kBufMaxBytes && lr_small_supports(M, q, q, R);
+}
+
+hipError_t launch_lr_small_fwd_gather(const void* image, const PatchGeom& g, const void* P, const void* Q, void* Yout, void* Tout, int64_t M, int q, int R,
+                                      hipStream_t s) {
+    if (!Tout || !lr_small_gather_supports(g, M, q, R)) return hipErrorInvalidValue;
+    SmallNt t{}, y{};
+    t.M = y.M = (int)M;
+    t.e[0] = SmallNtEntry{(const uint16_t*)image, (const uint16_t*)P, (uint16_t*)Tout};
+    t.N = R; t.K = g.kh * g.kw * g.Cin; t.u_bytes = (M / ((int64_t)g.RH * g.RW)) * g.H * g.W * g.Cin * 2;
+    t.H = g.H; t.W = g.W; t.Cin = g.Cin; t.kh = g.kh; t.kw = g.kw; t.RH = g.RH; t.RW = g.RW; t.mul = g.mul;
+    y.e[0] = SmallNtEntry{(const uint16_t*)Tout, (const uint16_t*)Q, (uint16_t*)Yout};
+    y.N = q; y.K = R; y.u_bytes = M * R * 2;
+    const hipError_t e = launch_t<true>(t, 1, s);
+    return e != hipSuccess || !Yout ? e : launch_y(y, 1, s);
 }
 
 hipError_t launch_lr_small_dt(const void* dY, const void* A, void* dT, int64_t M, int m, int r, hipStream_t s) {

@@ -1,8 +1,8 @@
-"""The backward kernels for few rows at the edges of their tiles (32 rows, 64 columns of the rank and of the factors), of the
+"""The kernels for few rows at the edges of their tiles (32 rows, 64 columns of the rank and of the factors), of the
 contraction that eight waves share, and of the rule that takes them (2048 or 4096 rows), against fp64.
 
 Tolerance: bf16 has eight significant bits, so a value is off by 2^-8 of itself at most after one rounding: dB carries that of dT, dX
-that of dT and its own; dA only carries fp32 sums of exact products, (M + 1) 2^-24 of the sum of their sizes at most."""
+that of dT and its own, T its own, Y its own beside that of the T it is compared with; dA only carries fp32 sums of exact products, (M + 1) 2^-24 of the sum of their sizes at most."""
 import pytest
 
 torch = pytest.importorskip("torch")
@@ -49,3 +49,55 @@ def test_not_finite_rows_stay_in_their_rows():
     dX = abt.lr_linear_bwd(dY, X, T, A, B, need_dA=False, need_dB=False)[0]
     keep = torch.arange(M, device="cuda") != 33
     assert torch.equal(dX[keep], ref[keep]) and not bool(torch.isfinite(dX[33]).any())
+
+
+def conv_patches(act, kh, kw, stride):
+    N, H, W, C = act.shape
+    p = torch.nn.functional.pad(act, (0, 0, kw // 2, kw // 2, kh // 2, kh // 2))
+    cols = [p[:, y:y + H:stride, x:x + W:stride] for y in range(kh) for x in range(kw)]
+    return torch.cat(cols, dim=-1).reshape(-1, kh * kw * C).contiguous()
+
+
+# rows / 32 times r / 32 tiles of T: up to 256, 512, 1024, more; Y in tiles of 64 x 64 or 64 x 128; rows 4096 and, at r = 224, 288 and 352, 24000
+@pytest.mark.parametrize("M,m,n,r", [(1, 64, 768, 32), (31, 192, 320, 96), (33, 64, 64, 256), (65, 2304, 768, 384), (197, 768, 3072, 352), (1000, 320, 576, 288),
+                                     (1025, 128, 192, 352), (2000, 64, 128, 384), (4096, 1088, 64, 384), (4096, 1024, 1920, 32), (4097, 576, 192, 224),
+                                     (24000, 64, 192, 288), (24001, 64, 192, 288)])
+def test_forward_of_few_rows(M, m, n, r):
+    g = torch.Generator(device="cuda").manual_seed(M + m + n + r)
+    rn = lambda std, *s: (torch.randn(s, generator=g, device="cuda") * std).to(BF)
+    X, A, B, dY = rn(1, M, n), rn(r ** -0.5, m, r), rn(n ** -0.5, r, n), rn(1e-2, M, m)
+    Y, T = abt.lr_linear_fwd(X, A, B)
+    assert rel(T, X.double() @ B.double().T) < 2 ** -8 and rel(Y, T.double() @ A.double().T) < 2 ** -8
+    # T in a workspace, and again for the factor gradient: the same bits; without a place for it the other kernels
+    assert torch.equal(abt.lr_linear_fwd(X, A, B, save_T=False)[0], Y)
+    kept, again = (abt.lr_linear_bwd(dY, X, t, A, B, need_dX=False, need_dB=False)[1] for t in (T, None))
+    assert torch.equal(kept, again)
+    bare = torch.empty_like(Y)
+    lib, stream = abt.load(), torch.cuda.current_stream().cuda_stream
+    assert lib.lr_linear_fwd(X.data_ptr(), A.data_ptr(), B.data_ptr(), bare.data_ptr(), None, M, m, n, r, abt.ABT_BF16, None, 0, stream) == 0
+    assert rel(bare, T.double() @ A.double().T) < 2 ** -7
+    # an output over the input: Y may lie there, and T sends the call to the other kernels
+    if m == n:
+        over = X.clone()
+        assert torch.equal(abt.lr_linear_fwd(over, A, B, Y=over)[0], Y)
+    # groups of it, each with inputs of its own
+    groups = [dict(X=X, A=A, B=B), dict(X=X * 2, A=A, B=B), dict(X=X, A=A, B=B * 2)]
+    for save in (True, False):
+        outs = abt.lr_linear_fwd_grouped(groups, save_T=save)
+        for k, (Yg, Tg) in zip((1, 2, 2), outs):
+            assert rel(Yg, k * (X.double() @ B.double().T) @ A.double().T) < 2 ** -6.5      # T and Y rounded: 2^-7, and its square
+            assert not save or rel(Tg, k * (X.double() @ B.double().T)) < 2 ** -8
+
+
+@pytest.mark.parametrize("N,H,W,C,k,stride,m,r", [(1, 1, 1, 64, 3, 1, 64, 256), (2, 7, 7, 512, 3, 1, 512, 64), (3, 14, 13, 128, 3, 2, 64, 96), (1, 9, 5, 64, 5, 2, 128, 384),
+                                                  (20, 14, 14, 256, 3, 1, 256, 32), (2, 28, 28, 64, 3, 1, 64, 320), (4, 7, 9, 192, 1, 2, 64, 160)])
+def test_forward_of_few_pixels(N, H, W, C, k, stride, m, r):
+    g = torch.Generator(device="cuda").manual_seed(N + H + C + r)
+    rn = lambda std, *s: (torch.randn(s, generator=g, device="cuda") * std).to(BF)
+    n = k * k * C
+    act, A, B = rn(1, N, H, W, C), rn(r ** -0.5, m, r), rn(n ** -0.5, r, n)
+    P = conv_patches(act, k, k, stride)
+    Y, T = abt.lr_conv_fwd(act, A, B, k, k, stride=stride)
+    Yl, Tl = abt.lr_linear_fwd(P, A, B)
+    assert torch.equal(T, Tl) and torch.equal(Y.reshape(Yl.shape), Yl)
+    assert rel(T, P.double() @ B.double().T) < 2 ** -8 and rel(Yl, T.double() @ A.double().T) < 2 ** -8
