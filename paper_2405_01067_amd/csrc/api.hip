@@ -328,6 +328,22 @@ int check_merge_layer(const abt_merge_desc& d) {
     return ABT_OK;
 }
 
+// Backward of few rows: all gradients come from one launch, and a factor gradient over something that it reads (kOver) has to wait for its end.
+enum SmallBwd { kNotSmall, kSmall, kOver };
+
+// Runs `launch(dA, dB, accumulate)`; kOver: into `part` (room for both), from where the gradients then go to their places.
+template <class F>
+hipError_t few_gradients(SmallBwd few, float* dA, float* dB, int64_t m, int64_t n, int64_t r, int acc, float* part, hipStream_t s, F&& launch) {
+    if (few == kSmall) return launch(dA, dB, acc);
+    const hipError_t e = launch(dA ? part : nullptr, dB ? part + (dA ? m * r : 0) : nullptr, 0);
+    if (e != hipSuccess) return e;
+    TnJob done[2];
+    int nd = 0;
+    if (dA) done[nd++] = TnJob{nullptr, nullptr, dA, (int)m, 0};
+    if (dB) done[nd++] = TnJob{nullptr, nullptr, dB, (int)n, 1};
+    return launch_tn_finish(done, nd, (int)r, acc, part, s);
+}
+
 }  // namespace
 
 extern "C" {
@@ -357,6 +373,9 @@ inline int64_t conv_rows(const abt_conv_geom& g) { return g.N * conv_out(g.H, g.
 PatchGeom conv_patches_geom(const abt_conv_geom& g) {        // rows = output pixels, image = act
     return PatchGeom{(int)g.H, (int)g.W, (int)g.C, g.kh, g.kw, +1,
                      (int)conv_out(g.H, g.stride), (int)conv_out(g.W, g.stride), g.stride, 0};
+}
+ConvShape conv_shape(const abt_conv_geom& g) {
+    return ConvShape{(int)g.N, (int)g.H, (int)g.W, (int)conv_out(g.H, g.stride), (int)conv_out(g.W, g.stride), (int)g.C, g.kh, g.kw, g.stride};
 }
 PatchGeom conv_adjoint_geom(const abt_conv_geom& g, int r) {  // rows = input pixels, image = dT on the output grid
     return PatchGeom{(int)conv_out(g.H, g.stride), (int)conv_out(g.W, g.stride), r, g.kh, g.kw, -1,
@@ -399,17 +418,37 @@ hipError_t conv_chain(const void* act, const abt_conv_geom& g, const void* A, co
 //   2304 x 768, 96: 1 row 27 / 13, 197 29 / 15, 1000 35 / 18, 4000 43 / 33, 8000 50 / 59; 384: 197 rows 56 / 19, 4000 78 / 74, 8000 89 / 139;
 //   768 x 3072, 32: 197 17 / 10, 4000 34 / 25, 8000 42 / 39; 3072 x 768, 384: 4000 91 / 87; 64 x 64, 96: 197 16 / 9, 2000 22 / 15, 4000 21 / 22;
 //   256 x 1024, 32: 4000 24 / 22.
-// All gradients come from one launch: a factor gradient over something that it reads (kOver) has to wait for its end.
-enum SmallBwd { kNotSmall, kSmall, kOver };
-SmallBwd small_bwd(const void* dY, const void* X, int64_t x_bytes, const void* T, const void* B, const void* dX, const void* dA, const void* dB,
+SmallBwd small_bwd(const void* dY, const void* X, const void* T, const void* B, const void* dX, const void* dA, const void* dB,
                    int64_t M, int64_t m, int64_t n, int64_t r) {
     if (g_chain_rows.load() != 0 || g_chain_parts.load() != 0) return kNotSmall;
     if (M > (m + n >= 1024 ? 4096 : 2048) || !lr_small_supports(M, (int)m, (int)n, (int)r)) return kNotSmall;
     auto over = [&](const void* out, int64_t bytes) {
-        return (dA && (overlap(out, bytes, dY, M * m * 2) || overlap(out, bytes, T, M * r * 2))) || (dB && overlap(out, bytes, X, x_bytes)) ||
+        return (dA && (overlap(out, bytes, dY, M * m * 2) || overlap(out, bytes, T, M * r * 2))) || (dB && overlap(out, bytes, X, M * n * 2)) ||
                (dX && overlap(out, bytes, B, r * n * 2));
     };
     if (over(dX, M * n * 2)) return kNotSmall;
+    return over(dA, m * r * 4) || over(dB, r * n * 4) ? kOver : kSmall;
+}
+
+// Where the two launches for few rows are the faster backward of a convolution (us, the other kernels / these; side x side x C, r):
+//   3 x 3: 14 x 14 x 256, 64: 1 image 27 / 9, 980 rows 38 / 12, 3920 49 / 23, 8036 45 / 38, 12544 49 / 57; r = 256 980 rows 66 / 21, 8036 71 / 70;
+//   stride 2, 64: 4067 rows 56 / 29, 8183 50 / 51, r = 128 59 / 66; 28 x 28 x 128, stride 2, 256: 8036 rows 75 / 56; 7 x 7 x 512, 64: 8183
+//   rows 54 / 47, r = 128 67 / 72, r = 256 4067 93 / 68, 5978 91 / 93; 1 x 1, stride 2: 7 x 7 x 2048, 256: 16 rows 87 / 10, 4096 137 / 118, 6000 142 / 169.
+// From 4096 rows on by the pixels of dAct and the products.
+bool few_pixels(const abt_conv_geom& g, int64_t M, int64_t m, int64_t r) {
+    const int64_t n = (int64_t)g.kh * g.kw * g.C;
+    if (M > 4096 && (M > 8192 || (int64_t)g.N * g.H * g.W * g.C > (4 << 20) || M * n * r > 3500000000ll)) return false;
+    return lr_small_conv_supports(conv_shape(g), M, (int)m, (int)r);
+}
+SmallBwd small_conv_bwd(const abt_conv_geom& g, const void* dY, const void* act, const void* T, const void* B, const void* dAct, const void* dA,
+                        const void* dB, int64_t M, int64_t m, int64_t r) {
+    if (g_chain_rows.load() != 0 || g_chain_parts.load() != 0 || !few_pixels(g, M, m, r)) return kNotSmall;
+    const int64_t n = (int64_t)g.kh * g.kw * g.C, image = (int64_t)g.N * g.H * g.W * g.C * 2;
+    auto over = [&](const void* out, int64_t bytes) {
+        return (dA && (overlap(out, bytes, dY, M * m * 2) || overlap(out, bytes, T, M * r * 2))) || (dB && overlap(out, bytes, act, image)) ||
+               (dAct && overlap(out, bytes, B, r * n * 2));
+    };
+    if (over(dAct, image)) return kNotSmall;
     return over(dA, m * r * 4) || over(dB, r * n * 4) ? kOver : kSmall;
 }
 
@@ -582,11 +621,16 @@ int lr_conv_bwd(const void* dY, const void* act, const void* T, const void* A, c
     // as a linear layer (backward, us, gathered before / now: 7 x 7 x 2048, m = 512, r = 64, batch 256 69 / 48, batch 1 34 / 27; 14 x 14 x
     // 1024, m = 256, batch 128 60 / 46; 56 x 56 x 256, m = 128, batch 128 198 / 142, r = 256 406 / 271)
     if (is_linear(g)) return linear_bwd(dY, act, Tp, A, B, dAct, dA, dB, M, m, g.C, r, dt, accumulate, workspace, workspace_bytes, SIZE_MAX, stream);
-    // few rows: dT and dA from the kernels of the linear layer (the same bits as on an explicit patch matrix)
-    const bool few = small_bwd(dY, act, g.N * g.H * g.W * g.C * 2, Tp, B, nullptr, dA, dB, M, m, taps * g.C, r) == kSmall;
-    if (few && (dAct || dB)) {
-        if (launch_lr_small_dt(dY, A, dT, M, (int)m, (int)r, s) != hipSuccess) return ABT_EHIP;
-    } else if (dAct || dB) {
+    // few rows: two launches, as for the linear layer (the same bits as on an explicit patch matrix)
+    const SmallBwd few = small_conv_bwd(g, dY, act, Tp, B, dAct, dA, dB, M, m, r);
+    if (few != kNotSmall) {
+        if ((dAct || dB) && launch_lr_small_dt(dY, A, dT, M, (int)m, (int)r, s) != hipSuccess) return ABT_EHIP;
+        const int64_t n = (int64_t)taps * g.C;
+        return few_gradients(few, dA, dB, m, n, r, acc, (float*)(ws + w.partials), s, [&](float* dA_to, float* dB_to, int add) {
+                   return launch_lr_small_conv_grad(conv_shape(g), dY, act, Tp, B, dAct, dA_to, dB_to, dT, M, (int)m, (int)r, add, s);
+               }) == hipSuccess ? ABT_OK : ABT_EHIP;
+    }
+    if (dAct || dB) {
         // dT = dY A = dY (A^T)^T: first stage of the plain chain on the transposed factor
         const TransposeJob tj{A, ws + w.At, (int)m, (int)r};
         if (launch_transpose_bf16(&tj, 1, s) != hipSuccess) return ABT_EHIP;
@@ -599,9 +643,7 @@ int lr_conv_bwd(const void* dY, const void* act, const void* T, const void* A, c
     // factor gradients: dA = dY^T T (plain) and dB = patches(act)^T dT (gathered), one launch
     TnJob jobs[2];
     int nj = 0;
-    if (dA && few) {
-        if (launch_lr_small_grad(dY, nullptr, Tp, nullptr, nullptr, dA, nullptr, nullptr, M, (int)m, (int)g.C, (int)r, acc, s) != hipSuccess) return ABT_EHIP;
-    } else if (dA) jobs[nj++] = TnJob{dY, Tp, dA, (int)m, 0};
+    if (dA) jobs[nj++] = TnJob{dY, Tp, dA, (int)m, 0};
     if (dB) jobs[nj++] = TnJob{act, dT, dB, taps * (int)g.C, 1};
     if (dB) {
         if (launch_tn_gather_bf16(jobs, nj, fwd_geom, M, (int)r, acc, (float*)(ws + w.partials), s) != hipSuccess) return ABT_EHIP;
@@ -783,20 +825,12 @@ int linear_bwd(const void* dY, const void* X, const void* T, const void* A, cons
         if (e != hipSuccess) return ABT_EHIP;
         Tp = ws + w.T;
     }
-    const SmallBwd few = small_bwd(dY, X, M * n * 2, Tp, B, dX, dA, dB, M, m, n, r);
+    const SmallBwd few = small_bwd(dY, X, Tp, B, dX, dA, dB, M, m, n, r);
     if (few != kNotSmall) {
-        float* const part = (float*)(ws + w.partials);           // room for both gradients
-        float* const dA_to = few == kOver && dA ? part : dA;
-        float* const dB_to = few == kOver && dB ? part + (dA ? m * r : 0) : dB;
         if ((dX || dB) && launch_lr_small_dt(dY, A, dT, M, (int)m, (int)r, s) != hipSuccess) return ABT_EHIP;
-        e = launch_lr_small_grad(dY, X, Tp, B, dX, dA_to, dB_to, dT, M, (int)m, (int)n, (int)r, few == kOver ? 0 : acc, s);
-        if (e == hipSuccess && few == kOver) {
-            TnJob done[2];
-            int nd = 0;
-            if (dA) done[nd++] = TnJob{nullptr, nullptr, dA, (int)m, 0};
-            if (dB) done[nd++] = TnJob{nullptr, nullptr, dB, (int)n, 1};
-            e = launch_tn_finish(done, nd, (int)r, acc, part, s);
-        }
+        e = few_gradients(few, dA, dB, m, n, r, acc, (float*)(ws + w.partials), s, [&](float* dA_to, float* dB_to, int add) {
+            return launch_lr_small_grad(dY, X, Tp, B, dX, dA_to, dB_to, dT, M, (int)m, (int)n, (int)r, add, s);
+        });
         return e == hipSuccess ? ABT_OK : ABT_EHIP;
     }
     if (dX || dB) {

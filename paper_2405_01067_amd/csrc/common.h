@@ -197,6 +197,11 @@ hipError_t launch_lr_small_fwd_gather(const void* image, const PatchGeom& g, con
 hipError_t launch_lr_small_dt(const void* dY, const void* A, void* dT, int64_t M, int m, int r, hipStream_t s);
 hipError_t launch_lr_small_grad(const void* dY, const void* X, const void* T, const void* B, void* dX, float* dA, float* dB, const void* dT,
                                 int64_t M, int m, int n, int r, int accumulate, hipStream_t s);
+// The same for a convolution (dAct [N, H, W, C] in the place of dX; image and factor as they lie), M = N Ho Wo rows, at most 16384.
+struct ConvShape { int N, H, W, Ho, Wo, C, kh, kw, stride; };
+bool lr_small_conv_supports(const ConvShape& g, int64_t M, int m, int r);
+hipError_t launch_lr_small_conv_grad(const ConvShape& g, const void* dY, const void* act, const void* T, const void* B, void* dAct, float* dA, float* dB,
+                                     const void* dT, int64_t M, int m, int r, int accumulate, hipStream_t s);
 
 // Pst [C, taps r_pad] (bf16) from B [r, taps C]: Pst[c, tap r_pad + j] = B[j, tap C + c], zero for j >= r.
 // by_parity: four matrices end to end instead, one per parity (py, px) of the pixel in the order (0,0), (0,1),

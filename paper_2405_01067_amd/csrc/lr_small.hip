@@ -1,7 +1,7 @@
 // The bf16 factored layer for few rows, two launches each way:
 //     T[M,r] = X[M,n] . B[r,n]^T,  Y[M,m] = T . A[m,r]^T                (small_nt_kernel, twice)
 //     dT[M,r] = dY[M,m] . A[m,r]                                       (small_dt_kernel)
-//     dX[M,n] = dT . B[r,n],  dA[m,r] = dY^T . T,  dB[r,n] = dT^T . X   (small_grad_kernel, all of them at once)
+//     dX[M,n] = dT . B[r,n],  dA[m,r] = dY^T . T,  dB[r,n] = dT^T . X   (small_grad_kernel, all of them at once; small_conv_grad_kernel)
 //
 // What bounds it: latency.  The kernels for many rows walk a contraction of thousands of columns in one work-group per
 // 64 rows, a barrier per slab of 64, behind a launch that transposes the factors, and the factor gradients
@@ -322,11 +322,29 @@ __device__ __forceinline__ void dx_tile(const SmallGrad& p, int rb, int tile, fl
     }
 }
 
-// 64 x 64 of C; wave w takes the steps of 16 rows w, w + 8, ..
-__device__ __forceinline__ void tn_tile(const SmallTn& g, int M, int accumulate, int tile, float (*red)[4][16][64]) {
+// A factored convolution: image [N, H, W, C], rows of dY, T and dT on the grid Ho x Wo
+struct SmallConv { int N, H, W, Ho, Wo, C, kh, kw, stride; };
+
+// 64 x 64 of C; wave w takes the steps of 16 rows w, w + 8, ..  GATHER: S is the patch matrix of an image; a tile's 64 columns lie in one tap, so the
+// work-group looks up the pixel of every row once (offsets in `red`, which is free until the sums).
+template <bool GATHER>
+__device__ __forceinline__ void tn_tile(const SmallTn& g, int M, int accumulate, int tile, float (*red)[4][16][64], const SmallConv& cv) {
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, j = lane & 31, h = lane >> 5;
     const int i0 = 64 * (tile / g.tiles_q), j0 = 64 * (tile % g.tiles_q);
-    const rsrc_t rres = make_rsrc(g.R, (int64_t)M * g.P * 2), sres = make_rsrc(g.S, (int64_t)M * g.Q * 2);
+    const rsrc_t rres = make_rsrc(g.R, (int64_t)M * g.P * 2);
+    const rsrc_t sres = make_rsrc(g.S, GATHER ? (int64_t)cv.N * cv.H * cv.W * cv.C * 2 : (int64_t)M * g.Q * 2);
+    const int steps = (M + 15) / 16;
+    int* const pixel = reinterpret_cast<int*>(red);
+    if constexpr (GATHER) {
+        const int tap = j0 / cv.C, ky = tap / cv.kw - cv.kh / 2, kx = tap % cv.kw - cv.kw / 2, per = cv.Ho * cv.Wo;
+        for (int i = tid; i < 16 * steps; i += 64 * kGradWaves) {
+            const int img = i / per, rem = i - img * per, yo = rem / cv.Wo;
+            const int y = cv.stride * yo + ky, x = cv.stride * (rem - yo * cv.Wo) + kx;
+            const bool ok = i < M && (unsigned)y < (unsigned)cv.H && (unsigned)x < (unsigned)cv.W;
+            pixel[i] = ok ? (((img * cv.H + y) * cv.W + x) * cv.C + (j0 - tap * cv.C)) * 2 : kBufNowhere;
+        }
+        __syncthreads();
+    }
     const bool rin = i0 + 2 * j < g.P, sin = j0 + 2 * j < g.Q;
     f32x16 acc[2][2];
     zero(acc[0][0]); zero(acc[0][1]); zero(acc[1][0]); zero(acc[1][1]);
@@ -338,7 +356,8 @@ __device__ __forceinline__ void tn_tile(const SmallTn& g, int M, int accumulate,
 #pragma unroll
         for (int i = 0; i < 8; ++i) {
             d.r[i] = load4(rres, rin ? ro + i * g.P * 2 : kBufNowhere, 0);
-            d.s[i] = load4(sres, sin ? so + i * g.Q * 2 : kBufNowhere, 0);
+            if constexpr (GATHER) d.s[i] = load4(sres, (int)((unsigned)pixel[16 * k + 8 * h + i] + 4u * j), 0);      // nowhere stays past any image
+            else d.s[i] = load4(sres, sin ? so + i * g.Q * 2 : kBufNowhere, 0);
         }
     };
     auto multiply = [&](const Step& d) {
@@ -350,7 +369,6 @@ __device__ __forceinline__ void tn_tile(const SmallTn& g, int M, int accumulate,
 #pragma unroll
             for (int y = 0; y < 2; ++y) acc[x][y] = mfma16(a[x], b[y], acc[x][y]);
     };
-    const int steps = (M + 15) / 16;
     int k = wave;
     if (k < steps) load(buf[0], k);
     for (; k < steps; k += 2 * kGradWaves) {
@@ -361,6 +379,7 @@ __device__ __forceinline__ void tn_tile(const SmallTn& g, int M, int accumulate,
             multiply(buf[1]);
         }
     }
+    if constexpr (GATHER) __syncthreads();
     // wave w takes over the sums of wave w + 4, then all add up those of the first four, in order
     constexpr int half = kGradWaves / 2;
     if (wave >= half) {
@@ -402,13 +421,102 @@ __global__ __launch_bounds__(64 * kGradWaves, 2) void small_grad_kernel(SmallGra
     // the factor gradients first: their contraction is the longer chain
     for (int i = 0; i < p.njobs; ++i) {
         const int tiles = ((p.job[i].P + 63) / 64) * p.job[i].tiles_q;
-        if (b < tiles) { tn_tile(p.job[i], p.M, p.accumulate, b, red); return; }
+        if (b < tiles) { tn_tile<false>(p.job[i], p.M, p.accumulate, b, red, SmallConv{}); return; }
         b -= tiles;
     }
     if (p.dX == nullptr) return;
     const int rb = b % p.rows_blocks, c = b / p.rows_blocks;
     if (p.dx_shared) dx_tile<true>(p, rb, c, reinterpret_cast<float (*)[2][16][64]>(red));
     else if (64 * (kGradWaves * c + wave) < p.n) dx_tile<false>(p, rb, kGradWaves * c + wave, nullptr);
+}
+
+// The gradients of a convolution, one launch for what were four or five (copy of B, dAct, dA, dB and the sums of its parts: 14 x 14 x 256, 3 x 3, r = 64,
+// 4 images 38 us, 12 here, most of it latency as above; M up to 16384 rows for the offsets in LDS): dAct [N, H, W, C] = the sum over taps of dT (shifted) . B, without a re-laid-out copy of B; dA and dB as above.
+struct SmallConvGrad {
+    const uint16_t* dT; const uint16_t* B; uint16_t* dAct;
+    SmallConv cv;
+    int M, n, r, accumulate, blocks_A, blocks_B;
+    SmallTn A_job, B_job;
+};
+
+// 32 pixels x 64 channels of dAct; wave w takes the steps of 16 columns of dT, tap by tap, w, w + 8, ..  With stride 2 a tap reaches only the pixels
+// of one parity, so the pixels are taken parity by parity.
+__device__ __forceinline__ void dact_tile(const SmallConvGrad& p, int b, float (*red)[2][16][64]) {
+    const SmallConv& cv = p.cv;
+    const int lane = threadIdx.x & 63, j = lane & 31, h = lane >> 5;
+    const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    const int tiles = cv.C / 64;
+    int rb = b / tiles, py = 0, px = 0, RH = cv.H, RW = cv.W;
+    const int col = 64 * (b - rb * tiles) + 2 * j, st = cv.stride;
+    if (st == 2)
+        for (int cls = 3; cls >= 0; --cls) {
+            py = cls >> 1; px = cls & 1;
+            RH = (cv.H - py + 1) / 2; RW = (cv.W - px + 1) / 2;
+            const int blocks = (cv.N * RH * RW + 31) / 32;
+            if (rb < blocks) break;
+            rb -= blocks;
+        }
+    const int per = RH * RW, i = 32 * rb + j, img = i / per, rem = i - img * per, ry = rem / RW;
+    const int y = st * ry + py, x = st * (rem - ry * RW) + px;
+    const bool live = img < cv.N;
+    const int at = live ? (img * cv.H + y) * cv.W + x : -1;
+    const int gy = live ? y + cv.kh / 2 : -(1 << 24), gx = x + cv.kw / 2;        // no pixel: never on the grid of dT
+    const int ky0 = (st - 1) & (py + cv.kh / 2), kx0 = (st - 1) & (px + cv.kw / 2);
+    const int rs = p.r / 16, steps = ((cv.kh - ky0 + st - 1) / st) * ((cv.kw - kx0 + st - 1) / st) * rs;
+    const rsrc_t tres = make_rsrc(p.dT, (int64_t)p.M * p.r * 2), bres = make_rsrc(p.B, (int64_t)p.r * p.n * 2);
+    const int boff = (8 * h * p.n + col) * 2;
+    f32x16 acc[2];
+    zero(acc[0]); zero(acc[1]);
+    struct Step { u32x4 t; uint32_t b[8]; } buf[2];
+    int c = wave, ky = ky0, kx = kx0;                    // of the next step
+    auto load = [&](Step& s) {
+        while (c >= rs) { c -= rs; kx += st; if (kx >= cv.kw) { kx = kx0; ky += st; } }
+        const int ty = (gy - ky) >> (st - 1), tx = (gx - kx) >> (st - 1);
+        const bool ok = (unsigned)ty < (unsigned)cv.Ho && (unsigned)tx < (unsigned)cv.Wo;
+        s.t = buf_load16(tres, ok ? (((img * cv.Ho + ty) * cv.Wo + tx) * p.r + 16 * c + 8 * h) * 2 : kBufNowhere, 0);
+#pragma unroll
+        for (int e = 0; e < 8; ++e) s.b[e] = load4(bres, boff, ((16 * c + e) * p.n + (ky * cv.kw + kx) * cv.C) * 2);
+        c += kGradWaves;
+    };
+    auto multiply = [&](const Step& s) {
+        u32x4 op[2];
+        unpair(s.b, op);
+        acc[0] = mfma16(s.t, op[0], acc[0]);
+        acc[1] = mfma16(s.t, op[1], acc[1]);
+    };
+    int k = wave;
+    if (k < steps) load(buf[0]);
+    for (; k < steps; k += 2 * kGradWaves) {
+        if (k + kGradWaves < steps) load(buf[1]);
+        multiply(buf[0]);
+        if (k + kGradWaves < steps) {
+            if (k + 2 * kGradWaves < steps) load(buf[0]);
+            multiply(buf[1]);
+        }
+    }
+#pragma unroll
+    for (int b2 = 0; b2 < 2; ++b2)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) red[wave][b2][v][lane] = acc[b2][v];
+    __syncthreads();
+    const rsrc_t xres = make_rsrc(p.dAct, (int64_t)cv.N * cv.H * cv.W * cv.C * 2);
+#pragma unroll
+    for (int e = 0; e < 16 / kGradWaves; ++e) {
+        const int v = wave + kGradWaves * e;
+        float t0 = 0.0f, t1 = 0.0f;
+#pragma unroll
+        for (int w = 0; w < kGradWaves; ++w) { t0 += red[w][0][v][lane]; t1 += red[w][1][v][lane]; }
+        const int to = __shfl(at, acc_row(v, h));
+        __builtin_amdgcn_raw_buffer_store_b32(pack2_bf16(t0, t1), xres, to >= 0 ? (to * cv.C + col) * 2 : kBufNowhere, 0, 0);
+    }
+}
+
+__global__ __launch_bounds__(64 * kGradWaves, 2) void small_conv_grad_kernel(SmallConvGrad p) {
+    __shared__ float red[kGradWaves / 2][4][16][64];
+    const int b = (int)blockIdx.x;
+    if (b < p.blocks_B) tn_tile<true>(p.B_job, p.M, p.accumulate, b, red, p.cv);
+    else if (b - p.blocks_B < p.blocks_A) tn_tile<false>(p.A_job, p.M, p.accumulate, b - p.blocks_B, red, p.cv);
+    else dact_tile(p, b - p.blocks_B - p.blocks_A, reinterpret_cast<float (*)[2][16][64]>(red));
 }
 
 }  // namespace
@@ -520,6 +628,34 @@ hipError_t launch_lr_small_grad(const void* dY, const void* X, const void* T, co
     g.dx_shared = r >= 160 && (int64_t)blocks * (n / 64) <= 256;
     if (dX) grid += (int64_t)blocks * (g.dx_shared ? n / 64 : ceil_div(n, 64 * kGradWaves));
     hipLaunchKernelGGL(small_grad_kernel, dim3((unsigned)grid), dim3(64 * kGradWaves), 0, s, g);
+    return hipGetLastError();
+}
+
+bool lr_small_conv_supports(const ConvShape& g, int64_t M, int m, int r) {
+    const int64_t n = (int64_t)g.kh * g.kw * g.C;
+    return M <= 16384 && g.C % 64 == 0 && n <= (1 << 20) && (int64_t)g.N * g.H * g.W * g.C * 2 < kBufMaxBytes && n * r * 2 < kBufMaxBytes &&
+           lr_small_supports(M, m, m, r);
+}
+
+hipError_t launch_lr_small_conv_grad(const ConvShape& g, const void* dY, const void* act, const void* T, const void* B, void* dAct, float* dA, float* dB,
+                                     const void* dT, int64_t M, int m, int r, int accumulate, hipStream_t s) {
+    if (!lr_small_conv_supports(g, M, m, r) || (dA && !T) || ((dAct || dB) && !dT)) return hipErrorInvalidValue;
+    const int64_t n = (int64_t)g.kh * g.kw * g.C;
+    SmallConvGrad p{};
+    p.dT = (const uint16_t*)dT; p.B = (const uint16_t*)B; p.dAct = (uint16_t*)dAct;
+    p.cv = SmallConv{g.N, g.H, g.W, g.Ho, g.Wo, g.C, g.kh, g.kw, g.stride};
+    p.M = (int)M; p.n = (int)n; p.r = r; p.accumulate = accumulate;
+    const int tiles_r = (int)ceil_div(r, 64);
+    if (dA) { p.A_job = SmallTn{(const uint16_t*)dY, (const uint16_t*)T, dA, m, r, tiles_r}; p.blocks_A = m / 64 * tiles_r; }
+    if (dB) { p.B_job = SmallTn{(const uint16_t*)dT, (const uint16_t*)act, dB, r, (int)n, (int)(n / 64)}; p.blocks_B = (int)(n / 64) * tiles_r; }
+    int64_t grid = (int64_t)p.blocks_A + p.blocks_B, rows = 0;
+    for (int cls = 0; cls < (g.stride == 2 ? 4 : 1); ++cls) {
+        const int64_t RH = g.stride == 2 ? (g.H - (cls >> 1) + 1) / 2 : g.H, RW = g.stride == 2 ? (g.W - (cls & 1) + 1) / 2 : g.W;
+        rows += ceil_div(g.N * RH * RW, 32);
+    }
+    if (dAct) grid += rows * (g.C / 64);
+    if (grid == 0) return hipSuccess;
+    hipLaunchKernelGGL(small_conv_grad_kernel, dim3((unsigned)grid), dim3(64 * kGradWaves), 0, s, p);
     return hipGetLastError();
 }
 

@@ -89,15 +89,31 @@ def test_forward_of_few_rows(M, m, n, r):
             assert not save or rel(Tg, k * (X.double() @ B.double().T)) < 2 ** -8
 
 
-@pytest.mark.parametrize("N,H,W,C,k,stride,m,r", [(1, 1, 1, 64, 3, 1, 64, 256), (2, 7, 7, 512, 3, 1, 512, 64), (3, 14, 13, 128, 3, 2, 64, 96), (1, 9, 5, 64, 5, 2, 128, 384),
-                                                  (20, 14, 14, 256, 3, 1, 256, 32), (2, 28, 28, 64, 3, 1, 64, 320), (4, 7, 9, 192, 1, 2, 64, 160)])
-def test_forward_of_few_pixels(N, H, W, C, k, stride, m, r):
+# grids of one pixel, odd sides, windows without a tap for some parity, and 4096 rows and their surroundings
+@pytest.mark.parametrize("N,H,W,C,kh,kw,stride,m,r", [(1, 1, 1, 64, 3, 3, 1, 64, 256), (2, 7, 7, 512, 3, 3, 1, 512, 64), (3, 14, 13, 128, 3, 3, 2, 64, 96),
+                                                      (1, 9, 5, 64, 5, 5, 2, 128, 384), (20, 14, 14, 256, 3, 3, 1, 256, 32), (2, 28, 28, 64, 3, 3, 1, 64, 320),
+                                                      (4, 7, 9, 192, 1, 1, 2, 64, 160), (5, 6, 11, 64, 1, 3, 2, 192, 64), (2, 1, 8, 128, 3, 1, 2, 64, 96),
+                                                      (21, 14, 14, 64, 3, 3, 1, 64, 128), (17, 31, 31, 64, 3, 3, 2, 64, 64), (32, 16, 16, 64, 3, 3, 1, 64, 192)])
+def test_convolution_of_few_pixels(N, H, W, C, kh, kw, stride, m, r):
     g = torch.Generator(device="cuda").manual_seed(N + H + C + r)
     rn = lambda std, *s: (torch.randn(s, generator=g, device="cuda") * std).to(BF)
-    n = k * k * C
+    n = kh * kw * C
     act, A, B = rn(1, N, H, W, C), rn(r ** -0.5, m, r), rn(n ** -0.5, r, n)
-    P = conv_patches(act, k, k, stride)
-    Y, T = abt.lr_conv_fwd(act, A, B, k, k, stride=stride)
-    Yl, Tl = abt.lr_linear_fwd(P, A, B)
-    assert torch.equal(T, Tl) and torch.equal(Y.reshape(Yl.shape), Yl)
-    assert rel(T, P.double() @ B.double().T) < 2 ** -8 and rel(Yl, T.double() @ A.double().T) < 2 ** -8
+    P = conv_patches(act, kh, kw, stride)
+    Y, T = abt.lr_conv_fwd(act, A, B, kh, kw, stride=stride)
+    if len(P) <= 4096:
+        Yl, Tl = abt.lr_linear_fwd(P, A, B)
+        assert torch.equal(T, Tl) and torch.equal(Y.reshape(Yl.shape), Yl)
+    assert rel(T, P.double() @ B.double().T) < 2 ** -8 and rel(Y.reshape(len(P), m), T.double() @ A.double().T) < 2 ** -8
+    dY = rn(1e-2, len(P), m)
+    dT = dY.double() @ A.double()
+    pixels = act.double().requires_grad_()
+    want = torch.autograd.grad(conv_patches(pixels, kh, kw, stride), pixels, dT @ B.double())[0]
+    got = abt.lr_conv_bwd(dY, act, T, A, B, kh, kw, stride=stride)
+    assert rel(got[0], want) < 2 ** -7 and rel(got[1], dY.double().T @ T.double()) < 1e-5 and rel(got[2], dT.T @ P.double()) < 2 ** -8
+    for which in ((True, False, False), (False, True, False), (False, False, True), (False, True, True)):
+        again = abt.lr_conv_bwd(dY, act, T, A, B, kh, kw, stride=stride, need_dAct=which[0], need_dA=which[1], need_dB=which[2])
+        for a, b, w in zip(got, again, which):
+            assert torch.equal(a, b) if w else b is None
+    twice = abt.lr_conv_bwd(dY, act, T, A, B, kh, kw, stride=stride, dA=got[1].clone(), dB=got[2].clone(), accumulate=True)
+    assert rel(twice[1], 2 * got[1].double()) < 1e-6 and rel(twice[2], 2 * got[2].double()) < 1e-6
