@@ -31,7 +31,7 @@ struct ChainShape { int rows, parts; };
 ChainShape choose_chain_shape(int64_t M, int p, int q, int R, bool second_stage, bool allow_parts) {
     const ChainShape small{64, 1};
     const int rows_forced = g_chain_rows.load(), parts_forced = g_chain_parts.load();
-    if (rows_forced == 64 || !chain2_tall_supports(R, p, q)) return small;
+    if (!chain2_tall_supports(R, p, q) || (rows_forced == 64 && chain2_supports(R, p, q))) return small;
     int parts = 1;
     if (allow_parts && second_stage && parts_forced > 1) {
         const int ntile = (int)ceil_div(q, 128);
@@ -147,15 +147,15 @@ bool narrow_chain(const ChainProblem* problems, int n, int64_t M, int p, int q, 
 //     Not where all of P is soon read (64 -> 64, r = 96 5.3 / 6.2; 64 -> 1920, r = 192 6.8 / 6.9, 4000 rows 11 / 15; 256 -> 1024, r = 32 5.3 / 6.0, r =
 //     128 7.9 / 6.4, r = 192 2000 rows 11 / 11, 4000 12.3 / 13.2), but for the ranks above 192, whose fused kernels have few loads in flight (64 -> 1920,
 //     r = 256: 25 / 7; 64 -> 64, r = 384 10.7 / 7.6, r = 224 one row 4.4 / 6.4).
-//   At r = 224, 288 and 352, which have no fused kernel with loads under way during the products, at any number of rows except where their 64-row
-//     blocks come out at nearly whole turns of two per compute unit: 768 -> 2304, r = 224 8000 rows 90 / 33, 16000 92 / 55, 25000 91 / 82, 33000
-//     178 / 100; 3072 -> 768, r = 352 127 / 50, 129 / 76, 134 / 118, 264 / 161, and 50000 266 / 256.
+//   At r = 224, 288 and 352, whose fused kernel is that of the next wider rank in 128-row work-groups, up to 10240 rows: 768 -> 2304, r = 224 3000 rows
+//     45 / 20, 8192 45 / 31, 12608 48 / 44, 16384 48 / 54; 3072 -> 768, r = 352 70 / 32, 71 / 48, 73 / 74, 76 / 78; 64 -> 1920, r = 288 39 / 17,
+//     40 / 29, 41 / 39, 39 / 46.
 bool two_products(int64_t rows, int p, int q, int R, bool image) {
     if (g_chain_rows.load() != 0 || g_chain_parts.load() != 0) return false;
     const bool small = R > 192 ? p + q >= 256 : (int64_t)p * R >= 24576 && (p >= 384 || rows <= 2048);
     const bool wide = R == 256 || (R > 256 && q >= 2 * p);
-    if (small && rows <= (image || wide ? 8192 : 4096)) return true;
-    return (R == 224 || R == 288 || R == 352) && p + q >= 256 && rows <= 24000 * ceil_div(rows, 32768);
+    const bool padded = R == 224 || R == 288 || R == 352;
+    return small && rows <= (padded ? 10240 : image || wide ? 8192 : 4096);
 }
 // T needs a place, and not over the first operand, whose rows several work-groups read.
 bool two_products(const ChainProblem* problems, int n, int64_t M, int p, int q, int R) {
@@ -212,8 +212,7 @@ hipError_t chain(const void* Xin, const void* P, const void* Q, void* Yout, void
     if (narrow_chain(&one, 1, M, p, q, R, s, &e)) return e;
     const ChainShape sh = choose_chain_shape(M, p, q, R, Yout != nullptr, true);
     if (sh.rows == 128) return launch_chain2_tall_bf16(Xin, P, Q, Yout, Tout, M, p, q, R, sh.parts, s);
-    if (chain2_supports(R, p, q)) return launch_chain2_bf16(Xin, P, Q, Yout, Tout, M, p, q, R, s);
-    return launch_chain_bf16(Xin, P, Q, Yout, Tout, M, p, q, R, s);
+    return launch_chain2_bf16(Xin, P, Q, Yout, Tout, M, p, q, R, s);
 }
 
 // The entry points promise not to throw: what the host-side tables of a call may throw (allocation
@@ -883,7 +882,7 @@ GroupedLayout grouped_layout_bf16(int G, int64_t M, int64_t m, int64_t n, int64_
 
 int chain_rows_for_groups(int G, int64_t M, int p, int q, int R) {
     const int forced = g_chain_rows.load();
-    if (forced == 64 || !chain2_tall_supports(R, p, q)) return 64;
+    if (!chain2_tall_supports(R, p, q) || (forced == 64 && chain2_supports(R, p, q))) return 64;
     if (forced == 128 || !chain2_supports(R, p, q)) return 128;
     const double cost64 = (double)ceil_div(G * ceil_div(M, 64), 256);
     const double cost128 = 1.58 * (double)ceil_div(G * ceil_div(M, 128), 256);
@@ -903,9 +902,6 @@ hipError_t chain_grouped(const ChainProblem* pr, int G, int64_t M, int p, int q,
         hipError_t e;
         if (two_products(sel, n, M, p, q, R)) {
             e = launch_lr_small_fwd(sel, n, M, p, q, R, s);
-        } else if (!chain2_supports(R, p, q) && !chain2_tall_supports(R, p, q)) {
-            e = hipSuccess;
-            for (int g = 0; g < n && e == hipSuccess; ++g) e = chain(sel[g].Xin, sel[g].P, sel[g].Q, sel[g].Yout, sel[g].Tout, M, p, q, R, s);
         } else if (!narrow_chain(sel, n, M, p, q, R, s, &e)) {
             e = launch_chain2_grouped_bf16(sel, n, M, p, q, R, chain_rows_for_groups(n, M, p, q, R), 1, s);
         }

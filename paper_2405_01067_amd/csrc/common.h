@@ -101,9 +101,7 @@ inline bool overlap(const void* a, int64_t na, const void* b, int64_t nb) {
 // ------------------------------------------------------------------ bf16 factored layer
 // Fused chain  Tout[M,R] = Xin[M,p] . P[R,p]^T ;  Yout[M,q] = Tout . Q[q,R]^T  (bf16, fp32 acc).
 // Yout or Tout may be NULL.  p, q multiples of 64; R in {32..384 step 32}.
-hipError_t launch_chain_bf16(const void* Xin, const void* P, const void* Q, void* Yout, void* Tout,
-                             int64_t M, int p, int q, int R, hipStream_t s);
-// The same chain with 64-row work-groups: four MFMA waves fed by four loader waves; covers
+// With 64-row work-groups: four MFMA waves fed by four loader waves; covers
 // R in {32, 64, 96, 128, 160, 192, 256, 320, 384} with p a multiple of 64 and p, q <= 2^20
 // (32-bit byte offsets inside a work-group's rows and inside the factors) (chain2_supports).
 bool chain2_supports(int R, int p, int q);
@@ -116,7 +114,7 @@ hipError_t launch_chain2_bf16(const void* Xin, const void* P, const void* Q, voi
 bool chain2_tall_supports(int R, int p, int q);
 hipError_t launch_chain2_tall_bf16(const void* Xin, const void* P, const void* Q, void* Yout, void* Tout,
                               int64_t M, int p, int q, int R, int parts, hipStream_t s);
-// (For R = 192, 256 and 384 the plain 128-row launches go to the kernel of eight equal waves below; the
+// (From R = 192 on the plain 128-row launches go to the kernel of eight equal waves below; the
 // gathered form has 128-row work-groups for R in {32, 64, 96, 128, 192, 384}.)
 // Up to kChainMaxGroups problems of one shape in one launch (the emulated groups of a training step).
 // rows = 64 or 128 (work-group height; the caller has checked chain2_supports / chain2_tall_supports);
@@ -125,7 +123,7 @@ constexpr int kChainMaxGroups = 8;
 struct ChainProblem { const void* Xin; const void* P; const void* Q; void* Yout; void* Tout; };
 hipError_t launch_chain2_grouped_bf16(const ChainProblem* problems, int G, int64_t M, int p, int q, int R,
                                       int rows, int parts, hipStream_t s);
-// The same chain for R = 192, 256, 384 with 128-row work-groups of eight equal waves, slabs loaded
+// The same chain for R = 192 .. 384 with 128-row work-groups of eight equal waves, slabs loaded
 // straight into LDS; p, q multiples of 64, at most 2^20; `parts` as above; groups as above.
 bool chain3_supports(int R, int p, int q);
 hipError_t launch_chain3_bf16(const ChainProblem* problems, int G, int64_t M, int p, int q, int R, int parts, hipStream_t s);

@@ -901,7 +901,7 @@ hipError_t launch_chain2_tall_gather_bf16(const void* image, const PatchGeom& g,
                                      void* Yout, void* Tout, int t_pitch, int64_t M, int q, int R, hipStream_t s) {
     const int cpb = (g.Cin + 63) / 64;
     const int64_t p = (int64_t)g.kh * g.kw * cpb * 64;
-    if (!gather_ok(g, M, p, t_pitch, R, 128) || !chain2_tall_supports(R, (int)p, q) || R == 256) return hipErrorInvalidValue;
+    if (!gather_ok(g, M, p, t_pitch, R, 128) || !chain2_tall_supports(R, (int)p, q) || R == 256 || R == 320) return hipErrorInvalidValue;
     const Ch2Gather gg = device_geom(g);
     return launch_chain_128<true>(one_problem(image, P, Q, Yout, Tout), 1, Yout != nullptr, M, (int)p, q, R, t_pitch, gg, 1, s);
 }

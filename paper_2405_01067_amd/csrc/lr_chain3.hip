@@ -1,4 +1,4 @@
-// Chain kernel for wide ranks and large batches (R = 192, 256, 384; 128-row work-groups):
+// Chain kernel for wide ranks and large batches (R = 192 .. 384; 128-row work-groups):
 //   Tout[M,R] = Xin[M,p] . P[R,p]^T  then  Yout[M,q] = Tout . Q[q,R]^T      (bf16 in, fp32 accumulate)
 // the same contract as the 64-row / 128-row chain kernel with its two roles of waves, for the
 // shapes where that one is held back by its loaders: at R = 384 a wave cannot keep 64 rows of T in
@@ -12,15 +12,17 @@
 //     on the source side (lane l fetches the chunk that belongs at LDS position l).  A wave waits for
 //     its own loads before the barrier that ends a slab, which makes the next slab visible to all.
 //   * stage 1: slabs of 64 contraction columns (128 rows of Xin, R rows of P); wave (h, c) owns
-//     rows 64h.. and columns (R/4)c.. of T in accumulators (R = 192: rows 32h.., columns 96c..).  Waves 0 and 1 load the Xin parts, three
+//     rows 64h.. and columns (R/4)c.. of T in accumulators (R = 192 and 320: rows 32h.., columns (R/2)c..).  Waves 0 and 1 load the Xin parts, three
 //     slabs ahead (HBM latency) into four slots; waves 2..7 the P parts, one slab ahead into two.
 //   * T: rounded to bf16 once, written as a 128 x R tile to LDS (and from there to Tout); every
 //     wave then loads 32 rows of it as MFMA operands, which stay in registers for all of stage 2.
-//   * stage 2: slabs of 128 rows of Q x 128 contraction columns (64 at R = 192), one slab ahead, every
+//   * stage 2: slabs of 128 rows of Q x 128 contraction columns (64 at R = 192 and 320), one slab ahead, every
 //     wave loading an eighth; wave (b, c) owns rows 32b.. and columns 64c.. of each 128 x 128 output tile: every Q
 //     operand read from LDS feeds one MFMA, every T operand is already in registers.  A finished
 //     tile is rounded at once, staged in LDS piece by piece during the next slab (two buffers)
 //     and leaves during the slab after that as full 256-byte row segments, four pieces per thread.
+//   * ranks that are no multiple of 64 run as the next wider one with zeros in the last 32 columns of T (forward, 50000 rows, 3072 -> 768, us: r =
+//     224 127, 256 131, 288 153, 352 175, 384 182; as two products 189, -, 242, 259).
 //   In both stages a wave keeps several operand reads in flight and holds the last step of a slab
 //   back across the barrier, as the MFMA waves of the other chain kernel do.
 //
@@ -100,9 +102,11 @@ struct Ch3Ptrs {
     uint16_t* T[kChainMaxGroups];
 };
 
-template <int R>
+// PAD: the rank is r, less than R by 32 (224, 288, 352): rows of P and columns of Q past it arrive as zeros, columns of T past it are not stored
+template <int R, bool PAD>
 __global__ __launch_bounds__(512) void chain3_bf16_kernel(Ch3Ptrs ptrs, int64_t M, int p, int q,
                                                           int full_blocks, int tail_parts, int stream_out) {
+    constexpr int r = PAD ? R - 32 : R;
     extern __shared__ __align__(1024) unsigned char lds[];
     const uint16_t* __restrict__ const Xin = ptrs.X[blockIdx.y];
     const uint16_t* __restrict__ const Pm = ptrs.P[blockIdx.y];
@@ -151,7 +155,7 @@ __global__ __launch_bounds__(512) void chain3_bf16_kernel(Ch3Ptrs ptrs, int64_t 
     // The row offset of Xin is part of the per-lane offset, the only part that the hardware
     // range-checks: rows past M arrive as zeros.
     const rsrc_t xres = make_rsrc(Xin + row0 * p, rows_valid * p * 2);
-    const rsrc_t pres = make_rsrc(Pm, (int64_t)R * p * 2);
+    const rsrc_t pres = make_rsrc(Pm, (int64_t)r * p * 2);
     const bool xwave = wave < L::NXW;
     const int r8 = lane >> 3;
     const int i0 = xwave ? wave : wave - L::NXW;        // first instruction of this wave
@@ -169,7 +173,10 @@ __global__ __launch_bounds__(512) void chain3_bf16_kernel(Ch3Ptrs ptrs, int64_t 
         constexpr int NPW = L::NW - L::NXW;
 #pragma unroll
         for (int j = 0; j < L::NI1P; ++j)
-            if (i0 + j * NPW < R / 8) dma16(pres, dst + j * (NPW * 1024), v1, so + j * (8 * NPW) * p * 2);
+            if (i0 + j * NPW < R / 8) {
+                if constexpr (PAD) dma16(pres, dst + j * (NPW * 1024), v1 + j * (8 * NPW) * p * 2, so);      // range-checked
+                else dma16(pres, dst + j * (NPW * 1024), v1, so + j * (8 * NPW) * p * 2);
+            }
     };
     // an Xin wave: all but its newest n slabs have landed; a P wave: all its loads have landed
     auto wait1 = [&](int n) {
@@ -184,15 +191,18 @@ __global__ __launch_bounds__(512) void chain3_bf16_kernel(Ch3Ptrs ptrs, int64_t 
     const int r4 = lane / L::CPR2;
     const int row2 = L::RPI2 * wave + r4;
     const int chunk2 = (lane % L::CPR2) ^ (L::CPR2 == 16 ? (row2 & 15) : ((row2 >> 1) & 7));
-    const int v2 = (row2 * R + chunk2 * 8) * 2;
+    const int v2 = (row2 * r + chunk2 * 8) * 2;
     auto issue2 = [&](int s) {
         const int t = tile_of(s / KSL);
         const int rows = q - t * 128 < 128 ? q - t * 128 : 128;
-        const rsrc_t qres = make_rsrc(Qm + (int64_t)t * 128 * R, (int64_t)rows * R * 2);
+        const rsrc_t qres = make_rsrc(Qm + (int64_t)t * 128 * r, (int64_t)rows * r * 2);
         unsigned char* dst = lds + (s & 1) * L::slab2 + wave * 1024;
         const int so = (s % KSL) * (BK2 * 2);
 #pragma unroll
-        for (int u = 0; u < L::NI2; ++u) dma16(qres, dst + u * 8192, v2 + u * (8 * L::RPI2) * R * 2, so);
+        for (int u = 0; u < L::NI2; ++u) {
+            const int at = v2 + u * (8 * L::RPI2) * r * 2;
+            dma16(qres, dst + u * 8192, !PAD || chunk2 * 8 + (s % KSL) * BK2 < r ? at : kBufNowhere, so);
+        }
     };
 
     // ------------------------------------------------------------------ stage 1
@@ -282,11 +292,11 @@ __global__ __launch_bounds__(512) void chain3_bf16_kernel(Ch3Ptrs ptrs, int64_t 
     if (Yout != nullptr) issue2(0);                     // slot 0 lies below the T tile
     wg_barrier3();                                      // T tile complete
     if (Tout != nullptr && part == 0) {
-        const rsrc_t tres = make_rsrc(Tout + row0 * R, rows_valid * R * 2);
-        constexpr int CPT = R / 8;                      // 16-byte chunks per T row
+        const rsrc_t tres = make_rsrc(Tout + row0 * r, rows_valid * r * 2);
+        constexpr int CPT = r / 8;                      // 16-byte chunks per T row
         for (int i = tid; i < ROWS * CPT; i += L::NT) {
             const int row = i / CPT, ch = i % CPT;
-            buf_store16_maybe_stream(stream_out != 0, *reinterpret_cast<const u32x4*>(ttile + row * L::tpitch + ch * 16), tres, (row * R + ch * 8) * 2, 0);
+            buf_store16_maybe_stream(stream_out != 0, *reinterpret_cast<const u32x4*>(ttile + row * L::tpitch + ch * 16), tres, (row * r + ch * 8) * 2, 0);
         }
     }
     if (Yout == nullptr) return;
@@ -417,7 +427,7 @@ __global__ __launch_bounds__(512) void chain3_bf16_kernel(Ch3Ptrs ptrs, int64_t 
     }
 }
 
-template <int R>
+template <int R, bool PAD = false>
 hipError_t launch_chain3_r(const Ch3Ptrs& ptrs, int G, bool second_stage, int64_t M, int p, int q, int parts, hipStream_t s) {
     using L = Ch3Cfg<R>;
     if (G < 1 || G > kChainMaxGroups || parts < 1 || parts > 64 || (second_stage && parts > (q + 127) / 128) ||
@@ -425,7 +435,7 @@ hipError_t launch_chain3_r(const Ch3Ptrs& ptrs, int G, bool second_stage, int64_
         return hipErrorInvalidValue;
     static std::atomic<bool> attr_set{false};
     if (!attr_set.load(std::memory_order_acquire)) {
-        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&chain3_bf16_kernel<R>),
+        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&chain3_bf16_kernel<R, PAD>),
                                            hipFuncAttributeMaxDynamicSharedMemorySize, L::lds_bytes);
         if (e != hipSuccess) return e;
         attr_set.store(true, std::memory_order_release);
@@ -451,7 +461,7 @@ hipError_t launch_chain3_r(const Ch3Ptrs& ptrs, int G, bool second_stage, int64_
         }
     }
     const int64_t grid = full + (nblocks - full) * tail_parts;
-    hipLaunchKernelGGL((chain3_bf16_kernel<R>), dim3((unsigned)grid, (unsigned)G), dim3(L::NT), L::lds_bytes, s,
+    hipLaunchKernelGGL((chain3_bf16_kernel<R, PAD>), dim3((unsigned)grid, (unsigned)G), dim3(L::NT), L::lds_bytes, s,
                        ptrs, M, p, q, (int)full, tail_parts, (int)(M * ((second_stage ? q : 0) + R) * 2 >= kStreamOutBytes));
     return hipGetLastError();
 }
@@ -460,11 +470,7 @@ hipError_t launch_chain3_r(const Ch3Ptrs& ptrs, int G, bool second_stage, int64_
 
 bool chain3_supports(int R, int p, int q) {
     if (p % 64 != 0 || p < 64 || q < 64 || q % 64 != 0 || p > (1 << 20) || q > (1 << 20)) return false;
-#ifdef ABT_NO_CHAIN3_384
-    return R == 192 || R == 256;
-#else
-    return R == 192 || R == 256 || R == 384;
-#endif
+    return R >= 192 && R <= 384 && R % 32 == 0;
 }
 
 hipError_t launch_chain3_bf16(const ChainProblem* problems, int G, int64_t M, int p, int q, int R, int parts, hipStream_t s) {
@@ -480,7 +486,11 @@ hipError_t launch_chain3_bf16(const ChainProblem* problems, int G, int64_t M, in
     if (second_stage && first_stage_only) return hipErrorInvalidValue;
     switch (R) {
         case 192: return launch_chain3_r<192>(t, G, second_stage, M, p, q, parts, s);
+        case 224: return launch_chain3_r<256, true>(t, G, second_stage, M, p, q, parts, s);
         case 256: return launch_chain3_r<256>(t, G, second_stage, M, p, q, parts, s);
+        case 288: return launch_chain3_r<320, true>(t, G, second_stage, M, p, q, parts, s);
+        case 320: return launch_chain3_r<320>(t, G, second_stage, M, p, q, parts, s);
+        case 352: return launch_chain3_r<384, true>(t, G, second_stage, M, p, q, parts, s);
         case 384: return launch_chain3_r<384>(t, G, second_stage, M, p, q, parts, s);
         default: return hipErrorInvalidValue;
     }

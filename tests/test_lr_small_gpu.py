@@ -58,10 +58,12 @@ def conv_patches(act, kh, kw, stride):
     return torch.cat(cols, dim=-1).reshape(-1, kh * kw * C).contiguous()
 
 
-# rows / 32 times r / 32 tiles of T: up to 256, 512, 1024, more; Y in tiles of 64 x 64 or 64 x 128; rows 4096 and, at r = 224, 288 and 352, 24000
+# rows / 32 times r / 32 tiles of T: up to 256, 512, 1024, more; Y in tiles of 64 x 64 or 64 x 128; rows 4096 and, at r = 224, 288 and 352,
+# 10240; beyond, those ranks and 320 in 128-row work-groups, whose last 32 columns of T may be padding
 @pytest.mark.parametrize("M,m,n,r", [(1, 64, 768, 32), (31, 192, 320, 96), (33, 64, 64, 256), (65, 2304, 768, 384), (197, 768, 3072, 352), (1000, 320, 576, 288),
                                      (1025, 128, 192, 352), (2000, 64, 128, 384), (4096, 1088, 64, 384), (4096, 1024, 1920, 32), (4097, 576, 192, 224),
-                                     (24000, 64, 192, 288), (24001, 64, 192, 288)])
+                                     (10240, 64, 192, 288), (10241, 64, 192, 288), (10241, 192, 64, 224), (12345, 128, 320, 352),
+                                     (20001, 192, 128, 320)])
 def test_forward_of_few_rows(M, m, n, r):
     g = torch.Generator(device="cuda").manual_seed(M + m + n + r)
     rn = lambda std, *s: (torch.randn(s, generator=g, device="cuda") * std).to(BF)
