@@ -512,6 +512,11 @@ int narrow_dact_chunk(const abt_conv_geom& g) {
     return 64;
 }
 
+ChainGather dact_gather(const abt_conv_geom& g, int r) {
+    return ChainGather{(int)conv_out(g.H, g.stride), (int)conv_out(g.W, g.stride), r, 0, g.kh, g.kw, -1, g.kh / 2, g.kw / 2,
+                       (int)g.H, (int)g.W, 1, 1, 0, 0, (int)g.H, (int)g.W};
+}
+
 // dAct[q, c] = sum over taps and j of dT[(q - shift(tap)) / stride, j] B[j, tap, c] (only where the division
 // is exact): the same gathered product as the forward, on the image dT [N, H', W', r] with mirrored
 // shifts, against the re-laid-out factor Pst; rows are the input pixels.
@@ -519,21 +524,18 @@ int narrow_dact_chunk(const abt_conv_geom& g) {
 // parity, each with its own taps: 2.25 instead of 9 taps per pixel for a 3 x 3 window.  All parities and blocks
 // of output channels go into one launch (whole backward, us, against the kernel for all taps, batch 64, r = 64:
 // 28 x 28 x 128 stride 2 56 / 75, stride 1 75 / 91; 56 x 56 x 64 stride 2 79 / 179; 7 x 7 x 2048 1 x 1 48 / 101).
-hipError_t conv_dact(const void* dT, const void* B, void* dAct, void* Pst, const abt_conv_geom& g, int r, int r_pad, hipStream_t s) {
+// Pst: B laid out for it, by parity if `narrow` and stride 2.
+hipError_t conv_dact(const void* dT, const void* B, void* dAct, void* Pst, const abt_conv_geom& g, int r, int r_pad, bool narrow, hipStream_t s) {
     const int C = (int)g.C, taps = g.kh * g.kw;
-    const int Ho = (int)conv_out(g.H, g.stride), Wo = (int)conv_out(g.W, g.stride);
     const int64_t M_in = g.N * g.H * g.W;
     hipError_t e;
-    const bool by_parity = g.stride == 2;
-    const int nchunk = narrow_dact_chunk(g);
-    const ChainGather whole{Ho, Wo, r, 0, g.kh, g.kw, -1, g.kh / 2, g.kw / 2, (int)g.H, (int)g.W, 1, 1, 0, 0, (int)g.H, (int)g.W};
-    if (narrow_dact(g, taps * r_pad, !by_parity && chain4_window(whole, nchunk, 128))) {
-        const int chunk = nchunk;
+    if (narrow) {
+        const bool by_parity = g.stride == 2;
+        const int chunk = narrow_dact_chunk(g);
+        const ChainGather whole = dact_gather(g, r);
         GatherProblem pr[kChainMaxGroups];
         int n = 0;
         bool wide = false;                       // a window that 32-bit offsets do not cover: the kernels below check again
-        e = launch_conv_bstack_bf16(B, Pst, r, C, g.kh, g.kw, r_pad, by_parity, s);
-        if (e != hipSuccess) return e;
         for (int cls = by_parity ? 3 : 0; cls >= 0 && !wide; --cls) {      // most taps first
             const int py = cls >> 1, px = cls & 1;
             ChainGather cg = whole;
@@ -561,8 +563,10 @@ hipError_t conv_dact(const void* dT, const void* B, void* dAct, void* Pst, const
         }
         if (!wide) return hipSuccess;
     }
-    e = launch_conv_bstack_bf16(B, Pst, r, C, g.kh, g.kw, r_pad, false, s);
-    if (e != hipSuccess) return e;
+    if (narrow && g.stride == 2) {               // laid out by parity
+        e = launch_conv_factors_bf16(nullptr, nullptr, 64, B, Pst, r, C, g.kh, g.kw, r_pad, false, s);
+        if (e != hipSuccess) return e;
+    }
     const PatchGeom adj = conv_adjoint_geom(g, r);
     const int chunk = conv_dact_chunk(C);        // one launch per block of output channels
     const int64_t pst_pitch = (int64_t)taps * r_pad;
@@ -629,14 +633,16 @@ int lr_conv_bwd(const void* dY, const void* act, const void* T, const void* A, c
                    return launch_lr_small_conv_grad(conv_shape(g), dY, act, Tp, B, dAct, dA_to, dB_to, dT, M, (int)m, (int)r, add, s);
                }) == hipSuccess ? ABT_OK : ABT_EHIP;
     }
+    const bool narrow = dAct && narrow_dact(g, taps * w.r_pad, g.stride == 1 && chain4_window(dact_gather(g, (int)r), narrow_dact_chunk(g), 128));
     if (dAct || dB) {
         // dT = dY A = dY (A^T)^T: first stage of the plain chain on the transposed factor
-        const TransposeJob tj{A, ws + w.At, (int)m, (int)r};
-        if (launch_transpose_bf16(&tj, 1, s) != hipSuccess) return ABT_EHIP;
+        if (launch_conv_factors_bf16(A, ws + w.At, (int)m, dAct ? B : nullptr, ws + w.Pst, (int)r, (int)g.C, g.kh, g.kw, w.r_pad, narrow && g.stride == 2, s) !=
+            hipSuccess)
+            return ABT_EHIP;
         if (chain(dY, ws + w.At, nullptr, nullptr, dT, M, (int)m, 64, (int)r, s) != hipSuccess) return ABT_EHIP;
     }
     if (dAct) {
-        const hipError_t e = conv_dact(dT, B, dAct, ws + w.Pst, g, (int)r, w.r_pad, s);
+        const hipError_t e = conv_dact(dT, B, dAct, ws + w.Pst, g, (int)r, w.r_pad, narrow, s);
         if (e != hipSuccess) return ABT_EHIP;
     }
     // factor gradients: dA = dY^T T (plain) and dB = patches(act)^T dT (gathered), one launch

@@ -204,7 +204,9 @@ hipError_t launch_lr_small_conv_grad(const ConvShape& g, const void* dY, const v
 // Pst [C, taps r_pad] (bf16) from B [r, taps C]: Pst[c, tap r_pad + j] = B[j, tap C + c], zero for j >= r.
 // by_parity: four matrices end to end instead, one per parity (py, px) of the pixel in the order (0,0), (0,1),
 // (1,0), (1,1), each [C, taps of that parity r_pad] with the taps ky = py + kh/2 (mod 2), kx = px + kw/2 (mod 2).
-hipError_t launch_conv_bstack_bf16(const void* B, void* Pst, int r, int C, int kh, int kw, int r_pad, bool by_parity, hipStream_t s);
+// Together with At [r, m] = A^T; A or B may be NULL (not wanted).
+hipError_t launch_conv_factors_bf16(const void* A, void* At, int m, const void* B, void* Pst, int r, int C, int kh, int kw, int r_pad, bool by_parity,
+                                    hipStream_t s);
 // taps of one parity along one axis of a window of k taps (centre k / 2): first, first + 2, ..; count may be 0
 inline __host__ __device__ int parity_first(int k, int parity) { return (parity + k / 2) & 1; }
 inline __host__ __device__ int parity_count(int k, int parity) { const int f = parity_first(k, parity); return f < k ? (k - f + 1) / 2 : 0; }

@@ -15,13 +15,8 @@ namespace {
 struct TrJob { const uint16_t* src; uint16_t* dst; int rows, cols, tiles_x, tile_begin; };
 struct TrArgs { TrJob job[kTransposeMaxJobs]; int njobs; };
 
-__global__ __launch_bounds__(256) void transpose_bf16_kernel(TrArgs args) {
+__device__ __forceinline__ void transpose_tile(const TrJob& j, int t) {
     __shared__ uint16_t tile[64][72];                  // pitch 144 B: 16-byte aligned rows
-    int jid = 0;
-    for (int i = 1; i < args.njobs; ++i)
-        if ((int)blockIdx.x >= args.job[i].tile_begin) jid = i;
-    const TrJob j = args.job[jid];
-    const int t = (int)blockIdx.x - j.tile_begin;
     const int r0 = (t / j.tiles_x) * 64, c0 = (t % j.tiles_x) * 64;
 #pragma unroll
     for (int e = 0; e < 2; ++e) {
@@ -48,15 +43,25 @@ __global__ __launch_bounds__(256) void transpose_bf16_kernel(TrArgs args) {
     }
 }
 
+__global__ __launch_bounds__(256) void transpose_bf16_kernel(TrArgs args) {
+    int jid = 0;
+    for (int i = 1; i < args.njobs; ++i)
+        if ((int)blockIdx.x >= args.job[i].tile_begin) jid = i;
+    transpose_tile(args.job[jid], (int)blockIdx.x - args.job[jid].tile_begin);
+}
+
 // Re-layout of the factor B [r, taps C] of a factored convolution for the activation gradient:
 // Pst [C, taps r_pad] with Pst[c, tap r_pad + j] = B[j, tap C + c] for j < r and 0 for r <= j < r_pad
 // (every tap padded to a multiple of 64 columns, the slab width of the chain kernel).  One thread
 // writes eight consecutive j (16 bytes).
-__global__ __launch_bounds__(256) void conv_bstack_kernel(const uint16_t* __restrict__ B, uint16_t* __restrict__ Pst,
-                                                          int r, int C, int kh, int kw, int r_pad, int by_parity) {
+struct BstackArgs { const uint16_t* B; uint16_t* Pst; int r, C, kh, kw, r_pad, by_parity; };
+__device__ __forceinline__ void bstack_piece(const BstackArgs& a, int block) {
+    const uint16_t* __restrict__ const B = a.B;
+    uint16_t* __restrict__ const Pst = a.Pst;
+    const int r = a.r, C = a.C, kh = a.kh, kw = a.kw, r_pad = a.r_pad, by_parity = a.by_parity;
     const int taps = kh * kw;
     const int per_row = taps * (r_pad / 8);
-    const int64_t idx = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    const int64_t idx = (int64_t)block * 256 + threadIdx.x;
     if (idx >= (int64_t)C * per_row) return;
     const int c = (int)(idx / per_row), rest = (int)(idx % per_row);
     const int tap = rest / (r_pad / 8), j0 = (rest % (r_pad / 8)) * 8;
@@ -77,13 +82,23 @@ __global__ __launch_bounds__(256) void conv_bstack_kernel(const uint16_t* __rest
     *reinterpret_cast<u32x4*>(Pst + dst + j0) = o;
 }
 
+// A^T and the re-laid-out B of a convolution's backward together: a launch costs more than either (3.6 us each)
+__global__ __launch_bounds__(256) void conv_factors_kernel(TrJob j, int tiles, BstackArgs a) {
+    if ((int)blockIdx.x < tiles) transpose_tile(j, (int)blockIdx.x);
+    else bstack_piece(a, (int)blockIdx.x - tiles);
+}
+
 }  // namespace
 
-hipError_t launch_conv_bstack_bf16(const void* B, void* Pst, int r, int C, int kh, int kw, int r_pad, bool by_parity, hipStream_t s) {
-    if (r < 1 || C < 1 || kh < 1 || kw < 1 || r_pad % 64 || r_pad < r) return hipErrorInvalidValue;
-    const int64_t n = (int64_t)C * kh * kw * (r_pad / 8);
-    hipLaunchKernelGGL(conv_bstack_kernel, dim3((unsigned)ceil_div(n, 256)), dim3(256), 0, s,
-                       (const uint16_t*)B, (uint16_t*)Pst, r, C, kh, kw, r_pad, by_parity ? 1 : 0);
+hipError_t launch_conv_factors_bf16(const void* A, void* At, int m, const void* B, void* Pst, int r, int C, int kh, int kw, int r_pad, bool by_parity,
+                                    hipStream_t s) {
+    if (r < 1 || C < 1 || kh < 1 || kw < 1 || r_pad % 64 || r_pad < r || m % 8 || r % 8) return hipErrorInvalidValue;
+    const TrJob j{(const uint16_t*)A, (uint16_t*)At, m, r, (r + 63) / 64, 0};
+    const int tiles = A ? j.tiles_x * ((m + 63) / 64) : 0;
+    const BstackArgs a{(const uint16_t*)B, (uint16_t*)Pst, r, C, kh, kw, r_pad, by_parity ? 1 : 0};
+    const int64_t pieces = B ? ceil_div((int64_t)C * kh * kw * (r_pad / 8), 256) : 0;
+    if (tiles + pieces == 0) return hipSuccess;
+    hipLaunchKernelGGL(conv_factors_kernel, dim3((unsigned)(tiles + pieces)), dim3(256), 0, s, j, tiles, a);
     return hipGetLastError();
 }
 
