@@ -144,15 +144,17 @@ bool narrow_chain(const ChainProblem* problems, int n, int64_t M, int p, int q, 
 //     10.5, 4000 22 / 17, 8192 24 / 25; r = 192 31 / 22, 31 / 33; r = 384 39 / 12, 43 / 33, 48 / 48.  More rows at r = 256, and above where the wide
 //     side is Y: 3072 -> 768, r = 256 8192 rows 36 / 35, r = 320 42 / 47; 768 -> 3072, r = 320 46 / 42.  From an image, whose fused kernels wait longer:
 //     3 x 3 on 14 x 14 x 256, r = 64 20 images 23 / 13, 8036 rows 23 / 14, 12544 24 / 20, r = 192 26 / 13, 27 / 25, 28 / 35.
-//     Not where all of P is soon read (64 -> 64, r = 96 5.3 / 6.2; 64 -> 1920, r = 192 6.8 / 6.9, 4000 rows 11 / 15; 256 -> 1024, r = 32 5.3 / 6.0, r =
-//     128 7.9 / 6.4, r = 192 2000 rows 11 / 11, 4000 12.3 / 13.2), but for the ranks above 192, whose fused kernels have few loads in flight (64 -> 1920,
-//     r = 256: 25 / 7; 64 -> 64, r = 384 10.7 / 7.6, r = 224 one row 4.4 / 6.4).
+//     A second launch costs the host 3.5 us, so not where the fused kernel is soon done: whole step of forward and backward, 768 -> 2304, 197 rows, fused /
+//     two products r = 32 25.8 / 29.6, r = 96 26.6 / 30.4, r = 128 30.3 / 30.2, r = 192 33.0 / 30.2, 2000 rows r = 64 34 / 33, r = 96 37.6 / 35.3, r = 128 40 / 34; 3072 ->
+//     768, 197 rows r = 32 25 / 30, r = 64 27 / 30, r = 96 30 / 30, r = 128 34 / 30, 2000 rows r = 32 32 / 30, r = 64 35 / 30.  (Forward alone, 64 ->
+//     64, r = 96 5.3 / 6.2, r = 384 10.7 / 7.6; 64 -> 1920, r = 192 6.8 / 6.9, r = 256 25 / 7; 256 -> 1024, r = 128 7.9 / 6.4.)
 //   At r = 224, 288 and 352, whose fused kernel is that of the next wider rank in 128-row work-groups, up to 10240 rows: 768 -> 2304, r = 224 3000 rows
 //     45 / 20, 8192 45 / 31, 12608 48 / 44, 16384 48 / 54; 3072 -> 768, r = 352 70 / 32, 71 / 48, 73 / 74, 76 / 78; 64 -> 1920, r = 288 39 / 17,
 //     40 / 29, 41 / 39, 39 / 46.
 bool two_products(int64_t rows, int p, int q, int R, bool image) {
     if (g_chain_rows.load() != 0 || g_chain_parts.load() != 0) return false;
-    const bool small = R > 192 ? p + q >= 256 : (int64_t)p * R >= 24576 && (p >= 384 || rows <= 2048);
+    const int64_t least = image ? (rows >= 2048 ? 36864 : rows >= 1024 ? 73728 : 147456) : (rows >= 2048 ? 73728 : rows >= 1024 ? 98304 : 147456);
+    const bool small = R > 192 ? p + q >= 1024 : (int64_t)p * R >= least && (image || R >= 96 || rows >= 1024);
     const bool wide = R == 256 || (R > 256 && q >= 2 * p);
     const bool padded = R == 224 || R == 288 || R == 352;
     return small && rows <= (padded ? 10240 : image || wide ? 8192 : 4096);
