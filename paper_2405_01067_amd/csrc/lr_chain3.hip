@@ -102,7 +102,8 @@ struct Ch3Ptrs {
     uint16_t* T[kChainMaxGroups];
 };
 
-// PAD: the rank is r, less than R by 32 (224, 288, 352): rows of P and columns of Q past it arrive as zeros, columns of T past it are not stored
+// PAD: the rank is r, less than R by 32 (224, 288, 352): rows of P and columns of Q past it arrive as zeros, columns of T past it are zeros in LDS
+// and not stored
 template <int R, bool PAD>
 __global__ __launch_bounds__(512) void chain3_bf16_kernel(Ch3Ptrs ptrs, int64_t M, int p, int q,
                                                           int full_blocks, int tail_parts, int stream_out) {
@@ -278,6 +279,7 @@ __global__ __launch_bounds__(512) void chain3_bf16_kernel(Ch3Ptrs ptrs, int64_t 
     mma1(ob[NB1 - 1]);
     // ------------------------------------------------------------------ T tile (bf16) to LDS
     // lane holds T[32 (RA rg + a) + lj][32 (cq CB + b) + 8g + 4 lh + (0..3)] in acc1[a][b][4g .. 4g+3]
+    // (PAD: the last 32 columns are sums of products with zeros, NaN where Xin is not finite: zeros instead)
 #pragma unroll
     for (int a = 0; a < RA; ++a)
 #pragma unroll
@@ -286,6 +288,7 @@ __global__ __launch_bounds__(512) void chain3_bf16_kernel(Ch3Ptrs ptrs, int64_t 
             for (int g = 0; g < 4; ++g) {
                 u32x2 o = {pack2_bf16(acc1[a][b][4 * g + 0], acc1[a][b][4 * g + 1]),
                            pack2_bf16(acc1[a][b][4 * g + 2], acc1[a][b][4 * g + 3])};
+                if (PAD && cq * CB + b == r / 32) o = u32x2{0, 0};
                 *reinterpret_cast<u32x2*>(ttile + (32 * (RA * rg + a) + lj) * L::tpitch +
                                           (32 * (cq * CB + b) + 8 * g + 4 * lh) * 2) = o;
             }
