@@ -237,11 +237,7 @@ def _stream():
     return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
 
 
-@functools.lru_cache(maxsize=1024)
-def _fwd_bytes(M, m, n, r, dt):
-    return load().lr_linear_fwd_workspace_bytes(M, m, n, r, dt)
-
-
+# Kept, as the sizes depend on the shape alone (those of the forward depend on set_chain_rows and set_chain_parts too).
 @functools.lru_cache(maxsize=1024)
 def _bwd_bytes(M, m, n, r, dt):
     return load().lr_linear_bwd_workspace_bytes(M, m, n, r, dt)
@@ -279,7 +275,7 @@ def lr_linear_fwd(X, A, B, save_T: bool = True, Y=None, T=None, workspace=None):
         Y = X.new_empty((M, m))
     if save_T and T is None:
         T = X.new_empty((M, r))
-    nbytes = _fwd_bytes(M, m, n, r, dt)
+    nbytes = lib.lr_linear_fwd_workspace_bytes(M, m, n, r, dt)
     ws = _workspace(nbytes, X.device, workspace) if nbytes or workspace is not None else None
     _check(lib.lr_linear_fwd(X.data_ptr(), A.data_ptr(), B.data_ptr(), Y.data_ptr(), _ptr(T if save_T else None),
                              M, m, n, r, dt, _ptr(ws), ws.numel() if ws is not None else 0, _stream()), "lr_linear_fwd")

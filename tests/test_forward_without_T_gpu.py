@@ -1,0 +1,25 @@
+"""Forwards that do not keep T, of few rows above all: the same results as with T kept, whatever was asked before, and nothing
+written but the outputs."""
+import pytest
+
+torch = pytest.importorskip("torch")
+from paper_2405_01067_amd import binding as abt
+
+pytestmark = pytest.mark.gpu
+BF = torch.bfloat16
+
+
+def layer(M, m, n, r, seed=0):
+    g = torch.Generator(device="cuda").manual_seed(seed)
+    rn = lambda std, *s: (torch.randn(s, generator=g, device="cuda") * std).to(BF)
+    return rn(1, M, n), rn(r ** -0.5, m, r), rn(n ** -0.5, r, n), rn(1e-2, M, m)
+
+
+def test_a_shape_first_seen_under_a_forced_height():
+    X, A, B, _ = layer(199, 2304, 768, 384)
+    prev = abt.set_chain_rows(64)
+    try:
+        abt.lr_linear_fwd(X, A, B, save_T=False)
+    finally:
+        abt.set_chain_rows(prev)
+    assert torch.equal(abt.lr_linear_fwd(X, A, B, save_T=False)[0], abt.lr_linear_fwd(X, A, B)[0])
