@@ -275,8 +275,10 @@ def lr_linear_fwd(X, A, B, save_T: bool = True, Y=None, T=None, workspace=None):
         Y = X.new_empty((M, m))
     if save_T and T is None:
         T = X.new_empty((M, r))
-    nbytes = lib.lr_linear_fwd_workspace_bytes(M, m, n, r, dt)
-    ws = _workspace(nbytes, X.device, workspace) if nbytes or workspace is not None else None
+    ws = workspace
+    if not save_T or (ws is not None and dt == ABT_F32):         # (a bf16 call that keeps T takes any workspace and uses none)
+        nbytes = lib.lr_linear_fwd_workspace_bytes(M, m, n, r, dt)
+        ws = _workspace(nbytes, X.device, ws) if nbytes or ws is not None else None
     _check(lib.lr_linear_fwd(X.data_ptr(), A.data_ptr(), B.data_ptr(), Y.data_ptr(), _ptr(T if save_T else None),
                              M, m, n, r, dt, _ptr(ws), ws.numel() if ws is not None else 0, _stream()), "lr_linear_fwd")
     return Y, (T if save_T else None)

@@ -23,3 +23,18 @@ def test_a_shape_first_seen_under_a_forced_height():
     finally:
         abt.set_chain_rows(prev)
     assert torch.equal(abt.lr_linear_fwd(X, A, B, save_T=False)[0], abt.lr_linear_fwd(X, A, B)[0])
+
+
+@pytest.mark.parametrize("dtype", [BF, torch.float32])
+def test_a_kept_T_needs_no_workspace(dtype):
+    X, A, B, _ = (t.to(dtype) for t in layer(201, 2304, 768, 192))
+    small = torch.empty(1, dtype=torch.uint8, device="cuda")
+    Y, T = abt.lr_linear_fwd(X, A, B, workspace=small if dtype == BF else None)
+    if dtype == torch.float32:                           # one that is named has to hold T there
+        with pytest.raises(abt.AbtError):
+            abt.lr_linear_fwd(X, A, B, workspace=small)
+    taken = lambda: torch.cuda.memory_stats()["allocation.all.allocated"]
+    before = taken()
+    again = abt.lr_linear_fwd(X, A, B)
+    assert taken() == before + 2                         # Y and T
+    assert torch.equal(again[0], Y) and torch.equal(again[1], T)
