@@ -70,19 +70,24 @@ const char* abt_status_string(int status);
  *
  *     T[M,r] = X[M,n] . B[r,n]^T          Y[M,m] = T[M,r] . A[m,r]^T
  *
- * X, A, B, Y are of type `dt`.  T_save is optional; when given it receives T in type `dt` (bf16: T rounded to nearest-even, the
- * same values the second product consumes).
+ * X, A, B, Y are of type `dt`.  T_save is optional; when given it receives T in type `dt` (bf16: T rounded to
+ * nearest-even, the same values the second product consumes).
  * Shapes: M >= 1 arbitrary.  ABT_BF16: m, n multiples of 64 and <= 2^20, r a multiple of 32, r <= 384.
  *         ABT_F32: any positive m, n, r.
- * Workspace: lr_linear_fwd_workspace_bytes.  ABT_BF16 asks for a place for T, without T_save, where the
- * two products run one after the other (few rows, and r = 224, 288, 352), and for none elsewhere; a call
- * that brings none keeps T on the chip.
+ * Workspace: lr_linear_fwd_workspace_bytes, without T_save; 0 for ABT_BF16, which writes nothing there.
+ * ABT_BF16, where lr_linear_fwd_wants_T says 1 (few rows, and r = 224, 288, 352): with T_save the two products run one after
+ * the other, several times faster; without it T stays on the chip, summed in another order, so that T and Y may differ by a
+ * rounding of bf16 from those of a call with T_save, and from the T that a backward computes again.
  * ------------------------------------------------------------------------------------- */
 int lr_linear_fwd(const void* X, const void* A, const void* B, void* Y, void* T_save,
                   int64_t M, int64_t m, int64_t n, int64_t r, int dt,
                   void* workspace, size_t workspace_bytes, void* stream);
 
 size_t lr_linear_fwd_workspace_bytes(int64_t M, int64_t m, int64_t n, int64_t r, int dt);
+
+/* 1 where a forward of G groups (G = 1: lr_linear_fwd) runs in fewer microseconds when it is given a T_save, 0 elsewhere and for
+ * shapes that are refused.  Follows abt_set_chain_rows and abt_set_chain_parts. */
+int lr_linear_fwd_wants_T(int G, int64_t M, int64_t m, int64_t n, int64_t r, int dt);
 
 /* ---------------------------------------------------------------------------------------
  * Factored layer, backward (chain rule through Eq. 3; during the group phase of
@@ -142,8 +147,7 @@ int lr_linear_bwd_static(const void* dY, const void* X, const void* T, const voi
  * Results per group are those of the single-group calls up to the summation order of dA / dB
  * (the row split depends on the number of tiles in the launch); two grouped calls on the same
  * inputs give bit-identical results.  Workspace: lr_linear_bwd_grouped_workspace_bytes for the
- * backward, lr_linear_fwd_workspace_bytes * G laid end to end for the forward without T_save (ABT_BF16: may be
- * left out, as above).
+ * backward, lr_linear_fwd_workspace_bytes * G laid end to end for the forward without T_save.
  * ------------------------------------------------------------------------------------- */
 typedef struct abt_lr_group {
     const void* X;      /* [M, n] */

@@ -20,7 +20,7 @@ _lib = None
 EXPORTS = (
     "abt_status_string", "abt_set_jacobi_max_sweeps", "abt_set_merge_groups", "abt_set_merge_stage_timing",
     "ab_merge_stage_ms", "abt_set_chain_rows", "abt_set_chain_parts",
-    "lr_linear_fwd", "lr_linear_fwd_workspace_bytes",
+    "lr_linear_fwd", "lr_linear_fwd_workspace_bytes", "lr_linear_fwd_wants_T",
     "lr_linear_bwd", "lr_linear_bwd_workspace_bytes", "lr_linear_bwd_static",
     "lr_linear_fwd_grouped", "lr_linear_bwd_grouped", "lr_linear_bwd_grouped_workspace_bytes",
     "ab_merge", "ab_merge_workspace_bytes",
@@ -111,6 +111,8 @@ def load():
     lib.lr_linear_fwd.argtypes = [vp, vp, vp, vp, vp, i64, i64, i64, i64, ci, vp, sz, vp]
     lib.lr_linear_fwd_workspace_bytes.restype = sz
     lib.lr_linear_fwd_workspace_bytes.argtypes = [i64, i64, i64, i64, ci]
+    lib.lr_linear_fwd_wants_T.restype = ci
+    lib.lr_linear_fwd_wants_T.argtypes = [ci, i64, i64, i64, i64, ci]
     lib.lr_linear_bwd.restype = ci
     lib.lr_linear_bwd.argtypes = [vp, vp, vp, vp, vp, vp, vp, vp, i64, i64, i64, i64, ci, ci, vp, sz, vp]
     lib.lr_linear_bwd_workspace_bytes.restype = sz
@@ -237,7 +239,7 @@ def _stream():
     return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
 
 
-# Kept, as the sizes depend on the shape alone (those of the forward depend on set_chain_rows and set_chain_parts too).
+# Kept, as the sizes depend on the shape alone (lr_linear_fwd_wants_T follows set_chain_rows and set_chain_parts).
 @functools.lru_cache(maxsize=1024)
 def _bwd_bytes(M, m, n, r, dt):
     return load().lr_linear_bwd_workspace_bytes(M, m, n, r, dt)
@@ -276,10 +278,10 @@ def lr_linear_fwd(X, A, B, save_T: bool = True, Y=None, T=None, workspace=None):
     if save_T and T is None:
         T = X.new_empty((M, r))
     ws = workspace
-    if not save_T or (ws is not None and dt == ABT_F32):         # (a bf16 call that keeps T takes any workspace and uses none)
-        nbytes = lib.lr_linear_fwd_workspace_bytes(M, m, n, r, dt)
-        ws = _workspace(nbytes, X.device, ws) if nbytes or ws is not None else None
-    _check(lib.lr_linear_fwd(X.data_ptr(), A.data_ptr(), B.data_ptr(), Y.data_ptr(), _ptr(T if save_T else None),
+    if dt == ABT_F32 and (ws is not None or not save_T):         # (bf16 uses none)
+        ws = _workspace(lib.lr_linear_fwd_workspace_bytes(M, m, n, r, dt), X.device, ws)
+    place = T if save_T else X.new_empty((M, r)) if lib.lr_linear_fwd_wants_T(1, M, m, n, r, dt) else None
+    _check(lib.lr_linear_fwd(X.data_ptr(), A.data_ptr(), B.data_ptr(), Y.data_ptr(), _ptr(place),
                              M, m, n, r, dt, _ptr(ws), ws.numel() if ws is not None else 0, _stream()), "lr_linear_fwd")
     return Y, (T if save_T else None)
 

@@ -736,8 +736,12 @@ int ab_merge_stage_ms(float* ms) {
 
 size_t lr_linear_fwd_workspace_bytes(int64_t M, int64_t m, int64_t n, int64_t r, int dt) {
     if (check_lr_shapes(M, m, n, r, dt) != ABT_OK) return 0;
-    if (dt == ABT_BF16) return two_products(M, (int)n, (int)m, (int)r, false) && lr_small_supports(M, (int)m, (int)n, (int)r) ? align_up((size_t)M * r * 2, 256) : 0;
-    return align_up((size_t)M * r * 4, 256);
+    return dt == ABT_F32 ? align_up((size_t)M * r * 4, 256) : 0;
+}
+
+int lr_linear_fwd_wants_T(int G, int64_t M, int64_t m, int64_t n, int64_t r, int dt) {
+    if (G < 1 || G > ABT_MAX_GROUPS || dt != ABT_BF16 || check_lr_shapes(M, m, n, r, dt) != ABT_OK) return 0;
+    return two_products(G * M, (int)n, (int)m, (int)r, false) && lr_small_supports(M, (int)m, (int)n, (int)r);
 }
 
 size_t lr_linear_bwd_workspace_bytes(int64_t M, int64_t m, int64_t n, int64_t r, int dt) {
@@ -755,9 +759,6 @@ int lr_linear_fwd(const void* X, const void* A, const void* B, void* Y, void* T_
         return ABT_EALIGN;
     hipStream_t s = (hipStream_t)stream;
     if (dt == ABT_BF16) {
-        // a place for T, if the call came with one, where T is not kept
-        const size_t place = T_save ? 0 : lr_linear_fwd_workspace_bytes(M, m, n, r, dt);
-        if (place && workspace && workspace_bytes >= place && aligned(workspace, 256)) T_save = workspace;
         return chain(X, B, A, Y, T_save, M, (int)n, (int)m, (int)r, s) == hipSuccess ? ABT_OK : ABT_EHIP;
     }
     float* T = (float*)T_save;
@@ -949,9 +950,6 @@ int lr_linear_fwd_grouped(const abt_lr_group* groups, int G,
     }
     ChainProblem pr[kChainMaxGroups];
     for (int g = 0; g < G; ++g) pr[g] = ChainProblem{groups[g].X, groups[g].B, groups[g].A, groups[g].Y, groups[g].T_save};
-    const size_t place = groups[0].T_save ? 0 : lr_linear_fwd_workspace_bytes(M, m, n, r, dt);
-    if (place && two_products(G * M, (int)n, (int)m, (int)r, false) && workspace && workspace_bytes >= place * G && aligned(workspace, 256))
-        for (int g = 0; g < G; ++g) pr[g].Tout = (char*)workspace + place * g;
     return chain_grouped(pr, G, M, (int)n, (int)m, (int)r, (hipStream_t)stream) == hipSuccess ? ABT_OK : ABT_EHIP;
 }
 

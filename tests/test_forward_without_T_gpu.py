@@ -38,3 +38,20 @@ def test_a_kept_T_needs_no_workspace(dtype):
     again = abt.lr_linear_fwd(X, A, B)
     assert taken() == before + 2                         # Y and T
     assert torch.equal(again[0], Y) and torch.equal(again[1], T)
+
+
+def test_a_forward_leaves_the_workspace_alone():
+    # one workspace may serve forwards on several streams: nothing of a bf16 forward is kept there
+    M, m, n, r = 203, 2304, 768, 192
+    X, A, B, _ = layer(M, m, n, r)
+    lib = abt.load()
+    assert lib.lr_linear_fwd_workspace_bytes(M, m, n, r, abt.ABT_BF16) == 0
+    ws = torch.full((M * r * 4,), 85, dtype=torch.uint8, device="cuda")
+    want = abt.lr_linear_fwd(X, A, B)[0]
+    assert torch.equal(abt.lr_linear_fwd(X, A, B, save_T=False, workspace=ws)[0], want) and bool((ws == 85).all())
+    assert torch.equal(abt.lr_linear_fwd(X, A, B, save_T=False, workspace=ws[:1])[0], want)
+    Y = torch.empty_like(want)
+    assert lib.lr_linear_fwd(X.data_ptr(), A.data_ptr(), B.data_ptr(), Y.data_ptr(), None, M, m, n, r, abt.ABT_BF16,
+                             ws.data_ptr(), ws.numel(), torch.cuda.current_stream().cuda_stream) == 0
+    assert bool((ws == 85).all())
+    assert float((Y.double() - want.double()).norm() / want.double().norm()) < 2 ** -7       # T and Y rounded once each
