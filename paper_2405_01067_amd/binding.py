@@ -354,6 +354,9 @@ def lr_linear_fwd_grouped(groups: List[dict], save_T: bool = True):
     G = len(groups)
     table = (LrGroup * G)()
     outs = []
+    places = None
+    if not save_T and lib.lr_linear_fwd_wants_T(G, M, m, n, r, dt):
+        places = torch.empty((G, M, r), dtype=groups[0]["X"].dtype, device=groups[0]["X"].device)
     for i, g in enumerate(groups):
         X = g["X"]
         Y = g.get("Y")
@@ -363,7 +366,7 @@ def lr_linear_fwd_grouped(groups: List[dict], save_T: bool = True):
         if save_T and T is None:
             T = torch.empty((M, r), dtype=X.dtype, device=X.device)
         e = table[i]
-        e.X, e.A, e.B, e.Y, e.T_save = _ptr(X), _ptr(g["A"]), _ptr(g["B"]), _ptr(Y), _ptr(T)
+        e.X, e.A, e.B, e.Y, e.T_save = _ptr(X), _ptr(g["A"]), _ptr(g["B"]), _ptr(Y), _ptr(T if places is None else places[i])
         outs.append((Y, T))
     each = lib.lr_linear_fwd_workspace_bytes(M, m, n, r, dt) if not save_T else 0
     ws = _workspace(each * G, groups[0]["X"].device, None)

@@ -55,3 +55,12 @@ def test_a_forward_leaves_the_workspace_alone():
                              ws.data_ptr(), ws.numel(), torch.cuda.current_stream().cuda_stream) == 0
     assert bool((ws == 85).all())
     assert float((Y.double() - want.double()).norm() / want.double().norm()) < 2 ** -7       # T and Y rounded once each
+
+
+# products of M rows below the rule of two launches, of G M rows above it, and shapes on one side with both
+@pytest.mark.parametrize("G,M,m,n,r", [(4, 500, 640, 768, 128), (8, 260, 2304, 768, 96), (3, 700, 1024, 960, 96), (2, 40, 64, 64, 32), (5, 300, 768, 768, 352)])
+def test_groups_without_T(G, M, m, n, r):
+    groups = [dict(zip("XAB", layer(M, m, n, r, seed=g))) for g in range(G)]
+    kept = abt.lr_linear_fwd_grouped(groups)
+    for (Y, T), (Yk, _) in zip(abt.lr_linear_fwd_grouped(groups, save_T=False), kept):
+        assert T is None and torch.equal(Y, Yk)
