@@ -338,7 +338,8 @@ int ab_reconstruct(const float* A, const float* B, float* W,
  * grid is H' x W' = ceil(H / stride) x ceil(W / stride) (ResNet-50's down-sampling 3 x 3 and 1 x 1
  * convolutions are the stride-2 case).  Y [N H' W', m], T [N H' W', r], dY likewise (row = output
  * pixel, row-major); dAct has act's shape.  bf16 only (fp32 accumulation).
- *   lr_conv_fwd:  T = patches(act) . B^T,  Y = T . A^T          (T_save may be NULL)
+ *   lr_conv_fwd:  T = patches(act) . B^T,  Y = T . A^T          (T_save may be NULL; where lr_conv_fwd_wants_T says 1, it is
+ *     worth a place all the same, as for lr_linear_fwd)
  *   lr_conv_bwd:  dT = dY . A,  dA = dY^T . T,  dB = dT^T . patches(act),
  *                 dAct = adjoint of the patch extraction applied to dT . B
  *     dAct [N, H, W, C] bf16, dA [m, r] and dB [r, kh kw C] fp32; each may be NULL (skipped);
@@ -355,6 +356,8 @@ typedef struct {
 
 int lr_conv_fwd(const void* act, const void* A, const void* B, void* Y, void* T_save,
                 const abt_conv_geom* geom, int64_t m, int64_t r, int dtype, void* stream);
+
+int lr_conv_fwd_wants_T(const abt_conv_geom* geom, int64_t m, int64_t r, int dtype);
 
 int lr_conv_bwd(const void* dY, const void* act, const void* T, const void* A, const void* B,
                 void* dAct, float* dA, float* dB,

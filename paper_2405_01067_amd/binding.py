@@ -28,7 +28,7 @@ EXPORTS = (
     "ab_factorize", "ab_factorize_workspace_bytes",
     "ab_factorize_batched", "ab_factorize_batched_workspace_bytes",
     "ab_adamw_step", "ab_lr_rebound_scale", "ab_reconstruct",
-    "lr_conv_fwd", "lr_conv_bwd", "lr_conv_bwd_workspace_bytes",
+    "lr_conv_fwd", "lr_conv_fwd_wants_T", "lr_conv_bwd", "lr_conv_bwd_workspace_bytes",
 )
 
 
@@ -158,6 +158,8 @@ def load():
     pg = ctypes.POINTER(ConvGeom)
     lib.lr_conv_fwd.restype = ci
     lib.lr_conv_fwd.argtypes = [vp, vp, vp, vp, vp, pg, i64, i64, ci, vp]
+    lib.lr_conv_fwd_wants_T.restype = ci
+    lib.lr_conv_fwd_wants_T.argtypes = [pg, i64, i64, ci]
     lib.lr_conv_bwd.restype = ci
     lib.lr_conv_bwd.argtypes = [vp, vp, vp, vp, vp, vp, vp, vp, pg, i64, i64, ci, ci, vp, sz, vp]
     lib.lr_conv_bwd_workspace_bytes.restype = sz
@@ -469,9 +471,11 @@ def lr_conv_fwd(act, A, B, kh: int, kw: int, save_T: bool = True, Y=None, T=None
         Y = torch.empty((M, m), dtype=act.dtype, device=act.device)
     if save_T and T is None:
         T = torch.empty((M, r), dtype=act.dtype, device=act.device)
+    place = T
     if not save_T:
-        T = None
-    _check(lib.lr_conv_fwd(_ptr(act), _ptr(A), _ptr(B), _ptr(Y), _ptr(T), ctypes.byref(geom), m, r, _dt(act), _stream()),
+        wanted = lib.lr_conv_fwd_wants_T(ctypes.byref(geom), m, r, _dt(act))
+        place, T = torch.empty((M, r), dtype=act.dtype, device=act.device) if wanted else None, None
+    _check(lib.lr_conv_fwd(_ptr(act), _ptr(A), _ptr(B), _ptr(Y), _ptr(place), ctypes.byref(geom), m, r, _dt(act), _stream()),
            "lr_conv_fwd")
     return Y, T
 

@@ -408,10 +408,11 @@ inline bool is_linear(const abt_conv_geom& g) { return g.kh == 1 && g.kw == 1 &&
 // ranks whose gathered form has more work-groups per compute unit than the other at large batches (forward, us, as a matrix /
 // gathered: 28 x 28 x 512, r = 192, batch 256 101 / 91, 128 55 / 51; 56 x 56 x 256, r = 128, batch 128 79 / 79, r = 192 117 / 106;
 // below: 14 x 14 x 1024, batch 256, r = 128 32 / 33, r = 192 40 / 42; 7 x 7 x 2048, r = 64 18 / 25; 28 x 28 x 512, r = 256 110 / 179).
+bool as_matrix(const abt_conv_geom& g, int64_t M, int64_t r) { return is_linear(g) && !(M > 65536 && r > 96 && r <= 192); }
 hipError_t conv_chain(const void* act, const abt_conv_geom& g, const void* A, const void* B, void* Y, void* T, int64_t m, int64_t r,
                       hipStream_t s) {
     const int64_t M = conv_rows(g);
-    if (is_linear(g) && !(M > 65536 && r > 96 && r <= 192)) return chain(act, B, A, Y, T, M, (int)g.C, (int)m, (int)r, s);
+    if (as_matrix(g, M, r)) return chain(act, B, A, Y, T, M, (int)g.C, (int)m, (int)r, s);
     return chain_gather(act, conv_patches_geom(g), B, A, Y, T, (int)r, M, (int)m, (int)r, s);
 }
 
@@ -584,6 +585,14 @@ hipError_t conv_dact(const void* dT, const void* B, void* dAct, void* Pst, const
 size_t lr_conv_bwd_workspace_bytes(const abt_conv_geom* geom, int64_t m, int64_t r, int dt) {
     if (check_conv(geom, m, r, dt) != ABT_OK) return 0;
     return conv_bwd_layout(*geom, m, r).total;
+}
+
+int lr_conv_fwd_wants_T(const abt_conv_geom* geom, int64_t m, int64_t r, int dt) {
+    if (check_conv(geom, m, r, dt) != ABT_OK) return 0;
+    const abt_conv_geom& g = *geom;
+    const int64_t M = conv_rows(g);
+    if (as_matrix(g, M, r)) return two_products(M, (int)g.C, (int)m, (int)r, false) && lr_small_supports(M, (int)m, (int)g.C, (int)r);
+    return two_products(M, g.kh * g.kw * (int)g.C, (int)m, (int)r, true) && lr_small_gather_supports(conv_patches_geom(g), M, (int)m, (int)r);
 }
 
 int lr_conv_fwd(const void* act, const void* A, const void* B, void* Y, void* T_save,

@@ -64,3 +64,18 @@ def test_groups_without_T(G, M, m, n, r):
     kept = abt.lr_linear_fwd_grouped(groups)
     for (Y, T), (Yk, _) in zip(abt.lr_linear_fwd_grouped(groups, save_T=False), kept):
         assert T is None and torch.equal(Y, Yk)
+
+
+# the two-product rule of the image and of the matrix (1 x 1), and shapes below it
+@pytest.mark.parametrize("N,H,W,C,kh,kw,stride,m,r", [(2, 14, 14, 256, 3, 3, 1, 256, 256), (1, 28, 28, 128, 3, 3, 2, 64, 192), (4, 7, 7, 2048, 1, 1, 1, 512, 128),
+                                                      (3, 14, 13, 1024, 1, 1, 2, 64, 384), (2, 6, 5, 64, 3, 3, 1, 64, 32)])
+def test_convolution_without_T(N, H, W, C, kh, kw, stride, m, r):
+    g = torch.Generator(device="cuda").manual_seed(N + C + r)
+    rn = lambda std, *s: (torch.randn(s, generator=g, device="cuda") * std).to(BF)
+    act, A, B = rn(1, N, H, W, C), rn(r ** -0.5, m, r), rn((kh * kw * C) ** -0.5, r, kh * kw * C)
+    Y, T = abt.lr_conv_fwd(act, A, B, kh, kw, stride=stride)
+    bare = abt.lr_conv_fwd(act, A, B, kh, kw, stride=stride, save_T=False)
+    assert bare[1] is None and torch.equal(bare[0], Y)
+    dY = rn(1e-2, *Y.shape)
+    kept, again = (abt.lr_conv_bwd(dY, act, t, A, B, kh, kw, stride=stride)[1] for t in (T, None))
+    assert torch.equal(kept, again)
