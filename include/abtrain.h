@@ -144,8 +144,9 @@ int lr_linear_bwd_static(const void* dY, const void* X, const void* T, const voi
  * ABT_BF16: the forward is one launch (few rows: two) for all groups; the backward is one launch each for the
  * transposes, the dT/dX chain (two if only some groups ask for dX), the factor gradients of all
  * groups and their split reduction.  ABT_F32: the single-group path, group by group.
- * Results per group are those of the single-group calls up to the summation order of dA / dB
- * (the row split depends on the number of tiles in the launch); two grouped calls on the same
+ * Results per group are those of the single-group calls up to the order of the fp32 sums, which depends on the rows of all
+ * groups (bf16: T, dT and what is computed from them may differ by a rounding).  A T that the backward computes again, for all
+ * groups or some, is the T_save of a forward of the same groups; two grouped calls on the same
  * inputs give bit-identical results.  Workspace: lr_linear_bwd_grouped_workspace_bytes for the
  * backward, lr_linear_fwd_workspace_bytes * G laid end to end for the forward without T_save.
  * ------------------------------------------------------------------------------------- */

@@ -110,13 +110,14 @@ int narrow_cols(int n, int64_t row_blocks, int R) {
     return R;
 }
 
-// Runs n problems of one shape, all with a second stage or none, in the narrow-rank kernel if the rule above says so.
+// Runs n problems of one shape, all with a second stage or none, in the narrow-rank kernel if the rule above says so for `of`
+// problems (n, or the groups of a call of which n compute T again: the order of the sums is then that of the forward).
 // Work-groups that share a row block all read its rows of Xin, and the first of them to finish writes: not with an output
 // over Xin (the other kernels have one reader per row block, which reads before it writes).
-bool narrow_chain(const ChainProblem* problems, int n, int64_t M, int p, int q, int R, hipStream_t s, hipError_t* e) {
-    if (!use_narrow(n * M, p, q, R)) return false;
+bool narrow_chain(const ChainProblem* problems, int n, int of, int64_t M, int p, int q, int R, hipStream_t s, hipError_t* e) {
+    if (!use_narrow(of * M, p, q, R)) return false;
     const bool second = problems[0].Yout != nullptr;
-    const int rows = narrow_rows(n * M);
+    const int rows = narrow_rows(of * M);
     const int64_t blocks = n * ceil_div(M, rows);
     const int parts = narrow_parts(blocks, p, q, second);
     int cols = second || n * M > 8192 ? R : narrow_cols(n, blocks, R);
@@ -160,8 +161,8 @@ bool two_products(int64_t rows, int p, int q, int R, bool image) {
     return small && rows <= (padded ? 10240 : image || wide ? 8192 : 4096);
 }
 // T needs a place, and not over the first operand, whose rows several work-groups read.
-bool two_products(const ChainProblem* problems, int n, int64_t M, int p, int q, int R) {
-    if (!two_products(n * M, p, q, R, false) || !lr_small_supports(M, q, p, R)) return false;
+bool two_products(const ChainProblem* problems, int n, int of, int64_t M, int p, int q, int R) {
+    if (!two_products(of * M, p, q, R, false) || !lr_small_supports(M, q, p, R)) return false;
     for (int g = 0; g < n; ++g)
         if (!problems[g].Tout || overlap(problems[g].Xin, M * p * 2, problems[g].Tout, M * R * 2)) return false;
     return true;
@@ -209,9 +210,9 @@ hipError_t chain_gather(const void* image, const PatchGeom& g, const void* P, co
 hipError_t chain(const void* Xin, const void* P, const void* Q, void* Yout, void* Tout,
                  int64_t M, int p, int q, int R, hipStream_t s) {
     const ChainProblem one{Xin, P, Q, Yout, Tout};
-    if (two_products(&one, 1, M, p, q, R)) return launch_lr_small_fwd(&one, 1, M, p, q, R, s);
+    if (two_products(&one, 1, 1, M, p, q, R)) return launch_lr_small_fwd(&one, 1, 1, M, p, q, R, s);
     hipError_t e;
-    if (narrow_chain(&one, 1, M, p, q, R, s, &e)) return e;
+    if (narrow_chain(&one, 1, 1, M, p, q, R, s, &e)) return e;
     const ChainShape sh = choose_chain_shape(M, p, q, R, Yout != nullptr, true);
     if (sh.rows == 128) return launch_chain2_tall_bf16(Xin, P, Q, Yout, Tout, M, p, q, R, sh.parts, s);
     return launch_chain2_bf16(Xin, P, Q, Yout, Tout, M, p, q, R, s);
@@ -907,8 +908,9 @@ int chain_rows_for_groups(int G, int64_t M, int p, int q, int R) {
     return cost128 < cost64 ? 128 : 64;
 }
 
-// one launch for the problems with a second stage and one for those without
-hipError_t chain_grouped(const ChainProblem* pr, int G, int64_t M, int p, int q, int R, hipStream_t s) {
+// One launch for the problems with a second stage and one for those without.  again: T for some of the groups, by the rules
+// for all of them.
+hipError_t chain_grouped(const ChainProblem* pr, int G, int64_t M, int p, int q, int R, bool again, hipStream_t s) {
     for (int second = 1; second >= 0; --second) {
         ChainProblem sel[kChainMaxGroups];
         int n = 0;
@@ -918,10 +920,11 @@ hipError_t chain_grouped(const ChainProblem* pr, int G, int64_t M, int p, int q,
         }
         if (n == 0) continue;
         hipError_t e;
-        if (two_products(sel, n, M, p, q, R)) {
-            e = launch_lr_small_fwd(sel, n, M, p, q, R, s);
-        } else if (!narrow_chain(sel, n, M, p, q, R, s, &e)) {
-            e = launch_chain2_grouped_bf16(sel, n, M, p, q, R, chain_rows_for_groups(n, M, p, q, R), 1, s);
+        const int of = again ? G : n;
+        if (two_products(sel, n, of, M, p, q, R)) {
+            e = launch_lr_small_fwd(sel, n, of, M, p, q, R, s);
+        } else if (!narrow_chain(sel, n, of, M, p, q, R, s, &e)) {
+            e = launch_chain2_grouped_bf16(sel, n, M, p, q, R, chain_rows_for_groups(of, M, p, q, R), 1, s);
         }
         if (e != hipSuccess) return e;
     }
@@ -959,7 +962,7 @@ int lr_linear_fwd_grouped(const abt_lr_group* groups, int G,
     }
     ChainProblem pr[kChainMaxGroups];
     for (int g = 0; g < G; ++g) pr[g] = ChainProblem{groups[g].X, groups[g].B, groups[g].A, groups[g].Y, groups[g].T_save};
-    return chain_grouped(pr, G, M, (int)n, (int)m, (int)r, (hipStream_t)stream) == hipSuccess ? ABT_OK : ABT_EHIP;
+    return chain_grouped(pr, G, M, (int)n, (int)m, (int)r, false, (hipStream_t)stream) == hipSuccess ? ABT_OK : ABT_EHIP;
 }
 
 int lr_linear_bwd_grouped(const abt_lr_group* groups, int G,
@@ -1005,7 +1008,7 @@ int lr_linear_bwd_grouped(const abt_lr_group* groups, int G,
             any = true;
         }
     }
-    if (any && chain_grouped(pr, G, M, (int)n, (int)m, (int)r, s) != hipSuccess) return ABT_EHIP;
+    if (any && chain_grouped(pr, G, M, (int)n, (int)m, (int)r, true, s) != hipSuccess) return ABT_EHIP;
     // dT = dY (A^T)^T, dX = dT (B^T)^T: the forward chain on the transposed factors of every group
     TransposeJob tj[kTransposeMaxJobs];
     int ntj = 0;
@@ -1021,7 +1024,7 @@ int lr_linear_bwd_grouped(const abt_lr_group* groups, int G,
     }
     if (any) {
         if (launch_transpose_bf16(tj, ntj, s) != hipSuccess) return ABT_EHIP;
-        if (chain_grouped(pr, G, M, (int)m, (int)n, (int)r, s) != hipSuccess) return ABT_EHIP;
+        if (chain_grouped(pr, G, M, (int)m, (int)n, (int)r, false, s) != hipSuccess) return ABT_EHIP;
     }
     // factor gradients of all groups in one launch (and one split reduction)
     TnJob jobs[kTnMaxJobs];

@@ -184,7 +184,8 @@ hipError_t launch_tn_finish(const TnJob* jobs, int njobs, int R, int accumulate,
 // 32-bit offsets: M, m, n and r against each other
 bool lr_small_supports(int64_t M, int m, int n, int r);
 // The chain for few rows as two products, T and Y or T alone (Yout NULL, for all problems or none); Tout must have a place that lies over no input.
-hipError_t launch_lr_small_fwd(const ChainProblem* problems, int G, int64_t M, int p, int q, int R, hipStream_t s);
+// The tile and the split of the contraction are those of a launch of `of` problems (at least G).
+hipError_t launch_lr_small_fwd(const ChainProblem* problems, int G, int of, int64_t M, int p, int q, int R, hipStream_t s);
 // first operand gathered from an image: sign = +1, shift = 0
 bool lr_small_gather_supports(const PatchGeom& g, int64_t M, int q, int R);
 hipError_t launch_lr_small_fwd_gather(const void* image, const PatchGeom& g, const void* P, const void* Q, void* Yout, void* Tout, int64_t M, int q, int R,

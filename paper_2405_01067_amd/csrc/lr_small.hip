@@ -53,8 +53,8 @@ __device__ __forceinline__ void unpair(const uint32_t (&d)[8], u32x4 (&op)[2]) {
 //   * Whole 128-byte lines travel through registers (two stages of SK units ahead) into two LDS buffers, one barrier per stage.  (Each
 //     lane loading the pieces of its operand: 32 lines per instruction instead of 8, 197 x 3072, r = 192 16.2 us, 11.1.)
 //   * A wave's tile with 64 x 64 values instead of 32 x 32: no gain below 16000 rows.
-// The order of the sums depends on the rows, the contraction and the rank alone: T is the same bits kept or recomputed, and from an image (a
-// convolution's patches, columns ordered tap, channel) or its patch matrix.
+// The order of the sums depends on SK, which launch_t picks by the rows of all groups of the call, the rank and the tile: T is the same bits
+// kept or computed again (for all groups of a call or some).
 struct SmallNtEntry { const uint16_t* U; const uint16_t* V; uint16_t* C; };
 struct SmallNt {
     SmallNtEntry e[kChainMaxGroups];                     // problems of one shape
@@ -548,8 +548,8 @@ hipError_t launch_nt(SmallNt p, int problems, hipStream_t s) {
 //   768 -> 2304, r = 384: 197 rows 10.6 / 10.1 / 11.6 / 12.1, 1000 18.3 / 16.2 / 17.3 / 18.3, 2000 27.7 / 26.1 / 23.7 / 24.4, 4000 48 / 40 / 38 / 35;
 //   3072 -> 768, r = 384: 13.2 / 15.4 / 18.6 / 25.6, 22.9 / 17.5 / 21.0 / 28.5, 32.6 / 29.8 / 24.5 / 30.7, 58 / 45 / 41 / 35.
 template <bool GATHER>
-hipError_t launch_t(const SmallNt& p, int problems, hipStream_t s) {
-    auto groups = [&](int rows, int cols) { return problems * ceil_div(p.M, rows) * ceil_div(p.N, cols); };
+hipError_t launch_t(const SmallNt& p, int problems, int of, hipStream_t s) {
+    auto groups = [&](int rows, int cols) { return of * ceil_div(p.M, rows) * ceil_div(p.N, cols); };
     if (groups(32, 32) <= 256) return launch_nt<1, 1, 8, GATHER>(p, problems, s);
     if (groups(32, 64) <= 256) return launch_nt<1, 2, 4, GATHER>(p, problems, s);
     if (groups(64, 64) <= 256) return launch_nt<2, 2, 2, GATHER>(p, problems, s);
@@ -563,8 +563,8 @@ hipError_t launch_y(const SmallNt& p, int problems, hipStream_t s) {
 }
 }  // namespace
 
-hipError_t launch_lr_small_fwd(const ChainProblem* problems, int G, int64_t M, int p, int q, int R, hipStream_t s) {
-    if (G < 1 || G > kChainMaxGroups || !lr_small_supports(M, q, p, R)) return hipErrorInvalidValue;
+hipError_t launch_lr_small_fwd(const ChainProblem* problems, int G, int of, int64_t M, int p, int q, int R, hipStream_t s) {
+    if (G < 1 || G > kChainMaxGroups || of < G || !lr_small_supports(M, q, p, R)) return hipErrorInvalidValue;
     SmallNt t{}, y{};
     t.M = y.M = (int)M;
     t.N = R; t.K = p; t.u_bytes = M * p * 2;
@@ -575,7 +575,7 @@ hipError_t launch_lr_small_fwd(const ChainProblem* problems, int G, int64_t M, i
         t.e[g] = SmallNtEntry{(const uint16_t*)c.Xin, (const uint16_t*)c.P, (uint16_t*)c.Tout};
         y.e[g] = SmallNtEntry{(const uint16_t*)c.Tout, (const uint16_t*)c.Q, (uint16_t*)c.Yout};
     }
-    const hipError_t e = launch_t<false>(t, G, s);
+    const hipError_t e = launch_t<false>(t, G, of, s);
     return e != hipSuccess || !problems[0].Yout ? e : launch_y(y, G, s);
 }
 
@@ -595,7 +595,7 @@ hipError_t launch_lr_small_fwd_gather(const void* image, const PatchGeom& g, con
     t.H = g.H; t.W = g.W; t.Cin = g.Cin; t.kh = g.kh; t.kw = g.kw; t.RH = g.RH; t.RW = g.RW; t.mul = g.mul;
     y.e[0] = SmallNtEntry{(const uint16_t*)Tout, (const uint16_t*)Q, (uint16_t*)Yout};
     y.N = q; y.K = R; y.u_bytes = M * R * 2;
-    const hipError_t e = launch_t<true>(t, 1, s);
+    const hipError_t e = launch_t<true>(t, 1, 1, s);
     return e != hipSuccess || !Yout ? e : launch_y(y, 1, s);
 }
 

@@ -79,3 +79,16 @@ def test_convolution_without_T(N, H, W, C, kh, kw, stride, m, r):
     dY = rn(1e-2, *Y.shape)
     kept, again = (abt.lr_conv_bwd(dY, act, t, A, B, kh, kw, stride=stride)[1] for t in (T, None))
     assert torch.equal(kept, again)
+
+
+# T again for one group or two of several: the values that the forward of all of them gave
+@pytest.mark.parametrize("G,M,m,n,r", [(4, 512, 192, 768, 192), (4, 512, 192, 384, 192), (8, 250, 640, 768, 384), (4, 2500, 64, 3072, 96), (3, 4000, 192, 192, 288)])
+def test_some_groups_compute_T_again(G, M, m, n, r):
+    groups = [dict(zip(("X", "A", "B", "dY"), layer(M, m, n, r, seed=g))) for g in range(G)]
+    for e, (_, T) in zip(groups, abt.lr_linear_fwd_grouped([{k: e[k] for k in "XAB"} for e in groups])):
+        e["T"] = T
+    kept = abt.lr_linear_bwd_grouped([dict(e, dA=True) for e in groups])
+    for without in ([G - 1], [0, 1]):
+        again = abt.lr_linear_bwd_grouped([dict(e, T=None if i in without else e["T"], dA=True) for i, e in enumerate(groups)])
+        for a, b in zip(again, kept):
+            assert torch.equal(a[1], b[1])
