@@ -18,4 +18,12 @@ inline int64_t grid_window(int64_t rows, int64_t RH, int64_t RW, int64_t mul, in
     return (steps * mul + crossings * extra) * W + mul * (RW - 1) + 1;
 }
 
+// The gathered chain through a window of the image in LDS: bytes of a work-group at rank R whose window has `pixels` pixels (two
+// slabs of 64 columns of the factor; 64 channels of each pixel, eight pixels at a time, and of a row of zeros).
+inline int64_t window_lds_bytes(int R, int64_t pixels) { return 2 * R * 128 + ((pixels + 7) / 8 * 8 + 1) * 128; }
+constexpr int kMaxWindow = 256;                          // 16-byte pieces that 256 threads load, eight each
+// Two work-groups have to share the 160 KB of a compute unit.  At R = 192 they do up to 248 pixels (forward of 60 x 60, 250 pixels, r = 192, 64800
+// rows, through the window / gathered, us: C = 64 35 / 30, 128 50 / 43, 192 66 / 57; 59 x 59, 248 pixels: 26 / 30, 39 / 42, 55 / 57).
+inline bool window_fits(int R, int64_t pixels) { return pixels <= kMaxWindow && 2 * window_lds_bytes(R, pixels) <= 160 * 1024; }
+
 }  // namespace abt

@@ -49,7 +49,8 @@ __device__ __forceinline__ void wave_lds_order() {
 }
 
 constexpr int kMaxRows = 128, NT = 256;
-constexpr int kWinPieces = 8, kMaxWindow = 32 * kWinPieces;          // image window in LDS: 16-byte pieces per thread, pixels of 64 channels
+constexpr int kWinPieces = 8;                        // image window in LDS: 16-byte pieces per thread
+static_assert(kMaxWindow == 32 * kWinPieces, "pixels of 64 channels");
 // Where the first operand comes from: a matrix; an image, per lane; an image through a window in LDS (one block of 64 channels;
 // several, with nine taps).
 enum Source { kMatrix, kGather, kWindow, kWindows };
@@ -497,7 +498,7 @@ bool chain4_window(const ChainGather& g, int R, int rows) {
     const int taps = g.kh * g.kw, cpb = (g.Cin + 63) / 64;
     if (g.mul != 1 || taps < 2 || (cpb > 1 && taps != 9)) return false;
     const int64_t w = window_pixels(g, rows);
-    return w <= kMaxWindow && !(R == 128 && cpb == 1 && w > 192) && !(R >= 128 && g.Cin <= 32);
+    return window_fits(R, w) && !(R == 128 && cpb == 1 && w > 192) && !(R >= 128 && g.Cin <= 32);
 }
 
 bool chain4_supports(int R, int p, int q) {
@@ -545,7 +546,7 @@ hipError_t launch_chain4_gather_bf16(const GatherProblem* problems, int n, int q
         a.e[i] = C4Entry{(const uint16_t*)c.image, (const uint16_t*)c.P, (const uint16_t*)c.Q, (uint16_t*)c.Yout, (uint16_t*)c.Tout, c.M, (int)p, g};
         if (ceil_div(c.M, rows) > blocks) blocks = ceil_div(c.M, rows);
         if (g.mul == 1 && window_pixels(g, rows) > window) window = window_pixels(g, rows);
-        windowed = windowed && (chain4_window(g, R, rows) || (single_tap_ok && g.kh * g.kw == 1 && g.mul == 1 && g.cpb == 1));
+        windowed = windowed && (chain4_window(g, R, rows) || (single_tap_ok && g.kh * g.kw == 1 && g.mul == 1 && g.cpb == 1 && window_fits(R, window)));
         single = single && g.cpb == 1;
         out_bytes += c.M * ((c.Yout ? q : 0) + (c.Tout ? R : 0)) * 2;
         second |= c.Yout != nullptr;

@@ -53,3 +53,31 @@ def test_window_is_the_largest_over_all_starts(tmp_path):
     r = subprocess.run([exe], stdout=subprocess.PIPE, text=True)
     assert r.returncode == 0, r.stdout
     assert int(r.stdout) > 1000
+
+
+FITS = r"""
+#include <cstdio>
+#include "grid_window.h"
+int main() {
+    int accepted = 0;
+    for (int R = 32; R <= 192; R += 32)
+        for (long pixels = 1; pixels <= 300; ++pixels) {
+            const long slots = (pixels + 7) / 8 * 8, bytes = 2l * R * 64 * 2 + (slots + 1) * 64 * 2;
+            if (abt::window_fits(R, pixels) != (pixels <= 256 && bytes <= 80 * 1024)) { std::printf("R %d, %ld pixels\n", R, pixels); return 1; }
+            accepted += abt::window_fits(R, pixels);
+        }
+    std::printf("%d\n", accepted);
+    return abt::window_fits(192, 248) && !abt::window_fits(192, 249) && abt::window_fits(160, 256) ? 0 : 2;
+}
+"""
+
+
+@pytest.mark.skipif(shutil.which("g++") is None, reason="no host compiler")
+def test_windows_leave_room_for_two_work_groups(tmp_path):
+    src = tmp_path / "fits.cpp"
+    src.write_text(FITS)
+    exe = str(tmp_path / "fits")
+    subprocess.run(["g++", "-std=c++17", "-O1", "-I", os.path.join(ROOT, "paper_2405_01067_amd", "csrc"), str(src), "-o", exe], check=True)
+    r = subprocess.run([exe], stdout=subprocess.PIPE, text=True)
+    assert r.returncode == 0, r.stdout
+    assert int(r.stdout) == 5 * 256 + 248
