@@ -117,3 +117,24 @@ def test_convolution_of_few_pixels(N, H, W, C, kh, kw, stride, m, r):
             assert torch.equal(a, b) if w else b is None
     twice = abt.lr_conv_bwd(dY, act, T, A, B, kh, kw, stride=stride, dA=got[1].clone(), dB=got[2].clone(), accumulate=True)
     assert rel(twice[1], 2 * got[1].double()) < 1e-6 and rel(twice[2], 2 * got[2].double()) < 1e-6
+
+
+# Which backward it is shows in the order of dA's fp32 sums: with the column parts named, the kernels for many rows.
+# Sizes on both sides of every limit: rows, products, a wide dX, a long contraction of dT.
+@pytest.mark.parametrize("M,m,n,r,few", [(2048, 64, 64, 32, True), (2049, 64, 64, 32, False), (4096, 768, 256, 32, True), (4097, 768, 256, 32, False),
+                                         (4096, 3072, 768, 192, True), (4096, 3072, 768, 256, False), (4096, 1024, 4096, 384, False), (2048, 4096, 4096, 384, False),
+                                         (2048, 64, 8192, 96, True), (2048, 64, 8192, 192, False), (1024, 128, 16384, 160, False), (1024, 64, 16384, 64, True),
+                                         (197, 7168, 64, 96, True), (197, 7232, 64, 96, False), (197, 8192, 64, 64, True), (1024, 8192, 64, 64, False),
+                                         (197, 8256, 64, 32, False), (100, 8320, 7232, 32, True)])
+def test_which_backward_a_linear_layer_takes(M, m, n, r, few):
+    g = torch.Generator(device="cuda").manual_seed(M + m + n + r)
+    rn = lambda std, *s: (torch.randn(s, generator=g, device="cuda") * std).to(BF)
+    X, dY, A, B, T = rn(1, M, n), rn(1e-2, M, m), rn(r ** -0.5, m, r), rn(n ** -0.5, r, n), rn(1, M, r)
+    dA = lambda: abt.lr_linear_bwd(dY, X, T, A, B, need_dX=False, need_dB=False)[1]
+    got = dA()
+    prev = abt.set_chain_parts(1)
+    try:
+        want = dA()
+    finally:
+        abt.set_chain_parts(prev)
+    assert rel(got, want.double()) < 1e-5 and torch.equal(got, want) != few
