@@ -451,14 +451,25 @@ SmallBwd small_bwd(const void* dY, const void* X, const void* T, const void* B, 
     return over(dA, m * r * 4) || over(dB, r * n * 4) ? kOver : kSmall;
 }
 
-// Where the two launches for few rows are the faster backward of a convolution (us, the other kernels / these; side x side x C, r):
-//   3 x 3: 14 x 14 x 256, 64: 1 image 27 / 9, 980 rows 38 / 12, 3920 49 / 23, 8036 45 / 38, 12544 49 / 57; r = 256 980 rows 66 / 21, 8036 71 / 70;
-//   stride 2, 64: 4067 rows 56 / 29, 8183 50 / 51, r = 128 59 / 66; 28 x 28 x 128, stride 2, 256: 8036 rows 75 / 56; 7 x 7 x 512, 64: 8183
-//   rows 54 / 47, r = 128 67 / 72, r = 256 4067 93 / 68, 5978 91 / 93; 1 x 1, stride 2: 7 x 7 x 2048, 256: 16 rows 87 / 10, 4096 137 / 118, 6000 142 / 169.
-// From 4096 rows on by the pixels of dAct and the products.
+// Where they are the faster backward of a convolution.  us, the other kernels / these; side x side x C, window, r:
+//   14 x 14 x 256, 3 x 3            r = 64, 1 image 27 / 9, 980 rows 38 / 12, 3920 49 / 23, 8036 45 / 38, 12544 49 / 57;  r = 256, 980 rows 66 / 21
+//   7 x 7 x 512, 3 x 3              r = 64, 8183 rows 54 / 47;  r = 128 67 / 72;  r = 256, 4067 rows 93 / 68, 5978 rows 91 / 93;  r = 384, 4067 rows 95 / 95
+//   28 x 28 x 128, 3 x 3, stride 2  r = 256, 8036 rows 75 / 56
+// Always up to 2048 rows.  Beyond, as many products, a patch matrix of many columns (read again for every 64 ranks) and an activation of
+// many pixels (dAct in 4-byte pieces, less of the whole at wide ranks) go to the others:
+//   31 x 31 x 2944, 3 x 3           r = 256, 3844 rows 231 / 342       53 x 53 x 1536, 3 x 3    r = 384, 2809 rows 160 / 205
+//   60 x 60 x 1344, 3 x 3           r = 128, 3600 rows 71 / 83         11 x 11 x 1024, 3 x 3    r = 256, 1936 rows 88 / 67
+//   14 x 14 x 1024, 1 x 1, stride 2 r = 32, 4067 rows 57 / 64, r = 192 73 / 73
+//   7 x 7 x 2048, 1 x 1, stride 2   r = 64, 2992 rows 87 / 75, 4096 rows 88 / 98;  r = 256, 16 rows 87 / 10, 4096 rows 125 / 121, 6000 rows 142 / 169
+// From 4096 rows on only few of each, and of the products with A (57 x 57 x 320, 3 x 3, m = 1728, r = 160, 6498 rows: 74 / 79).
 bool few_pixels(const abt_conv_geom& g, int64_t M, int64_t m, int64_t r) {
-    const int64_t n = (int64_t)g.kh * g.kw * g.C;
-    if (M > 4096 && (M > 8192 || (int64_t)g.N * g.H * g.W * g.C > (4 << 20) || M * n * r > 3500000000ll)) return false;
+    const int64_t n = (int64_t)g.kh * g.kw * g.C, pixels = (int64_t)g.N * g.H * g.W * g.C;
+    if (M > 8192) return false;
+    if (M > 4096) {
+        if (pixels > (4 << 20) || M * n * r > 3500000000ll || M * m > 10000000) return false;
+    } else if (M > 2048) {
+        if (M * n * r > 7500000000ll || M * n > 40000000 || M * pixels > (r >= 256 ? 110000000000ll : 60000000000ll)) return false;
+    }
     return lr_small_conv_supports(conv_shape(g), M, (int)m, (int)r);
 }
 SmallBwd small_conv_bwd(const abt_conv_geom& g, const void* dY, const void* act, const void* T, const void* B, const void* dAct, const void* dA,

@@ -138,3 +138,23 @@ def test_which_backward_a_linear_layer_takes(M, m, n, r, few):
     finally:
         abt.set_chain_parts(prev)
     assert rel(got, want.double()) < 1e-5 and torch.equal(got, want) != few
+
+
+# the same for convolutions: rows, products, columns of the patch matrix, pixels, products with A
+@pytest.mark.parametrize("N,side,C,kh,stride,m,r,few", [(1, 45, 512, 3, 1, 64, 384, True), (20, 14, 576, 3, 1, 64, 384, False), (20, 14, 512, 3, 1, 64, 192, True),
+                                                        (20, 14, 1024, 3, 1, 64, 32, True), (1, 60, 1344, 3, 1, 64, 128, False), (83, 14, 1024, 1, 2, 64, 64, False),
+                                                        (187, 7, 2048, 1, 2, 64, 64, True), (256, 7, 2048, 1, 2, 64, 192, False), (256, 7, 2048, 1, 2, 64, 256, True),
+                                                        (2, 57, 64, 3, 1, 1472, 160, True), (2, 57, 64, 3, 1, 1600, 160, False), (169, 7, 64, 3, 1, 64, 64, False)])
+def test_which_backward_a_convolution_takes(N, side, C, kh, stride, m, r, few):
+    g = torch.Generator(device="cuda").manual_seed(N + C + r)
+    rn = lambda std, *s: (torch.randn(s, generator=g, device="cuda") * std).to(BF)
+    rows = N * (-(-side // stride)) ** 2
+    act, A, B, dY, T = rn(1, N, side, side, C), rn(r ** -0.5, m, r), rn(0.01, r, kh * kh * C), rn(1e-2, rows, m), rn(1, rows, r)
+    dA = lambda: abt.lr_conv_bwd(dY, act, T, A, B, kh, kh, stride=stride, need_dAct=False, need_dB=False)[1]
+    got = dA()
+    prev = abt.set_chain_parts(1)
+    try:
+        want = dA()
+    finally:
+        abt.set_chain_parts(prev)
+    assert rel(got, want.double()) < 1e-5 and torch.equal(got, want) != few
