@@ -139,25 +139,39 @@ bool narrow_chain(const ChainProblem* problems, int n, int of, int64_t M, int p,
     return true;
 }
 
-// Where the chain runs as two products, T and then Y (forward, us, the fused kernels / two products):
-//   Few rows (of all problems together), too few row blocks for the chip.  768 -> 2304: r = 32 197 rows 8.2 / 7.1, 4000 14.0 / 14.3; r = 96 11.7 / 7.3,
-//     16.3 / 15.4, 8192 rows 20.4 / 23.2; r = 192 4000 24 / 21, 8192 28 / 26; r = 384 37.7 / 9.1, 39 / 25, 42 / 39.  3072 -> 768: r = 96 197 rows 19.3 /
-//     10.5, 4000 22 / 17, 8192 24 / 25; r = 192 31 / 22, 31 / 33; r = 384 39 / 12, 43 / 33, 48 / 48.  More rows at r = 256, and above where the wide
-//     side is Y: 3072 -> 768, r = 256 8192 rows 36 / 35, r = 320 42 / 47; 768 -> 3072, r = 320 46 / 42.  From an image, whose fused kernels wait longer:
-//     3 x 3 on 14 x 14 x 256, r = 64 20 images 23 / 13, 8036 rows 23 / 14, 12544 24 / 20, r = 192 26 / 13, 27 / 25, 28 / 35.
-//     A second launch costs the host 3.5 us, so not where the fused kernel is soon done: whole step of forward and backward, 768 -> 2304, 197 rows, fused /
-//     two products r = 32 25.8 / 29.6, r = 96 26.6 / 30.4, r = 128 30.3 / 30.2, r = 192 33.0 / 30.2, 2000 rows r = 64 34 / 33, r = 96 37.6 / 35.3, r = 128 40 / 34; 3072 ->
-//     768, 197 rows r = 32 25 / 30, r = 64 27 / 30, r = 96 30 / 30, r = 128 34 / 30, 2000 rows r = 32 32 / 30, r = 64 35 / 30.  (Forward alone, 64 ->
-//     64, r = 96 5.3 / 6.2, r = 384 10.7 / 7.6; 64 -> 1920, r = 192 6.8 / 6.9, r = 256 25 / 7; 256 -> 1024, r = 128 7.9 / 6.4.)
-//   At r = 224, 288 and 352, whose fused kernel is that of the next wider rank in 128-row work-groups, up to 10240 rows: 768 -> 2304, r = 224 3000 rows
-//     45 / 20, 8192 45 / 31, 12608 48 / 44, 16384 48 / 54; 3072 -> 768, r = 352 70 / 32, 71 / 48, 73 / 74, 76 / 78; 64 -> 1920, r = 288 39 / 17,
-//     40 / 29, 41 / 39, 39 / 46.
+// Where the chain runs as two products, T and then Y (lr_small.hip), by the rows of all problems together.  Forward, us, the fused kernels /
+// two products.
+//   Too few row blocks for the chip, rows up to 4096, and 8192 where the fused kernel's row block takes longest (r = 256; above where Y is the wide
+//   side; from an image):
+//                               197 rows     4000         8192                                197 rows     4000       8192
+//     768 -> 2304   r = 32     8.2 / 7.1   14.0 / 14.3                3072 -> 768  r = 96   19.3 / 10.5   22 / 17   24 / 25
+//                   r = 96    11.7 / 7.3   16.3 / 15.4  20.4 / 23.2                r = 192               31 / 22   31 / 33
+//                   r = 192                  24 / 21      28 / 26                  r = 256                         36 / 35
+//                   r = 384   37.7 / 9.1     39 / 25      42 / 39                  r = 320                         42 / 47
+//     768 -> 3072   r = 320                               46 / 42                  r = 384    39 / 12    43 / 33   48 / 48
+//     3 x 3 on 14 x 14 x 256: r = 64 3920 rows 23 / 13, 8036 23 / 14, 12544 24 / 20;  r = 192 26 / 13, 27 / 25, 28 / 35.
+//   Not where the fused kernel is soon done, since a second launch costs the host 3.5 us: limits on the rank and on p r that fall with the rows.
+//     Forward and backward together, fused / two products:
+//     768 -> 2304  197 rows   r = 32 25.8 / 29.6, r = 96 26.6 / 30.4, r = 128 30.3 / 30.2 (p r = 98304), r = 192 33.0 / 30.2 (147456)
+//                  2000 rows  r = 64 34 / 33, r = 96 37.6 / 35.3 (73728), r = 128 40 / 34
+//     3072 -> 768  197 rows   r = 32 25 / 30, r = 64 27 / 30, r = 96 30 / 30, r = 128 34 / 30
+//                  2000 rows  r = 32 32 / 30 (98304), r = 64 35 / 30
+//     Above r = 192 the fused kernel takes long at any size but the smallest (forward, 64 -> 64, r = 384 10.7 / 7.6; 64 -> 1920, r = 256 25 / 7).
+//   Not for many rows of a short contraction and a very wide Y, which one work-group per row block writes from a T that it has at once:
+//     1088 -> 16320, 4096 rows, r = 96 43 / 48;  640 -> 8832, 8108 rows, r = 256 103 / 108;  384 -> 10432, 4096 rows, r = 96 23.5 / 23.1
+//     (1984 -> 15040, 4096 rows, r = 128 61 / 53;  832 -> 15808, 2048 rows, r = 128 36 / 31;  64 -> 16384, 4096 rows, r = 384 185 / 88).
+//   r = 224, 288 and 352, whose fused kernel is that of the next wider rank in 128-row work-groups, up to 10240 rows:
+//                             3000 rows   8192      12608     16384
+//     768 -> 2304  r = 224     45 / 20   45 / 31   48 / 44   48 / 54
+//     3072 -> 768  r = 352     70 / 32   71 / 48   73 / 74   76 / 78
+//     64 -> 1920   r = 288     39 / 17   40 / 29   41 / 39   39 / 46
 bool two_products(int64_t rows, int p, int q, int R, bool image) {
     if (g_chain_rows.load() != 0 || g_chain_parts.load() != 0) return false;
     const int64_t least = image ? (rows >= 2048 ? 36864 : rows >= 1024 ? 73728 : 147456) : (rows >= 2048 ? 73728 : rows >= 1024 ? 98304 : 147456);
     const bool small = R > 192 ? p + q >= 1024 : (int64_t)p * R >= least && (image || R >= 96 || rows >= 1024);
     const bool wide = R == 256 || (R > 256 && q >= 2 * p);
     const bool padded = R == 224 || R == 288 || R == 352;
+    if (!padded && !image && R <= 256 && rows > 2048 && q > 8192 && q >= 8 * p) return false;
     return small && rows <= (padded ? 10240 : image || wide ? 8192 : 4096);
 }
 // T needs a place, and not over the first operand, whose rows several work-groups read.

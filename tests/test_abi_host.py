@@ -61,6 +61,29 @@ def test_workspace_queries(lib):
     assert lib.ab_merge_workspace_bytes(0, 10, 10, 32, 32, 0) == 0
 
 
+def test_where_a_forward_wants_a_place_for_T(lib):
+    want = lambda *a: lib.lr_linear_fwd_wants_T(*a, abt.ABT_BF16)
+    # rows, of all groups; p r; ranks above 192; padded ranks
+    assert [want(1, M, 2304, 768, 192) for M in (197, 4096, 4097)] == [1, 1, 0]
+    assert [want(G, 500, 640, 768, 128) for G in (1, 2, 4, 8)] == [0, 0, 1, 1] and want(8, 513, 640, 768, 128) == 0
+    assert [want(1, 8192, m, n, r) for m, n, r in ((768, 3072, 256), (3072, 768, 320), (768, 3072, 320), (64, 960, 224), (64, 896, 224))] == [1, 1, 0, 1, 0]
+    assert [want(1, M, 768, 3072, 352) for M in (10240, 10241)] == [1, 0]
+    # a very wide Y of a short contraction
+    assert [want(1, M, m, n, r) for M, m, n, r in ((2048, 8256, 1024, 192), (2049, 8256, 1024, 192), (2049, 8256, 1088, 192), (4096, 8192, 512, 192),
+                                                   (4096, 8256, 1024, 320), (4096, 8256, 512, 352))] == [1, 0, 1, 1, 1, 1]
+    # refused shapes, fp32, a forced height
+    assert want(0, 197, 2304, 768, 384) == want(9, 197, 2304, 768, 384) == want(1, 197, 2300, 768, 384) == 0
+    assert lib.lr_linear_fwd_wants_T(1, 197, 2304, 768, 384, abt.ABT_F32) == 0
+    prev = abt.set_chain_rows(128)
+    try:
+        assert want(1, 197, 2304, 768, 384) == 0
+    finally:
+        abt.set_chain_rows(prev)
+    conv = lambda N, side, C, k, s, m, r: lib.lr_conv_fwd_wants_T(ctypes.byref(abt.ConvGeom(N, side, side, C, k, k, s)), m, r, abt.ABT_BF16)
+    assert [conv(N, 14, 256, 3, 1, 256, 64) for N in (1, 20, 41, 42)] == [1, 1, 1, 0]
+    assert conv(4, 7, 2048, 1, 1, 512, 128) == conv(3, 14, 1024, 1, 2, 64, 384) == 1 and conv(2, 6, 64, 3, 1, 64, 32) == conv(2, 6, 64, 2, 1, 64, 32) == 0
+
+
 def test_fp32_backward_workspace_holds_the_full_split(lib):
     # beside dT and T the partial sums of the split that fills the chip, whatever the static scratch array could hold
     need = lambda M, m, n, r: lib.lr_linear_bwd_workspace_bytes(M, m, n, r, abt.ABT_F32) - 2 * (M * r * 4 + 255) // 256 * 256
