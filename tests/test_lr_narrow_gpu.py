@@ -149,3 +149,45 @@ def test_convolution_gradients_between_one_and_two_work_groups_per_unit(N):
     dT = (dY.float() @ A.float()).to(BF).float()
     assert rel(host(dB), (dT.t() @ patches).cpu()) < TOL
     assert rel(host(dA), (dY.float().t() @ T.float()).cpu()) < TOL
+
+
+# More than 8192 output pixels, beyond the kernels for few pixels: the activation gradient with a window of several taps in this kernel,
+# parity by parity with stride 2 (a parity's window of the image in LDS, or gathered), and with stride 1.
+@pytest.mark.parametrize("N,H,W,C,m,r,kh,kw,stride", [
+    (34, 31, 33, 64, 64, 64, 3, 3, 2),       # odd sides, one block of 64 ranks: parities of 4, 2, 2 and 1 taps through windows in one launch
+    (34, 31, 33, 64, 64, 96, 3, 3, 2),       # two blocks of ranks with fewer than nine taps: gathered
+    (40, 29, 30, 64, 64, 64, 5, 3, 2),       # 3 + 2 taps by 1 + 2
+    (9, 63, 65, 192, 64, 64, 3, 3, 2),       # blocks of 192 channels
+    (34, 31, 31, 512, 64, 32, 3, 3, 2),      # four blocks of 128 channels x four parities: two launches
+    (2100, 3, 3, 64, 64, 64, 3, 3, 2),       # the odd pixels of tiny images, an image each: no window holds a row block's
+    (1100, 1, 15, 64, 64, 64, 3, 3, 2),      # height 1: two parities without a row
+    (150, 15, 16, 64, 64, 32, 1, 1, 2),      # 1 x 1: three parities without a tap
+    (60, 13, 11, 64, 64, 64, 5, 3, 1),       # stride 1, a window of 15 taps
+    (60, 12, 12, 320, 64, 160, 3, 3, 1),     # three blocks of ranks, channel blocks of 160
+])
+def test_many_pixels_against_the_kernels_for_all_ranks(N, H, W, C, m, r, kh, kw, stride):
+    assert N * -(-H // stride) * -(-W // stride) > 8192
+    g = torch.Generator(device="cuda").manual_seed(N + H + C + r)
+    rn = lambda std, *s: (torch.randn(s, generator=g, device="cuda") * std).to(BF)
+    act, A, B = rn(1, N, H, W, C), rn(r ** -0.5, m, r), rn((kh * kw * C) ** -0.5, r, kh * kw * C)
+    dY = rn(1e-2, N * -(-H // stride) * -(-W // stride), m)
+
+    def step():
+        Y, T = abt.lr_conv_fwd(act, A, B, kh, kw, stride=stride)
+        return (Y, T) + tuple(abt.lr_conv_bwd(dY, act, T, A, B, kh, kw, stride=stride))
+
+    got = step()
+    prev = abt.set_chain_rows(64)
+    try:
+        want = step()
+    finally:
+        abt.set_chain_rows(prev)
+    for name, a, b in zip(("Y", "T", "dAct", "dA", "dB"), got, want):
+        assert rel(host(a), host(b)) < TOL_ORDER, name
+    assert torch.equal(got[2] == 0, want[2] == 0)
+    # dAct itself, in fp32 from the same dT: the sum over taps of shifted products
+    dT = (dY.float() @ A.float()).to(BF).float().view(N, -(-H // stride), -(-W // stride), r)
+    dAct = torch.nn.functional.conv_transpose2d(dT.permute(0, 3, 1, 2).cpu(), B.float().cpu().view(r, kh, kw, C).permute(0, 3, 1, 2),
+                                                stride=stride, padding=(kh // 2, kw // 2),
+                                                output_padding=((H - 1) % stride, (W - 1) % stride)).permute(0, 2, 3, 1)
+    assert rel(host(got[2]), dAct) < TOL
