@@ -822,10 +822,15 @@ hipError_t launch_chain_128(const Ch2Ptrs& ptrs, int G, bool second_stage,
                             int64_t M, int p, int q, int R, int t_pitch, const Ch2Gather& gg, int parts, hipStream_t s) {
     switch (R) {
 #define ABT_CASE(RR) case RR: return launch_chain_r<RR, 2, GATHER>(ptrs, G, second_stage, M, p, q, t_pitch, gg, parts, s);
-        ABT_CASE(32) ABT_CASE(64) ABT_CASE(96) ABT_CASE(128) ABT_CASE(192) ABT_CASE(384)
+        ABT_CASE(32) ABT_CASE(64) ABT_CASE(96) ABT_CASE(128)
 #undef ABT_CASE
-        default: return hipErrorInvalidValue;
+        // (a plain operand at these ranks: the kernel of eight equal waves)
+#define ABT_CASE(RR) case RR: if constexpr (GATHER) return launch_chain_r<RR, 2, GATHER>(ptrs, G, second_stage, M, p, q, t_pitch, gg, parts, s); else break;
+        ABT_CASE(192) ABT_CASE(384)
+#undef ABT_CASE
+        default: break;
     }
+    return hipErrorInvalidValue;
 }
 
 Ch2Ptrs one_problem(const void* Xin, const void* P, const void* Q, void* Yout, void* Tout) {

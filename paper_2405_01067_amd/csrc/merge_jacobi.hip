@@ -18,14 +18,14 @@
 // product taken as (Q^T P^T) the result tile comes out of the matrix core in that same layout, so
 // the update is in place.  Step 1 needs the transposed operand order (contraction over rows); each
 // wave passes its row tiles through a private 4 KB LDS tile for that.
-#include <type_traits>
-
 //
 // What bounds it: a round is one dependent chain.  K = 384, cycles of a work-group: panel load 3400 alone, 7000 to 10000 with 576
 // of them (nothing survives in L2 from the round before), Gram matrix 3000 (6500 with the tiles inside the blocks), rotations 14000 of which Q
 // 2000, update 6400 (fp64 matrix instructions), store 2000, and some 10000 between the end of a round and the start of
 // the next.  Sweeps of config 5 (48 cores of 384, 8 sweeps): 6.07 ms before the rotations moved to registers, 4.97 after,
 // 4.60 with the kept diagonal tiles; 16 cores of 768, 9 sweeps: 17.5, 16.7, 16.2 ms (one work-group per compute unit, 384 of them).
+#include <type_traits>
+
 #include "merge_internal.h"
 
 namespace abt {
