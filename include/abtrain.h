@@ -16,8 +16,9 @@
  *   - Unless a parameter is documented as a HOST pointer it is a DEVICE pointer owned by the
  *     caller; the library never allocates, frees or retains caller memory.
  *   - `stream` is a hipStream_t passed as void* (NULL = the default stream).  lr_linear_fwd,
- *     lr_linear_bwd, lr_linear_bwd_static, lr_linear_fwd_grouped, lr_linear_bwd_grouped, lr_conv_fwd, lr_conv_bwd, ab_adamw_step and ab_reconstruct enqueue work on it
- *     and return without synchronising the host.  Calls that DO block the host:
+ *     lr_linear_bwd, lr_linear_bwd_static, lr_linear_fwd_grouped, lr_linear_bwd_grouped, lr_conv_fwd, lr_conv_bwd,
+ *     ab_adamw_step and ab_reconstruct enqueue work on it and return without synchronising the host.  Calls that DO
+ *     block the host:
  *       ab_merge, ab_merge_batched, ab_factorize, ab_factorize_batched: once after uploading
  *         their layer tables, and from the third Jacobi sweep on once per sweep, for the copy of
  *         the convergence flags of the sweep BEFORE the one just enqueued (the host stays one

@@ -13,10 +13,9 @@ namespace {
 
 std::atomic<int> g_max_sweeps{30};
 
-// Chain kernel choice: the narrow-rank kernel where use_narrow / narrow_gather say so; else for large batches the
-// 128-row kernel where it supports the rank (32, 64, 96,
-// 128, 192); else the 64-row kernel with loader and MFMA waves wherever that supports the rank
-// (32, 64, 96, 128, 160, 192, 256, 320, 384), else the older kernel (224, 288, 352).
+// Chain kernel choice: two products where two_products says so; else the narrow-rank kernel where use_narrow / narrow_gather do; else
+// by choose_chain_shape work-groups of 128 rows (r = 32, 64, 96, 128, and 192 to 384 in the kernel of eight equal waves; from an image 192 and
+// 384 too) or of 64 rows with loader and MFMA waves (r = 32, 64, 96, 128, 160, 192, 256, 320, 384).
 std::atomic<int> g_chain_rows{0};    // 0: automatic; 64 or 128: force that work-group height where the rank allows it
 std::atomic<int> g_chain_parts{0};   // 0: automatic; n: force n column parts for 128-row work-groups
 

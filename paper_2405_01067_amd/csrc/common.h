@@ -159,10 +159,10 @@ hipError_t launch_chain4_bf16(const ChainProblem* problems, int G, int64_t M, in
 struct ChainGather { int H, W, Cin, cpb, kh, kw, sign, cy, cx, RH, RW, mul, omul, oy, ox, OH, OW; };   // cpb: set by the launcher
 struct GatherProblem { const void* image; const void* P; const void* Q; void* Yout; void* Tout; int64_t M; ChainGather g; };
 // Does it read this image through a window in LDS?  Two taps or more, stride 1; one block of 64 channels, or several with nine taps;
-// the pixels that a row block's patches touch at most as window_fits says; R = 128 with one block: 192 (three work-groups share a compute
-// unit up to 168, two beyond, as against three of the gathered form; forward, us, window / gathered: 31 x 31 x 64, 64387 rows, 192 pixels 19.1 / 22.7,
-// 56 x 56 x 64, batch 64, 242 pixels 57 / 55); not wide results of 32 channels,
-// the other half of whose slabs is zeros (activation gradient of 28 x 28 x 128, r = 32, batch 256 61 / 58).
+// no more pixels touched by a row block's patches than window_fits allows, and at R = 128 with one block no more than 192 (three
+// work-groups share a compute unit up to 168, two beyond; the gathered form has three; forward, us, window / gathered:
+// 31 x 31 x 64, 64387 rows, 192 pixels 19.1 / 22.7, 56 x 56 x 64, batch 64, 242 pixels 57 / 55); not wide results of 32
+// channels, the other half of whose slabs is zeros (activation gradient of 28 x 28 x 128, r = 32, batch 256 61 / 58).
 bool chain4_window(const ChainGather& g, int R, int rows);
 hipError_t launch_chain4_gather_bf16(const GatherProblem* problems, int n, int q, int R, int t_pitch, int rows, int parts, hipStream_t s);
 // dst[c, r] = src[r, c] for a bf16 matrix of `rows` x `cols`.

@@ -430,8 +430,9 @@ __global__ __launch_bounds__(64 * kGradWaves, 2) void small_grad_kernel(SmallGra
     else if (64 * (kGradWaves * c + wave) < p.n) dx_tile<false>(p, rb, kGradWaves * c + wave, nullptr);
 }
 
-// The gradients of a convolution, one launch for what were four or five (copy of B, dAct, dA, dB and the sums of its parts: 14 x 14 x 256, 3 x 3, r = 64,
-// 4 images 38 us, 12 here, most of it latency as above; M up to 16384 rows for the offsets in LDS): dAct [N, H, W, C] = the sum over taps of dT (shifted) . B, without a re-laid-out copy of B; dA and dB as above.
+// The gradients of a convolution: dAct [N, H, W, C] = the sum over taps of dT (shifted) . B, without a re-laid-out copy of B; dA and dB as
+// above.  One launch for what are four or five elsewhere (copy of B, dAct, dA, dB and the sums of its parts).  Bound by latency as above: 14 x 14 x
+// 256, 3 x 3, r = 64, 4 images, whole backward 38 us in the other kernels, 12 here.  M up to 16384 rows, whose offsets fit the LDS.
 struct SmallConvGrad {
     const uint16_t* dT; const uint16_t* B; uint16_t* dAct;
     SmallConv cv;
