@@ -435,19 +435,22 @@ hipError_t conv_chain(const void* act, const abt_conv_geom& g, const void* A, co
 //   768 x 3072    r = 32, 197 rows 17 / 10, 4000 rows 34 / 25
 //   64 x 64       r = 96, 197 rows 16 / 9, 2000 rows 22 / 15, 4000 rows 21 / 22: the smallest layers up to 2048 rows
 // Their products take no operand through LDS, so with many of them the others win, the more so where those run as two products.
-// dY is read twice, for dT and for dA, so m counts three halves of n:
+// dY is read twice, for dT and for dA, so m counts three halves of n; fewer gradients leave room for more rows:
 //   3072 x 768    4096 rows r = 192 51 / 52, r = 256 56 / 61, r = 384 76 / 87;  2500 rows r = 320 55 / 59
 //   1024 x 4096   4096 rows r = 192 55 / 57, r = 384 79 / 98
 //   1920 x 1920   3000 rows r = 192 45 / 44, r = 256 50 / 54;  4096 rows r = 320 67 / 81
 //   4096 x 4096   2048 rows r = 384 80 / 97, 4096 rows 114 / 170;  4096 rows r = 96 59 / 58
+//   dX and dA     768 x 3072, 4055 rows, r = 352 and T again 83 / 76;  3072 x 768, r = 384 2491 rows 57 / 60, 4096 rows 71 / 83
+//   dX and dB     2304 x 768, 3066 rows, r = 384 54 / 47;  768 x 3072, 4055 rows, r = 352 64 / 69
 // Wide dX of a short contraction, stored in 4-byte pieces, where the rank makes it more than latency:
 //   64 x 16384    1024 rows r = 96 34 / 37, r = 192 43 / 55;  64 x 8192, 2048 rows r = 192 37 / 29
 // dT, one work-group per 32 rows and 64 columns, whose eight waves share out all of m:
 //   8192 x 2048   197 rows r = 96 34 / 41, r = 384 46 / 56;  6464 x 1664, 161 rows r = 96 29 / 32
 // but where dT would otherwise come from the fused kernel (few rows at r = 32 and 64), longer by one that waits for less:
 //   8192 x 512    197 rows r = 64 40 / 32;  16384 x 64 r = 32 48 / 60;  8320 x 7232, 175 rows r = 32 64 / 34
-bool few_rows(int64_t M, int64_t m, int64_t n, int64_t r) {
-    if (M > (m + n >= 1024 ? 4096 : 2048) || M * r * (3 * m + 2 * n) > 8500000000ll) return false;
+bool few_rows(int64_t M, int64_t m, int64_t n, int64_t r, bool dA, bool dB) {
+    const int64_t work = M * r * ((dA ? 30 : 24) * m + (!dB ? 10 : dA ? 20 : 19) * n);
+    if (M > (m + n >= 1024 ? 4096 : 2048) || work > 85000000000ll) return false;
     if (r >= 96 && n >= 16 * m && M * n * r > 2500000000ll) return false;
     if (m > 7168 && (r >= 96 || M >= 1024 || (m > (r == 32 ? 8192 : 12288) && 2 * n < m))) return false;
     return lr_small_supports(M, (int)m, (int)n, (int)r);
@@ -455,7 +458,7 @@ bool few_rows(int64_t M, int64_t m, int64_t n, int64_t r) {
 SmallBwd small_bwd(const void* dY, const void* X, const void* T, const void* B, const void* dX, const void* dA, const void* dB,
                    int64_t M, int64_t m, int64_t n, int64_t r) {
     if (g_chain_rows.load() != 0 || g_chain_parts.load() != 0) return kNotSmall;
-    if (!few_rows(M, m, n, r)) return kNotSmall;
+    if (!few_rows(M, m, n, r, dA != nullptr, dB != nullptr)) return kNotSmall;
     auto over = [&](const void* out, int64_t bytes) {
         return (dA && (overlap(out, bytes, dY, M * m * 2) || overlap(out, bytes, T, M * r * 2))) || (dB && overlap(out, bytes, X, M * n * 2)) ||
                (dX && overlap(out, bytes, B, r * n * 2));
