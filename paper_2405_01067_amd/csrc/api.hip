@@ -449,8 +449,8 @@ hipError_t conv_chain(const void* act, const abt_conv_geom& g, const void* A, co
 // but where dT would otherwise come from the fused kernel (few rows at r = 32 and 64), longer by one that waits for less:
 //   8192 x 512    197 rows r = 64 40 / 32;  16384 x 64 r = 32 48 / 60;  8320 x 7232, 175 rows r = 32 64 / 34
 bool few_rows(int64_t M, int64_t m, int64_t n, int64_t r, bool dA, bool dB) {
-    const int64_t work = M * r * ((dA ? 30 : 24) * m + (!dB ? 10 : dA ? 20 : 19) * n);
-    if (M > (m + n >= 1024 ? 4096 : 2048) || work > 85000000000ll) return false;
+    if (M > (m + n >= 1024 ? 4096 : 2048)) return false;
+    if (M * r * ((dA ? 30 : 24) * m + (!dB ? 10 : dA ? 20 : 19) * n) > 85000000000ll) return false;
     if (r >= 96 && n >= 16 * m && M * n * r > 2500000000ll) return false;
     if (m > 7168 && (r >= 96 || M >= 1024 || (m > (r == 32 ? 8192 : 12288) && 2 * n < m))) return false;
     return lr_small_supports(M, (int)m, (int)n, (int)r);

@@ -92,3 +92,24 @@ def test_some_groups_compute_T_again(G, M, m, n, r):
         again = abt.lr_linear_bwd_grouped([dict(e, T=None if i in without else e["T"], dA=True) for i, e in enumerate(groups)])
         for a, b in zip(again, kept):
             assert torch.equal(a[1], b[1])
+
+
+@pytest.mark.parametrize("M", [205, 5000])
+def test_a_captured_forward_without_T(M):
+    # the place for T comes from the graph's own memory: several replays, the program's work in between
+    X, A, B, _ = layer(M, 2304, 768, 192)
+    want = abt.lr_linear_fwd(X, A, B)[0]
+    Y = torch.empty_like(want)
+    abt.lr_linear_fwd(X, A, B, save_T=False, Y=Y)
+    graph, side = torch.cuda.CUDAGraph(), torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.graph(graph, stream=side):
+        abt.lr_linear_fwd(X, A, B, save_T=False, Y=Y)
+    for k in range(3):
+        Y.zero_()
+        if k == 2:
+            X.mul_(2)                                    # exact in bf16, and in every product and sum
+            want = want * 2
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(Y, want)
