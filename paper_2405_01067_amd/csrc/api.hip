@@ -173,12 +173,48 @@ bool two_products(int64_t rows, int p, int q, int R, bool image) {
     if (!padded && !image && R <= 256 && rows > 2048 && q > 8192 && q >= 8 * p) return false;
     return small && rows <= (padded ? 10240 : image || wide ? 8192 : 4096);
 }
+// Where the chain runs as the two products for many rows (lr_pair.hip), by the rows of all problems together.  Forward, us, the other kernels /
+// these, on a card that keeps what fits in the last-level cache between the calls:
+//   More than 32768 rows, where the fused kernels' 128-row work-groups need a second round (mean of old / new over all shapes 1.15):
+//                          r = 64        r = 96        r = 128       r = 192       r = 384
+//     768 -> 3072  36000   60 / 57       67 / 59       76 / 63       94 / 71       149 / 127
+//                  50432   84 / 80       97 / 87       115 / 93      116 / 91      175 / 160
+//     3072 -> 768  36000   59 / 53       71 / 57       88 / 65       94 / 73       149 / 116
+//                  50432   82 / 74       93 / 78       112 / 92      115 / 104      188 / 175
+//     768 -> 768   36000   31 / 31       33 / 31       39 / 34       51 / 38       71 / 61
+//     Narrow ranks and layers gain least, and lose below the limits here (64 -> 640, 49000 rows, r = 288 32 / 42).  From 114688 rows on the
+//     rounds are many and even: from r = 160 on nothing to gain (768 -> 3072, 150000 rows, r = 384 430 / 452; r = 96 277 / 240).
+//   r = 288 and 352 from 10240 rows on, where the fused kernel is that of the next wider rank in 128-row work-groups (768 -> 3072, 12000
+//     rows, r = 288 66 / 40; 16384: even with it from there on); r = 160, whose fused kernel has 64-row work-groups (768 -> 3072, 25000 rows 69 / 53).
+//   Wide results of short contractions, where a fused work-group's time is the stores of Y: 4096 to 10240 rows (768 -> 3072, r = 192, 6000 rows
+//     31 / 24) and, less, 16384 to 22528 (20000 rows 54 / 44).  Between them one round of 64-row work-groups fills the chip (14000 rows 39 / 42).
+bool wide_products(int64_t rows, int p, int q, int R) {
+    if (g_chain_rows.load() != 0 || g_chain_parts.load() != 0 || rows <= 4096 || p < 256 || q < 128) return false;
+    if (rows > 32768) {
+        if (R >= 160) return rows <= 114688 && p + q >= (rows <= 49152 ? 704 : 1536);
+        if (R == 128) return rows <= 49152 ? p >= 1024 || q > 1024 : p + q >= 3072;
+        if (R == 96) return q >= 2304 || p >= 3072 || (rows <= 40960 && p >= 512 && q >= 512 && p + q >= 1280);
+        return R == 64 && q >= 2304;
+    }
+    if ((R == 288 || R == 352) && rows > 10240 && rows <= 16384) return p + q >= 1280;
+    if (R == 160 && rows > 16384) return q >= 512 && p + q >= 1472;
+    if (rows <= 8192 && R >= 96 && R <= 192) return q >= 1024 && p <= 1920;
+    if (rows <= 10240) return ((R >= 64 && R <= 192) || R == 288) && q >= 1344 && q >= 2 * p;
+    return rows > 16384 && rows <= 22528 && R >= 64 && q >= 1344 && 2 * q >= 5 * p;
+}
 // T needs a place, and not over the first operand, whose rows several work-groups read.
-bool two_products(const ChainProblem* problems, int n, int of, int64_t M, int p, int q, int R) {
-    if (!two_products(of * M, p, q, R, false) || !lr_small_supports(M, q, p, R)) return false;
+bool place_for_T(const ChainProblem* problems, int n, int64_t M, int p, int R) {
     for (int g = 0; g < n; ++g)
         if (!problems[g].Tout || overlap(problems[g].Xin, M * p * 2, problems[g].Tout, M * R * 2)) return false;
     return true;
+}
+bool two_products(const ChainProblem* problems, int n, int of, int64_t M, int p, int q, int R) {
+    if (!two_products(of * M, p, q, R, false) || !lr_small_supports(M, q, p, R)) return false;
+    return place_for_T(problems, n, M, p, R);
+}
+// Does a forward of these rows go faster with a place for T?
+bool place_pays(int64_t rows, int64_t M, int p, int q, int R) {
+    return (wide_products(rows, p, q, R) && pair_supports(M, p, q, R)) || (two_products(rows, p, q, R, false) && lr_small_supports(M, q, p, R));
 }
 
 // From an image: a lane has one pixel for the whole kernel, while the loader waves of the other kernels compute
@@ -223,6 +259,8 @@ hipError_t chain_gather(const void* image, const PatchGeom& g, const void* P, co
 hipError_t chain(const void* Xin, const void* P, const void* Q, void* Yout, void* Tout,
                  int64_t M, int p, int q, int R, hipStream_t s) {
     const ChainProblem one{Xin, P, Q, Yout, Tout};
+    if (wide_products(M, p, q, R) && pair_supports(M, p, q, R) && place_for_T(&one, 1, M, p, R))
+        return launch_pair_bf16(&one, 1, 1, M, p, q, R, s);
     if (two_products(&one, 1, 1, M, p, q, R)) return launch_lr_small_fwd(&one, 1, 1, M, p, q, R, s);
     hipError_t e;
     if (narrow_chain(&one, 1, 1, M, p, q, R, s, &e)) return e;
@@ -637,7 +675,7 @@ int lr_conv_fwd_wants_T(const abt_conv_geom* geom, int64_t m, int64_t r, int dt)
     if (check_conv(geom, m, r, dt) != ABT_OK) return 0;
     const abt_conv_geom& g = *geom;
     const int64_t M = conv_rows(g);
-    if (as_matrix(g, M, r)) return two_products(M, (int)g.C, (int)m, (int)r, false) && lr_small_supports(M, (int)m, (int)g.C, (int)r);
+    if (as_matrix(g, M, r)) return place_pays(M, M, (int)g.C, (int)m, (int)r);
     return two_products(M, g.kh * g.kw * (int)g.C, (int)m, (int)r, true) && lr_small_gather_supports(conv_patches_geom(g), M, (int)m, (int)r);
 }
 
@@ -796,7 +834,7 @@ size_t lr_linear_fwd_workspace_bytes(int64_t M, int64_t m, int64_t n, int64_t r,
 
 int lr_linear_fwd_wants_T(int G, int64_t M, int64_t m, int64_t n, int64_t r, int dt) {
     if (G < 1 || G > ABT_MAX_GROUPS || dt != ABT_BF16 || check_lr_shapes(M, m, n, r, dt) != ABT_OK) return 0;
-    return two_products(G * M, (int)n, (int)m, (int)r, false) && lr_small_supports(M, (int)m, (int)n, (int)r);
+    return place_pays(G * M, M, (int)n, (int)m, (int)r);
 }
 
 size_t lr_linear_bwd_workspace_bytes(int64_t M, int64_t m, int64_t n, int64_t r, int dt) {
@@ -966,7 +1004,10 @@ hipError_t chain_grouped(const ChainProblem* pr, int G, int64_t M, int p, int q,
         if (n == 0) continue;
         hipError_t e;
         const int of = again ? G : n;
-        if (two_products(sel, n, of, M, p, q, R)) {
+        // (the rule and the split of the rows are those of all groups: the order of the sums of T is the same for some of them)
+        if (wide_products(G * M, p, q, R) && pair_supports(M, p, q, R) && place_for_T(sel, n, M, p, R)) {
+            e = launch_pair_bf16(sel, n, G, M, p, q, R, s);
+        } else if (two_products(sel, n, of, M, p, q, R)) {
             e = launch_lr_small_fwd(sel, n, of, M, p, q, R, s);
         } else if (!narrow_chain(sel, n, of, M, p, q, R, s, &e)) {
             e = launch_chain2_grouped_bf16(sel, n, M, p, q, R, chain_rows_for_groups(of, M, p, q, R), 1, s);

@@ -182,6 +182,11 @@ hipError_t launch_tn_bf16(const TnJob* jobs, int njobs, int64_t M, int R, int ac
 // out (+)= sums, which lie end to end in the order of the jobs (their operands are not looked at)
 hipError_t launch_tn_finish(const TnJob* jobs, int njobs, int R, int accumulate, const float* sums, hipStream_t s);
 
+// The chain of many rows as two products (lr_pair.hip), T and Y or T alone (Yout NULL, for all problems or none); Tout must have a place that lies
+// over no input.  The rows per work-group are those of a launch of `of` problems (at least G).
+bool pair_supports(int64_t M, int p, int q, int R);
+hipError_t launch_pair_bf16(const ChainProblem* problems, int G, int of, int64_t M, int p, int q, int R, hipStream_t s);
+
 // 32-bit offsets: M, m, n and r against each other
 bool lr_small_supports(int64_t M, int m, int n, int r);
 // The chain for few rows as two products, T and Y or T alone (Yout NULL, for all problems or none); Tout must have a place that lies over no input.
