@@ -15,8 +15,8 @@
 // Measured: 4096 x 4096 x 1024 279 us = 123 TFLOP/s of the 133 that a large library product reaches;
 // 768 x 3072 x 384 (W = A B of a ViT-B/16 MLP layer) 26 us, 79 us in an earlier form with 128 x 128 tiles
 // and 4-byte loads one slab ahead; the products of a factored layer at M = 3152, m = 3072, n = 768,
-// r = 192: T 17 us, Y 47, dT 47, dX 17, dA 52, dB 23; forward and backward together 1.95 ms -> 228 us,
-// of the 64 x 256 x 256 layer at r = 32 151 -> 40 us.
+// r = 192: T 15 us, Y 52, dT 55, and dX, dA and dB in one launch 64 and 7; forward and backward together 175 us,
+// of the 64 x 256 x 256 layer at r = 32 26 us.
 //
 // LDS: both operands lie [row][k], 16-byte chunks of four k XOR-swizzled by the row; an operand read is
 // one 16-byte read for four matrix instructions: instruction i of a group of eight k takes k = 4 h + i
@@ -37,7 +37,7 @@ constexpr int NT = 256;
 
 struct GemmF32Dev {
     GemmF32 d;
-    int tile_begin;      // first tile of this problem in the launch
+    int begin;           // problems in the kernel arguments: first slot of an XCD's share; in a table: first tile
     int tiles_q, tiles;  // tiles per row of tiles, tiles of one split
     int splits, k_split; // splits of the contraction, columns of each (a multiple of 64)
     float* part;         // splits > 1: partial sums [split][P][Q]
@@ -136,9 +136,8 @@ struct GemmF32Args { GemmF32Dev g[kGemmArgs]; };
 
 // The work of one tile; KCA, KCB: k is the fast index of A / B in memory.
 template <class C, bool VEC, bool KCA, bool KCB>
-__device__ __forceinline__ void gemm_tile(const GemmF32Dev& g, int tile, float* lds) {
+__device__ __forceinline__ void gemm_tile(const GemmF32Dev& g, int local, float* lds) {
     const GemmF32& d = g.d;
-    int local = tile - g.tile_begin;
     const int split = local / g.tiles;
     local -= split * g.tiles;
     const int i0 = (local / g.tiles_q) * C::TM;
@@ -284,25 +283,32 @@ __device__ __forceinline__ void gemm_tile(const GemmF32Dev& g, int tile, float* 
 }
 
 template <class C, bool VEC>
-__global__ __launch_bounds__(NT, 3) void gemm_f32_kernel(const GemmF32Dev* __restrict__ table, GemmF32Args args, int ndesc, int ntiles) {
+__global__ __launch_bounds__(NT, 3) void gemm_f32_kernel(const GemmF32Dev* __restrict__ table, GemmF32Args args, int ndesc) {
     __shared__ __align__(16) float lds[C::lds_floats];
-    // Tiles are numbered problem by problem; block b works on tile (b % 8) * (grid / 8) + b / 8, so each
-    // XCD (block index modulo 8) gets a contiguous eighth of the list and the tiles of one problem
-    // share their operand panels through one L2.  The grid is the tile count rounded up to 8.
-    const int tile = (int)(blockIdx.x & 7) * (int)(gridDim.x >> 3) + (int)(blockIdx.x >> 3);
-    if (tile >= ntiles) return;
+    // Block b runs on XCD b % 8.  A few problems: every XCD gets a contiguous eighth of the tiles of each, which share their operand panels through
+    // one L2; problems of unlike contractions weigh the same on every XCD then (an eighth of the whole list instead left two thirds
+    // of the work of the joint launch of dA, dB and dX to three of them: 124 us against 64, 3152 x 3072 x 768, r = 192).  A table of
+    // many: an eighth of the list, whole problems for the most part (96 back-projections of a merge 294 us, 380 the other way).
+    const int slot = (int)(blockIdx.x >> 3), xcd = (int)(blockIdx.x & 7);
     GemmF32Dev g;
+    int tile;
     if (table == nullptr) {
         int i = 0;
-        while (i + 1 < ndesc && args.g[i + 1].tile_begin <= tile) ++i;
+        while (i + 1 < ndesc && args.g[i + 1].begin <= slot) ++i;
         g = args.g[i];
+        const int all = g.tiles * g.splits;
+        tile = xcd * ((all + 7) >> 3) + slot - g.begin;
+        if (tile >= all) return;
     } else {
+        const int at = xcd * (int)(gridDim.x >> 3) + slot;
         int lo = 0, hi = ndesc - 1;
-        while (lo < hi) {  // last descriptor whose tile_begin <= tile
+        while (lo < hi) {  // last descriptor whose first tile is not beyond
             int mid = (lo + hi + 1) >> 1;
-            if (table[mid].tile_begin <= tile) lo = mid; else hi = mid - 1;
+            if (table[mid].begin <= at) lo = mid; else hi = mid - 1;
         }
         g = table[lo];
+        tile = at - g.begin;
+        if (tile >= g.tiles) return;
     }
     if (g.d.transA) {
         if (g.d.transB) gemm_tile<C, VEC, false, true>(g, tile, lds);
@@ -338,10 +344,10 @@ bool vec_ok(const GemmF32& d) {
     return ok(d.A, d.lda, d.transA ? d.P : d.K) && ok(d.B, d.ldb, d.transB ? d.K : d.Q);
 }
 
-GemmF32Dev describe(const GemmF32& d, int tm, int tn, int tile_begin, int splits) {
+GemmF32Dev describe(const GemmF32& d, int tm, int tn, int begin, int splits) {
     GemmF32Dev g{};
     g.d = d;
-    g.tile_begin = tile_begin;
+    g.begin = begin;
     g.tiles_q = (int)ceil_div(d.Q, tn);
     g.tiles = tiles_of(d, tm, tn);
     g.k_split = (int)ceil_div(ceil_div(d.K, splits), 64) * 64;
@@ -349,12 +355,14 @@ GemmF32Dev describe(const GemmF32& d, int tm, int tn, int tile_begin, int splits
     return g;
 }
 
-void launch_form(bool small, bool vec, int tiles, const GemmF32Dev* table, const GemmF32Args& a, int n, hipStream_t s) {
-    const dim3 grid((tiles + 7) / 8 * 8), block(NT);
-    if (small && vec) hipLaunchKernelGGL((gemm_f32_kernel<Small, true>), grid, block, 0, s, table, a, n, tiles);
-    else if (small) hipLaunchKernelGGL((gemm_f32_kernel<Small, false>), grid, block, 0, s, table, a, n, tiles);
-    else if (vec) hipLaunchKernelGGL((gemm_f32_kernel<Wide, true>), grid, block, 0, s, table, a, n, tiles);
-    else hipLaunchKernelGGL((gemm_f32_kernel<Wide, false>), grid, block, 0, s, table, a, n, tiles);
+int slots_of(const GemmF32Dev& g) { return (g.tiles * g.splits + 7) / 8; }
+
+void launch_form(bool small, bool vec, int slots, const GemmF32Dev* table, const GemmF32Args& a, int n, hipStream_t s) {
+    const dim3 grid(8 * slots), block(NT);
+    if (small && vec) hipLaunchKernelGGL((gemm_f32_kernel<Small, true>), grid, block, 0, s, table, a, n);
+    else if (small) hipLaunchKernelGGL((gemm_f32_kernel<Small, false>), grid, block, 0, s, table, a, n);
+    else if (vec) hipLaunchKernelGGL((gemm_f32_kernel<Wide, true>), grid, block, 0, s, table, a, n);
+    else hipLaunchKernelGGL((gemm_f32_kernel<Wide, false>), grid, block, 0, s, table, a, n);
 }
 
 // 64 x 64 tiles once they give every compute unit one; below that the 32 x 32 form (measured: 150 tiles of
@@ -392,21 +400,21 @@ hipError_t launch_gemm_f32(const GemmF32* p, const int* splits, int n, float* pa
     const bool small = use_small(wide_tiles);
     const int tm = small ? Small::TM : Wide::TM, tn = small ? Small::TN : Wide::TN;
     GemmF32Args a{};
-    int tiles = 0;
+    int slots = 0;
     int64_t largest = 0;
     char* part = (char*)partials;
     for (int i = 0; i < n; ++i) {
-        a.g[i] = describe(p[i], tm, tn, tiles, splits ? splits[i] : 1);
+        a.g[i] = describe(p[i], tm, tn, slots, splits ? splits[i] : 1);
         if (a.g[i].splits > 1) {
             if (!partials) return hipErrorInvalidValue;
             a.g[i].part = (float*)part;
             part += gemm_f32_partial_bytes(p[i], a.g[i].splits);
             if ((int64_t)p[i].P * p[i].Q > largest) largest = (int64_t)p[i].P * p[i].Q;
         }
-        tiles += a.g[i].tiles * a.g[i].splits;
+        slots += slots_of(a.g[i]);
     }
-    if (tiles <= 0) return hipSuccess;
-    launch_form(small, vec, tiles, nullptr, a, n, s);
+    if (slots <= 0) return hipSuccess;
+    launch_form(small, vec, slots, nullptr, a, n, s);
     if (any_split && largest > 0) {
         const int64_t blocks = ceil_div(largest, NT);
         hipLaunchKernelGGL(gemm_f32_reduce_kernel, dim3((unsigned)(blocks < 2048 ? blocks : 2048), n), dim3(NT), 0, s, a, n);
@@ -439,7 +447,7 @@ GemmF32Table gemm_f32_build_table(const GemmF32* descs_host, int n, void* host_i
 
 hipError_t launch_gemm_f32_table(const void* dev_image, const GemmF32Table& t, hipStream_t s) {
     if (t.n <= 0 || t.tiles <= 0) return hipSuccess;
-    launch_form(t.small, t.vec, t.tiles, (const GemmF32Dev*)dev_image, GemmF32Args{}, t.n, s);
+    launch_form(t.small, t.vec, (t.tiles + 7) / 8, (const GemmF32Dev*)dev_image, GemmF32Args{}, t.n, s);
     return hipGetLastError();
 }
 
