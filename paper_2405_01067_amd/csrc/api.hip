@@ -1304,13 +1304,10 @@ int ab_factorize(const float* W, int64_t m, int64_t n, float tau, int64_t k_fixe
 int ab_merge_info_batched(const void* workspace, int first, int count, int32_t* sweeps, int32_t* n_sigma, void* stream) {
     if (!workspace || first < 0 || count < 1) return ABT_EINVAL;
     return guarded([&]() -> int {
-        int layers = 0;
-        const hipError_t e = merge_layer_count(workspace, &layers, (hipStream_t)stream);
-        if (e == hipErrorInvalidValue) return ABT_EINVAL;       // not a merge workspace
+        std::vector<int32_t> info;                              // (not resized before the count has been checked)
+        const hipError_t e = merge_read_info(workspace, first, count, info, (hipStream_t)stream);
+        if (e == hipErrorInvalidValue) return ABT_EINVAL;       // not a merge workspace, or no such layers in it
         if (e != hipSuccess) return ABT_EHIP;
-        if (count > layers || first > layers - count) return ABT_EINVAL;       // no such layers in it
-        std::vector<int32_t> info(4 * (size_t)count);
-        if (merge_read_info(workspace, first, count, info.data()) != hipSuccess) return ABT_EHIP;
         bool converged = true;
         for (int i = 0; i < count; ++i) {
             if (sweeps) sweeps[i] = info[4 * i];

@@ -6,6 +6,8 @@
 #include <stddef.h>
 #include <stdint.h>
 
+#include <vector>
+
 #include "abtrain.h"
 
 namespace abt {
@@ -260,10 +262,9 @@ size_t merge_workspace_bytes(const abt_merge_desc* layers, int L);
 // identity: per layer the side whose (only) copy is the K x K identity, i.e. the layer is a dense weight; NULL: none
 enum class MergeSide : uint8_t { none, A, B };
 hipError_t merge_run(const abt_merge_desc* layers, const MergeSide* identity, int L, void* workspace, int max_sweeps, hipStream_t s);
-// Layers of the last merge on this workspace (waits for the stream); hipErrorInvalidValue: not a merge workspace.
-hipError_t merge_layer_count(const void* workspace, int* layers, hipStream_t s);
-// (sweeps, values, converged, rank) of `count` of its layers
-hipError_t merge_read_info(const void* workspace, int first, int count, int32_t* out);
+// (sweeps, values, converged, rank) of `count` layers of the last merge on this workspace (waits for the stream); hipErrorInvalidValue: not a
+// merge workspace, or no such layers in it.
+hipError_t merge_read_info(const void* workspace, int first, int count, std::vector<int32_t>& out, hipStream_t s);
 hipError_t launch_identity_f32(float* dst, int K, hipStream_t s);   // dst[K, K] = I
 // Stage timers of the batched merge: with the switch on, merge_run records events on the caller's
 // stream at its stage boundaries and merge_stage_ms waits for the last and returns the elapsed

@@ -46,36 +46,6 @@ struct CholMat {
     int K;
 };
 
-__device__ __forceinline__ double lane_value(double v, int src) {
-    const int lo = __builtin_amdgcn_readlane(__double2loint(v), src);
-    const int hi = __builtin_amdgcn_readlane(__double2hiint(v), src);
-    return __hiloint2double(hi, lo);
-}
-
-// Factor a 32 x 32 block in one wave: lane r (and r + 32) holds row r; step c takes the pivot and the
-// finished column c from the other lanes with lane reads (no LDS, no waits).  keep(c, 1 / pivot or 0).
-template <class F>
-__device__ __forceinline__ void factor_diagonal_block(double (&row)[32], int r, double floor_piv, F&& keep) {
-#pragma unroll
-    for (int c = 0; c < 32; ++c) {
-        const double d = lane_value(row[c], c);
-        const bool ok = d > floor_piv;
-        // 1 / sqrt(d): hardware estimate and two Newton steps (a square root and a division in
-        // fp64 would be several times the rest of the step); the pivot itself is d / sqrt(d)
-        const double dd = ok ? d : 1.0;
-        double y = __builtin_amdgcn_rsq(dd);
-        y = y * fma(-0.5 * dd, y * y, 1.5);
-        y = y * fma(-0.5 * dd, y * y, 1.5);
-        const double ip = ok ? y : 0.0;
-        const double piv = ok ? dd * y : 0.0;
-        const double v = (r == c) ? piv : (r > c ? row[c] * ip : 0.0);
-        row[c] = v;
-        keep(c, ip);
-#pragma unroll
-        for (int cc = c + 1; cc < 32; ++cc) row[cc] = fma(-v, lane_value(v, cc), row[cc]);
-    }
-}
-
 // ---- blocked form over several launches (K > kCholSmallK): per block column of 32 one launch that factors the
 // diagonal block and solves the rows below, 64 rows per wave, and one that updates the trailing matrix, 64 x 64
 // tiles on the fp64 matrix cores; a last one zeroes the upper triangle.  A single work-group per matrix walks
@@ -751,7 +721,7 @@ struct Plan {
     size_t lds_jacobi = 0;  // largest jb * K * 8 over the layers
     struct PerLayer {
         int K, jb, nb;
-        size_t Abar, Bbar, LA, GB, LB, Ct, Yt, sigma, s3, s5, trace, diag, nrm, perm, PA, PB, chol;
+        size_t Abar, Bbar, LA, GB, LB, Ct, Yt, sigma, s3, s5, trace, diag, nrm, perm, PA, PB, chol, gparts;
     };
     std::vector<PerLayer> pl;
 };
@@ -863,6 +833,7 @@ Plan make_plan(const abt_merge_desc* layers, int L) {
         q.PA = take(sizeof(float) * K * kc);
         q.PB = take(sizeof(float) * kc * K);
         q.chol = take(sizeof(double) * 2 * (32 * K + 2));
+        q.gparts = K == 32 ? take(sizeof(double) * 2 * kGramParts * 1024) : 0;
     }
     p.total = off;
     return p;
@@ -988,22 +959,35 @@ hipError_t launch_identity_f32(float* dst, int K, hipStream_t s) {
 
 constexpr int kWorkspaceMagic = 0x41425431;
 
-hipError_t merge_layer_count(const void* workspace, int* layers, hipStream_t s) {
+// Header and info table lie next to each other at the start (see make_plan): a few layers are read with one copy, which a workspace too small for
+// it refuses; then, and for many, the header alone.
+hipError_t merge_read_info(const void* workspace, int first, int count, std::vector<int32_t>& out, hipStream_t s) {
     hipError_t e = hipStreamSynchronize(s);
     if (e != hipSuccess) return e;
-    int hdr[4] = {0, 0, 0, 0};
-    e = hipMemcpy(hdr, workspace, sizeof(hdr), hipMemcpyDeviceToHost);
-    if (e != hipSuccess) return e;
-    if (hdr[0] != kWorkspaceMagic || hdr[1] < 1) return hipErrorInvalidValue;
-    *layers = hdr[1];
-    return hipSuccess;
+    const int64_t end = 256 + (int64_t)sizeof(int) * kInfoInts * ((int64_t)first + count);
+    int32_t head[256];
+    const bool together = end <= (int64_t)sizeof(head) && hipMemcpy(head, workspace, (size_t)end, hipMemcpyDeviceToHost) == hipSuccess;
+    if (!together) {
+        (void)hipGetLastError();
+        e = hipMemcpy(head, workspace, 16, hipMemcpyDeviceToHost);
+        if (e != hipSuccess) return e;
+    }
+    if (head[0] != kWorkspaceMagic || head[1] < 1 || count > head[1] || first > head[1] - count) return hipErrorInvalidValue;
+    out.resize(kInfoInts * (size_t)count);
+    if (together) {
+        memcpy(out.data(), head + 64 + kInfoInts * first, sizeof(int32_t) * out.size());
+        return hipSuccess;
+    }
+    return hipMemcpy(out.data(), (const char*)workspace + 256 + sizeof(int) * kInfoInts * (size_t)first, sizeof(int32_t) * out.size(), hipMemcpyDeviceToHost);
 }
 
-hipError_t merge_read_info(const void* workspace, int first, int count, int32_t* out) {
-    // the info table follows the 256-byte header slot (see make_plan)
-    return hipMemcpy(out, (const char*)workspace + 256 + sizeof(int) * kInfoInts * (size_t)first,
-                     sizeof(int) * kInfoInts * (size_t)count, hipMemcpyDeviceToHost);
+namespace {
+// Tables of up to two of these (one or two layers) go up without a copy and without a wait: the merge of one 256 x 256 layer 161 -> 156 us.
+struct UploadWords { uint32_t w[960]; };
+__global__ __launch_bounds__(256) void upload_kernel(UploadWords u, uint32_t* dst, int n) {
+    for (int i = threadIdx.x; i < n; i += 256) gstore(dst + i, u.w[i]);
 }
+}  // namespace
 
 hipError_t merge_run(const abt_merge_desc* layers, const MergeSide* identity, int L, void* workspace, int max_sweeps, hipStream_t s) {
     const Plan p = make_plan(layers, L);
@@ -1048,6 +1032,7 @@ hipError_t merge_run(const abt_merge_desc* layers, const MergeSide* identity, in
         v.diag = (double*)(ws + q.diag);
         v.nrm = (double*)(ws + q.nrm);
         v.perm = (int*)(ws + q.perm);
+        v.gparts = (double*)(ws + q.gparts);
         v.PA = (float*)(ws + q.PA); v.PB = (float*)(ws + q.PB);
         v.rotated = (int*)(ws + p.off_rotated) + (size_t)l * (kMaxSweepsCap + 1);
         v.info = (int*)(ws + p.off_info) + (size_t)l * kInfoInts;
@@ -1143,9 +1128,20 @@ hipError_t merge_run(const abt_merge_desc* layers, const MergeSide* identity, in
     put(p.off_chol, chol.data(), sizeof(CholMat) * chol.size());
     put(p.off_pairs, pairs.data(), sizeof(TriPair) * pairs.size());
     const GemmF32Table table32 = gemm_f32_build_table(g32.data(), (int)g32.size(), image.data() + p.off_gemm32);
-    ABT_TRY(hipMemcpyAsync(ws, image.data(), image.size(), hipMemcpyHostToDevice, s));
-    // the upload must have left the host image before it is destroyed
-    ABT_TRY(hipStreamSynchronize(s));
+    if (image.size() <= 2 * sizeof(UploadWords::w)) {
+        // a small one travels in the arguments of one or two launches, which have copied it when they return
+        for (size_t at = 0; at < image.size(); at += sizeof(UploadWords::w)) {
+            UploadWords u;
+            const size_t bytes = image.size() - at < sizeof(u.w) ? image.size() - at : sizeof(u.w);
+            memcpy(u.w, image.data() + at, bytes);
+            hipLaunchKernelGGL(upload_kernel, dim3(1), dim3(256), 0, s, u, (uint32_t*)(ws + at), (int)(bytes / 4));
+        }
+        ABT_TRY(hipGetLastError());
+    } else {
+        ABT_TRY(hipMemcpyAsync(ws, image.data(), image.size(), hipMemcpyHostToDevice, s));
+        // the upload must have left the host image before it is destroyed
+        ABT_TRY(hipStreamSynchronize(s));
+    }
 
     std::unique_lock<std::mutex> stage_lock(g_stage_mutex, std::defer_lock);
     bool timed = false;
@@ -1162,20 +1158,24 @@ hipError_t merge_run(const abt_merge_desc* layers, const MergeSide* identity, in
     };
     const LayerDev* dl = (const LayerDev*)(ws + p.off_layers);
     ABT_TRY(mark(0));
-    ABT_TRY(launch_mean_gram(dl, (const GramJob*)(ws + p.off_gram_tiles), gram_aligned, p.n_gram_tiles - gram_aligned, s));
+    // every core one pair of blocks (and no dense weight): the stages around the iteration in a launch each (merge_small.hip)
+    const bool cores32 = p.K_max == 32 && identity == nullptr;
+    if (cores32) ABT_TRY(launch_gram32(dl, L, s));
+    else ABT_TRY(launch_mean_gram(dl, (const GramJob*)(ws + p.off_gram_tiles), gram_aligned, p.n_gram_tiles - gram_aligned, s));
     ABT_TRY(mark(1));
     const CholMat* mats = (const CholMat*)(ws + p.off_chol);
-    ABT_TRY(launch_cholesky(mats, (int)n_gram, K_gram, s));
+    if (cores32) ABT_TRY(launch_core32(dl, L, s));
+    else ABT_TRY(launch_cholesky(mats, (int)n_gram, K_gram, s));
     ABT_TRY(mark(2));
     const GemmF64* d64 = (const GemmF64*)(ws + p.off_gemm64);
-    hipLaunchKernelGGL(gemm_f64_kernel, dim3(align_up(tb0, 8)), dim3(256), 0, s, d64, p.n_gemm64, tb0);
+    if (!cores32) hipLaunchKernelGGL(gemm_f64_kernel, dim3(align_up(tb0, 8)), dim3(256), 0, s, d64, p.n_gemm64, tb0);
     if (!pairs.empty()) {
         ABT_TRY(launch_cholesky(mats + n_gram, (int)pairs.size(), K_core, s));
         const unsigned nt = (unsigned)(K_core / 32);
         hipLaunchKernelGGL(lower_to_columns_kernel, dim3(nt, nt, (unsigned)pairs.size()), dim3(256), 0, s,
                            (const TriPair*)(ws + p.off_pairs));
     }
-    hipLaunchKernelGGL(frob2_kernel, dim3(8, L), dim3(256), 0, s, dl);
+    if (!cores32) hipLaunchKernelGGL(frob2_kernel, dim3(8, L), dim3(256), 0, s, dl);
     ABT_TRY(hipGetLastError());
     ABT_TRY(mark(3));
 
@@ -1289,12 +1289,16 @@ hipError_t merge_run(const abt_merge_desc* layers, const MergeSide* identity, in
         }
     }
     ABT_TRY(mark(4));
-    int n2 = 1;
-    while (n2 < p.K_max) n2 <<= 1;
-    hipLaunchKernelGGL(colnorm_kernel, dim3((p.K_max + 3) / 4, L), dim3(256), 0, s, dl);
-    hipLaunchKernelGGL(finalize_kernel, dim3(L), dim3(256), (sizeof(double) + sizeof(int)) * n2, s, dl, max_sweeps);
-    if (tb1 > 0) hipLaunchKernelGGL(gemm_f64_kernel, dim3(align_up(tb1, 8)), dim3(256), 0, s, d64 + p.n_gemm64, p.n_gemm64, tb1);
-    if (tb2 > 0) hipLaunchKernelGGL(gemm_f64_kernel, dim3(align_up(tb2, 8)), dim3(256), 0, s, d64 + 2 * p.n_gemm64, p.n_gemm64, tb2);
+    if (cores32) {
+        ABT_TRY(launch_finish32(dl, L, max_sweeps, s));
+    } else {
+        int n2 = 1;
+        while (n2 < p.K_max) n2 <<= 1;
+        hipLaunchKernelGGL(colnorm_kernel, dim3((p.K_max + 3) / 4, L), dim3(256), 0, s, dl);
+        hipLaunchKernelGGL(finalize_kernel, dim3(L), dim3(256), (sizeof(double) + sizeof(int)) * n2, s, dl, max_sweeps);
+        if (tb1 > 0) hipLaunchKernelGGL(gemm_f64_kernel, dim3(align_up(tb1, 8)), dim3(256), 0, s, d64 + p.n_gemm64, p.n_gemm64, tb1);
+        if (tb2 > 0) hipLaunchKernelGGL(gemm_f64_kernel, dim3(align_up(tb2, 8)), dim3(256), 0, s, d64 + 2 * p.n_gemm64, p.n_gemm64, tb2);
+    }
     ABT_TRY(hipGetLastError());
     ABT_TRY(mark(5));
     ABT_TRY(launch_gemm_f32_table(ws + p.off_gemm32, table32, s));

@@ -23,6 +23,8 @@ constexpr double kSigmaFloor = 1e-7;   // sigma_i <= floor * sigma_1: singular v
 // kSigmaFloor sigma_1 (||C||_F <= sqrt(K) sigma_1).
 constexpr double kZeroColumn2 = 1e-18;
 
+constexpr int kGramParts = 16;    // work-groups that share a side's contraction where K = 32
+
 struct LayerDev {
     const float* const* A_ptrs;
     const float* const* B_ptrs;
@@ -36,6 +38,7 @@ struct LayerDev {
     double* diag;          // [K / 16][16][16]: Gram matrices of the column blocks between two rounds of a sweep
     double* nrm;           // [K]: squared column norms of the rotated core (colnorm_kernel -> finalize_kernel)
     int* perm;
+    double* gparts;        // K = 32: parts of the Gram matrices [A, B][kGramParts][32][32]
     float* PA; float* PB;
     int* rotated;          // [kMaxSweepsCap + 1]
     int* info;             // [kInfoInts]
@@ -87,6 +90,36 @@ __device__ __forceinline__ bool jacobi_rotation(double alpha, double beta, doubl
     return true;
 }
 
+__device__ __forceinline__ double lane_value(double v, int src) {
+    const int lo = __builtin_amdgcn_readlane(__double2loint(v), src);
+    const int hi = __builtin_amdgcn_readlane(__double2hiint(v), src);
+    return __hiloint2double(hi, lo);
+}
+
+// Factor a 32 x 32 block in one wave: lane r (and r + 32) holds row r; step c takes the pivot and the
+// finished column c from the other lanes with lane reads (no LDS, no waits).  keep(c, 1 / pivot or 0).
+template <class F>
+__device__ __forceinline__ void factor_diagonal_block(double (&row)[32], int r, double floor_piv, F&& keep) {
+#pragma unroll
+    for (int c = 0; c < 32; ++c) {
+        const double d = lane_value(row[c], c);
+        const bool ok = d > floor_piv;
+        // 1 / sqrt(d): hardware estimate and two Newton steps (a square root and a division in
+        // fp64 would be several times the rest of the step); the pivot itself is d / sqrt(d)
+        const double dd = ok ? d : 1.0;
+        double y = __builtin_amdgcn_rsq(dd);
+        y = y * fma(-0.5 * dd, y * y, 1.5);
+        y = y * fma(-0.5 * dd, y * y, 1.5);
+        const double ip = ok ? y : 0.0;
+        const double piv = ok ? dd * y : 0.0;
+        const double v = (r == c) ? piv : (r > c ? row[c] * ip : 0.0);
+        row[c] = v;
+        keep(c, ip);
+#pragma unroll
+        for (int cc = c + 1; cc < 32; ++cc) row[cc] = fma(-v, lane_value(v, cc), row[cc]);
+    }
+}
+
 // Average of the copies + Gram matrices (merge_gram.hip): one work-group per job; layer < 0 marks
 // an empty slot; (ti, tj), ti >= tj, is a 128 x 128 tile of the lower triangle; which = 0: G_A
 // (stored into LA), 1: G_B (stored into GB and LB).  The diagonal tiles also write Abar / Bbar.
@@ -103,5 +136,11 @@ hipError_t launch_jacobi_block_round(const LayerDev* layers, const int2* wg_map,
 
 // All sweeps of layers with K = 32 (every layer of the batch): one work-group per layer, one launch.
 hipError_t launch_jacobi_single_pair(const LayerDev* layers, const int2* wg_map, int n_wg, int max_sweeps, hipStream_t s);
+
+// The stages around it where every core is 32 wide and no layer a dense weight (merge_small.hip): averages and parts of the Gram matrices;
+// Cholesky factors and core; values, rank and projections.
+hipError_t launch_gram32(const LayerDev* layers, int L, hipStream_t s);
+hipError_t launch_core32(const LayerDev* layers, int L, hipStream_t s);
+hipError_t launch_finish32(const LayerDev* layers, int L, int max_sweeps, hipStream_t s);
 
 }  // namespace abt

@@ -80,3 +80,27 @@ def test_block_iteration_at_the_edges_of_its_forms(K, zero_tail):
     want = (U[:, :keep] * s[:keep]) @ V[:keep]
     # fp32 back-projections: sums of K products, (K + 2) 2^-24 at most, some sqrt(K) 2^-24 in the norm; factors rounded to fp32
     assert float((got - want).norm() / want.norm()) < 4e-6
+
+
+# shapes around the 64 contraction indices of a step and the 16 work-groups of a side, rows that are not multiples of four, one to five copies, more
+# columns than the core has and fewer
+@pytest.mark.parametrize("m,n,G,k_cap,k_fixed", [(33, 32, 1, 32, 0), (64, 65, 2, 32, 0), (1024, 1025, 3, 20, 0), (1088, 2047, 5, 40, 7), (3072, 130, 4, 32, 32)])
+def test_stages_around_a_core_of_32(m, n, G, k_cap, k_fixed):
+    layers = [dict(layer(m, n, 32, seed=m + n + i, g=G), k_cap=k_cap, k_fixed=k_fixed, tau=0.01, want_W=True) for i in range(2)]
+    for lay, out in zip(layers, abt.ab_merge_batched(layers)):
+        A, B = (torch.stack(lay[x]).double().mean(0) for x in ("A_copies", "B_copies"))
+        W = (A @ B).cpu()
+        U, S, Vt = torch.linalg.svd(W, full_matrices=False)
+        want = min(k_fixed or int((S[:32].float() >= 0.01 * S[0].float()).sum()), k_cap, 32)
+        k = int(out["k"])
+        assert k == want
+        # values: fp32 averages of the factors and fp32 output, 2^-24 each, relative to the largest by the products
+        kept = min(k_cap, 32)
+        assert float((out["S"][:kept].double().cpu() - S[:kept]).abs().max() / S[0]) < 1e-6 and not bool(out["S"][kept:].any())
+        T = U[:, :k] * S[:k] @ Vt[:k]
+        a, b = out["A"].double().cpu(), out["B"].double().cpu()
+        assert float((a @ b - T).norm() / T.norm()) < 6e-6 and not bool(a[:, k:].any()) and not bool(b[k:].any())
+        assert float((out["W"].double().cpu() - W).norm() / W.norm()) < 1e-6
+        # A'^T A' = B' B'^T = the values
+        for q in (a[:, :k].T @ a[:, :k], b[:k] @ b[:k].T):
+            assert float((q - torch.diag(S[:k])).norm() / S[:k].norm()) < 1e-4
