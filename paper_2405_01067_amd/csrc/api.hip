@@ -2,6 +2,7 @@
 // Every operation is documented in include/abtrain.h.
 #include <atomic>
 #include <cmath>
+#include <initializer_list>
 #include <new>
 #include <vector>
 
@@ -304,6 +305,16 @@ GemmF32 gemm(const float* A, const float* B, float* C, int64_t P, int64_t Q, int
     g.lda = (int)lda; g.ldb = (int)ldb; g.ldc = (int)ldc;
     g.transA = tA; g.transB = tB; g.accumulate = acc; g.alpha = 1.0f;
     return g;
+}
+
+// The smallest fp32 layers go in one launch each way, in which no output may lie over what another work-group reads.
+struct Place { const void* at; int64_t count; };
+bool tiny_f32(int64_t M, int64_t m, int64_t n, int64_t r, std::initializer_list<Place> in, std::initializer_list<Place> out) {
+    if (!tiny_f32_supports(M, m, n, r)) return false;
+    for (const Place& o : out)
+        for (const Place& i : in)
+            if (overlap(o.at, o.count * 4, i.at, i.count * 4)) return false;
+    return true;
 }
 
 // fp32 backward: dT, T (each M x r) and the partial sums of the factor gradients, whose contraction over
@@ -855,11 +866,14 @@ int lr_linear_fwd(const void* X, const void* A, const void* B, void* Y, void* T_
         return chain(X, B, A, Y, T_save, M, (int)n, (int)m, (int)r, s) == hipSuccess ? ABT_OK : ABT_EHIP;
     }
     float* T = (float*)T_save;
+    const bool tiny = tiny_f32(M, m, n, r, {{X, M * n}, {A, m * r}, {B, r * n}}, {{Y, M * m}, {T_save, M * r}});
     if (!T) {
         if (!workspace || workspace_bytes < lr_linear_fwd_workspace_bytes(M, m, n, r, dt)) return ABT_EWORKSPACE;
         if (!aligned(workspace, 256)) return ABT_EALIGN;
         T = (float*)workspace;
     }
+    if (tiny)
+        return launch_tiny_f32_fwd((const float*)X, (const float*)A, (const float*)B, (float*)Y, (float*)T_save, M, m, n, r, s) == hipSuccess ? ABT_OK : ABT_EHIP;
     // T = X B^T ; Y = T A^T
     if (launch_gemm_f32_one(gemm((const float*)X, (const float*)B, T, M, r, n, n, n, r, 0, 1, 0), s) != hipSuccess) return ABT_EHIP;
     if (launch_gemm_f32_one(gemm(T, (const float*)A, (float*)Y, M, m, r, r, r, m, 0, 1, 0), s) != hipSuccess) return ABT_EHIP;
@@ -885,6 +899,10 @@ int linear_bwd(const void* dY, const void* X, const void* T, const void* A, cons
     if (!dX && !dA && !dB) return ABT_OK;
 
     if (dt == ABT_F32) {
+        // (dT of 32 rows once per work-group, of two blocks of rows in tiles of dB: no more than two chunks of 256 of the contraction in all)
+        if ((T || !dA) && ceil_div(M, 32) * ceil_div(m, 256) <= 2 && tiny_f32(M, m, n, r, {{dY, M * m}, {X, M * n}, {T, M * r}, {A, m * r}, {B, r * n}}, {{dX, M * n}, {dA, m * r}, {dB, r * n}}))
+            return launch_tiny_f32_bwd((const float*)dY, (const float*)X, (const float*)T, (const float*)A, (const float*)B, (float*)dX, dA, dB, M, m, n, r, acc, s) ==
+                   hipSuccess ? ABT_OK : ABT_EHIP;
         // two launches (and one that adds the split sums): first what depends on the inputs alone, then the rest
         const BwdLayoutF32 w = bwd_layout_f32(M, m, n, r, limit);
         float* dT = (float*)(ws + w.dT);

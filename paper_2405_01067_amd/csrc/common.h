@@ -255,6 +255,13 @@ size_t gemm_f32_desc_bytes();
 GemmF32Table gemm_f32_build_table(const GemmF32* descs_host, int n, void* host_image);
 hipError_t launch_gemm_f32_table(const void* dev_image, const GemmF32Table& t, hipStream_t s);
 
+// The smallest fp32 layers in one launch each way (layer_f32_small.hip).  No output may lie over an input; T (or NULL) as in the other calls, but
+// dA needs it.
+bool tiny_f32_supports(int64_t M, int64_t m, int64_t n, int64_t r);
+hipError_t launch_tiny_f32_fwd(const float* X, const float* A, const float* B, float* Y, float* T, int64_t M, int64_t m, int64_t n, int64_t r, hipStream_t s);
+hipError_t launch_tiny_f32_bwd(const float* dY, const float* X, const float* T, const float* A, const float* B, float* dX, float* dA, float* dB,
+                               int64_t M, int64_t m, int64_t n, int64_t r, int accumulate, hipStream_t s);
+
 // ------------------------------------------------------------------ merge
 // Host-side plan of a batched merge: validates nothing (api.hip does), lays out the workspace
 // and enqueues every stage.

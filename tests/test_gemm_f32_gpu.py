@@ -99,3 +99,33 @@ def test_split_beside_the_static_scratch(M):
         for o, a, b, err in ((got[0], dYd, T, dYd.abs().T @ T_err), (got[1], dT, Xd, dT_err.T @ Xd.abs())):
             bound = (M + 4) * EPS * (a.abs().T @ b.abs()) + err * (1 + 1e-3)
             assert bool(((o.double() - a.T @ b).abs() <= bound).all())
+
+
+# one launch each way: blocks of 32 rows, 128 columns of the widths, chunks of 256 of the contraction, widths that are not multiples of four, and
+# the sizes next to its limits
+@pytest.mark.parametrize("M,m,n,r", [(1, 1, 1, 1), (31, 127, 129, 32), (32, 512, 511, 5), (33, 256, 512, 32), (64, 255, 257, 31), (64, 257, 256, 32),
+                                     (64, 512, 512, 32), (65, 256, 256, 32), (64, 256, 513, 32), (64, 256, 256, 33)])
+@pytest.mark.parametrize("accumulate", [False, True])
+def test_smallest_layers(M, m, n, r, accumulate):
+    g = torch.Generator(device="cuda").manual_seed(M + m + n + r)
+    X, dY, A, B = rnd(g, M, n), rnd(g, M, m), rnd(g, m, r), rnd(g, r, n)
+    Xd, dYd, Ad, Bd = (t.double() for t in (X, dY, A, B))
+    Y, T = abt.lr_linear_fwd(X, A, B)
+    close(T, Xd, Bd.T), close(Y, T.double(), Ad.T)        # of the T that was kept, Y is one product
+    assert torch.equal(abt.lr_linear_fwd(X, A, B, save_T=False)[0], Y)
+    dA0, dB0 = rnd(g, m, r), rnd(g, r, n)
+    run = lambda **kw: abt.lr_linear_bwd(dY, X, T, A, B, accumulate=accumulate, **{
+        k: v.clone() for k, v in (("dA", dA0), ("dB", dB0)) if accumulate and kw.get("need_" + k, True)}, **kw)
+    dX, dA, dB = run()
+    base = lambda out, b: out - b if accumulate else out
+    slack = lambda b: 4 * EPS * b.double().abs() if accumulate else 0.0
+    assert bool(((base(dA, dA0).double() - dYd.T @ T.double()).abs() <= (M + 3) * EPS * (dYd.abs().T @ T.double().abs()) + slack(dA0)).all())
+    # dT carries (m + 2) EPS |dY| |A|, which the products that follow pass on
+    dT, mag = dYd @ Ad, dYd.abs() @ Ad.abs()
+    bound = lambda a, b, K: ((m + 2) + (K + 4)) * EPS * (a @ b) * 1.001
+    assert bool(((dX.double() - dT @ Bd).abs() <= bound(mag, Bd.abs(), r)).all())
+    assert bool(((base(dB, dB0).double() - dT.T @ Xd).abs() <= bound(mag.T, Xd.abs(), M) + slack(dB0)).all())
+    # the same bits whatever else is asked for
+    for which in ((True, False, True), (False, True, False), (False, False, True), (True, False, False)):
+        for a, b, w in zip(run(need_dX=which[0], need_dA=which[1], need_dB=which[2]), (dX, dA, dB), which):
+            assert (torch.equal(a, b) or M > 64 or r > 32 or n > 512) if w else a is None
