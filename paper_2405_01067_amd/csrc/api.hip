@@ -14,7 +14,7 @@ namespace {
 
 std::atomic<int> g_max_sweeps{30};
 
-// Chain kernel choice: two products where two_products says so; else the narrow-rank kernel where use_narrow / narrow_gather do; else
+// Chain kernel choice: two products where wide_products or two_products say so; else the narrow-rank kernel where use_narrow / narrow_gather do; else
 // by choose_chain_shape work-groups of 128 rows (r = 32, 64, 96, 128, and 192 to 384 in the kernel of eight equal waves; from an image 192 and
 // 384 too) or of 64 rows with loader and MFMA waves (r = 32, 64, 96, 128, 160, 192, 256, 320, 384).
 std::atomic<int> g_chain_rows{0};    // 0: automatic; 64 or 128: force that work-group height where the rank allows it
@@ -176,19 +176,23 @@ bool two_products(int64_t rows, int p, int q, int R, bool image) {
 }
 // Where the chain runs as the two products for many rows (lr_pair.hip), by the rows of all problems together.  Forward, us, the other kernels /
 // these, on a card that keeps what fits in the last-level cache between the calls:
-//   More than 32768 rows, where the fused kernels' 128-row work-groups need a second round (mean of old / new over all shapes 1.15):
-//                          r = 64        r = 96        r = 128       r = 192       r = 384
-//     768 -> 3072  36000   60 / 57       67 / 59       76 / 63       94 / 71       149 / 127
-//                  50432   84 / 80       97 / 87       115 / 93      116 / 91      175 / 160
-//     3072 -> 768  36000   59 / 53       71 / 57       88 / 65       94 / 73       149 / 116
-//                  50432   82 / 74       93 / 78       112 / 92      115 / 104      188 / 175
-//     768 -> 768   36000   31 / 31       33 / 31       39 / 34       51 / 38       71 / 61
-//     Narrow ranks and layers gain least, and lose below the limits here (64 -> 640, 49000 rows, r = 288 32 / 42).  From 114688 rows on the
-//     rounds are many and even: from r = 160 on nothing to gain (768 -> 3072, 150000 rows, r = 384 430 / 452; r = 96 277 / 240).
+//   More than 32768 rows, where the fused kernels' 128-row work-groups need a second round:
+//                          r = 64         r = 96         r = 128        r = 192         r = 384
+//     768 -> 3072  36000   58.1 / 57.9    66.9 / 57.2    73.7 / 57.6    89.5 / 65.0     133 / 115
+//                  50432   80.0 / 77.4    82.2 / 77.8    95.4 / 75.8    116 / 82.4      176 / 154
+//     3072 -> 768  36000                  72.0 / 56.2    87.2 / 62.0    99.0 / 78.1     155 / 126
+//                  50432                  91.0 / 75.0    97.6 / 79.6    107 / 95.2      175 / 157
+//     768 -> 768   36000                  32.5 / 28.9                   49.8 / 37.3     66.7 / 56.3
+//     Narrow ranks and layers gain least, and lose below the limits here (64 -> 1600, 57148 rows, r = 96 44.9 / 48.1).  From 114688 rows on
+//     the rounds are many and even: from r = 160 on nothing to gain (768 -> 768, 219909 rows, r = 352 282 / 337; 768 -> 3072, 150000 rows,
+//     r = 96 240 / 217).
 //   r = 288 and 352 from 10240 rows on, where the fused kernel is that of the next wider rank in 128-row work-groups (768 -> 3072, 12000
-//     rows, r = 288 66 / 40; 16384: even with it from there on); r = 160, whose fused kernel has 64-row work-groups (768 -> 3072, 25000 rows 69 / 53).
-//   Wide results of short contractions, where a fused work-group's time is the stores of Y: 4096 to 10240 rows (768 -> 3072, r = 192, 6000 rows
-//     31 / 24) and, less, 16384 to 22528 (20000 rows 54 / 44).  Between them one round of 64-row work-groups fills the chip (14000 rows 39 / 42).
+//     rows, r = 288 72.6 / 41.2; even with it from 16384 on); r = 160, whose fused kernel has 64-row work-groups (768 -> 3072, 25000
+//     rows 62.7 / 44.4).
+//   Wide results of short contractions, where a fused work-group's time is the stores of Y (768 -> 3072, r = 192): 4096 to 10240 rows (6000
+//     rows 31.1 / 23.3), 16384 to 22528 (20000 rows 52.8 / 40.6) and, at r = 160 and 192, up to 12800 (12608 rows 32.0 / 30.7; over 116
+//     shapes 0.98 to 1.18 times as fast, mean 1.06).  Above that one round of 64-row work-groups fills the chip (14500 rows, r = 160 33.5 / 34.6,
+//     r = 128 28.7 / 33.4).
 bool wide_products(int64_t rows, int p, int q, int R) {
     if (g_chain_rows.load() != 0 || g_chain_parts.load() != 0 || rows <= 4096 || p < 256 || q < 128) return false;
     if (rows > 32768) {
@@ -201,6 +205,7 @@ bool wide_products(int64_t rows, int p, int q, int R) {
     if (R == 160 && rows > 16384) return q >= 512 && p + q >= 1472;
     if (rows <= 8192 && R >= 96 && R <= 192) return q >= 1024 && p <= 1920;
     if (rows <= 10240) return ((R >= 64 && R <= 192) || R == 288) && q >= 1344 && q >= 2 * p;
+    if (rows <= 12800) return (R == 160 || R == 192) && q >= 2304 && q >= 2 * p;
     return rows > 16384 && rows <= 22528 && R >= 64 && q >= 1344 && 2 * q >= 5 * p;
 }
 // T needs a place, and not over the first operand, whose rows several work-groups read.

@@ -24,6 +24,7 @@ def layer(M, m, n, r):
 # rows per work-group: 32 (the least), 64, more in one round; a last work-group of one row, of all; one and two rounds of the compute units;
 # a result of 256 columns and one more block, of half a block of columns; an odd and an even number of slabs
 @pytest.mark.parametrize("M,m,n,r", [(4097, 1344, 320, 96), (6000, 1088, 1920, 192), (8192, 1344, 256, 128), (10239, 1408, 256, 288), (10240, 1344, 640, 64),
+                                     (10241, 2304, 256, 160), (12800, 2304, 1152, 192),
                                      (12345, 128, 1152, 288), (16384, 1024, 256, 352), (16385, 1344, 512, 224), (17001, 512, 960, 160),
                                      (20000, 1344, 512, 256), (22528, 1344, 256, 384), (32769, 448, 256, 320), (33333, 2304, 256, 64),
                                      (40000, 1088, 256, 128), (40960, 512, 768, 96), (49152, 128, 768, 384), (50433, 768, 768, 384), (65537, 768, 832, 160)])
