@@ -198,58 +198,80 @@ constexpr int kDtWaves = 8;
 
 struct SmallDt { const uint16_t* dY; const uint16_t* A; uint16_t* dT; int M, m, r; };
 
-// 32 rows x 64 columns of dT; wave w takes the slabs of 64 columns of dY w, w + 8, ..
+// 32 rows x COLS columns of dT; wave w takes the slabs of 64 columns of dY w, w + 8, ..  Of 64 columns a lane loads two neighbours for all eight k of
+// its operands, of 32 for four of them, and lanes j and j + 16 exchange halves.
+// Bound by the loads a wave may have on the way (63) and their latency: 36 loads per slab of 64 columns, 20 of 32.  The wave's number has to be
+// known to be uniform (readfirstlane), or every load whose offset depends on it sits in a loop over the distinct values of its lanes
+// (108 such loops; 197 x 768 -> 2304, r = 96: 11.0 us, 9.0 without them, 8.0 with tiles of 32 columns and three slabs ahead).
+template <int COLS>
 __global__ __launch_bounds__(64 * kDtWaves, 2) void small_dt_kernel(SmallDt p) {
-    __shared__ float red[kDtWaves][2][16][64];
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, j = lane & 31, h = lane >> 5;
-    const int row0 = 32 * (int)blockIdx.x, col = 64 * (int)blockIdx.y + 2 * j;
+    constexpr int CB = COLS / 32, KI = 4 * CB, NB = COLS == 64 ? 2 : 4;      // blocks, loads per operand, slabs in flight
+    __shared__ float red[kDtWaves][CB][16][64];
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), j = lane & 31, h = lane >> 5;
+    const int row0 = 32 * (int)blockIdx.x, col = COLS * (int)blockIdx.y + 2 * (j & (COLS / 2 - 1)), kq = 8 * h + (COLS == 32 ? 4 * (j >> 4) : 0);
     const rsrc_t xres = make_rsrc(p.dY, (int64_t)p.M * p.m * 2), ares = make_rsrc(p.A, (int64_t)p.m * p.r * 2);
     const int xoff = ((row0 + j) * p.m + 8 * h) * 2;                 // rows past M: outside the descriptor, zeros
-    const int aoff = col < p.r ? (8 * h * p.r + col) * 2 : kBufNowhere;
-    f32x16 acc[2];
-    zero(acc[0]); zero(acc[1]);
-    struct Slab { u32x4 x[4]; uint32_t a[4][8]; } buf[2];
+    const int aoff = col < p.r ? (kq * p.r + col) * 2 : kBufNowhere;
+    f32x16 acc[CB];
+#pragma unroll
+    for (int b = 0; b < CB; ++b) zero(acc[b]);
+    struct Slab { u32x4 x[4]; uint32_t a[4][KI]; } buf[NB];
     auto load = [&](Slab& s, int slab) {
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
             s.x[q] = buf_load16(xres, xoff, (64 * slab + 16 * q) * 2);
 #pragma unroll
-            for (int i = 0; i < 8; ++i) s.a[q][i] = load4(ares, aoff, (64 * slab + 16 * q + i) * p.r * 2);
+            for (int i = 0; i < KI; ++i) s.a[q][i] = load4(ares, aoff, (64 * slab + 16 * q + i) * p.r * 2);
         }
     };
     auto multiply = [&](const Slab& s) {
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
-            u32x4 op[2];
-            unpair(s.a[q], op);
-            acc[0] = mfma16(s.x[q], op[0], acc[0]);
-            acc[1] = mfma16(s.x[q], op[1], acc[1]);
+            if constexpr (CB == 2) {
+                u32x4 op[2];
+                unpair(s.a[q], op);
+                acc[0] = mfma16(s.x[q], op[0], acc[0]);
+                acc[1] = mfma16(s.x[q], op[1], acc[1]);
+            } else {
+                u32x4 op;                                    // lane j: column 2 (j % 16) + j / 16 of the tile
+#pragma unroll
+                for (int i = 0; i < 2; ++i) {
+                    const uint32_t even = __builtin_amdgcn_perm(s.a[q][2 * i + 1], s.a[q][2 * i], 0x05040100u);
+                    const uint32_t odd = __builtin_amdgcn_perm(s.a[q][2 * i + 1], s.a[q][2 * i], 0x07060302u);
+                    const auto both = __builtin_amdgcn_permlane16_swap(even, odd, false, false);
+                    op[i] = both[0];
+                    op[2 + i] = both[1];
+                }
+                acc[0] = mfma16(s.x[q], op, acc[0]);
+            }
         }
     };
     const int slabs = p.m / 64;
-    int s = wave;
-    if (s < slabs) load(buf[0], s);
-    for (; s < slabs; s += 2 * kDtWaves) {
-        if (s + kDtWaves < slabs) load(buf[1], s + kDtWaves);
-        multiply(buf[0]);
-        if (s + kDtWaves < slabs) {
-            if (s + 2 * kDtWaves < slabs) load(buf[0], s + 2 * kDtWaves);
-            multiply(buf[1]);
-        }
-    }
 #pragma unroll
-    for (int b = 0; b < 2; ++b)
+    for (int b = 0; b < NB - 1; ++b)
+        if (wave + b * kDtWaves < slabs) load(buf[b], wave + b * kDtWaves);
+    for (int s = wave; s < slabs; s += NB * kDtWaves)
+#pragma unroll
+        for (int b = 0; b < NB; ++b) {
+            const int at = s + b * kDtWaves;
+            if (at + (NB - 1) * kDtWaves < slabs) load(buf[(b + NB - 1) % NB], at + (NB - 1) * kDtWaves);
+            if (at < slabs) multiply(buf[b]);
+        }
+#pragma unroll
+    for (int b = 0; b < CB; ++b)
 #pragma unroll
         for (int v = 0; v < 16; ++v) red[wave][b][v][lane] = acc[b][v];
     __syncthreads();
-    const rsrc_t tres = make_rsrc(p.dT, (int64_t)p.M * p.r * 2);
+    const rsrc_t tres = make_rsrc(p.dT, (int64_t)p.M * p.r * 2);     // rows past M are dropped
 #pragma unroll
-    for (int e = 0; e < 2; ++e) {
-        const int v = wave + kDtWaves * e;
+    for (int e = 0; e < CB; ++e) {
+        // a pair of columns: two blocks of one lane, or one block of the lanes c and c + 16
+        const int v = CB == 2 ? wave + kDtWaves * e : 2 * wave + h, c = CB == 2 ? lane : (lane & 15) + 2 * (lane & 16);
+        const int hh = CB == 2 ? h : (lane >> 4) & 1, oc = COLS * (int)blockIdx.y + 2 * (lane & (COLS / 2 - 1));
         float t0 = 0.0f, t1 = 0.0f;
 #pragma unroll
-        for (int w = 0; w < kDtWaves; ++w) { t0 += red[w][0][v][lane]; t1 += red[w][1][v][lane]; }
-        const int off = col < p.r ? ((row0 + acc_row(v, h)) * p.r + col) * 2 : kBufNowhere;      // rows past M are dropped
+        for (int w = 0; w < kDtWaves; ++w) { t0 += red[w][0][v][c]; t1 += CB == 2 ? red[w][CB - 1][v][c] : red[w][0][v][c + 16]; }
+        const int off = oc < p.r ? ((row0 + acc_row(v, hh)) * p.r + oc) * 2 : kBufNowhere;
         __builtin_amdgcn_raw_buffer_store_b32(pack2_bf16(t0, t1), tres, off, 0, 0);
     }
 }
@@ -269,7 +291,7 @@ struct SmallGrad {
 // steps of 16 columns of dT w, w + 8, ..
 template <bool SHARED>
 __device__ __forceinline__ void dx_tile(const SmallGrad& p, int rb, int tile, float (*red)[2][16][64]) {
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
     const int j = lane & 31, h = lane >> 5, row0 = 32 * rb, col = 64 * tile + 2 * j;
     const rsrc_t tres = make_rsrc(p.dT, (int64_t)p.M * p.r * 2), bres = make_rsrc(p.B, (int64_t)p.r * p.n * 2);
     const int toff = ((row0 + j) * p.r + 8 * h) * 2, boff = (8 * h * p.n + col) * 2;
@@ -329,7 +351,7 @@ struct SmallConv { int N, H, W, Ho, Wo, C, kh, kw, stride; };
 // work-group looks up the pixel of every row once (offsets in `red`, which is free until the sums).
 template <bool GATHER>
 __device__ __forceinline__ void tn_tile(const SmallTn& g, int M, int accumulate, int tile, float (*red)[4][16][64], const SmallConv& cv) {
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, j = lane & 31, h = lane >> 5;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), j = lane & 31, h = lane >> 5;
     const int i0 = 64 * (tile / g.tiles_q), j0 = 64 * (tile % g.tiles_q);
     const rsrc_t rres = make_rsrc(g.R, (int64_t)M * g.P * 2);
     const rsrc_t sres = make_rsrc(g.S, GATHER ? (int64_t)cv.N * cv.H * cv.W * cv.C * 2 : (int64_t)M * g.Q * 2);
@@ -416,7 +438,7 @@ __device__ __forceinline__ void tn_tile(const SmallTn& g, int M, int accumulate,
 
 __global__ __launch_bounds__(64 * kGradWaves, 2) void small_grad_kernel(SmallGrad p) {
     __shared__ float red[kGradWaves / 2][4][16][64];
-    const int wave = threadIdx.x >> 6;
+    const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
     int b = (int)blockIdx.x;
     // the factor gradients first: their contraction is the longer chain
     for (int i = 0; i < p.njobs; ++i) {
@@ -603,7 +625,11 @@ hipError_t launch_lr_small_fwd_gather(const void* image, const PatchGeom& g, con
 hipError_t launch_lr_small_dt(const void* dY, const void* A, void* dT, int64_t M, int m, int r, hipStream_t s) {
     if (!lr_small_supports(M, m, m, r)) return hipErrorInvalidValue;
     const SmallDt d{(const uint16_t*)dY, (const uint16_t*)A, (uint16_t*)dT, (int)M, m, r};
-    hipLaunchKernelGGL(small_dt_kernel, dim3((unsigned)ceil_div(M, 32), (unsigned)ceil_div(r, 64)), dim3(64 * kDtWaves), 0, s, d);
+    // (tiles of 32 columns / 64, backward, us: 197 x 768 -> 2304, r = 96 12.2 / 13.2, 1600 rows 20.2 / 21.3; 94 row blocks x 2 even; past one tile
+    // for each compute unit 64 columns read dY less often: 800 rows, r = 384, 300 tiles 31 / 25, 3000 rows, r = 96, 282 tiles 34 / 27)
+    const int64_t blocks = ceil_div(M, 32);
+    if (blocks * (r / 32) <= 256) hipLaunchKernelGGL(small_dt_kernel<32>, dim3((unsigned)blocks, (unsigned)(r / 32)), dim3(64 * kDtWaves), 0, s, d);
+    else hipLaunchKernelGGL(small_dt_kernel<64>, dim3((unsigned)blocks, (unsigned)ceil_div(r, 64)), dim3(64 * kDtWaves), 0, s, d);
     return hipGetLastError();
 }
 

@@ -39,6 +39,17 @@ def test_backward_of_few_rows(M, m, n, r, accumulate):
             assert torch.equal(a, b) if w else b is None
 
 
+@pytest.mark.parametrize("M,m,n,r", [(5, 1600, 64, 32), (2048, 1984, 64, 128), (2049, 1088, 320, 128), (2720, 576, 64, 96), (2721, 2112, 512, 96)])
+def test_tiles_of_dT_of_either_width(M, m, n, r):
+    # 32 columns up to 256 tiles, 64 beyond; contractions that end at every one of the slabs in flight
+    g = torch.Generator(device="cuda").manual_seed(M + m)
+    rn = lambda std, *s: (torch.randn(s, generator=g, device="cuda") * std).to(BF)
+    X, dY, A, B = rn(1, M, n), rn(1e-2, M, m), rn(r ** -0.5, m, r), rn(n ** -0.5, r, n)
+    dX, _, dB = abt.lr_linear_bwd(dY, X, None, A, B, need_dA=False)
+    dT = dY.double() @ A.double()
+    assert rel(dX, dT @ B.double()) < 2 ** -7 and rel(dB, dT.T @ X.double()) < 2 ** -8
+
+
 def test_not_finite_rows_stay_in_their_rows():
     M, m, n, r = 70, 128, 192, 64
     g = torch.Generator(device="cuda").manual_seed(1)
