@@ -245,6 +245,8 @@ struct GemmF32 {
 // (gemm_f32_partial_bytes each, laid end to end in `partials`) are added in a fixed order by a second
 // launch.  gemm_f32_splits is the split that fills the chip.
 int gemm_f32_splits(const GemmF32& d);
+// The split of a product of the batch's rows (T, dT): few columns, a contraction over a width of the layer.
+int gemm_f32_row_splits(const GemmF32& d);
 size_t gemm_f32_partial_bytes(const GemmF32& d, int splits);
 hipError_t launch_gemm_f32(const GemmF32* problems, const int* splits, int n, float* partials, hipStream_t s);
 hipError_t launch_gemm_f32_one(const GemmF32& d, hipStream_t s);

@@ -10,12 +10,12 @@
 //     of a slab dealt out between its matrix instructions,
 //   * small tiles (64 x 64; 32 x 32 with the four waves sharing out the contraction for launches that
 //     would not give every compute unit a tile), four work-groups per compute unit,
-//   * a contraction over the batch (factor gradients) is split over work-groups; the partial sums are
+//   * a contraction over the batch (factor gradients) or, in a backward pass, over a long width (dT) is split over work-groups; the partial sums are
 //     added in a fixed order by a second launch.
 // Measured: 4096 x 4096 x 1024 279 us = 123 TFLOP/s of the 133 that a large library product reaches;
 // 768 x 3072 x 384 (W = A B of a ViT-B/16 MLP layer) 26 us, 79 us in an earlier form with 128 x 128 tiles
 // and 4-byte loads one slab ahead; the products of a factored layer at M = 3152, m = 3072, n = 768,
-// r = 192: T 15 us, Y 52, dT 55, and dX, dA and dB in one launch 64 and 7; forward and backward together 175 us,
+// r = 192: T 15 us, Y 52, dT 47 and 4, and dX, dA and dB in one launch 64 and 7; forward and backward together 171 us,
 // of the 64 x 256 x 256 layer at r = 32 26 us.
 //
 // LDS: both operands lie [row][k], 16-byte chunks of four k XOR-swizzled by the row; an operand read is
@@ -382,6 +382,24 @@ int gemm_f32_splits(const GemmF32& d) {
     if (s > by_k) s = by_k;
     if (s > 64) s = 64;
     return s < 1 ? 1 : (int)s;
+}
+
+// The time of a product and of the sum of its partial ones, us, fitted to backward passes of 100 to 3152 rows, r = 32 to 384, K = 1024 to 3072, in up
+// to 12 splits (120 shapes: 2.97 ms in all with the splits of this estimate, 2.93 with the best, 3.34 unsplit; none slower by more than
+// 4 %): 32 x 32 tiles cost 11 us per 3072 of the contraction and 0.05 per tile (traffic from L2), 64 x 64 tiles 54 for each round of the compute
+// units.  dT and a dX of 768 columns: 3152 x 3072, r = 192 63.6 -> 59.5 us (594 tiles of 32 x 32; 750 of 64 x 64), 3152 x 2304, r = 384 103 -> 85,
+// 800 x 3072, r = 64 27.7 -> 20.
+int gemm_f32_row_splits(const GemmF32& d) {
+    const int64_t wide = (int64_t)tiles_of(d, Wide::TM, Wide::TN), narrow = (int64_t)tiles_of(d, Small::TM, Small::TN);
+    auto time = [&](int s) {
+        const double k = (double)(ceil_div(ceil_div(d.K, s), 64) * 64) / 3072.0;
+        const double t = use_small(wide * s) ? k * (11.0 + 0.05 * (double)(narrow * s)) : k * 54.0 * (double)ceil_div(wide * s, 256);
+        return s == 1 ? t : t + 3.5 + (s + 1) * 0.7e-6 * (double)d.P * (double)d.Q;
+    };
+    int best = 1;
+    for (int s = 2; s <= 8 && (int64_t)s * 512 <= d.K; ++s)
+        if (time(s) < time(best)) best = s;
+    return best;
 }
 
 size_t gemm_f32_partial_bytes(const GemmF32& d, int splits) {

@@ -101,6 +101,23 @@ def test_split_beside_the_static_scratch(M):
             assert bool(((o.double() - a.T @ b).abs() <= bound).all())
 
 
+# T and dT with a split contraction: one to 3152 rows, tiles of either size, contractions that are not multiples of 4, 64 or the splits, both split, and
+# where the static scratch has no room for all of the partial sums of dT (16385 rows: of two of four)
+@pytest.mark.parametrize("M,m,n,r", [(1, 1024, 64, 32), (65, 3071, 96, 33), (800, 2304, 1500, 64), (3152, 3072, 64, 192), (3152, 2304, 64, 384), (16385, 3072, 64, 255)])
+def test_split_products_of_the_rows(M, m, n, r):
+    g = torch.Generator(device="cuda").manual_seed(M + m + n + r)
+    X, dY, A, B = rnd(g, M, n), rnd(g, M, m), rnd(g, m, r), rnd(g, r, n)
+    dX, dA, dB = abt.lr_linear_bwd(dY, X, None, A, B)
+    out = [torch.full_like(t, 7.0) for t in (dX, dA, dB)]
+    abt.lr_linear_bwd_static(dY, X, None, A, B, *out)
+    Xd, dYd, Ad, Bd = (t.double() for t in (X, dY, A, B))
+    T, dT = Xd @ Bd.T, dYd @ Ad
+    T_err, dT_err = (Xd.abs() @ Bd.abs().T) * (n + 2) * EPS, (dYd.abs() @ Ad.abs()) * (m + 2) * EPS
+    for got in ((dX, dA, dB), out):
+        for o, a, b, err in ((got[0], dT, Bd, dT_err @ Bd.abs()), (got[1], dYd.T, T, dYd.abs().T @ T_err), (got[2], dT.T, Xd, dT_err.T @ Xd.abs())):
+            assert bool(((o.double() - a @ b).abs() <= (a.shape[1] + 4) * EPS * (a.abs() @ b.abs()) + err * (1 + 1e-3)).all())
+
+
 # one launch each way: blocks of 32 rows, 128 columns of the widths, chunks of 256 of the contraction, widths that are not multiples of four, and
 # the sizes next to its limits
 @pytest.mark.parametrize("M,m,n,r", [(1, 1, 1, 1), (31, 127, 129, 32), (32, 512, 511, 5), (33, 256, 512, 32), (64, 255, 257, 31), (64, 257, 256, 32),
