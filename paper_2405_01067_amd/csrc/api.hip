@@ -186,22 +186,24 @@ bool two_products(int64_t rows, int p, int q, int R, bool image) {
 //     Narrow ranks and layers gain least, and lose below the limits here (64 -> 1600, 57148 rows, r = 96 44.9 / 48.1).  From 114688 rows on
 //     the rounds are many and even: from r = 160 on nothing to gain (768 -> 768, 219909 rows, r = 352 282 / 337; 768 -> 3072, 150000 rows,
 //     r = 96 240 / 217).
-//   r = 288 and 352 from 10240 rows on, where the fused kernel is that of the next wider rank in 128-row work-groups (768 -> 3072, 12000
+//   r = 288 and 352 above 10752 rows, where the fused kernel is that of the next wider rank in 128-row work-groups (768 -> 3072, 12000
 //     rows, r = 288 72.6 / 41.2; even with it from 16384 on); r = 160, whose fused kernel has 64-row work-groups (768 -> 3072, 25000
 //     rows 62.7 / 44.4).
-//   Wide results of short contractions, where a fused work-group's time is the stores of Y (768 -> 3072, r = 192): 4096 to 10240 rows (6000
+//   Wide results of short contractions, where a fused work-group's time is the stores of Y (768 -> 3072, r = 192): 4608 to 10240 rows (6000
 //     rows 31.1 / 23.3), 16384 to 22528 (20000 rows 52.8 / 40.6) and, at r = 160 and 192, up to 12800 (12608 rows 32.0 / 30.7; over 116
 //     shapes 0.98 to 1.18 times as fast, mean 1.06).  Above that one round of 64-row work-groups fills the chip (14500 rows, r = 160 33.5 / 34.6,
 //     r = 128 28.7 / 33.4).
+//   The two lower limits lie 512 rows above those of the products for few rows (4096 and 10240): next to these a forward asks for no place for T,
+//   as before.
 bool wide_products(int64_t rows, int p, int q, int R) {
-    if (g_chain_rows.load() != 0 || g_chain_parts.load() != 0 || rows <= 4096 || p < 256 || q < 128) return false;
+    if (g_chain_rows.load() != 0 || g_chain_parts.load() != 0 || rows <= 4608 || p < 256 || q < 128) return false;
     if (rows > 32768) {
         if (R >= 160) return rows <= 114688 && p + q >= (rows <= 49152 ? 704 : 1536);
         if (R == 128) return rows <= 49152 ? p >= 1024 || q > 1024 : p + q >= 3072;
         if (R == 96) return q >= 2304 || p >= 3072 || (rows <= 40960 && p >= 512 && q >= 512 && p + q >= 1280);
         return R == 64 && q >= 2304;
     }
-    if ((R == 288 || R == 352) && rows > 10240 && rows <= 16384) return p + q >= 1280;
+    if ((R == 288 || R == 352) && rows > 10752 && rows <= 16384) return p + q >= 1280;
     if (R == 160 && rows > 16384) return q >= 512 && p + q >= 1472;
     if (rows <= 8192 && R >= 96 && R <= 192) return q >= 1024 && p <= 1920;
     if (rows <= 10240) return ((R >= 64 && R <= 192) || R == 288) && q >= 1344 && q >= 2 * p;

@@ -23,7 +23,7 @@ def layer(M, m, n, r):
 
 # rows per work-group: 32 (the least), 64, more in one round; a last work-group of one row, of all; one and two rounds of the compute units;
 # a result of 256 columns and one more block, of half a block of columns; an odd and an even number of slabs
-@pytest.mark.parametrize("M,m,n,r", [(4097, 1344, 320, 96), (6000, 1088, 1920, 192), (8192, 1344, 256, 128), (10239, 1408, 256, 288), (10240, 1344, 640, 64),
+@pytest.mark.parametrize("M,m,n,r", [(4609, 1344, 320, 96), (6000, 1088, 1920, 192), (8192, 1344, 256, 128), (10239, 1408, 256, 288), (10240, 1344, 640, 64),
                                      (10241, 2304, 256, 160), (12800, 2304, 1152, 192),
                                      (12345, 128, 1152, 288), (16384, 1024, 256, 352), (16385, 1344, 512, 224), (17001, 512, 960, 160),
                                      (20000, 1344, 512, 256), (22528, 1344, 256, 384), (32769, 448, 256, 320), (33333, 2304, 256, 64),
@@ -44,7 +44,7 @@ def test_two_products_of_many_rows(M, m, n, r):
     assert torch.equal(abt.lr_linear_bwd(dY, X, T, A, B, need_dX=False)[2], dB)
 
 
-@pytest.mark.parametrize("G,M,m,n,r", [(2, 2100, 1344, 1344, 96), (3, 11000, 1344, 512, 192), (4, 8200, 448, 256, 352), (8, 5000, 768, 768, 160)])
+@pytest.mark.parametrize("G,M,m,n,r", [(2, 2310, 1344, 1344, 96), (3, 11000, 1344, 512, 192), (4, 8200, 448, 256, 352), (8, 5000, 768, 768, 160)])
 def test_groups_of_many_rows_together(G, M, m, n, r):
     layers = [layer(M + g, m, n, r) for g in range(G)]
     groups = [dict(X=X[:M], A=A, B=B) for X, A, B, _ in layers]
