@@ -14,7 +14,7 @@ namespace {
 
 std::atomic<int> g_max_sweeps{30};
 
-// Chain kernel choice: two products where wide_products or two_products say so; else the narrow-rank kernel where use_narrow / narrow_gather do; else
+// Chain kernel choice: one launch of few_fwd_kernel where few_rows says so, two products where wide_products or two_products do; else the narrow-rank kernel where use_narrow / narrow_gather do; else
 // by choose_chain_shape work-groups of 128 rows (r = 32, 64, 96, 128, and 192 to 384 in the kernel of eight equal waves; from an image 192 and
 // 384 too) or of 64 rows with loader and MFMA waves (r = 32, 64, 96, 128, 160, 192, 256, 320, 384).
 std::atomic<int> g_chain_rows{0};    // 0: automatic; 64 or 128: force that work-group height where the rank allows it
@@ -210,6 +210,39 @@ bool wide_products(int64_t rows, int p, int q, int R) {
     if (rows <= 12800) return (R == 160 || R == 192) && q >= 2304 && q >= 2 * p;
     return rows > 16384 && rows <= 22528 && R >= 64 && q >= 1344 && 2 * q >= 5 * p;
 }
+// Where a few rows go through both products in one launch whose work-groups make the rows of T themselves (lr_few.hip), a round of work-groups of
+// 32 rows and 256 columns of Y (128 above r = 96).  Forward, GPU time in us, the other kernels / this one:
+//                             1 row        197         512          1024         2048
+//     768 -> 2304   r = 32   7.7 / 3.5   8.0 / 4.1   8.2 / 4.3    8.5 / 6.0   10.5 / 8.8
+//                   r = 96    11 / 5.4    12 / 5.9    12 / 6.2   12.2 / 11.0                  (288 work-groups)
+//                   r = 128   14 / 6.2    15 / 6.6  14.6 / 12.2                               (288 work-groups)
+//                   r = 192  7.0 / 7.6   7.7 / 8.3   8.4 / 15.7                               (two launches / one; 288 work-groups)
+//     3072 -> 768   r = 32    13 / 5.3    14 / 5.8    14 / 5.9     10 / 6.2     11 / 7.3
+//                   r = 64    16 / 7.4    16 / 7.9    17 / 8.1     10 / 8.4    11.5 / 10
+//                   r = 96   9.6 / 9.1  10.3 / 9.7  10.5 / 9.9                               (two launches / one)
+//     64 -> 64      r = 64   4.3 / 2.7   4.6 / 3.0   4.7 / 3.0    4.7 / 3.1    4.7 / 3.1
+// Over 300 shapes of 16 to 4096 rows 1.4 times as fast in the mean, none slower.  From r = 96 on not where two_products holds: T alone, which shares its
+// contraction among more work-groups there, took up to 1.4 us longer (3072 columns, r = 96, 10.7 -> 12.1 with dA).
+// From an image over 165 layers and batches 1.5 times as fast in the mean, none slower: 28 x 28 x 128, stride 2, r = 32, 3 images 14.6 / 5.5;
+// 7 x 7 x 64, r = 160, 9 images 19.7 / 7.7.
+// At r = 32 two work-groups share a compute unit (768 -> 3072, 1024 rows 8.7 / 6.4; 3072 -> 768, 3200 rows 12.4 / 11.9).
+bool few_rows(int64_t rows, int p, int q, int R, bool image) {
+    if (g_chain_rows.load() != 0 || g_chain_parts.load() != 0 || rows > 4096 || p > 3072 || R > 192) return false;
+    const int64_t groups = ceil_div(rows, 32) * ceil_div(q, R <= 96 ? 256 : 128);
+    return groups <= (R == 32 ? 512 : 256) && ((R <= 64 && !image) || !two_products(rows, p, q, R, image));
+}
+// Several work-groups read the rows of X and the factors: no output may lie over them.
+bool no_output_over(const ChainProblem& c, int64_t x_bytes, int64_t M, int p, int q, int R) {
+    const void* out[2] = {c.Yout, c.Tout};
+    const int64_t bytes[2] = {M * q * 2, M * R * 2};
+    for (int i = 0; i < 2; ++i)
+        if (overlap(out[i], bytes[i], c.Xin, x_bytes) || overlap(out[i], bytes[i], c.P, (int64_t)R * p * 2) || overlap(out[i], bytes[i], c.Q, (int64_t)q * R * 2))
+            return false;
+    return true;
+}
+bool few_rows(const ChainProblem& c, int64_t M, int p, int q, int R) {
+    return few_rows(M, p, q, R, false) && few_supports(M, p, q, R) && no_output_over(c, M * p * 2, M, p, q, R);
+}
 // T needs a place, and not over the first operand, whose rows several work-groups read.
 bool place_for_T(const ChainProblem* problems, int n, int64_t M, int p, int R) {
     for (int g = 0; g < n; ++g)
@@ -222,6 +255,7 @@ bool two_products(const ChainProblem* problems, int n, int of, int64_t M, int p,
 }
 // Does a forward of these rows go faster with a place for T?
 bool place_pays(int64_t rows, int64_t M, int p, int q, int R) {
+    if (rows == M && few_rows(M, p, q, R, false) && few_supports(M, p, q, R)) return false;
     return (wide_products(rows, p, q, R) && pair_supports(M, p, q, R)) || (two_products(rows, p, q, R, false) && lr_small_supports(M, q, p, R));
 }
 
@@ -246,6 +280,10 @@ hipError_t chain_gather(const void* image, const PatchGeom& g, const void* P, co
     if (Tout && t_pitch == R && two_products(M, p, q, R, true) && lr_small_gather_supports(g, M, q, R) &&
         !overlap(image, (M / (g.RH * g.RW)) * g.H * g.W * g.Cin * 2, Tout, M * R * 2))
         return launch_lr_small_fwd_gather(image, g, P, Q, Yout, Tout, M, q, R, s);
+    const ChainProblem c{image, P, Q, Yout, Tout};
+    if ((!Tout || t_pitch == R) && few_rows(M, p, q, R, true) && few_gather_supports(g, M, q, R) &&
+        no_output_over(c, (M / ((int64_t)g.RH * g.RW)) * g.H * g.W * g.Cin * 2, M, p, q, R))
+        return launch_few_fwd_gather(c, g, M, q, R, s);
     const ChainGather cg{g.H, g.W, g.Cin, 0, g.kh, g.kw, g.sign, g.kh / 2, g.kw / 2, g.RH, g.RW, g.mul, 1, 0, 0, g.RH, g.RW};
     if (g.sign > 0 && narrow_gather(ceil_div(M, 128), g.Cin <= 64 && chain4_window(cg, R, narrow_rows(M)), g.mul, p, q, R)) {
         const GatherProblem one{image, P, Q, Yout, Tout, M, cg};
@@ -269,6 +307,7 @@ hipError_t chain(const void* Xin, const void* P, const void* Q, void* Yout, void
     const ChainProblem one{Xin, P, Q, Yout, Tout};
     if (wide_products(M, p, q, R) && pair_supports(M, p, q, R) && place_for_T(&one, 1, M, p, R))
         return launch_pair_bf16(&one, 1, 1, M, p, q, R, s);
+    if (few_rows(one, M, p, q, R)) return launch_few_fwd(one, M, p, q, R, s);
     if (two_products(&one, 1, 1, M, p, q, R)) return launch_lr_small_fwd(&one, 1, 1, M, p, q, R, s);
     hipError_t e;
     if (narrow_chain(&one, 1, 1, M, p, q, R, s, &e)) return e;
@@ -1028,6 +1067,7 @@ int chain_rows_for_groups(int G, int64_t M, int p, int q, int R) {
 // One launch for the problems with a second stage and one for those without.  again: T for some of the groups, by the rules
 // for all of them.
 hipError_t chain_grouped(const ChainProblem* pr, int G, int64_t M, int p, int q, int R, bool again, hipStream_t s) {
+    if (G == 1 && (pr[0].Yout || pr[0].Tout) && few_rows(pr[0], M, p, q, R)) return launch_few_fwd(pr[0], M, p, q, R, s);
     for (int second = 1; second >= 0; --second) {
         ChainProblem sel[kChainMaxGroups];
         int n = 0;

@@ -189,6 +189,12 @@ hipError_t launch_tn_finish(const TnJob* jobs, int njobs, int R, int accumulate,
 bool pair_supports(int64_t M, int p, int q, int R);
 hipError_t launch_pair_bf16(const ChainProblem* problems, int G, int of, int64_t M, int p, int q, int R, hipStream_t s);
 
+// The chain of a few rows in one launch, R = 32, 64, 96 (lr_few.hip): T, Y or both; neither may lie over an input.
+bool few_supports(int64_t M, int p, int q, int R);
+hipError_t launch_few_fwd(const ChainProblem& c, int64_t M, int p, int q, int R, hipStream_t s);
+bool few_gather_supports(const PatchGeom& g, int64_t M, int q, int R);      // the rows of an image's patch matrix
+hipError_t launch_few_fwd_gather(const ChainProblem& c, const PatchGeom& g, int64_t M, int q, int R, hipStream_t s);
+
 // 32-bit offsets: M, m, n and r against each other
 bool lr_small_supports(int64_t M, int m, int n, int r);
 // The chain for few rows as two products, T and Y or T alone (Yout NULL, for all problems or none); Tout must have a place that lies over no input.
