@@ -76,8 +76,8 @@ const char* abt_status_string(int status);
  * Shapes: M >= 1 arbitrary.  ABT_BF16: m, n multiples of 64 and <= 2^20, r a multiple of 32, r <= 384.
  *         ABT_F32: any positive m, n, r.
  * Workspace: lr_linear_fwd_workspace_bytes, without T_save; 0 for ABT_BF16, which writes nothing there.
- * ABT_BF16, where lr_linear_fwd_wants_T says 1 (few rows, and r = 224, 288, 352): with T_save the two products run one after
- * the other, several times faster; without it T stays on the chip, summed in another order, so that T and Y may differ by a
+ * ABT_BF16, where lr_linear_fwd_wants_T says 1 (some ranges of few and of many rows, and r = 224, 288, 352): with T_save the two products run
+ * one after the other, up to several times faster; without it T stays on the chip, summed in another order, so that T and Y may differ by a
  * rounding of bf16 from those of a call with T_save, and from the T that a backward computes again.
  * ------------------------------------------------------------------------------------- */
 int lr_linear_fwd(const void* X, const void* A, const void* B, void* Y, void* T_save,

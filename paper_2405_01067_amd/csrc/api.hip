@@ -221,15 +221,18 @@ bool wide_products(int64_t rows, int p, int q, int R) {
 //                   r = 64    16 / 7.4    16 / 7.9    17 / 8.1     10 / 8.4    11.5 / 10
 //                   r = 96   9.6 / 9.1  10.3 / 9.7  10.5 / 9.9                               (two launches / one)
 //     64 -> 64      r = 64   4.3 / 2.7   4.6 / 3.0   4.7 / 3.0    4.7 / 3.1    4.7 / 3.1
-// Over 300 shapes of 16 to 4096 rows 1.4 times as fast in the mean, none slower.  From r = 96 on not where two_products holds: T alone, which shares its
+// Over 300 shapes of 16 to 4096 rows 1.4 times as fast in the mean, none slower.  From r = 96 on, and from an image, not where two_products holds: T alone, which shares its
 // contraction among more work-groups there, took up to 1.4 us longer (3072 columns, r = 96, 10.7 -> 12.1 with dA).
 // From an image over 165 layers and batches 1.5 times as fast in the mean, none slower: 28 x 28 x 128, stride 2, r = 32, 3 images 14.6 / 5.5;
 // 7 x 7 x 64, r = 160, 9 images 19.7 / 7.7.
+// Groups of a call, each with factors of its own, over 450 shapes 1.47 times as fast in the mean: four of 40 rows, 640 -> 768, r = 160 15.9 / 6.6; where
+// two_products holds they stay with it at any rank (eight of 197 rows, 3072 -> 768, r = 64 12.7 / 13.6).
 // At r = 32 two work-groups share a compute unit (768 -> 3072, 1024 rows 8.7 / 6.4; 3072 -> 768, 3200 rows 12.4 / 11.9).
-bool few_rows(int64_t rows, int p, int q, int R, bool image) {
+bool few_rows(int G, int64_t M, int p, int q, int R, bool image) {
+    const int64_t rows = G * M;
     if (g_chain_rows.load() != 0 || g_chain_parts.load() != 0 || rows > 4096 || p > 3072 || R > 192) return false;
-    const int64_t groups = ceil_div(rows, 32) * ceil_div(q, R <= 96 ? 256 : 128);
-    return groups <= (R == 32 ? 512 : 256) && ((R <= 64 && !image) || !two_products(rows, p, q, R, image));
+    const int64_t groups = G * ceil_div(M, 32) * ceil_div(q, R <= 96 ? 256 : 128);
+    return groups <= (R == 32 ? 512 : 256) && ((R <= 64 && !image && G == 1) || !two_products(rows, p, q, R, image));
 }
 // Several work-groups read the rows of X and the factors: no output may lie over them.
 bool no_output_over(const ChainProblem& c, int64_t x_bytes, int64_t M, int p, int q, int R) {
@@ -240,8 +243,12 @@ bool no_output_over(const ChainProblem& c, int64_t x_bytes, int64_t M, int p, in
             return false;
     return true;
 }
-bool few_rows(const ChainProblem& c, int64_t M, int p, int q, int R) {
-    return few_rows(M, p, q, R, false) && few_supports(M, p, q, R) && no_output_over(c, M * p * 2, M, p, q, R);
+// (n of the G problems of a call: the rule is that of all of them)
+bool few_rows(const ChainProblem* problems, int n, int G, int64_t M, int p, int q, int R) {
+    if (!few_rows(G, M, p, q, R, false) || !few_supports(M, p, q, R)) return false;
+    for (int g = 0; g < n; ++g)
+        if (!no_output_over(problems[g], M * p * 2, M, p, q, R)) return false;
+    return true;
 }
 // T needs a place, and not over the first operand, whose rows several work-groups read.
 bool place_for_T(const ChainProblem* problems, int n, int64_t M, int p, int R) {
@@ -255,7 +262,7 @@ bool two_products(const ChainProblem* problems, int n, int of, int64_t M, int p,
 }
 // Does a forward of these rows go faster with a place for T?
 bool place_pays(int64_t rows, int64_t M, int p, int q, int R) {
-    if (rows == M && few_rows(M, p, q, R, false) && few_supports(M, p, q, R)) return false;
+    if (few_rows((int)(rows / M), M, p, q, R, false) && few_supports(M, p, q, R)) return false;
     return (wide_products(rows, p, q, R) && pair_supports(M, p, q, R)) || (two_products(rows, p, q, R, false) && lr_small_supports(M, q, p, R));
 }
 
@@ -281,7 +288,7 @@ hipError_t chain_gather(const void* image, const PatchGeom& g, const void* P, co
         !overlap(image, (M / (g.RH * g.RW)) * g.H * g.W * g.Cin * 2, Tout, M * R * 2))
         return launch_lr_small_fwd_gather(image, g, P, Q, Yout, Tout, M, q, R, s);
     const ChainProblem c{image, P, Q, Yout, Tout};
-    if ((!Tout || t_pitch == R) && few_rows(M, p, q, R, true) && few_gather_supports(g, M, q, R) &&
+    if ((!Tout || t_pitch == R) && few_rows(1, M, p, q, R, true) && few_gather_supports(g, M, q, R) &&
         no_output_over(c, (M / ((int64_t)g.RH * g.RW)) * g.H * g.W * g.Cin * 2, M, p, q, R))
         return launch_few_fwd_gather(c, g, M, q, R, s);
     const ChainGather cg{g.H, g.W, g.Cin, 0, g.kh, g.kw, g.sign, g.kh / 2, g.kw / 2, g.RH, g.RW, g.mul, 1, 0, 0, g.RH, g.RW};
@@ -307,7 +314,7 @@ hipError_t chain(const void* Xin, const void* P, const void* Q, void* Yout, void
     const ChainProblem one{Xin, P, Q, Yout, Tout};
     if (wide_products(M, p, q, R) && pair_supports(M, p, q, R) && place_for_T(&one, 1, M, p, R))
         return launch_pair_bf16(&one, 1, 1, M, p, q, R, s);
-    if (few_rows(one, M, p, q, R)) return launch_few_fwd(one, M, p, q, R, s);
+    if (few_rows(&one, 1, 1, M, p, q, R)) return launch_few_fwd(&one, 1, M, p, q, R, s);
     if (two_products(&one, 1, 1, M, p, q, R)) return launch_lr_small_fwd(&one, 1, 1, M, p, q, R, s);
     hipError_t e;
     if (narrow_chain(&one, 1, 1, M, p, q, R, s, &e)) return e;
@@ -1067,7 +1074,6 @@ int chain_rows_for_groups(int G, int64_t M, int p, int q, int R) {
 // One launch for the problems with a second stage and one for those without.  again: T for some of the groups, by the rules
 // for all of them.
 hipError_t chain_grouped(const ChainProblem* pr, int G, int64_t M, int p, int q, int R, bool again, hipStream_t s) {
-    if (G == 1 && (pr[0].Yout || pr[0].Tout) && few_rows(pr[0], M, p, q, R)) return launch_few_fwd(pr[0], M, p, q, R, s);
     for (int second = 1; second >= 0; --second) {
         ChainProblem sel[kChainMaxGroups];
         int n = 0;
@@ -1081,6 +1087,8 @@ hipError_t chain_grouped(const ChainProblem* pr, int G, int64_t M, int p, int q,
         // (the rule and the split of the rows are those of all groups: the order of the sums of T is the same for some of them)
         if (wide_products(G * M, p, q, R) && pair_supports(M, p, q, R) && place_for_T(sel, n, M, p, R)) {
             e = launch_pair_bf16(sel, n, G, M, p, q, R, s);
+        } else if (few_rows(sel, n, G, M, p, q, R)) {
+            e = launch_few_fwd(sel, n, M, p, q, R, s);
         } else if (two_products(sel, n, of, M, p, q, R)) {
             e = launch_lr_small_fwd(sel, n, of, M, p, q, R, s);
         } else if (!narrow_chain(sel, n, of, M, p, q, R, s, &e)) {

@@ -189,9 +189,9 @@ hipError_t launch_tn_finish(const TnJob* jobs, int njobs, int R, int accumulate,
 bool pair_supports(int64_t M, int p, int q, int R);
 hipError_t launch_pair_bf16(const ChainProblem* problems, int G, int of, int64_t M, int p, int q, int R, hipStream_t s);
 
-// The chain of a few rows in one launch, R = 32, 64, 96 (lr_few.hip): T, Y or both; neither may lie over an input.
+// The chain of a few rows in one launch, R <= 192 (lr_few.hip): T, Y or both (Yout NULL for all problems or none); neither may lie over an input.
 bool few_supports(int64_t M, int p, int q, int R);
-hipError_t launch_few_fwd(const ChainProblem& c, int64_t M, int p, int q, int R, hipStream_t s);
+hipError_t launch_few_fwd(const ChainProblem* problems, int G, int64_t M, int p, int q, int R, hipStream_t s);
 bool few_gather_supports(const PatchGeom& g, int64_t M, int q, int R);      // the rows of an image's patch matrix
 hipError_t launch_few_fwd_gather(const ChainProblem& c, const PatchGeom& g, int64_t M, int q, int R, hipStream_t s);
 

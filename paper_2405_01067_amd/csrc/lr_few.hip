@@ -56,14 +56,21 @@ struct FewCfg {
 // (mul y + ky - kh / 2, mul x + kx - kw / 2), zero outside the image; a piece of 32 columns lies in one tap (C is a multiple of 64).
 struct FewImage { int H, W, C, kh, kw, RH, RW, mul, bytes; };
 
+struct FewPtrs { const uint16_t* X[kChainMaxGroups]; const uint16_t* P[kChainMaxGroups]; const uint16_t* Q[kChainMaxGroups]; uint16_t* Y[kChainMaxGroups]; uint16_t* T[kChainMaxGroups]; };
+
 template <int R, bool GATHER>
-__global__ __launch_bounds__(FewCfg<R>::NW * 64) void few_fwd_kernel(const uint16_t* X, const uint16_t* P, const uint16_t* Q, uint16_t* Y, uint16_t* T, int M, int p, int q, int parts,
+__global__ __launch_bounds__(FewCfg<R>::NW * 64) void few_fwd_kernel(FewPtrs ptrs, int M, int p, int q, int parts,
                                                                      FewImage im) {
     using L = FewCfg<R>;
     constexpr int RB = L::RB, NL = L::NL, NW = L::NW;
     extern __shared__ __align__(1024) unsigned char lds[];
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int lj = lane & 31, lh = lane >> 5;
+    const uint16_t* const X = ptrs.X[blockIdx.y];
+    const uint16_t* const P = ptrs.P[blockIdx.y];
+    const uint16_t* const Q = ptrs.Q[blockIdx.y];
+    uint16_t* const Y = ptrs.Y[blockIdx.y];
+    uint16_t* const T = ptrs.T[blockIdx.y];
     // block b runs on XCD b % 8: each takes a contiguous eighth of the (rows, columns), so that the parts of a row block share X through one L2
     int part = blockIdx.x;
     {
@@ -192,7 +199,7 @@ __global__ __launch_bounds__(FewCfg<R>::NW * 64) void few_fwd_kernel(const uint1
 }
 
 template <int R, bool GATHER>
-hipError_t launch_few_r(const ChainProblem& c, int M, int p, int q, const FewImage& im, hipStream_t s) {
+hipError_t launch_few_r(const FewPtrs& c, int G, int M, int p, int q, const FewImage& im, hipStream_t s) {
     using L = FewCfg<R>;
     static std::atomic<bool> attr_set{false};
     if (!attr_set.load(std::memory_order_acquire)) {
@@ -200,21 +207,28 @@ hipError_t launch_few_r(const ChainProblem& c, int M, int p, int q, const FewIma
         if (e != hipSuccess) return e;
         attr_set.store(true, std::memory_order_release);
     }
-    const int parts = c.Yout ? (q + L::NC - 1) / L::NC : 1;
-    hipLaunchKernelGGL((few_fwd_kernel<R, GATHER>), dim3((unsigned)(parts * ((M + 31) / 32))), dim3(64 * L::NW), L::lds, s, (const uint16_t*)c.Xin, (const uint16_t*)c.P, (const uint16_t*)c.Q, (uint16_t*)c.Yout,
-                       (uint16_t*)c.Tout, M, p, q, parts, im);
+    const int parts = c.Y[0] ? (q + L::NC - 1) / L::NC : 1;
+    hipLaunchKernelGGL((few_fwd_kernel<R, GATHER>), dim3((unsigned)(parts * ((M + 31) / 32)), (unsigned)G), dim3(64 * L::NW), L::lds, s, c, M, p, q, parts, im);
     return hipGetLastError();
 }
 
 template <bool GATHER>
-hipError_t launch_few(const ChainProblem& c, int M, int p, int q, int R, const FewImage& im, hipStream_t s) {
+hipError_t launch_few(const ChainProblem* problems, int G, int M, int p, int q, int R, const FewImage& im, hipStream_t s) {
+    if (G < 1 || G > kChainMaxGroups) return hipErrorInvalidValue;
+    FewPtrs c{};
+    for (int g = 0; g < G; ++g) {
+        const ChainProblem& f = problems[g];
+        if ((!f.Yout && !f.Tout) || (f.Yout != nullptr) != (problems[0].Yout != nullptr)) return hipErrorInvalidValue;
+        c.X[g] = (const uint16_t*)f.Xin; c.P[g] = (const uint16_t*)f.P; c.Q[g] = (const uint16_t*)f.Q;
+        c.Y[g] = (uint16_t*)f.Yout; c.T[g] = (uint16_t*)f.Tout;
+    }
     switch (R / 32) {
-        case 1: return launch_few_r<32, GATHER>(c, M, p, q, im, s);
-        case 2: return launch_few_r<64, GATHER>(c, M, p, q, im, s);
-        case 3: return launch_few_r<96, GATHER>(c, M, p, q, im, s);
-        case 4: return launch_few_r<128, GATHER>(c, M, p, q, im, s);
-        case 5: return launch_few_r<160, GATHER>(c, M, p, q, im, s);
-        case 6: return launch_few_r<192, GATHER>(c, M, p, q, im, s);
+        case 1: return launch_few_r<32, GATHER>(c, G, M, p, q, im, s);
+        case 2: return launch_few_r<64, GATHER>(c, G, M, p, q, im, s);
+        case 3: return launch_few_r<96, GATHER>(c, G, M, p, q, im, s);
+        case 4: return launch_few_r<128, GATHER>(c, G, M, p, q, im, s);
+        case 5: return launch_few_r<160, GATHER>(c, G, M, p, q, im, s);
+        case 6: return launch_few_r<192, GATHER>(c, G, M, p, q, im, s);
     }
     return hipErrorInvalidValue;
 }
@@ -225,9 +239,9 @@ bool few_supports(int64_t M, int p, int q, int R) {
     return M >= 1 && M <= 8192 && p % 64 == 0 && q % 64 == 0 && p >= 64 && q >= 64 && p <= (1 << 20) && q <= (1 << 20) && R % 32 == 0 && R >= 32 && R <= 192;
 }
 
-hipError_t launch_few_fwd(const ChainProblem& c, int64_t M, int p, int q, int R, hipStream_t s) {
-    if (!few_supports(M, p, q, R) || (!c.Yout && !c.Tout)) return hipErrorInvalidValue;
-    return launch_few<false>(c, (int)M, p, q, R, FewImage{}, s);
+hipError_t launch_few_fwd(const ChainProblem* problems, int G, int64_t M, int p, int q, int R, hipStream_t s) {
+    if (!few_supports(M, p, q, R)) return hipErrorInvalidValue;
+    return launch_few<false>(problems, G, (int)M, p, q, R, FewImage{}, s);
 }
 
 bool few_gather_supports(const PatchGeom& g, int64_t M, int q, int R) {
@@ -237,9 +251,9 @@ bool few_gather_supports(const PatchGeom& g, int64_t M, int q, int R) {
 }
 
 hipError_t launch_few_fwd_gather(const ChainProblem& c, const PatchGeom& g, int64_t M, int q, int R, hipStream_t s) {
-    if (!few_gather_supports(g, M, q, R) || (!c.Yout && !c.Tout)) return hipErrorInvalidValue;
+    if (!few_gather_supports(g, M, q, R)) return hipErrorInvalidValue;
     const FewImage im{g.H, g.W, g.Cin, g.kh, g.kw, g.RH, g.RW, g.mul, (int)((M / ((int64_t)g.RH * g.RW)) * g.H * g.W * g.Cin * 2)};
-    return launch_few<true>(c, (int)M, g.kh * g.kw * g.Cin, q, R, im, s);
+    return launch_few<true>(&c, 1, (int)M, g.kh * g.kw * g.Cin, q, R, im, s);
 }
 
 }  // namespace abt

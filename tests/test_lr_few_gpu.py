@@ -48,6 +48,20 @@ def test_outputs_over_inputs_and_rows_that_are_not_finite(r):
     assert torch.equal(Y2[:-1], Y[:-1]) and bool(torch.isinf(T2[-1]).all()) and not bool(torch.isfinite(Y2[-1]).any())
 
 
+@pytest.mark.parametrize("G,M,m,n,r", [(2, 33, 512, 320, 96), (8, 65, 640, 192, 32), (3, 100, 320, 768, 128), (4, 197, 2304, 768, 96), (5, 197, 2304, 768, 96)])
+def test_groups_in_one_launch(G, M, m, n, r):
+    layers = [layer(M, m, n, r) for _ in range(G)]
+    groups = [dict(X=X + g, A=A, B=B) for g, (X, A, B, _) in enumerate(layers)]
+    outs = abt.lr_linear_fwd_grouped(groups)
+    for e, (Y, T) in zip(groups, outs):
+        assert rel(T, e["X"].double() @ e["B"].double().T) < 2 ** -8 and rel(Y, T.double() @ e["A"].double().T) < 2 ** -8
+    for (Y, _), (Y2, _) in zip(outs, abt.lr_linear_fwd_grouped(groups, save_T=False)):
+        assert torch.equal(Y, Y2)
+    grad = lambda keep: abt.lr_linear_bwd_grouped([dict(e, dY=l[3], T=o[1] if keep(i) else None, dA=True) for i, (e, l, o) in enumerate(zip(groups, layers, outs))])
+    for a, b in zip(grad(lambda i: True), grad(lambda i: i == 0)):
+        assert torch.equal(a[1], b[1])
+
+
 def patches(act, w, stride):
     N, H, W, C = act.shape
     h = w // 2
