@@ -32,11 +32,11 @@ METRIC = "factored fwd+bwd TFLOP/s (% bf16 MFMA peak) + ab_merge ms per ViT-B/16
 PEAK_BF16_TFLOPS = 2500.0   # MI355X dense bf16 MFMA
 PEAK_HBM_GBS = 8000.0       # MI355X HBM3E
 CACHE_BYTES = 256 << 20     # last-level cache: a rotated working set must exceed it
-# HBM bytes of one launch of the dominant kernel (forward chain of fc1 at r = 384, M = 50432) from two
+# HBM bytes of one call of the dominant kernels (forward of fc1 at r = 384, M = 50432: two launches) from two
 # rocprofv3 --pmc runs of `bench.py --only-launch fc1_r384 --pmc-copy` (profiles/chain_fwd_pmc_counters.txt,
-# second table): FETCH_SIZE 58308.8 KiB x 2.00 (the factor that makes a plain 256 MiB copy read 256 MiB)
-# + WRITE_SIZE 340459.5 KiB x 1.00.  A stored measurement: re-collect it when the kernel changes.
-DOMINANT_TRAFFIC_BYTES = int((58308.8 * 2.0 + 340459.5) * 1024)
+# third table): FETCH_SIZE 40199.6 and 33700.2 KiB x 2.00 (the factor that makes a plain 256 MiB copy read 256 MiB)
+# + WRITE_SIZE 37824.0 and 302592.1 KiB x 1.00.  A stored measurement: re-collect it when the kernels change.
+DOMINANT_TRAFFIC_BYTES = int(((40199.6 + 33700.2) * 2.0 + 37824.0 + 302592.1) * 1024)
 
 
 def main():
@@ -266,8 +266,8 @@ def main():
         cases = [case_report(name, st) for name, st in steps3]
         summed_ms = sum(cs["ms"] for cs in cases)
 
-        # dominant kernel of a step: the fused chain kernel at R = 384 on the widest layer (fc1: the
-        # forward launch T = X B^T, Y = T A^T; the backward runs the same kernel for dT, dX).  The case
+        # dominant kernels of a step: the two products at R = 384, here on the widest layer (fc1: the
+        # forward T = X B^T, Y = T A^T; the backward runs the same kernels for dT, dX).  The case
         # is MFMA-bound (474 flop per algorithmic byte against a ridge of 312).
         dom_name = "fc1_r384"
         dom = dict(steps3)[dom_name]
@@ -275,15 +275,15 @@ def main():
         dom_flops = 2.0 * dom.M * dom.r * (dom.m + dom.n)
         achieved = dom_flops / (dom_avg * 1e-3) / 1e12
         roofline = {
-            "kernel": "chain3_bf16_kernel<384> (lr_linear_fwd of fc1 at r = 384, M = 50432: "
-                      "T = X B^T and Y = T A^T fused, one launch per call)",
+            "kernel": "contract_kernel<384> and expand_kernel<384> (lr_linear_fwd of fc1 at r = 384, M = 50432: "
+                      "T = X B^T, then Y = T A^T, two launches per call)",
             "bound": "mfma", "achieved": round(achieved, 1), "peak": PEAK_BF16_TFLOPS, "unit": "TFLOP/s",
             "frac": round(achieved / PEAK_BF16_TFLOPS, 4), "traffic": DOMINANT_TRAFFIC_BYTES,
         "traffic_source": "stored measurement, not live: profiles/chain_fwd_pmc_counters.txt",
             "algorithmic_flops_per_launch": dom_flops, "algorithmic_bytes_per_launch": dom.bytes_fwd,
             "avg_launch_ms": round(dom_avg, 5),
             "hbm_frac": round(dom.bytes_fwd / (dom_avg * 1e-3) / 1e9 / PEAK_HBM_GBS, 4),
-            "profile": "profiles/chain3_r384_cfg3_fc1_kernel_trace.txt",
+            "profile": "profiles/step_cfg3_kernel_trace.txt",
         }
 
         out = {
