@@ -167,19 +167,28 @@ __global__ __launch_bounds__(256) void finish32_kernel(const LayerDev* __restric
         A[j][i] = gload(L.LA + j * 32 + i);
         B[j][i] = gload(L.GB + j * 32 + i);
     }
-    if (t < 32) perm[t] = t;
     __syncthreads();
     if (t < 64) {                                         // one wave: lanes l and l + 32 do the same
         double ss = 0.0;
 #pragma unroll 8
         for (int k = 0; k < 32; ++k) ss = fma(C[i][k], C[i][k], ss);
-        const double mine = sqrt(ss);
-        int at = 0;                                       // place in descending order (ties: lower index first)
-        for (int j = 0; j < 32; ++j) {
-            const double other = __shfl(mine, j, 64);
-            at += other > mine || (other == mine && j < i) ? 1 : 0;
-        }
-        if (lane < 32) { key[at] = mine; perm[at] = i; }
+        // Bitonic sort, descending (ties: lower index first), by the comparisons of the sort for all sizes: it only exchanges entries, so that values
+        // which compare false against any other (NaN) come out too, each once and in the same places as there.
+        double mine = sqrt(ss);
+        int from = i;
+#pragma unroll
+        for (int size = 2; size <= 32; size <<= 1)
+#pragma unroll
+            for (int stride = size >> 1; stride > 0; stride >>= 1) {
+                const double other = __shfl_xor(mine, stride, 64);
+                const int other_from = __shfl_xor(from, stride, 64);
+                const bool low = (i & stride) == 0;       // the pair's lower place is this lane's
+                const double klo = low ? mine : other, khi = low ? other : mine;
+                const int ilo = low ? from : other_from, ihi = low ? other_from : from;
+                const bool lo_first = klo > khi || (klo == khi && ilo < ihi);
+                if (lo_first != ((i & size) == 0)) { mine = other; from = other_from; }
+            }
+        if (lane < 32) { key[i] = mine; perm[i] = from; }
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
         __builtin_amdgcn_wave_barrier();
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");

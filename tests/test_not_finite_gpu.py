@@ -50,3 +50,31 @@ def test_pixels_of_a_convolution(N, H, W, C, r, stride):
     hit = torch.zeros((N, H, W), dtype=torch.bool, device="cuda")
     hit[1, 3 * stride - 1:3 * stride + 2, 2 * stride - 1:2 * stride + 2] = True
     assert bool((dAct[hit] == float("-inf")).all()) and bool(torch.isfinite(dAct[~hit]).all())
+
+
+# A merge of a rank-32 layer, whose sorted values must be those of this call and no others.  Every column of the core is then not finite, or, with
+# the fault in B, one is zero; the stages for all sizes, taken when a layer of another rank is in the batch, do the same.
+@pytest.mark.parametrize("side", ["A", "B"])
+@pytest.mark.parametrize("value", [float("nan"), float("inf"), float("-inf")])
+@pytest.mark.parametrize("row,col", [(0, 0), (17, 31), (31, 5)])
+def test_merge_of_a_core_of_32(side, value, row, col):
+    g = torch.Generator(device="cuda").manual_seed(row + col)
+    rn = lambda *s: torch.randn(s, generator=g, device="cuda")
+    lay = lambda k, scale: {"A_copies": [scale * rn(96, k) for _ in range(2)], "B_copies": [rn(k, 80) for _ in range(2)], "tau": 0.3}
+    bad, other = lay(32, 1.0), lay(64, 1.0)
+    bad[side + "_copies"][1][row, col] = value
+    runs = []
+    for scale in (1.0, 1e3):                              # what merges before it leave behind
+        abt.ab_merge_batched([lay(32, scale) for _ in range(300)])
+        runs.append(abt.ab_merge_batched([bad])[0])
+    for out in runs + [abt.ab_merge_batched([bad, other])[0]]:
+        assert not bool((torch.isfinite(out["S"]) & (out["S"] != 0)).any())
+        assert int(out["k"]) == 1                         # no value passes the comparison with the largest
+    first, again = runs
+    for name in ("S", "k", "A", "B"):
+        assert torch.equal(first[name].view(torch.int32), again[name].view(torch.int32))
+    # a layer beside it is not touched
+    good = lay(32, 1.0)
+    alone = abt.ab_merge_batched([good])[0]
+    beside = abt.ab_merge_batched([bad, good])[1]
+    assert all(torch.equal(alone[name], beside[name]) for name in ("S", "k", "A", "B"))
