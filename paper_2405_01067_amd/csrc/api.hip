@@ -373,9 +373,9 @@ bool tiny_f32(int64_t M, int64_t m, int64_t n, int64_t r, std::initializer_list<
 // fp32 backward: dT, T (each M x r) and the partial sums of the factor gradients, whose contraction over
 // the batch is split over work-groups.  `limit`: in the static scratch array the split only takes what dT and T
 // leave of it, so that every shape that fits without one is served; a workspace of the caller's has room for the
-// split that fills the chip (whole backward, 256 x 256, r = 256, 32768 rows: 285 us; 783 without a split).  The partial sums of T and dT
-// themselves, where their contraction is split too, are added before the others come, in the same place.
-struct BwdLayoutF32 { size_t dT, T, partials, total; int split_T, split_dT, split_A, split_B; };
+// split that fills the chip (whole backward, 256 x 256, r = 256, 32768 rows: 285 us; 783 without a split).  The partial sums of dT
+// itself, where its contraction is split too, are added before the others come, in the same place.  T again is not split: its sums are the forward's.
+struct BwdLayoutF32 { size_t dT, T, partials, total; int split_dT, split_A, split_B; };
 
 GemmF32 grad_A_f32(const float* dY, const float* T, float* dA, int64_t M, int64_t m, int64_t r, int acc) {
     return gemm(dY, T, dA, m, r, M, m, r, r, 1, 0, acc);
@@ -391,18 +391,15 @@ BwdLayoutF32 bwd_layout_f32(int64_t M, int64_t m, int64_t n, int64_t r, size_t l
     const GemmF32 a = grad_A_f32(nullptr, nullptr, nullptr, M, m, r, 0), b = grad_B_f32(nullptr, nullptr, nullptr, M, n, r, 0);
     w.split_A = gemm_f32_splits(a);
     w.split_B = gemm_f32_splits(b);
-    const GemmF32 t = gemm(nullptr, nullptr, nullptr, M, r, n, n, n, r, 0, 1, 0), d = gemm(nullptr, nullptr, nullptr, M, r, m, m, r, r, 0, 0, 0);
-    w.split_T = gemm_f32_row_splits(t);
+    const GemmF32 d = gemm(nullptr, nullptr, nullptr, M, r, m, m, r, r, 0, 0, 0);
     w.split_dT = gemm_f32_row_splits(d);
-    auto fit = [&](const GemmF32& p, int& sp, const GemmF32& q, int& sq) {
-        auto bytes = [&] { return gemm_f32_partial_bytes(p, sp) + gemm_f32_partial_bytes(q, sq); };
-        while (w.partials + bytes() > limit && (sp > 1 || sq > 1)) {
-            sp = sp > 1 ? sp / 2 : 1;
-            sq = sq > 1 ? sq / 2 : 1;
-        }
-        return bytes();
-    };
-    const size_t first = fit(t, w.split_T, d, w.split_dT), second = fit(a, w.split_A, b, w.split_B);
+    while (w.partials + gemm_f32_partial_bytes(d, w.split_dT) > limit && w.split_dT > 1) w.split_dT /= 2;
+    auto bytes = [&] { return gemm_f32_partial_bytes(a, w.split_A) + gemm_f32_partial_bytes(b, w.split_B); };
+    while (w.partials + bytes() > limit && (w.split_A > 1 || w.split_B > 1)) {
+        w.split_A = w.split_A > 1 ? w.split_A / 2 : 1;
+        w.split_B = w.split_B > 1 ? w.split_B / 2 : 1;
+    }
+    const size_t first = gemm_f32_partial_bytes(d, w.split_dT), second = bytes();
     w.total = w.partials + (first > second ? first : second);
     return w;
 }
@@ -970,14 +967,21 @@ int linear_bwd(const void* dY, const void* X, const void* T, const void* A, cons
         const float* Tp = (const float*)T;
         GemmF32 g[3];
         int split[3], k = 0;
+        // T again: unsplit, and in tiles of the size that the forward takes, so that it has the bits of the forward's
         if (!Tp && dA) {
             float* Tw = (float*)(ws + w.T);
-            split[k] = w.split_T;
+            split[k] = 1;
             g[k++] = gemm((const float*)X, (const float*)B, Tw, M, r, n, n, n, r, 0, 1, 0);
             Tp = Tw;
         }
         if (dX || dB) { split[k] = w.split_dT; g[k++] = gemm((const float*)dY, (const float*)A, dT, M, r, m, m, r, r, 0, 0, 0); }
         float* const partials = (float*)(ws + w.partials);
+        if (k == 2 && !gemm_f32_first_as_alone(g, split, k)) {
+            if (launch_gemm_f32_one(g[0], s) != hipSuccess) return ABT_EHIP;
+            g[0] = g[1];
+            split[0] = split[1];
+            k = 1;
+        }
         if (k && launch_gemm_f32(g, split, k, partials, s) != hipSuccess) return ABT_EHIP;
         // an output over an operand of the second launch is written after its readers: one product after the other
         const void* out[3] = {dX, dA, dB};

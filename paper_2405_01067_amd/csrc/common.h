@@ -251,11 +251,13 @@ struct GemmF32 {
 // (gemm_f32_partial_bytes each, laid end to end in `partials`) are added in a fixed order by a second
 // launch.  gemm_f32_splits is the split that fills the chip.
 int gemm_f32_splits(const GemmF32& d);
-// The split of a product of the batch's rows (T, dT): few columns, a contraction over a width of the layer.
+// The split of dT: few columns, a contraction over a width of the layer.
 int gemm_f32_row_splits(const GemmF32& d);
 size_t gemm_f32_partial_bytes(const GemmF32& d, int splits);
 hipError_t launch_gemm_f32(const GemmF32* problems, const int* splits, int n, float* partials, hipStream_t s);
 hipError_t launch_gemm_f32_one(const GemmF32& d, hipStream_t s);
+// Are the sums of the first problem in the order of launch_gemm_f32_one, if it is not split?
+bool gemm_f32_first_as_alone(const GemmF32* problems, const int* splits, int n);
 // n problems in one launch: build the table on the host (n * gemm_f32_desc_bytes() bytes), copy it to the
 // device, then launch from the device copy.
 struct GemmF32Table { int n, tiles; bool small, vec; };

@@ -369,6 +369,12 @@ void launch_form(bool small, bool vec, int slots, const GemmF32Dev* table, const
 // 64 x 64, K = 768: 19.1 us against 17.1; K = 3072: 62.8 against 47.2; 432 tiles, K = 384: 19.5 against 24.2)
 bool use_small(int64_t wide_tiles) { return wide_tiles < 256; }
 
+int64_t wide_tiles_of(const GemmF32* p, const int* splits, int n) {
+    int64_t tiles = 0;
+    for (int i = 0; i < n; ++i) tiles += (int64_t)tiles_of(p[i], Wide::TM, Wide::TN) * (splits ? splits[i] : 1);
+    return tiles;
+}
+
 }  // namespace
 
 int gemm_f32_splits(const GemmF32& d) {
@@ -406,16 +412,16 @@ size_t gemm_f32_partial_bytes(const GemmF32& d, int splits) {
     return splits > 1 ? align_up((size_t)splits * d.P * d.Q * sizeof(float), 256) : 0;
 }
 
+bool gemm_f32_first_as_alone(const GemmF32* p, const int* splits, int n) { return use_small(wide_tiles_of(p, splits, n)) == use_small(wide_tiles_of(p, nullptr, 1)); }
+
 hipError_t launch_gemm_f32(const GemmF32* p, const int* splits, int n, float* partials, hipStream_t s) {
     if (n < 1 || n > kGemmArgs) return hipErrorInvalidValue;
-    int64_t wide_tiles = 0;
     bool any_split = false, vec = true;
     for (int i = 0; i < n; ++i) {
-        wide_tiles += (int64_t)tiles_of(p[i], Wide::TM, Wide::TN) * (splits ? splits[i] : 1);
         if (splits && splits[i] > 1) any_split = true;
         vec = vec && vec_ok(p[i]);
     }
-    const bool small = use_small(wide_tiles);
+    const bool small = use_small(wide_tiles_of(p, splits, n));
     const int tm = small ? Small::TM : Wide::TM, tn = small ? Small::TN : Wide::TN;
     GemmF32Args a{};
     int slots = 0;

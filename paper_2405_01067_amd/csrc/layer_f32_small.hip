@@ -8,7 +8,8 @@
 //
 // v_mfma_f32_32x32x2: A operand lane l = A[l % 32][l / 32], B operand = B[l / 32][l % 32], accumulator register v = C[8 (v / 4) + 4 (l / 32) + v % 4][l % 32].
 // Instruction i of a group of eight k takes k = 4 h + i from the lanes of half h, the same permutation on both sides: one 16-byte LDS read
-// per operand and group.
+// per operand and group.  All sums are in the order of the 32 x 32 tiles of gemm_f32.hip (four parts, two groups of each 64 k; their sum), which
+// serve the calls that do not come here: whether one does (its T kept or not, an output over an input) changes no bit.
 #include "common.h"
 
 namespace abt {
@@ -102,12 +103,14 @@ __device__ __forceinline__ void rows_of_T(TinyLds& sh, const float* P, const flo
         }
         __syncthreads();
         const int groups = K - k0 < CH ? (K - k0 + 7) / 8 : CH / 8;
-        for (int g = wave; g < groups; g += 4) {          // the waves share out the contraction
-            const f32x4 a = *reinterpret_cast<const f32x4*>(sh.P + li * PITCH + 8 * g + 4 * lh);
-            const f32x4 b = *reinterpret_cast<const f32x4*>(sh.F + li * PITCH + 8 * g + 4 * lh);
+        for (int g0 = 2 * wave; g0 < groups; g0 += 8)     // the waves share out the contraction, two groups of each 64 columns
 #pragma unroll
-            for (int i = 0; i < 4; ++i) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a[i], b[i], acc, 0, 0, 0);
-        }
+            for (int g = g0; g < g0 + 2; ++g) {
+                const f32x4 a = *reinterpret_cast<const f32x4*>(sh.P + li * PITCH + 8 * g + 4 * lh);
+                const f32x4 b = *reinterpret_cast<const f32x4*>(sh.F + li * PITCH + 8 * g + 4 * lh);
+#pragma unroll
+                for (int i = 0; i < 4; ++i) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a[i], b[i], acc, 0, 0, 0);
+            }
     }
 #pragma unroll
     for (int v = 0; v < 16; ++v) sh.red[wave][v * 64 + lane] = acc[v];
@@ -134,13 +137,15 @@ __device__ __forceinline__ void column_operands(float (&f)[N][4], const float* m
             f[g][i] = gload(m + (int64_t)(k < rows ? k : 0) * ld + (col < cols ? col : 0));
         }
 }
-// C[32 x 32] of a wave over `rows` k: a(g) gives the first operand's four values of group g
+// C[32 x 32] of a wave over `rows` k: a(g) gives the first operand's four values of group g.  A sum for each two groups, added in order.
 template <int N, class A>
 __device__ __forceinline__ f32x16 tile_product(A&& a, const float (&f)[N][4], int rows) {
     const int lh = (threadIdx.x >> 5) & 1;
-    f32x16 acc;
+    f32x16 acc[N / 2];
 #pragma unroll
-    for (int v = 0; v < 16; ++v) acc[v] = 0.0f;
+    for (int w = 0; w < N / 2; ++w)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) acc[w][v] = 0.0f;
 #pragma unroll
     for (int g = 0; g < N; ++g) {
         if (8 * g >= rows) break;
@@ -148,10 +153,12 @@ __device__ __forceinline__ f32x16 tile_product(A&& a, const float (&f)[N][4], in
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
             const bool in = 8 * g + 4 * lh + i < rows;    // past the contraction both sides are zero
-            acc = __builtin_amdgcn_mfma_f32_32x32x2f32(in ? x[i] : 0.0f, in ? f[g][i] : 0.0f, acc, 0, 0, 0);
+            acc[g / 2] = __builtin_amdgcn_mfma_f32_32x32x2f32(in ? x[i] : 0.0f, in ? f[g][i] : 0.0f, acc[g / 2], 0, 0, 0);
         }
     }
-    return acc;
+#pragma unroll
+    for (int w = 1; w < N / 2; ++w) acc[0] += acc[w];
+    return acc[0];
 }
 template <class F>
 __device__ __forceinline__ void each_value(const f32x16& acc, F&& f) {

@@ -146,3 +146,23 @@ def test_smallest_layers(M, m, n, r, accumulate):
     for which in ((True, False, True), (False, True, False), (False, False, True), (True, False, False)):
         for a, b, w in zip(run(need_dX=which[0], need_dA=which[1], need_dB=which[2]), (dX, dA, dB), which):
             assert (torch.equal(a, b) or M > 64 or r > 32 or n > 512) if w else a is None
+
+
+# T again is the T of the forward, bit for bit, whatever is asked for with it: one launch each way, tiles of either size alone and beside dT, a
+# contraction that is long against the rows
+@pytest.mark.parametrize("M,m,n,r", [(64, 256, 256, 32), (33, 130, 511, 7), (64, 512, 512, 32), (100, 64, 1024, 32), (800, 64, 3072, 64), (3152, 3072, 768, 192),
+                                     (3152, 768, 2304, 384), (1030, 200, 96, 36), (300, 131, 512, 36)])
+def test_T_again_is_the_T_of_the_forward(M, m, n, r):
+    g = torch.Generator(device="cuda").manual_seed(M + m + n + r)
+    X, dY, A, B = rnd(g, M, n), rnd(g, M, m), rnd(g, m, r), rnd(g, r, n)
+    T = abt.lr_linear_fwd(X, A, B)[1]
+    # (rows of dY with a single one: dA is then rows of T, whose sum has one term)
+    pick = torch.zeros_like(dY)
+    rows = torch.randperm(M, generator=g, device="cuda")[:m]
+    pick[rows, torch.arange(len(rows), device="cuda")] = 1.0
+    for kw in ({"need_dX": False, "need_dB": False}, {"need_dX": False}, {}):
+        dA = abt.lr_linear_bwd(pick, X, None, A, B, **kw)[1]
+        assert torch.equal(dA[:len(rows)], T[rows])
+    if M <= 64 and m <= 512 and n <= 512 and r <= 32:     # and nothing else depends on whether it was kept
+        for a, b in zip(abt.lr_linear_bwd(dY, X, None, A, B), abt.lr_linear_bwd(dY, X, T, A, B)):
+            assert torch.equal(a, b)
