@@ -393,7 +393,9 @@ BwdLayoutF32 bwd_layout_f32(int64_t M, int64_t m, int64_t n, int64_t r, size_t l
     w.split_B = gemm_f32_splits(b);
     const GemmF32 d = gemm(nullptr, nullptr, nullptr, M, r, m, m, r, r, 0, 0, 0);
     w.split_dT = gemm_f32_row_splits(d);
-    while (w.partials + gemm_f32_partial_bytes(d, w.split_dT) > limit && w.split_dT > 1) w.split_dT /= 2;
+    // (a shape that the static array serves: no further than that has room for, so that dX has the same bits in either call)
+    const size_t room = w.partials <= ABT_STATIC_SCRATCH_BYTES ? ABT_STATIC_SCRATCH_BYTES : limit;
+    while (w.partials + gemm_f32_partial_bytes(d, w.split_dT) > room && w.split_dT > 1) w.split_dT /= 2;
     auto bytes = [&] { return gemm_f32_partial_bytes(a, w.split_A) + gemm_f32_partial_bytes(b, w.split_B); };
     while (w.partials + bytes() > limit && (w.split_A > 1 || w.split_B > 1)) {
         w.split_A = w.split_A > 1 ? w.split_A / 2 : 1;

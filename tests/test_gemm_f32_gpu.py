@@ -166,3 +166,13 @@ def test_T_again_is_the_T_of_the_forward(M, m, n, r):
     if M <= 64 and m <= 512 and n <= 512 and r <= 32:     # and nothing else depends on whether it was kept
         for a, b in zip(abt.lr_linear_bwd(dY, X, None, A, B), abt.lr_linear_bwd(dY, X, T, A, B)):
             assert torch.equal(a, b)
+
+
+# dX is that of lr_linear_bwd: dT is split no further than the static scratch has room for the parts
+def test_static_scratch_gives_the_same_dX():
+    M, m, n, r = 16385, 3072, 64, 255
+    g = torch.Generator(device="cuda").manual_seed(M)
+    X, dY, A, B = rnd(g, M, n), rnd(g, M, m), rnd(g, m, r), rnd(g, r, n)
+    dX, out = abt.lr_linear_bwd(dY, X, None, A, B)[0], torch.empty_like(X)
+    abt.lr_linear_bwd_static(dY, X, None, A, B, dX=out)
+    assert torch.equal(out, dX)
