@@ -1269,6 +1269,7 @@ int ab_merge_batched(const abt_merge_desc* layers, int L, void* workspace, size_
     return guarded([&]() -> int {
         if (!workspace || workspace_bytes < merge_workspace_bytes(layers, L)) return ABT_EWORKSPACE;
         if (!aligned(workspace, 256)) return ABT_EALIGN;
+        if (merge_stream_captures((hipStream_t)stream)) return ABT_EHIP;
         return merge_run(layers, nullptr, L, workspace, g_max_sweeps, (hipStream_t)stream) == hipSuccess ? ABT_OK : ABT_EHIP;
     });
 }
@@ -1367,6 +1368,7 @@ int ab_factorize_batched(const abt_factorize_desc* layers, int L, void* workspac
         const int st = check_merge_layer(p.merge[l]);
         if (st != ABT_OK) return st;
     }
+    if (merge_stream_captures((hipStream_t)stream)) return ABT_EHIP;
     for (size_t i = 0; i < p.Ks.size(); ++i)
         if (launch_identity_f32((float*)((char*)workspace + p.eye_off[i]), (int)p.Ks[i], (hipStream_t)stream) != hipSuccess)
             return ABT_EHIP;

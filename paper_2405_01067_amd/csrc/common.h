@@ -278,6 +278,8 @@ hipError_t launch_tiny_f32_bwd(const float* dY, const float* X, const float* T, 
 size_t merge_workspace_bytes(const abt_merge_desc* layers, int L);
 // identity: per layer the side whose (only) copy is the K x K identity, i.e. the layer is a dense weight; NULL: none
 enum class MergeSide : uint8_t { none, A, B };
+// A merge cannot be captured in a graph: the host decides between sweeps.  (The smallest ones do not come to a call that a capture would refuse.)
+bool merge_stream_captures(hipStream_t s);
 hipError_t merge_run(const abt_merge_desc* layers, const MergeSide* identity, int L, void* workspace, int max_sweeps, hipStream_t s);
 // (sweeps, values, converged, rank) of `count` layers of the last merge on this workspace (waits for the stream); hipErrorInvalidValue: not a
 // merge workspace, or no such layers in it.

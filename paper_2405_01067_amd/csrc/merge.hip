@@ -981,6 +981,11 @@ hipError_t merge_read_info(const void* workspace, int first, int count, std::vec
     return hipMemcpy(out.data(), (const char*)workspace + 256 + sizeof(int) * kInfoInts * (size_t)first, sizeof(int32_t) * out.size(), hipMemcpyDeviceToHost);
 }
 
+bool merge_stream_captures(hipStream_t s) {
+    hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+    return hipStreamIsCapturing(s, &status) != hipSuccess || status != hipStreamCaptureStatusNone;
+}
+
 namespace {
 // Tables of up to two of these (one or two layers) go up without a copy and without a wait: the merge of one 256 x 256 layer 161 -> 156 us.
 struct UploadWords { uint32_t w[960]; };

@@ -104,3 +104,28 @@ def test_stages_around_a_core_of_32(m, n, G, k_cap, k_fixed):
         # A'^T A' = B' B'^T = the values
         for q in (a[:, :k].T @ a[:, :k], b[:k] @ b[:k].T):
             assert float((q - torch.diag(S[:k])).norm() / S[:k].norm()) < 1e-4
+
+
+# the smallest tables go up in launch arguments, larger ones as a copy: a stream that is being captured is refused by both, before anything is launched
+@pytest.mark.parametrize("k,count,dense", [(32, 1, False), (32, 64, False), (64, 1, False), (32, 1, True), (64, 1, True)])
+def test_a_capture_is_refused(k, count, dense):
+    layers = [dict(layer(96, 80, k, seed=i), k_cap=k) for i in range(count)]
+    W = torch.randn((96, k), generator=torch.Generator().manual_seed(k)).to("cuda:0")
+    merge = lambda: abt.ab_factorize(W, tau=0.0, check_converged=False) if dense else abt.ab_merge_batched(layers, check_converged=False)
+    merge()
+    x = torch.zeros(16, device="cuda:0")
+    stream, graph = torch.cuda.Stream(), torch.cuda.CUDAGraph()
+    torch.cuda.synchronize()
+    with torch.cuda.stream(stream):
+        graph.capture_begin(capture_error_mode="thread_local")
+        try:
+            x.add_(1.0)
+            with pytest.raises(abt.AbtError, match="ABT_EHIP"):
+                merge()
+        finally:
+            graph.capture_end()
+    graph.replay()
+    graph.replay()
+    torch.cuda.synchronize()
+    assert bool((x == 2.0).all())
+    merge()                                               # and is served again afterwards
