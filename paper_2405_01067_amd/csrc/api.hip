@@ -183,32 +183,44 @@ bool two_products(int64_t rows, int p, int q, int R, bool image) {
 //     3072 -> 768  36000                  72.0 / 56.2    87.2 / 62.0    99.0 / 78.1     155 / 126
 //                  50432                  91.0 / 75.0    97.6 / 79.6    107 / 95.2      175 / 157
 //     768 -> 768   36000                  32.5 / 28.9                   49.8 / 37.3     66.7 / 56.3
-//     Narrow ranks and layers gain least, and lose below the limits here (64 -> 1600, 57148 rows, r = 96 44.9 / 48.1).  From 114688 rows on
-//     the rounds are many and even: from r = 160 on nothing to gain (768 -> 768, 219909 rows, r = 352 282 / 337; 768 -> 3072, 150000 rows,
-//     r = 96 240 / 217).
+//     Narrow ranks and layers gain least, and lose below the limits here (64 -> 1600, 57148 rows, r = 96 44.9 / 48.1; 1472 -> 832, 37521 rows, r = 96
+//     41.0 / 45.5).  The more rows the last round of the fused work-groups has, the less there is to gain, and nothing for a narrow result, whose T is
+//     read for few columns each: beyond 49152 rows from 768 columns on (1024 -> 640, 50460 rows, r = 256 57 / 62; r = 160, with its rounds of 16384 rows,
+//     beyond 40960 too: 320 -> 640, 47971 rows 27 / 31), beyond 57344 only at ranks up to 192, from 1088 columns on and not where the last round is
+//     all but full (768 -> 3072, 150000 rows, r = 96 240 / 217; 2816 -> 1984, 92516 rows, r = 256 251 / 290; 1920 -> 384, 61160 rows, r = 192 74 / 82),
+//     and up to r = 224 where a third round has just begun (65537 to 73728 rows: 0.98 to 1.54 times as fast).
 //   r = 288 and 352 above 10752 rows, where the fused kernel is that of the next wider rank in 128-row work-groups (768 -> 3072, 12000
-//     rows, r = 288 72.6 / 41.2; even with it from 16384 on); r = 160, whose fused kernel has 64-row work-groups (768 -> 3072, 25000
-//     rows 62.7 / 44.4).
+//     rows, r = 288 72.6 / 41.2; even with it from 16384 on; not r = 352 into few columns: 1152 -> 128, 13406 rows 29 / 32); r = 160, whose fused
+//     kernel has 64-row work-groups (768 -> 3072, 25000 rows 62.7 / 44.4), until a second round of those is three fifths full (1280 -> 640, 30343 rows 33 / 36).
 //   Wide results of short contractions, where a fused work-group's time is the stores of Y (768 -> 3072, r = 192): 4608 to 10240 rows (6000
 //     rows 31.1 / 23.3), 16384 to 22528 (20000 rows 52.8 / 40.6) and, at r = 160 and 192, up to 12800 (12608 rows 32.0 / 30.7; over 116
 //     shapes 0.98 to 1.18 times as fast, mean 1.06).  Above that one round of 64-row work-groups fills the chip (14500 rows, r = 160 33.5 / 34.6,
-//     r = 128 28.7 / 33.4).
+//     r = 128 28.7 / 33.4).  Of contractions so short that X and P are soon there a second launch is the longer way (256 -> 2496, 7237 rows, r = 64
+//     14.9 / 16.5; 256 -> 1536, 6018 rows, r = 160 14.8 / 16.2; 384 -> 1408, 22481 rows, r = 320 38 / 41), sooner at one rank than at another.
+//   Forwards of 8800 shapes inside these limits: 1.2 times as fast in the mean, 1 in 280 of them more than 3 % slower, 0.84 at worst; of 3100 outside
+//   that went this way up to wider limits, 1 in 8 were.
 //   The two lower limits lie 512 rows above those of the products for few rows (4096 and 10240): next to these a forward asks for no place for T,
 //   as before.
 bool wide_products(int64_t rows, int p, int q, int R) {
     if (g_chain_rows.load() != 0 || g_chain_parts.load() != 0 || rows <= 4608 || p < 256 || q < 128) return false;
     if (rows > 32768) {
-        if (R >= 160) return rows <= 114688 && p + q >= (rows <= 49152 ? 704 : 1536);
-        if (R == 128) return rows <= 49152 ? p >= 1024 || q > 1024 : p + q >= 3072;
-        if (R == 96) return q >= 2304 || p >= 3072 || (rows <= 40960 && p >= 512 && q >= 512 && p + q >= 1280);
-        return R == 64 && q >= 2304;
+        const int64_t last = (rows - 1) % 32768 + 1;      // rows of the last round
+        if (R >= 160) {
+            if (rows <= 49152) return p + q >= (R == 224 ? 960 : 704) && !(R == 160 && rows > 40960 && q < 768);
+            if (rows <= 57344) return q >= 768 && p + q >= 1536;
+            if (rows > 65536 && rows <= 73728 && R <= 224) return p + q >= 1536;
+            return R <= 192 && rows <= 114688 && last <= 28672 && q >= 1088 && p + q >= 1536;
+        }
+        if (R == 128) return rows <= 49152 ? p >= 1024 || q > 1024 : p + q >= 3072 && (q >= 768 || last <= 24576);
+        if (R == 96) return q >= 2304 || (p >= 3072 && q >= 512) || (rows <= 40960 && p >= 512 && q >= 512 && p + q >= 1280 && (q >= 1024 || p <= 1024));
+        return R == 64 && q >= 2304 && p <= q;
     }
-    if ((R == 288 || R == 352) && rows > 10752 && rows <= 16384) return p + q >= 1280;
-    if (R == 160 && rows > 16384) return q >= 512 && p + q >= 1472;
-    if (rows <= 8192 && R >= 96 && R <= 192) return q >= 1024 && p <= 1920;
-    if (rows <= 10240) return ((R >= 64 && R <= 192) || R == 288) && q >= 1344 && q >= 2 * p;
-    if (rows <= 12800) return (R == 160 || R == 192) && q >= 2304 && q >= 2 * p;
-    return rows > 16384 && rows <= 22528 && R >= 64 && q >= 1344 && 2 * q >= 5 * p;
+    if ((R == 288 || R == 352) && rows > 10752 && rows <= 16384) return p + q >= 1280 && (R == 288 || q >= 640);
+    if (R == 160 && rows > 16384) return rows <= 26624 && p >= 576 && q >= 512 && p + q >= 1472;
+    if (rows <= 8192 && R >= 96 && R <= 192) return q >= 1024 && p <= 1920 && p >= (R == 128 ? 256 : R == 96 ? 320 : 384);
+    if (rows <= 10240) return q >= 1344 && q >= 2 * p && ((R == 64 && p >= 640) || (R >= 96 && R <= 192) || (R == 288 && rows > 5632));
+    if (rows <= 12800) return (R == 160 || (R == 192 && p >= 640)) && q >= 2304 && q >= 2 * p;
+    return rows > 16384 && rows <= 22528 && R >= 64 && q >= 1344 && 2 * q >= 5 * p && (p >= 512 || R == 384);
 }
 // Where a few rows go through both products in one launch whose work-groups make the rows of T themselves (lr_few.hip), a round of work-groups of
 // 32 rows and 256 columns of Y (128 above r = 96).  Forward, GPU time in us, the other kernels / this one:

@@ -84,6 +84,22 @@ def test_where_a_forward_wants_a_place_for_T(lib):
     assert conv(4, 7, 2048, 1, 1, 512, 128) == conv(3, 14, 1024, 1, 2, 64, 384) == 1 and conv(2, 6, 64, 3, 1, 64, 32) == conv(2, 6, 64, 2, 1, 64, 32) == 0
 
 
+def test_limits_of_the_two_products_of_many_rows(lib):
+    # both sides of every limit: rows, columns of the result, width of the contraction
+    want = lambda rows, p, q, r: lib.lr_linear_fwd_wants_T(1, rows, q, p, r, abt.ABT_BF16)
+    inside = [(40960, 320, 640, 160), (49152, 320, 768, 160), (49153, 768, 768, 160), (49152, 320, 640, 224), (49152, 1024, 640, 256), (57344, 1024, 768, 256), (73728, 2048, 320, 192),
+              (94208, 2048, 1088, 192), (60000, 3712, 768, 128), (57344, 3712, 512, 128), (90112, 3712, 512, 128), (40960, 1024, 832, 96), (40960, 1472, 1024, 96),
+              (50000, 3072, 512, 96), (50000, 2304, 2304, 64), (16384, 1152, 640, 352), (16384, 1152, 128, 288), (26624, 1280, 640, 160),
+              (6000, 256, 1088, 128), (6000, 320, 1088, 96), (6000, 384, 1088, 160), (6000, 640, 1344, 64), (12608, 640, 2560, 192),
+              (20000, 512, 1600, 320)]
+    outside = [(40961, 320, 640, 160), (49153, 704, 768, 160), (49152, 256, 640, 224), (49153, 1024, 640, 256), (57345, 1024, 1088, 256), (73729, 2048, 320, 192),
+               (94209, 2048, 1088, 192), (60000, 3712, 704, 128), (57345, 3712, 512, 128), (90113, 3712, 512, 128), (40960, 1088, 832, 96), (40961, 1472, 1024, 96),
+               (50000, 3072, 448, 96), (50000, 2368, 2304, 64), (16384, 1152, 576, 352), (16384, 1088, 128, 288), (26625, 1280, 640, 160), (20000, 512, 1152, 160),
+               (8193, 256, 1088, 128), (6000, 256, 1088, 96), (6000, 320, 1088, 160), (6000, 576, 1344, 64), (12608, 576, 2560, 192),
+               (20000, 448, 1600, 320)]
+    assert [a for a in inside if not want(*a)] == [] == [a for a in outside if want(*a)]
+
+
 def test_fp32_backward_workspace_holds_the_full_split(lib):
     # beside dT and T the partial sums of the split that fills the chip, whatever the static scratch array could hold
     need = lambda M, m, n, r: lib.lr_linear_bwd_workspace_bytes(M, m, n, r, abt.ABT_F32) - 2 * (M * r * 4 + 255) // 256 * 256
