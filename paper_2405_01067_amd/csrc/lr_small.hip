@@ -654,7 +654,11 @@ hipError_t launch_lr_small_grad(const void* dY, const void* X, const void* T, co
     // tiles 12.8 / 10.4).
     g.dx_shared = r >= 160 && (int64_t)blocks * (n / 64) <= 256;
     if (dX) grid += (int64_t)blocks * (g.dx_shared ? n / 64 : ceil_div(n, 64 * kGradWaves));
-    hipLaunchKernelGGL(small_grad_kernel, dim3((unsigned)grid), dim3(64 * kGradWaves), 0, s, g);
+    // Two work-groups share a compute unit; of many rows only one (LDS that nobody uses keeps the other away): the tiles of dA and dB, the longest
+    // chains, would wait for those of dX beside them.  Backward, us, two / one: 4063 rows, 1280 -> 256, r = 288 34.7 / 29.7;  2494 rows, 1792 -> 128,
+    // r = 160 22.0 / 19.1;  over 1100 shapes two are 1.02 times as fast in the mean up to 1856 rows, one from 2560 rows on, and as fast as each other between.
+    const size_t alone = M > 1856 ? 24 * 1024 : 0;
+    hipLaunchKernelGGL(small_grad_kernel, dim3((unsigned)grid), dim3(64 * kGradWaves), alone, s, g);
     return hipGetLastError();
 }
 
