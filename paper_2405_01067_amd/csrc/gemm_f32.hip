@@ -37,7 +37,7 @@ constexpr int NT = 256;
 
 struct GemmF32Dev {
     GemmF32 d;
-    int begin;           // problems in the kernel arguments: first slot of an XCD's share; in a table: first tile
+    int begin;           // problems in the kernel arguments: the XCD that its shares begin with; in a table: first tile
     int tiles_q, tiles;  // tiles per row of tiles, tiles of one split
     int splits, k_split; // splits of the contraction, columns of each (a multiple of 64)
     float* part;         // splits > 1: partial sums [split][P][Q]
@@ -287,18 +287,24 @@ __global__ __launch_bounds__(NT, 3) void gemm_f32_kernel(const GemmF32Dev* __res
     __shared__ __align__(16) float lds[C::lds_floats];
     // Block b runs on XCD b % 8.  A few problems: every XCD gets a contiguous eighth of the tiles of each, which share their operand panels through
     // one L2; problems of unlike contractions weigh the same on every XCD then (an eighth of the whole list instead left two thirds
-    // of the work of the joint launch of dA, dB and dX to three of them: 124 us against 64, 3152 x 3072 x 768, r = 192).  A table of
+    // of the work of the joint launch of dA, dB and dX to three of them: 124 us against 64, 3152 x 3072 x 768, r = 192).  The tiles that eighths leave over
+    // go to the XCDs in turn, on from one problem to the next (rounded up for each, dA and dB of 5675 x 28 x 770, r = 30, were 33 work-groups for
+    // the 32 compute units of an XCD: 21.5 us, 16.0 so).  A table of
     // many: an eighth of the list, whole problems for the most part (96 back-projections of a merge 294 us, 380 the other way).
     const int slot = (int)(blockIdx.x >> 3), xcd = (int)(blockIdx.x & 7);
     GemmF32Dev g;
     int tile;
     if (table == nullptr) {
-        int i = 0;
-        while (i + 1 < ndesc && args.g[i + 1].begin <= slot) ++i;
+        int i = 0, at = slot;
+        for (;; ++i) {
+            if (i == ndesc) return;
+            const int all = args.g[i].tiles * args.g[i].splits, x = (xcd - args.g[i].begin) & 7, over = all & 7;
+            const int share = (all >> 3) + (x < over ? 1 : 0);
+            tile = x * (all >> 3) + (x < over ? x : over) + at;
+            if (at < share) break;
+            at -= share;
+        }
         g = args.g[i];
-        const int all = g.tiles * g.splits;
-        tile = xcd * ((all + 7) >> 3) + slot - g.begin;
-        if (tile >= all) return;
     } else {
         const int at = xcd * (int)(gridDim.x >> 3) + slot;
         int lo = 0, hi = ndesc - 1;
@@ -354,8 +360,6 @@ GemmF32Dev describe(const GemmF32& d, int tm, int tn, int begin, int splits) {
     g.splits = (int)ceil_div(d.K, g.k_split);
     return g;
 }
-
-int slots_of(const GemmF32Dev& g) { return (g.tiles * g.splits + 7) / 8; }
 
 void launch_form(bool small, bool vec, int slots, const GemmF32Dev* table, const GemmF32Args& a, int n, hipStream_t s) {
     const dim3 grid(8 * slots), block(NT);
@@ -424,21 +428,21 @@ hipError_t launch_gemm_f32(const GemmF32* p, const int* splits, int n, float* pa
     const bool small = use_small(wide_tiles_of(p, splits, n));
     const int tm = small ? Small::TM : Wide::TM, tn = small ? Small::TN : Wide::TN;
     GemmF32Args a{};
-    int slots = 0;
+    int tiles = 0;
     int64_t largest = 0;
     char* part = (char*)partials;
     for (int i = 0; i < n; ++i) {
-        a.g[i] = describe(p[i], tm, tn, slots, splits ? splits[i] : 1);
+        a.g[i] = describe(p[i], tm, tn, tiles & 7, splits ? splits[i] : 1);
         if (a.g[i].splits > 1) {
             if (!partials) return hipErrorInvalidValue;
             a.g[i].part = (float*)part;
             part += gemm_f32_partial_bytes(p[i], a.g[i].splits);
             if ((int64_t)p[i].P * p[i].Q > largest) largest = (int64_t)p[i].P * p[i].Q;
         }
-        slots += slots_of(a.g[i]);
+        tiles += a.g[i].tiles * a.g[i].splits;
     }
-    if (slots <= 0) return hipSuccess;
-    launch_form(small, vec, slots, nullptr, a, n, s);
+    if (tiles <= 0) return hipSuccess;
+    launch_form(small, vec, (tiles + 7) / 8, nullptr, a, n, s);
     if (any_split && largest > 0) {
         const int64_t blocks = ceil_div(largest, NT);
         hipLaunchKernelGGL(gemm_f32_reduce_kernel, dim3((unsigned)(blocks < 2048 ? blocks : 2048), n), dim3(NT), 0, s, a, n);
