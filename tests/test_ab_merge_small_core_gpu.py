@@ -1,6 +1,7 @@
-"""Merges whose core is a single pair of column blocks (K = 32) run all Jacobi sweeps in one launch; with a larger
-layer in the batch the same layer goes through a launch per round.  Both do the same rotations in the same
-order on the same numbers: the singular values agree bit for bit.  And decompositions of dense weights around
+"""Merges whose core is a single pair of column blocks (K = 32) run all Jacobi sweeps in one launch, and sum their Gram matrices in
+parts; with a larger layer in the batch the same layer goes through the launches for all sizes.  Both do the same rotations in the same
+order, on numbers that differ by the order of fp64 sums: the singular values agree but for their rounding to fp32, 2^-23 at most
+where one lies on either side of a boundary.  And decompositions of dense weights around
 the sizes where the Cholesky factorisation changes its form, against an fp64 SVD."""
 import numpy as np
 import pytest
@@ -24,7 +25,7 @@ def test_single_pair_core_agrees_with_a_mixed_batch(m, n, count):
     alone = abt.ab_merge_batched(small)
     mixed = abt.ab_merge_batched(small + [layer(128, 96, 64, seed=3)])
     for a, b in zip(alone, mixed):
-        assert torch.equal(a["S"], b["S"]) and a["sweeps"] == b["sweeps"] > 1
+        assert bool(((a["S"] - b["S"]).abs() <= 2 ** -23 * b["S"]).all()) and a["sweeps"] == b["sweeps"] > 1
         W, V = (o["A"].double() @ o["B"].double() for o in (a, b))
         assert float((W - V).norm() / V.norm()) < 1e-6
 

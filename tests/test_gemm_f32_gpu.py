@@ -145,7 +145,7 @@ def test_smallest_layers(M, m, n, r, accumulate):
     # the same bits whatever else is asked for
     for which in ((True, False, True), (False, True, False), (False, False, True), (True, False, False)):
         for a, b, w in zip(run(need_dX=which[0], need_dA=which[1], need_dB=which[2]), (dX, dA, dB), which):
-            assert (torch.equal(a, b) or M > 64 or r > 32 or n > 512) if w else a is None
+            assert torch.equal(a, b) if w else a is None
 
 
 # T again is the T of the forward, bit for bit, whatever is asked for with it: one launch each way, tiles of either size alone and beside dT, a
