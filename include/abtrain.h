@@ -20,13 +20,17 @@
  *     ab_adamw_step and ab_reconstruct enqueue work on it and return without synchronising the host.  Calls that DO
  *     block the host:
  *       ab_merge, ab_merge_batched, ab_factorize, ab_factorize_batched: once after uploading
- *         their layer tables, and from the third Jacobi sweep on once per sweep, for the copy of
+ *         their layer tables (tables of up to 7680 bytes, which one or two layers may have, travel in
+ *         the arguments of launches instead, without this wait), and, unless every core is 32
+ *         wide, from the third Jacobi sweep on once per sweep, for the copy of
  *         the convergence flags of the sweep BEFORE the one just enqueued (the host stays one
- *         sweep ahead, so the GPU does not idle meanwhile).  With more than one layer they also
+ *         sweep ahead, so the GPU does not idle meanwhile).  A merge with such tables and
+ *         cores of 32 therefore does not block at all: nothing that was enqueued on `stream` before or by it
+ *         need be done when it returns.  With more than one layer they also
  *         run layer groups on up to three streams of the library's own (default priority),
  *         forked from and joined back into `stream` inside the call.  The stages they enqueue
  *         last (back-projection) may still be running when they return.  Not capturable in a
- *         HIP graph.
+ *         HIP graph: a stream that is being captured is refused with ABT_EHIP, before anything is launched.
  *       ab_merge_info, ab_merge_info_batched: wait for `stream`.
  *   - `workspace` is caller-owned device scratch of at least the size the matching
  *     *_workspace_bytes() query returns, 256-byte aligned; its contents are undefined
@@ -142,9 +146,9 @@ int lr_linear_bwd_static(const void* dY, const void* X, const void* T, const voi
  *   forward : X, A, B, Y required, T_save optional (all groups or none).
  *   backward: dY, X, A, B required; T optional (NULL = recomputed); dX, dA, dB optional per group
  *             (a group that trains A passes dB = NULL and the other way round).
- * ABT_BF16: the forward is one launch (few rows: two) for all groups; the backward is one launch each for the
- * transposes, the dT/dX chain (two if only some groups ask for dX), the factor gradients of all
- * groups and their split reduction.  ABT_F32: the single-group path, group by group.
+ * ABT_BF16: the forward is one launch for all groups, or two where lr_linear_fwd_wants_T says 1 and T_save is given; the backward is one
+ * launch each for the transposes, the dT/dX chain (two where a forward of its widths would be two; each again if only some groups ask for
+ * dX), the factor gradients of all groups and their split reduction.  ABT_F32: the single-group path, group by group.
  * Results per group are those of the single-group calls up to the order of the fp32 sums, which depends on the rows of all
  * groups (bf16: T, dT and what is computed from them may differ by a rounding).  A T that the backward computes again, for all
  * groups or some, is the T_save of a forward of the same groups; two grouped calls on the same
@@ -226,7 +230,8 @@ typedef struct {
 
 /* The same merge for L layers at once (one model's layer set per call): every stage is one
  * grouped launch over all layers instead of L launches.  `layers` is a HOST array read
- * before the call returns.  Layers may differ in every field. */
+ * before the call returns.  Layers may differ in every field.  The order of the fp64 sums of a layer's Gram matrices, and so the last bits of its results,
+ * may depend on the layers beside it (on whether every core of the call is 32 wide); the same call gives the same bits. */
 int ab_merge_batched(const abt_merge_desc* layers, int L,
                      void* workspace, size_t workspace_bytes, void* stream);
 

@@ -233,7 +233,8 @@ bool wide_products(int64_t rows, int p, int q, int R) {
 //                   r = 64    16 / 7.4    16 / 7.9    17 / 8.1     10 / 8.4    11.5 / 10
 //                   r = 96   9.6 / 9.1  10.3 / 9.7  10.5 / 9.9                               (two launches / one)
 //     64 -> 64      r = 64   4.3 / 2.7   4.6 / 3.0   4.7 / 3.0    4.7 / 3.1    4.7 / 3.1
-// Over 300 shapes of 16 to 4096 rows 1.4 times as fast in the mean, none slower.  From r = 96 on, and from an image, not where two_products holds: T alone, which shares its
+// Over 300 shapes of 16 to 4096 rows 1.4 times as fast in the mean, none slower.  T alone at r = 32 and 64, a work-group per 32 rows, is as fast as the two
+// products' (a backward of T again and dA, 3072 -> 64: r = 32 1024 rows 16.2 / 14.4, 4096 rows 26.7 / 26.3; r = 64 16.5 / 16.1, 29.7 / 29.4).  From r = 96 on, and from an image, not where two_products holds: T alone, which shares its
 // contraction among more work-groups there, took up to 1.4 us longer (3072 columns, r = 96, 10.7 -> 12.1 with dA).
 // From an image over 165 layers and batches 1.5 times as fast in the mean, none slower: 28 x 28 x 128, stride 2, r = 32, 3 images 14.6 / 5.5;
 // 7 x 7 x 64, r = 160, 9 images 19.7 / 7.7.

@@ -15,8 +15,7 @@
 // Measured: 4096 x 4096 x 1024 279 us = 123 TFLOP/s of the 133 that a large library product reaches;
 // 768 x 3072 x 384 (W = A B of a ViT-B/16 MLP layer) 26 us, 79 us in an earlier form with 128 x 128 tiles
 // and 4-byte loads one slab ahead; the products of a factored layer at M = 3152, m = 3072, n = 768,
-// r = 192: T 15 us, Y 52, dT 47 and 4, and dX, dA and dB in one launch 64 and 7; forward and backward together 171 us,
-// of the 64 x 256 x 256 layer at r = 32 26 us.
+// r = 192: T 15 us, Y 52, dT 47 and 4, and dX, dA and dB in one launch 64 and 7; forward and backward together 171 us.
 //
 // LDS: both operands lie [row][k], 16-byte chunks of four k XOR-swizzled by the row; an operand read is
 // one 16-byte read for four matrix instructions: instruction i of a group of eight k takes k = 4 h + i

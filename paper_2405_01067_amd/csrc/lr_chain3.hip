@@ -407,10 +407,8 @@ __global__ __launch_bounds__(512) void chain3_bf16_kernel(Ch3Ptrs ptrs, int64_t 
                 }
                 __builtin_amdgcn_sched_barrier(0);
             }
-            // the next slab has landed.  The stores of a flush go out only now: loads and stores need not
-            // complete in one common order, so no count of outstanding operations is used to tell the
-            // slab's loads from stores issued before this wait; issued after it, the stores are on
-            // their way during the next slab and complete long before its closing wait
+            // the next slab has landed.  The stores of a flush go out only now, so that no count has to tell the slab's loads from them: issued
+            // after this wait, they are on their way during the next slab and complete long before its closing wait
             wait_loads3();
             if (flush_now) {
                 flush_store(flushed);

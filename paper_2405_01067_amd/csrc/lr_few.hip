@@ -5,7 +5,7 @@
 // at a time, each through two buffers of its own in LDS (whole 64-byte pieces, no barrier, the loads of two pieces on their way); their sums are
 // added in the order of the waves, and each wave then makes 32 columns of Y, whose rows of Q have come meanwhile to where its buffers were.  The fused
 // kernels walk through the contraction with a barrier per 64 columns, the two products add a launch.  197 rows, 768 -> 2304, us: r = 32 8.0 -> 4.1,
-// r = 96 11.7 -> 5.9, r = 128 14.5 -> 6.6; the layer's step at r = 96 25.8 -> 24.3, which the host's calls bound.  With the parts of a row block on eight XCDs,
+// r = 96 11.7 -> 5.9, r = 128 14.5 -> 6.6.  With the parts of a row block on eight XCDs,
 // as they come, 3072 -> 768, r = 96, 788 rows took 13.6 instead of 10.1.
 #include <atomic>
 #include <type_traits>

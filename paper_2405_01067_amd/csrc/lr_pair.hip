@@ -4,10 +4,11 @@
 // (bf16 in and out, fp32 accumulators).  A fused work-group has to stream both factors past its 64 or 128 rows, and its rows come in whole
 // blocks: 50432 rows are 394 work-groups of 128 on 256 compute units.  Here Q is read once per work-group whatever its rows, and contract shares
 // out the rows of the batch evenly, 8 at a time; what it costs is the second launch and T read again, from the cache.
-// Alone, M = 50432, in brackets the share of the bytes' time at the 5.9 (read) and 6.8 TB/s (written) of plain streams:
-//                               r = 32 or 96             r = 192               r = 384
-//   contract, p = 3072     51 us, r = 32 (1.0)      82 us (0.7)          127 us: 940 TFLOP/s
-//   expand, q = 3072       48 us, r = 96, 39597 rows (0.8)   67 us (0.7)  124 us: 960 TFLOP/s
+// Alone, M = 50432, buffers in turn, in brackets the share of the bytes' time at the 5.9 and 6.8 TB/s of launches that only read or only write, as these
+// nearly do (a copy, half of each, moves 4.8 TB/s):
+//                          r = 96           r = 192          r = 384
+//   contract, p = 3072     63 us (0.85)     83 us (0.67)     134 us: 890 TFLOP/s
+//   expand, q = 3072       57 us (0.83)     66 us (0.75)     119 us: 1000 TFLOP/s
 // Products of random values alone, operands in registers, run at 1200 to 1500 TFLOP/s on this card (the clock falls).
 #include <atomic>
 #include <type_traits>
@@ -200,7 +201,8 @@ __global__ __launch_bounds__(ExCfg<R>::NT) void expand_kernel(PairPtrs ptrs, int
     int at = 0;                                           // slot of the chunk
     for (int ch = ch0; ch < ch1; ++ch) {
         // The loads of this chunk have landed (the first did with Q): behind them this wave has issued the eight stores of each chunk since
-        // and the loads of the chunk after.  Accesses of one wave are counted off in the order of issue.
+        // and the loads of the chunk after.  Accesses of one wave, loads and stores, are counted off in the order of issue (the compiler relies on it too: a
+        // load with two stores behind it is waited for with two left).
         if (ch > ch0) {
             if constexpr (NS == 2) wait_newest<8>();
             else if (ch == ch0 + 1) {
