@@ -91,6 +91,28 @@ __device__ __forceinline__ void buf_store16_maybe_stream(bool stream, u32x4 v, r
 // are one output.
 constexpr int64_t kStreamOutBytes = 64ll << 20;
 
+// ---- what the kernels share that load straight to LDS without a barrier per load (lr_few.hip, lr_pair.hip)
+__device__ __forceinline__ f32x16 mfma_bf16(u32x4 a, u32x4 b, f32x16 c) {
+    return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
+}
+// All but the newest N global accesses of this wave (loads, loads to LDS, stores) have completed: they are counted off in the order of issue, on which
+// the compiler relies too (a load with two stores behind it is waited for with two left).
+template <int N>
+__device__ __forceinline__ void wait_newest() {
+    static_assert(N >= 0 && N < 64, "six bits");
+    __builtin_amdgcn_s_waitcnt((N & 15) | ((N >> 4) << 14) | (7 << 4) | (15 << 8));
+    asm volatile("" ::: "memory");
+}
+// this wave's LDS traffic has completed, then s_barrier (global accesses stay in flight)
+__device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
+// 1 KB: lane l's 16 bytes go to LDS address dst + 16 l
+__device__ __forceinline__ void load_lds16(rsrc_t r, unsigned char* dst, int lane_off, int wave_off) {
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (__attribute__((address_space(3))) void*)dst, 16, lane_off, wave_off, 0, 0);
+}
+// Row i of a block of 32 of the first MFMA operand is matrix row out_row(i): the 16 accumulators of a lane are then
+// 16 consecutive columns of the result, 16 (lane / 32) .. + 15.
+__device__ __forceinline__ int out_row(int i) { return 16 * ((i >> 2) & 1) + 4 * (i >> 3) + (i & 3); }
+
 inline int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
 inline size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 // Do two byte ranges share memory?  (A caller may hand in an output that lies over an input, as far as everything

@@ -16,26 +16,7 @@ namespace abt {
 
 namespace {
 
-__device__ __forceinline__ f32x16 mfma_f(u32x4 a, u32x4 b, f32x16 c) {
-    return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
-}
-// all but the newest N global accesses of this wave have completed
-template <int N>
-__device__ __forceinline__ void wait_newest() {
-    static_assert(N >= 0 && N < 64, "six bits");
-    __builtin_amdgcn_s_waitcnt((N & 15) | ((N >> 4) << 14) | (7 << 4) | (15 << 8));
-    asm volatile("" ::: "memory");
-}
 __device__ __forceinline__ void lds_done() { asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); }
-// this wave's LDS traffic has completed, then s_barrier (global accesses stay in flight)
-__device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
-// 1 KB: lane l's 16 bytes go to LDS address dst + 16 l
-__device__ __forceinline__ void load_lds16(rsrc_t r, unsigned char* dst, int lane_off, int wave_off) {
-    __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (__attribute__((address_space(3))) void*)dst, 16, lane_off, wave_off, 0, 0);
-}
-// Row i of a block of 32 of the first MFMA operand is matrix row out_row(i): the 16 accumulators of a lane are then
-// 16 consecutive columns of the result, 16 (lane / 32) .. + 15.
-__device__ __forceinline__ int out_row(int i) { return 16 * ((i >> 2) & 1) + 4 * (i >> 3) + (i & 3); }
 
 template <int R>
 struct FewCfg {
@@ -141,7 +122,7 @@ __global__ __launch_bounds__(FewCfg<R>::NW * 64) void few_fwd_kernel(FewPtrs ptr
 #pragma unroll
         for (int j = 0; j < 2; ++j)
 #pragma unroll
-            for (int k = 0; k < RB; ++k) acc[k] = mfma_f(f[j][k], x[j], acc[k]);
+            for (int k = 0; k < RB; ++k) acc[k] = mfma_bf16(f[j][k], x[j], acc[k]);
     }
     // ---- this wave's rows of Q on their way, its sums to LDS behind them (its buffers are read)
     const int col0 = part * L::NC + 32 * wave;
@@ -177,7 +158,7 @@ __global__ __launch_bounds__(FewCfg<R>::NW * 64) void few_fwd_kernel(FewPtrs ptr
         for (int k = 0; k < R / 16; ++k) {
             const u32x4 a = *reinterpret_cast<const u32x4*>(own + prow * (R * 2) + (2 * k + lh) * 16);
             const u32x4 t = *reinterpret_cast<const u32x4*>(tl + lj * L::pitch + (2 * k + lh) * 16);
-            y = mfma_f(a, t, y);
+            y = mfma_bf16(a, t, y);
         }
         const rsrc_t yr = make_rsrc(Y + row0 * q + col0, ((int64_t)(rows - 1) * q + 32) * 2);
 #pragma unroll

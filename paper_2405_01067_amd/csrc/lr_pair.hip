@@ -19,26 +19,6 @@ namespace abt {
 
 namespace {
 
-__device__ __forceinline__ f32x16 mfma_p(u32x4 a, u32x4 b, f32x16 c) {
-    return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
-}
-// this wave's LDS traffic has completed, then s_barrier (global accesses stay in flight)
-__device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
-// all but the newest N global accesses of this wave (loads, loads to LDS, stores) have completed
-template <int N>
-__device__ __forceinline__ void wait_newest() {
-    static_assert(N >= 0 && N < 64, "six bits");
-    __builtin_amdgcn_s_waitcnt((N & 15) | ((N >> 4) << 14) | (7 << 4) | (15 << 8));
-    asm volatile("" ::: "memory");
-}
-// 1 KB: lane l's 16 bytes go to LDS address dst + 16 l
-__device__ __forceinline__ void load_lds16(rsrc_t r, unsigned char* dst, int lane_off, int wave_off) {
-    __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (__attribute__((address_space(3))) void*)dst, 16, lane_off, wave_off, 0, 0);
-}
-// Row i of a block of 32 of the first MFMA operand is matrix row out_row(i): the 16 accumulators of a lane are then
-// 16 consecutive columns of the result, 16 (lane / 32) .. + 15.
-__device__ __forceinline__ int out_row(int i) { return 16 * ((i >> 2) & 1) + 4 * (i >> 3) + (i & 3); }
-
 // f(0), .., f(N - 1) with constants: at wide ranks the loops below are beyond what the compiler unrolls, and an array of registers with
 // an index that is not a constant goes to memory
 template <int I, int N, class F>
@@ -194,15 +174,14 @@ __global__ __launch_bounds__(ExCfg<R>::NT) void expand_kernel(PairPtrs ptrs, int
         for (int e = 12 * step / KB; e < 12 * (step + 1) / KB; ++e) out_piece(x, e, yr);
     };
     auto mma = [&](int x, int kk, u32x4 t) {
-        acc[x][0] = mfma_p(qf[0][kk], t, kk == 0 ? zero : acc[x][0]);
-        acc[x][1] = mfma_p(qf[1][kk], t, kk == 0 ? zero : acc[x][1]);
+        acc[x][0] = mfma_bf16(qf[0][kk], t, kk == 0 ? zero : acc[x][0]);
+        acc[x][1] = mfma_bf16(qf[1][kk], t, kk == 0 ? zero : acc[x][1]);
     };
     rsrc_t y0 = yres(ch0 - 1, 0), y1 = y0;                // where the blocks of the chunk before go
     int at = 0;                                           // slot of the chunk
     for (int ch = ch0; ch < ch1; ++ch) {
         // The loads of this chunk have landed (the first did with Q): behind them this wave has issued the eight stores of each chunk since
-        // and the loads of the chunk after.  Accesses of one wave, loads and stores, are counted off in the order of issue (the compiler relies on it too: a
-        // load with two stores behind it is waited for with two left).
+        // and the loads of the chunk after.  Accesses of one wave are counted off in the order of issue.
         if (ch > ch0) {
             if constexpr (NS == 2) wait_newest<8>();
             else if (ch == ch0 + 1) {
@@ -362,10 +341,10 @@ __global__ __launch_bounds__(512) void contract_kernel(PairPtrs ptrs, int M, int
     };
     auto mma = [&](const Ops& o) {
 #pragma unroll
-        for (int b = 0; b < CB; ++b) acc[0][b] = mfma_p(o.f[b], o.x[0], acc[0][b]);
+        for (int b = 0; b < CB; ++b) acc[0][b] = mfma_bf16(o.f[b], o.x[0], acc[0][b]);
         if (xlive > 1) {
 #pragma unroll
-            for (int b = 0; b < CB; ++b) acc[1][b] = mfma_p(o.f[b], o.x[1], acc[1][b]);
+            for (int b = 0; b < CB; ++b) acc[1][b] = mfma_bf16(o.f[b], o.x[1], acc[1][b]);
         }
     };
 #pragma unroll
