@@ -649,15 +649,17 @@ hipError_t launch_lr_small_grad(const void* dY, const void* X, const void* T, co
     };
     if (dA) job(dY, T, dA, m, r);
     if (dB) job(dT, X, dB, r, n);
+    const int64_t tiles = grid;
     // A work-group per tile of dX for few tiles and wide ranks, else a wave per tile (backward, us, n = 768: r = 384, 84 tiles
     // 18.8 / 24.9, 384 tiles 28.9 / 30.7; r = 192, 84 tiles 14.9 / 17.0, 384 tiles 22.3 / 19.8; r = 96 the same for few, n = 3072, 336
     // tiles 12.8 / 10.4).
     g.dx_shared = r >= 160 && (int64_t)blocks * (n / 64) <= 256;
     if (dX) grid += (int64_t)blocks * (g.dx_shared ? n / 64 : ceil_div(n, 64 * kGradWaves));
-    // Two work-groups share a compute unit; of many rows only one (LDS that nobody uses keeps the other away): the tiles of dA and dB, the longest
-    // chains, would wait for those of dX beside them.  Backward, us, two / one: 4063 rows, 1280 -> 256, r = 288 34.7 / 29.7;  2494 rows, 1792 -> 128,
-    // r = 160 22.0 / 19.1;  over 1100 shapes two are 1.02 times as fast in the mean up to 1856 rows, one from 2560 rows on, and as fast as each other between.
-    const size_t alone = M > 1856 ? 24 * 1024 : 0;
+    // Two work-groups share a compute unit.  Only one does (LDS that nobody uses keeps the other away) where the few tiles of dA and dB are the longest chains,
+    // in rows, and would wait for those of dX, in ranks, beside them.  Backward, us, two / one: 4063 rows, 1280 -> 256, r = 288 (120 tiles) 34.7 / 29.7;
+    // 2494 rows, 1792 -> 128, r = 160 (90) 22.0 / 19.1;  2051 rows, 1344 -> 704, r = 320 (160) 40.8 / 42.3.  Of 4500 shapes of 300 to 4096 rows two are more than
+    // 3 % slower for 190 than the kernel was with one, one for 860 than with two; by this rule some 25 each.
+    const size_t alone = tiles <= 120 && grid <= 640 && M > 1400 && M > 10 * (int64_t)r ? 24 * 1024 : 0;
     hipLaunchKernelGGL(small_grad_kernel, dim3((unsigned)grid), dim3(64 * kGradWaves), alone, s, g);
     return hipGetLastError();
 }
