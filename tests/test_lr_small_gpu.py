@@ -39,6 +39,13 @@ def test_backward_of_few_rows(M, m, n, r, accumulate):
             assert torch.equal(a, b) if w else b is None
 
 
+# one work-group of the gradients per compute unit, and two, next to each limit: rows (1400, ten times the rank), tiles of dA and dB (120), work-groups (640)
+@pytest.mark.parametrize("M,m,n,r", [(1400, 128, 1920, 96), (1401, 128, 1920, 96), (1920, 128, 1920, 192), (1921, 128, 1920, 192), (4063, 256, 1280, 288),
+                                     (4063, 320, 1280, 288), (3300, 64, 2560, 96), (3700, 64, 2560, 96)])
+def test_gradients_that_share_a_compute_unit_and_that_do_not(M, m, n, r):
+    test_backward_of_few_rows(M, m, n, r, False)
+
+
 @pytest.mark.parametrize("M,m,n,r", [(5, 1600, 64, 32), (2048, 1984, 64, 128), (2049, 1088, 320, 128), (2720, 576, 64, 96), (2721, 2112, 512, 96)])
 def test_tiles_of_dT_of_either_width(M, m, n, r):
     # 32 columns up to 256 tiles, 64 beyond; contractions that end at every one of the slabs in flight
