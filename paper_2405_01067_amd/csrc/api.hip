@@ -201,26 +201,33 @@ bool two_products(int64_t rows, int p, int q, int R, bool image) {
 //   that went this way up to wider limits, 1 in 8 were.
 //   The two lower limits lie 512 rows above those of the products for few rows (4096 and 10240): next to these a forward asks for no place for T,
 //   as before.
-bool wide_products(int64_t rows, int p, int q, int R) {
+//   Groups share launches of 64- or 128-row work-groups that split no tail and have no form of eight equal waves, so that they gain more: of 800 calls
+//   outside the limits for one problem 577 are more than 3 % faster as two products (8 x 2255 rows, 320 -> 2112, r = 160 52.9 / 29.4), 64 slower, of these most
+//   below 8192 rows, which keep them, and at r = 224, 256, 352 and 384 where a third round is full to more than a half (5 x 17187 rows, 1472 -> 1792, r = 256 177 / 214).
+bool wide_products(int64_t rows, int p, int q, int R, bool groups) {
     if (g_chain_rows.load() != 0 || g_chain_parts.load() != 0 || rows <= 4608 || p < 256 || q < 128) return false;
     if (rows > 32768) {
         const int64_t last = (rows - 1) % 32768 + 1;      // rows of the last round
         if (R >= 160) {
-            if (rows <= 49152) return p + q >= (R == 224 ? 960 : 704) && !(R == 160 && rows > 40960 && q < 768);
-            if (rows <= 57344) return q >= 768 && p + q >= 1536;
-            if (rows > 65536 && rows <= 73728 && R <= 224) return p + q >= 1536;
-            return R <= 192 && rows <= 114688 && last <= 28672 && q >= 1088 && p + q >= 1536;
+            if (rows > 114688 || p + q < (rows <= 49152 ? 704 : 1536)) return false;
+            if (groups) return R == 160 || R == 192 || R == 288 || R == 320 || rows <= 81920 || rows > 98304;
+            if (rows <= 49152) return (R != 224 || p + q >= 960) && (R != 160 || rows <= 40960 || q >= 768);
+            if (rows <= 57344) return q >= 768;
+            if (rows > 65536 && rows <= 73728 && R <= 224) return true;
+            return R <= 192 && last <= 28672 && q >= 1088;
         }
-        if (R == 128) return rows <= 49152 ? p >= 1024 || q > 1024 : p + q >= 3072 && (q >= 768 || last <= 24576);
-        if (R == 96) return q >= 2304 || (p >= 3072 && q >= 512) || (rows <= 40960 && p >= 512 && q >= 512 && p + q >= 1280 && (q >= 1024 || p <= 1024));
-        return R == 64 && q >= 2304 && p <= q;
+        if (R == 128) return rows <= 49152 ? p >= 1024 || q > 1024 : p + q >= 3072 && (groups || q >= 768 || last <= 24576);
+        if (R == 96) return q >= 2304 || (p >= 3072 && (groups || q >= 512)) ||
+                            (rows <= 40960 && p >= 512 && q >= 512 && p + q >= 1280 && (groups || q >= 1024 || p <= 1024));
+        return R == 64 && q >= 2304 && (groups || p <= q);
     }
-    if ((R == 288 || R == 352) && rows > 10752 && rows <= 16384) return p + q >= 1280 && (R == 288 || q >= 640);
-    if (R == 160 && rows > 16384) return rows <= 26624 && p >= 576 && q >= 512 && p + q >= 1472;
+    if ((R == 288 || R == 352) && rows > 10752 && rows <= 16384) return p + q >= 1280 && (groups || R == 288 || q >= 640);
+    if (R == 160 && rows > 16384) return q >= 512 && p + q >= 1472 && (groups || (rows <= 26624 && p >= 576));
     if (rows <= 8192 && R >= 96 && R <= 192) return q >= 1024 && p <= 1920 && p >= (R == 128 ? 256 : R == 96 ? 320 : 384);
-    if (rows <= 10240) return q >= 1344 && q >= 2 * p && ((R == 64 && p >= 640) || (R >= 96 && R <= 192) || (R == 288 && rows > 5632));
-    if (rows <= 12800) return (R == 160 || (R == 192 && p >= 640)) && q >= 2304 && q >= 2 * p;
-    return rows > 16384 && rows <= 22528 && R >= 64 && q >= 1344 && 2 * q >= 5 * p && (p >= 512 || R == 384);
+    if (rows <= 10240)
+        return q >= 1344 && q >= 2 * p && (R == 64 ? p >= 640 || (groups && rows > 8192) : R == 288 ? groups || rows > 5632 : R >= 96 && R <= 192);
+    if (rows <= 12800) return (R == 160 || (R == 192 && (groups || p >= 640))) && q >= 2304 && q >= 2 * p;
+    return rows > 16384 && rows <= 22528 && R >= 64 && q >= 1344 && 2 * q >= 5 * p && (groups || p >= 512 || R == 384);
 }
 // Where a few rows go through both products in one launch whose work-groups make the rows of T themselves (lr_few.hip), a round of work-groups of
 // 32 rows and 256 columns of Y (128 above r = 96).  Forward, GPU time in us, the other kernels / this one:
@@ -276,7 +283,7 @@ bool two_products(const ChainProblem* problems, int n, int of, int64_t M, int p,
 // Does a forward of these rows go faster with a place for T?
 bool place_pays(int64_t rows, int64_t M, int p, int q, int R) {
     if (few_rows((int)(rows / M), M, p, q, R, false) && few_supports(M, p, q, R)) return false;
-    return (wide_products(rows, p, q, R) && pair_supports(M, p, q, R)) || (two_products(rows, p, q, R, false) && lr_small_supports(M, q, p, R));
+    return (wide_products(rows, p, q, R, rows > M) && pair_supports(M, p, q, R)) || (two_products(rows, p, q, R, false) && lr_small_supports(M, q, p, R));
 }
 
 // From an image: a lane has one pixel for the whole kernel, while the loader waves of the other kernels compute
@@ -325,7 +332,7 @@ hipError_t chain_gather(const void* image, const PatchGeom& g, const void* P, co
 hipError_t chain(const void* Xin, const void* P, const void* Q, void* Yout, void* Tout,
                  int64_t M, int p, int q, int R, hipStream_t s) {
     const ChainProblem one{Xin, P, Q, Yout, Tout};
-    if (wide_products(M, p, q, R) && pair_supports(M, p, q, R) && place_for_T(&one, 1, M, p, R))
+    if (wide_products(M, p, q, R, false) && pair_supports(M, p, q, R) && place_for_T(&one, 1, M, p, R))
         return launch_pair_bf16(&one, 1, 1, M, p, q, R, s);
     if (few_rows(&one, 1, 1, M, p, q, R)) return launch_few_fwd(&one, 1, M, p, q, R, s);
     if (two_products(&one, 1, 1, M, p, q, R)) return launch_lr_small_fwd(&one, 1, 1, M, p, q, R, s);
@@ -1104,7 +1111,7 @@ hipError_t chain_grouped(const ChainProblem* pr, int G, int64_t M, int p, int q,
         hipError_t e;
         const int of = again ? G : n;
         // (the rule and the split of the rows are those of all groups: the order of the sums of T is the same for some of them)
-        if (wide_products(G * M, p, q, R) && pair_supports(M, p, q, R) && place_for_T(sel, n, M, p, R)) {
+        if (wide_products(G * M, p, q, R, G > 1) && pair_supports(M, p, q, R) && place_for_T(sel, n, M, p, R)) {
             e = launch_pair_bf16(sel, n, G, M, p, q, R, s);
         } else if (few_rows(sel, n, G, M, p, q, R)) {
             e = launch_few_fwd(sel, n, M, p, q, R, s);

@@ -98,6 +98,12 @@ def test_limits_of_the_two_products_of_many_rows(lib):
                (8193, 256, 1088, 128), (6000, 256, 1088, 96), (6000, 320, 1088, 160), (6000, 576, 1344, 64), (12608, 576, 2560, 192),
                (20000, 448, 1600, 320)]
     assert [a for a in inside if not want(*a)] == [] == [a for a in outside if want(*a)]
+    # groups: wider limits
+    together = lambda M, p, q, r: lib.lr_linear_fwd_wants_T(4, M, q, p, r, abt.ABT_BF16)
+    inside = [(12000, 320, 640, 160), (12500, 1024, 640, 256), (20480, 1024, 832, 352), (23000, 1024, 832, 320), (24577, 1024, 832, 352), (2500, 320, 1344, 64),
+              (7000, 320, 1152, 160), (5000, 320, 1600, 224), (28672, 2048, 320, 192)]
+    outside = [(1500, 320, 1344, 64), (1500, 256, 1088, 96), (20481, 1024, 832, 352), (24576, 1024, 832, 384), (28673, 2048, 320, 192), (12289, 512, 512, 256)]
+    assert [a for a in inside if not together(*a)] == [] == [a for a in outside if together(*a)]
 
 
 def test_fp32_backward_workspace_holds_the_full_split(lib):
