@@ -718,6 +718,7 @@ struct Plan {
            off_wg_intra = 0, off_gemm64 = 0, off_chol = 0, off_pairs = 0, off_gemm32 = 0, off_rotated = 0, off_data = 0, total = 0;
     int n_gram_tiles = 0, n_wg_cross = 0, n_wg_intra = 0, n_gemm64 = 0, n_gemm32 = 0, n_ptrs = 0;
     int nb_max = 0, K_max = 0, jb_max = 0;
+    bool one_size = false;  // all cores are K_max wide
     size_t lds_jacobi = 0;  // largest jb * K * 8 over the layers
     struct PerLayer {
         int K, jb, nb;
@@ -812,6 +813,14 @@ Plan make_plan(const abt_merge_desc* layers, int L) {
     p.off_pairs = take(sizeof(TriPair) * L);
     p.off_rotated = take(sizeof(int) * (kMaxSweepsCap + 1) * L);
     p.off_data = off;
+    p.one_size = true;
+    for (int l = 0; l < L; ++l) {                             // (see core_doubles())
+        Plan::PerLayer& q = p.pl[l];
+        if (q.K != p.K_max) p.one_size = false;
+        q.Ct = take(sizeof(double) * core_doubles(q.K));
+        q.diag = q.Ct + sizeof(double) * core_diag(q.K);
+        q.trace = q.Ct + sizeof(double) * core_trace(q.K);
+    }
     for (int l = 0; l < L; ++l) {
         const abt_merge_desc& d = layers[l];
         Plan::PerLayer& q = p.pl[l];
@@ -821,13 +830,10 @@ Plan make_plan(const abt_merge_desc* layers, int L) {
         q.LA = take(sizeof(double) * K * K);
         q.GB = take(sizeof(double) * K * K);
         q.LB = take(sizeof(double) * K * K);
-        q.Ct = take(sizeof(double) * K * K);
         q.Yt = take(sizeof(double) * K * K);
         q.sigma = take(sizeof(double) * K);
         q.s3 = take(sizeof(double) * K);
         q.s5 = take(sizeof(double) * K);
-        q.trace = take(sizeof(double) * 10);
-        q.diag = take(sizeof(double) * 16 * K);
         q.nrm = take(sizeof(double) * K);
         q.perm = take(sizeof(int) * K);
         q.PA = take(sizeof(float) * K * kc);
@@ -1194,7 +1200,7 @@ hipError_t merge_run(const abt_merge_desc* layers, const MergeSide* identity, in
         return false;
     };
     if (p.K_max == 32) {
-        ABT_TRY(launch_jacobi_single_pair(dl, cross, p.n_wg_cross, max_sweeps, s));
+        ABT_TRY(launch_jacobi_single_pair((double*)(ws + p.pl[0].Ct), (int*)(ws + p.off_rotated), L, max_sweeps, s));
     } else if (p.K_max <= 768) {
         // block form on the matrix cores, layers in groups (contiguous layer ranges with about the
         // same number of work-groups); wcross is layer-major, so a group is a slice of it
@@ -1250,7 +1256,8 @@ hipError_t merge_run(const abt_merge_desc* layers, const MergeSide* identity, in
                 for (Group& G : groups) {
                     if (G.done || round >= G.rounds) continue;
                     any = true;
-                    fail = launch_jacobi_block_round(dl, cross + G.wg0, G.wg1 - G.wg0, p.K_max, sweep, round, G.s);
+                    fail = launch_jacobi_block_round(dl, cross + G.wg0, G.wg1 - G.wg0, p.K_max, sweep, round, p.one_size ? (double*)(ws + p.pl[G.l0].Ct) : nullptr,
+                                                     (int*)(ws + p.off_rotated) + (size_t)G.l0 * (kMaxSweepsCap + 1), G.s);
                     if (fail != hipSuccess) break;
                 }
             if (!any || fail != hipSuccess) break;

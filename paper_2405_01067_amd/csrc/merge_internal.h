@@ -53,12 +53,19 @@ __device__ __forceinline__ bool sweep_finished(const LayerDev& L, int sweep) {
     return sweep > 0 && L.rotated[sweep - 1] == 0;
 }
 
-__device__ __forceinline__ double frob2(const LayerDev& L) {
+__device__ __forceinline__ double frob2(const double* trace) {
     double s = 0.0;
 #pragma unroll
-    for (int j = 0; j < 8; ++j) s += L.trace[2 + j];
+    for (int j = 0; j < 8; ++j) s += gload(trace + 2 + j);
     return s;
 }
+__device__ __forceinline__ double frob2(const LayerDev& L) { return frob2(L.trace); }
+
+// Ct, diag and trace of a layer lie behind each other, those of the layers too: where all cores are of one size, the kernels of the
+// iteration find theirs without the table.
+__host__ __device__ inline int64_t core_diag(int K) { return (int64_t)K * K; }
+__host__ __device__ inline int64_t core_trace(int K) { return (int64_t)K * K + 16 * K; }
+__host__ __device__ inline int64_t core_doubles(int K) { return (int64_t)K * K + 16 * K + 32; }
 
 // Rotation for a pair with squared norms alpha, beta and inner product gamma; returns false when
 // the pair counts as orthogonal.  x' = c x - s y, y' = s x + c y.
@@ -130,12 +137,13 @@ hipError_t launch_mean_gram(const LayerDev* layers, const GramJob* jobs, int njo
 
 // One round of the block Jacobi iteration for cores with K <= 768 (every layer of the batch):
 // `n_wg` work-groups, wg_map[i] = (layer, pair slot).  Round 0 of a sweep also orthogonalises the
-// columns inside every block.
+// columns inside every block.  `cores`: the first core's record where the launch has whole layers one behind the other, all of size K_max, whose
+// convergence flags begin at `rotated` (otherwise null, and the work-groups look everything up in the tables).
 hipError_t launch_jacobi_block_round(const LayerDev* layers, const int2* wg_map, int n_wg, int K_max,
-                                     int sweep, int round, hipStream_t s);
+                                     int sweep, int round, double* cores, int* rotated, hipStream_t s);
 
-// All sweeps of layers with K = 32 (every layer of the batch): one work-group per layer, one launch.
-hipError_t launch_jacobi_single_pair(const LayerDev* layers, const int2* wg_map, int n_wg, int max_sweeps, hipStream_t s);
+// All sweeps of `n` layers with K = 32 (every layer of the batch): one work-group per layer, one launch.
+hipError_t launch_jacobi_single_pair(double* cores, int* rotated, int n, int max_sweeps, hipStream_t s);
 
 // The stages around it where every core is 32 wide and no layer a dense weight (merge_small.hip): averages and parts of the Gram matrices;
 // Cholesky factors and core; values, rank and projections.

@@ -40,9 +40,10 @@ __device__ __forceinline__ int stage_addr(int n, int c) {
 
 struct __align__(16) JacobiShared {
     double stage[4][16 * 32];       // per wave: transposition tile; afterwards the waves' partial Gram tiles
-    double S[32][48];
     double Q[32][48];
-    f64x2 cs[31][16];               // (cosine, sine) of the rotations of all steps
+    float S[32][33];                // the Gram matrix times a power of two
+    int flags;                      // of a round: 1 rotated anything, 2 anything significant
+    float tan[2][31][16];           // tangents of the rotations of all steps (second half: what other lanes than the pairs' own come to)
 };
 
 // ---- The rotations of a block pair.  Columns 0..31 (the two blocks) are paired by exclusive or: step m pairs every i with
@@ -52,115 +53,179 @@ struct __align__(16) JacobiShared {
 __device__ __forceinline__ int left_of(int u, int p) { return ((u >> p) << (p + 1)) | (u & ((1 << p) - 1)); }
 __device__ __forceinline__ int right_of(int u, int p) { return left_of(u, p) | (1 << p); }
 
+__device__ __forceinline__ void lds_barrier() {    // leaves stores to memory on their way
+    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+}
+__device__ __forceinline__ void wave_lds_fence() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+// cosine and sine of a tangent to fp64 rounding (hardware reciprocal square root, two Newton steps)
+__device__ __forceinline__ f64x2 cosine_sine(float tangent) {
+    const double t = (double)tangent, w = fma(t, t, 1.0);
+    double y = __builtin_amdgcn_rsq(w);
+    y = y * fma(-0.5 * w, y * y, 1.5);
+    y = y * fma(-0.5 * w, y * y, 1.5);
+    return f64x2{y, y * t};
+}
+
 template <int N, class F, int I = 0>
 __device__ __forceinline__ void static_for(F&& f) {
     if constexpr (I < N) { f(std::integral_constant<int, I>{}); static_for<N, F, I + 1>(static_cast<F&&>(f)); }
 }
 
 template <int CTRL>
-__device__ __forceinline__ double dpp(double v) {
-    return __hiloint2double(__builtin_amdgcn_update_dpp(0, __double2hiint(v), CTRL, 0xf, 0xf, true),
-                            __builtin_amdgcn_update_dpp(0, __double2loint(v), CTRL, 0xf, 0xf, true));
-}
+__device__ __forceinline__ int dpp(int v) { return __builtin_amdgcn_update_dpp(0, v, CTRL, 0xf, 0xf, true); }
+template <int CTRL, int ROWS>
+__device__ __forceinline__ int dpp_rows(int old, int v) { return __builtin_amdgcn_update_dpp(old, v, CTRL, ROWS, 0xf, false); }
 // the value of lane ^ B (B = 1, 2, 3, 4, 8) by data-parallel moves: quad permutations, mirrored half rows, rotated rows
 template <int B>
-__device__ __forceinline__ double lane_xor(double v) {
+__device__ __forceinline__ int lane_xor(int v) {
     if constexpr (B == 1) return dpp<0xB1>(v);
     else if constexpr (B == 2) return dpp<0x4E>(v);
     else if constexpr (B == 3) return dpp<0x1B>(v);
     else if constexpr (B == 4) return dpp<0x1B>(dpp<0x141>(v));
     else return dpp<0x128>(v);
 }
-
-// The rotation of jacobi_rotation(), arranged for a short dependency chain (the 16 steps of a block
-// pair are serial, and this is the longest link of a step): no branches, the tangent in fp32, the
-// cosine from an fp32 reciprocal square root corrected by two terms of its series.  Any tangent
-// gives a rotation that is orthogonal to fp64 rounding (c = (1 + t^2)^(-1/2), s = c t); a tangent
-// good to 1e-7 leaves the pair with 1e-7 of its cosine.  `scale` is a power of two near
-// 1 / ||C||_F^2: squared norms lie between kZeroColumn2 and 1 times ||C||_F^2, so scaled inputs of a
-// pair that is rotated stay inside the fp32 range (|gamma| scale >= 1e-9 sqrt(1e-18 1e-18)).
-__device__ __forceinline__ void fast_rotation(double alpha, double beta, double gamma, double floor2, double scale,
-                                              double& c, double& s, bool& significant) {
-    const double lim = alpha * beta;
-    const double g2 = gamma * gamma;
-    const bool live = alpha > floor2 && beta > floor2;
-    significant = live && g2 > (kSignifTol * kSignifTol) * lim;
-    const bool rot = live && g2 > (kRotateTol * kRotateTol) * lim;
-    const float d = (float)((beta - alpha) * scale);
-    const float g2x = (float)((gamma + gamma) * scale);
-    const float zeta = d * __builtin_amdgcn_rcpf(g2x);
-    const float az = fabsf(zeta);                        // an overflow of az^2 ends in t = 0 (|t| < 1e-19)
-    const float ta = __builtin_amdgcn_rcpf(az + __builtin_amdgcn_sqrtf(fmaf(az, az, 1.0f)));
-    const float tf = zeta >= 0.0f ? ta : -ta;
-    const double c0 = (double)__builtin_amdgcn_rsqf(fmaf(tf, tf, 1.0f));
-    const double tn = (double)tf;
-    const double w = fma(tn, tn, 1.0);
-    const double e = fma(-(c0 * c0), w, 1.0);            // c = c0 (1 - e)^(-1/2) = c0 (1 + e/2 + 3 e^2/8 + ...)
-    const double cc = fma(c0, e * fma(0.375, e, 0.5), c0);
-    c = rot ? cc : 1.0;
-    s = rot ? cc * tn : 0.0;
+template <int B>
+__device__ __forceinline__ float lane_xor(float v) { return __int_as_float(lane_xor<B>(__float_as_int(v))); }
+template <int B>
+__device__ __forceinline__ double lane_xor(double v) {
+    return __hiloint2double(lane_xor<B>(__double2hiint(v)), lane_xor<B>(__double2loint(v)));
+}
+// the value of lane ^ 16 or ^ 32: whole rows of 16 lanes change places
+template <int B>
+__device__ __forceinline__ float row_xor(float v) {
+    const unsigned x = __float_as_uint(v);
+    if constexpr (B == 16) {
+        const auto r = __builtin_amdgcn_permlane16_swap(x, x, false, false);      // r[0]: even rows twice, r[1]: odd rows twice
+        return __uint_as_float((threadIdx.x & 16) ? r[0] : r[1]);
+    } else {
+        const auto r = __builtin_amdgcn_permlane32_swap(x, x, false, false);
+        return __uint_as_float((threadIdx.x & 32) ? r[0] : r[1]);
+    }
+}
+// lanes 0..15 to all four rows
+__device__ __forceinline__ float first_row(float v) {
+    const unsigned x = __float_as_uint(v);
+    const unsigned lo = __builtin_amdgcn_permlane32_swap(x, x, false, false)[0];
+    return __uint_as_float(__builtin_amdgcn_permlane16_swap(lo, lo, false, false)[0]);
+}
+// of a value that all rows hold alike: lane u ^ 4 q of it for lane (u, q)
+__device__ __forceinline__ float xor_by_row(float v) {
+    int x = __float_as_int(v);
+    x = dpp_rows<0x128, 0xc>(x, x);                           // rows 2, 3: lanes 8 apart
+    const int w = dpp_rows<0x141, 0xa>(x, x);                 // rows 1, 3: lanes 4 apart, in two moves
+    return __int_as_float(dpp_rows<0x1B, 0xa>(w, w));
 }
 
-// Level p on S by one wave, S in registers: lane (u = l % 16, q = l / 16) owns, for x = 4 q + e, the 2 x 2 cell rows
+// Level p on S by one wave, S in registers in fp32: lane (u = l % 16, q = l / 16) owns, for x = 4 q + e, the 2 x 2 cell rows
 // L(u), R(u ^ t) x columns L(v), R(v ^ t) with v = u ^ x.  t runs through a Gray code; when bit b of it changes, a cell finds its new
 // off-diagonal entries in the cell x ^ b (another register of the lane for b = 1, 2) and its new last
 // entry, like the one below the diagonal, in lane ^ b: register names and data-parallel moves, no LDS and no barrier
-// in a step.  The pairs' own cells are x = 0, in the first 16 lanes, which work the rotations out; the lanes that need
-// them fetch them with a lane permute.  A step takes 790 cycles, most of it the chain of the rotation formula, the permute
-// and the update of the pairs' cells.  With S in LDS, cells dealt to four waves and a barrier a step it took 1150; in a loop of four
-// steps a turn, with half the code, 920.
+// in a step.  The pairs' own cells are x = 0, in the first 16 lanes, which work the tangents out; these go to the other lanes by row
+// swaps and row-masked moves.
+// The tangent is that of jacobi_rotation(), without branches.  Any tangent gives a rotation that is orthogonal to fp64 rounding, as
+// the work-group forms cosine and sine from it in fp64 afterwards; one good to 1e-7 leaves the pair with 1e-7 of its cosine.  S is
+// scaled by a power of two near 1 / ||C||_F^2: squared norms lie between kZeroColumn2 and 1, inner products of a pair that is
+// rotated above 1e-9 of that, inside the fp32 range (their squares are not: the cosine is formed from two reciprocal square roots).
+// fp32 is enough for S: the columns themselves, the rotations and their product Q stay in fp64, and what 1e-7 of a cosine leaves is seen
+// by the next sweep, which forms S anew; the sweeps are as many (simulated for cores of 128 to 768, measured on those of the case table).
+// The steps are serial, so the chain through the pairs' own cells sets the pace, and the issue of the other cells' updates comes next: a
+// step updates the cells that the next tangent needs first and the others between the links of its formula.
+// A cell is multiplied by (1, -t; t, 1) from both sides and by the product of the cosines.
+// A step took 790 cycles in fp64 with lane permutes, 720 in fp32 with all cells ahead of the formula.
 template <int P>
-__device__ __forceinline__ void rotate_level(double (*S)[48], f64x2 (*cs)[16], double floor2, double scale, bool& any_signif,
-                                             double* diagI = nullptr, double* diagJ = nullptr) {
+__device__ __forceinline__ void rotate_level(float (*S)[33], float* tangents, float floor2, bool& any, bool& any_signif, int* flags = nullptr,
+                                             double unscale = 1.0, double* diagI = nullptr, double* diagJ = nullptr) {
     const int lane = threadIdx.x & 63, u = lane & 15, q = lane >> 4;
-    double m00[4], m01[4], m10[4], m11[4];
+    float* const mine = tangents + u + (q ? 31 * 16 : 0);
+    float m00[4], m01[4], m10[4], m11[4];
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
         const int v = u ^ (4 * q + e);
         m00[e] = S[left_of(u, P)][left_of(v, P)]; m01[e] = S[left_of(u, P)][right_of(v, P)];
         m10[e] = S[right_of(u, P)][left_of(v, P)]; m11[e] = S[right_of(u, P)][right_of(v, P)];
     }
+    // the tangent of the pair with squared norms alpha, beta and inner product gamma, in three links
+    float zeta, w, ra, rb, rg, own;
+    auto link1 = [&](float alpha, float beta, float gamma) {
+        rg = __builtin_amdgcn_rcpf(gamma + gamma);
+        ra = __builtin_amdgcn_rsqf(alpha); rb = __builtin_amdgcn_rsqf(beta);
+        zeta = beta - alpha;
+    };
+    auto link2 = [&]() {
+        zeta *= rg;                                      // an overflow of its square ends in t = 0 (|t| < 1e-19)
+        w = __builtin_amdgcn_sqrtf(fmaf(zeta, zeta, 1.0f));
+    };
+    auto link3 = [&](float alpha, float beta, float gamma) {
+        const float cosine = fabsf(gamma) * ra * rb;
+        const bool live = alpha > floor2 && beta > floor2;
+        any_signif |= live && cosine > (float)kSignifTol;                  // (this and the next count in the first 16 lanes)
+        any |= live && cosine > (float)kRotateTol;
+        const float ta = __builtin_amdgcn_rcpf(fabsf(zeta) + w);
+        own = live && cosine > (float)kRotateTol ? copysignf(ta, zeta) : 0.0f;
+    };
+    link1(m00[0], m11[0], m01[0]); link2(); link3(m00[0], m11[0], m01[0]);
     // one step; B: the bit of t that changes after it (0: the last step)
     auto step = [&](auto bit, int k) {
         constexpr int B = decltype(bit)::value;
-        double c, s; bool signif;
-        fast_rotation(m00[0], m11[0], m01[0], floor2, scale, c, s, signif);
-        if (lane < 16) { any_signif |= signif; cs[k][u] = f64x2{c, s}; }
-        const double c1 = __shfl(c, u, 64), s1 = __shfl(s, u, 64);
-        double c2[4], s2[4];
-        c2[0] = __shfl(c, u ^ (4 * q), 64); s2[0] = __shfl(s, u ^ (4 * q), 64);
-        c2[1] = lane_xor<1>(c2[0]); s2[1] = lane_xor<1>(s2[0]);
-        c2[2] = lane_xor<2>(c2[0]); s2[2] = lane_xor<2>(s2[0]);
-        c2[3] = lane_xor<3>(c2[0]); s2[3] = lane_xor<3>(s2[0]);
-        double n01[4], n10[4], n11[4];
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            const double t00 = c1 * m00[e] - s1 * m10[e], t01 = c1 * m01[e] - s1 * m11[e];
-            const double t10 = s1 * m00[e] + c1 * m10[e], t11 = s1 * m01[e] + c1 * m11[e];
-            m00[e] = c2[e] * t00 - s2[e] * t01; n01[e] = s2[e] * t00 + c2[e] * t01;
-            n10[e] = c2[e] * t10 - s2[e] * t11; n11[e] = s2[e] * t10 + c2[e] * t11;
+        constexpr int E1 = B == 2 ? 2 : 1, E2 = B == 2 ? 1 : 2;            // the second cell to be updated, the third
+        mine[16 * k] = own;
+        const float t = first_row(own);
+        float t2[4], c12[4];
+        t2[0] = xor_by_row(t);
+        const float c1 = __builtin_amdgcn_rsqf(fmaf(t, t, 1.0f));
+        const float c2 = xor_by_row(c1);
+        t2[1] = lane_xor<1>(t2[0]); t2[2] = lane_xor<2>(t2[0]); t2[3] = lane_xor<3>(t2[0]);
+        c12[0] = c1 * c2; c12[1] = c1 * lane_xor<1>(c2); c12[2] = c1 * lane_xor<2>(c2); c12[3] = c1 * lane_xor<3>(c2);
+        float n01[4], n10[4], n11[4];
+        auto update = [&](auto which) {
+            constexpr int e = decltype(which)::value;
+            const float a = fmaf(-t, m10[e], m00[e]), b = fmaf(-t, m11[e], m01[e]), c = fmaf(t, m00[e], m10[e]), d = fmaf(t, m01[e], m11[e]);
+            m00[e] = fmaf(-t2[e], b, a) * c12[e]; n01[e] = fmaf(t2[e], a, b) * c12[e];
+            n10[e] = fmaf(-t2[e], d, c) * c12[e]; n11[e] = fmaf(t2[e], c, d) * c12[e];
+        };
+        update(std::integral_constant<int, 0>{});
+        if constexpr (B == 1 || B == 2) update(std::integral_constant<int, E1>{});
+        float beta = 0.0f, gamma = 0.0f;
+        if constexpr (B != 0) {
+            beta = lane_xor<B>(n11[0]);
+            if constexpr (B < 4) gamma = n01[E1];
+            else gamma = row_xor<4 * B>(n01[0]);
+            link1(m00[0], beta, gamma);
         }
+        __builtin_amdgcn_sched_barrier(0);
+        if constexpr (B != 1 && B != 2) update(std::integral_constant<int, E1>{});
+        update(std::integral_constant<int, E2>{});
+        if constexpr (B != 0) link2();
+        __builtin_amdgcn_sched_barrier(0);
+        update(std::integral_constant<int, 3>{});
+        if constexpr (B != 0) link3(m00[0], beta, gamma);
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
             if constexpr (B == 0) { m01[e] = n01[e]; m10[e] = n10[e]; m11[e] = n11[e]; }
             else if constexpr (B < 4) { m01[e] = n01[e ^ B]; m10[e] = lane_xor<B>(n10[e ^ B]); m11[e] = lane_xor<B>(n11[e]); }
-            else {
-                m01[e] = __shfl_xor(n01[e], 4 * B, 64); m10[e] = __shfl_xor(n10[e], 5 * B, 64); m11[e] = lane_xor<B>(n11[e]);
-            }
+            else { m01[e] = row_xor<4 * B>(n01[e]); m10[e] = row_xor<4 * B>(lane_xor<B>(n10[e])); m11[e] = lane_xor<B>(n11[e]); }
         }
     };
     static_for<(1 << P)>([&](auto i) {
         constexpr int k = decltype(i)::value;
+        if constexpr (P == 4 && k == 8) lds_barrier();   // the first eight tangents: the other waves begin with Q
         step(std::integral_constant<int, (k + 1 < (1 << P) ? (k + 1) & -(k + 1) : 0)>{}, k);
     });
     constexpr int t = ((1 << P) - 1) ^ (((1 << P) - 1) >> 1);
-    if (P == 4) {                                        // the last level: the two diagonal blocks, for the next round
+    if constexpr (P == 4) {                              // the last level: the two diagonal blocks, for the next round
+        const bool r = __builtin_amdgcn_ballot_w64(any && lane < 16) != 0, sg = __builtin_amdgcn_ballot_w64(any_signif && lane < 16) != 0;
+        if (lane == 0) *flags = (r ? 1 : 0) | (sg ? 2 : 0);
+        lds_barrier();
         if (diagI == nullptr) return;
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
             const int v = u ^ (4 * q + e);
-            gstore(diagI + 16 * u + v, m00[e]);
-            gstore(diagJ + 16 * (u ^ t) + (v ^ t), m11[e]);
+            gstore(diagI + 16 * u + v, (double)m00[e] * unscale);
+            gstore(diagJ + 16 * (u ^ t) + (v ^ t), (double)m11[e] * unscale);
         }
         return;
     }
@@ -170,35 +235,90 @@ __device__ __forceinline__ void rotate_level(double (*S)[48], f64x2 (*cs)[16], d
         S[left_of(u, P)][left_of(v, P)] = m00[e]; S[left_of(u, P)][right_of(v ^ t, P)] = m01[e];
         S[right_of(u ^ t, P)][left_of(v, P)] = m10[e]; S[right_of(u ^ t, P)][right_of(v ^ t, P)] = m11[e];
     }
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    wave_lds_fence();
 }
 
-// The same rotations on the columns of Q, rows 8 wave .. 8 wave + 7 by this wave: lane (u, q) owns columns L(u), R(u ^ t) of
-// rows q and q + 4 of them.
+// The rotations on the columns of Q, by the three waves that do not work them out (w = 0..2): rows 12 w .. 12 w + 11, lane (u, q) owning
+// rows q, q + 4 and q + 8 of them (up to row 31).
+// A level inside the blocks: columns L(u), R(u ^ t).
 template <int P>
-__device__ __forceinline__ void accumulate_level(double (*Q)[48], const f64x2 (*cs)[16]) {
-    const int lane = threadIdx.x & 63, u = lane & 15, r = 8 * (threadIdx.x >> 6) + (lane >> 4);
-    double a0 = Q[r][left_of(u, P)], b0 = Q[r][right_of(u, P)], a1 = Q[r + 4][left_of(u, P)], b1 = Q[r + 4][right_of(u, P)];
-    auto step = [&](auto bit, int k) {
-        constexpr int B = decltype(bit)::value;
-        const f64x2 rot = cs[k][u];
-        const double c = rot[0], s = rot[1];
-        const double x0 = c * a0 - s * b0, y0 = s * a0 + c * b0, x1 = c * a1 - s * b1, y1 = s * a1 + c * b1;
-        a0 = x0; a1 = x1;
-        if constexpr (B == 0) { b0 = y0; b1 = y1; }
-        else { b0 = lane_xor<B>(y0); b1 = lane_xor<B>(y1); }
-    };
-    static_for<(1 << P)>([&](auto i) {
-        constexpr int k = decltype(i)::value;
-        step(std::integral_constant<int, (k + 1 < (1 << P) ? (k + 1) & -(k + 1) : 0)>{}, k);
+__device__ __forceinline__ void accumulate_level(double (*Q)[48], const f64x2* table, int w) {
+    const int lane = threadIdx.x & 63, u = lane & 15, r = 12 * w + (lane >> 4);
+    double a[3], b[3];
+#pragma unroll
+    for (int i = 0; i < 3; ++i) { a[i] = Q[(r + 4 * i) & 31][left_of(u, P)]; b[i] = Q[(r + 4 * i) & 31][right_of(u, P)]; }
+    static_for<(1 << P)>([&](auto which) {
+        constexpr int k = decltype(which)::value, B = k + 1 < (1 << P) ? (k + 1) & -(k + 1) : 0;
+        const f64x2 rot = table[16 * k + u];
+#pragma unroll
+        for (int j = 0; j < 3; ++j) {
+            const double x = rot[0] * a[j] - rot[1] * b[j], y = rot[1] * a[j] + rot[0] * b[j];
+            a[j] = x;
+            if constexpr (B == 0) b[j] = y;
+            else b[j] = lane_xor<B>(y);
+        }
     });
     constexpr int t = ((1 << P) - 1) ^ (((1 << P) - 1) >> 1);
-    Q[r][left_of(u, P)] = a0; Q[r][right_of(u ^ t, P)] = b0; Q[r + 4][left_of(u, P)] = a1; Q[r + 4][right_of(u ^ t, P)] = b1;
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+#pragma unroll
+    for (int i = 0; i < 3; ++i)
+        if (r + 4 * i < 32) { Q[r + 4 * i][left_of(u, P)] = a[i]; Q[r + 4 * i][right_of(u ^ t, P)] = b[i]; }
+    wave_lds_fence();
+}
+// All levels inside the blocks, on the identity, once their tangents are there
+__device__ __forceinline__ void accumulate_inside(double (*Q)[48], const float (*tangents)[16], f64x2* table, int w) {
+    const int lane = threadIdx.x & 63;
+#pragma unroll
+    for (int i = 0; i < 6; ++i) {
+        const int row = 12 * w + 2 * i + (lane >> 5), col = lane & 31;
+        if (row < 32) Q[row][col] = row == col ? 1.0 : 0.0;
+    }
+    lds_barrier();
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const int k = 4 * i + (lane >> 4);
+        if (k < 15) table[64 * i + lane] = cosine_sine(tangents[16 + k][lane & 15]);
+    }
+    wave_lds_fence();
+    accumulate_level<3>(Q, table, w);
+    accumulate_level<2>(Q, table + 16 * 8, w);
+    accumulate_level<1>(Q, table + 16 * 12, w);
+    accumulate_level<0>(Q, table + 16 * 14, w);
+}
+
+// The rotations between the blocks: columns u and 16 + (u ^ t).  The tangents come in two halves; each wave makes a table of its own of
+// their cosines and sines.  FRESH: Q is the identity so far.
+template <bool FRESH>
+__device__ __forceinline__ void accumulate_cross(double (*Q)[48], const float (*tangents)[16], f64x2* table, int w) {
+    const int lane = threadIdx.x & 63, u = lane & 15, r = 12 * w + (lane >> 4);
+    double a[3], b[3];
+#pragma unroll
+    for (int i = 0; i < 3; ++i) {
+        const int row = r + 4 * i;
+        if (FRESH) { a[i] = row == u ? 1.0 : 0.0; b[i] = row == u + 16 ? 1.0 : 0.0; }
+        else { a[i] = Q[row & 31][u]; b[i] = Q[row & 31][u + 16]; }
+    }
+    static_for<2>([&](auto half) {
+        constexpr int H = decltype(half)::value;
+        lds_barrier();
+        table[lane] = cosine_sine(tangents[8 * H + (lane >> 4)][u]);
+        table[64 + lane] = cosine_sine(tangents[8 * H + 4 + (lane >> 4)][u]);
+        wave_lds_fence();
+        static_for<8>([&](auto i) {
+            constexpr int k = 8 * H + decltype(i)::value, B = k + 1 < 16 ? (k + 1) & -(k + 1) : 0;
+            const f64x2 rot = table[16 * (k & 7) + u];
+#pragma unroll
+            for (int j = 0; j < 3; ++j) {
+                const double x = rot[0] * a[j] - rot[1] * b[j], y = rot[1] * a[j] + rot[0] * b[j];
+                a[j] = x;
+                if constexpr (B == 0) b[j] = y;
+                else b[j] = lane_xor<B>(y);
+            }
+        });
+        wave_lds_fence();
+    });
+#pragma unroll
+    for (int i = 0; i < 3; ++i)
+        if (r + 4 * i < 32) { Q[r + 4 * i][u] = a[i]; Q[r + 4 * i][16 + (u ^ 8)] = b[i]; }
 }
 
 // NT: 16-row tiles per wave (two per 32-row chunk: its even and its odd rows), K <= 64 NT.
@@ -208,28 +328,44 @@ __device__ __forceinline__ void accumulate_level(double (*Q)[48], const f64x2 (*
 // sweep took 129 us for one core of 32, this 54.
 template <int NT, bool WHOLE>
 __global__ __launch_bounds__(256, (WHOLE ? 1 : NT <= 2 ? 3 : NT <= 6 ? 2 : 1))
-void jacobi_block_kernel(const LayerDev* __restrict__ layers, const int2* __restrict__ wg_map, int sweep, int round) {
+void jacobi_block_kernel(double* cores, int* rotated, int K, int sweep, int round, const LayerDev* __restrict__ layers, const int2* __restrict__ wg_map) {
     __shared__ JacobiShared sh;
-    const int2 wm = wg_map[blockIdx.x];                   // (layer, pair slot)
-    const LayerDev& L = layers[wm.x];
-    if (sweep_finished(L, sweep)) return;
-    const int K = L.K, nb = K >> 4;
+    // Layers of one size: everything follows from the arguments.  Looked up in the tables, work-group -> layer -> flag
+    // and pointers -> panel, four loads that wait for each other and miss every cache at the start of a launch took 8000 of the 40000
+    // cycles of a round of 12 cores of 384.
+    double *Ct, *diag;
+    const double* trace;
+    int slot;
+    if (cores != nullptr) {
+        Ct = cores + (int64_t)blockIdx.y * core_doubles(K);
+        diag = Ct + core_diag(K);
+        trace = Ct + core_trace(K);
+        rotated += (int)blockIdx.y * (kMaxSweepsCap + 1);
+        slot = (int)blockIdx.x;
+    } else {
+        const int2 wm = wg_map[blockIdx.x];               // (layer, pair slot)
+        const LayerDev& L = layers[wm.x];
+        Ct = L.Ct; diag = L.diag; trace = L.trace; rotated = L.rotated; K = L.K;
+        slot = wm.y;
+    }
+    if (sweep > 0 && rotated[sweep - 1] == 0) return;     // the previous sweep found no significant pair: the iteration has converged
+    const int nb = K >> 4;
     const int max_sweeps = WHOLE ? round : 0;
     if (WHOLE) round = 0;
     if (round >= nb - 1 || K > 64 * NT || (WHOLE && nb != 2)) return;
     // circle method: slot 0 pairs block nb-1 with `round`; slot j pairs (round + j) with (round - j)
-    int bI, bJ;
-    if (wm.y == 0) { bI = nb - 1; bJ = round; }
-    else { bI = (round + wm.y) % (nb - 1); bJ = (round - wm.y + (nb - 1)) % (nb - 1); }
+    int bI = round + slot, bJ = round - slot;
+    if (slot == 0) bI = nb - 1;
+    else { if (bI >= nb - 1) bI -= nb - 1; if (bJ < 0) bJ += nb - 1; }
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, n = lane & 15, kq = lane >> 4;
 
     // Gram matrices of the two blocks as the last round left them, a value of each per thread; ||C||_F^2
     const int gi = (tid >> 6) + 4 * (tid & 3), gj = (tid >> 2) & 15;      // this thread's element of a 16 x 16 tile
-    double* const diagI = L.diag + bI * 256;
-    double* const diagJ = L.diag + bJ * 256;
+    double* const diagI = diag + bI * 256;
+    double* const diagJ = diag + bJ * 256;
     const bool fresh = WHOLE || round == 0;               // formed again from the columns once per sweep
     double ownII = fresh ? 0.0 : gload(diagI + 16 * gi + gj), ownJJ = fresh ? 0.0 : gload(diagJ + 16 * gi + gj);
-    const double frob = frob2(L);
+    const double frob = frob2(trace);
     // ---- load the panel: D[t][s] = P[row(t, n)][column kq + 4 s], columns 0..15 = block I, 16..31 = block J (rows past K
     // repeat row 0 and are cleared behind the last load: a predicate on a load would be waited for with it)
     double D[NT][8];
@@ -239,7 +375,7 @@ void jacobi_block_kernel(const LayerDev* __restrict__ layers, const int2* __rest
 #pragma unroll
         for (int s = 0; s < 8; ++s) {
             const int col = (s < 4 ? bI * 16 + kq + 4 * s : bJ * 16 + kq + 4 * (s - 4));
-            const f64x2 v = gload(reinterpret_cast<const f64x2*>(L.Ct + (int64_t)col * K + (row0 < K ? row0 : 0)));
+            const f64x2 v = gload(reinterpret_cast<const f64x2*>(Ct + (int64_t)col * K + (row0 < K ? row0 : 0)));
             D[2 * tt][s] = v[0];
             D[2 * tt + 1][s] = v[1];
         }
@@ -295,8 +431,9 @@ void jacobi_block_kernel(const LayerDev* __restrict__ layers, const int2* __rest
         if (fresh) stage[0 * 256 + lane * 4 + v] = gII[v];
     }
     __syncthreads();
+    const double scale = ldexp(1.0, -__builtin_amdgcn_frexp_exp(frob));
     {
-        const double sIJ = total(256 + tid);
+        const float sIJ = (float)(total(256 + tid) * scale);
         sh.S[gi][16 + gj] = sIJ;
         sh.S[16 + gj][gi] = sIJ;
         if (fresh) ownII = total(tid);
@@ -308,58 +445,39 @@ void jacobi_block_kernel(const LayerDev* __restrict__ layers, const int2* __rest
         __syncthreads();
         ownJJ = total(tid);
     }
-    sh.S[gi][gj] = ownII;
-    sh.S[16 + gi][16 + gj] = ownJJ;
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-        const int idx = tid + 256 * e;
-        sh.Q[idx >> 5][idx & 31] = (idx >> 5) == (idx & 31) ? 1.0 : 0.0;
-    }
+    sh.S[gi][gj] = (float)(ownII * scale);
+    sh.S[16 + gi][16 + gj] = (float)(ownJJ * scale);
+    const bool intra = round == 0;
     __syncthreads();
 
-    // ---- anything to rotate?  (pairs inside the blocks count in round 0 only)
-    const double floor2 = kZeroColumn2 * frob;
-    const double scale = ldexp(1.0, -__builtin_amdgcn_frexp_exp(frob));
-    const bool intra = round == 0;
-    int need = 0;
-    {
-        const int i = tid >> 4, j = tid & 15;
-        auto test = [&](int p, int q) {
-            const double a = sh.S[p][p], b = sh.S[q][q], g = sh.S[p][q];
-            if (a > floor2 && b > floor2 && g * g > (kRotateTol * kRotateTol) * (a * b)) need = 1;
-        };
-        test(i, 16 + j);
-        if (intra && i < j) { test(i, j); test(16 + i, 16 + j); }
+    // ---- cyclic Jacobi on S by one wave (which one differs among the work-groups that share a compute unit), the same
+    // rotations on Q by the others, eight steps behind
+    const float floor2 = (float)(kZeroColumn2 * frob * scale);
+    const int other = (wave - (int)((blockIdx.x + blockIdx.y) & 3) - 1) & 3;         // 3: this wave works the rotations out
+    bool any = false, any_signif = false;
+    if (other == 3) {
+        if (intra) {
+            rotate_level<3>(sh.S, sh.tan[0][16], floor2, any, any_signif);
+            rotate_level<2>(sh.S, sh.tan[0][24], floor2, any, any_signif);
+            rotate_level<1>(sh.S, sh.tan[0][28], floor2, any, any_signif);
+            rotate_level<0>(sh.S, sh.tan[0][30], floor2, any, any_signif);
+            lds_barrier();
+        }
+        rotate_level<4>(sh.S, sh.tan[0][0], floor2, any, any_signif, &sh.flags, 1.0 / scale, WHOLE ? nullptr : diagI, WHOLE ? nullptr : diagJ);
+    } else if (intra) {
+        accumulate_inside(sh.Q, sh.tan[0], reinterpret_cast<f64x2*>(stage), other);
+        accumulate_cross<false>(sh.Q, sh.tan[0], reinterpret_cast<f64x2*>(stage), other);
+    } else {
+        accumulate_cross<true>(sh.Q, sh.tan[0], reinterpret_cast<f64x2*>(stage), other);
     }
-    if (!__syncthreads_or(need)) {
+    lds_barrier();
+    const int flags = sh.flags;
+    const bool again = WHOLE && (flags & 2);
+    if (tid == 0 && (flags & 2)) gstore(rotated + sweep, 1);
+    if (!(flags & 1)) {
         if (WHOLE) break;
-        if (fresh) { gstore(diagI + 16 * gi + gj, ownII); gstore(diagJ + 16 * gi + gj, ownJJ); }
         return;                              // the columns are untouched: nothing else to store
     }
-
-    // ---- cyclic Jacobi on S by one wave (which one differs among the work-groups that share a compute unit), then the
-    // same rotations on Q by all
-    bool any_signif = false;
-    if (wave == (int)(blockIdx.x & 3)) {
-        if (intra) {
-            rotate_level<3>(sh.S, sh.cs + 16, floor2, scale, any_signif);
-            rotate_level<2>(sh.S, sh.cs + 24, floor2, scale, any_signif);
-            rotate_level<1>(sh.S, sh.cs + 28, floor2, scale, any_signif);
-            rotate_level<0>(sh.S, sh.cs + 30, floor2, scale, any_signif);
-        }
-        rotate_level<4>(sh.S, sh.cs, floor2, scale, any_signif, WHOLE ? nullptr : diagI, WHOLE ? nullptr : diagJ);
-    }
-    __syncthreads();
-    if (intra) {
-        accumulate_level<3>(sh.Q, sh.cs + 16);
-        accumulate_level<2>(sh.Q, sh.cs + 24);
-        accumulate_level<1>(sh.Q, sh.cs + 28);
-        accumulate_level<0>(sh.Q, sh.cs + 30);
-    }
-    accumulate_level<4>(sh.Q, sh.cs);
-    __syncthreads();
-    const bool again = WHOLE && __syncthreads_or(any_signif);
-    if (any_signif) L.rotated[sweep] = 1;
 
     // ---- P <- P Q as (Q^T P^T): A operand = Q^T tile, B operand = the panel registers
     double qa[2][8];
@@ -390,7 +508,7 @@ void jacobi_block_kernel(const LayerDev* __restrict__ layers, const int2* __rest
 #pragma unroll
             for (int s = 0; s < 8; ++s) {
                 const int col = (s < 4 ? bI * 16 + kq + 4 * s : bJ * 16 + kq + 4 * (s - 4));
-                gstore(reinterpret_cast<f64x2*>(L.Ct + (int64_t)col * K + row0), f64x2{D[2 * tt][s], D[2 * tt + 1][s]});
+                gstore(reinterpret_cast<f64x2*>(Ct + (int64_t)col * K + row0), f64x2{D[2 * tt][s], D[2 * tt + 1][s]});
             }
         }
     }
@@ -399,21 +517,22 @@ void jacobi_block_kernel(const LayerDev* __restrict__ layers, const int2* __rest
 }  // namespace
 
 hipError_t launch_jacobi_block_round(const LayerDev* layers, const int2* wg_map, int n_wg, int K_max,
-                                     int sweep, int round, hipStream_t s) {
+                                     int sweep, int round, double* cores, int* rotated, hipStream_t s) {
     if (n_wg <= 0) return hipSuccess;
-    const dim3 grid(n_wg), block(256);
-    if (K_max <= 128) hipLaunchKernelGGL((jacobi_block_kernel<2, false>), grid, block, 0, s, layers, wg_map, sweep, round);
-    else if (K_max <= 256) hipLaunchKernelGGL((jacobi_block_kernel<4, false>), grid, block, 0, s, layers, wg_map, sweep, round);
-    else if (K_max <= 384) hipLaunchKernelGGL((jacobi_block_kernel<6, false>), grid, block, 0, s, layers, wg_map, sweep, round);
-    else if (K_max <= 512) hipLaunchKernelGGL((jacobi_block_kernel<8, false>), grid, block, 0, s, layers, wg_map, sweep, round);
-    else if (K_max <= 768) hipLaunchKernelGGL((jacobi_block_kernel<12, false>), grid, block, 0, s, layers, wg_map, sweep, round);
+    const int slots = K_max / 32;
+    const dim3 grid(cores ? slots : n_wg, cores ? n_wg / slots : 1), block(256);
+    if (K_max <= 128) hipLaunchKernelGGL((jacobi_block_kernel<2, false>), grid, block, 0, s, cores, rotated, K_max, sweep, round, layers, wg_map);
+    else if (K_max <= 256) hipLaunchKernelGGL((jacobi_block_kernel<4, false>), grid, block, 0, s, cores, rotated, K_max, sweep, round, layers, wg_map);
+    else if (K_max <= 384) hipLaunchKernelGGL((jacobi_block_kernel<6, false>), grid, block, 0, s, cores, rotated, K_max, sweep, round, layers, wg_map);
+    else if (K_max <= 512) hipLaunchKernelGGL((jacobi_block_kernel<8, false>), grid, block, 0, s, cores, rotated, K_max, sweep, round, layers, wg_map);
+    else if (K_max <= 768) hipLaunchKernelGGL((jacobi_block_kernel<12, false>), grid, block, 0, s, cores, rotated, K_max, sweep, round, layers, wg_map);
     else return hipErrorInvalidValue;
     return hipGetLastError();
 }
 
-hipError_t launch_jacobi_single_pair(const LayerDev* layers, const int2* wg_map, int n_wg, int max_sweeps, hipStream_t s) {
-    if (n_wg <= 0) return hipSuccess;
-    hipLaunchKernelGGL((jacobi_block_kernel<2, true>), dim3(n_wg), dim3(256), 0, s, layers, wg_map, 0, max_sweeps);
+hipError_t launch_jacobi_single_pair(double* cores, int* rotated, int n, int max_sweeps, hipStream_t s) {
+    if (n <= 0) return hipSuccess;
+    hipLaunchKernelGGL((jacobi_block_kernel<2, true>), dim3(1, n), dim3(256), 0, s, cores, rotated, 32, 0, max_sweeps, (const LayerDev*)nullptr, (const int2*)nullptr);
     return hipGetLastError();
 }
 
