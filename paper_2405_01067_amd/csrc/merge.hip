@@ -718,10 +718,11 @@ struct Plan {
            off_wg_intra = 0, off_gemm64 = 0, off_chol = 0, off_pairs = 0, off_gemm32 = 0, off_rotated = 0, off_data = 0, total = 0;
     int n_gram_tiles = 0, n_wg_cross = 0, n_wg_intra = 0, n_gemm64 = 0, n_gemm32 = 0, n_ptrs = 0;
     int nb_max = 0, K_max = 0, jb_max = 0;
-    bool one_size = false;  // all cores are K_max wide
+    bool one_size = true;   // all cores are K_max wide
+    bool quad = false;      // four blocks of columns a work-group in the iteration
     size_t lds_jacobi = 0;  // largest jb * K * 8 over the layers
     struct PerLayer {
-        int K, jb, nb;
+        int K, jb, nb, slots;    // slots: work-groups of a round
         size_t Abar, Bbar, LA, GB, LB, Ct, Yt, sigma, s3, s5, trace, diag, nrm, perm, PA, PB, chol, gparts;
     };
     std::vector<PerLayer> pl;
@@ -789,7 +790,6 @@ Plan make_plan(const abt_merge_desc* layers, int L) {
         Plan::PerLayer& q = p.pl[l];
         q.K = K; q.jb = jacobi_block(K); q.nb = K / q.jb;
         p.n_ptrs += 2 * d.G;
-        p.n_wg_cross += q.nb / 2;
         p.n_wg_intra += q.nb;
         if (q.nb > p.nb_max) p.nb_max = q.nb;
         if (K > p.K_max) p.K_max = K;
@@ -803,6 +803,20 @@ Plan make_plan(const abt_merge_desc* layers, int L) {
         build_gram_jobs(layers, L, jobs);
         p.n_gram_tiles = (int)jobs.size();
     }
+    int pairs = 0;
+    bool even = true;                                          // whole pairs of double blocks everywhere
+    for (const Plan::PerLayer& q : p.pl) {
+        p.one_size = p.one_size && q.K == p.K_max;
+        pairs += q.K / 32;
+        even = even && q.K % 64 == 0;
+    }
+    // Four blocks a work-group halve the traffic and the launches, two blocks have the shorter chain: with few work-groups that chain is
+    // what counts, with many the traffic.  Merge, ms, two blocks / four: 384 columns, 1 layer 3.14 / 3.81, 12 (144 pairs) 4.68 / 4.74, 16
+    // (192) 4.90 / 4.84, 48 6.82 / 6.39; 512 columns, 12 (192) 9.33 / 9.50, 16 9.82 / 9.80, 48 16.1 / 14.7; 256 columns, 8 2.36 / 2.43, 48 3.84 / 3.41;
+    // 128 columns, 1 0.84 / 0.89, 4 1.19 / 1.06, 48 1.80 / 1.67.  An odd double block costs a round with half of the pairs (160 columns, 48 layers 2.30 /
+    // 2.41).  Cores of 64 make all their sweeps in one launch with four blocks: 1 layer 0.52 / 0.49, 4 0.81 / 0.54.
+    p.quad = even && p.K_max <= 512 && (pairs >= 192 || (p.K_max <= 128 && L >= 4) || (p.K_max == 64 && p.one_size));
+    for (Plan::PerLayer& q : p.pl) p.n_wg_cross += q.slots = p.K_max <= 768 ? jacobi_slots(q.K, p.quad) : q.nb / 2;
     p.off_ptrs = take(sizeof(void*) * p.n_ptrs);
     p.off_gram_tiles = take(sizeof(GramJob) * p.n_gram_tiles);
     p.off_wg_cross = take(sizeof(int2) * p.n_wg_cross);
@@ -813,10 +827,8 @@ Plan make_plan(const abt_merge_desc* layers, int L) {
     p.off_pairs = take(sizeof(TriPair) * L);
     p.off_rotated = take(sizeof(int) * (kMaxSweepsCap + 1) * L);
     p.off_data = off;
-    p.one_size = true;
     for (int l = 0; l < L; ++l) {                             // (see core_doubles())
         Plan::PerLayer& q = p.pl[l];
-        if (q.K != p.K_max) p.one_size = false;
         q.Ct = take(sizeof(double) * core_doubles(q.K));
         q.diag = q.Ct + sizeof(double) * core_diag(q.K);
         q.trace = q.Ct + sizeof(double) * core_trace(q.K);
@@ -1050,7 +1062,7 @@ hipError_t merge_run(const abt_merge_desc* layers, const MergeSide* identity, in
         v.S_out = d.S_out; v.k_out = d.k_out;
 
         const int K = q.K;
-        for (int sidx = 0; sidx < q.nb / 2; ++sidx) wcross.push_back(make_int2(l, sidx));
+        for (int sidx = 0; sidx < q.slots; ++sidx) wcross.push_back(make_int2(l, sidx));
         for (int b = 0; b < q.nb; ++b) wintra.push_back(make_int2(l, b));
 
         const int kc = (int)(d.k_cap < K ? d.k_cap : K);
@@ -1201,6 +1213,8 @@ hipError_t merge_run(const abt_merge_desc* layers, const MergeSide* identity, in
     };
     if (p.K_max == 32) {
         ABT_TRY(launch_jacobi_single_pair((double*)(ws + p.pl[0].Ct), (int*)(ws + p.off_rotated), L, max_sweeps, s));
+    } else if (p.K_max == 64 && p.one_size && p.quad) {
+        ABT_TRY(launch_jacobi_block_round(dl, cross, p.n_wg_cross, 64, p.quad, 0, 0, max_sweeps, (double*)(ws + p.pl[0].Ct), (int*)(ws + p.off_rotated), s));
     } else if (p.K_max <= 768) {
         // block form on the matrix cores, layers in groups (contiguous layer ranges with about the
         // same number of work-groups); wcross is layer-major, so a group is a slice of it
@@ -1216,8 +1230,8 @@ hipError_t merge_run(const abt_merge_desc* layers, const MergeSide* identity, in
                 Group G{l, l, wg, wg, 0, false, g == 0 ? s : g_side.stream[g - 1]};
                 const int target = (int)((int64_t)p.n_wg_cross * (g + 1) / ngroups);
                 while (G.l1 < L && (G.wg1 < target || g == ngroups - 1)) {
-                    G.wg1 += p.pl[G.l1].nb / 2;
-                    if (p.pl[G.l1].nb - 1 > G.rounds) G.rounds = p.pl[G.l1].nb - 1;
+                    G.wg1 += p.pl[G.l1].slots;
+                    if (jacobi_rounds(p.pl[G.l1].K, p.quad) > G.rounds) G.rounds = jacobi_rounds(p.pl[G.l1].K, p.quad);
                     ++G.l1;
                 }
                 l = G.l1; wg = G.wg1;
@@ -1252,11 +1266,11 @@ hipError_t merge_run(const abt_merge_desc* layers, const MergeSide* identity, in
         };
         for (int sweep = 0; sweep < max_sweeps && fail == hipSuccess; ++sweep) {
             bool any = false;
-            for (int round = 0; round < p.nb_max - 1 && fail == hipSuccess; ++round)
+            for (int round = 0; round < jacobi_rounds(p.K_max, p.quad) && fail == hipSuccess; ++round)
                 for (Group& G : groups) {
                     if (G.done || round >= G.rounds) continue;
                     any = true;
-                    fail = launch_jacobi_block_round(dl, cross + G.wg0, G.wg1 - G.wg0, p.K_max, sweep, round, p.one_size ? (double*)(ws + p.pl[G.l0].Ct) : nullptr,
+                    fail = launch_jacobi_block_round(dl, cross + G.wg0, G.wg1 - G.wg0, p.K_max, p.quad, sweep, round, 0, p.one_size ? (double*)(ws + p.pl[G.l0].Ct) : nullptr,
                                                      (int*)(ws + p.off_rotated) + (size_t)G.l0 * (kMaxSweepsCap + 1), G.s);
                     if (fail != hipSuccess) break;
                 }

@@ -135,12 +135,15 @@ struct GramJob { int layer, which, ti, tj; };
 // whose row length n is not a multiple of four) for the element-wise one.
 hipError_t launch_mean_gram(const LayerDev* layers, const GramJob* jobs, int njobs, int njobs_unaligned, hipStream_t s);
 
-// One round of the block Jacobi iteration for cores with K <= 768 (every layer of the batch):
-// `n_wg` work-groups, wg_map[i] = (layer, pair slot).  Round 0 of a sweep also orthogonalises the
-// columns inside every block.  `cores`: the first core's record where the launch has whole layers one behind the other, all of size K_max, whose
-// convergence flags begin at `rotated` (otherwise null, and the work-groups look everything up in the tables).
-hipError_t launch_jacobi_block_round(const LayerDev* layers, const int2* wg_map, int n_wg, int K_max,
-                                     int sweep, int round, double* cores, int* rotated, hipStream_t s);
+// One round of the block Jacobi iteration for cores with K <= 768 (every layer of the batch): `n_wg` work-groups,
+// wg_map[i] = (layer, slot), jacobi_slots() slots a layer, jacobi_rounds() rounds a sweep: `quad` pairs double blocks of 32 columns
+// (K_max up to 512), otherwise blocks of 16.  Round 0 of a sweep also orthogonalises the columns inside every (double) block.  `cores`: the first core's record where the launch has whole layers one behind the other, all of size K_max, whose
+// convergence flags begin at `rotated` (otherwise null, and the work-groups look everything up in the tables).  max_sweeps: 0, or, with `quad` where all
+// cores are 64 wide (and `cores` is given), the number of sweeps that the launch may make.
+inline int jacobi_slots(int K, bool quad) { return quad ? (K / 32 + 1) / 2 : K / 32; }
+inline int jacobi_rounds(int K, bool quad) { return 2 * jacobi_slots(K, quad) - 1; }
+hipError_t launch_jacobi_block_round(const LayerDev* layers, const int2* wg_map, int n_wg, int K_max, bool quad,
+                                     int sweep, int round, int max_sweeps, double* cores, int* rotated, hipStream_t s);
 
 // All sweeps of `n` layers with K = 32 (every layer of the batch): one work-group per layer, one launch.
 hipError_t launch_jacobi_single_pair(double* cores, int* rotated, int n, int max_sweeps, hipStream_t s);

@@ -6,24 +6,28 @@
 // columns P (K x 32) a work-group
 //   1. forms the Gram matrix S = P^T P (32 x 32) with v_mfma_f64_16x16x4: the 16 x 16 tile between the blocks; the
 //      tiles inside them are what the last round's rotations left of S, and formed anew in round 0 of a sweep only,
-//   2. runs the cyclic Jacobi eigenvalue iteration on S: 16 steps of 16 disjoint rotations, every rotation applied to S
-//      from both sides and accumulated in Q (32 x 32).  These are the plane rotations the column form of the
+//   2. runs the cyclic Jacobi eigenvalue iteration on S, by one wave: 16 steps of 16 disjoint rotations, every rotation applied to S
+//      from both sides; three other waves accumulate them in Q (32 x 32).  These are the plane rotations the column form of the
 //      method would apply to the 256 column pairs of the two blocks, in the same order; they are
 //      worked out on the 32 x 32 Gram matrix instead of on K-long columns,
-//   3. applies them at once: P <- P Q, again on the matrix cores.
+//   3. applies them at once: P <- P Q, again on the matrix cores, all waves.
 // Round 0 of a sweep first rotates the pairs inside each of the two blocks the same way (15 steps).
 //
+// With many work-groups (the rule is where the batch is planned) a work-group has four blocks instead, a, b | c, d: double blocks meet in
+// the tournament, and a round rotates the pairs (a, c) and (b, d), then (a, d) and (b, c), two at a time; round 0 begins with (a, b) and (c, d).
+//
 // The panel lives in registers from load to store, in the operand layout of step 3: a lane holds
-// the rows r = l % 16 of its wave's row tiles and the columns l / 16 + 4 s (s = 0..7); with the
+// the rows r = l % 16 of its wave's row tiles and the columns l / 16 + 4 s of a block (s = 0..3); with the
 // product taken as (Q^T P^T) the result tile comes out of the matrix core in that same layout, so
 // the update is in place.  Step 1 needs the transposed operand order (contraction over rows); each
-// wave passes its row tiles through a private 4 KB LDS tile for that.
+// wave passes its row tiles through a private LDS tile for that.
 //
-// What bounds it: a round is one dependent chain.  K = 384, cycles of a work-group: panel load 3400 alone, 7000 to 10000 with 576
-// of them (nothing survives in L2 from the round before), Gram matrix 3000 (6500 with the tiles inside the blocks), rotations 14000 of which Q
-// 2000, update 6400 (fp64 matrix instructions), store 2000, and some 10000 between the end of a round and the start of
-// the next.  Sweeps of config 5 (48 cores of 384, 8 sweeps): 6.07 ms before the rotations moved to registers, 4.97 after,
-// 4.60 with the kept diagonal tiles; 16 cores of 768, 9 sweeps: 17.5, 16.7, 16.2 ms (one work-group per compute unit, 384 of them).
+// What bounds it: nothing survives in L2 from one round to the next, so a round reads and writes all cores beyond it: 64 GB for 16 cores
+// of 768 in 9 sweeps, 5.0 TB/s in 12.7 ms, which is what a large copy reaches (two work-groups per compute unit; one at a time 13.5 ms; 14.0 without the
+// loads and stores that overlap the arithmetic; 16.2 with the rotations in fp64).  48 cores of 384, 8 sweeps: 4.6 ms with the rotations in fp64, 4.05 in
+// fp32, 3.7 with four blocks, which is half the traffic.  With few cores a work-group's chain counts: cycles at K = 384 (two blocks): arguments and flag 1500, first
+// columns 3000, Gram matrix 5600, rotations 9800, the last of Q 1100, update 6400 (fp64 matrix instructions); four blocks 72000 a round of three times
+// those links.  Launches follow each other in 1.3 us.
 #include <type_traits>
 
 #include "merge_internal.h"
@@ -38,11 +42,11 @@ __device__ __forceinline__ int stage_addr(int n, int c) {
     return 32 * n + ((c + 16 * (n & 1) + 2 * (n >> 1)) & 31);
 }
 
-struct __align__(16) JacobiShared {
-    double stage[4][16 * 32];       // per wave: transposition tile; afterwards the waves' partial Gram tiles
+// What the rotations of a block pair need in LDS
+struct __align__(16) PairShared {
     double Q[32][48];
     float S[32][33];                // the Gram matrix times a power of two
-    int flags;                      // of a round: 1 rotated anything, 2 anything significant
+    int did;                        // 0: rotated nothing, 1: nothing significant, 2: something
     float tan[2][31][16];           // tangents of the rotations of all steps (second half: what other lanes than the pairs' own come to)
 };
 
@@ -53,6 +57,12 @@ struct __align__(16) JacobiShared {
 __device__ __forceinline__ int left_of(int u, int p) { return ((u >> p) << (p + 1)) | (u & ((1 << p) - 1)); }
 __device__ __forceinline__ int right_of(int u, int p) { return left_of(u, p) | (1 << p); }
 
+// threadIdx.x, anew: what is computed from it in a loop is not carried through the loop in registers (150 of them otherwise, and as many spilled)
+__device__ __forceinline__ int thread_anew() {
+    int t = threadIdx.x;
+    asm volatile("" : "+v"(t));
+    return t;
+}
 __device__ __forceinline__ void lds_barrier() {    // leaves stores to memory on their way
     asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
 }
@@ -137,9 +147,9 @@ __device__ __forceinline__ float xor_by_row(float v) {
 // A cell is multiplied by (1, -t; t, 1) from both sides and by the product of the cosines.
 // A step took 790 cycles in fp64 with lane permutes, 720 in fp32 with all cells ahead of the formula.
 template <int P>
-__device__ __forceinline__ void rotate_level(float (*S)[33], float* tangents, float floor2, bool& any, bool& any_signif, int* flags = nullptr,
-                                             double unscale = 1.0, double* diagI = nullptr, double* diagJ = nullptr) {
-    const int lane = threadIdx.x & 63, u = lane & 15, q = lane >> 4;
+__device__ __forceinline__ void rotate_level(float (*S)[33], float* tangents, float floor2, bool& any, bool& any_signif, int* did = nullptr,
+                                             float* diagI = nullptr, float* diagJ = nullptr) {
+    const int lane = thread_anew() & 63, u = lane & 15, q = lane >> 4;
     float* const mine = tangents + u + (q ? 31 * 16 : 0);
     float m00[4], m01[4], m10[4], m11[4];
 #pragma unroll
@@ -209,6 +219,7 @@ __device__ __forceinline__ void rotate_level(float (*S)[33], float* tangents, fl
             else if constexpr (B < 4) { m01[e] = n01[e ^ B]; m10[e] = lane_xor<B>(n10[e ^ B]); m11[e] = lane_xor<B>(n11[e]); }
             else { m01[e] = row_xor<4 * B>(n01[e]); m10[e] = row_xor<4 * B>(lane_xor<B>(n10[e])); m11[e] = lane_xor<B>(n11[e]); }
         }
+        __builtin_amdgcn_sched_barrier(0);
     };
     static_for<(1 << P)>([&](auto i) {
         constexpr int k = decltype(i)::value;
@@ -218,14 +229,14 @@ __device__ __forceinline__ void rotate_level(float (*S)[33], float* tangents, fl
     constexpr int t = ((1 << P) - 1) ^ (((1 << P) - 1) >> 1);
     if constexpr (P == 4) {                              // the last level: the two diagonal blocks, for the next round
         const bool r = __builtin_amdgcn_ballot_w64(any && lane < 16) != 0, sg = __builtin_amdgcn_ballot_w64(any_signif && lane < 16) != 0;
-        if (lane == 0) *flags = (r ? 1 : 0) | (sg ? 2 : 0);
+        if (lane == 0) *did = sg ? 2 : r ? 1 : 0;
         lds_barrier();
         if (diagI == nullptr) return;
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
             const int v = u ^ (4 * q + e);
-            gstore(diagI + 16 * u + v, (double)m00[e] * unscale);
-            gstore(diagJ + 16 * (u ^ t) + (v ^ t), (double)m11[e] * unscale);
+            diagI[17 * u + v] = m00[e];
+            diagJ[17 * (u ^ t) + (v ^ t)] = m11[e];
         }
         return;
     }
@@ -243,7 +254,7 @@ __device__ __forceinline__ void rotate_level(float (*S)[33], float* tangents, fl
 // A level inside the blocks: columns L(u), R(u ^ t).
 template <int P>
 __device__ __forceinline__ void accumulate_level(double (*Q)[48], const f64x2* table, int w) {
-    const int lane = threadIdx.x & 63, u = lane & 15, r = 12 * w + (lane >> 4);
+    const int lane = thread_anew() & 63, u = lane & 15, r = 12 * w + (lane >> 4);
     double a[3], b[3];
 #pragma unroll
     for (int i = 0; i < 3; ++i) { a[i] = Q[(r + 4 * i) & 31][left_of(u, P)]; b[i] = Q[(r + 4 * i) & 31][right_of(u, P)]; }
@@ -266,7 +277,7 @@ __device__ __forceinline__ void accumulate_level(double (*Q)[48], const f64x2* t
 }
 // All levels inside the blocks, on the identity, once their tangents are there
 __device__ __forceinline__ void accumulate_inside(double (*Q)[48], const float (*tangents)[16], f64x2* table, int w) {
-    const int lane = threadIdx.x & 63;
+    const int lane = thread_anew() & 63;
 #pragma unroll
     for (int i = 0; i < 6; ++i) {
         const int row = 12 * w + 2 * i + (lane >> 5), col = lane & 31;
@@ -289,7 +300,7 @@ __device__ __forceinline__ void accumulate_inside(double (*Q)[48], const float (
 // their cosines and sines.  FRESH: Q is the identity so far.
 template <bool FRESH>
 __device__ __forceinline__ void accumulate_cross(double (*Q)[48], const float (*tangents)[16], f64x2* table, int w) {
-    const int lane = threadIdx.x & 63, u = lane & 15, r = 12 * w + (lane >> 4);
+    const int lane = thread_anew() & 63, u = lane & 15, r = 12 * w + (lane >> 4);
     double a[3], b[3];
 #pragma unroll
     for (int i = 0; i < 3; ++i) {
@@ -321,172 +332,380 @@ __device__ __forceinline__ void accumulate_cross(double (*Q)[48], const float (*
         if (r + 4 * i < 32) { Q[r + 4 * i][u] = a[i]; Q[r + 4 * i][16 + (u ^ 8)] = b[i]; }
 }
 
-// NT: 16-row tiles per wave (two per 32-row chunk: its even and its odd rows), K <= 64 NT.
-// (Three work-groups per compute unit at K = 384 spill and take 7.0 ms in place of 4.6 over a merge; two at K = 768, 24.7 of 16.2.)
-// WHOLE (K = 32: two blocks, one pair): the work-group holds the whole core, so it runs all sweeps in one launch, the
-// panel in registers throughout; `round` is the sweep cap.  A launch and a poll of the convergence flags per
-// sweep took 129 us for one core of 32, this 54.
-template <int NT, bool WHOLE>
-__global__ __launch_bounds__(256, (WHOLE ? 1 : NT <= 2 ? 3 : NT <= 6 ? 2 : 1))
-void jacobi_block_kernel(double* cores, int* rotated, int K, int sweep, int round, const LayerDev* __restrict__ layers, const int2* __restrict__ wg_map) {
-    __shared__ JacobiShared sh;
-    // Layers of one size: everything follows from the arguments.  Looked up in the tables, work-group -> layer -> flag
-    // and pointers -> panel, four loads that wait for each other and miss every cache at the start of a launch took 8000 of the 40000
-    // cycles of a round of 12 cores of 384.
-    double *Ct, *diag;
-    const double* trace;
-    int slot;
-    if (cores != nullptr) {
-        Ct = cores + (int64_t)blockIdx.y * core_doubles(K);
-        diag = Ct + core_diag(K);
-        trace = Ct + core_trace(K);
-        rotated += (int)blockIdx.y * (kMaxSweepsCap + 1);
-        slot = (int)blockIdx.x;
-    } else {
-        const int2 wm = wg_map[blockIdx.x];               // (layer, pair slot)
-        const LayerDev& L = layers[wm.x];
-        Ct = L.Ct; diag = L.diag; trace = L.trace; rotated = L.rotated; K = L.K;
-        slot = wm.y;
-    }
-    if (sweep > 0 && rotated[sweep - 1] == 0) return;     // the previous sweep found no significant pair: the iteration has converged
-    const int nb = K >> 4;
-    const int max_sweeps = WHOLE ? round : 0;
-    if (WHOLE) round = 0;
-    if (round >= nb - 1 || K > 64 * NT || (WHOLE && nb != 2)) return;
-    // circle method: slot 0 pairs block nb-1 with `round`; slot j pairs (round + j) with (round - j)
-    int bI = round + slot, bJ = round - slot;
-    if (slot == 0) bI = nb - 1;
-    else { if (bI >= nb - 1) bI -= nb - 1; if (bJ < 0) bJ += nb - 1; }
-    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, n = lane & 15, kq = lane >> 4;
-
-    // Gram matrices of the two blocks as the last round left them, a value of each per thread; ||C||_F^2
-    const int gi = (tid >> 6) + 4 * (tid & 3), gj = (tid >> 2) & 15;      // this thread's element of a 16 x 16 tile
-    double* const diagI = diag + bI * 256;
-    double* const diagJ = diag + bJ * 256;
-    const bool fresh = WHOLE || round == 0;               // formed again from the columns once per sweep
-    double ownII = fresh ? 0.0 : gload(diagI + 16 * gi + gj), ownJJ = fresh ? 0.0 : gload(diagJ + 16 * gi + gj);
-    const double frob = frob2(trace);
-    // ---- load the panel: D[t][s] = P[row(t, n)][column kq + 4 s], columns 0..15 = block I, 16..31 = block J (rows past K
-    // repeat row 0 and are cleared behind the last load: a predicate on a load would be waited for with it)
-    double D[NT][8];
-#pragma unroll
-    for (int tt = 0; tt < NT / 2; ++tt) {
-        const int row0 = 32 * (wave + 4 * tt) + 2 * n;
-#pragma unroll
-        for (int s = 0; s < 8; ++s) {
-            const int col = (s < 4 ? bI * 16 + kq + 4 * s : bJ * 16 + kq + 4 * (s - 4));
-            const f64x2 v = gload(reinterpret_cast<const f64x2*>(Ct + (int64_t)col * K + (row0 < K ? row0 : 0)));
-            D[2 * tt][s] = v[0];
-            D[2 * tt + 1][s] = v[1];
-        }
-    }
-    __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-    for (int tt = 0; tt < NT / 2; ++tt) {
-        const bool in = 32 * (wave + 4 * tt) + 2 * n < K;
-#pragma unroll
-        for (int s = 0; s < 8; ++s) {
-            D[2 * tt][s] = in ? D[2 * tt][s] : 0.0;
-            D[2 * tt + 1][s] = in ? D[2 * tt + 1][s] : 0.0;
-        }
-    }
-
-    for (;; ++sweep) {                                   // one turn; WHOLE: until a sweep rotates nothing of weight
-    // ---- S = P^T P: the tile between the blocks, and those inside them (II, JJ) if there are none of the last round
-    f64x4 gII = {0.0, 0.0, 0.0, 0.0}, gIJ = gII, gJJ = gII;
-    double* stage = sh.stage[wave];
-    auto gram = [&](auto all) {
-#pragma unroll
-        for (int t = 0; t < NT; ++t) {
-#pragma unroll
-            for (int s = 0; s < 8; ++s) stage[stage_addr(n, kq + 4 * s)] = D[t][s];
-            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-            __builtin_amdgcn_wave_barrier();
-            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-            double a0[4], a1[4];
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                a0[q] = stage[stage_addr(4 * q + kq, n)];
-                a1[q] = stage[stage_addr(4 * q + kq, 16 + n)];
-            }
-            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-            __builtin_amdgcn_wave_barrier();
-            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                if (decltype(all)::value) gII = __builtin_amdgcn_mfma_f64_16x16x4f64(a0[q], a0[q], gII, 0, 0, 0);
-                gIJ = __builtin_amdgcn_mfma_f64_16x16x4f64(a0[q], a1[q], gIJ, 0, 0, 0);
-                if (decltype(all)::value) gJJ = __builtin_amdgcn_mfma_f64_16x16x4f64(a1[q], a1[q], gJJ, 0, 0, 0);
-            }
-        }
-    };
-    if (fresh) gram(std::true_type{});
-    else gram(std::false_type{});
-    // partial tiles of the four waves, added in wave order; result element (i, j) of a tile sits in
-    // lane (j, i % 4), register i / 4
-    auto total = [&](int at) { return ((sh.stage[0][at] + sh.stage[1][at]) + sh.stage[2][at]) + sh.stage[3][at]; };
-#pragma unroll
-    for (int v = 0; v < 4; ++v) {
-        stage[1 * 256 + lane * 4 + v] = gIJ[v];
-        if (fresh) stage[0 * 256 + lane * 4 + v] = gII[v];
-    }
-    __syncthreads();
-    const double scale = ldexp(1.0, -__builtin_amdgcn_frexp_exp(frob));
-    {
-        const float sIJ = (float)(total(256 + tid) * scale);
-        sh.S[gi][16 + gj] = sIJ;
-        sh.S[16 + gj][gi] = sIJ;
-        if (fresh) ownII = total(tid);
-    }
-    if (fresh) {
-        __syncthreads();
-#pragma unroll
-        for (int v = 0; v < 4; ++v) stage[lane * 4 + v] = gJJ[v];
-        __syncthreads();
-        ownJJ = total(tid);
-    }
-    sh.S[gi][gj] = (float)(ownII * scale);
-    sh.S[16 + gi][16 + gj] = (float)(ownJJ * scale);
-    const bool intra = round == 0;
-    __syncthreads();
-
-    // ---- cyclic Jacobi on S by one wave (which one differs among the work-groups that share a compute unit), the same
-    // rotations on Q by the others, eight steps behind
-    const float floor2 = (float)(kZeroColumn2 * frob * scale);
-    const int other = (wave - (int)((blockIdx.x + blockIdx.y) & 3) - 1) & 3;         // 3: this wave works the rotations out
-    bool any = false, any_signif = false;
-    if (other == 3) {
-        if (intra) {
+// The sixteen steps of a block pair, after those inside its blocks if `inside`, by the waves that share it: `role` 3 works the rotations out,
+// 0 to 2 accumulate them.  `table`: 4 KB of LDS of the wave's own.  Four barriers with `inside`, three without; Q and `did` are
+// there after the last.
+__device__ __forceinline__ void rotate_pair(PairShared& sh, bool inside, int role, f64x2* table, float floor2, float* diagI, float* diagJ) {
+    if (role == 3) {
+        bool any = false, any_signif = false;
+        if (inside) {
             rotate_level<3>(sh.S, sh.tan[0][16], floor2, any, any_signif);
             rotate_level<2>(sh.S, sh.tan[0][24], floor2, any, any_signif);
             rotate_level<1>(sh.S, sh.tan[0][28], floor2, any, any_signif);
             rotate_level<0>(sh.S, sh.tan[0][30], floor2, any, any_signif);
             lds_barrier();
         }
-        rotate_level<4>(sh.S, sh.tan[0][0], floor2, any, any_signif, &sh.flags, 1.0 / scale, WHOLE ? nullptr : diagI, WHOLE ? nullptr : diagJ);
-    } else if (intra) {
-        accumulate_inside(sh.Q, sh.tan[0], reinterpret_cast<f64x2*>(stage), other);
-        accumulate_cross<false>(sh.Q, sh.tan[0], reinterpret_cast<f64x2*>(stage), other);
+        rotate_level<4>(sh.S, sh.tan[0][0], floor2, any, any_signif, &sh.did, diagI, diagJ);
+    } else if (inside) {
+        accumulate_inside(sh.Q, sh.tan[0], table, role);
+        accumulate_cross<false>(sh.Q, sh.tan[0], table, role);
     } else {
-        accumulate_cross<true>(sh.Q, sh.tan[0], reinterpret_cast<f64x2*>(stage), other);
+        accumulate_cross<true>(sh.Q, sh.tan[0], table, role);
     }
     lds_barrier();
-    const int flags = sh.flags;
-    const bool again = WHOLE && (flags & 2);
-    if (tid == 0 && (flags & 2)) gstore(rotated + sweep, 1);
-    if (!(flags & 1)) {
-        if (WHOLE) break;
-        return;                              // the columns are untouched: nothing else to store
+}
+
+struct Core { double *Ct, *diag; const double* trace; int* rotated; int K, slot; };
+// Layers of one size: everything follows from the arguments.  Looked up in the tables, work-group -> layer -> flag
+// and pointers -> columns, four loads that wait for each other and miss every cache at the start of a launch took 8000
+// cycles of a round of 12 cores of 384, now 1500.
+__device__ __forceinline__ Core find_core(double* cores, int* rotated, int K, const LayerDev* layers, const int2* wg_map) {
+    if (cores != nullptr) {
+        double* const Ct = cores + (int64_t)blockIdx.y * core_doubles(K);
+        return Core{Ct, Ct + core_diag(K), Ct + core_trace(K), rotated + (int)blockIdx.y * (kMaxSweepsCap + 1), K, (int)blockIdx.x};
+    }
+    const int2 wm = wg_map[blockIdx.x];                   // (layer, pair slot)
+    const LayerDev& L = layers[wm.x];
+    return Core{L.Ct, L.diag, L.trace, L.rotated, L.K, wm.y};
+}
+
+// NT: 16-row tiles per wave (two per 32-row chunk: its even and its odd rows), K <= 128 NT.  Eight waves, one work-group per compute
+// unit; waves 0 to 3 work on the first block pair of the two, 4 to 7 on the second, and all of them on both where rows count.
+// max_sweeps > 0 (cores of 64, one pair of double blocks): the work-group holds the whole core and runs all sweeps in one launch.
+template <int NT>
+__global__ __launch_bounds__(512, 1)
+void jacobi_quad_kernel(double* cores, int* rotated, int K, int sweep, int round, int max_sweeps, const LayerDev* __restrict__ layers, const int2* __restrict__ wg_map) {
+    __shared__ struct __align__(16) {
+        double stage[8][2][16 * 32];    // per wave: transposition tiles; afterwards the waves' partial Gram tiles, then tables of rotations
+        PairShared pair[2];
+        float diag[4][16 * 17];         // Gram matrices of the blocks, scaled
+    } sh;
+    const Core c = find_core(cores, rotated, K, layers, wg_map);
+    double* const Ct = c.Ct;
+    double* const diag = c.diag;
+    K = c.K;
+    rotated = c.rotated;
+    const int slot = c.slot;
+    if (sweep > 0 && rotated[sweep - 1] == 0) return;     // the previous sweep found no significant pair: the iteration has converged
+    const int nd = K >> 5, np = nd + (nd & 1);            // double blocks; with an empty one where their number is odd
+    const bool whole = max_sweeps > 0;
+    if (round >= np - 1 || K > 128 * NT) return;
+    // circle method: slot 0 pairs double block np - 1 with `round`; slot j pairs (round + j) with (round - j)
+    int dI = round + slot, dJ = round - slot;
+    if (slot == 0) dI = np - 1;
+    else { if (dI >= np - 1) dI -= np - 1; if (dJ < 0) dJ += np - 1; }
+    if (dI >= nd) { dI = dJ; dJ = -1; }                   // no partner: round 0 has the pair inside the double block
+    if (dJ < 0 && round != 0) return;
+    const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, n = lane & 15, kq = lane >> 4;
+    const int half = wave >> 2, t8 = tid & 255;            // block pair of this wave, thread within it
+    const int gi = (t8 >> 6) + 4 * (t8 & 3), gj = (t8 >> 2) & 15;         // this thread's element of a 16 x 16 tile
+    PairShared& mine = sh.pair[half];
+
+    // Position i holds block blk[i], whose Gram matrix is tile id[i]; the pairs are positions (0, 2) and (1, 3).  Round 0 begins
+    // with positions 1 and 2 exchanged, so that its first pairs are (a, b) and (c, d).
+    int blk[4], id[4] = {0, 1, 2, 3};
+    {
+        const int b0 = 2 * dI, b1 = 2 * dI + 1, b2 = dJ < 0 ? -1 : 2 * dJ, b3 = dJ < 0 ? -1 : 2 * dJ + 1;
+        blk[0] = b0; blk[1] = round == 0 ? b2 : b1; blk[2] = round == 0 ? b1 : b2; blk[3] = b3;
+        if (round == 0) { id[1] = 2; id[2] = 1; }
+    }
+    // Gram matrices of the blocks as the last round left them, two values of each thread; ||C||_F^2
+    double kept[2] = {0.0, 0.0};
+    if (round != 0) {
+        kept[0] = gload(diag + (half ? blk[1] : blk[0]) * 256 + 16 * gi + gj);
+        kept[1] = gload(diag + (half ? blk[3] : blk[2]) * 256 + 16 * gi + gj);
+    }
+    const double frob = frob2(c.trace);
+    // ---- load the columns: D[t][4 i + s] = C[row(t, n)][16 blk[i] + kq + 4 s].  Chunks past K and blocks that are not there are zero, both
+    // the same for the whole wave, so nothing is done to a value that has just been asked for and the Gram matrix begins with the first chunk.
+    double D[NT][16];
+#pragma unroll
+    for (int tt = 0; tt < NT / 2; ++tt) {
+        const int row0 = 32 * (wave + 8 * tt) + 2 * n;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            if (32 * (wave + 8 * tt) < K && blk[i] >= 0) {
+#pragma unroll
+                for (int s = 0; s < 4; ++s) {
+                    const f64x2 v = gload(reinterpret_cast<const f64x2*>(Ct + (int64_t)(16 * blk[i] + kq + 4 * s) * K + row0));
+                    D[2 * tt][4 * i + s] = v[0];
+                    D[2 * tt + 1][4 * i + s] = v[1];
+                }
+            } else {
+#pragma unroll
+                for (int s = 0; s < 4; ++s) D[2 * tt][4 * i + s] = D[2 * tt + 1][4 * i + s] = 0.0;
+            }
+        }
+    }
+    const double scale = ldexp(1.0, -__builtin_amdgcn_frexp_exp(frob));
+    const float floor2 = (float)(kZeroColumn2 * frob * scale);
+    if (round != 0) {
+        sh.diag[half][17 * gi + gj] = (float)(kept[0] * scale);           // (id[i] = i)
+        sh.diag[2 + half][17 * gi + gj] = (float)(kept[1] * scale);
+    }
+    // exchange positions A and B
+    auto exchange = [&](auto a, auto b) {
+        constexpr int A = decltype(a)::value, B = decltype(b)::value;
+#pragma unroll
+        for (int t = 0; t < NT; ++t)
+#pragma unroll
+            for (int s = 0; s < 4; ++s) { const double v = D[t][4 * A + s]; D[t][4 * A + s] = D[t][4 * B + s]; D[t][4 * B + s] = v; }
+        int v = blk[A]; blk[A] = blk[B]; blk[B] = v;
+        v = id[A]; id[A] = id[B]; id[B] = v;
+    };
+    using One = std::integral_constant<int, 1>;
+    using Two = std::integral_constant<int, 2>;
+    using Three = std::integral_constant<int, 3>;
+
+    auto store_chunk = [&](int tt, int n, int kq) {
+        const int row0 = 32 * (wave + 8 * tt) + 2 * n;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            if (blk[i] < 0) continue;
+#pragma unroll
+            for (int s = 0; s < 4; ++s)
+                gstore(reinterpret_cast<f64x2*>(Ct + (int64_t)(16 * blk[i] + kq + 4 * s) * K + row0), f64x2{D[2 * tt][4 * i + s], D[2 * tt + 1][4 * i + s]});
+        }
+    };
+    int touched = 0, seen = 0;                            // the most that was done, ever and in this sweep
+    for (;; ++sweep) {                                    // one turn; a whole core: until a sweep rotates nothing of weight
+#pragma unroll 1
+    for (int inner = round == 0 ? 0 : 1; inner < 3; ++inner) {
+        const bool inside = inner == 0;
+        const int tid = thread_anew(), lane = tid & 63, n = lane & 15, kq = lane >> 4;
+        const int gi = ((tid >> 6) & 3) + 4 * (tid & 3), gj = (tid >> 2) & 15;
+        // ---- S = P^T P of both pairs: the tile between the blocks, and those inside them if there are none yet
+        f64x4 gIJ[2] = {}, gII[2] = {}, gJJ[2] = {};
+        auto gram = [&](auto all) {
+#pragma unroll
+            for (int t = 0; t < NT; ++t) {
+                if (t % 2 == 0 && 32 * (wave + 4 * t) >= K) break;        // no rows of this core
+                double a0[2][4], a1[2][4];
+#pragma unroll
+                for (int p = 0; p < 2; ++p)
+#pragma unroll
+                    for (int s = 0; s < 4; ++s) {
+                        sh.stage[wave][p][stage_addr(n, kq + 4 * s)] = D[t][4 * p + s];
+                        sh.stage[wave][p][stage_addr(n, 16 + kq + 4 * s)] = D[t][8 + 4 * p + s];
+                    }
+                wave_lds_fence();
+#pragma unroll
+                for (int p = 0; p < 2; ++p)
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) {
+                        a0[p][q] = sh.stage[wave][p][stage_addr(4 * q + kq, n)];
+                        a1[p][q] = sh.stage[wave][p][stage_addr(4 * q + kq, 16 + n)];
+                    }
+                wave_lds_fence();
+#pragma unroll
+                for (int q = 0; q < 4; ++q)
+#pragma unroll
+                    for (int p = 0; p < 2; ++p) {
+                        gIJ[p] = __builtin_amdgcn_mfma_f64_16x16x4f64(a0[p][q], a1[p][q], gIJ[p], 0, 0, 0);
+                        if constexpr (decltype(all)::value) {
+                            gII[p] = __builtin_amdgcn_mfma_f64_16x16x4f64(a0[p][q], a0[p][q], gII[p], 0, 0, 0);
+                            gJJ[p] = __builtin_amdgcn_mfma_f64_16x16x4f64(a1[p][q], a1[p][q], gJJ[p], 0, 0, 0);
+                        }
+                    }
+            }
+        };
+        if (inside) gram(std::true_type{});
+        else gram(std::false_type{});
+        // partial tiles of the eight waves, added in wave order; result element (i, j) of a tile sits in
+        // lane (j, i % 4), register i / 4.  Each pair's by the threads of its half.
+        auto total = [&](const f64x4 (&g)[2]) {
+#pragma unroll
+            for (int p = 0; p < 2; ++p)
+#pragma unroll
+                for (int v = 0; v < 4; ++v) sh.stage[wave][0][256 * p + 4 * lane + v] = g[p][v];
+            __syncthreads();
+            double sum = sh.stage[0][0][tid];
+#pragma unroll
+            for (int w = 1; w < 8; ++w) sum += sh.stage[w][0][tid];
+            return (float)(sum * scale);
+        };
+        const float sIJ = total(gIJ);
+        mine.S[gi][16 + gj] = sIJ;
+        mine.S[16 + gj][gi] = sIJ;
+        if (inside) {
+            __syncthreads();
+            mine.S[gi][gj] = total(gII);
+            __syncthreads();
+            mine.S[16 + gi][16 + gj] = total(gJJ);
+        } else {
+            mine.S[gi][gj] = sh.diag[half ? id[1] : id[0]][17 * gi + gj];
+            mine.S[16 + gi][16 + gj] = sh.diag[half ? id[3] : id[2]][17 * gi + gj];
+        }
+        __syncthreads();
+
+        // ---- the rotations of the two pairs; the waves that work them out sit on two SIMDs
+        rotate_pair(mine, inside, ((wave & 3) - 2 * half - 1) & 3, reinterpret_cast<f64x2*>(sh.stage[wave][0]), floor2,
+                    sh.diag[half ? id[1] : id[0]], sh.diag[half ? id[3] : id[2]]);
+        // (Compared as numbers: with one bit of a scalar tested for several branches the compiler inverted some of them.)
+        const int did[2] = {__builtin_amdgcn_readfirstlane(sh.pair[0].did), __builtin_amdgcn_readfirstlane(sh.pair[1].did)};
+        const int more = did[0] > did[1] ? did[0] : did[1];
+        if (more > touched) touched = more;
+        if (more > seen) seen = more;
+
+        // ---- P <- P Q as (Q^T P^T): A operand = Q^T tile, B operand = the columns in registers.  The last time (not of a core that is
+        // here for all sweeps) a chunk leaves as soon as it is done.
+        const bool leave = inner == 2 && !whole && touched > 0;
+#pragma unroll
+        for (int p = 0; p < 2; ++p) {
+            if (did[p] == 0 && !(p == 1 && leave)) continue;
+            double qa[2][8];
+#pragma unroll
+            for (int ct = 0; ct < 2; ++ct)
+#pragma unroll
+                for (int s = 0; s < 8; ++s) qa[ct][s] = sh.pair[p].Q[kq + 4 * s][16 * ct + n];
+#pragma unroll
+            for (int t = 0; t < NT; ++t) {
+                if (t % 2 == 0 && 32 * (wave + 4 * t) >= K) break;        // no rows of this core
+                if (did[p] != 0) {
+                    f64x4 acc0 = {0.0, 0.0, 0.0, 0.0}, acc1 = acc0;
+#pragma unroll
+                    for (int s = 0; s < 8; ++s) {
+                        const double d = s < 4 ? D[t][4 * p + s] : D[t][8 + 4 * p + s - 4];
+                        acc0 = __builtin_amdgcn_mfma_f64_16x16x4f64(qa[0][s], d, acc0, 0, 0, 0);
+                        acc1 = __builtin_amdgcn_mfma_f64_16x16x4f64(qa[1][s], d, acc1, 0, 0, 0);
+                    }
+#pragma unroll
+                    for (int v = 0; v < 4; ++v) { D[t][4 * p + v] = acc0[v]; D[t][8 + 4 * p + v] = acc1[v]; }
+                }
+                if (p == 1 && t % 2 == 1 && leave) store_chunk(t / 2, n, kq);
+            }
+        }
+        if (inner == 0) exchange(One{}, Two{});
+        else exchange(Two{}, Three{});                    // the second time back to a, b, c, d
+    }
+    if (tid == 0 && seen == 2) gstore(rotated + sweep, 1);
+    if (!whole || seen != 2 || sweep + 1 >= max_sweeps) break;
+    seen = 0;
+    exchange(One{}, Two{});
     }
 
-    // ---- P <- P Q as (Q^T P^T): A operand = Q^T tile, B operand = the panel registers
+    if (!whole) {                                        // (a, b, c, d again; scaled by a power of two)
+        const double unscale = 1.0 / scale;
+        gstore(diag + (half ? blk[1] : blk[0]) * 256 + 16 * gi + gj, (double)sh.diag[half][17 * gi + gj] * unscale);
+        if (dJ >= 0) gstore(diag + (half ? blk[3] : blk[2]) * 256 + 16 * gi + gj, (double)sh.diag[2 + half][17 * gi + gj] * unscale);
+    }
+    if (whole && touched > 0) {
+#pragma unroll
+        for (int tt = 0; tt < NT / 2; ++tt)
+            if (32 * (wave + 8 * tt) < K) store_chunk(tt, n, kq);
+    }
+}
+
+// Two blocks per work-group, four waves of up to NT row tiles, K <= 64 NT.  Work-groups per compute unit: as many as the registers allow (K = 768: two
+// 12.7 ms, one 13.5 over 16 decompositions; four blocks, one work-group per compute unit and some registers in memory, 15.0).
+template <int NT>
+__global__ __launch_bounds__(256, (NT <= 2 ? 4 : NT <= 6 ? 3 : 2))
+void jacobi_pair_kernel(double* cores, int* rotated, int K, int sweep, int round, const LayerDev* __restrict__ layers, const int2* __restrict__ wg_map) {
+    __shared__ struct __align__(16) { double stage[4][16 * 32]; PairShared pair; float diag[2][16 * 17]; } sh;
+    const Core c = find_core(cores, rotated, K, layers, wg_map);
+    if (sweep > 0 && c.rotated[sweep - 1] == 0) return;   // the previous sweep found no significant pair: the iteration has converged
+    K = c.K;
+    const int nb = K >> 4;
+    if (round >= nb - 1 || K > 64 * NT) return;
+    // circle method: slot 0 pairs block nb - 1 with `round`; slot j pairs (round + j) with (round - j)
+    int bI = round + c.slot, bJ = round - c.slot;
+    if (c.slot == 0) bI = nb - 1;
+    else { if (bI >= nb - 1) bI -= nb - 1; if (bJ < 0) bJ += nb - 1; }
+    const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, n = lane & 15, kq = lane >> 4;
+    const int gi = wave + 4 * (tid & 3), gj = (tid >> 2) & 15;            // this thread's element of a 16 x 16 tile
+    const bool inside = round == 0;
+    double* const diagI = c.diag + bI * 256;
+    double* const diagJ = c.diag + bJ * 256;
+    const double keptI = inside ? 0.0 : gload(diagI + 16 * gi + gj), keptJ = inside ? 0.0 : gload(diagJ + 16 * gi + gj);
+    const double frob = frob2(c.trace);
+    // columns 4 s + kq of block I in D[t][s], of block J in D[t][4 + s]
+    double D[NT][8];
+#pragma unroll
+    for (int tt = 0; tt < NT / 2; ++tt) {
+        if (32 * (wave + 4 * tt) < K) {
+            const int row0 = 32 * (wave + 4 * tt) + 2 * n;
+#pragma unroll
+            for (int s = 0; s < 8; ++s) {
+                const int col = 16 * (s < 4 ? bI : bJ) + kq + 4 * (s & 3);
+                const f64x2 v = gload(reinterpret_cast<const f64x2*>(c.Ct + (int64_t)col * K + row0));
+                D[2 * tt][s] = v[0];
+                D[2 * tt + 1][s] = v[1];
+            }
+        } else {
+#pragma unroll
+            for (int s = 0; s < 8; ++s) D[2 * tt][s] = D[2 * tt + 1][s] = 0.0;
+        }
+    }
+    const double scale = ldexp(1.0, -__builtin_amdgcn_frexp_exp(frob));
+    const float floor2 = (float)(kZeroColumn2 * frob * scale);
+    double* const stage = sh.stage[wave];
+    f64x4 g[3] = {};                                      // IJ, II, JJ
+    auto gram = [&](auto all) {
+#pragma unroll
+        for (int t = 0; t < NT; ++t) {
+            if (t % 2 == 0 && 32 * (wave + 2 * t) >= K) break;
+#pragma unroll
+            for (int s = 0; s < 8; ++s) stage[stage_addr(n, kq + 4 * s)] = D[t][s];
+            wave_lds_fence();
+            double a0[4], a1[4];
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                a0[q] = stage[stage_addr(4 * q + kq, n)];
+                a1[q] = stage[stage_addr(4 * q + kq, 16 + n)];
+            }
+            wave_lds_fence();
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                g[0] = __builtin_amdgcn_mfma_f64_16x16x4f64(a0[q], a1[q], g[0], 0, 0, 0);
+                if constexpr (decltype(all)::value) {
+                    g[1] = __builtin_amdgcn_mfma_f64_16x16x4f64(a0[q], a0[q], g[1], 0, 0, 0);
+                    g[2] = __builtin_amdgcn_mfma_f64_16x16x4f64(a1[q], a1[q], g[2], 0, 0, 0);
+                }
+            }
+        }
+    };
+    if (inside) gram(std::true_type{});
+    else gram(std::false_type{});
+    // partial tiles of the four waves, added in wave order (see jacobi_quad_kernel)
+    auto total = [&](const f64x4& part) {
+#pragma unroll
+        for (int v = 0; v < 4; ++v) stage[4 * lane + v] = part[v];
+        __syncthreads();
+        return (float)((((sh.stage[0][tid] + sh.stage[1][tid]) + sh.stage[2][tid]) + sh.stage[3][tid]) * scale);
+    };
+    const float sIJ = total(g[0]);
+    sh.pair.S[gi][16 + gj] = sIJ;
+    sh.pair.S[16 + gj][gi] = sIJ;
+    if (inside) {
+        __syncthreads();
+        sh.pair.S[gi][gj] = total(g[1]);
+        __syncthreads();
+        sh.pair.S[16 + gi][16 + gj] = total(g[2]);
+    } else {
+        sh.pair.S[gi][gj] = (float)(keptI * scale);
+        sh.pair.S[16 + gi][16 + gj] = (float)(keptJ * scale);
+    }
+    __syncthreads();
+    rotate_pair(sh.pair, inside, (wave - (int)((blockIdx.x + blockIdx.y) & 3) - 1) & 3, reinterpret_cast<f64x2*>(stage), floor2, sh.diag[0], sh.diag[1]);
+    {
+    const int tid = thread_anew(), lane = tid & 63, n = lane & 15, kq = lane >> 4;
+    const int gi = wave + 4 * (tid & 3), gj = (tid >> 2) & 15;
+    const int did = __builtin_amdgcn_readfirstlane(sh.pair.did);
+    const double unscale = 1.0 / scale;
+    gstore(diagI + 16 * gi + gj, (double)sh.diag[0][17 * gi + gj] * unscale);
+    gstore(diagJ + 16 * gi + gj, (double)sh.diag[1][17 * gi + gj] * unscale);
+    if (did == 0) return;                                 // the columns are what they were
+    if (tid == 0 && did == 2) gstore(c.rotated + sweep, 1);
+
+    // ---- P <- P Q as (Q^T P^T); a chunk leaves as soon as it is done
     double qa[2][8];
 #pragma unroll
     for (int ct = 0; ct < 2; ++ct)
 #pragma unroll
-        for (int s = 0; s < 8; ++s) qa[ct][s] = sh.Q[kq + 4 * s][16 * ct + n];
+        for (int s = 0; s < 8; ++s) qa[ct][s] = sh.pair.Q[kq + 4 * s][16 * ct + n];
 #pragma unroll
     for (int t = 0; t < NT; ++t) {
+        if (t % 2 == 0 && 32 * (wave + 2 * t) >= K) break;
         f64x4 acc0 = {0.0, 0.0, 0.0, 0.0}, acc1 = acc0;
 #pragma unroll
         for (int s = 0; s < 8; ++s) {
@@ -495,44 +714,125 @@ void jacobi_block_kernel(double* cores, int* rotated, int K, int sweep, int roun
         }
 #pragma unroll
         for (int v = 0; v < 4; ++v) { D[t][v] = acc0[v]; D[t][4 + v] = acc1[v]; }
-    }
-    if (!again || sweep + 1 >= max_sweeps) break;
-    __syncthreads();                                     // Q is read, the next sweep's stages may overwrite
-    }
-
-    // ---- store
-#pragma unroll
-    for (int tt = 0; tt < NT / 2; ++tt) {
-        const int row0 = 32 * (wave + 4 * tt) + 2 * n;
-        if (row0 < K) {
+        if (t % 2 == 1) {
+            const int row0 = 32 * (wave + 2 * (t - 1)) + 2 * n;
 #pragma unroll
             for (int s = 0; s < 8; ++s) {
-                const int col = (s < 4 ? bI * 16 + kq + 4 * s : bJ * 16 + kq + 4 * (s - 4));
-                gstore(reinterpret_cast<f64x2*>(Ct + (int64_t)col * K + row0), f64x2{D[2 * tt][s], D[2 * tt + 1][s]});
+                const int col = 16 * (s < 4 ? bI : bJ) + kq + 4 * (s & 3);
+                gstore(reinterpret_cast<f64x2*>(c.Ct + (int64_t)col * K + row0), f64x2{D[t - 1][s], D[t][s]});
             }
         }
+    }
+    }
+}
+
+// Cores of 32: two blocks, one pair.  The work-group (four waves, of which the first has all rows) holds the whole core and runs all
+// sweeps in one launch, the columns in registers throughout.  A launch and a poll of the convergence flags per
+// sweep took 129 us for one core of 32, this 54 with the rotations in fp64, 33 in fp32.
+__global__ __launch_bounds__(256, 1)
+void jacobi_single_pair_kernel(double* cores, int* rotated, int max_sweeps) {
+    __shared__ struct __align__(16) { double stage[4][16 * 32]; PairShared pair; } sh;
+    constexpr int K = 32;
+    double* const Ct = cores + (int64_t)blockIdx.x * core_doubles(K);
+    rotated += (int)blockIdx.x * (kMaxSweepsCap + 1);
+    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, n = lane & 15, kq = lane >> 4;
+    const int gi = (tid >> 6) + 4 * (tid & 3), gj = (tid >> 2) & 15;      // this thread's element of a 16 x 16 tile
+    const double frob = frob2(Ct + core_trace(K));
+    // D[t][s] = C[2 n + t][kq + 4 s], in the first wave
+    double D[2][8];
+#pragma unroll
+    for (int s = 0; s < 8; ++s) {
+        const f64x2 v = gload(reinterpret_cast<const f64x2*>(Ct + (kq + 4 * s) * K + 2 * n));
+        D[0][s] = v[0];
+        D[1][s] = v[1];
+    }
+    const double scale = ldexp(1.0, -__builtin_amdgcn_frexp_exp(frob));
+    const float floor2 = (float)(kZeroColumn2 * frob * scale);
+    for (int sweep = 0;; ++sweep) {
+        const int lane = thread_anew() & 63, n = lane & 15, kq = lane >> 4;
+        if (wave == 0) {
+            f64x4 g[3] = {};
+#pragma unroll
+            for (int t = 0; t < 2; ++t) {
+#pragma unroll
+                for (int s = 0; s < 8; ++s) sh.stage[t][stage_addr(n, kq + 4 * s)] = D[t][s];
+            }
+            wave_lds_fence();
+#pragma unroll
+            for (int t = 0; t < 2; ++t)
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    const double a0 = sh.stage[t][stage_addr(4 * q + kq, n)], a1 = sh.stage[t][stage_addr(4 * q + kq, 16 + n)];
+                    g[0] = __builtin_amdgcn_mfma_f64_16x16x4f64(a0, a0, g[0], 0, 0, 0);
+                    g[1] = __builtin_amdgcn_mfma_f64_16x16x4f64(a0, a1, g[1], 0, 0, 0);
+                    g[2] = __builtin_amdgcn_mfma_f64_16x16x4f64(a1, a1, g[2], 0, 0, 0);
+                }
+            // result element (i, j) of a tile sits in lane (j, i % 4), register i / 4
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                const int i = kq + 4 * v, j = n;
+                sh.pair.S[i][j] = (float)(g[0][v] * scale);
+                const float cross = (float)(g[1][v] * scale);
+                sh.pair.S[i][16 + j] = cross;
+                sh.pair.S[16 + j][i] = cross;
+                sh.pair.S[16 + i][16 + j] = (float)(g[2][v] * scale);
+            }
+        }
+        __syncthreads();
+        rotate_pair(sh.pair, true, (wave - 1) & 3, reinterpret_cast<f64x2*>(sh.stage[wave]), floor2, nullptr, nullptr);
+        const int did = __builtin_amdgcn_readfirstlane(sh.pair.did);
+        if (did == 0) break;
+        if (wave == 0) {
+            double qa[2][8];
+#pragma unroll
+            for (int ct = 0; ct < 2; ++ct)
+#pragma unroll
+                for (int s = 0; s < 8; ++s) qa[ct][s] = sh.pair.Q[kq + 4 * s][16 * ct + n];
+#pragma unroll
+            for (int t = 0; t < 2; ++t) {
+                f64x4 acc0 = {0.0, 0.0, 0.0, 0.0}, acc1 = acc0;
+#pragma unroll
+                for (int s = 0; s < 8; ++s) {
+                    acc0 = __builtin_amdgcn_mfma_f64_16x16x4f64(qa[0][s], D[t][s], acc0, 0, 0, 0);
+                    acc1 = __builtin_amdgcn_mfma_f64_16x16x4f64(qa[1][s], D[t][s], acc1, 0, 0, 0);
+                }
+#pragma unroll
+                for (int v = 0; v < 4; ++v) { D[t][v] = acc0[v]; D[t][4 + v] = acc1[v]; }
+            }
+        }
+        if (tid == 0 && did == 2) gstore(rotated + sweep, 1);
+        if (did != 2 || sweep + 1 >= max_sweeps) break;
+        __syncthreads();                                 // Q is read, the next sweep's tiles may overwrite
+    }
+    if (wave == 0) {
+#pragma unroll
+        for (int s = 0; s < 8; ++s) gstore(reinterpret_cast<f64x2*>(Ct + (kq + 4 * s) * K + 2 * n), f64x2{D[0][s], D[1][s]});
     }
 }
 
 }  // namespace
 
-hipError_t launch_jacobi_block_round(const LayerDev* layers, const int2* wg_map, int n_wg, int K_max,
-                                     int sweep, int round, double* cores, int* rotated, hipStream_t s) {
+hipError_t launch_jacobi_block_round(const LayerDev* layers, const int2* wg_map, int n_wg, int K_max, bool quad,
+                                     int sweep, int round, int max_sweeps, double* cores, int* rotated, hipStream_t s) {
     if (n_wg <= 0) return hipSuccess;
-    const int slots = K_max / 32;
-    const dim3 grid(cores ? slots : n_wg, cores ? n_wg / slots : 1), block(256);
-    if (K_max <= 128) hipLaunchKernelGGL((jacobi_block_kernel<2, false>), grid, block, 0, s, cores, rotated, K_max, sweep, round, layers, wg_map);
-    else if (K_max <= 256) hipLaunchKernelGGL((jacobi_block_kernel<4, false>), grid, block, 0, s, cores, rotated, K_max, sweep, round, layers, wg_map);
-    else if (K_max <= 384) hipLaunchKernelGGL((jacobi_block_kernel<6, false>), grid, block, 0, s, cores, rotated, K_max, sweep, round, layers, wg_map);
-    else if (K_max <= 512) hipLaunchKernelGGL((jacobi_block_kernel<8, false>), grid, block, 0, s, cores, rotated, K_max, sweep, round, layers, wg_map);
-    else if (K_max <= 768) hipLaunchKernelGGL((jacobi_block_kernel<12, false>), grid, block, 0, s, cores, rotated, K_max, sweep, round, layers, wg_map);
-    else return hipErrorInvalidValue;
+    if (K_max > (quad ? 512 : 768)) return hipErrorInvalidValue;
+    const int slots = jacobi_slots(K_max, quad);
+    const dim3 grid(cores ? slots : n_wg, cores ? n_wg / slots : 1), block(quad ? 512 : 256);
+    if (quad) {
+        if (K_max <= 256) hipLaunchKernelGGL((jacobi_quad_kernel<2>), grid, block, 0, s, cores, rotated, K_max, sweep, round, max_sweeps, layers, wg_map);
+        else hipLaunchKernelGGL((jacobi_quad_kernel<4>), grid, block, 0, s, cores, rotated, K_max, sweep, round, max_sweeps, layers, wg_map);
+    }
+    else if (K_max <= 128) hipLaunchKernelGGL((jacobi_pair_kernel<2>), grid, block, 0, s, cores, rotated, K_max, sweep, round, layers, wg_map);
+    else if (K_max <= 256) hipLaunchKernelGGL((jacobi_pair_kernel<4>), grid, block, 0, s, cores, rotated, K_max, sweep, round, layers, wg_map);
+    else if (K_max <= 384) hipLaunchKernelGGL((jacobi_pair_kernel<6>), grid, block, 0, s, cores, rotated, K_max, sweep, round, layers, wg_map);
+    else if (K_max <= 512) hipLaunchKernelGGL((jacobi_pair_kernel<8>), grid, block, 0, s, cores, rotated, K_max, sweep, round, layers, wg_map);
+    else hipLaunchKernelGGL((jacobi_pair_kernel<12>), grid, block, 0, s, cores, rotated, K_max, sweep, round, layers, wg_map);
     return hipGetLastError();
 }
 
 hipError_t launch_jacobi_single_pair(double* cores, int* rotated, int n, int max_sweeps, hipStream_t s) {
     if (n <= 0) return hipSuccess;
-    hipLaunchKernelGGL((jacobi_block_kernel<2, true>), dim3(1, n), dim3(256), 0, s, cores, rotated, 32, 0, max_sweeps, (const LayerDev*)nullptr, (const int2*)nullptr);
+    hipLaunchKernelGGL(jacobi_single_pair_kernel, dim3(n), dim3(256), 0, s, cores, rotated, max_sweeps);
     return hipGetLastError();
 }
 

@@ -83,6 +83,39 @@ def test_block_iteration_at_the_edges_of_its_forms(K, zero_tail):
     assert float((got - want).norm() / want.norm()) < 4e-6
 
 
+# batches that take four blocks of columns a work-group: one pair of double blocks (all sweeps in one launch), two, sizes up to the limit, and
+# sizes mixed, where the work-groups look their layer up in the tables
+@pytest.mark.parametrize("zero_tail", [0, 20])
+@pytest.mark.parametrize("sizes", [(64,), (64, 64, 64), (128,) * 4, (192,) * 32, (320,) * 20, (384,) * 16, (512,) * 12, (512, 64, 128, 448) * 6])
+def test_four_blocks_a_work_group(sizes, zero_tail):
+    made = {}
+    for i, K in enumerate(sizes):                        # two different layers of every size
+        key = (K, i // len(set(sizes)) % 2)
+        if key not in made:
+            g = torch.Generator().manual_seed(K + zero_tail + key[1])
+            scale = torch.logspace(0, -2, K, dtype=torch.float64)
+            scale[K - zero_tail:] = 0.0
+            A = (torch.randn((K + 24, K), generator=g, dtype=torch.float64) * scale).float()
+            B = torch.randn((K, K + 12), generator=g, dtype=torch.float64).float()
+            B[K - zero_tail:] = 0.0
+            made[key] = (A.to("cuda:0"), B.to("cuda:0"), (K - zero_tail) // 2)
+    keys = [(K, i // len(set(sizes)) % 2) for i, K in enumerate(sizes)]
+    outs = abt.ab_merge_batched([{"A_copies": [made[k][0]], "B_copies": [made[k][1]], "tau": 0.0, "k_fixed": made[k][2]} for k in keys])
+    first = {}
+    for k, out in zip(keys, outs):
+        if k in first:                                   # the same layer again: the same bits
+            assert all(torch.equal(out[x], first[k][x]) for x in ("A", "B", "S"))
+            continue
+        first[k] = out
+        A, B, keep = made[k]
+        U, s, V = torch.linalg.svd((A.cpu().double() @ B.cpu().double()), full_matrices=False)
+        # (bounds as above)
+        assert float(((out["S"].cpu().double()[:keep] - s[:keep]).abs() / s[:keep]).max()) < 3e-7
+        want = (U[:, :keep] * s[:keep]) @ V[:keep]
+        got = out["A"].cpu().double()[:, :keep] @ out["B"].cpu().double()[:keep]
+        assert float((got - want).norm() / want.norm()) < 4e-6
+
+
 # shapes around the 64 contraction indices of a step and the 16 work-groups of a side, rows that are not multiples of four, one to five copies, more
 # columns than the core has and fewer
 @pytest.mark.parametrize("m,n,G,k_cap,k_fixed", [(33, 32, 1, 32, 0), (64, 65, 2, 32, 0), (1024, 1025, 3, 20, 0), (1088, 2047, 5, 40, 7), (3072, 130, 4, 32, 32)])
