@@ -13,7 +13,7 @@
 // 8 x 8 blocks in registers (byte permutes) on the way, so the MFMA waves read their operands
 // with plain 16-byte LDS loads.  (Reading row-major slabs with the transposing LDS load
 // ds_read_b64_tr_b16 instead was limited by the rate of those 8-byte reads.)
-#include "common.h"
+#include "tn_args.h"
 
 namespace abt {
 
@@ -30,7 +30,7 @@ constexpr int BKM = 64;      // batch rows per slab
 constexpr int NMW = 4;       // MFMA waves
 
 // Two work-groups per compute unit for a gathered operand at narrow ranks: a loader wave there spends a slab on
-// range checks and transposition with nobody to take its place, and a second work-group on half the ring does
+// range checks and transposition with nobody to take its place, and a second work-group on half the ring does (windows three wide up to r = 96 have lr_taps.hip since)
 // (factor gradients of 256 x 14 x 14, batch 256, r = 64: 59 -> 42 us; 128 x 28 x 28, stride 2: 46 -> 33).  A
 // matrix operand streams at memory rate with one.
 constexpr bool tn2_two(int R, bool gather) { return gather && R <= 128; }
@@ -57,15 +57,6 @@ struct Tn2 {
     static constexpr int WPS = tn2_two(R, GATHER) ? 4 : 1;
     static_assert(lds_bytes <= 160 * 1024, "slab shape");
 };
-
-struct Tn2Job { const uint16_t* U; const uint16_t* V; float* part; int P; int tile_begin; int transposed; int gather; };
-// Gather form of U (jobs with gather != 0): U is a channels-last image [M / (H W), H, W, C] and column
-// tap C + c of row i of the virtual U is channel c of pixel (y + ky - kh/2, x + kx - kw/2) of the
-// same image (tap = ky kw + kx), zero outside it.  job.P = kh kw C.
-// Rows are the pixels of a grid RH x RW per image; row (y, x) is centred on image pixel (mul y, mul x)
-// (mul = 1 with RH x RW = H x W: every pixel; mul = 2: the patches of a stride-2 convolution).
-struct Tn2Gather { int H, W, C, kh, kw, RH, RW, mul; };
-struct Tn2Args { Tn2Job job[kTnMaxJobs]; int njobs; int tiles; int splits; int64_t M; int64_t rows_per_split; Tn2Gather g; };
 
 // LDS slab: column-major, 64 batch rows = 128 bytes per column, two columns per 256-byte line.  The
 // sixteen 16-byte units of a line are XOR-swizzled with bits of the column-pair index p so that
@@ -507,10 +498,16 @@ bool tn2_result_over_operand(const TnJob* jobs, int njobs, int64_t M, int R, con
 }
 
 hipError_t launch_tn_common(const TnJob* jobs, int njobs, int64_t M, int R, int accumulate,
-                            float* partials, const Tn2Gather* gather, hipStream_t s) {
+                            float* partials, const Tn2Gather* gather, hipStream_t s, int taps = 0) {   // taps: splits for lr_taps.hip
+
     if (njobs < 1 || njobs > kTnMaxJobs || (gather && njobs > 2)) return hipErrorInvalidValue;
-    const int tiles = tn2_total_tiles(jobs, njobs);
-    const int splits = tn2_choose_splits(M, tiles, tn2_two(R, gather != nullptr) ? 2 : 1);
+    int tiles = tn2_total_tiles(jobs, njobs);
+    int splits = tn2_choose_splits(M, tiles, tn2_two(R, gather != nullptr) ? 2 : 1);
+    if (taps) {
+        splits = taps;
+        tiles = 0;
+        for (int i = 0; i < njobs; ++i) tiles += taps_tiles(jobs[i], i == njobs - 1 ? gather : nullptr);
+    }
     Tn2Args args{};
     Red2Args red{};
     args.njobs = red.njobs = njobs;
@@ -520,7 +517,8 @@ hipError_t launch_tn_common(const TnJob* jobs, int njobs, int64_t M, int R, int 
     args.M = M;
     if (gather) args.g = *gather;
     int64_t rps = ceil_div(M, splits);
-    rps = ceil_div(rps, 64) * 64;
+    const int slab = taps ? taps_rows(R) : 64;
+    rps = ceil_div(rps, slab) * slab;
     args.rows_per_split = rps;
     red.splits = splits; red.accumulate = accumulate;
     float* part = partials;
@@ -536,13 +534,14 @@ hipError_t launch_tn_common(const TnJob* jobs, int njobs, int64_t M, int R, int 
         red.job[i].part = part;
         red.job[i].out = jobs[i].out;
         red.job[i].total = (int64_t)jobs[i].P * R;
-        tile_begin += (jobs[i].P + TP - 1) / TP;
+        tile_begin += taps ? taps_tiles(jobs[i], args.job[i].gather ? gather : nullptr) : (jobs[i].P + TP - 1) / TP;
         red.job[i].block_begin = red_blocks;
         red_blocks += (int)ceil_div((int64_t)jobs[i].P * R / 4, splits < kRedSplit ? 256 : 64);
         part += (size_t)jobs[i].P * R * splits;
     }
     hipError_t e;
-    switch (R) {
+    if (taps) e = launch_taps(args, R, s);
+    else switch (R) {
 #define ABT_CASE(RR) case RR: e = gather ? launch_tn2_r<RR, true>(args, tiles, splits, s) \
                                          : launch_tn2_r<RR, false>(args, tiles, splits, s); break;
         ABT_CASE(32) ABT_CASE(64) ABT_CASE(96) ABT_CASE(128) ABT_CASE(160) ABT_CASE(192)
@@ -597,7 +596,9 @@ hipError_t launch_tn_gather_bf16(const TnJob* jobs, int njobs, const PatchGeom& 
         if ((span + 2 * reach) * g.Cin * 2 >= kBufMaxBytes) return hipErrorInvalidValue;
     }
     const Tn2Gather tg{g.H, g.W, g.Cin, g.kh, g.kw, g.RH, g.RW, g.mul};
-    return launch_tn_common(jobs, njobs, M, R, accumulate, partials, &tg, s);
+    // (no more splits than the workspace is laid out for)
+    const int room = tn2_choose_splits(M, tn2_total_tiles(jobs, njobs), tn2_two(R, true) ? 2 : 1), own = taps_splits(jobs, njobs, tg, M, R), taps = own < room ? own : room;
+    return launch_tn_common(jobs, njobs, M, R, accumulate, partials, &tg, s, taps_supports(jobs, njobs, tg, M, R, taps) ? taps : 0);
 }
 
 }  // namespace abt
