@@ -15,7 +15,8 @@
 // Measured: 4096 x 4096 x 1024 279 us = 123 TFLOP/s of the 133 that a large library product reaches;
 // 768 x 3072 x 384 (W = A B of a ViT-B/16 MLP layer) 26 us, 79 us in an earlier form with 128 x 128 tiles
 // and 4-byte loads one slab ahead; the products of a factored layer at M = 3152, m = 3072, n = 768,
-// r = 192: T 15 us, Y 52, dT 47 and 4, and dX, dA and dB in one launch 64 and 7; forward and backward together 171 us.
+// r = 192: T 15 us, Y 52, dT 47 and 4, and dX, dA and dB in one launch 64 and 7; forward and backward together 171 us, 164 with work-groups
+// that stay (gemm_stream).
 //
 // LDS: both operands lie [row][k], 16-byte chunks of four k XOR-swizzled by the row; an operand read is
 // one 16-byte read for four matrix instructions: instruction i of a group of eight k takes k = 4 h + i
@@ -324,6 +325,170 @@ __global__ __launch_bounds__(NT, 3) void gemm_f32_kernel(const GemmF32Dev* __res
     }
 }
 
+// The same tiles by work-groups that stay: each takes tiles first, first + stride, .. below `share` of a problem, and the slabs of all of them are one
+// stream, so a tile's first loads are on their way while the one before is multiplied out, and its values leave meanwhile.  Whole slabs
+// and 16-byte loads only.  Short contractions gain: 3152 x 3072 x 192 46.0 -> 39.6 us, the forward at M = 3152, m = 3072, n = 768, r = 192 72 -> 65,
+// 3072 x 768 x 384 27.2 -> 25.7, 4096 x 4096 x 1024 310 -> 306; gradients, whose contractions are long, are equal.  (Two to a compute unit: 42, 69, 26.8, 324.)
+template <class C, bool KCA, bool KCB>
+__device__ __forceinline__ void gemm_stream(const GemmF32Dev& g, int origin, int first, int share, int stride, float* lds) {
+    const GemmF32& d = g.d;
+    struct Tile { int split, i0, j0, k0, kend; };
+    auto tile_at = [&](int at) {
+        int local = origin + at;
+        Tile t;
+        t.split = local / g.tiles;
+        local -= t.split * g.tiles;
+        t.i0 = (local / g.tiles_q) * C::TM;
+        t.j0 = (local % g.tiles_q) * C::TN;
+        t.k0 = t.split * g.k_split;
+        t.kend = t.k0 + g.k_split < d.K ? t.k0 + g.k_split : d.K;
+        return t;
+    };
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int wi = (wave / C::WC) * (32 * C::RA), wj = (wave % C::WC) * (32 * C::CB);
+    const int li = lane & 31, lh = lane >> 5;
+    f32x16 acc[C::RA][C::CB];
+    auto clear = [&] {
+#pragma unroll
+        for (int a = 0; a < C::RA; ++a)
+#pragma unroll
+            for (int b = 0; b < C::CB; ++b)
+#pragma unroll
+                for (int v = 0; v < 16; ++v) acc[a][b][v] = 0.0f;
+    };
+    clear();
+
+    // the loaders run ahead through the tiles; past the last one they read the last slab's neighbours of the first rows again
+    Loader<C::TM, C::BK, true, KCA> la;
+    Loader<C::TN, C::BK, true, KCB> lb;
+    int next = first, left = 0;                            // slabs of the loaders' tile that are still to be asked for
+    auto turn = [&] {
+        if (left > 0) return;
+        if (next < share) {
+            const Tile t = tile_at(next);
+            la.init(d.A, d.lda, t.i0, d.P, t.k0, t.kend, d.K);
+            lb.init(d.B, d.ldb, t.j0, d.Q, t.k0, t.kend, d.K);
+            left = (t.kend - t.k0) / C::BK;
+            next += stride;
+        } else {
+#pragma unroll
+            for (int e = 0; e < C::NVA; ++e) la.ptr[e] = d.A;
+#pragma unroll
+            for (int e = 0; e < C::NVB; ++e) lb.ptr[e] = d.B;
+            la.step = lb.step = 0;
+            left = 1 << 30;
+        }
+    };
+    f32x4 ra[2][C::NVA], rb[2][C::NVB];
+    constexpr int NPIECE = 2 * (C::NVA + C::NVB);
+    auto piece = [&](int i, int buffer, int r) {
+        float* buf = lds + buffer * C::slab;
+        if (i < C::NVA) la.template store<true>(ra[r][i], i, buf, 0);
+        else if (i < C::NVA + C::NVB) lb.template store<true>(rb[r][i - C::NVA], i - C::NVA, buf + C::TM * C::BK, 0);
+        else if (i < 2 * C::NVA + C::NVB) la.template load<true>(ra[r][i - C::NVA - C::NVB], i - C::NVA - C::NVB, 0);
+        else lb.template load<true>(rb[r][i - 2 * C::NVA - C::NVB], i - 2 * C::NVA - C::NVB, 0);
+    };
+    struct Ops { f32x4 a[C::RA], b[C::CB]; } ops[2];
+    auto read = [&](Ops& o, int buffer, int gq) {
+        const float* As = lds + buffer * C::slab;
+        const float* Bs = As + C::TM * C::BK;
+        const int c = 2 * gq + lh;
+#pragma unroll
+        for (int x = 0; x < C::RA; ++x) o.a[x] = *reinterpret_cast<const f32x4*>(As + lds_at<C::BK>(wi + 32 * x + li, c));
+#pragma unroll
+        for (int x = 0; x < C::CB; ++x) o.b[x] = *reinterpret_cast<const f32x4*>(Bs + lds_at<C::BK>(wj + 32 * x + li, c));
+    };
+    auto request = [&](int r) {
+        turn();
+#pragma unroll
+        for (int i = NPIECE / 2; i < NPIECE; ++i) piece(i, 0, r);
+        --left;
+    };
+    gemm_barrier();                                        // (the problem before has left the LDS)
+    request(0);
+    request(1);
+#pragma unroll
+    for (int i = 0; i < NPIECE / 2; ++i) piece(i, 0, 0);
+    request(0);
+    gemm_barrier();
+
+    Tile cur = tile_at(first);
+    int at = first, slabs = (cur.kend - cur.k0) / C::BK;
+    while (at < share) {
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+            if (at >= share) break;
+            turn();
+            read(ops[0], u, 0);
+#pragma unroll
+            for (int gq = 0; gq < C::GPW; ++gq) {
+                if (gq + 1 < C::GPW) read(ops[(gq + 1) & 1], u, gq + 1);
+                __builtin_amdgcn_sched_barrier(0);
+                const Ops& o = ops[gq & 1];
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+#pragma unroll
+                    for (int x = 0; x < C::RA; ++x)
+#pragma unroll
+                        for (int y = 0; y < C::CB; ++y) acc[x][y] = __builtin_amdgcn_mfma_f32_32x32x2f32(o.a[x][i], o.b[y][i], acc[x][y], 0, 0, 0);
+                    constexpr int NSLOT = 4 * C::GPW;
+                    const int slot = gq * 4 + i;
+#pragma unroll
+                    for (int q = slot * NPIECE / NSLOT; q < (slot + 1) * NPIECE / NSLOT; ++q) piece(q, u ^ 1, u ^ 1);
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+            }
+            --left;
+            gemm_barrier();
+            if (--slabs > 0) continue;
+            const bool partial = g.splits > 1;
+            float* const out = partial ? g.part + (int64_t)cur.split * d.P * d.Q : d.C;
+            const int ldo = partial ? d.Q : d.ldc;
+#pragma unroll
+            for (int a = 0; a < C::RA; ++a)
+#pragma unroll
+                for (int b = 0; b < C::CB; ++b)
+#pragma unroll
+                    for (int v = 0; v < 16; ++v) {
+                        const int row = cur.i0 + wi + a * 32 + 8 * (v >> 2) + 4 * lh + (v & 3);
+                        const int col = cur.j0 + wj + b * 32 + li;
+                        if (row < d.P && col < d.Q) {
+                            float* c = out + (int64_t)row * ldo + col;
+                            if (partial) { gstore(c, acc[a][b][v]); continue; }
+                            float val = d.alpha * acc[a][b][v];
+                            if (d.accumulate) val += gload(c);
+                            gstore(c, val);
+                        }
+                    }
+            clear();
+            at += stride;
+            if (at < share) { cur = tile_at(at); slabs = (cur.kend - cur.k0) / C::BK; }
+        }
+    }
+}
+
+template <class C>
+__global__ __launch_bounds__(NT, 3) void gemm_f32_stream_kernel(GemmF32Args args, int ndesc) {
+    __shared__ __align__(16) float lds[C::lds_floats];
+    const int slot = (int)(blockIdx.x >> 3), xcd = (int)(blockIdx.x & 7), slots = (int)(gridDim.x >> 3);      // shares as in gemm_f32_kernel
+    int before = 0;
+    for (int i = 0; i < ndesc; ++i) {
+        const GemmF32Dev& g = args.g[i];
+        const int all = g.tiles * g.splits, x = (xcd - g.begin) & 7, over = all & 7;
+        const int share = (all >> 3) + (x < over ? 1 : 0), origin = x * (all >> 3) + (x < over ? x : over);
+        const int first = ((slot - before) % slots + slots) % slots;
+        before += share;
+        if (first >= share) continue;
+        if (g.d.transA) {
+            if (g.d.transB) gemm_stream<C, false, true>(g, origin, first, share, slots, lds);
+            else gemm_stream<C, false, false>(g, origin, first, share, slots, lds);
+        } else {
+            if (g.d.transB) gemm_stream<C, true, true>(g, origin, first, share, slots, lds);
+            else gemm_stream<C, true, false>(g, origin, first, share, slots, lds);
+        }
+    }
+}
+
 // C (+)= alpha * (sum over the splits of the partial sums, in order), for the split problems of a launch
 __global__ __launch_bounds__(NT) void gemm_f32_reduce_kernel(GemmF32Args args, int ndesc) {
     const GemmF32Dev& g = args.g[blockIdx.y];
@@ -441,7 +606,16 @@ hipError_t launch_gemm_f32(const GemmF32* p, const int* splits, int n, float* pa
         tiles += a.g[i].tiles * a.g[i].splits;
     }
     if (tiles <= 0) return hipSuccess;
-    launch_form(small, vec, (tiles + 7) / 8, nullptr, a, n, s);
+    // Whole slabs: work-groups that stay, as many to a compute unit (three or four) as give it the fewest tiles to work through.
+    bool stream = !small && vec;
+    for (int i = 0; i < n; ++i) stream = stream && p[i].limit == nullptr && p[i].K % Wide::BK == 0;
+    if (stream) {
+        const int share = (tiles + 7) / 8, three = (share + 95) / 96 * 3, four = (share + 127) / 128 * 4;
+        const int room = three <= four ? 96 : 128;
+        hipLaunchKernelGGL((gemm_f32_stream_kernel<Wide>), dim3(8 * (share < room ? share : room)), dim3(NT), 0, s, a, n);
+    } else {
+        launch_form(small, vec, (tiles + 7) / 8, nullptr, a, n, s);
+    }
     if (any_split && largest > 0) {
         const int64_t blocks = ceil_div(largest, NT);
         hipLaunchKernelGGL(gemm_f32_reduce_kernel, dim3((unsigned)(blocks < 2048 ? blocks : 2048), n), dim3(NT), 0, s, a, n);

@@ -176,3 +176,31 @@ def test_static_scratch_gives_the_same_dX():
     dX, out = abt.lr_linear_bwd(dY, X, None, A, B)[0], torch.empty_like(X)
     abt.lr_linear_bwd_static(dY, X, None, A, B, dX=out)
     assert torch.equal(out, dX)
+
+
+# one tile per work-group and several: tiles on both sides of three and of four work-groups per compute unit, one slab to many, ragged edges
+@pytest.mark.parametrize("m,n,k", [(1664, 1664, 32), (1700, 1820, 64), (2048, 2048, 96), (2049, 2052, 32), (3150, 3068, 192), (64 * 257, 64, 160), (4100, 4, 320)])
+def test_work_groups_that_stay(m, n, k):
+    g = torch.Generator().manual_seed(m + k)
+    A, B = torch.randn((m, k), generator=g).to("cuda:0"), torch.randn((k, n), generator=g).to("cuda:0")
+    W = abt.ab_reconstruct(A, B)
+    want = A.double() @ B.double()
+    # k products and their sum in fp32, each rounded once: k 2^-24 of the sum of their magnitudes at most
+    bound = (k + 1) * 2.0 ** -24 * (A.double().abs() @ B.double().abs())
+    assert bool(((W.double() - want).abs() <= bound).all())
+
+
+# three unlike problems in a launch, two of them split, added to what is there
+@pytest.mark.parametrize("M,m,n,r", [(3136, 1024, 512, 192), (2000, 1472, 1984, 64)])
+def test_gradients_by_work_groups_that_stay(M, m, n, r):
+    g = torch.Generator().manual_seed(M + r)
+    make = lambda *s: torch.randn(s, generator=g).to("cuda:0")
+    X, dY, A, B = make(M, n), make(M, m), make(m, r), make(r, n)
+    T = abt.lr_linear_fwd(X, A, B)[1]
+    dA, dB = torch.ones_like(A), torch.ones_like(B)
+    dX, _, _ = abt.lr_linear_bwd(dY, X, T, A, B, dA=dA, dB=dB, accumulate=True)
+    d = lambda t: t.double()
+    dT = d(dY) @ d(A)
+    for got, want in ((dX, dT @ d(B)), (dA - 1, d(dY).T @ d(T)), (dB - 1, dT.T @ d(X))):
+        # sums of up to 3136 products, rounded some sqrt(3136) 2^-24 in the norm, dT once before
+        assert float((d(got) - want).norm() / want.norm()) < 6e-6
