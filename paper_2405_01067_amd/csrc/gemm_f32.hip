@@ -134,6 +134,42 @@ __device__ __forceinline__ void gemm_barrier() {   // keeps the global loads in 
 constexpr int kGemmArgs = 4;         // problems that travel in the kernel arguments
 struct GemmF32Args { GemmF32Dev g[kGemmArgs]; };
 
+// The values of a wave's blocks to the output (or to the split's partial sums): rows from r0, columns from c0 on.  What decides is the same for the
+// whole work-group and looked at once; what is added to is read before anything is written (with a predicate, a branch and, where
+// something is added to, a load and a wait per value, layers of 200 to 1400 rows took 1.05 to 1.16 times as long).
+template <class C>
+__device__ __forceinline__ void put_values(const GemmF32Dev& g, const f32x16 (&acc)[C::RA][C::CB], int split, int r0, int c0, int rows_left, int cols_left) {
+    const GemmF32& d = g.d;
+    const bool partial = g.splits > 1;
+    float* const out = partial ? g.part + (int64_t)split * d.P * d.Q : d.C;
+    const int64_t ldo = partial ? d.Q : d.ldc;
+    const int lane = threadIdx.x & 63, li = lane & 31, lh = lane >> 5;
+    const float alpha = partial ? 1.0f : d.alpha;
+    const bool add = !partial && d.accumulate;
+    const bool inside = rows_left >= 32 * C::RA && cols_left >= 32 * C::CB;      // (of the wave)
+#pragma unroll
+    for (int a = 0; a < C::RA; ++a)
+#pragma unroll
+        for (int b = 0; b < C::CB; ++b) {
+            float* const c = out + (int64_t)(r0 + 32 * a + 4 * lh) * ldo + c0 + 32 * b + li;
+            auto row = [](int v) { return 8 * (v >> 2) + (v & 3); };
+            float old[16];
+            const bool col_in = 32 * b + li < cols_left;
+            if (add) {
+#pragma unroll
+                for (int v = 0; v < 16; ++v) old[v] = inside || (col_in && 32 * a + 4 * lh + row(v) < rows_left) ? gload(c + row(v) * ldo) : 0.0f;
+            }
+            if (inside) {
+#pragma unroll
+                for (int v = 0; v < 16; ++v) gstore(c + row(v) * ldo, add ? alpha * acc[a][b][v] + old[v] : alpha * acc[a][b][v]);
+            } else {
+#pragma unroll
+                for (int v = 0; v < 16; ++v)
+                    if (col_in && 32 * a + 4 * lh + row(v) < rows_left) gstore(c + row(v) * ldo, add ? alpha * acc[a][b][v] + old[v] : alpha * acc[a][b][v]);
+            }
+        }
+}
+
 // The work of one tile; KCA, KCB: k is the fast index of A / B in memory.
 template <class C, bool VEC, bool KCA, bool KCB>
 __device__ __forceinline__ void gemm_tile(const GemmF32Dev& g, int local, float* lds) {
@@ -260,9 +296,10 @@ __device__ __forceinline__ void gemm_tile(const GemmF32Dev& g, int local, float*
         return;
     }
 
-    const bool partial = g.splits > 1;
-    float* const out = partial ? g.part + (int64_t)split * d.P * d.Q : d.C;
-    const int ldo = partial ? d.Q : d.ldc;
+    if (d.limit == nullptr) {
+        put_values<C>(g, acc, split, i0 + wi, j0 + wj, d.P - i0 - wi, d.Q - j0 - wj);
+        return;
+    }
 #pragma unroll
     for (int a = 0; a < C::RA; ++a)
 #pragma unroll
@@ -271,14 +308,8 @@ __device__ __forceinline__ void gemm_tile(const GemmF32Dev& g, int local, float*
             for (int v = 0; v < 16; ++v) {
                 const int row = i0 + wi + a * 32 + 8 * (v >> 2) + 4 * lh + (v & 3);
                 const int col = j0 + wj + b * 32 + li;
-                if (row < d.P && col < d.Q) {
-                    float* c = out + (int64_t)row * ldo + col;
-                    if (partial) { gstore(c, acc[a][b][v]); continue; }
-                    const bool zero = d.limit && (d.limit_rows ? (row >= lim) : (col >= lim));
-                    float val = zero ? 0.0f : d.alpha * acc[a][b][v];
-                    if (d.accumulate && !zero) val += gload(c);
-                    gstore(c, val);
-                }
+                if (row < d.P && col < d.Q)              // (never split, never added to)
+                    gstore(d.C + (int64_t)row * d.ldc + col, (d.limit_rows ? (row >= lim) : (col >= lim)) ? 0.0f : d.alpha * acc[a][b][v]);
             }
 }
 
@@ -327,8 +358,8 @@ __global__ __launch_bounds__(NT, 3) void gemm_f32_kernel(const GemmF32Dev* __res
 
 // The same tiles by work-groups that stay: each takes tiles first, first + stride, .. below `share` of a problem, and the slabs of all of them are one
 // stream, so a tile's first loads are on their way while the one before is multiplied out, and its values leave meanwhile.  Whole slabs
-// and 16-byte loads only.  Short contractions gain: 3152 x 3072 x 192 46.0 -> 39.6 us, the forward at M = 3152, m = 3072, n = 768, r = 192 72 -> 65,
-// 3072 x 768 x 384 27.2 -> 25.7, 4096 x 4096 x 1024 310 -> 306; gradients, whose contractions are long, are equal.  (Two to a compute unit: 42, 69, 26.8, 324.)
+// and 16-byte loads only.  Short contractions gain: 3072 x 3072 x 192 46.0 -> 38.8 us, the forward at M = 3152, m = 3072, n = 768, r = 192 72 -> 64,
+// 3072 x 768 x 384 27.2 -> 25.5; long ones are equal.  (Two to a compute unit: 42, 69, 26.8, and 4096 x 4096 x 1024 324 of 310; four spill.)
 template <class C, bool KCA, bool KCB>
 __device__ __forceinline__ void gemm_stream(const GemmF32Dev& g, int origin, int first, int share, int stride, float* lds) {
     const GemmF32& d = g.d;
@@ -441,25 +472,7 @@ __device__ __forceinline__ void gemm_stream(const GemmF32Dev& g, int origin, int
             --left;
             gemm_barrier();
             if (--slabs > 0) continue;
-            const bool partial = g.splits > 1;
-            float* const out = partial ? g.part + (int64_t)cur.split * d.P * d.Q : d.C;
-            const int ldo = partial ? d.Q : d.ldc;
-#pragma unroll
-            for (int a = 0; a < C::RA; ++a)
-#pragma unroll
-                for (int b = 0; b < C::CB; ++b)
-#pragma unroll
-                    for (int v = 0; v < 16; ++v) {
-                        const int row = cur.i0 + wi + a * 32 + 8 * (v >> 2) + 4 * lh + (v & 3);
-                        const int col = cur.j0 + wj + b * 32 + li;
-                        if (row < d.P && col < d.Q) {
-                            float* c = out + (int64_t)row * ldo + col;
-                            if (partial) { gstore(c, acc[a][b][v]); continue; }
-                            float val = d.alpha * acc[a][b][v];
-                            if (d.accumulate) val += gload(c);
-                            gstore(c, val);
-                        }
-                    }
+            put_values<C>(g, acc, cur.split, cur.i0 + wi, cur.j0 + wj, d.P - cur.i0 - wi, d.Q - cur.j0 - wj);
             clear();
             at += stride;
             if (at < share) { cur = tile_at(at); slabs = (cur.kend - cur.k0) / C::BK; }
@@ -606,13 +619,12 @@ hipError_t launch_gemm_f32(const GemmF32* p, const int* splits, int n, float* pa
         tiles += a.g[i].tiles * a.g[i].splits;
     }
     if (tiles <= 0) return hipSuccess;
-    // Whole slabs: work-groups that stay, as many to a compute unit (three or four) as give it the fewest tiles to work through.
+    // whole slabs: work-groups that stay, three to a compute unit
     bool stream = !small && vec;
     for (int i = 0; i < n; ++i) stream = stream && p[i].limit == nullptr && p[i].K % Wide::BK == 0;
     if (stream) {
-        const int share = (tiles + 7) / 8, three = (share + 95) / 96 * 3, four = (share + 127) / 128 * 4;
-        const int room = three <= four ? 96 : 128;
-        hipLaunchKernelGGL((gemm_f32_stream_kernel<Wide>), dim3(8 * (share < room ? share : room)), dim3(NT), 0, s, a, n);
+        const int share = (tiles + 7) / 8;
+        hipLaunchKernelGGL((gemm_f32_stream_kernel<Wide>), dim3(8 * (share < 96 ? share : 96)), dim3(NT), 0, s, a, n);
     } else {
         launch_form(small, vec, (tiles + 7) / 8, nullptr, a, n, s);
     }
