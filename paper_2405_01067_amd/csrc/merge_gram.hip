@@ -11,6 +11,10 @@
 // diagonal tiles also write Abar / Bbar for the back-projection.  The tiles of one matrix sit
 // next to each other on one XCD (block index modulo 8), so that the strips they share come out of
 // that XCD's L2.
+//
+// What bounds it: one wave per SIMD, whose vector work (addresses and sums of the copies, conversions) stands beside its products instead of under them.  48 layers
+// of rank 384, four copies: 0.92 ms with the pointers in LDS and swizzled operands, 0.83 as it is (0.45 of matrix time on the CU with the most rows; 1.06 GB
+// fetched for 0.91); 16 dense weights, K = 768: 1.00 and 0.89.  Slabs of 16 and two work-groups per compute unit: 0.90 and 0.80.
 #include "merge_internal.h"
 
 namespace abt {
@@ -19,15 +23,14 @@ namespace {
 
 constexpr int GT = 128;        // tile edge
 constexpr int GCC = 32;        // contraction indices per slab
-constexpr int kGramPtrs = 64;  // copy pointers kept in LDS (more copies than that: fetched from the table)
-constexpr int GPITCH = 272;    // floats per contraction index in LDS (two strips of 128 + 16: the four
-                               // 16-lane rows of an operand read land in different quarters of the banks)
+constexpr int GPITCH = 272;    // floats per contraction index in LDS (two strips of 128 + 16)
+constexpr int GQPITCH = 4 * GPITCH + 16;       // of the four contraction indices of a matrix step
 
-// column swizzle: contraction index cc stores column c at c ^ (8 ((cc >> 2) & 7)).  Keeps aligned
-// groups of 8 columns together (16-byte stores of the A side), permutes inside aligned groups of 64,
-// and makes the transposing stores of the B side (8 lanes per row, 8 rows per wave and instruction)
-// hit 64 different banks.
-__device__ __forceinline__ int gsw(int cc, int c) { return c ^ (((cc >> 2) & 7) << 3); }
+// Where column c of contraction index cc lies in LDS.  The four 16-lane rows of an operand read land in different quarters of the
+// banks, and the transposing stores of the B side (8 lanes per row, 8 rows per wave and instruction: contraction indices 4 i + c, i = 0..7)
+// meet two at a time.  All operands of a wave are constant distances from one address that moves on by a constant per step: with one wave
+// on a SIMD the address arithmetic between two steps stands alone.  (A swizzle in place of the 16 cost 24 instructions a step.)
+__device__ __forceinline__ constexpr int gat(int cc, int c) { return (cc >> 2) * GQPITCH + (cc & 3) * GPITCH + c; }
 
 // VEC: every row of the source matrices starts 16-byte aligned and holds a multiple of four
 // elements (always true for the A side; for the B side when n % 4 == 0): 16-byte loads without
@@ -35,8 +38,7 @@ __device__ __forceinline__ int gsw(int cc, int c) { return c ^ (((cc >> 2) & 7) 
 template <bool VEC>
 __global__ __launch_bounds__(256, 1) void mean_gram_kernel(const LayerDev* __restrict__ layers,
                                                            const GramJob* __restrict__ jobs) {
-    __shared__ float X[2][GCC * GPITCH];
-    __shared__ const float* copy_ptr[kGramPtrs];
+    __shared__ __align__(16) float X[2][GCC / 4 * GQPITCH];
     const GramJob job = jobs[blockIdx.x];
     if (job.layer < 0) return;
     const LayerDev& L = layers[job.layer];
@@ -52,12 +54,12 @@ __global__ __launch_bounds__(256, 1) void mean_gram_kernel(const LayerDev* __res
     float* mean_out = bside ? L.Bbar : L.Abar;
     const int ncopies = mode == 0 ? G : 1;
     const float scale = (mode == 0 || !bside) ? 1.0f / (float)G : 1.0f;
-    // The pointers of the copies go to LDS once.  Fetched from the table in memory when a copy is
-    // issued, each would be a load the data loads depend on, and waiting for it (loads return in
-    // order) would also wait for every data load still in flight: one full memory latency per copy
-    // with nothing overlapped.
-    for (int g = t; g < G && g < kGramPtrs; g += 256) copy_ptr[g] = gload(src + g);
-    __syncthreads();
+    // The pointers of the copies come through the scalar cache, each a copy ahead of its use.  As vector loads, or read from LDS beside a branch
+    // with a vector load, each is waited for together with every data load in flight (loads return in order): a memory latency
+    // per copy with nothing overlapped.
+    typedef const float* const __attribute__((address_space(4)))* PtrTable;
+    const PtrTable table = (PtrTable)(uintptr_t)src;
+    const float* next_copy = table[0];
 
     // ---- this thread's chunks of a slab: 4 per strip.  Chunk e of strip s (id = 256 e + t):
     //   A side: contraction row id >> 5 of the slab, columns 4 (id & 31) .. + 3 of the strip
@@ -88,7 +90,8 @@ __global__ __launch_bounds__(256, 1) void mean_gram_kernel(const LayerDev* __res
     // issue: loads only (every address is clamped into the matrix, so none needs a predicate and no
     // instruction between them waits for data); absorb: drops what was out of range and adds the rest
     auto issue = [&](int sl, int g, f32x4 (&pend)[2][4]) {
-        const float* base = mode != 0 ? nullptr : (g < kGramPtrs ? copy_ptr[g] : gload(src + g));
+        const float* base = next_copy;
+        next_copy = table[g + 1 < ncopies ? g + 1 : 0];
 #pragma unroll
         for (int s = 0; s < 2; ++s) {
             if (s >= nstrip) break;
@@ -148,13 +151,13 @@ __global__ __launch_bounds__(256, 1) void mean_gram_kernel(const LayerDev* __res
                 const f32x4 v = sum[s][e] * scale;
                 if (!bside) {
                     const int cc = id >> 5, col = 4 * (id & 31);
-                    *reinterpret_cast<f32x4*>(Xb + cc * GPITCH + gsw(cc, GT * s + col)) = v;
+                    *reinterpret_cast<f32x4*>(Xb + gat(cc, GT * s + col)) = v;
                     if (diag && c0 + cc < len && sb + col < K)
                         gstore(reinterpret_cast<f32x4*>(mean_out + (int64_t)(c0 + cc) * K + sb + col), v);
                 } else {
                     const int row = id >> 3, cc0 = 4 * (id & 7);
 #pragma unroll
-                    for (int c = 0; c < 4; ++c) Xb[(cc0 + c) * GPITCH + gsw(cc0 + c, GT * s + row)] = v[c];
+                    for (int c = 0; c < 4; ++c) Xb[gat(cc0 + c, GT * s + row)] = v[c];
                     if (diag && sb + row < K) {
                         float* dst = mean_out + (int64_t)(sb + row) * len + c0 + cc0;
                         if (VEC) { if (c0 + cc0 < len) gstore(reinterpret_cast<f32x4*>(dst), v); }
@@ -181,12 +184,12 @@ __global__ __launch_bounds__(256, 1) void mean_gram_kernel(const LayerDev* __res
     const bool idle = (diag && wr == 0 && wc == 1) || na <= 0 || nb <= 0;      // the mirror image of wave (1, 0), or nothing inside K
     const bool whole = na >= 4 && nb >= 4;
     float fa[4], fb[4];
+    const int base_a = kq * GPITCH + offA + n, base_b = kq * GPITCH + offB + n;
     auto fetch = [&](const float* Xb, int q) {
-        const int cc = 4 * q + kq;
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-            fa[i] = Xb[cc * GPITCH + gsw(cc, offA + 16 * i + n)];
-            fb[i] = Xb[cc * GPITCH + gsw(cc, offB + 16 * i + n)];
+            fa[i] = Xb[q * GQPITCH + base_a + 16 * i];
+            fb[i] = Xb[q * GQPITCH + base_b + 16 * i];
         }
     };
     auto kstep = [&](const float* Xb, int q) {
