@@ -736,7 +736,6 @@ void jacobi_single_pair_kernel(double* cores, int* rotated, int max_sweeps) {
     double* const Ct = cores + (int64_t)blockIdx.x * core_doubles(K);
     rotated += (int)blockIdx.x * (kMaxSweepsCap + 1);
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, n = lane & 15, kq = lane >> 4;
-    const int gi = (tid >> 6) + 4 * (tid & 3), gj = (tid >> 2) & 15;      // this thread's element of a 16 x 16 tile
     const double frob = frob2(Ct + core_trace(K));
     // D[t][s] = C[2 n + t][kq + 4 s], in the first wave
     double D[2][8];
