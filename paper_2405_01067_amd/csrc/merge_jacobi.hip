@@ -23,10 +23,9 @@
 // wave passes its row tiles through a private LDS tile for that.
 //
 // What bounds it: nothing survives in L2 from one round to the next, so a round reads and writes all cores beyond it: 64 GB for 16 cores
-// of 768 in 9 sweeps, 5.0 TB/s in 12.7 ms, which is what a large copy reaches (two work-groups per compute unit; one at a time 13.5 ms; 14.0 without the
-// loads and stores that overlap the arithmetic; 16.2 with the rotations in fp64).  48 cores of 384, 8 sweeps: 4.6 ms with the rotations in fp64, 4.05 in
-// fp32, 3.7 with four blocks, which is half the traffic.  With few cores a work-group's chain counts: cycles at K = 384 (two blocks): arguments and flag 1500, first
-// columns 3000, Gram matrix 5600, rotations 9800, the last of Q 1100, update 6400 (fp64 matrix instructions); four blocks 72000 a round of three times
+// of 768 in 9 sweeps, 4.8 TB/s in 13.3 ms, near what a large copy reaches (one work-group per compute unit, one thing after the other, 16.2).  48 cores
+// of 384, 8 sweeps: 4.6 ms that way, 4.0 with four blocks, which is half the traffic.  With few cores a work-group's chain counts: cycles at K = 384 (two blocks): arguments and flag 1500, first
+// columns 3000, Gram matrix 5600, rotations 12000, the last of Q 1100, update 6400 (fp64 matrix instructions); four blocks some 80000 a round of three times
 // those links.  Launches follow each other in 1.3 us.
 #include <type_traits>
 
@@ -45,9 +44,9 @@ __device__ __forceinline__ int stage_addr(int n, int c) {
 // What the rotations of a block pair need in LDS
 struct __align__(16) PairShared {
     double Q[32][48];
-    float S[32][33];                // the Gram matrix times a power of two
+    double S[32][33];               // the Gram matrix times a power of two
     int did;                        // 0: rotated nothing, 1: nothing significant, 2: something
-    float tan[2][31][16];           // tangents of the rotations of all steps (second half: what other lanes than the pairs' own come to)
+    float tan[31][16];              // tangents of the rotations of all steps
 };
 
 // ---- The rotations of a block pair.  Columns 0..31 (the two blocks) are paired by exclusive or: step m pairs every i with
@@ -106,16 +105,17 @@ __device__ __forceinline__ double lane_xor(double v) {
 }
 // the value of lane ^ 16 or ^ 32: whole rows of 16 lanes change places
 template <int B>
-__device__ __forceinline__ float row_xor(float v) {
-    const unsigned x = __float_as_uint(v);
+__device__ __forceinline__ int row_xor(int x) {
     if constexpr (B == 16) {
         const auto r = __builtin_amdgcn_permlane16_swap(x, x, false, false);      // r[0]: even rows twice, r[1]: odd rows twice
-        return __uint_as_float((threadIdx.x & 16) ? r[0] : r[1]);
+        return (threadIdx.x & 16) ? r[0] : r[1];
     } else {
         const auto r = __builtin_amdgcn_permlane32_swap(x, x, false, false);
-        return __uint_as_float((threadIdx.x & 32) ? r[0] : r[1]);
+        return (threadIdx.x & 32) ? r[0] : r[1];
     }
 }
+template <int B>
+__device__ __forceinline__ double row_xor(double v) { return __hiloint2double(row_xor<B>(__double2hiint(v)), row_xor<B>(__double2loint(v))); }
 // lanes 0..15 to all four rows
 __device__ __forceinline__ float first_row(float v) {
     const unsigned x = __float_as_uint(v);
@@ -123,35 +123,37 @@ __device__ __forceinline__ float first_row(float v) {
     return __uint_as_float(__builtin_amdgcn_permlane16_swap(lo, lo, false, false)[0]);
 }
 // of a value that all rows hold alike: lane u ^ 4 q of it for lane (u, q)
-__device__ __forceinline__ float xor_by_row(float v) {
-    int x = __float_as_int(v);
+__device__ __forceinline__ int xor_by_row(int x) {
     x = dpp_rows<0x128, 0xc>(x, x);                           // rows 2, 3: lanes 8 apart
     const int w = dpp_rows<0x141, 0xa>(x, x);                 // rows 1, 3: lanes 4 apart, in two moves
-    return __int_as_float(dpp_rows<0x1B, 0xa>(w, w));
+    return dpp_rows<0x1B, 0xa>(w, w);
 }
+__device__ __forceinline__ float xor_by_row(float v) { return __int_as_float(xor_by_row(__float_as_int(v))); }
+__device__ __forceinline__ double xor_by_row(double v) { return __hiloint2double(xor_by_row(__double2hiint(v)), xor_by_row(__double2loint(v))); }
 
-// Level p on S by one wave, S in registers in fp32: lane (u = l % 16, q = l / 16) owns, for x = 4 q + e, the 2 x 2 cell rows
+// Level p on S by one wave, S in registers: lane (u = l % 16, q = l / 16) owns, for x = 4 q + e, the 2 x 2 cell rows
 // L(u), R(u ^ t) x columns L(v), R(v ^ t) with v = u ^ x.  t runs through a Gray code; when bit b of it changes, a cell finds its new
 // off-diagonal entries in the cell x ^ b (another register of the lane for b = 1, 2) and its new last
 // entry, like the one below the diagonal, in lane ^ b: register names and data-parallel moves, no LDS and no barrier
 // in a step.  The pairs' own cells are x = 0, in the first 16 lanes, which work the tangents out; these go to the other lanes by row
 // swaps and row-masked moves.
-// The tangent is that of jacobi_rotation(), without branches.  Any tangent gives a rotation that is orthogonal to fp64 rounding, as
-// the work-group forms cosine and sine from it in fp64 afterwards; one good to 1e-7 leaves the pair with 1e-7 of its cosine.  S is
+// The tangent is that of jacobi_rotation(), without branches, in fp32 from a difference taken in fp64.  Any tangent gives a rotation
+// that is orthogonal to fp64 rounding, as cosine and sine are formed from it in fp64; one good to 1e-7 leaves the pair with 1e-7 of its cosine.  S is
 // scaled by a power of two near 1 / ||C||_F^2: squared norms lie between kZeroColumn2 and 1, inner products of a pair that is
-// rotated above 1e-9 of that, inside the fp32 range (their squares are not: the cosine is formed from two reciprocal square roots).
-// fp32 is enough for S: the columns themselves, the rotations and their product Q stay in fp64, and what 1e-7 of a cosine leaves is seen
-// by the next sweep, which forms S anew; the sweeps are as many (simulated for cores of 128 to 768, measured on those of the case table).
+// rotated above 1e-9 of that, inside the fp32 range.
+// S itself is fp64 throughout.  In fp32 the difference of the norms of nearly equal columns is rounding, and what is left of a small
+// column's norm beside a large one's too: two clusters of values 1e-3 apart took 18 to 20 sweeps of 768 columns instead of 14 or 15 and were
+// left twice as far off.  (A step is 750 cycles, 540 in fp32: one core of 32 41 us / 33, 48 cores of 384 4.0 ms / 3.7, 16 of 768 13.3 / 12.7.)
 // The steps are serial, so the chain through the pairs' own cells sets the pace, and the issue of the other cells' updates comes next: a
 // step updates the cells that the next tangent needs first and the others between the links of its formula.
 // A cell is multiplied by (1, -t; t, 1) from both sides and by the product of the cosines.
-// A step took 790 cycles in fp64 with lane permutes, 720 in fp32 with all cells ahead of the formula.
-template <int P>
-__device__ __forceinline__ void rotate_level(float (*S)[33], float* tangents, float floor2, bool& any, bool& any_signif, int* did = nullptr,
-                                             float* diagI = nullptr, float* diagJ = nullptr) {
+// `spare`: where other lanes than the pairs' own put what they come to for a tangent.
+// keep(block, row, column, value): what is left of the two blocks' own Gram matrices (level 4).
+template <int P, class Keep>
+__device__ __forceinline__ void rotate_level(double (*S)[33], float* tangents, float* spare, double floor2, bool& any, bool& any_signif, int* did, Keep&& keep) {
     const int lane = thread_anew() & 63, u = lane & 15, q = lane >> 4;
-    float* const mine = tangents + u + (q ? 31 * 16 : 0);
-    float m00[4], m01[4], m10[4], m11[4];
+    float* const mine = (q ? spare : tangents) + u;
+    double m00[4], m01[4], m10[4], m11[4];
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
         const int v = u ^ (4 * q + e);
@@ -159,49 +161,51 @@ __device__ __forceinline__ void rotate_level(float (*S)[33], float* tangents, fl
         m10[e] = S[right_of(u, P)][left_of(v, P)]; m11[e] = S[right_of(u, P)][right_of(v, P)];
     }
     // the tangent of the pair with squared norms alpha, beta and inner product gamma, in three links
-    float zeta, w, ra, rb, rg, own;
-    auto link1 = [&](float alpha, float beta, float gamma) {
-        rg = __builtin_amdgcn_rcpf(gamma + gamma);
-        ra = __builtin_amdgcn_rsqf(alpha); rb = __builtin_amdgcn_rsqf(beta);
-        zeta = beta - alpha;
+    float zeta, w, own;
+    bool turn;
+    auto link1 = [&](double alpha, double beta, double gamma) {
+        const float g = (float)gamma;
+        zeta = (float)(beta - alpha) * __builtin_amdgcn_rcpf(g + g);
+        const double lim = alpha * beta, g2 = gamma * gamma;
+        const bool live = alpha > floor2 && beta > floor2;
+        any_signif |= live && g2 > (kSignifTol * kSignifTol) * lim;        // (this and the next count in the first 16 lanes)
+        turn = live && g2 > (kRotateTol * kRotateTol) * lim;
+        any |= turn;
     };
     auto link2 = [&]() {
-        zeta *= rg;                                      // an overflow of its square ends in t = 0 (|t| < 1e-19)
-        w = __builtin_amdgcn_sqrtf(fmaf(zeta, zeta, 1.0f));
+        w = __builtin_amdgcn_sqrtf(fmaf(zeta, zeta, 1.0f));                // an overflow of the square ends in t = 0 (|t| < 1e-19)
     };
-    auto link3 = [&](float alpha, float beta, float gamma) {
-        const float cosine = fabsf(gamma) * ra * rb;
-        const bool live = alpha > floor2 && beta > floor2;
-        any_signif |= live && cosine > (float)kSignifTol;                  // (this and the next count in the first 16 lanes)
-        any |= live && cosine > (float)kRotateTol;
+    auto link3 = [&]() {
         const float ta = __builtin_amdgcn_rcpf(fabsf(zeta) + w);
-        own = live && cosine > (float)kRotateTol ? copysignf(ta, zeta) : 0.0f;
+        own = turn ? copysignf(ta, zeta) : 0.0f;
     };
-    link1(m00[0], m11[0], m01[0]); link2(); link3(m00[0], m11[0], m01[0]);
+    link1(m00[0], m11[0], m01[0]); link2(); link3();
     // one step; B: the bit of t that changes after it (0: the last step)
     auto step = [&](auto bit, int k) {
         constexpr int B = decltype(bit)::value;
         constexpr int E1 = B == 2 ? 2 : 1, E2 = B == 2 ? 1 : 2;            // the second cell to be updated, the third
         mine[16 * k] = own;
         const float t = first_row(own);
-        float t2[4], c12[4];
-        t2[0] = xor_by_row(t);
-        const float c1 = __builtin_amdgcn_rsqf(fmaf(t, t, 1.0f));
-        const float c2 = xor_by_row(c1);
-        t2[1] = lane_xor<1>(t2[0]); t2[2] = lane_xor<2>(t2[0]); t2[3] = lane_xor<3>(t2[0]);
-        c12[0] = c1 * c2; c12[1] = c1 * lane_xor<1>(c2); c12[2] = c1 * lane_xor<2>(c2); c12[3] = c1 * lane_xor<3>(c2);
-        float n01[4], n10[4], n11[4];
+        const float f2 = xor_by_row(t);
+        const double t1 = (double)t;
+        // c = c0 (1 - e)^(-1/2) = c0 (1 + e/2 + 3 e^2/8 + ..) with c0 in fp32
+        const double c0 = (double)__builtin_amdgcn_rsqf(fmaf(t, t, 1.0f));
+        const double err = fma(-(c0 * c0), fma(t1, t1, 1.0), 1.0), c1 = fma(c0, err * fma(0.375, err, 0.5), c0), c2 = xor_by_row(c1);
+        double n01[4], n10[4], n11[4];
         auto update = [&](auto which) {
             constexpr int e = decltype(which)::value;
-            const float a = fmaf(-t, m10[e], m00[e]), b = fmaf(-t, m11[e], m01[e]), c = fmaf(t, m00[e], m10[e]), d = fmaf(t, m01[e], m11[e]);
-            m00[e] = fmaf(-t2[e], b, a) * c12[e]; n01[e] = fmaf(t2[e], a, b) * c12[e];
-            n10[e] = fmaf(-t2[e], d, c) * c12[e]; n11[e] = fmaf(t2[e], c, d) * c12[e];
+            double t2, c12;
+            if constexpr (e == 0) { t2 = (double)f2; c12 = c1 * c2; }
+            else { t2 = (double)lane_xor<e>(f2); c12 = c1 * lane_xor<e>(c2); }
+            const double a = fma(-t1, m10[e], m00[e]), b = fma(-t1, m11[e], m01[e]), c = fma(t1, m00[e], m10[e]), d = fma(t1, m01[e], m11[e]);
+            m00[e] = fma(-t2, b, a) * c12; n01[e] = fma(t2, a, b) * c12;
+            n10[e] = fma(-t2, d, c) * c12; n11[e] = fma(t2, c, d) * c12;
         };
         update(std::integral_constant<int, 0>{});
         if constexpr (B == 1 || B == 2) update(std::integral_constant<int, E1>{});
-        float beta = 0.0f, gamma = 0.0f;
         if constexpr (B != 0) {
-            beta = lane_xor<B>(n11[0]);
+            const double beta = lane_xor<B>(n11[0]);
+            double gamma;
             if constexpr (B < 4) gamma = n01[E1];
             else gamma = row_xor<4 * B>(n01[0]);
             link1(m00[0], beta, gamma);
@@ -212,7 +216,7 @@ __device__ __forceinline__ void rotate_level(float (*S)[33], float* tangents, fl
         if constexpr (B != 0) link2();
         __builtin_amdgcn_sched_barrier(0);
         update(std::integral_constant<int, 3>{});
-        if constexpr (B != 0) link3(m00[0], beta, gamma);
+        if constexpr (B != 0) link3();
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
             if constexpr (B == 0) { m01[e] = n01[e]; m10[e] = n10[e]; m11[e] = n11[e]; }
@@ -231,12 +235,11 @@ __device__ __forceinline__ void rotate_level(float (*S)[33], float* tangents, fl
         const bool r = __builtin_amdgcn_ballot_w64(any && lane < 16) != 0, sg = __builtin_amdgcn_ballot_w64(any_signif && lane < 16) != 0;
         if (lane == 0) *did = sg ? 2 : r ? 1 : 0;
         lds_barrier();
-        if (diagI == nullptr) return;
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
             const int v = u ^ (4 * q + e);
-            diagI[17 * u + v] = m00[e];
-            diagJ[17 * (u ^ t) + (v ^ t)] = m11[e];
+            keep(0, u, v, m00[e]);
+            keep(1, u ^ t, v ^ t, m11[e]);
         }
         return;
     }
@@ -334,23 +337,28 @@ __device__ __forceinline__ void accumulate_cross(double (*Q)[48], const float (*
 
 // The sixteen steps of a block pair, after those inside its blocks if `inside`, by the waves that share it: `role` 3 works the rotations out,
 // 0 to 2 accumulate them.  `table`: 4 KB of LDS of the wave's own.  Four barriers with `inside`, three without; Q and `did` are
-// there after the last.
-__device__ __forceinline__ void rotate_pair(PairShared& sh, bool inside, int role, f64x2* table, float floor2, float* diagI, float* diagJ) {
+// there after the last.  after(): at the end, by the wave that works the rotations out.
+template <class Keep, class After>
+__device__ __forceinline__ void rotate_pair(PairShared& sh, bool inside, int role, f64x2* table, double floor2, Keep&& keep, After&& after) {
     if (role == 3) {
         bool any = false, any_signif = false;
+        float* const spare = reinterpret_cast<float*>(table);
         if (inside) {
-            rotate_level<3>(sh.S, sh.tan[0][16], floor2, any, any_signif);
-            rotate_level<2>(sh.S, sh.tan[0][24], floor2, any, any_signif);
-            rotate_level<1>(sh.S, sh.tan[0][28], floor2, any, any_signif);
-            rotate_level<0>(sh.S, sh.tan[0][30], floor2, any, any_signif);
+            rotate_level<3>(sh.S, sh.tan[16], spare, floor2, any, any_signif, nullptr, keep);
+            rotate_level<2>(sh.S, sh.tan[24], spare, floor2, any, any_signif, nullptr, keep);
+            rotate_level<1>(sh.S, sh.tan[28], spare, floor2, any, any_signif, nullptr, keep);
+            rotate_level<0>(sh.S, sh.tan[30], spare, floor2, any, any_signif, nullptr, keep);
             lds_barrier();
         }
-        rotate_level<4>(sh.S, sh.tan[0][0], floor2, any, any_signif, &sh.did, diagI, diagJ);
+        rotate_level<4>(sh.S, sh.tan[0], spare, floor2, any, any_signif, &sh.did, keep);
+        lds_barrier();
+        after();
+        return;
     } else if (inside) {
-        accumulate_inside(sh.Q, sh.tan[0], table, role);
-        accumulate_cross<false>(sh.Q, sh.tan[0], table, role);
+        accumulate_inside(sh.Q, sh.tan, table, role);
+        accumulate_cross<false>(sh.Q, sh.tan, table, role);
     } else {
-        accumulate_cross<true>(sh.Q, sh.tan[0], table, role);
+        accumulate_cross<true>(sh.Q, sh.tan, table, role);
     }
     lds_barrier();
 }
@@ -378,7 +386,7 @@ void jacobi_quad_kernel(double* cores, int* rotated, int K, int sweep, int round
     __shared__ struct __align__(16) {
         double stage[8][2][16 * 32];    // per wave: transposition tiles; afterwards the waves' partial Gram tiles, then tables of rotations
         PairShared pair[2];
-        float diag[4][16 * 17];         // Gram matrices of the blocks, scaled
+        double diag[4][16 * 17];        // Gram matrices of the blocks, scaled
     } sh;
     const Core c = find_core(cores, rotated, K, layers, wg_map);
     double* const Ct = c.Ct;
@@ -438,10 +446,10 @@ void jacobi_quad_kernel(double* cores, int* rotated, int K, int sweep, int round
         }
     }
     const double scale = ldexp(1.0, -__builtin_amdgcn_frexp_exp(frob));
-    const float floor2 = (float)(kZeroColumn2 * frob * scale);
+    const double floor2 = kZeroColumn2 * frob * scale;
     if (round != 0) {
-        sh.diag[half][17 * gi + gj] = (float)(kept[0] * scale);           // (id[i] = i)
-        sh.diag[2 + half][17 * gi + gj] = (float)(kept[1] * scale);
+        sh.diag[half][17 * gi + gj] = kept[0] * scale;           // (id[i] = i)
+        sh.diag[2 + half][17 * gi + gj] = kept[1] * scale;
     }
     // exchange positions A and B
     auto exchange = [&](auto a, auto b) {
@@ -522,9 +530,9 @@ void jacobi_quad_kernel(double* cores, int* rotated, int K, int sweep, int round
             double sum = sh.stage[0][0][tid];
 #pragma unroll
             for (int w = 1; w < 8; ++w) sum += sh.stage[w][0][tid];
-            return (float)(sum * scale);
+            return sum * scale;
         };
-        const float sIJ = total(gIJ);
+        const double sIJ = total(gIJ);
         mine.S[gi][16 + gj] = sIJ;
         mine.S[16 + gj][gi] = sIJ;
         if (inside) {
@@ -540,7 +548,7 @@ void jacobi_quad_kernel(double* cores, int* rotated, int K, int sweep, int round
 
         // ---- the rotations of the two pairs; the waves that work them out sit on two SIMDs
         rotate_pair(mine, inside, ((wave & 3) - 2 * half - 1) & 3, reinterpret_cast<f64x2*>(sh.stage[wave][0]), floor2,
-                    sh.diag[half ? id[1] : id[0]], sh.diag[half ? id[3] : id[2]]);
+                    [&](int block, int i, int j, double v) { sh.diag[block ? (half ? id[3] : id[2]) : (half ? id[1] : id[0])][17 * i + j] = v; }, [] {});
         // (Compared as numbers: with one bit of a scalar tested for several branches the compiler inverted some of them.)
         const int did[2] = {__builtin_amdgcn_readfirstlane(sh.pair[0].did), __builtin_amdgcn_readfirstlane(sh.pair[1].did)};
         const int more = did[0] > did[1] ? did[0] : did[1];
@@ -586,8 +594,8 @@ void jacobi_quad_kernel(double* cores, int* rotated, int K, int sweep, int round
 
     if (!whole) {                                        // (a, b, c, d again; scaled by a power of two)
         const double unscale = 1.0 / scale;
-        gstore(diag + (half ? blk[1] : blk[0]) * 256 + 16 * gi + gj, (double)sh.diag[half][17 * gi + gj] * unscale);
-        if (dJ >= 0) gstore(diag + (half ? blk[3] : blk[2]) * 256 + 16 * gi + gj, (double)sh.diag[2 + half][17 * gi + gj] * unscale);
+        gstore(diag + (half ? blk[1] : blk[0]) * 256 + 16 * gi + gj, sh.diag[half][17 * gi + gj] * unscale);
+        if (dJ >= 0) gstore(diag + (half ? blk[3] : blk[2]) * 256 + 16 * gi + gj, sh.diag[2 + half][17 * gi + gj] * unscale);
     }
     if (whole && touched > 0) {
 #pragma unroll
@@ -596,12 +604,15 @@ void jacobi_quad_kernel(double* cores, int* rotated, int K, int sweep, int round
     }
 }
 
-// Two blocks per work-group, four waves of up to NT row tiles, K <= 64 NT.  Work-groups per compute unit: as many as the registers allow (K = 768: two
-// 12.7 ms, one 13.5 over 16 decompositions; four blocks, one work-group per compute unit and some registers in memory, 15.0).
+// Two blocks per work-group, four waves of up to NT row tiles, K <= 64 NT.  Work-groups per compute unit: as many as the registers allow, three or
+// two (K = 768: 13.3 ms over 16 decompositions; four blocks, one work-group per compute unit and some registers in memory, 15.0 where two blocks took 12.7).
 template <int NT>
-__global__ __launch_bounds__(256, (NT <= 2 ? 4 : NT <= 6 ? 3 : 2))
+__global__ __launch_bounds__(256, (NT <= 6 ? 3 : 2))
 void jacobi_pair_kernel(double* cores, int* rotated, int K, int sweep, int round, const LayerDev* __restrict__ layers, const int2* __restrict__ wg_map) {
-    __shared__ struct __align__(16) { double stage[4][16 * 32]; PairShared pair; float diag[2][16 * 17]; } sh;
+    // the wave that works the rotations out has no registers for its whole panel meanwhile: its last rows wait in LDS (16 cores of 768 13.3 ms, 15.3
+    // with 60 registers spilled to memory)
+    constexpr int PARK = NT == 12 ? 32 : NT == 6 ? 16 : 0;
+    __shared__ struct __align__(16) { double stage[4][16 * 32]; PairShared pair; double parked[PARK ? PARK : 1][64]; } sh;
     const Core c = find_core(cores, rotated, K, layers, wg_map);
     if (sweep > 0 && c.rotated[sweep - 1] == 0) return;   // the previous sweep found no significant pair: the iteration has converged
     K = c.K;
@@ -637,7 +648,7 @@ void jacobi_pair_kernel(double* cores, int* rotated, int K, int sweep, int round
         }
     }
     const double scale = ldexp(1.0, -__builtin_amdgcn_frexp_exp(frob));
-    const float floor2 = (float)(kZeroColumn2 * frob * scale);
+    const double floor2 = kZeroColumn2 * frob * scale;
     double* const stage = sh.stage[wave];
     f64x4 g[3] = {};                                      // IJ, II, JJ
     auto gram = [&](auto all) {
@@ -666,14 +677,20 @@ void jacobi_pair_kernel(double* cores, int* rotated, int K, int sweep, int round
     };
     if (inside) gram(std::true_type{});
     else gram(std::false_type{});
+    const int role = (wave - (int)((blockIdx.x + blockIdx.y) & 3) - 1) & 3;
+    if (PARK && role == 3) {
+        const int lane = thread_anew() & 63;
+#pragma unroll
+        for (int i = 0; i < PARK; ++i) sh.parked[i][lane] = D[NT - 1 - i / 8][i % 8];
+    }
     // partial tiles of the four waves, added in wave order (see jacobi_quad_kernel)
     auto total = [&](const f64x4& part) {
 #pragma unroll
         for (int v = 0; v < 4; ++v) stage[4 * lane + v] = part[v];
         __syncthreads();
-        return (float)((((sh.stage[0][tid] + sh.stage[1][tid]) + sh.stage[2][tid]) + sh.stage[3][tid]) * scale);
+        return (((sh.stage[0][tid] + sh.stage[1][tid]) + sh.stage[2][tid]) + sh.stage[3][tid]) * scale;
     };
-    const float sIJ = total(g[0]);
+    const double sIJ = total(g[0]);
     sh.pair.S[gi][16 + gj] = sIJ;
     sh.pair.S[16 + gj][gi] = sIJ;
     if (inside) {
@@ -682,18 +699,20 @@ void jacobi_pair_kernel(double* cores, int* rotated, int K, int sweep, int round
         __syncthreads();
         sh.pair.S[16 + gi][16 + gj] = total(g[2]);
     } else {
-        sh.pair.S[gi][gj] = (float)(keptI * scale);
-        sh.pair.S[16 + gi][16 + gj] = (float)(keptJ * scale);
+        sh.pair.S[gi][gj] = keptI * scale;
+        sh.pair.S[16 + gi][16 + gj] = keptJ * scale;
     }
     __syncthreads();
-    rotate_pair(sh.pair, inside, (wave - (int)((blockIdx.x + blockIdx.y) & 3) - 1) & 3, reinterpret_cast<f64x2*>(stage), floor2, sh.diag[0], sh.diag[1]);
+    rotate_pair(sh.pair, inside, role, reinterpret_cast<f64x2*>(stage), floor2,
+                [&](int block, int i, int j, double v) { gstore((block ? diagJ : diagI) + 16 * i + j, v * (1.0 / scale)); },
+                [&] {
+                    const int lane = thread_anew() & 63;
+#pragma unroll
+                    for (int i = 0; i < PARK; ++i) D[NT - 1 - i / 8][i % 8] = sh.parked[i][lane];
+                });
     {
     const int tid = thread_anew(), lane = tid & 63, n = lane & 15, kq = lane >> 4;
-    const int gi = wave + 4 * (tid & 3), gj = (tid >> 2) & 15;
     const int did = __builtin_amdgcn_readfirstlane(sh.pair.did);
-    const double unscale = 1.0 / scale;
-    gstore(diagI + 16 * gi + gj, (double)sh.diag[0][17 * gi + gj] * unscale);
-    gstore(diagJ + 16 * gi + gj, (double)sh.diag[1][17 * gi + gj] * unscale);
     if (did == 0) return;                                 // the columns are what they were
     if (tid == 0 && did == 2) gstore(c.rotated + sweep, 1);
 
@@ -728,7 +747,7 @@ void jacobi_pair_kernel(double* cores, int* rotated, int K, int sweep, int round
 
 // Cores of 32: two blocks, one pair.  The work-group (four waves, of which the first has all rows) holds the whole core and runs all
 // sweeps in one launch, the columns in registers throughout.  A launch and a poll of the convergence flags per
-// sweep took 129 us for one core of 32, this 54 with the rotations in fp64, 33 in fp32.
+// sweep took 129 us for one core of 32, this 41.
 __global__ __launch_bounds__(256, 1)
 void jacobi_single_pair_kernel(double* cores, int* rotated, int max_sweeps) {
     __shared__ struct __align__(16) { double stage[4][16 * 32]; PairShared pair; } sh;
@@ -746,7 +765,7 @@ void jacobi_single_pair_kernel(double* cores, int* rotated, int max_sweeps) {
         D[1][s] = v[1];
     }
     const double scale = ldexp(1.0, -__builtin_amdgcn_frexp_exp(frob));
-    const float floor2 = (float)(kZeroColumn2 * frob * scale);
+    const double floor2 = kZeroColumn2 * frob * scale;
     for (int sweep = 0;; ++sweep) {
         const int lane = thread_anew() & 63, n = lane & 15, kq = lane >> 4;
         if (wave == 0) {
@@ -770,15 +789,15 @@ void jacobi_single_pair_kernel(double* cores, int* rotated, int max_sweeps) {
 #pragma unroll
             for (int v = 0; v < 4; ++v) {
                 const int i = kq + 4 * v, j = n;
-                sh.pair.S[i][j] = (float)(g[0][v] * scale);
-                const float cross = (float)(g[1][v] * scale);
+                sh.pair.S[i][j] = g[0][v] * scale;
+                const double cross = g[1][v] * scale;
                 sh.pair.S[i][16 + j] = cross;
                 sh.pair.S[16 + j][i] = cross;
-                sh.pair.S[16 + i][16 + j] = (float)(g[2][v] * scale);
+                sh.pair.S[16 + i][16 + j] = g[2][v] * scale;
             }
         }
         __syncthreads();
-        rotate_pair(sh.pair, true, (wave - 1) & 3, reinterpret_cast<f64x2*>(sh.stage[wave]), floor2, nullptr, nullptr);
+        rotate_pair(sh.pair, true, (wave - 1) & 3, reinterpret_cast<f64x2*>(sh.stage[wave]), floor2, [](int, int, int, double) {}, [] {});
         const int did = __builtin_amdgcn_readfirstlane(sh.pair.did);
         if (did == 0) break;
         if (wave == 0) {

@@ -116,6 +116,52 @@ def test_four_blocks_a_work_group(sizes, zero_tail):
         assert float((got - want).norm() / want.norm()) < 4e-6
 
 
+def planted(m, n, values, seed):
+    """Factors (fp32) with these singular values (fp64), their columns mixed, and the product that they make."""
+    g = torch.Generator().manual_seed(seed)
+    K = values.numel()
+    frame = lambda rows: torch.linalg.qr(torch.randn((rows, K), generator=g, dtype=torch.float64).to("cuda:0"))[0]
+    U, V, R, root = frame(m), frame(n), frame(K), values.to("cuda:0").sqrt()
+    A, B = ((U * root) @ R).float().contiguous(), (R.T @ (root[:, None] * V.T)).float().contiguous()
+    return A, B, A.double() @ B.double()
+
+
+# Two clusters of values three orders apart.  With the Gram matrix of a block pair in fp64 the iteration takes 14 or 15 sweeps of 768 columns (two
+# blocks a work-group) and of 512 (four) at any of six seeds; in fp32, where the difference of nearly equal squared norms and what is left of a
+# small column's beside a large one's are rounding, 18 to 20 and 16 or 17.
+@pytest.mark.parametrize("K,count,sweeps", [(768, 1, 16), (512, 12, 15)])
+def test_clusters_far_apart_take_the_sweeps_of_fp64(K, count, sweeps):
+    g = torch.Generator().manual_seed(K)
+    s = torch.where(torch.arange(K) < K // 2, 1.0, 1e-3).double() * (1 + 1e-5 * torch.rand(K, generator=g, dtype=torch.float64))
+    A, B, W = planted(K + 72, K + 40, s, seed=K)
+    out = abt.ab_merge_batched([{"A_copies": [A], "B_copies": [B], "tau": 0.0, "k_fixed": K, "k_cap": K}] * count)[-1]
+    assert out["sweeps"] <= sweeps
+    ref = torch.linalg.svdvals(W)[:K]
+    # columns of a cluster that are left with a cosine of c have norms c / 2 off the values; the last sweep leaves some 1e-7 inside a cluster
+    assert float(((out["S"].double() - ref).abs() / ref).max()) < 1e-6
+
+
+# Eight clusters between 1 and 1/2, equal inside or nearly so, through every form of the iteration: one pair of blocks, one pair of double blocks in one
+# launch, two blocks a work-group, four.
+@pytest.mark.parametrize("gap", [0.0, 1e-6, 1e-5, 1e-4, 1e-3])
+@pytest.mark.parametrize("K,count", [(32, 1), (64, 1), (96, 1), (128, 4), (256, 1), (384, 16), (768, 1)])
+def test_clustered_values(K, count, gap):
+    i = torch.arange(K, dtype=torch.float64)
+    s = 2.0 ** -((i // (K // 8)) / 8) * (1 + gap * (i % (K // 8)) / (K // 8))
+    A, B, W = planted(K + 72, K + 40, s, seed=K + 1)
+    out = abt.ab_merge_batched([{"A_copies": [A], "B_copies": [B], "tau": 0.0, "k_fixed": K, "k_cap": K}] * count)[-1]
+    a, b = out["A"].double(), out["B"].double().T
+    # The iteration ends with a sweep in which no pair that it came to had a cosine above 3e-4: that is what columns may be left with where values are
+    # equal, and up to twice that (the ratio of the values) on the side that is found from the other.
+    for x in (a, b):
+        x = x / x.norm(dim=0)
+        assert float((x.T @ x - torch.eye(K, device="cuda:0", dtype=torch.float64)).abs().max()) < 6e-4
+    # U U^T W for the U that was found: as far off as its columns are from orthogonal, in the norm
+    assert float((a @ b.T - W).norm() / W.norm()) < 6e-4
+    ref = torch.linalg.svdvals(W)[:K]
+    assert float(((out["S"].double() - ref).abs() / ref).max()) < 3e-4 / 2
+
+
 # shapes around the 64 contraction indices of a step and the 16 work-groups of a side, rows that are not multiples of four, one to five copies, more
 # columns than the core has and fewer
 @pytest.mark.parametrize("m,n,G,k_cap,k_fixed", [(33, 32, 1, 32, 0), (64, 65, 2, 32, 0), (1024, 1025, 3, 20, 0), (1088, 2047, 5, 40, 7), (3072, 130, 4, 32, 32)])
