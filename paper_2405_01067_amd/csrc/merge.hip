@@ -810,12 +810,16 @@ Plan make_plan(const abt_merge_desc* layers, int L) {
         pairs += q.K / 32;
         even = even && q.K % 64 == 0;
     }
-    // Four blocks a work-group halve the traffic and the launches, two blocks have the shorter chain: with few work-groups that chain is
-    // what counts, with many the traffic.  Merge, ms, two blocks / four: 384 columns, 1 layer 3.14 / 3.81, 12 (144 pairs) 4.68 / 4.74, 16
-    // (192) 4.90 / 4.84, 48 6.82 / 6.39; 512 columns, 12 (192) 9.33 / 9.50, 16 9.82 / 9.80, 48 16.1 / 14.7; 256 columns, 8 2.36 / 2.43, 48 3.84 / 3.41;
-    // 128 columns, 1 0.84 / 0.89, 4 1.19 / 1.06, 48 1.80 / 1.67.  An odd double block costs a round with half of the pairs (160 columns, 48 layers 2.30 /
-    // 2.41).  Cores of 64 make all their sweeps in one launch with four blocks: 1 layer 0.52 / 0.49, 4 0.81 / 0.54.
-    p.quad = even && p.K_max <= 512 && (pairs >= 192 || (p.K_max <= 128 && L >= 4) || (p.K_max == 64 && p.one_size));
+    // Four blocks a work-group halve the traffic and the launches, two blocks have the shorter chain: with few pairs of blocks that chain is
+    // what counts, with many the traffic, the later the wider the cores.  The iteration, ms, two blocks / four, at pairs below and above each limit:
+    //   128 columns  12 1.05 / 1.10    16 1.19 / 1.12    192 1.37 / 1.20         320 columns  160 4.88 / 4.94    200 5.05 / 4.97    480 5.66 / 5.06
+    //   192 columns 120 2.16 / 2.20   144 2.23 / 2.22    288 2.47 / 2.33         384 columns  120 5.96 / 6.08    192 6.38 / 6.21    576 7.68 / 6.94
+    //   256 columns  64 2.89 / 3.02    96 3.12 / 3.07    384 3.83 / 3.28         448 columns  336 8.40 / 8.51    448 8.89 / 8.71
+    //                                                                            512 columns  288 9.96 / 10.07   384 10.6 / 10.3    512 12.0 / 10.6
+    // An odd double block costs a round with half of the pairs (160 columns, 48 layers 2.30 / 2.41).  Cores of
+    // 64 make all their sweeps in one launch with four blocks: 1 layer 0.38 / 0.34, 48 0.62 / 0.38.
+    const int quad_from = p.K_max <= 64 ? 0 : p.K_max <= 128 ? 16 : p.K_max <= 192 ? 144 : p.K_max <= 256 ? 96 : p.K_max <= 384 ? 192 : 384;
+    p.quad = even && p.K_max <= 512 && pairs >= quad_from;
     for (Plan::PerLayer& q : p.pl) p.n_wg_cross += q.slots = p.K_max <= 768 ? jacobi_slots(q.K, p.quad) : q.nb / 2;
     p.off_ptrs = take(sizeof(void*) * p.n_ptrs);
     p.off_gram_tiles = take(sizeof(GramJob) * p.n_gram_tiles);
@@ -1213,7 +1217,7 @@ hipError_t merge_run(const abt_merge_desc* layers, const MergeSide* identity, in
     };
     if (p.K_max == 32) {
         ABT_TRY(launch_jacobi_single_pair((double*)(ws + p.pl[0].Ct), (int*)(ws + p.off_rotated), L, max_sweeps, s));
-    } else if (p.K_max == 64 && p.one_size && p.quad) {
+    } else if (p.K_max == 64 && p.quad) {                  // (all of one size, then)
         ABT_TRY(launch_jacobi_block_round(dl, cross, p.n_wg_cross, 64, p.quad, 0, 0, max_sweeps, (double*)(ws + p.pl[0].Ct), (int*)(ws + p.off_rotated), s));
     } else if (p.K_max <= 768) {
         // block form on the matrix cores, layers in groups (contiguous layer ranges with about the

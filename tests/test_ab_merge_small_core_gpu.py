@@ -86,7 +86,8 @@ def test_block_iteration_at_the_edges_of_its_forms(K, zero_tail):
 # batches that take four blocks of columns a work-group: one pair of double blocks (all sweeps in one launch), two, sizes up to the limit, and
 # sizes mixed, where the work-groups look their layer up in the tables
 @pytest.mark.parametrize("zero_tail", [0, 20])
-@pytest.mark.parametrize("sizes", [(64,), (64, 64, 64), (128,) * 4, (192,) * 32, (320,) * 20, (384,) * 16, (512,) * 12, (512, 64, 128, 448) * 6])
+@pytest.mark.parametrize("sizes", [(64,), (64, 64, 64), (128,) * 4, (192,) * 32, (320,) * 20, (384,) * 16, (512,) * 24, (512, 64, 128, 448) * 11,
+                                   (512,) * 12, (512, 64, 128, 448) * 6])    # (the last two: two blocks)
 def test_four_blocks_a_work_group(sizes, zero_tail):
     made = {}
     for i, K in enumerate(sizes):                        # two different layers of every size
@@ -129,7 +130,7 @@ def planted(m, n, values, seed):
 # Two clusters of values three orders apart.  With the Gram matrix of a block pair in fp64 the iteration takes 14 or 15 sweeps of 768 columns (two
 # blocks a work-group) and of 512 (four) at any of six seeds; in fp32, where the difference of nearly equal squared norms and what is left of a
 # small column's beside a large one's are rounding, 18 to 20 and 16 or 17.
-@pytest.mark.parametrize("K,count,sweeps", [(768, 1, 16), (512, 12, 15)])
+@pytest.mark.parametrize("K,count,sweeps", [(768, 1, 16), (512, 24, 15)])
 def test_clusters_far_apart_take_the_sweeps_of_fp64(K, count, sweeps):
     g = torch.Generator().manual_seed(K)
     s = torch.where(torch.arange(K) < K // 2, 1.0, 1e-3).double() * (1 + 1e-5 * torch.rand(K, generator=g, dtype=torch.float64))
