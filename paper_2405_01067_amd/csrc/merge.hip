@@ -816,7 +816,7 @@ Plan make_plan(const abt_merge_desc* layers, int L) {
     //   192 columns 120 2.16 / 2.20   144 2.23 / 2.22    288 2.47 / 2.33         384 columns  120 5.96 / 6.08    192 6.38 / 6.21    576 7.68 / 6.94
     //   256 columns  64 2.89 / 3.02    96 3.12 / 3.07    384 3.83 / 3.28         448 columns  336 8.40 / 8.51    448 8.89 / 8.71
     //                                                                            512 columns  288 9.96 / 10.07   384 10.6 / 10.3    512 12.0 / 10.6
-    // An odd double block costs a round with half of the pairs (160 columns, 48 layers 2.30 / 2.41).  Cores of
+    // (An odd double block, idle in a round of its own, made 48 layers of 160 columns 2.30 / 2.41: two blocks there.)  Cores of
     // 64 make all their sweeps in one launch with four blocks: 1 layer 0.38 / 0.34, 48 0.62 / 0.38.
     const int quad_from = p.K_max <= 64 ? 0 : p.K_max <= 128 ? 16 : p.K_max <= 192 ? 144 : p.K_max <= 256 ? 96 : p.K_max <= 384 ? 192 : 384;
     p.quad = even && p.K_max <= 512 && pairs >= quad_from;

@@ -138,10 +138,10 @@ hipError_t launch_mean_gram(const LayerDev* layers, const GramJob* jobs, int njo
 
 // One round of the block Jacobi iteration for cores with K <= 768 (every layer of the batch): `n_wg` work-groups,
 // wg_map[i] = (layer, slot), jacobi_slots() slots a layer, jacobi_rounds() rounds a sweep: `quad` pairs double blocks of 32 columns
-// (K_max up to 512), otherwise blocks of 16.  Round 0 of a sweep also orthogonalises the columns inside every (double) block.  `cores`: the first core's record where the launch has whole layers one behind the other, all of size K_max, whose
+// (K_max up to 512, every K a multiple of 64), otherwise blocks of 16.  Round 0 of a sweep also orthogonalises the columns inside every (double) block.  `cores`: the first core's record where the launch has whole layers one behind the other, all of size K_max, whose
 // convergence flags begin at `rotated` (otherwise null, and the work-groups look everything up in the tables).  max_sweeps: 0, or, with `quad` where all
 // cores are 64 wide (and `cores` is given), the number of sweeps that the launch may make.
-inline int jacobi_slots(int K, bool quad) { return quad ? (K / 32 + 1) / 2 : K / 32; }
+inline int jacobi_slots(int K, bool quad) { return quad ? K / 64 : K / 32; }
 inline int jacobi_rounds(int K, bool quad) { return 2 * jacobi_slots(K, quad) - 1; }
 hipError_t launch_jacobi_block_round(const LayerDev* layers, const int2* wg_map, int n_wg, int K_max, bool quad,
                                      int sweep, int round, int max_sweeps, double* cores, int* rotated, hipStream_t s);

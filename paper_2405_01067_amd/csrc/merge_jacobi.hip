@@ -395,15 +395,13 @@ void jacobi_quad_kernel(double* cores, int* rotated, int K, int sweep, int round
     rotated = c.rotated;
     const int slot = c.slot;
     if (sweep > 0 && rotated[sweep - 1] == 0) return;     // the previous sweep found no significant pair: the iteration has converged
-    const int nd = K >> 5, np = nd + (nd & 1);            // double blocks; with an empty one where their number is odd
+    const int nd = K >> 5;                                // double blocks, an even number
     const bool whole = max_sweeps > 0;
-    if (round >= np - 1 || K > 128 * NT) return;
-    // circle method: slot 0 pairs double block np - 1 with `round`; slot j pairs (round + j) with (round - j)
+    if (round >= nd - 1 || K > 128 * NT) return;
+    // circle method: slot 0 pairs double block nd - 1 with `round`; slot j pairs (round + j) with (round - j)
     int dI = round + slot, dJ = round - slot;
-    if (slot == 0) dI = np - 1;
-    else { if (dI >= np - 1) dI -= np - 1; if (dJ < 0) dJ += np - 1; }
-    if (dI >= nd) { dI = dJ; dJ = -1; }                   // no partner: round 0 has the pair inside the double block
-    if (dJ < 0 && round != 0) return;
+    if (slot == 0) dI = nd - 1;
+    else { if (dI >= nd - 1) dI -= nd - 1; if (dJ < 0) dJ += nd - 1; }
     const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, n = lane & 15, kq = lane >> 4;
     const int half = wave >> 2, t8 = tid & 255;            // block pair of this wave, thread within it
     const int gi = (t8 >> 6) + 4 * (t8 & 3), gj = (t8 >> 2) & 15;         // this thread's element of a 16 x 16 tile
@@ -413,7 +411,7 @@ void jacobi_quad_kernel(double* cores, int* rotated, int K, int sweep, int round
     // with positions 1 and 2 exchanged, so that its first pairs are (a, b) and (c, d).
     int blk[4], id[4] = {0, 1, 2, 3};
     {
-        const int b0 = 2 * dI, b1 = 2 * dI + 1, b2 = dJ < 0 ? -1 : 2 * dJ, b3 = dJ < 0 ? -1 : 2 * dJ + 1;
+        const int b0 = 2 * dI, b1 = 2 * dI + 1, b2 = 2 * dJ, b3 = 2 * dJ + 1;
         blk[0] = b0; blk[1] = round == 0 ? b2 : b1; blk[2] = round == 0 ? b1 : b2; blk[3] = b3;
         if (round == 0) { id[1] = 2; id[2] = 1; }
     }
@@ -424,7 +422,7 @@ void jacobi_quad_kernel(double* cores, int* rotated, int K, int sweep, int round
         kept[1] = gload(diag + (half ? blk[3] : blk[2]) * 256 + 16 * gi + gj);
     }
     const double frob = frob2(c.trace);
-    // ---- load the columns: D[t][4 i + s] = C[row(t, n)][16 blk[i] + kq + 4 s].  Chunks past K and blocks that are not there are zero, both
+    // ---- load the columns: D[t][4 i + s] = C[row(t, n)][16 blk[i] + kq + 4 s].  Chunks past K are zero,
     // the same for the whole wave, so nothing is done to a value that has just been asked for and the Gram matrix begins with the first chunk.
     double D[NT][16];
 #pragma unroll
@@ -432,7 +430,7 @@ void jacobi_quad_kernel(double* cores, int* rotated, int K, int sweep, int round
         const int row0 = 32 * (wave + 8 * tt) + 2 * n;
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-            if (32 * (wave + 8 * tt) < K && blk[i] >= 0) {
+            if (32 * (wave + 8 * tt) < K) {
 #pragma unroll
                 for (int s = 0; s < 4; ++s) {
                     const f64x2 v = gload(reinterpret_cast<const f64x2*>(Ct + (int64_t)(16 * blk[i] + kq + 4 * s) * K + row0));
@@ -469,7 +467,6 @@ void jacobi_quad_kernel(double* cores, int* rotated, int K, int sweep, int round
         const int row0 = 32 * (wave + 8 * tt) + 2 * n;
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-            if (blk[i] < 0) continue;
 #pragma unroll
             for (int s = 0; s < 4; ++s)
                 gstore(reinterpret_cast<f64x2*>(Ct + (int64_t)(16 * blk[i] + kq + 4 * s) * K + row0), f64x2{D[2 * tt][4 * i + s], D[2 * tt + 1][4 * i + s]});
@@ -549,7 +546,7 @@ void jacobi_quad_kernel(double* cores, int* rotated, int K, int sweep, int round
         // ---- the rotations of the two pairs; the waves that work them out sit on two SIMDs
         rotate_pair(mine, inside, ((wave & 3) - 2 * half - 1) & 3, reinterpret_cast<f64x2*>(sh.stage[wave][0]), floor2,
                     [&](int block, int i, int j, double v) { sh.diag[block ? (half ? id[3] : id[2]) : (half ? id[1] : id[0])][17 * i + j] = v; }, [] {});
-        // (Compared as numbers: with one bit of a scalar tested for several branches the compiler inverted some of them.)
+        // (the larger is what was done to the two together, see PairShared::did)
         const int did[2] = {__builtin_amdgcn_readfirstlane(sh.pair[0].did), __builtin_amdgcn_readfirstlane(sh.pair[1].did)};
         const int more = did[0] > did[1] ? did[0] : did[1];
         if (more > touched) touched = more;
@@ -595,7 +592,7 @@ void jacobi_quad_kernel(double* cores, int* rotated, int K, int sweep, int round
     if (!whole) {                                        // (a, b, c, d again; scaled by a power of two)
         const double unscale = 1.0 / scale;
         gstore(diag + (half ? blk[1] : blk[0]) * 256 + 16 * gi + gj, sh.diag[half][17 * gi + gj] * unscale);
-        if (dJ >= 0) gstore(diag + (half ? blk[3] : blk[2]) * 256 + 16 * gi + gj, sh.diag[2 + half][17 * gi + gj] * unscale);
+        gstore(diag + (half ? blk[3] : blk[2]) * 256 + 16 * gi + gj, sh.diag[2 + half][17 * gi + gj] * unscale);
     }
     if (whole && touched > 0) {
 #pragma unroll
@@ -833,7 +830,7 @@ void jacobi_single_pair_kernel(double* cores, int* rotated, int max_sweeps) {
 hipError_t launch_jacobi_block_round(const LayerDev* layers, const int2* wg_map, int n_wg, int K_max, bool quad,
                                      int sweep, int round, int max_sweeps, double* cores, int* rotated, hipStream_t s) {
     if (n_wg <= 0) return hipSuccess;
-    if (K_max > (quad ? 512 : 768)) return hipErrorInvalidValue;
+    if (K_max > (quad ? 512 : 768) || (quad && K_max % 64)) return hipErrorInvalidValue;
     const int slots = jacobi_slots(K_max, quad);
     const dim3 grid(cores ? slots : n_wg, cores ? n_wg / slots : 1), block(quad ? 512 : 256);
     if (quad) {
