@@ -50,20 +50,30 @@ bool current_stream(void** s) {
     Py_DECREF(raw);
     return !PyErr_Occurred();
 }
-bool passed(int code, const char* what) {
-    if (code == 0) return true;
-    PyObject* r = PyObject_CallFunction(check, "is", code, what);     // raises
+// The results, or for an error of the library what binding._check raises
+PyObject* finished(PyObject* results, int code, const char* what) {
+    if (code == 0) return results;
+    Py_DECREF(results);
+    PyObject* r = PyObject_CallFunction(check, "is", code, what);
     Py_XDECREF(r);
-    return false;
+    return nullptr;
 }
 PyObject* wrap_or_none(const at::Tensor& t) {
     if (t.defined()) return THPVariable_Wrap(t);
     Py_RETURN_NONE;
 }
 
+// Everything that can fail comes before the launch: a call that is answered with None has done nothing.  Addresses are asked for with
+// data_ptr(), as from Python: what materialises or refuses there does here.
+
 // (X, A, B, save_T) -> (Y, T or None), or None
 PyObject* fwd(PyObject*, PyObject* const* args, Py_ssize_t n) {
     if (n != 4) { PyErr_SetString(PyExc_TypeError, "fwd(X, A, B, save_T)"); return nullptr; }
+    void *stream, *x, *a, *b, *y, *t = nullptr;
+    int64_t M, m, cols, r;
+    int dt;
+    PyObject* results;
+    at::Tensor Y, T;
     try {
         const at::Tensor *X = plain(args[0]), *A = plain(args[1]), *B = plain(args[2]);
         const int save = PyObject_IsTrue(args[3]);
@@ -71,46 +81,51 @@ PyObject* fwd(PyObject*, PyObject* const* args, Py_ssize_t n) {
         if (!X || !A || !B || watched()) Py_RETURN_NONE;
         const auto dtype = X->scalar_type();
         const bool f32 = dtype == at::kFloat;
-        const int64_t M = X->size(0), cols = X->size(1), m = A->size(0), r = A->size(1);
+        M = X->size(0); cols = X->size(1); m = A->size(0); r = A->size(1);
         if ((!f32 && dtype != at::kBFloat16) || A->scalar_type() != dtype || B->scalar_type() != dtype || B->size(0) != r || B->size(1) != cols || (f32 && !save))
             Py_RETURN_NONE;
-        void* stream;
         if (!current_stream(&stream)) return nullptr;
         const auto opt = X->options().requires_grad(false);
-        at::Tensor Y = at::empty({M, m}, opt), T;
-        const int dt = f32 ? 0 : 1;
+        dt = f32 ? 0 : 1;
+        Y = at::empty({M, m}, opt);
         if (save || wants_fn(1, M, m, cols, r, dt)) T = at::empty({M, r}, opt);
-        int code;
-        Py_BEGIN_ALLOW_THREADS
-        code = fwd_fn(X->const_data_ptr(), A->const_data_ptr(), B->const_data_ptr(), Y.data_ptr(), T.defined() ? T.data_ptr() : nullptr, M, m, cols, r, dt, nullptr, 0, stream);
-        Py_END_ALLOW_THREADS
-        if (!passed(code, "lr_linear_fwd")) return nullptr;
-        PyObject *y = THPVariable_Wrap(Y), *t = wrap_or_none(save ? T : at::Tensor());
-        return Py_BuildValue("(NN)", y, t);
+        x = X->data_ptr(); a = A->data_ptr(); b = B->data_ptr(); y = Y.data_ptr();
+        if (T.defined()) t = T.data_ptr();
+        results = Py_BuildValue("(NN)", THPVariable_Wrap(Y), wrap_or_none(save ? T : at::Tensor()));
     } catch (...) {
         PyErr_Clear();
         Py_RETURN_NONE;                                  // out of memory and the like: the Python code meets it again and says so
     }
+    if (!results) return nullptr;
+    int code;
+    Py_BEGIN_ALLOW_THREADS
+    code = fwd_fn(x, a, b, y, t, M, m, cols, r, dt, nullptr, 0, stream);
+    Py_END_ALLOW_THREADS
+    return finished(results, code, "lr_linear_fwd");
 }
 
 // (dY, X, T, A, B, need_dX, need_dA, need_dB, dX, dA, dB, accumulate) -> (dX, dA, dB), or None
 PyObject* bwd(PyObject*, PyObject* const* args, Py_ssize_t n) {
     if (n != 12) { PyErr_SetString(PyExc_TypeError, "bwd takes 12 arguments"); return nullptr; }
+    void *stream, *space, *in[5], *to[3];
+    int64_t M, m, cols, r;
+    int dt, flag[4];
+    size_t size;
+    PyObject* results;
+    at::Tensor ws, out[3];                               // dX, dA, dB
     try {
         const at::Tensor *dY = plain(args[0]), *X = plain(args[1]), *A = plain(args[3]), *B = plain(args[4]);
         const at::Tensor* T = args[2] == Py_None ? nullptr : plain(args[2]);
         if (!dY || !X || !A || !B || (!T && args[2] != Py_None) || watched()) Py_RETURN_NONE;
-        int flag[4];
         const int at_arg[4] = {5, 6, 7, 11};
         for (int i = 0; i < 4; ++i)
             if ((flag[i] = PyObject_IsTrue(args[at_arg[i]])) < 0) return nullptr;
         const auto dtype = X->scalar_type();
         const bool f32 = dtype == at::kFloat;
-        const int64_t M = X->size(0), cols = X->size(1), m = A->size(0), r = A->size(1);
+        M = X->size(0); cols = X->size(1); m = A->size(0); r = A->size(1);
         if ((!f32 && dtype != at::kBFloat16) || A->scalar_type() != dtype || B->scalar_type() != dtype || dY->scalar_type() != dtype || (T && T->scalar_type() != dtype) ||
             dY->size(0) != M || dY->size(1) != m || B->size(0) != r || B->size(1) != cols || (T && (T->size(0) != M || T->size(1) != r)))
             Py_RETURN_NONE;
-        at::Tensor out[3];                               // dX, dA, dB
         const int64_t shape[3][2] = {{M, cols}, {m, r}, {r, cols}};
         const auto opt = X->options().requires_grad(false);
         for (int i = 0; i < 3; ++i) {
@@ -123,30 +138,33 @@ PyObject* bwd(PyObject*, PyObject* const* args, Py_ssize_t n) {
                 Py_RETURN_NONE;                          // accumulate needs them
             }
         }
-        void* stream;
         if (!current_stream(&stream)) return nullptr;
         for (int i = 0; i < 3; ++i)
             if (flag[i] && !out[i].defined()) out[i] = at::empty({shape[i][0], shape[i][1]}, i == 0 ? opt : opt.dtype(at::kFloat));
-        const int dt = f32 ? 0 : 1;
-        const size_t bytes = bytes_fn(M, m, cols, r, dt), size = bytes < 256 ? 256 : bytes;
-        at::Tensor ws = at::empty({(int64_t)size}, opt.dtype(at::kByte));
-        auto ptr = [](const at::Tensor& t) { return t.defined() ? t.data_ptr() : nullptr; };
-        int code;
-        Py_BEGIN_ALLOW_THREADS
-        code = bwd_fn(dY->const_data_ptr(), X->const_data_ptr(), T ? T->const_data_ptr() : nullptr, A->const_data_ptr(), B->const_data_ptr(), ptr(out[0]), ptr(out[1]),
-                      ptr(out[2]), M, m, cols, r, dt, flag[3], ws.data_ptr(), size, stream);
-        Py_END_ALLOW_THREADS
-        if (!passed(code, "lr_linear_bwd")) return nullptr;
+        dt = f32 ? 0 : 1;
+        const size_t bytes = bytes_fn(M, m, cols, r, dt);
+        size = bytes < 256 ? 256 : bytes;
+        ws = at::empty({(int64_t)size}, opt.dtype(at::kByte));
+        space = ws.data_ptr();
+        const at::Tensor* operands[5] = {dY, X, T, A, B};
+        for (int i = 0; i < 5; ++i) in[i] = operands[i] ? operands[i]->data_ptr() : nullptr;
+        for (int i = 0; i < 3; ++i) to[i] = out[i].defined() ? out[i].data_ptr() : nullptr;
         PyObject* res[3];
         for (int i = 0; i < 3; ++i) {
             if (flag[i] && args[8 + i] != Py_None) { Py_INCREF(args[8 + i]); res[i] = args[8 + i]; }
             else res[i] = wrap_or_none(out[i]);
         }
-        return Py_BuildValue("(NNN)", res[0], res[1], res[2]);
+        results = Py_BuildValue("(NNN)", res[0], res[1], res[2]);
     } catch (...) {
         PyErr_Clear();
         Py_RETURN_NONE;
     }
+    if (!results) return nullptr;
+    int code;
+    Py_BEGIN_ALLOW_THREADS
+    code = bwd_fn(in[0], in[1], in[2], in[3], in[4], to[0], to[1], to[2], M, m, cols, r, dt, flag[3], space, size, stream);
+    Py_END_ALLOW_THREADS
+    return finished(results, code, "lr_linear_bwd");
 }
 
 // (addresses of lr_linear_fwd, lr_linear_fwd_wants_T, lr_linear_bwd, lr_linear_bwd_workspace_bytes, the three callables)

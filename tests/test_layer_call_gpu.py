@@ -72,6 +72,21 @@ def test_refused_as_before():
         torch.func.vmap(lambda x: abt.lr_linear_fwd(x, A, B)[0])(X.view(2, 35, 64))
 
 
+def test_what_torch_refuses_is_refused_before_the_launch():
+    dY, X, A, B = layer(torch.float32)
+    T = abt.lr_linear_fwd(X, A, B)[1]
+    dA, dB = torch.ones_like(A), torch.ones_like(B)
+    torch._C._set_throw_on_mutable_data_ptr(dB)          # an address that may not be asked for
+    with pytest.raises(RuntimeError):
+        abt.lr_linear_bwd(dY, X, T, A, B, dA=dA, dB=dB, accumulate=True)
+    torch.cuda.synchronize()
+    assert bool((dA == 1).all())                         # nothing was added, once or twice
+    Z = X.clone()
+    torch._C._set_throw_on_mutable_data_ptr(Z)
+    with pytest.raises(RuntimeError):
+        abt.lr_linear_fwd(Z, A, B)
+
+
 def test_allocations_of_a_mode_are_seen_by_it():
     from torch.utils._python_dispatch import TorchDispatchMode
     _, X, A, B = layer(torch.float32)
