@@ -226,17 +226,21 @@ def _torch():
 
 @functools.lru_cache(maxsize=None)
 def layer_call():
-    """The native code of lr_linear_fwd and lr_linear_bwd.  Needs no GPU."""
+    """The native code of lr_linear_fwd and lr_linear_bwd, or None (and a warning) where it is not there or was built for another
+    Python or torch: the Python code makes the same calls of the library, some 5 us later.  Needs no GPU."""
     import importlib.machinery
     import importlib.util
     torch = _torch()
-    path = os.path.join(os.path.dirname(_LIB_PATH), "layer_call.so")
-    if not os.path.exists(path):
-        raise AbtError(f"{path} is missing: run `python __graft_entry__.py` (build) first")
-    loader = importlib.machinery.ExtensionFileLoader("layer_call", path)
-    module = importlib.util.module_from_spec(importlib.util.spec_from_loader("layer_call", loader))
-    loader.exec_module(module)
     lib = load()
+    path = os.path.join(os.path.dirname(_LIB_PATH), "layer_call.so")
+    try:
+        loader = importlib.machinery.ExtensionFileLoader("layer_call", path)
+        module = importlib.util.module_from_spec(importlib.util.spec_from_loader("layer_call", loader))
+        loader.exec_module(module)
+    except ImportError as e:
+        import warnings
+        warnings.warn(f"{path} does not load ({e}): calls of a single layer go through Python; `python __graft_entry__.py` builds it", RuntimeWarning)
+        return None
     addr = (ctypes.cast(f, ctypes.c_void_p).value for f in (lib.lr_linear_fwd, lib.lr_linear_fwd_wants_T, lib.lr_linear_bwd, lib.lr_linear_bwd_workspace_bytes))
     module.setup(*addr, torch._C._cuda_getDevice, torch._C._cuda_getCurrentRawStream, _check)
     return module
@@ -286,7 +290,8 @@ def _workspace(nbytes: int, device, workspace=None):
 def lr_linear_fwd(X, A, B, save_T: bool = True, Y=None, T=None, workspace=None):
     """Y = (X B^T) A^T.  Returns (Y, T) (T is None when save_T is False)."""
     if Y is None and T is None and workspace is None:
-        done = layer_call().fwd(X, A, B, save_T)
+        native = layer_call()
+        done = native.fwd(X, A, B, save_T) if native is not None else None
         if done is not None:
             return done
     torch = _torch()
@@ -316,7 +321,8 @@ def lr_linear_bwd(dY, X, T, A, B, need_dX: bool = True, need_dA: bool = True, ne
     """dX = (dY A) B, dA = dY^T T, dB = (dY A)^T X.  T may be None (recomputed).
     Returns (dX, dA, dB); skipped gradients are None."""
     if workspace is None:
-        done = layer_call().bwd(dY, X, T, A, B, need_dX, need_dA, need_dB, dX, dA, dB, accumulate)
+        native = layer_call()
+        done = native.bwd(dY, X, T, A, B, need_dX, need_dA, need_dB, dX, dA, dB, accumulate) if native is not None else None
         if done is not None:
             return done
     torch = _torch()

@@ -273,6 +273,23 @@ def test_binding_refuses_cpu_tensors(lib):
         abt.ab_merge([a.float()], [b.float()], tau=0.1)
 
 
+@pytest.mark.parametrize("content", [None, b"not a library"])
+def test_binding_without_its_native_calls(lib, monkeypatch, tmp_path, content):
+    import torch
+    if content is not None:
+        (tmp_path / "layer_call.so").write_bytes(content)
+    monkeypatch.setattr(abt, "_LIB_PATH", str(tmp_path / "libabtrain.so"))       # (the library itself is loaded)
+    abt.layer_call.cache_clear()
+    try:
+        X, A, B = torch.zeros(64, 128), torch.zeros(64, 32), torch.zeros(32, 128)
+        with pytest.warns(RuntimeWarning, match="layer_call.so"), pytest.raises(abt.AbtError, match="on the GPU"):
+            abt.lr_linear_fwd(X, A, B)                     # the Python code is reached
+        with pytest.raises(abt.AbtError, match="on the GPU"):
+            abt.lr_linear_bwd(torch.zeros(64, 64), X, None, A, B)
+    finally:
+        abt.layer_call.cache_clear()
+
+
 def test_chain_shape_setters(lib):
     assert abt.set_chain_rows(128) == 0
     assert abt.set_chain_rows(77) == 128          # ignored value, setting kept
