@@ -179,7 +179,8 @@ def test_static_scratch_gives_the_same_dX():
 
 
 # one tile per work-group and several: tiles on both sides of three and of four work-groups per compute unit, one slab to many, ragged edges
-@pytest.mark.parametrize("m,n,k", [(1664, 1664, 32), (1700, 1820, 64), (2048, 2048, 96), (2049, 2052, 32), (3150, 3068, 192), (64 * 257, 64, 160), (4100, 4, 320)])
+@pytest.mark.parametrize("m,n,k", [(1664, 1664, 32), (1700, 1820, 64), (2048, 2048, 96), (2049, 2052, 32), (3150, 3068, 192), (64 * 257, 64, 160), (64 * 300 + 4, 4, 320),
+                                   (4100, 4, 320)])       # (the last one has too few tiles: 32 x 32)
 def test_work_groups_that_stay(m, n, k):
     g = torch.Generator().manual_seed(m + k)
     A, B = torch.randn((m, k), generator=g).to("cuda:0"), torch.randn((k, n), generator=g).to("cuda:0")
@@ -190,8 +191,9 @@ def test_work_groups_that_stay(m, n, k):
     assert bool(((W.double() - want).abs() <= bound).all())
 
 
-# three unlike problems in a launch, two of them split, added to what is there
-@pytest.mark.parametrize("M,m,n,r", [(3136, 1024, 512, 192), (2000, 1472, 1984, 64)])
+# three unlike problems in a launch, two of them split, added to what is there; an odd number of slabs, ragged edges of the outputs
+@pytest.mark.parametrize("M,m,n,r", [(3136, 1024, 512, 192), (2016, 1472, 1984, 64), (3168, 1028, 516, 96),
+                                       (2000, 1472, 1984, 64)])       # (the last one's rows are no whole slabs: one tile after the other)
 def test_gradients_by_work_groups_that_stay(M, m, n, r):
     g = torch.Generator().manual_seed(M + r)
     make = lambda *s: torch.randn(s, generator=g).to("cuda:0")
