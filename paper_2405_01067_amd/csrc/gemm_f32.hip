@@ -12,10 +12,10 @@
 //     would not give every compute unit a tile), four work-groups per compute unit,
 //   * a contraction over the batch (factor gradients) or, in a backward pass, over a long width (dT) is split over work-groups; the partial sums are
 //     added in a fixed order by a second launch.
-// Measured: 4096 x 4096 x 1024 279 us = 123 TFLOP/s of the 133 that a large library product reaches;
+// Measured: 4096 x 4096 x 1024 279 to 302 us = 114 to 123 TFLOP/s by the card, a large library product of this size 139;
 // 768 x 3072 x 384 (W = A B of a ViT-B/16 MLP layer) 26 us, 79 us in an earlier form with 128 x 128 tiles
 // and 4-byte loads one slab ahead; the products of a factored layer at M = 3152, m = 3072, n = 768,
-// r = 192: T 15 us, Y 52, dT 47 and 4, and dX, dA and dB in one launch 64 and 7; forward and backward together 171 us, 164 with work-groups
+// r = 192: T 18 us, Y 46, dT 44 and 6, and dX, dA and dB in one launch 63 and 7; forward and backward together 161 us, 171 without work-groups
 // that stay (gemm_stream).
 //
 // LDS: both operands lie [row][k], 16-byte chunks of four k XOR-swizzled by the row; an operand read is
