@@ -291,7 +291,7 @@ def main():
             "n_gpus": 1, "steps": args.steps, "warmup": args.warmup,
             "ms_per_step": round(sec * 1e3, 5), "higher_is_better": True, "scaling": "weak",
             "vs_baseline": None, "dtype": "bf16", "data": "synthetic",
-            "config": {"workload": "configs[2]: all four ViT-B/16 linear shapes (qkv 2304x768, proj 768x768, "
+            "config": {"workload": "all four ViT-B/16 linear shapes (qkv 2304x768, proj 768x768, "
                                    "fc1 3072x768, fc2 768x3072) factored at r in {96, 192, 384}, X 50432 rows "
                                    "(batch 256 x 197 tokens), bf16 in / fp32 accumulate, fwd+bwd of all twelve "
                                    "cases = one step",
@@ -470,7 +470,7 @@ def main():
         streaming_ms = stages["mean_gram"] + stages["back_projection"]
         out["ab_merge_ms_per_layer_set"] = round(med, 3)
         out["ab_merge"] = {
-            "workload": "configs[4]: 48 ViT-B/16 layers x G = 4 copies, k_in = 384, gap-centred threshold (k' = 192)",
+            "workload": "48 ViT-B/16 layers x G = 4 copies, k_in = 384, gap-centred threshold (k' = 192)",
             "layers": len(gap), "G": gen.CFG5_G, "k_in": gen.CFG5_K_IN, "tau": gen.CFG5_TAU_GAP,
             "ms_median": round(med, 3), "ms_min": round(mn, 3), "timed_merges": args.merge_iters, "warmup_merges": 4,
             "ranks_min_max": [min(ranks), max(ranks)], "jacobi_sweeps_min_max": [min(sweeps), max(sweeps)],
